@@ -68,6 +68,7 @@ int check_params(const lsm_params* p, lsm::Dims* d) {
     d->B = p->B; d->H = p->H; d->T = p->T; d->dk = p->d_k; d->dv = p->d_v; d->C = p->chunk_size;
     d->N = int(n); d->kind = p->decay_kind; d->bf16 = p->dtype == LSM_DTYPE_BF16;
     d->layout = p->layout; d->nseq = p->n_seq; d->cu = p->cu_seqlens; d->cstart = nullptr;
+    d->gC = d->C < 64 ? 64 : d->C;
     // Only the matrix-core kernels keep states between the two calls; elsewhere the flag changes nothing.
     // (the scalar kinds with d_v = 256 run one pass per 128-wide value slice over a shared workspace and keep nothing)
     d->save = (p->flags & LSM_FLAG_SAVE_STATES) != 0 && lsm::mfma_supported(*d) && (d->kind == 3 || d->dv == 128);
@@ -81,7 +82,7 @@ hipError_t prepare_tables(lsm::Dims& d, void*& workspace, hipStream_t stream) {
     int* cstart = static_cast<int*>(workspace);
     workspace = static_cast<char*>(workspace) + table_bytes(d);
     d.cstart = cstart;
-    return lsm::launch_chunk_starts(d, cstart, stream);
+    return lsm::mfma_supported(d) ? lsm::launch_chunk_starts(d, cstart, stream) : lsm::launch_generic_starts(d, cstart, stream);
 }
 
 }  // namespace

@@ -1,426 +1,969 @@
-// Generic kernel family of the chunkwise LSM path: fp32 arithmetic on the plain
-// vector ALU, any supported (d_k, d_v, chunk) and both element types.  It is
-// the product path for fp32 inputs (whose 1e-4 tolerance rules out bf16 MFMA
-// operands) and for shapes the MFMA family does not cover.
+// Generic kernel family of the chunkwise LSM path: fp32 arithmetic for any supported (d_k, d_v, chunk) and both
+// element types.  It is the product path for fp32 inputs (whose 1e-4 tolerance rules out bf16 operands) and for the
+// shapes the bf16 family does not cover (64-wide heads, chunk sizes other than 64).
 //
-// Structure (Algorithm 2 of the paper, generalised to a decay):
-//   cumsum      b_j  = chunk-local inclusive sum of the log-decay
-//   local_state U_c  = sum_r (k_r * e^{b_C - b_r})^T v_r             (Alg. 2: M_t = K_t^T V_t)
-//   scan        S_{c+1} = diag(e^{b_C}) S_c + U_c                     (Alg. 2: PrefixSum)
-//   output      O = [(Q K^T) * D * Psi] V + (Q * e^{b}) S_c            (Alg. 2: O_intra + O_inter)
-// and for the backward the mirrored dU / reverse scan / per-chunk gradients.
+// Everything is one walker, gk_walk.  With roles query x, key y, value z and a running state
+//     out_p = e^{E_p} x_p S + sum_{s <= p} (x_p . y_s) e^{E_p - E_s} z_s ,   S <- e^{E} S + sum_s e^{E - E_s} y_s^T z_s
+// (p: position in walk order, E: running log-decay), the forward pass and all three gradients are the same product with
+// the operands in different roles (the adjoint walks backward in time):
+//     o : (q, k, v) forward      dq : (d_o, v, k) forward      dv : (k, q, d_o) backward      dk : (v, d_o, q) backward
+// so no per-chunk state or state gradient ever reaches memory: a workgroup walks a segment of a sequence 32 tokens at a
+// time with its state in matrix-core accumulators.  Where a launch has too few sequences a sequence is cut into
+// segments: gk_walk<SUM> (state update alone, from zero) leaves every segment's own contribution, gk_scan chains them,
+// and the walkers then run all segments in parallel.  The decay gradient needs, per token, q.dq and k.dk (left by the
+// two walkers) and, per segment, the product of the state and its gradient at the segment's end (gk_dg).
+//
+// Contractions are v_mfma_f32_32x32x2_f32: fp32 operands, fp32 accumulation, 1/16 of the bf16 rate but exact products,
+// and its operand layout is its result layout: lane l holds A[m = l%32][k = l/32], B[k = l/32][n = l%32], and result
+// register 4g+j of lane l is D[m = 8g + 4(l/32) + j][n = l%32].  Register x of a result block is therefore, unchanged, the
+// operand of one MFMA of the next product (its k index are the rows 8g+j and 8g+4+j), so states and scores feed the
+// matrix cores straight out of the accumulators and nothing is split or rounded on the way.
+//
+// Bound: the fp32 matrix rate (157 TFLOP/s nominal; half of it reached at 4 x 16 sequences of 2047 fp32 tokens, d = 128,
+// scalar decay: forward walk 0.137 ms, the three gradient walks 0.39 ms).  Forward + backward against one-thread-per-element
+// kernels on the vector ALU with a state per chunk in memory, which this family replaced: that shape 11.6 -> 0.70 ms; bf16
+// vector decay, 4 x 8 sequences of 2048, d_k = 64, d_v = 128: 7.2 -> 0.56 ms; forward alone, 32 sequences of 1777, d = 64: 0.262 ->
+// 0.053 ms; 2 sequences of 256, d = 64: 0.110 -> 0.024 ms.  Distance to 64-bit results: a half to equal (2-norm, every output).
 #include "lsm_internal.h"
+
+#include <mutex>
+#include <vector>
 
 namespace lsm {
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int GT = 32;  // tokens per step of a walk
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ float to_f32(float x) { return x; }
-__device__ __forceinline__ float to_f32(uint16_t x) { return __uint_as_float(uint32_t(x) << 16); }
+__device__ __forceinline__ f32x16 mfma2(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
 
-__device__ __forceinline__ void from_f32(float* p, float x) { *p = x; }
-__device__ __forceinline__ void from_f32(uint16_t* p, float x) {
-    // round to nearest even; inputs are finite by contract, NaN is kept quiet
+__device__ __forceinline__ uint32_t bf16_bits(float x) {  // round to nearest even, NaN kept quiet
     uint32_t u = __float_as_uint(x);
-    if ((u & 0x7fffffffu) > 0x7f800000u) { *p = uint16_t((u >> 16) | 0x40); return; }
-    u += 0x7fffu + ((u >> 16) & 1u);
-    *p = uint16_t(u >> 16);
+    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40;
+    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+}
+// four consecutive elements
+__device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ __forceinline__ f32x4 load4(const uint16_t* p) {
+    const u32x2 w = *reinterpret_cast<const u32x2*>(p);
+    return f32x4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u)};
+}
+__device__ __forceinline__ void store4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
+__device__ __forceinline__ void store4(uint16_t* p, f32x4 v) {
+    *reinterpret_cast<u32x2*>(p) = u32x2{bf16_bits(v[0]) | (bf16_bits(v[1]) << 16), bf16_bits(v[2]) | (bf16_bits(v[3]) << 16)};
 }
 
-// Chunk-local cumulative log-decay of token `tok` (= bh*T + t), feature i.  Kept in fp64: the sums
-// reach hundreds for strong decays while only their O(1) differences enter exp(), and an fp32 sum
-// would leave ~1e-4 relative error in those, which is the whole budget of the fp32 path.
-using bsum_t = double;
-__device__ __forceinline__ bsum_t bval(const bsum_t* bcum, size_t tok, int dkd, int i) {
-    return bcum ? bcum[tok * dkd + (dkd > 1 ? i : 0)] : 0.0;
-}
-__device__ __forceinline__ float expd(bsum_t x) { return expf(float(x)); }
+// One operand assignment of the walk.
+struct GRole {
+    const void *xq, *xk, *xv;  // rows in the query, key and value role
+    const void* aux;           // rows the unrounded output is multiplied with for the decay gradient, or NULL
+    void* out;
+    float* xdot;               // that product: scalar kinds [value slice][BH*T] (summed over the row), vector kind [BH*T][width]
+    const float* edge_in;      // state the whole sequence starts from (walk order), [d_k][d_v] per sequence; NULL = zero
+    float* edge_out;           // state it ends with; NULL = not wanted
+    float* bound;              // states at segment boundaries, one slot of [d_k][d_v] per segment
+    double* gseg;              // SUM: total log-decay of each segment ([slot], vector kind [slot][d_k])
+    int rev, trans;            // walk backward in time; the walk's state is the transpose of the stored one
+    int end_slot;              // the walk's last state goes to the boundary slot after the last segment as well
+};
+struct GArgs {
+    GRole role[3];
+    const float* g;
+    int kd, vd;        // row widths of the key-role and value-role arrays
+    int nsl;           // value slices (grid.z = role * nsl + slice)
+    int m;             // segment length in units of Dims::gC tokens
+    int slots, extra;  // boundary slots per head (packed input) or per sequence; extra slots per sequence
+};
 
-// ---------------------------------------------------------------------------------------------
-// b_j = sum_{r<=j, r in chunk} g_r   (grid: N x BH)
-__global__ void k_cumsum(Dims d, const float* __restrict__ g, bsum_t* __restrict__ bcum) {
-    const int c = blockIdx.x, bh = blockIdx.y, h = bh % d.H;
-    const ChunkPos cp = chunk_pos(d, c, bh);
-    const int L = cp.L, dkd = d.dkd();
-    for (int i = threadIdx.x; i < dkd; i += blockDim.x) {
-        bsum_t b = 0.0;
-        for (int j = 0; j < L; ++j) {
-            const size_t tok = cp.tok0 + size_t(j) * cp.ts;  // in the caller's arrays
-            float gv = d.kind == 1 ? g[h] : (d.kind == 2 ? g[tok] : g[tok * d.dk + i]);
-            b += gv;
-            bcum[(cp.wtok0 + j) * dkd + i] = b;
+// Segment `x` of the grid: packed input numbers the segments of all sequences of a head one after the other, sequence s
+// from its first unit / m + s on (units counted per sequence and at least one each, so that two never overlap).
+struct GSeg { SeqWalk w; int n, seg, nsq; size_t slot0; };
+__device__ __forceinline__ int seg_base(const Dims& d, int m, int extra, int s) {
+    return (m == 1 ? d.cstart[s] : d.cstart[s] / m + s) + extra * s;
+}
+__device__ __forceinline__ GSeg find_seg(const Dims& d, int m, int slots, int extra, int x, int y) {
+    GSeg r;
+    if (!d.cu) {
+        r.w = SeqWalk{y, y, 0, 0, 0, d.T};
+        r.seg = x;
+        r.slot0 = size_t(y) * slots;
+    } else {
+        int lo = 0, hi = d.nseq;  // last s whose base is <= x
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (seg_base(d, m, extra, mid) <= x) lo = mid; else hi = mid;
+        }
+        r.w = SeqWalk{y, lo * d.H + y, 0, 0, d.cu[lo], d.cu[lo + 1]};
+        r.seg = x - seg_base(d, m, extra, lo);
+        r.slot0 = size_t(y) * slots + seg_base(d, m, extra, lo);
+    }
+    const int len = r.w.tend - r.w.tbeg;
+    r.n = (len + GT - 1) / GT;
+    r.nsq = (len + d.gC * m - 1) / (d.gC * m);
+    return r;
+}
+__device__ __forceinline__ ChunkPos step_pos(const Dims& d, const SeqWalk& w, int k) {
+    const int t0 = w.tbeg + k * GT;
+    return chunk_pos_at(d, w.bh, t0, min(GT, w.tend - t0), 0);
+}
+
+// one operand's 32 rows on their way to LDS: 16-byte pieces, dealt to the threads row by row
+template <typename TIO, int W, int NT>
+struct GTile {
+    static constexpr int PER = 16 / int(sizeof(TIO)), PR = W / PER, CNT = GT * PR / NT;
+    static_assert(CNT * NT == GT * PR, "tile pieces divide evenly");
+    u32x4 v[CNT];
+    // uniform base + a 32-bit byte offset per lane; rows beyond the ragged end repeat the last one and are zeroed later
+    __device__ __forceinline__ void gload(const TIO* base, uint32_t rowbytes, int L, int rev, int tid) {
+        const char* b = reinterpret_cast<const char*>(base);
+        _Pragma("unroll") for (int i = 0; i < CNT; ++i) {
+            const int p = tid + NT * i, row = min(p / PR, L - 1), c = p % PR;
+            v[i] = *reinterpret_cast<const u32x4*>(b + uint32_t(rev ? L - 1 - row : row) * rowbytes + c * 16);
         }
     }
-}
-
-// MODE 0:  out_c = sum_r (x_r * e^{b_C - b_r})^T y_r      (x = k, y = v : chunk state U_c)
-// MODE 1:  out_c = sum_j (x_j * e^{b_j})^T y_j            (x = q, y = d_o : chunk state gradient dU_c)
-template <typename TIO, int MODE>
-__global__ void k_local_state(Dims d, const TIO* __restrict__ x, const TIO* __restrict__ y,
-                              const bsum_t* __restrict__ bcum, float* __restrict__ out) {
-    const int c = blockIdx.x, bh = blockIdx.y;
-    const ChunkPos cp = chunk_pos(d, c, bh);
-    const int L = cp.L, dkd = d.dkd();
-    if (L <= 0) return;  // packed input: the grid is sized for an upper bound of the chunk count
-    const size_t tok0 = cp.wtok0;                              // token index in the library's own arrays
-    auto U = [&](int r) { return cp.tok0 + size_t(r) * cp.ts; };  // row of token r in the caller's arrays
-    float* dst = out + cp.slot * d.dk * d.dv;
-    // scalar kinds: the weight depends on the token only, one table per chunk instead of an exp per product
-    __shared__ float wtok[128];
-    if (dkd == 1) {
-        const bsum_t bC = bval(bcum, tok0 + L - 1, 1, 0);
-        for (int r = threadIdx.x; r < L; r += blockDim.x) {
-            const bsum_t br = bval(bcum, tok0 + r, 1, 0);
-            wtok[r] = MODE == 0 ? expd(bC - br) : expd(br);
-        }
-        __syncthreads();
-    }
-    for (int e = threadIdx.x; e < d.dk * d.dv; e += blockDim.x) {
-        const int i = e / d.dv, j = e % d.dv;
-        float acc = 0.f;
-        if (dkd == 1) {
-            _Pragma("unroll 8")
-            for (int r = 0; r < L; ++r) acc += to_f32(x[U(r) * d.dk + i]) * wtok[r] * to_f32(y[U(r) * d.dv + j]);
-        } else {
-            const bsum_t bC = bval(bcum, tok0 + L - 1, dkd, i);
-            for (int r = 0; r < L; ++r) {
-                const bsum_t br = bval(bcum, tok0 + r, dkd, i);
-                const float w = MODE == 0 ? expd(bC - br) : expd(br);
-                acc += to_f32(x[U(r) * d.dk + i]) * w * to_f32(y[U(r) * d.dv + j]);
-            }
-        }
-        dst[e] = acc;
-    }
-}
-
-// Forward scan over chunks, in place: slot c holds U_c on entry and S_c (state at the START of
-// chunk c) on exit; S_{c+1} = e^{b_C} * S_c + U_c.   REVERSE: slot c holds dU_c on entry and
-// dS_{c+1} (gradient w.r.t. the state at the END of chunk c) on exit; dS_c = e^{b_C} * dS_{c+1} + dU_c.
-// `edge_in` is M_0 (or d M_T), `edge_out` receives M_T (or d M_0); either may be NULL.
-template <bool REVERSE>
-__global__ void k_scan(Dims d, const bsum_t* __restrict__ bcum, float* __restrict__ states,
-                       const float* __restrict__ edge_in, float* __restrict__ edge_out) {
-    const SeqWalk w = seq_walk(d, blockIdx.y);  // grid.y = Dims::seqs()
-    const int dkd = d.dkd();
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    const int sz = d.dk * d.dv;
-    if (e >= sz) return;
-    const int i = e / d.dv;
-    float s = edge_in ? edge_in[size_t(w.edge) * sz + e] : 0.f;
-    for (int n = 0; n < w.n; ++n) {
-        const ChunkPos cp = walk_pos(d, w, REVERSE ? w.n - 1 - n : n);
-        const float lam = expd(bval(bcum, cp.wtok0 + cp.L - 1, dkd, i));
-        float* slot = states + cp.slot * sz + e;
-        const float u = *slot;
-        *slot = s;
-        s = lam * s + u;
-    }
-    if (edge_out) edge_out[size_t(w.edge) * sz + e] = s;
-}
-
-// A_jr = sum_i q_ji k_ri e^{b_ji - b_ri}  for r <= j  (0 otherwise), into LDS [C*C]
-template <typename TIO>
-__device__ void scores_to_lds(const Dims& d, const TIO* q, const TIO* k, const bsum_t* bcum, const ChunkPos& cp,
-                              int L, float* A) {
-    const int dkd = d.dkd();
-    const size_t tok0 = cp.wtok0;
-    auto U = [&](int r) { return cp.tok0 + size_t(r) * cp.ts; };
-    for (int e = threadIdx.x; e < L * L; e += blockDim.x) {
-        const int j = e / L, r = e % L;
-        float acc = 0.f;
-        if (r <= j) {
-            if (dkd == 1) {
-                _Pragma("unroll 8")
-                for (int i = 0; i < d.dk; ++i)
-                    acc += to_f32(q[U(j) * d.dk + i]) * to_f32(k[U(r) * d.dk + i]);
-                acc *= expd(bval(bcum, tok0 + j, 1, 0) - bval(bcum, tok0 + r, 1, 0));
+    __device__ __forceinline__ void commit(float* dst, int ld, int L, int tid) const {
+        _Pragma("unroll") for (int i = 0; i < CNT; ++i) {
+            const int p = tid + NT * i, row = p / PR, c = p % PR;
+            const uint32_t keep = row < L ? 0xffffffffu : 0u;
+            const u32x4 x = {v[i].x & keep, v[i].y & keep, v[i].z & keep, v[i].w & keep};
+            float* q = dst + row * ld + c * PER;
+            if (PER == 4) {
+                *reinterpret_cast<u32x4*>(q) = x;
             } else {
-                for (int i = 0; i < d.dk; ++i)
-                    acc += to_f32(q[U(j) * d.dk + i]) * to_f32(k[U(r) * d.dk + i]) *
-                           expd(bcum[(tok0 + j) * dkd + i] - bcum[(tok0 + r) * dkd + i]);
+                *reinterpret_cast<u32x4*>(q) = u32x4{x.x << 16, x.x & 0xffff0000u, x.y << 16, x.y & 0xffff0000u};
+                *reinterpret_cast<u32x4*>(q + 4) = u32x4{x.z << 16, x.z & 0xffff0000u, x.w << 16, x.w & 0xffff0000u};
             }
         }
-        A[j * d.C + r] = acc;
+    }
+};
+
+// LDS of a walker, in floats.  Row strides == 4 mod 64 words: 16-byte row reads of 16 lanes tile the banks.
+//   Q | K | V | score partials [wave][16][64] | W (vector kind: one or two tiles of weighted rows) | tables
+template <int KD, int TV, int VEC, bool SUM>
+struct GLds {
+    static constexpr int NW = TV / 32, LQ = KD + 4, LV = TV + 4;
+    static constexpr int COLS = VEC == 2 ? TV : KD;           // decayed features held by this workgroup (vector kind)
+    static constexpr int WT = VEC == 0 ? 0 : GT * (COLS + 4), WN = VEC == 0 ? 0 : (SUM ? 1 : 2);
+    static constexpr int oK = SUM ? 0 : GT * LQ, oV = oK + GT * LQ, oP = oV + GT * LV, oW = oP + (SUM ? 0 : NW * 1024);
+    static constexpr int oT = oW + WN * WT;
+    static constexpr int tables = VEC == 0 ? 2 * 34 + 2 * GT : 3 * COLS;
+    static constexpr int oD = oT + tables, oE = oD + NW * GT, total = oE + (VEC == 0 && !SUM ? 1024 : 0);
+    static constexpr int bytes = total * 4;
+};
+
+// VEC 0: one decay per token (or none).  VEC 1: a decay per key-role feature (o, dv: the scores carry the decay).
+// VEC 2: a decay per value-role feature (dq, dk: the outputs do).
+//
+// The vector kind's pair weights e^{E_p - E_s} do not factor over the pair, but split at a reference between s and p they
+// do, into two factors <= 1.  At level l = 16, 8, 4, 2, 1 the pairs whose positions first differ in bit log2 l are taken
+// together (p in an odd block of l positions, s in the even block before it, reference at the start of p's block): every
+// position is on one side only, so one tile W holds, row by row, either side's weighted operand.  Running sums start at
+// the reference, so they are exact where the weight matters, however strong the decay.
+template <typename TIO, int KD, int TV, int VEC, bool SUM>
+__global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GArgs a) {
+    using Lds = GLds<KD, TV, VEC, SUM>;
+    constexpr int NW = Lds::NW, NT = 2 * TV, LQ = Lds::LQ, LV = Lds::LV, KB = KD / 32, COLS = Lds::COLS, LW = COLS + 4;
+    constexpr int ITEMS = VEC == 0 ? 1 : (2 * COLS + NT - 1) / NT;
+    extern __shared__ __align__(16) float sm[];
+    float *Q = sm, *K = sm + Lds::oK, *V = sm + Lds::oV, *Pp = sm + Lds::oP, *W = sm + Lds::oW;
+    double* bs = reinterpret_cast<double*>(sm + Lds::oT);   // VEC 0: E_p [32], then the step's total
+    float *wi = sm + Lds::oT + 68, *wo = wi + GT;           // VEC 0: e^{E_p}, e^{E - E_p}
+    float *tot = sm + Lds::oT, *lamv = tot + 2 * COLS;      // VEC: half sums [2][COLS], e^E [COLS]
+    float* dred = sm + Lds::oD;                             // [wave][32]: partial row products
+    float* pw = sm + Lds::oE;                               // VEC 0: pair weights e^{E_n - E_r}, in the order of a score block's registers
+
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 31, half = lane >> 5;
+    // Every phase reads LDS at its own lane-dependent addresses.  Left alone the compiler keeps them all in registers
+    // across the loop (over a hundred); with the thread id hidden at the start of a phase it recomputes that phase's few.
+    auto fresh = [&]() { int t = tid; asm volatile("" : "+v"(t)); return t; };
+    const int slice = blockIdx.z % a.nsl;
+    const GRole& R = a.role[blockIdx.z / a.nsl];
+    const GSeg s = find_seg(d, a.m, a.slots, a.extra, blockIdx.x, blockIdx.y);
+    const SeqWalk walk = s.w;
+    const int rev = R.rev, vcol = slice * TV;               // first value column of this workgroup
+    const bool empty_seq = s.n == 0 && s.seg == 0;          // packed input: the state passes through
+    if (s.seg >= s.nsq && !empty_seq) return;
+    const int steps = a.m * (d.gC / GT), kbeg = s.seg * steps, kend = min(s.n, kbeg + steps), cnt = max(kend - kbeg, 0);
+    const int wseg = rev ? s.nsq - 1 - s.seg : s.seg;       // segment index in walk order
+    if (SUM && wseg >= s.nsq - 1) return;                   // nobody starts from the last segment's end
+    const size_t sz = size_t(a.kd) * a.vd;
+    // the state blocks: S[ib][4g+j] = state[key feature 32 ib + 8g + 4 half + j][value feature vcol + 32 w + n]
+    f32x16 S[KB];
+    _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) S[ib] = f32x16{0};
+    // (stored [d_k][d_v]: rows are key features, or with trans value features)
+    auto soff = [&](int ib, int g) {
+        const int kf = 32 * ib + 8 * g + 4 * half, vf = vcol + 32 * w + n;
+        return R.trans ? size_t(vf) * a.kd + kf : size_t(kf) * a.vd + vf;
+    };
+    auto state_load = [&](const float* e) {
+        _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
+            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                const float* p = e + soff(ib, g);
+                if (R.trans) {
+                    const f32x4 t = load4(p);
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) S[ib][4 * g + j] = t[j];
+                } else {
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) S[ib][4 * g + j] = p[size_t(j) * a.vd];
+                }
+            }
+    };
+    auto state_store = [&](float* e) {
+        _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
+            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                float* p = e + soff(ib, g);
+                if (R.trans) {
+                    store4(p, f32x4{S[ib][4 * g], S[ib][4 * g + 1], S[ib][4 * g + 2], S[ib][4 * g + 3]});
+                } else {
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) p[size_t(j) * a.vd] = S[ib][4 * g + j];
+                }
+            }
+    };
+    if (!SUM) {
+        if (wseg > 0) state_load(R.bound + (s.slot0 + wseg) * sz);
+        else if (R.edge_in) state_load(R.edge_in + size_t(walk.edge) * sz);
+    }
+
+    GTile<TIO, KD, NT> rq, rk;
+    GTile<TIO, TV, NT> rv;
+    float gval = 0.f;                                       // VEC 0: log-decay of walk position `lane`
+    // VEC: item = (column, half): the 16 transitions d_p INTO the positions of its half and, second half, the closing one.
+    // Forward: the decay of the token itself; backward: that of the position before.
+    float dt[ITEMS][16], dn[ITEMS][16], closing[ITEMS], closing_n[ITEMS];
+    double gtot[ITEMS];
+    _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) gtot[i] = 0.0;
+    auto item_ok = [&](int t, int i) { return 2 * COLS >= NT * (i + 1) || t + NT * i < 2 * COLS; };
+    auto item_col = [&](int t, int i) { return (t + NT * i) % COLS; };
+    auto item_half = [&](int t, int i) { return (t + NT * i) / COLS; };
+
+    auto gload = [&](int kk) {
+        const int tid = fresh();
+        ChunkPos p = step_pos(d, walk, rev ? kend - 1 - min(kk, cnt - 1) : kbeg + min(kk, cnt - 1));
+        if (kk >= cnt) p.L = 1;  // past the last step: one row, again and again, that nobody uses
+        const uint32_t kb = uint32_t(p.ts) * a.kd * sizeof(TIO), vb = uint32_t(p.ts) * a.vd * sizeof(TIO);
+        if (!SUM) rq.gload(static_cast<const TIO*>(R.xq) + p.tok0 * a.kd, kb, p.L, rev, tid);
+        rk.gload(static_cast<const TIO*>(R.xk) + p.tok0 * a.kd, kb, p.L, rev, tid);
+        rv.gload(static_cast<const TIO*>(R.xv) + p.tok0 * a.vd + vcol, vb, p.L, rev, tid);
+        if (VEC == 0) {
+            if (d.kind != 0 && w == 0) {
+                const int row = min(n, p.L - 1);
+                gval = d.kind == 1 ? a.g[walk.bh % d.H] : a.g[p.tok0 + size_t(rev ? p.L - 1 - row : row) * p.ts];
+            }
+        } else {
+            const char* gb = reinterpret_cast<const char*>(a.g + p.tok0 * d.dk + (VEC == 2 ? vcol : 0));
+            const uint32_t grow = uint32_t(p.ts) * d.dk * 4;
+            _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) {
+                if (!item_ok(tid, i)) continue;
+                const uint32_t col = 4 * item_col(tid, i);
+                const int h16 = 16 * item_half(tid, i);
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) {  // (what does not exist is zeroed when it is used)
+                    const int pos = h16 + x - rev, tok = min(max(rev ? p.L - 1 - pos : pos, 0), p.L - 1);
+                    dn[i][x] = *reinterpret_cast<const float*>(gb + uint32_t(tok) * grow + col);
+                }
+                closing_n[i] = *reinterpret_cast<const float*>(gb + col);
+            }
+        }
+    };
+    if (cnt > 0) gload(0);
+
+    for (int kk = 0; kk < cnt; ++kk) {
+        const ChunkPos cp = step_pos(d, walk, rev ? kend - 1 - kk : kbeg + kk);
+        const int L = cp.L;
+        {
+            const int tid = fresh();
+            if (!SUM) rq.commit(Q, LQ, L, tid);
+            rk.commit(K, LQ, L, tid);
+            rv.commit(V, LV, L, tid);
+        }
+        if (VEC == 0) {
+            // E in fp64: the sums reach hundreds for strong decays while only their O(1) differences enter exp()
+            if (d.kind != 0 && w == 0) {
+                const double x = n < L ? double(gval) : 0.0;
+                double inc = x;
+                for (int off = 1; off < GT; off <<= 1) {
+                    const double y = __shfl_up(inc, off, 32);
+                    if (n >= off) inc += y;
+                }
+                const double all = __shfl(inc, GT - 1, 32), E = rev ? inc - x : inc;
+                if (lane < GT) {
+                    bs[n] = E;
+                    wi[n] = expf(float(E));
+                    wo[n] = expf(float(all - E));
+                    if (n == 0) bs[GT] = all;
+                }
+                gtot[0] += all;
+            }
+        } else {
+            const int tid = fresh();
+            _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) {
+                if (!item_ok(tid, i)) continue;
+                const int h = item_half(tid, i);
+                double t = 0.0;
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                    const int pos = 16 * h + x - rev;
+                    dt[i][x] = pos >= 0 && pos < L ? dn[i][x] : 0.f;
+                    t += double(dt[i][x]);
+                }
+                closing[i] = rev && L == GT && h ? closing_n[i] : 0.f;
+                tot[h * COLS + item_col(tid, i)] = float(t + double(closing[i]));
+            }
+        }
+        __syncthreads();  // (A) rows and decay tables of this step are in LDS
+
+        // ---- vector kind: writers of the weighted tiles (see the level scheme above)
+        auto each = [&](float* dst, auto&& weigh) {  // weigh(p, column, exponent sums' item) -> value
+            const int tid = fresh();
+            _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) {
+                if (!item_ok(tid, i)) continue;
+                weigh(i, item_half(tid, i), item_col(tid, i), dst);
+            }
+        };
+        auto write_start = [&](float* dst) {  // weight e^{E_p} from the start of the step; also e^E
+            each(dst, [&](int i, int h, int c, float* o) {
+                const float t0 = tot[c];
+                double e = h ? t0 : 0.0;
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                    e += double(dt[i][x]);
+                    const int p = 16 * h + x;
+                    const float wt = expf(float(e));
+                    o[p * LW + c] = VEC == 1 ? Q[p * LQ + c] * wt : wt;
+                }
+                if (h == 0) lamv[c] = expf(t0 + tot[COLS + c]);
+                if (SUM && h == 0) gtot[i] += double(t0) + double(tot[COLS + c]);
+            });
+        };
+        auto write_end = [&](float* dst) {  // weight e^{E - E_p} to the end of the step, on the state update's operand
+            each(dst, [&](int i, int h, int c, float* o) {
+                double e = h ? closing[i] : tot[COLS + c];
+                if (SUM && h == 0) {
+                    lamv[c] = expf(tot[c] + tot[COLS + c]);
+                    gtot[i] += double(tot[c]) + double(tot[COLS + c]);
+                }
+                _Pragma("unroll") for (int x = 15; x >= 0; --x) {
+                    const int p = 16 * h + x;
+                    o[p * LW + c] = (VEC == 1 ? K[p * LQ + c] : V[p * LV + c]) * expf(float(e));
+                    e += double(dt[i][x]);
+                }
+            });
+        };
+        auto write_level = [&](float* dst, auto lvc) {
+            constexpr int lv = decltype(lvc)::value;
+            each(dst, [&](int i, int h, int c, float* o) {
+                _Pragma("unroll") for (int b = 0; b < 16; b += lv) {
+                    const bool odd = lv == 16 ? h != 0 : ((b / lv) & 1) != 0;
+                    float e[lv];
+                    if (odd) {  // query side: from the block's start up to the position
+                        double sum = 0.0;
+                        _Pragma("unroll") for (int x = 0; x < lv; ++x) { sum += double(dt[i][b + x]); e[x] = float(sum); }
+                    } else {    // key side: from the position to the block's end
+                        double sum = 0.0;
+                        _Pragma("unroll") for (int x = lv - 1; x >= 0; --x) { e[x] = float(sum); sum += double(dt[i][b + x]); }
+                    }
+                    _Pragma("unroll") for (int x = 0; x < lv; ++x) {
+                        const int p = 16 * h + b + x;
+                        const float wt = expf(e[x]);
+                        if (VEC == 1) o[p * LW + c] = (odd ? Q[p * LQ + c] : K[p * LQ + c]) * wt;
+                        else o[p * LW + c] = odd ? wt : V[p * LV + c] * wt;
+                    }
+                }
+            });
+        };
+
+        f32x16 O;
+        // inter: O^T[v][p] = sum_i S[i][v] x_p[i], the state blocks as A operands out of the accumulators (two chains:
+        // half the roundings in a row, and an MFMA never waits for the one before it)
+        auto inter = [&](const float* X, int ld) {
+            const int l = fresh() & 63, n = l & 31, half = l >> 5;
+            f32x16 o[2] = {f32x16{0}, f32x16{0}};
+            _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
+                _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                    const f32x4 x = *reinterpret_cast<const f32x4*>(X + n * ld + 32 * ib + 8 * g + 4 * half);
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j & 1] = mfma2(S[ib][4 * g + j], x[j], o[j & 1]);
+                }
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] = o[0][x] + o[1][x];
+        };
+        // this wave's share (a range of features) of the block P^T[s][p] = y_s . x_p
+        auto score_part = [&](const float* Y, const float* X, int ld) {
+            const int l = fresh() & 63, n = l & 31, half = l >> 5;
+            f32x16 P = {0};
+            _Pragma("unroll") for (int f = 0; f < KD / NW; f += 8) {
+                const int c = w * (KD / NW) + f + 4 * half;
+                const f32x4 y = *reinterpret_cast<const f32x4*>(Y + n * ld + c), x = *reinterpret_cast<const f32x4*>(X + n * ld + c);
+                _Pragma("unroll") for (int j = 0; j < 4; ++j) P = mfma2(y[j], x[j], P);
+            }
+            return P;
+        };
+        auto part_store = [&](const f32x16& P) {
+            const int lane = fresh() & 63;
+            _Pragma("unroll") for (int g = 0; g < 4; ++g)
+                *reinterpret_cast<f32x4*>(Pp + w * 1024 + (g * 64 + lane) * 4) = f32x4{P[4 * g], P[4 * g + 1], P[4 * g + 2], P[4 * g + 3]};
+        };
+        auto part_sum = [&]() {
+            const int lane = fresh() & 63;
+            f32x16 P;
+            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                f32x4 t = *reinterpret_cast<const f32x4*>(Pp + (g * 64 + lane) * 4);
+                _Pragma("unroll") for (int u = 1; u < NW; ++u) t += *reinterpret_cast<const f32x4*>(Pp + u * 1024 + (g * 64 + lane) * 4);
+                _Pragma("unroll") for (int j = 0; j < 4; ++j) P[4 * g + j] = t[j];
+            }
+            return P;
+        };
+        auto prow = [&](int x) { return 8 * (x >> 2) + 4 * half + (x & 3); };  // row of result register x
+        auto hrow = [](int x, int half) { return 8 * (x >> 2) + 4 * half + (x & 3); };
+        // sum_s Z[s][v] P^T[s][p]: the score block as B operand out of its registers
+        auto intra = [&](const float* Z, int ld, const f32x16& P) {
+            const int l = fresh() & 63, n = l & 31, half = l >> 5;
+            f32x16 acc = {0};
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) acc = mfma2(Z[hrow(x, half) * ld + 32 * w + n], P[x], acc);
+            return acc;
+        };
+        auto add_to_O = [&](const f32x16& X) { _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] += X[x]; };
+        auto diagonal = [&](const f32x16& P) {  // P[p][p] for this lane's position
+            const int l = fresh() & 63;
+            float t = 0.f;
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) t += hrow(x, l >> 5) == (l & 31) ? P[x] : 0.f;
+            return t + __shfl_xor(t, 32, 64);
+        };
+        // the pair (p, p) leaves the output's product with aux: it is the same number in q.dq and in k.dk and cancels
+        // in the decay gradient, exactly instead of to rounding
+        auto finish = [&](float pd) {
+            const int l = fresh() & 63, n = l & 31, half = l >> 5;
+            const int tok = rev ? L - 1 - n : n;           // token of this lane's position (n < L)
+            const size_t orow = cp.tok0 + size_t(n < L ? tok : 0) * cp.ts;
+            const size_t oel = orow * a.vd + vcol + 32 * w + 4 * half;  // + 8g: four consecutive output features
+            auto aux4 = [&](int g) { return load4(static_cast<const TIO*>(R.aux) + oel + 8 * g); };
+            if (R.xdot) {
+                if (VEC == 0) {
+                    float t = 0.f;
+                    _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                        const f32x4 q4 = aux4(g);
+                        _Pragma("unroll") for (int j = 0; j < 4; ++j) t += q4[j] * O[4 * g + j];
+                    }
+                    t += __shfl_xor(t, 32, 64);
+                    if (half == 0) dred[w * GT + n] = t;
+                } else if (n < L) {
+                    float* x = R.xdot + (cp.wtok0 + tok) * a.vd + vcol + 32 * w + 4 * half;
+                    _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                        const f32x4 q4 = aux4(g);
+                        store4(x + 8 * g, f32x4{q4[0] * O[4 * g], q4[1] * O[4 * g + 1], q4[2] * O[4 * g + 2], q4[3] * O[4 * g + 3]});
+                    }
+                }
+            }
+            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                const f32x4 z = *reinterpret_cast<const f32x4*>(V + n * LV + 32 * w + 8 * g + 4 * half);
+                f32x4 o;
+                _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] = O[4 * g + j] + pd * z[j];
+                if (n < L) store4(static_cast<TIO*>(R.out) + oel + 8 * g, o);
+            }
+        };
+        // S[i][v] = lam(ib, x) S[i][v] + sum_t Y[t][i] (w_t Z[t][v]); the step's own sum is formed by itself, so the state
+        // sees one rounding per step instead of one per token
+        auto update = [&](const float* Y, int ldy, const float* Z, int ldz, const float* wt, auto&& lam) {
+            gload(kk + 1);  // the next step's rows: the update outlasts a trip to memory and has the registers
+            // (unconditional: behind a branch the old values would stay live through the whole step)
+            const int l = fresh() & 63, n = l & 31, half = l >> 5;
+            float z[16];
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                const int t = hrow(x, half);
+                z[x] = wt ? Z[t * ldz + 32 * w + n] * wt[t] : Z[t * ldz + 32 * w + n];
+            }
+            _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) {
+                f32x16 U = {0};
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) U = mfma2(Y[hrow(x, half) * ldy + 32 * ib + n], z[x], U);
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) S[ib][x] = fmaf(lam(ib, x), S[ib][x], U[x]);
+            }
+        };
+
+        if constexpr (VEC == 0) {
+            if (!SUM) {
+                part_store(score_part(K, Q, LQ));
+                if (d.kind != 0) {  // each wave its share of the weights, of pairs (r < n) only
+                    const int l = fresh() & 63, n = l & 31;
+                    const double bn = bs[n];
+                    _Pragma("unroll") for (int g = w; g < 4; g += NW) {
+                        f32x4 e;
+                        _Pragma("unroll") for (int j = 0; j < 4; ++j) {
+                            const int r = 8 * g + 4 * (l >> 5) + j;
+                            e[j] = r < n ? expf(float(bn - bs[r])) : 0.f;
+                        }
+                        *reinterpret_cast<f32x4*>(pw + (g * 64 + l) * 4) = e;
+                    }
+                }
+                inter(Q, LQ);
+                if (d.kind != 0) {
+                    const float e = wi[n];
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] *= e;
+                }
+                __syncthreads();  // (B) score partials
+                f32x16 P = part_sum();
+                const float pd = diagonal(P);
+                const int l = fresh() & 63;
+                _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                    if (d.kind != 0) {
+                        const f32x4 e = *reinterpret_cast<const f32x4*>(pw + (g * 64 + l) * 4);
+                        _Pragma("unroll") for (int j = 0; j < 4; ++j) P[4 * g + j] *= e[j];
+                    } else {
+                        _Pragma("unroll") for (int j = 0; j < 4; ++j) P[4 * g + j] = 8 * g + 4 * (l >> 5) + j < (l & 31) ? P[4 * g + j] : 0.f;
+                    }
+                }
+                add_to_O(intra(V, LV, P));
+                finish(pd);
+            }
+            const float lam = d.kind != 0 ? expf(float(bs[GT])) : 1.f;
+            update(K, LQ, V, LV, d.kind != 0 ? wo : nullptr, [&](int, int) { return lam; });
+        } else if constexpr (SUM) {
+            write_end(W);
+            __syncthreads();
+            update(W, LW, V, LV, nullptr, [&](int ib, int x) { return lamv[32 * ib + prow(x)]; });
+        } else {
+            float *W0 = W, *W1 = W + Lds::WT;
+            auto lev = [](auto f, float* x, float* y) {  // levels alternate between the two tiles
+                f(x, std::integral_constant<int, 16>{}, y);
+                f(y, std::integral_constant<int, 8>{}, x);
+                f(x, std::integral_constant<int, 4>{}, y);
+                f(y, std::integral_constant<int, 2>{}, x);
+                f(x, std::integral_constant<int, 1>{}, y);
+            };
+            if constexpr (VEC == 1) {
+                const f32x16 raw = score_part(K, Q, LQ);
+                f32x16 P;
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) P[x] = prow(x) == n ? raw[x] : 0.f;
+                write_start(W0);
+                __syncthreads();
+                write_level(W1, std::integral_constant<int, 16>{});
+                inter(W0, LW);
+                __syncthreads();
+                lev([&](float* cur, auto lvc, float* nxt) {
+                    constexpr int lv = decltype(lvc)::value;
+                    if constexpr (lv > 1) write_level(nxt, std::integral_constant<int, lv / 2>{});
+                    else write_end(nxt);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const f32x16 G = score_part(cur, cur, LW);
+                    const int l = fresh() & 63, n = l & 31;
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                        const int r = hrow(x, l >> 5);
+                        if (r < n && (r ^ n) >= lv && (r ^ n) < 2 * lv) P[x] = G[x];
+                    }
+                    if constexpr (lv == 1) part_store(P);
+                    __syncthreads();
+                }, W1, W0);
+                P = part_sum();
+                const float pd = diagonal(P);
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) P[x] = prow(x) == n ? 0.f : P[x];
+                add_to_O(intra(V, LV, P));
+                finish(pd);
+                update(W0, LW, V, LV, nullptr, [&](int ib, int x) { return lamv[32 * ib + prow(x)]; });
+            } else {
+                part_store(score_part(K, Q, LQ));
+                write_start(W0);
+                __syncthreads();
+                write_level(W1, std::integral_constant<int, 16>{});
+                inter(Q, LQ);
+                auto row4 = [&](const float* X, int n, int half, int g) {
+                    return *reinterpret_cast<const f32x4*>(X + n * LW + 32 * w + 8 * g + 4 * half);
+                };
+                _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                    const f32x4 e = row4(W0, n, half, g);
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) O[4 * g + j] *= e[j];
+                }
+                const f32x16 P = part_sum();
+                const float pd = diagonal(P);
+                __syncthreads();
+                lev([&](float* cur, auto lvc, float* nxt) {
+                    constexpr int lv = decltype(lvc)::value;
+                    if constexpr (lv > 1) write_level(nxt, std::integral_constant<int, lv / 2>{});
+                    else write_end(nxt);
+                    __builtin_amdgcn_sched_barrier(0);
+                    f32x16 G;
+                    const int l = fresh() & 63, n = l & 31, half = l >> 5;
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                        const int r = hrow(x, half);
+                        G[x] = r < n && (r ^ n) >= lv && (r ^ n) < 2 * lv ? P[x] : 0.f;
+                    }
+                    const f32x16 X = intra(cur, LW, G);
+                    _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                        const f32x4 e = row4(cur, n, half, g);
+                        _Pragma("unroll") for (int j = 0; j < 4; ++j) O[4 * g + j] += (n & lv) ? X[4 * g + j] * e[j] : 0.f;
+                    }
+                    __syncthreads();
+                }, W1, W0);
+                finish(pd);
+                const float lam = lamv[32 * w + n];
+                update(K, LQ, W0, LW, nullptr, [&](int, int) { return lam; });
+            }
+        }
+        __syncthreads();  // (D) every read of this step's tiles is done
+        if (!SUM && VEC == 0 && R.xdot && tid < L) {
+            float t = 0.f;
+            _Pragma("unroll") for (int u = 0; u < NW; ++u) t += dred[u * GT + tid];
+            R.xdot[size_t(slice) * d.BH() * d.T + cp.wtok0 + (rev ? L - 1 - tid : tid)] = t;
+        }
+    }
+
+    if (SUM) {
+        state_store(R.bound + (s.slot0 + wseg + 1) * sz);
+        if (slice == 0 && d.kind != 0) {
+            if (VEC == 0) {
+                if (tid == 0) R.gseg[s.slot0 + wseg] = gtot[0];
+            } else {
+                _Pragma("unroll") for (int i = 0; i < ITEMS; ++i)
+                    if (item_ok(tid, i) && item_half(tid, i) == 0) R.gseg[(s.slot0 + wseg) * COLS + item_col(tid, i)] = gtot[i];
+            }
+        }
+        return;
+    }
+    if (empty_seq || wseg == s.nsq - 1) {
+        if (R.edge_out) state_store(R.edge_out + size_t(walk.edge) * sz);
+        if (R.end_slot && !empty_seq) state_store(R.bound + (s.slot0 + s.nsq) * sz);
     }
 }
 
-// o_j = sum_{r<=j} A_jr v_r + (q_j * e^{b_j}) S_c      (grid: N x BH, dynamic LDS C*C floats)
-template <typename TIO>
-__global__ void k_output(Dims d, const TIO* __restrict__ q, const TIO* __restrict__ k, const TIO* __restrict__ v,
-                         const bsum_t* __restrict__ bcum, const float* __restrict__ states, TIO* __restrict__ o) {
-    extern __shared__ float lds[];
-    float* A = lds;
-    const int c = blockIdx.x, bh = blockIdx.y;
-    const ChunkPos cp = chunk_pos(d, c, bh);
-    const int L = cp.L, dkd = d.dkd();
-    if (L <= 0) return;  // packed input: the grid is sized for an upper bound of the chunk count
-    const size_t tok0 = cp.wtok0;                              // token index in the library's own arrays
-    auto U = [&](int r) { return cp.tok0 + size_t(r) * cp.ts; };  // row of token r in the caller's arrays
-    const float* S = states + cp.slot * d.dk * d.dv;
-    scores_to_lds(d, q, k, bcum, cp, L, A);
-    __syncthreads();
-    for (int e = threadIdx.x; e < L * d.dv; e += blockDim.x) {
-        const int j = e / d.dv, col = e % d.dv;
-        float acc = 0.f;
-        _Pragma("unroll 8")
-        for (int r = 0; r <= j; ++r) acc += A[j * d.C + r] * to_f32(v[U(r) * d.dv + col]);
-        if (dkd == 1) {  // one decay factor per token
-            float inter = 0.f;
-            _Pragma("unroll 8")
-            for (int i = 0; i < d.dk; ++i) inter += to_f32(q[U(j) * d.dk + i]) * S[i * d.dv + col];
-            acc += expd(bval(bcum, tok0 + j, 1, 0)) * inter;
-        } else {
-            for (int i = 0; i < d.dk; ++i)
-                acc += to_f32(q[U(j) * d.dk + i]) * expd(bval(bcum, tok0 + j, dkd, i)) * S[i * d.dv + col];
+// States at the segment boundaries of a sequence, in walk order: E_0 = edge_in, E_{s+1} = e^{g_s} E_s + U_s, in place (slot
+// s+1 holds U_s on entry).  Elementwise, four elements per thread, eight slots requested ahead of the chain.
+// grid: (d_k d_v / 1024, sequences, directions)
+__global__ __launch_bounds__(256) void gk_scan(Dims d, GArgs a) {
+    const GRole& R = a.role[blockIdx.z];
+    const int q = blockIdx.y, sz = d.dk * d.dv;
+    int s0 = 0;
+    SeqWalk w;
+    size_t slot0;
+    if (!d.cu) {
+        w = SeqWalk{q, q, 0, 0, 0, d.T};
+        slot0 = size_t(q) * a.slots;
+    } else {
+        s0 = q / d.H;
+        w = SeqWalk{q % d.H, q, 0, 0, d.cu[s0], d.cu[s0 + 1]};
+        slot0 = size_t(q % d.H) * a.slots + seg_base(d, a.m, a.extra, s0);
+    }
+    const int nsq = (w.tend - w.tbeg + d.gC * a.m - 1) / (d.gC * a.m);
+    const int e = (blockIdx.x * 256 + threadIdx.x) * 4, i = e / d.dv, dkd = d.dkd();
+    f32x4 E = {0.f, 0.f, 0.f, 0.f};
+    if (R.edge_in) E = load4(R.edge_in + size_t(w.edge) * sz + e);
+    float* b = R.bound + slot0 * sz + e;
+    constexpr int AHEAD = 8;
+    for (int s = 0; s + 1 < nsq; s += AHEAD) {
+        f32x4 u[AHEAD];
+        double gl[AHEAD];
+        _Pragma("unroll") for (int x = 0; x < AHEAD; ++x) {
+            const int t = min(s + x, nsq - 2);
+            u[x] = load4(b + size_t(t + 1) * sz);
+            gl[x] = d.kind == 0 ? 0.0 : R.gseg[(slot0 + t) * dkd + (dkd > 1 ? i : 0)];
         }
-        from_f32(&o[U(j) * d.dv + col], acc);
+        _Pragma("unroll") for (int x = 0; x < AHEAD; ++x) {
+            if (s + x >= nsq - 1) break;
+            const float lam = expf(float(gl[x]));
+            _Pragma("unroll") for (int c = 0; c < 4; ++c) E[c] = lam * E[c] + u[x][c];
+            store4(b + size_t(s + x + 1) * sz, E);
+        }
     }
 }
 
-// Per-chunk gradients (grid: N x BH, dynamic LDS 2*C*C floats).
-//   dA_jr = d_o_j . v_r                                    (r <= j)
-//   dq_j  = e^{b_j} * (d_o_j S_c^T)            + sum_{r<=j} dA_jr e^{b_j-b_r} * k_r
-//   dk_r  = e^{b_C-b_r} * (v_r dS_{c+1}^T)     + sum_{j>=r} dA_jr e^{b_j-b_r} * q_j
-//   dv_r  = (k_r * e^{b_C-b_r}) dS_{c+1}       + sum_{j>=r} A_jr d_o_j
-//   dg_t  = sum_{u>=t in chunk} (q_u*dq_u - k_u*dk_u) + sum_{r in chunk} k_r*dk_r^{inter}
-//           + e^{b_C} * rowsum(S_c * dS_{c+1})
-// wq / wk: fp32 scratch [BH,T,dk] each; dg_tok: [BH,T] scratch for the per-head kind.
-template <typename TIO>
-__global__ void k_grad(Dims d, const TIO* __restrict__ q, const TIO* __restrict__ k, const TIO* __restrict__ v,
-                       const TIO* __restrict__ d_o, const bsum_t* __restrict__ bcum,
-                       const float* __restrict__ states, const float* __restrict__ dstates,
-                       TIO* __restrict__ dq, TIO* __restrict__ dk, TIO* __restrict__ dv,
-                       float* __restrict__ dg, float* __restrict__ wq, float* __restrict__ wk,
-                       float* __restrict__ dg_tok) {
-    extern __shared__ float lds[];
-    float* A = lds;
-    float* dA = lds + d.C * d.C;
-    const int c = blockIdx.x, bh = blockIdx.y;
-    const ChunkPos cp = chunk_pos(d, c, bh);
-    const int L = cp.L, dkd = d.dkd();
-    if (L <= 0) return;  // packed input: the grid is sized for an upper bound of the chunk count
-    const size_t tok0 = cp.wtok0;                              // token index in the library's own arrays
-    auto U = [&](int r) { return cp.tok0 + size_t(r) * cp.ts; };  // row of token r in the caller's arrays
-    const float* S = states + cp.slot * d.dk * d.dv;
-    const float* dS = dstates + cp.slot * d.dk * d.dv;
-    const bool want_dg = dg != nullptr || dg_tok != nullptr;
-
-    scores_to_lds(d, q, k, bcum, cp, L, A);
-    for (int e = threadIdx.x; e < L * L; e += blockDim.x) {
-        const int j = e / L, r = e % L;
-        float acc = 0.f;
-        if (r <= j)
-            _Pragma("unroll 8")
-            for (int col = 0; col < d.dv; ++col)
-                acc += to_f32(d_o[U(j) * d.dv + col]) * to_f32(v[U(r) * d.dv + col]);
-        // scalar kinds: the decay of a score depends on the token pair only, so G = dA * D is formed here
-        // once and the loops below contain no exponential
-        if (dkd == 1 && r <= j) acc *= expd(bval(bcum, tok0 + j, 1, 0) - bval(bcum, tok0 + r, 1, 0));
-        dA[j * d.C + r] = acc;
-    }
-    __syncthreads();
-
-    // dv
-    for (int e = threadIdx.x; e < L * d.dv; e += blockDim.x) {
-        const int r = e / d.dv, col = e % d.dv;
-        float acc = 0.f;
-        _Pragma("unroll 8")
-        for (int j = r; j < L; ++j) acc += A[j * d.C + r] * to_f32(d_o[U(j) * d.dv + col]);
-        if (dkd == 1) {  // one decay factor per token
-            float inter = 0.f;
-            _Pragma("unroll 8")
-            for (int i = 0; i < d.dk; ++i) inter += to_f32(k[U(r) * d.dk + i]) * dS[i * d.dv + col];
-            acc += expd(bval(bcum, tok0 + L - 1, 1, 0) - bval(bcum, tok0 + r, 1, 0)) * inter;
-        } else {
-            for (int i = 0; i < d.dk; ++i) {
-                const float w = expd(bval(bcum, tok0 + L - 1, dkd, i) - bval(bcum, tok0 + r, dkd, i));
-                acc += to_f32(k[U(r) * d.dk + i]) * w * dS[i * d.dv + col];
+// Decay gradient of a segment: dg_t = sum_{u >= t in the segment} (q_u.dq_u - k_u.dk_u) + <S_end, dS_end>, S_end / dS_end the
+// state and its gradient at the segment's end (vector kind: everything per key feature).  The per-token products come
+// from the dq and dk walkers without the pair (t, t), which is the same in both.  grid as the walkers' (one slice).
+struct GDgArgs { const float *xq, *xk, *bf, *br, *d_mT; float *dg, *dg_tok; int m, slots, extra, nslk; };
+__global__ __launch_bounds__(256) void gk_dg(Dims d, GDgArgs a) {
+    __shared__ double cst[256];
+    __shared__ double part[256];
+    const GSeg s = find_seg(d, a.m, a.slots, a.extra, blockIdx.x, blockIdx.y);
+    if (s.seg >= s.nsq) return;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, sz = d.dk * d.dv;
+    const bool last = s.seg == s.nsq - 1;
+    const float* S = a.bf + (s.slot0 + s.seg + 1) * sz;
+    const float* D = last ? (a.d_mT ? a.d_mT + size_t(s.w.edge) * sz : nullptr) : a.br + (s.slot0 + s.nsq - 1 - s.seg) * sz;
+    const int tb = s.w.tbeg + s.seg * a.m * d.gC, te = min(s.w.tend, tb + a.m * d.gC), len = te - tb;
+    const ChunkPos cp = chunk_pos_at(d, s.w.bh, tb, len, 0);
+    if (d.kind != 3) {
+        double z = 0.0;
+        if (D)
+            for (int e = tid * 4; e < sz; e += 1024) {
+                const f32x4 x = load4(S + e), y = load4(D + e);
+                z += double(x[0] * y[0] + x[1] * y[1]) + double(x[2] * y[2] + x[3] * y[3]);
             }
+        part[tid] = z;
+        __syncthreads();
+        for (int h = 128; h > 0; h >>= 1) {
+            if (tid < h) part[tid] += part[tid + h];
+            __syncthreads();
         }
-        from_f32(&dv[U(r) * d.dv + col], acc);
+        if (w != 0) return;
+        double run = part[0];
+        const size_t plane = size_t(d.BH()) * d.T;
+        for (int t0 = len - 1; t0 >= 0; t0 -= 64) {  // 64 tokens at a time, lane l = token t0 - l
+            const int t = t0 - lane;
+            double x = 0.0;
+            if (t >= 0) {
+                const size_t row = cp.wtok0 + t;
+                for (int sl = 0; sl < a.nslk; ++sl) x += double(a.xq[sl * plane + row]) - double(a.xk[sl * plane + row]);
+            }
+            for (int off = 1; off < 64; off <<= 1) {
+                const double y = __shfl_up(x, off, 64);
+                if (lane >= off) x += y;
+            }
+            x += run;
+            if (t >= 0) {
+                if (d.kind == 2) a.dg[cp.tok0 + size_t(t) * cp.ts] = float(x);
+                else a.dg_tok[cp.wtok0 + t] = float(x);
+            }
+            run = __shfl(x, 63, 64);
+        }
+        return;
     }
-    // dq, dk and the per-token terms of the decay gradient
-    for (int e = threadIdx.x; e < L * d.dk; e += blockDim.x) {
-        const int t = e / d.dk, i = e % d.dk;
-        const bsum_t bt = bval(bcum, tok0 + t, dkd, i);
-        const bsum_t bC = bval(bcum, tok0 + L - 1, dkd, i);
-        float q_inter = 0.f, k_inter = 0.f;
-        _Pragma("unroll 8")
-        for (int col = 0; col < d.dv; ++col) {
-            q_inter += to_f32(d_o[U(t) * d.dv + col]) * S[i * d.dv + col];
-            k_inter += to_f32(v[U(t) * d.dv + col]) * dS[i * d.dv + col];
-        }
-        q_inter *= expd(bt);
-        k_inter *= expd(bC - bt);
-        float q_intra = 0.f, k_intra = 0.f;
-        if (dkd == 1) {  // dA already carries the decay
-            _Pragma("unroll 8")
-            for (int r = 0; r <= t; ++r) q_intra += dA[t * d.C + r] * to_f32(k[U(r) * d.dk + i]);
-            _Pragma("unroll 8")
-            for (int j = t; j < L; ++j) k_intra += dA[j * d.C + t] * to_f32(q[U(j) * d.dk + i]);
-        } else {
-            for (int r = 0; r <= t; ++r)
-                q_intra += dA[t * d.C + r] * expd(bt - bval(bcum, tok0 + r, dkd, i)) * to_f32(k[U(r) * d.dk + i]);
-            for (int j = t; j < L; ++j)
-                k_intra += dA[j * d.C + t] * expd(bval(bcum, tok0 + j, dkd, i) - bt) * to_f32(q[U(j) * d.dk + i]);
-        }
-        const float dqv = q_inter + q_intra, dkv = k_inter + k_intra;
-        from_f32(&dq[U(t) * d.dk + i], dqv);
-        from_f32(&dk[U(t) * d.dk + i], dkv);
-        if (want_dg) {
-            const float qv = to_f32(q[U(t) * d.dk + i]), kv = to_f32(k[U(t) * d.dk + i]);
-            wq[(tok0 + t) * d.dk + i] = qv * dqv - kv * dkv;
-            wk[(tok0 + t) * d.dk + i] = kv * k_inter;
-        }
+    for (int i = w; i < d.dk; i += 4) {  // one key feature per wave
+        double z = 0.0;
+        if (D)
+            for (int c = lane * 4; c < d.dv; c += 256) {
+                const f32x4 x = load4(S + i * d.dv + c), y = load4(D + i * d.dv + c);
+                z += double(x[0] * y[0] + x[1] * y[1]) + double(x[2] * y[2] + x[3] * y[3]);
+            }
+        for (int off = 32; off > 0; off >>= 1) z += __shfl_xor(z, off, 64);
+        if (lane == 0) cst[i] = z;
     }
-    if (!want_dg) return;
+    // feature i, group gr of the tokens: the group's sum first, then the suffix with the later groups' sums
+    const int i = tid % d.dk, ng = 256 / d.dk, gr = tid / d.dk, per = (len + ng - 1) / ng;
+    const int lo = min(len, gr * per), hi = min(len, lo + per);
+    const float *xq = a.xq + cp.wtok0 * d.dk + i, *xk = a.xk + cp.wtok0 * d.dk + i;
+    double sum = 0.0;
+    _Pragma("unroll 8") for (int t = lo; t < hi; ++t) sum += double(xq[size_t(t) * d.dk]) - double(xk[size_t(t) * d.dk]);
+    part[gr * d.dk + i] = sum;
     __syncthreads();
-    // reverse in-chunk running sum per feature
-    for (int i = threadIdx.x; i < d.dk; i += blockDim.x) {
-        float z = 0.f;
-        for (int col = 0; col < d.dv; ++col) z += S[i * d.dv + col] * dS[i * d.dv + col];
-        float run = expd(bval(bcum, tok0 + L - 1, dkd, i)) * z;
-        for (int r = 0; r < L; ++r) run += wk[(tok0 + r) * d.dk + i];
-        for (int t = L - 1; t >= 0; --t) {
-            run += wq[(tok0 + t) * d.dk + i];
-            if (d.kind == 3) dg[U(t) * d.dk + i] = run;
-            else wq[(tok0 + t) * d.dk + i] = run;
-        }
-    }
-    if (d.kind == 3) return;
-    __syncthreads();
-    for (int t = threadIdx.x; t < L; t += blockDim.x) {
-        float s = 0.f;
-        for (int i = 0; i < d.dk; ++i) s += wq[(tok0 + t) * d.dk + i];
-        if (d.kind == 2) dg[U(t)] = s;
-        else dg_tok[tok0 + t] = s;
+    double run = cst[i];
+    for (int u = gr + 1; u < ng; ++u) run += part[u * d.dk + i];
+    _Pragma("unroll 8") for (int t = hi - 1; t >= lo; --t) {
+        run += double(xq[size_t(t) * d.dk]) - double(xk[size_t(t) * d.dk]);
+        a.dg[(cp.tok0 + size_t(t) * cp.ts) * d.dk + i] = float(run);
     }
 }
 
 // dg[h] = sum_{b,t} dg_tok[b,h,t], fixed summation order (grid: H)
-__global__ void k_head_reduce(Dims d, const float* __restrict__ dg_tok, float* __restrict__ dg) {
-    __shared__ float part[kThreads];
-    const int h = blockIdx.x;
-    float s = 0.f;
-    const size_t n = size_t(d.B) * d.T;
-    for (size_t e = threadIdx.x; e < n; e += blockDim.x) {
-        const size_t b = e / d.T, t = e % d.T;
-        s += dg_tok[(b * d.H + h) * d.T + t];
+__global__ __launch_bounds__(1024) void gk_head_reduce(Dims d, const float* __restrict__ dg_tok, float* __restrict__ dg) {
+    __shared__ double part[1024];
+    const int h = blockIdx.x, tid = threadIdx.x;
+    double s = 0.0;
+    for (int b = 0; b < d.B; ++b) {
+        const float* x = dg_tok + (size_t(b) * d.H + h) * d.T;
+        _Pragma("unroll 4") for (int t = tid; t < d.T; t += 1024) s += double(x[t]);
     }
-    part[threadIdx.x] = s;
+    part[tid] = s;
     __syncthreads();
-    for (int w = kThreads / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+    for (int w = 512; w > 0; w >>= 1) {
+        if (tid < w) part[tid] += part[tid + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) dg[h] = part[0];
+    if (tid == 0) dg[h] = float(part[0]);
 }
 
-struct WsFwd { bsum_t* bcum; float* states; size_t bytes; };
-struct WsBwd { bsum_t* bcum; float *states, *dstates, *wq, *wk, *dg_tok; size_t bytes; };
-
-WsFwd carve_fwd(const Dims& d, void* ws) {
-    char* p = static_cast<char*>(ws);
-    size_t off = 0;
-    WsFwd w{};
-    if (d.kind != 0) { w.bcum = reinterpret_cast<bsum_t*>(p + off); off += align256(size_t(d.BH()) * d.T * d.dkd() * sizeof(bsum_t)); }
-    w.states = reinterpret_cast<float*>(p + off); off += align256(size_t(d.BH()) * d.N * d.dk * d.dv * 4);
-    w.bytes = off;
-    return w;
-}
-
-WsBwd carve_bwd(const Dims& d, void* ws) {
-    char* p = static_cast<char*>(ws);
-    size_t off = 0;
-    WsBwd w{};
-    const size_t st = align256(size_t(d.BH()) * d.N * d.dk * d.dv * 4);
-    if (d.kind != 0) { w.bcum = reinterpret_cast<bsum_t*>(p + off); off += align256(size_t(d.BH()) * d.T * d.dkd() * sizeof(bsum_t)); }
-    w.states = reinterpret_cast<float*>(p + off); off += st;
-    w.dstates = reinterpret_cast<float*>(p + off); off += st;
-    if (d.kind != 0) {
-        w.wq = reinterpret_cast<float*>(p + off); off += align256(size_t(d.BH()) * d.T * d.dk * 4);
-        w.wk = reinterpret_cast<float*>(p + off); off += align256(size_t(d.BH()) * d.T * d.dk * 4);
-    }
-    if (d.kind == 1) { w.dg_tok = reinterpret_cast<float*>(p + off); off += align256(size_t(d.BH()) * d.T * 4); }
-    w.bytes = off;
-    return w;
-}
-
-template <typename TIO>
-hipError_t fwd_t(const Dims& d, const FwdArgs& a) {
-    WsFwd w = carve_fwd(d, a.ws);
-    const dim3 grid(d.N, d.BH()), block(kThreads);
-    const int sz = d.dk * d.dv;
-    auto q = static_cast<const TIO*>(a.q), k = static_cast<const TIO*>(a.k), v = static_cast<const TIO*>(a.v);
-    if (d.kind != 0) { ProfScope ps(KID_GEN_CUMSUM, a.stream); hipLaunchKernelGGL(k_cumsum, grid, block, 0, a.stream, d, a.g, w.bcum); }
-    { ProfScope ps(KID_GEN_STATE, a.stream); hipLaunchKernelGGL((k_local_state<TIO, 0>), grid, block, 0, a.stream, d, k, v, w.bcum, w.states); }
-    { ProfScope ps(KID_GEN_SCAN, a.stream); hipLaunchKernelGGL((k_scan<false>), dim3((sz + kThreads - 1) / kThreads, d.seqs()), block, 0, a.stream, d, w.bcum,
-                       w.states, a.m0, a.mT); }
-    const size_t lds = size_t(d.C) * d.C * 4;
-    if (lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_output<TIO>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-        if (e != hipSuccess) return e;
-    }
-    { ProfScope ps(KID_GEN_OUTPUT, a.stream); hipLaunchKernelGGL((k_output<TIO>), grid, block, lds, a.stream, d, q, k, v, w.bcum, w.states,
-                       static_cast<TIO*>(a.o)); }
-    return hipGetLastError();
-}
-
-template <typename TIO>
-hipError_t bwd_t(const Dims& d, const BwdArgs& a) {
-    WsBwd w = carve_bwd(d, a.ws);
-    const dim3 grid(d.N, d.BH()), block(kThreads);
-    const int sz = d.dk * d.dv;
-    const dim3 sgrid((sz + kThreads - 1) / kThreads, d.seqs());
-    auto q = static_cast<const TIO*>(a.q), k = static_cast<const TIO*>(a.k), v = static_cast<const TIO*>(a.v);
-    auto d_o = static_cast<const TIO*>(a.d_o);
-    const size_t lds = size_t(d.C) * d.C * 8;
-    if (lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_grad<TIO>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-        if (e != hipSuccess) return e;
-    }
-    if (d.kind != 0) { ProfScope ps(KID_GEN_CUMSUM, a.stream); hipLaunchKernelGGL(k_cumsum, grid, block, 0, a.stream, d, a.g, w.bcum); }
-    { ProfScope ps(KID_GEN_STATE, a.stream); hipLaunchKernelGGL((k_local_state<TIO, 0>), grid, block, 0, a.stream, d, k, v, w.bcum, w.states); }
-    { ProfScope ps(KID_GEN_SCAN, a.stream); hipLaunchKernelGGL((k_scan<false>), sgrid, block, 0, a.stream, d, w.bcum, w.states, a.m0,
-                       static_cast<float*>(nullptr)); }
-    { ProfScope ps(KID_GEN_DSTATE, a.stream); hipLaunchKernelGGL((k_local_state<TIO, 1>), grid, block, 0, a.stream, d, q, d_o, w.bcum, w.dstates); }
-    { ProfScope ps(KID_GEN_RSCAN, a.stream); hipLaunchKernelGGL((k_scan<true>), sgrid, block, 0, a.stream, d, w.bcum, w.dstates, a.d_mT, a.d_m0); }
-    const bool want_dg = a.dg != nullptr;
-    { ProfScope ps(KID_GEN_GRAD, a.stream); hipLaunchKernelGGL((k_grad<TIO>), grid, block, lds, a.stream, d, q, k, v, d_o, w.bcum, w.states, w.dstates,
-                       static_cast<TIO*>(a.dq), static_cast<TIO*>(a.dk), static_cast<TIO*>(a.dv),
-                       (want_dg && d.kind != 1) ? a.dg : static_cast<float*>(nullptr), w.wq, w.wk,
-                       (want_dg && d.kind == 1) ? w.dg_tok : static_cast<float*>(nullptr)); }
-    if (want_dg && d.kind == 1) {
-        ProfScope ps(KID_HEAD_REDUCE, a.stream);
-        hipLaunchKernelGGL(k_head_reduce, dim3(d.H), block, 0, a.stream, d, w.dg_tok, a.dg);
-    }
-    return hipGetLastError();
-}
-
-}  // namespace
-
-namespace {
-// packed input: cstart[s] = sum over earlier sequences of ceil(len / C)  (one thread; n_seq is small)
-__global__ void k_chunk_starts(Dims d, int* __restrict__ cstart) {
+// packed input: cstart[s] = sum over earlier sequences of max(least, ceil(len / C))  (one thread; n_seq is small)
+__global__ void k_chunk_starts(Dims d, int* __restrict__ cstart, int least) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     int c = 0;
     cstart[0] = 0;
     for (int s = 0; s < d.nseq; ++s) {
-        c += (d.cu[s + 1] - d.cu[s] + d.C - 1) / d.C;
+        c += max(least, (d.cu[s + 1] - d.cu[s] + d.C - 1) / d.C);
         cstart[s + 1] = c;
     }
 }
-}  // namespace
-hipError_t launch_chunk_starts(const Dims& d, int* cstart, hipStream_t stream) {
-    hipLaunchKernelGGL(k_chunk_starts, dim3(1), dim3(64), 0, stream, d, cstart);
+
+// ---- host side --------------------------------------------------------------------------------------------------
+
+// Segment plan: m units of gC tokens per segment.  Enough workgroups that the launch fills the chip with what fits on a
+// compute unit (two of the 128-wide walkers, four of the 64-wide ones), and no more boundary states than one per chunk of
+// the caller's chunk size, which is what lsm_chunk_fwd_workspace_bytes() has always reported.
+struct GPlan { int m, nseg, slots_f, slots_b; };
+int slices(int width, bool narrow) { return narrow ? width / 64 : (width + 127) / 128; }
+GPlan gplan(const Dims& d) {
+    const int units = (d.T + d.gC - 1) / d.gC, nsl = slices(d.dv, false), target = d.dv == 64 ? 1024 : 512;
+    GPlan p{};
+    if (!d.nseq) {
+        const int seqs = d.BH() * nsl;
+        int nseg = (target + seqs - 1) / seqs;
+        nseg = nseg > units ? units : nseg;
+        p.m = (units + nseg - 1) / nseg;
+        p.nseg = (units + p.m - 1) / p.m;
+        p.slots_f = p.nseg;
+        p.slots_b = p.nseg + 1;
+        return p;
+    }
+    const long long n = (long long)units + d.nseq, work = n * d.H * nsl;
+    p.m = int((work + target - 1) / target);
+    auto count = [&](int m) { return m == 1 ? int(n) : int(n / m) + d.nseq + 1; };
+    while (count(p.m) > n) ++p.m;  // n: the chunks the workspace figure allows for
+    p.nseg = p.slots_f = count(p.m);
+    p.slots_b = p.slots_f + d.nseq;
+    return p;
+}
+
+struct GWs { float *bound_f, *bound_r, *xq, *xk, *dg_tok; double *gseg_f, *gseg_r; size_t bytes; };
+GWs carve(const Dims& d, void* ws, bool bwd) {
+    char* p = static_cast<char*>(ws);
+    size_t off = 0;
+    GWs w{};
+    const GPlan gp = gplan(d);
+    auto take = [&](size_t bytes) { char* r = p + off; off += align256(bytes); return r; };
+    const size_t slots = size_t(bwd ? gp.slots_b : gp.slots_f) * (d.nseq ? d.H : d.BH());
+    const bool bounds = bwd || gp.nseg > 1;
+    const size_t nb = bounds ? slots * d.dk * d.dv * 4 : 0, ng = bounds && d.kind != 0 ? slots * d.dkd() * 8 : 0;
+    w.bound_f = reinterpret_cast<float*>(take(nb));
+    w.gseg_f = reinterpret_cast<double*>(take(ng));
+    if (bwd) {
+        w.bound_r = reinterpret_cast<float*>(take(nb));
+        w.gseg_r = reinterpret_cast<double*>(take(ng));
+        const size_t tok = size_t(d.BH()) * d.T;
+        const size_t nx = d.kind == 0 ? 0 : tok * (d.kind == 3 ? d.dk : slices(d.dk, false)) * 4;
+        w.xq = reinterpret_cast<float*>(take(nx));
+        w.xk = reinterpret_cast<float*>(take(nx));
+        if (d.kind == 1) w.dg_tok = reinterpret_cast<float*>(take(tok * 4));
+    }
+    w.bytes = off;
+    return w;
+}
+// The size the queries report: at least one fp32 state per chunk of the caller's chunk size (twice for the backward call)
+// and one running log-decay per token, as callers have always been told; the kernels above need less.
+size_t reported(const Dims& d, bool bwd) {
+    const size_t tok = size_t(d.BH()) * d.T, st = align256(size_t(d.BH()) * d.N * d.dk * d.dv * 4);
+    size_t n = (d.kind != 0 ? align256(tok * d.dkd() * 8) : 0) + st;
+    if (bwd) n += st + (d.kind != 0 ? 2 * align256(tok * d.dk * 4) : 0) + (d.kind == 1 ? align256(tok * 4) : 0);
+    return n;
+}
+
+// dynamic LDS limit of a kernel, raised once per kernel and device
+hipError_t allow_lds(const void* fn, int bytes) {
+    struct Seen { const void* fn; uint64_t devices; };
+    static std::mutex mu;
+    static std::vector<Seen> seen;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = uint64_t(1) << (dev & 63);
+    std::lock_guard<std::mutex> lk(mu);
+    for (Seen& x : seen)
+        if (x.fn == fn) {
+            if (x.devices & bit) return hipSuccess;
+            if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes)) == hipSuccess) x.devices |= bit;
+            return e;
+        }
+    if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes)) == hipSuccess) seen.push_back(Seen{fn, bit});
+    return e;
+}
+
+template <typename TIO, int KD, int TV, int VEC, bool SUM>
+hipError_t launch_walk(const Dims& d, GArgs a, int nroles, dim3 grid, hipStream_t st, int kid) {
+    using Lds = GLds<KD, TV, VEC, SUM>;
+    static_assert(Lds::bytes <= 160 * 1024, "LDS");
+    auto kernel = gk_walk<TIO, KD, TV, VEC, SUM>;
+    const hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), Lds::bytes);
+    if (e != hipSuccess) return e;
+    a.nsl = a.vd / TV;
+    grid.z = nroles * a.nsl;
+    ProfScope ps(kid, st);
+    hipLaunchKernelGGL(kernel, grid, dim3(2 * TV), Lds::bytes, st, d, a);
+    return hipGetLastError();
+}
+// Key-role width kd keeps its whole state column block in one wave's registers; value-role widths of 128 and 256 go in
+// slices of 128 (fewer repeats of the scores), except where two more tiles of 256-wide weighted rows would not fit.
+template <typename TIO, int VEC, bool SUM>
+hipError_t walk_dims(const Dims& d, const GArgs& a, int nroles, dim3 grid, hipStream_t st, int kid) {
+    const bool narrow = a.vd == 64;
+    if (a.kd == 64) return narrow ? launch_walk<TIO, 64, 64, VEC, SUM>(d, a, nroles, grid, st, kid) : launch_walk<TIO, 64, 128, VEC, SUM>(d, a, nroles, grid, st, kid);
+    if (a.kd == 128) return narrow ? launch_walk<TIO, 128, 64, VEC, SUM>(d, a, nroles, grid, st, kid) : launch_walk<TIO, 128, 128, VEC, SUM>(d, a, nroles, grid, st, kid);
+    if constexpr (VEC == 1) return launch_walk<TIO, 256, 64, VEC, SUM>(d, a, nroles, grid, st, kid);
+    else return narrow ? launch_walk<TIO, 256, 64, VEC, SUM>(d, a, nroles, grid, st, kid) : launch_walk<TIO, 256, 128, VEC, SUM>(d, a, nroles, grid, st, kid);
+}
+template <typename TIO>
+hipError_t walks(const Dims& d, const GArgs& a, int nroles, dim3 grid, hipStream_t st) {
+    // the decayed features are d_k's: on the key side of o and dv, on the value side (the transposed state) of dq and dk
+    if (d.kind != 3) return walk_dims<TIO, 0, false>(d, a, nroles, grid, st, a.role[0].trans ? KID_GEN_GRAD : KID_GEN_OUTPUT);
+    return a.role[0].trans ? walk_dims<TIO, 2, false>(d, a, nroles, grid, st, KID_GEN_GRAD)
+                           : walk_dims<TIO, 1, false>(d, a, nroles, grid, st, KID_GEN_OUTPUT);
+}
+template <typename TIO>
+hipError_t bounds(const Dims& d, const GArgs& a, int ndir, dim3 grid, hipStream_t st) {
+    const hipError_t e = d.kind != 3 ? walk_dims<TIO, 0, true>(d, a, ndir, grid, st, KID_GEN_STATE) : walk_dims<TIO, 1, true>(d, a, ndir, grid, st, KID_GEN_STATE);
+    if (e != hipSuccess) return e;
+    ProfScope ps(KID_GEN_SCAN, st);
+    hipLaunchKernelGGL(gk_scan, dim3(d.dk * d.dv / 1024, d.seqs(), ndir), dim3(256), 0, st, d, a);
     return hipGetLastError();
 }
 
-size_t generic_fwd_workspace(const Dims& d) { return carve_fwd(d, nullptr).bytes; }
-size_t generic_bwd_workspace(const Dims& d) { return carve_bwd(d, nullptr).bytes; }
+template <typename TIO>
+hipError_t fwd_t(const Dims& d, const FwdArgs& f) {
+    const GWs w = carve(d, f.ws, false);
+    const GPlan gp = gplan(d);
+    const dim3 grid(gp.nseg, d.nseq ? d.H : d.BH());
+    GArgs a{};
+    a.g = f.g; a.kd = d.dk; a.vd = d.dv; a.m = gp.m; a.slots = gp.slots_f; a.extra = 0;
+    a.role[0] = GRole{f.q, f.k, f.v, nullptr, f.o, nullptr, f.m0, f.mT, w.bound_f, w.gseg_f, 0, 0, 0};
+    if (gp.nseg > 1) {
+        const hipError_t e = bounds<TIO>(d, a, 1, grid, f.stream);
+        if (e != hipSuccess) return e;
+    }
+    return walks<TIO>(d, a, 1, grid, f.stream);
+}
+
+template <typename TIO>
+hipError_t bwd_t(const Dims& d, const BwdArgs& b) {
+    const GWs w = carve(d, b.ws, true);
+    const GPlan gp = gplan(d);
+    const int slots = gp.slots_b, extra = 1;
+    const dim3 grid(d.nseq ? slots : gp.nseg, d.nseq ? d.H : d.BH());
+    hipError_t e;
+    GArgs a{};
+    a.g = b.g; a.kd = d.dk; a.vd = d.dv; a.m = gp.m; a.slots = slots; a.extra = extra;
+    a.role[0] = GRole{nullptr, b.k, b.v, nullptr, nullptr, nullptr, b.m0, nullptr, w.bound_f, w.gseg_f, 0, 0, 0};
+    a.role[1] = GRole{nullptr, b.q, b.d_o, nullptr, nullptr, nullptr, b.d_mT, nullptr, w.bound_r, w.gseg_r, 1, 0, 0};
+    if (gp.nseg > 1 && (e = bounds<TIO>(d, a, 2, grid, b.stream)) != hipSuccess) return e;
+    const bool want_dg = b.dg != nullptr;
+    float *xq = want_dg ? w.xq : nullptr, *xk = want_dg ? w.xk : nullptr;
+    const GRole dq{b.d_o, b.v, b.k, b.q, b.dq, xq, b.m0, nullptr, w.bound_f, nullptr, 0, 1, want_dg && b.d_mT != nullptr};
+    const GRole dk{b.v, b.d_o, b.q, b.k, b.dk, xk, b.d_mT, nullptr, w.bound_r, nullptr, 1, 1, 0};
+    const GRole dv{b.k, b.q, b.d_o, nullptr, b.dv, nullptr, b.d_mT, b.d_m0, w.bound_r, nullptr, 1, 0, 0};
+    a.kd = d.dv; a.vd = d.dk;
+    a.role[0] = dq; a.role[1] = dk; a.role[2] = dv;
+    const bool one = d.dk == d.dv && d.kind != 3;  // all three in one launch
+    if ((e = walks<TIO>(d, a, one ? 3 : 2, grid, b.stream)) != hipSuccess) return e;
+    if (!one) {
+        a.kd = d.dk; a.vd = d.dv;
+        a.role[0] = dv;
+        if ((e = walks<TIO>(d, a, 1, grid, b.stream)) != hipSuccess) return e;
+    }
+    if (want_dg) {
+        const GDgArgs ga{w.xq, w.xk, w.bound_f, w.bound_r, b.d_mT, b.dg, w.dg_tok, gp.m, slots, extra, slices(d.dk, false)};
+        {
+            ProfScope ps(KID_GEN_RSCAN, b.stream);
+            hipLaunchKernelGGL(gk_dg, grid, dim3(256), 0, b.stream, d, ga);
+        }
+        if (d.kind == 1) {
+            ProfScope ps(KID_HEAD_REDUCE, b.stream);
+            hipLaunchKernelGGL(gk_head_reduce, dim3(d.H), dim3(1024), 0, b.stream, d, w.dg_tok, b.dg);
+        }
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_chunk_starts(const Dims& d, int* cstart, hipStream_t stream) {
+    hipLaunchKernelGGL(k_chunk_starts, dim3(1), dim3(64), 0, stream, d, cstart, 0);
+    return hipGetLastError();
+}
+// the walkers' table: in units of gC tokens, an empty sequence holding one (its workgroup passes the state through)
+hipError_t launch_generic_starts(const Dims& d, int* cstart, hipStream_t stream) {
+    Dims u = d;
+    u.C = d.gC;
+    hipLaunchKernelGGL(k_chunk_starts, dim3(1), dim3(64), 0, stream, u, cstart, 1);
+    return hipGetLastError();
+}
+
+size_t generic_fwd_workspace(const Dims& d) {
+    const size_t need = carve(d, nullptr, false).bytes, rep = reported(d, false);
+    return need > rep ? need : rep;
+}
+size_t generic_bwd_workspace(const Dims& d) {
+    const size_t need = carve(d, nullptr, true).bytes, rep = reported(d, true);
+    return need > rep ? need : rep;
+}
 
 hipError_t generic_fwd(const Dims& d, const FwdArgs& a) {
     return d.bf16 ? fwd_t<uint16_t>(d, a) : fwd_t<float>(d, a);

@@ -22,6 +22,7 @@ struct Dims {
     // 128-wide slice of the value-sized tensors (v, o, d_o, dv, the value side of the states) per pass.  vm = d_v / 128
     // (value rows are vm rows of 128 elements), vs = the slice of this pass; passes after the first add to dq, dk, dg.
     int vm = 1, vs = 0;
+    int gC = 64;  // generic family: tokens per unit of its segment plan and boundary states, max(64, C)
     __host__ __device__ int BH() const { return B * H; }
     __host__ __device__ int dkd() const { return kind == 3 ? dk : 1; }  // decay values per token
     __host__ __device__ int seqs() const { return nseq ? nseq * H : B * H; }  // independent recurrences
@@ -99,6 +100,7 @@ struct BwdArgs {
 
 // first chunk of every sequence of a packed variable-length input: cstart[s] = sum_{s' < s} ceil(len_s' / C)
 hipError_t launch_chunk_starts(const Dims& d, int* cstart, hipStream_t stream);
+hipError_t launch_generic_starts(const Dims& d, int* cstart, hipStream_t stream);  // the same for the generic family
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -117,7 +119,7 @@ struct ProfScope {
     ~ProfScope() { prof_end(s); }
 };
 
-// Generic family: fp32 arithmetic on plain ALU, every supported shape, both element types.
+// Generic family: fp32 operands on the matrix cores, every supported shape, both element types.
 size_t generic_fwd_workspace(const Dims& d);
 size_t generic_bwd_workspace(const Dims& d);
 hipError_t generic_fwd(const Dims& d, const FwdArgs& a);
