@@ -91,11 +91,14 @@ __device__ __forceinline__ GSeg find_seg(const Dims& d, int m, int slots, int ex
         r.seg = x;
         r.slot0 = size_t(y) * slots;
     } else {
-        int lo = 0, hi = d.nseq;  // last s whose base is <= x
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (seg_base(d, m, extra, mid) <= x) lo = mid; else hi = mid;
+        int lo = -1;  // last s whose base is <= x, 64 sequences at a time (one per lane)
+        for (int s0 = 0; s0 < d.nseq; s0 += 64) {
+            const int t = s0 + int(threadIdx.x & 63);
+            const uint64_t le = __ballot(t < d.nseq && seg_base(d, m, extra, min(t, d.nseq)) <= x);
+            lo += __popcll(le);
+            if (le != ~uint64_t(0)) break;
         }
+        lo = __builtin_amdgcn_readfirstlane(lo);
         r.w = SeqWalk{y, lo * d.H + y, 0, 0, d.cu[lo], d.cu[lo + 1]};
         r.seg = x - seg_base(d, m, extra, lo);
         r.slot0 = size_t(y) * slots + seg_base(d, m, extra, lo);

@@ -70,6 +70,34 @@ __device__ __forceinline__ SeqWalk seq_walk(const Dims& d, int q) {
     const int s = q / d.H;
     return SeqWalk{q % d.H, q, d.cstart[s], d.cstart[s + 1] - d.cstart[s], d.cu[s], d.cu[s + 1]};
 }
+// First boundary-state slot of recurrence `seq` whose sequence is cut into segments of m chunks (at most nseg of them).
+// Packed input: the segments of all sequences of a head are numbered one after the other, so that the slots follow the
+// tokens there are and not the longest sequence there might be.  Sequence s, of n_s chunks from chunk c_s on, takes
+// ceil(n_s / m) <= (c_s + n_s) / m + 1 - c_s / m slots; an empty one takes none (its only state is the one it starts from).
+__host__ __device__ __forceinline__ int head_slots(const Dims& d, int m) { return m == 1 ? d.N : d.N / m + d.nseq + 1; }
+__device__ __forceinline__ size_t bound_slot(const Dims& d, int seq, int m, int nseg) {
+    if (!d.cu) return size_t(seq) * nseg;
+    const int s = seq / d.H;
+    return size_t(seq % d.H) * head_slots(d, m) + (m == 1 ? d.cstart[s] : d.cstart[s] / m + s);
+}
+// Segment of a walker's workgroup.  Packed input: grid (walk_grid_x, H), the segments of a head's sequences one after the
+// other (every sequence at least one), so that workgroups with work are dealt evenly over the chip; else (nseg, B * H).
+struct SegIndex { int seq, seg; };
+__device__ __forceinline__ SegIndex seg_index(const Dims& d, int m, int x, int y) {
+    if (!d.cu) return SegIndex{y, x};
+    // last s with cstart[s] / m + s <= x: 64 sequences at a time, one per lane (a search by halves is a chain of loads)
+    int lo = -1;
+    for (int s0 = 0; s0 < d.nseq; s0 += 64) {
+        const int s = s0 + int(threadIdx.x & 63);
+        const uint64_t le = __ballot(s < d.nseq && d.cstart[min(s, d.nseq)] / m + s <= x);
+        lo += __popcll(le);
+        if (le != ~uint64_t(0)) break;
+    }
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    return SegIndex{lo * d.H + y, x - d.cstart[lo] / m - lo};
+}
+inline int walk_grid_x(const Dims& d, int m, int nseg) { return d.nseq ? d.N / m + d.nseq : nseg; }
+inline int walk_grid_y(const Dims& d) { return d.nseq ? d.H : d.B * d.H; }
 // k-th chunk of a walk
 __device__ __forceinline__ ChunkPos walk_pos(const Dims& d, const SeqWalk& w, int k) {
     const int t0 = w.tbeg + k * d.C;

@@ -120,7 +120,7 @@ struct StateArgs {
     uint16_t* states_twin;  // MODE 2 only: second copy of the head, untransposed (dS^T [v][i]), or NULL
     // scan cut into segments (seg_n > 1; grid = seg_n times the plain one): segment s walks chunks
     // [s seg_m, (s+1) seg_m) from the state in seg_bound, which holds fp32 [i][v] entry states at a finer grain
-    // (one per fine_m chunks, fine_n slots per sequence, slot f = the state the walk enters fine segment f with)
+    // (one per fine_m chunks, numbered by bound_slot(); slot f = the state the walk enters fine segment f with)
     const float* seg_bound;
     int seg_m, seg_n, fine_m, fine_n;
 };
@@ -303,11 +303,11 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
 
     // acc[4g+j] = state element (m = 32mb + 8g + 4half + j, n = 32nb + lane%32); MODE 0: m = i, else m = v
     f32x16 acc = {0};
-    if (nsegs > 1) {
+    if (nsegs > 1 && walk.n > 0) {
         // MODE 2 walks backward: it enters with the state of the last fine segment it covers
-        const int nfine = max(1, (walk.n + sa.fine_m - 1) / sa.fine_m), per = sa.seg_m / sa.fine_m;
+        const int nfine = (walk.n + sa.fine_m - 1) / sa.fine_m, per = sa.seg_m / sa.fine_m;
         const int f = MODE == 2 ? min(nfine, (seg + 1) * per) - 1 : seg * per;
-        const float* e = sa.seg_bound + (size_t(seq) * sa.fine_n + f) * D * D;
+        const float* e = sa.seg_bound + (bound_slot(d, seq, sa.fine_m, sa.fine_n) + f) * D * D;
         _Pragma("unroll") for (int r = 0; r < 16; ++r) {
             const int mm = 32 * mb + 8 * (r >> 2) + 4 * half + (r & 3), nn = 32 * nb + n;
             acc[r] = MODE == 0 ? e[mm * D + nn] : e[nn * D + mm];
@@ -668,12 +668,38 @@ Ws carve(const Dims& d, void* ws, bool bwd) {
 // unit, and one hides the other's waits), no more (each extra segment adds a share of the summary pass).  m = chunks per segment.
 constexpr int kWalkTargetWgs = 512;
 struct SegPlan { int m, nseg; };
-SegPlan seg_plan(const Dims& d) {
-    const int nmax = (d.T + C - 1) / C;  // chunks of the longest possible sequence
+SegPlan even_plan(const Dims& d) {  // seqs() sequences of up to T tokens
+    const int nmax = (d.T + C - 1) / C;
     int nseg = (kWalkTargetWgs + d.seqs() - 1) / d.seqs();
     nseg = nseg < 1 ? 1 : (nseg > nmax ? nmax : nseg);
     const int m = (nmax + nseg - 1) / nseg;
     return SegPlan{m, (nmax + m - 1) / m};
+}
+size_t even_slots(const Dims& d) {
+    const int nseg = even_plan(d).nseg;
+    return nseg > 1 ? size_t(d.seqs()) * nseg : 0;
+}
+// A packed batch holds T tokens in all, not T per sequence: its segments are a 512th of all chunks.  Measured, forward,
+// d = 128: 8 sequences of 1 to 4096 tokens, 16 heads, 0.265 ms with the 37 chunks that the longest possible sequence would
+// be cut into and 0.093 with 6 (5: 0.097, 8: 0.094, 12: 0.123); 12 sequences of 500 to 5500, 32 heads, 0.35 -> 0.24.
+// The boundary states may take more than that plan's only where that one exceeds the built-in scratch of
+// lsm_chunk_fwd_noalloc, which so accepts what it always has.
+SegPlan seg_plan(const Dims& d) {
+    if (!d.nseq) return even_plan(d);
+    const int nmax = (d.T + C - 1) / C;
+    const size_t even = even_slots(d), state = size_t(D) * D * 4, kept = size_t(8) << 20;
+    const size_t most = even * state >= kept ? (even > 2048 ? even : 2048) : even;
+    // half a segment per sequence is left over on average: the workgroups that have work are to fit the chip at once
+    const long long work = (long long)d.N * d.H, wgs = kWalkTargetWgs - d.seqs() / 2 > 128 ? kWalkTargetWgs - d.seqs() / 2 : 128;
+    int m = int((work + wgs - 1) / wgs);
+    while (m < nmax && size_t(d.H) * head_slots(d, m) > most) ++m;
+    m = m > nmax ? nmax : m;
+    return SegPlan{m, (nmax + m - 1) / m};
+}
+// boundary-state slots to allow for: what the plan needs, and no less than for sequences of equal length
+size_t bound_slots(const Dims& d, const SegPlan& sp) {
+    const size_t need = sp.nseg > 1 ? (d.nseq ? size_t(d.H) * head_slots(d, sp.m) : size_t(d.seqs()) * sp.nseg) : 0;
+    return d.nseq && even_slots(d) > need ? even_slots(d) : need;
 }
 // The reverse scan of the state gradients has four workgroups per sequence.  With fewer than one per compute
 // unit it is cut into segments as well: `per` of the walkers' segments to each of its own, entry gradients from a
@@ -703,7 +729,7 @@ WalkWs carve_walk(const Dims& d, void* ws, bool bwd) {
     WalkWs w{};
     const SegPlan sp = seg_plan(d);
     auto take = [&](size_t bytes) { float* r = reinterpret_cast<float*>(p + off); off += align256(bytes); return r; };
-    const size_t nb = sp.nseg > 1 ? size_t(d.seqs()) * sp.nseg * D * D * 4 : 0, ng = sp.nseg > 1 ? size_t(d.seqs()) * sp.nseg * 4 : 0;
+    const size_t nb = bound_slots(d, sp) * D * D * 4, ng = bound_slots(d, sp) * 4;
     w.bound_f = take(nb);
     w.gseg_f = take(ng);
     if (bwd) {
@@ -842,7 +868,7 @@ hipError_t walk_bounds(const Dims& d, hipStream_t st, const SegPlan& sp, const u
     WalkArgs a{};
     a.xk = xk; a.xv = xv; a.g = g; a.bound = bound; a.gseg = gseg; a.m = sp.m; a.nseg = sp.nseg; a.skip = skip; a.xv_lo = xv_lo;
     hipError_t e;
-    const dim3 grid(sp.nseg, d.seqs()), block(kThreads);
+    const dim3 grid(walk_grid_x(d, sp.m, sp.nseg), walk_grid_y(d)), block(kThreads);
     {
         ProfScope ps(KID_WALK_SUMMARY, st);
         constexpr int lds = walk_lds(true);
@@ -878,7 +904,7 @@ hipError_t walk_fwd_slice(const Dims& d, const FwdArgs& a) {
     WalkArgs wa{};
     wa.xq = q; wa.xk = k; wa.xv = v; wa.g = a.g; wa.out = static_cast<uint16_t*>(a.o);
     wa.edge_in = a.m0; wa.edge_out = a.mT; wa.bound = w.bound_f; wa.m = sp.m; wa.nseg = sp.nseg;
-    const dim3 grid(sp.nseg, d.seqs()), block(kThreads);
+    const dim3 grid(walk_grid_x(d, sp.m, sp.nseg), walk_grid_y(d)), block(kThreads);
     constexpr int lds = walk_lds(false);
     ProfScope ps(KID_WALK_FWD, a.stream);
     if (d.kind == 0) {
@@ -901,7 +927,7 @@ hipError_t walk_fwd(const Dims& d0, const FwdArgs& a) {
 }
 
 hipError_t launch_walk_grad(const Dims& d, const SegPlan& sp, const GradArgs& ga, hipStream_t st) {
-    const dim3 grid(sp.nseg, d.seqs()), block(kGrad8Threads);
+    const dim3 grid(walk_grid_x(d, sp.m, sp.nseg), walk_grid_y(d)), block(kGrad8Threads);
     hipError_t e;
     ProfScope ps(KID_WALK_GRAD, st);
     if (ga.v_lo) {  // values in two planes (delta-rule backward)

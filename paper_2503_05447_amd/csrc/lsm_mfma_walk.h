@@ -24,8 +24,8 @@ struct WalkArgs {
     uint16_t* out;
     const float* edge_in;  // state a whole sequence starts from, [i][v] fp32 per sequence; NULL = zero
     float* edge_out;       // state it ends with; NULL = not wanted
-    float* bound;          // [seqs][nseg][128 x 128] fp32, [i][v]: entry state of every segment (nseg > 1)
-    float* gseg;           // [seqs][nseg]: total log-decay of each segment (SUMMARY writes)
+    float* bound;          // [slot][128 x 128] fp32, [i][v]: entry state of every segment but the first (nseg > 1; bound_slot())
+    float* gseg;           // [slot]: total log-decay of each segment (SUMMARY writes)
     int m, nseg;           // chunks per segment, segments per sequence (upper bound for packed input)
     int skip;              // SUMMARY, REV: segments [0, skip) feed no other walk and are left out (at least 1)
     const uint16_t* xv_lo; // VSPLIT (summary pass only): remainder plane of the value-role rows
@@ -334,7 +334,7 @@ __device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, int 
     f32x16 S[4];
     _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) S[ib] = f32x16{0};
     if (!SUMMARY) {
-        if (a.nseg > 1) walk_state_load(S, a.bound + (size_t(seq) * a.nseg + seg) * D * D, false, wave, n, half);
+        if (seg > 0) walk_state_load(S, a.bound + (bound_slot(d, seq, a.m, a.nseg) + seg) * D * D, false, wave, n, half);
         else if (a.edge_in) walk_state_load(S, a.edge_in + edge_off(d, seq), false, wave, n, half, D * d.vm);
     }
 
@@ -389,8 +389,9 @@ __device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, int 
 
     // ---- the state this walk ends with
     if (SUMMARY) {
-        walk_state_store(S, a.bound + (size_t(seq) * a.nseg + (REV ? seg - 1 : seg + 1)) * D * D, false, wave, n, half);
-        if (tid == 0) a.gseg[size_t(seq) * a.nseg + seg] = gtot;
+        const size_t slot = bound_slot(d, seq, a.m, a.nseg) + seg;
+        walk_state_store(S, a.bound + (REV ? slot - 1 : slot + 1) * D * D, false, wave, n, half);
+        if (tid == 0) a.gseg[slot] = gtot;
         return;
     }
     if (last && a.edge_out) walk_state_store(S, a.edge_out + edge_off(d, seq), false, wave, n, half, D * d.vm);
@@ -400,7 +401,8 @@ __device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, int 
 template <bool REV, bool DEC, bool SUMMARY, bool VSPLIT = false>
 __global__ __launch_bounds__(kThreads, 2) void mk_walk(Dims d, WalkArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    walk_body<REV, DEC, SUMMARY, VSPLIT>(d, a, blockIdx.y, blockIdx.x, smem);
+    const SegIndex i = seg_index(d, a.m, blockIdx.x, blockIdx.y);
+    walk_body<REV, DEC, SUMMARY, VSPLIT>(d, a, i.seq, i.seg, smem);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -429,14 +431,14 @@ struct GradArgs {
     uint16_t *dq, *dk, *dv;
     float* dg_tok;            // per-token scalar kind: d_log_decay itself; per-head kind: [BH*N] per-chunk sums
     const float* edge_in;     // M_0 [i][v] per sequence or NULL
-    const float* bound;       // entry states of the segments ([i][v]) when nseg > 1
+    const float* bound;       // entry states of the segments but the first ([i][v]) when nseg > 1
     int m, nseg;
     const uint16_t* v_lo;     // VSPLIT: remainder plane of the values (same layout as v)
     // VSPLIT: dU (head, remainder; [BH*T][128] in the library's own order) and the product dW = -dU S^T of every chunk with
     // the state it starts from (head, remainder, same order)
     const uint16_t *du_h, *du_l;
     uint16_t *dw_h, *dw_l;
-    // the entry states may be kept at a finer grain than this walk's segments: bound holds bound_n slots per sequence,
+    // the entry states may be kept at a finer grain than this walk's segments: bound is numbered for bound_n segments per sequence,
     // one per m / bound_per chunks, and segment s enters with slot s * bound_per (0: same grain, nseg slots)
     int bound_per, bound_n;
     // d_v = 256 (two passes, one per 128-wide value slice; dq and dk sum over them): the first pass leaves its dq and dk as
@@ -521,7 +523,8 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
     static_assert(2 * C * LDP >= C * LD, "the dW stage fits the area of As");
     constexpr int NT = VSPLIT ? 256 : kGrad8Threads;  // threads that share the tile traffic
 
-    const int seq = blockIdx.y, seg = blockIdx.x;
+    const SegIndex si = seg_index(d, a.m, blockIdx.x, blockIdx.y);
+    const int seq = si.seq, seg = si.seg;
     // the wave index as a scalar: the branch between the two groups is then a scalar branch (each group's barriers are
     // executed by its own waves only, whatever the compiler makes of the vector condition), and 32 * wave offsets are scalars
     const int tid = threadIdx.x, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave8 & 3;
@@ -627,9 +630,9 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
         f32x16 S[4];
         _Pragma("unroll") for (int vb = 0; vb < 4; ++vb) S[vb] = f32x16{0};
         {
-            if (a.nseg > 1)
-                walk_state_load(S, a.bound + (size_t(seq) * (a.bound_per ? a.bound_n : a.nseg) + seg * (a.bound_per ? a.bound_per : 1)) * D * D,
-                                true, wave, n, half);
+            const int per = a.bound_per ? a.bound_per : 1;
+            if (seg > 0)
+                walk_state_load(S, a.bound + (bound_slot(d, seq, a.m / per, a.bound_per ? a.bound_n : a.nseg) + seg * per) * D * D, true, wave, n, half);
             else if (a.edge_in) walk_state_load(S, a.edge_in + edge_off(d, seq), true, wave, n, half, D * d.vm);
         }
         float gval = 0.f;
@@ -893,15 +896,16 @@ __global__ __launch_bounds__(kThreads) void mk_bound_scan(Dims d, const float* _
                                                           const float* __restrict__ gseg, int m, int nseg, int skip) {
     const int seq = blockIdx.y, e = blockIdx.x * kThreads + threadIdx.x;
     const SeqWalk walk = seq_walk(d, seq);
-    const int nsq = max(1, (walk.n + m - 1) / m);
-    float* b = bound + size_t(seq) * nseg * D * D + e;
-    const float* gs = gseg + size_t(seq) * nseg;
+    const int nsq = (walk.n + m - 1) / m;
+    if (nsq <= 1 && (!REV || nsq == 0)) return;  // forward, the first segment starts from edge_in itself
+    const size_t slot = bound_slot(d, seq, m, nseg);
+    float* b = bound + slot * D * D + e;
+    const float* gs = gseg + slot;
     float E = edge_in ? edge_in[edge_off(d, seq) + size_t(e / D) * D * d.vm + e % D] : 0.f;
     // The contributions are read eight segments at a time before any of them is replaced: the reads of a batch do not
     // depend on each other, only the recurrence does (read - update - write in turn pays one memory latency per segment).
     constexpr int G = 8;
     if (!REV) {
-        b[0] = E;
         for (int s0 = 0; s0 + 1 < nsq; s0 += G) {
             float u[G], w[G];
             _Pragma("unroll") for (int i = 0; i < G; ++i) {
