@@ -19,11 +19,12 @@
 // operand of one MFMA of the next product (its k index are the rows 8g+j and 8g+4+j), so states and scores feed the
 // matrix cores straight out of the accumulators and nothing is split or rounded on the way.
 //
-// Bound: the fp32 matrix rate (157 TFLOP/s nominal; half of it reached at 4 x 16 sequences of 2047 fp32 tokens, d = 128,
-// scalar decay: forward walk 0.137 ms, the three gradient walks 0.39 ms).  Forward + backward against one-thread-per-element
-// kernels on the vector ALU with a state per chunk in memory, which this family replaced: that shape 11.6 -> 0.70 ms; bf16
-// vector decay, 4 x 8 sequences of 2048, d_k = 64, d_v = 128: 7.2 -> 0.56 ms; forward alone, 32 sequences of 1777, d = 64: 0.262 ->
-// 0.053 ms; 2 sequences of 256, d = 64: 0.110 -> 0.024 ms.  Distance to 64-bit results: a half to equal (2-norm, every output).
+// Bound: the fp32 matrix rate (155 TFLOP/s measured; half of it reached at 4 x 16 sequences of 2047 fp32 tokens, d = 128,
+// scalar decay: forward walk 0.136 ms, the three gradient walks 0.39 ms) and, for the vector kind, as much vector work.
+// Forward + backward against one-thread-per-element kernels on the vector ALU with a state per chunk in memory, which this
+// family replaced: that shape 11.6 -> 0.69 ms; bf16 vector decay, 4 x 8 sequences of 2048, d_k = 64, d_v = 128: 7.2 -> 0.445 ms;
+// forward alone, 32 sequences of 1777, d = 64: 0.262 -> 0.051 ms; 2 sequences of 256, d = 64: 0.110 -> 0.025 ms.  Distance to
+// 64-bit results: a half to equal (2-norm, every output).
 #include "lsm_internal.h"
 
 #include <mutex>
@@ -143,8 +144,64 @@ struct GTile {
     }
 };
 
+// state blocks <-> a stored state [d_k][d_v] (rows are key features; trans: value features): S[ib][4g+j] = state[key feature
+// kf + 32 ib + 8g + 4 half + j][value feature vf + lane % 32]
+template <int KB>
+__device__ __forceinline__ void state_load(f32x16 (&S)[KB], const float* e, int trans, int kd, int vd, int kf, int vf, int lane) {
+    const int v = vf + (lane & 31);
+    _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
+        _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+            const int k = kf + 32 * ib + 8 * g + 4 * (lane >> 5);
+            if (trans) {
+                const f32x4 t = load4(e + size_t(v) * kd + k);
+                _Pragma("unroll") for (int j = 0; j < 4; ++j) S[ib][4 * g + j] = t[j];
+            } else {
+                _Pragma("unroll") for (int j = 0; j < 4; ++j) S[ib][4 * g + j] = e[size_t(k + j) * vd + v];
+            }
+        }
+}
+template <int KB>
+__device__ __forceinline__ void state_store(const f32x16 (&S)[KB], float* e, int trans, int kd, int vd, int kf, int vf, int lane) {
+    const int v = vf + (lane & 31);
+    _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
+        _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+            const int k = kf + 32 * ib + 8 * g + 4 * (lane >> 5);
+            if (trans) {
+                store4(e + size_t(v) * kd + k, f32x4{S[ib][4 * g], S[ib][4 * g + 1], S[ib][4 * g + 2], S[ib][4 * g + 3]});
+            } else {
+                _Pragma("unroll") for (int j = 0; j < 4; ++j) e[size_t(k + j) * vd + v] = S[ib][4 * g + j];
+            }
+        }
+}
+__device__ __forceinline__ int hrow(int x, int half) { return 8 * (x >> 2) + 4 * half + (x & 3); }  // row of result register x
+
+// What a workgroup walks.
+struct GWalk {
+    SeqWalk walk;
+    size_t slot0;
+    int nsq, kbeg, kend, cnt, wseg;  // segments of the sequence; steps [kbeg, kend); segment index in walk order
+    bool empty;                      // packed input, an empty sequence: the state passes through
+    bool none;                       // no work
+};
+__device__ __forceinline__ GWalk find_walk(const Dims& d, const GArgs& a, int rev, bool sum) {
+    const GSeg s = find_seg(d, a.m, a.slots, a.extra, blockIdx.x, blockIdx.y);
+    const int steps = a.m * (d.gC / GT), kbeg = s.seg * steps, kend = min(s.n, kbeg + steps);
+    GWalk g{s.w, s.slot0, s.nsq, kbeg, kend, max(kend - kbeg, 0), rev ? s.nsq - 1 - s.seg : s.seg, s.n == 0 && s.seg == 0, false};
+    g.none = (s.seg >= s.nsq && !g.empty) || (sum && g.wseg >= s.nsq - 1);  // (nobody starts from the last segment's end)
+    return g;
+}
+// position of the kk-th step; past the last it is one row of it, that nobody uses: rows are requested a step ahead and
+// unconditionally (behind a branch the old values would stay live through the whole step)
+__device__ __forceinline__ ChunkPos walk_step(const Dims& d, const GWalk& g, int rev, int kk) {
+    const int k = min(kk, g.cnt - 1);
+    ChunkPos p = step_pos(d, g.walk, rev ? g.kend - 1 - k : g.kbeg + k);
+    if (kk >= g.cnt) p.L = 1;
+    return p;
+}
+
 // LDS of a walker, in floats.  Row strides == 4 mod 64 words: 16-byte row reads of 16 lanes tile the banks.
-//   Q | K | V | score partials [wave][16][64] | W (vector kind: one or two tiles of weighted rows) | tables
+//   Q | K | V | score partials (vector kind: then half of the inter product) [wave][16][64] | W (vector kind: one or two
+//   tiles of weighted rows) | tables
 template <int KD, int TV, int VEC, bool SUM>
 struct GLds {
     static constexpr int NW = TV / 32, LQ = KD + 4, LV = TV + 4;
@@ -157,122 +214,80 @@ struct GLds {
     static constexpr int bytes = total * 4;
 };
 
-// VEC 0: one decay per token (or none).  VEC 1: a decay per key-role feature (o, dv: the scores carry the decay).
-// VEC 2: a decay per value-role feature (dq, dk: the outputs do).
-//
-// The vector kind's pair weights e^{E_p - E_s} do not factor over the pair, but split at a reference between s and p they
-// do, into two factors <= 1.  At level l = 16, 8, 4, 2, 1 the pairs whose positions first differ in bit log2 l are taken
-// together (p in an odd block of l positions, s in the even block before it, reference at the start of p's block): every
-// position is on one side only, so one tile W holds, row by row, either side's weighted operand.  Running sums start at
-// the reference, so they are exact where the weight matters, however strong the decay.
-template <typename TIO, int KD, int TV, int VEC, bool SUM>
+// Walker of the scalar kinds.  TV / 32 waves, wave w owning value features [32 w, 32 w + 32)
+// of the state, all key features.  Two workgroups of the 128-wide form share a compute unit, and one's matrix work runs
+// under the other's waits.  (Two groups of waves in one workgroup, as in the vector kind's walker below, took 0.155 ms
+// where this takes 0.136: the forward walk at the top.)
+template <typename TIO, int KD, int TV, bool SUM>
 __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GArgs a) {
-    using Lds = GLds<KD, TV, VEC, SUM>;
-    constexpr int NW = Lds::NW, NT = 2 * TV, LQ = Lds::LQ, LV = Lds::LV, KB = KD / 32, COLS = Lds::COLS, LW = COLS + 4;
-    constexpr int ITEMS = VEC == 0 ? 1 : (2 * COLS + NT - 1) / NT;
+    using Lds = GLds<KD, TV, 0, SUM>;
+    constexpr int NW = Lds::NW, NT = 2 * TV, LQ = Lds::LQ, LV = Lds::LV, KB = KD / 32;
     extern __shared__ __align__(16) float sm[];
-    float *Q = sm, *K = sm + Lds::oK, *V = sm + Lds::oV, *Pp = sm + Lds::oP, *W = sm + Lds::oW;
-    double* bs = reinterpret_cast<double*>(sm + Lds::oT);   // VEC 0: E_p [32], then the step's total
-    float *wi = sm + Lds::oT + 68, *wo = wi + GT;           // VEC 0: e^{E_p}, e^{E - E_p}
-    float *tot = sm + Lds::oT, *lamv = tot + 2 * COLS;      // VEC: half sums [2][COLS], e^E [COLS]
+    float *Q = sm, *K = sm + Lds::oK, *V = sm + Lds::oV, *Pp = sm + Lds::oP;
+    double* bs = reinterpret_cast<double*>(sm + Lds::oT);   // E_p [32], then the step's total
+    float *wi = sm + Lds::oT + 68, *wo = wi + GT;           // e^{E_p}, e^{E - E_p}
     float* dred = sm + Lds::oD;                             // [wave][32]: partial row products
-    float* pw = sm + Lds::oE;                               // VEC 0: pair weights e^{E_n - E_r}, in the order of a score block's registers
+    float* pw = sm + Lds::oE;                               // pair weights e^{E_n - E_r}, in the order of a score block's registers
 
-    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 31, half = lane >> 5;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Every phase reads LDS at its own lane-dependent addresses.  Left alone the compiler keeps them all in registers
     // across the loop (over a hundred); with the thread id hidden at the start of a phase it recomputes that phase's few.
     auto fresh = [&]() { int t = tid; asm volatile("" : "+v"(t)); return t; };
     const int slice = blockIdx.z % a.nsl;
     const GRole& R = a.role[blockIdx.z / a.nsl];
-    const GSeg s = find_seg(d, a.m, a.slots, a.extra, blockIdx.x, blockIdx.y);
-    const SeqWalk walk = s.w;
     const int rev = R.rev, vcol = slice * TV;               // first value column of this workgroup
-    const bool empty_seq = s.n == 0 && s.seg == 0;          // packed input: the state passes through
-    if (s.seg >= s.nsq && !empty_seq) return;
-    const int steps = a.m * (d.gC / GT), kbeg = s.seg * steps, kend = min(s.n, kbeg + steps), cnt = max(kend - kbeg, 0);
-    const int wseg = rev ? s.nsq - 1 - s.seg : s.seg;       // segment index in walk order
-    if (SUM && wseg >= s.nsq - 1) return;                   // nobody starts from the last segment's end
+    const GWalk s = find_walk(d, a, rev, SUM);
+    if (s.none) return;
     const size_t sz = size_t(a.kd) * a.vd;
-    // the state blocks: S[ib][4g+j] = state[key feature 32 ib + 8g + 4 half + j][value feature vcol + 32 w + n]
     f32x16 S[KB];
     _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) S[ib] = f32x16{0};
-    // (stored [d_k][d_v]: rows are key features, or with trans value features)
-    auto soff = [&](int ib, int g) {
-        const int kf = 32 * ib + 8 * g + 4 * half, vf = vcol + 32 * w + n;
-        return R.trans ? size_t(vf) * a.kd + kf : size_t(kf) * a.vd + vf;
-    };
-    auto state_load = [&](const float* e) {
-        _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
-            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                const float* p = e + soff(ib, g);
-                if (R.trans) {
-                    const f32x4 t = load4(p);
-                    _Pragma("unroll") for (int j = 0; j < 4; ++j) S[ib][4 * g + j] = t[j];
-                } else {
-                    _Pragma("unroll") for (int j = 0; j < 4; ++j) S[ib][4 * g + j] = p[size_t(j) * a.vd];
-                }
-            }
-    };
-    auto state_store = [&](float* e) {
-        _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
-            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                float* p = e + soff(ib, g);
-                if (R.trans) {
-                    store4(p, f32x4{S[ib][4 * g], S[ib][4 * g + 1], S[ib][4 * g + 2], S[ib][4 * g + 3]});
-                } else {
-                    _Pragma("unroll") for (int j = 0; j < 4; ++j) p[size_t(j) * a.vd] = S[ib][4 * g + j];
-                }
-            }
-    };
     if (!SUM) {
-        if (wseg > 0) state_load(R.bound + (s.slot0 + wseg) * sz);
-        else if (R.edge_in) state_load(R.edge_in + size_t(walk.edge) * sz);
+        const float* e = s.wseg > 0 ? R.bound + (s.slot0 + s.wseg) * sz : R.edge_in ? R.edge_in + size_t(s.walk.edge) * sz : nullptr;
+        if (e) state_load(S, e, R.trans, a.kd, a.vd, 0, vcol + 32 * w, fresh() & 63);
     }
 
     GTile<TIO, KD, NT> rq, rk;
     GTile<TIO, TV, NT> rv;
-    float gval = 0.f;                                       // VEC 0: log-decay of walk position `lane`
-    // VEC: item = (column, half): the 16 transitions d_p INTO the positions of its half and, second half, the closing one.
-    // Forward: the decay of the token itself; backward: that of the position before.
-    float dt[ITEMS][16], dn[ITEMS][16], closing[ITEMS], closing_n[ITEMS];
-    double gtot[ITEMS];
-    _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) gtot[i] = 0.0;
-    auto item_ok = [&](int t, int i) { return 2 * COLS >= NT * (i + 1) || t + NT * i < 2 * COLS; };
-    auto item_col = [&](int t, int i) { return (t + NT * i) % COLS; };
-    auto item_half = [&](int t, int i) { return (t + NT * i) / COLS; };
-
+    float gval = 0.f;                                       // log-decay of walk position lane % 32
+    double gtot = 0.0;
     auto gload = [&](int kk) {
         const int tid = fresh();
-        ChunkPos p = step_pos(d, walk, rev ? kend - 1 - min(kk, cnt - 1) : kbeg + min(kk, cnt - 1));
-        if (kk >= cnt) p.L = 1;  // past the last step: one row, again and again, that nobody uses
+        const ChunkPos p = walk_step(d, s, rev, kk);
         const uint32_t kb = uint32_t(p.ts) * a.kd * sizeof(TIO), vb = uint32_t(p.ts) * a.vd * sizeof(TIO);
         if (!SUM) rq.gload(static_cast<const TIO*>(R.xq) + p.tok0 * a.kd, kb, p.L, rev, tid);
         rk.gload(static_cast<const TIO*>(R.xk) + p.tok0 * a.kd, kb, p.L, rev, tid);
         rv.gload(static_cast<const TIO*>(R.xv) + p.tok0 * a.vd + vcol, vb, p.L, rev, tid);
-        if (VEC == 0) {
-            if (d.kind != 0 && w == 0) {
-                const int row = min(n, p.L - 1);
-                gval = d.kind == 1 ? a.g[walk.bh % d.H] : a.g[p.tok0 + size_t(rev ? p.L - 1 - row : row) * p.ts];
-            }
-        } else {
-            const char* gb = reinterpret_cast<const char*>(a.g + p.tok0 * d.dk + (VEC == 2 ? vcol : 0));
-            const uint32_t grow = uint32_t(p.ts) * d.dk * 4;
-            _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) {
-                if (!item_ok(tid, i)) continue;
-                const uint32_t col = 4 * item_col(tid, i);
-                const int h16 = 16 * item_half(tid, i);
-                _Pragma("unroll") for (int x = 0; x < 16; ++x) {  // (what does not exist is zeroed when it is used)
-                    const int pos = h16 + x - rev, tok = min(max(rev ? p.L - 1 - pos : pos, 0), p.L - 1);
-                    dn[i][x] = *reinterpret_cast<const float*>(gb + uint32_t(tok) * grow + col);
-                }
-                closing_n[i] = *reinterpret_cast<const float*>(gb + col);
-            }
+        if (d.kind != 0 && w == 0) {
+            const int row = min(tid & 31, p.L - 1);
+            gval = d.kind == 1 ? a.g[s.walk.bh % d.H] : a.g[p.tok0 + size_t(rev ? p.L - 1 - row : row) * p.ts];
         }
     };
-    if (cnt > 0) gload(0);
+    // its share of the pair weights, of pairs (r < n) only
+    auto pair_weights = [&]() {
+        const int lane = fresh() & 63, n = lane & 31;
+        const double bn = bs[n];
+        _Pragma("unroll") for (int g = w; g < 4; g += NW) {
+            f32x4 e;
+            _Pragma("unroll") for (int j = 0; j < 4; ++j) {
+                const int r = 8 * g + 4 * (lane >> 5) + j;
+                e[j] = r < n ? expf(float(bn - bs[r])) : 0.f;
+            }
+            *reinterpret_cast<f32x4*>(pw + (g * 64 + lane) * 4) = e;
+        }
+    };
+    if (s.cnt > 0) gload(0);
+    if (d.kind == 0) {  // the tables of a step without decay, once
+        if (tid == 0) bs[GT] = 0.0;
+        if (tid < GT) wi[tid] = wo[tid] = 1.f;
+        if (!SUM)
+            for (int e = tid; e < 1024; e += NT) {  // element e = (4-register group, lane, register) of a score block
+                const int l = (e >> 2) & 63;
+                pw[e] = hrow(4 * (e >> 8) + (e & 3), l >> 5) < (l & 31) ? 1.f : 0.f;
+            }
+    }
 
-    for (int kk = 0; kk < cnt; ++kk) {
-        const ChunkPos cp = step_pos(d, walk, rev ? kend - 1 - kk : kbeg + kk);
+    for (int kk = 0; kk < s.cnt; ++kk) {
+        const ChunkPos cp = walk_step(d, s, rev, kk);
         const int L = cp.L;
         {
             const int tid = fresh();
@@ -280,51 +295,288 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
             rk.commit(K, LQ, L, tid);
             rv.commit(V, LV, L, tid);
         }
-        if (VEC == 0) {
-            // E in fp64: the sums reach hundreds for strong decays while only their O(1) differences enter exp()
-            if (d.kind != 0 && w == 0) {
-                const double x = n < L ? double(gval) : 0.0;
-                double inc = x;
-                for (int off = 1; off < GT; off <<= 1) {
-                    const double y = __shfl_up(inc, off, 32);
-                    if (n >= off) inc += y;
-                }
-                const double all = __shfl(inc, GT - 1, 32), E = rev ? inc - x : inc;
-                if (lane < GT) {
-                    bs[n] = E;
-                    wi[n] = expf(float(E));
-                    wo[n] = expf(float(all - E));
-                    if (n == 0) bs[GT] = all;
-                }
-                gtot[0] += all;
+        // E in fp64: the sums reach hundreds for strong decays while only their O(1) differences enter exp()
+        if (w == 0 && d.kind != 0) {
+            const int lane = fresh() & 63, n = lane & 31;
+            const double x = n < L ? double(gval) : 0.0;
+            double inc = x;
+            for (int off = 1; off < GT; off <<= 1) {
+                const double y = __shfl_up(inc, off, 32);
+                if (n >= off) inc += y;
             }
-        } else {
-            const int tid = fresh();
-            _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) {
-                if (!item_ok(tid, i)) continue;
-                const int h = item_half(tid, i);
-                double t = 0.0;
-                _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-                    const int pos = 16 * h + x - rev;
-                    dt[i][x] = pos >= 0 && pos < L ? dn[i][x] : 0.f;
-                    t += double(dt[i][x]);
-                }
-                closing[i] = rev && L == GT && h ? closing_n[i] : 0.f;
-                tot[h * COLS + item_col(tid, i)] = float(t + double(closing[i]));
+            const double all = __shfl(inc, GT - 1, 32), E = rev ? inc - x : inc;
+            if (lane < GT) {
+                bs[n] = E;
+                wi[n] = expf(float(E));
+                wo[n] = expf(float(all - E));
+                if (n == 0) bs[GT] = all;
             }
+            gtot += all;
         }
         __syncthreads();  // (A) rows and decay tables of this step are in LDS
+        f32x16 O;
+        if (!SUM) {
+            {   // this wave's share (a range of features) of the block P^T[s][p] = y_s . x_p
+                const int lane = fresh() & 63, n = lane & 31, half = lane >> 5;
+                f32x16 P = {0};
+                _Pragma("unroll") for (int f = 0; f < KD / NW; f += 8) {
+                    const int c = w * (KD / NW) + f + 4 * half;
+                    const f32x4 y = *reinterpret_cast<const f32x4*>(K + n * LQ + c), x = *reinterpret_cast<const f32x4*>(Q + n * LQ + c);
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) P = mfma2(y[j], x[j], P);
+                }
+                _Pragma("unroll") for (int g = 0; g < 4; ++g)
+                    *reinterpret_cast<f32x4*>(Pp + w * 1024 + (g * 64 + lane) * 4) = f32x4{P[4 * g], P[4 * g + 1], P[4 * g + 2], P[4 * g + 3]};
+            }
+            if (d.kind != 0) pair_weights();
+            {   // inter: O^T[v][p] = e^{E_p} sum_i S[i][v] x_p[i], the state blocks as A operands out of the accumulators (two
+                // chains: half the roundings in a row)
+                const int lane = fresh() & 63, n = lane & 31, half = lane >> 5;
+                f32x16 o[2] = {f32x16{0}, f32x16{0}};
+                _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
+                    _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                        const f32x4 x = *reinterpret_cast<const f32x4*>(Q + n * LQ + 32 * ib + 8 * g + 4 * half);
+                        _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j & 1] = mfma2(S[ib][4 * g + j], x[j], o[j & 1]);
+                    }
+                const float e = wi[n];
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] = (o[0][x] + o[1][x]) * e;
+            }
+            __syncthreads();  // (B) score partials, pair weights
+            const int lane = fresh() & 63, n = lane & 31, half = lane >> 5;
+            f32x16 P;
+            float pd = 0.f;
+            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                f32x4 t = *reinterpret_cast<const f32x4*>(Pp + (g * 64 + lane) * 4);
+                _Pragma("unroll") for (int u = 1; u < NW; ++u) t += *reinterpret_cast<const f32x4*>(Pp + u * 1024 + (g * 64 + lane) * 4);
+                const f32x4 e = *reinterpret_cast<const f32x4*>(pw + (g * 64 + lane) * 4);
+                _Pragma("unroll") for (int j = 0; j < 4; ++j) {
+                    pd += hrow(4 * g + j, half) == n ? t[j] : 0.f;
+                    P[4 * g + j] = t[j] * e[j];
+                }
+            }
+            pd += __shfl_xor(pd, 32, 64);  // the pair (p, p) of this lane's position
+            f32x16 X = {0};  // sum_s z_s P^T[s][p], s < p: the score block as B operand out of its registers
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) X = mfma2(V[hrow(x, half) * LV + 32 * w + n], P[x], X);
+            // The pair (p, p) stays out of the product with aux: it is the same number in q.dq and in k.dk and cancels in the
+            // decay gradient, exactly instead of to rounding.
+            const int tok = rev ? L - 1 - n : n;           // token of this lane's position (n < L)
+            const size_t orow = cp.tok0 + size_t(n < L ? tok : 0) * cp.ts;
+            const size_t oel = orow * a.vd + vcol + 32 * w + 4 * half;  // + 8g: four consecutive output features
+            float t = 0.f;
+            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                f32x4 o;
+                _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] = O[4 * g + j] + X[4 * g + j];
+                if (R.xdot) {
+                    const f32x4 q4 = load4(static_cast<const TIO*>(R.aux) + oel + 8 * g);
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) t += q4[j] * o[j];
+                }
+                const f32x4 z = *reinterpret_cast<const f32x4*>(V + n * LV + 32 * w + 8 * g + 4 * half);
+                _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] += pd * z[j];
+                if (n < L) store4(static_cast<TIO*>(R.out) + oel + 8 * g, o);
+            }
+            if (R.xdot) {
+                t += __shfl_xor(t, 32, 64);
+                if (half == 0) dred[w * GT + n] = t;
+            }
+        }
+        gload(kk + 1);  // the update outlasts a trip to memory and has the registers
+        {   // S[i][v] = e^E S[i][v] + sum_t e^{E - E_t} y_t[i] z_t[v]; the step's own sum is formed by itself, so the state sees
+            // one rounding per step instead of one per token
+            const int lane = fresh() & 63, n = lane & 31, half = lane >> 5;
+            float z[16];
+            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                const f32x4 e = *reinterpret_cast<const f32x4*>(wo + 8 * g + 4 * half);
+                _Pragma("unroll") for (int j = 0; j < 4; ++j) z[4 * g + j] = V[(8 * g + 4 * half + j) * LV + 32 * w + n] * e[j];
+            }
+            const float lam = expf(float(bs[GT]));
+            _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) {
+                f32x16 U = {0};
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) U = mfma2(K[hrow(x, half) * LQ + 32 * ib + n], z[x], U);
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) S[ib][x] = fmaf(lam, S[ib][x], U[x]);
+            }
+        }
+        __syncthreads();  // (D) every read of this step's tiles is done
+        if (!SUM && R.xdot && tid < L) {
+            float t = 0.f;
+            _Pragma("unroll") for (int u = 0; u < NW; ++u) t += dred[u * GT + tid];
+            R.xdot[size_t(slice) * d.BH() * d.T + cp.wtok0 + (rev ? L - 1 - tid : tid)] = t;
+        }
+    }
 
+    float* e = nullptr;
+    if (SUM) e = R.bound + (s.slot0 + s.wseg + 1) * sz;
+    else if (s.empty || s.wseg == s.nsq - 1) e = R.edge_out ? R.edge_out + size_t(s.walk.edge) * sz : nullptr;
+    if (e) state_store(S, e, R.trans, a.kd, a.vd, 0, vcol + 32 * w, fresh() & 63);
+    if (!SUM && R.end_slot && !s.empty && s.wseg == s.nsq - 1)
+        state_store(S, R.bound + (s.slot0 + s.nsq) * sz, R.trans, a.kd, a.vd, 0, vcol + 32 * w, fresh() & 63);
+    if (SUM && slice == 0 && d.kind != 0 && tid == 0) R.gseg[s.slot0 + s.wseg] = gtot;
+}
+
+// Walker of the vector kind.  VEC 1: a decay per key-role feature (o, dv: the scores carry the decay).  VEC 2: a decay per
+// value-role feature (dq, dk: the outputs do).
+//
+// The pair weights e^{E_p - E_s} do not factor over the pair, but split at a reference between s and p they
+// do, into two factors <= 1.  At level l = 16, 8, 4, 2, 1 the pairs whose positions first differ in bit log2 l are taken
+// together (p in an odd block of l positions, s in the even block before it, reference at the start of p's block): every
+// position is on one side only, so one tile W holds, row by row, either side's weighted operand.  Running sums start at
+// the reference, so they are exact where the weight matters, however strong the decay.
+//
+// Two groups of TV / 32 waves; wave w of either group owns value features [32 w, 32 w + 32) and half of the key features:
+//   lead  the score blocks, what is done with them, and the output;
+//   aux   the rows (requested a step ahead) and the weighted tiles (a phase ahead).
+// Both hold their half of the state, form its part of the inter product and move it on, so that the vector work of one
+// group runs under the matrix work of the other (one group doing both in turn, gradient walks of d_k = 64, d_v = 128, bf16,
+// 4 x 8 sequences of 2048: 0.260 ms; this: 0.171).  Each group runs a loop of its own with the same barriers, which the
+// comments of both number.
+template <typename TIO, int KD, int TV, int VEC, bool SUM>
+__global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d, GArgs a) {
+    using Lds = GLds<KD, TV, VEC, SUM>;
+    constexpr int NW = Lds::NW, NT = 2 * TV, LQ = Lds::LQ, LV = Lds::LV, KB = KD / 64, COLS = Lds::COLS, LW = COLS + 4;
+    constexpr int ITEMS = (2 * COLS + NT - 1) / NT;
+    extern __shared__ __align__(16) float sm[];
+    float *Q = sm, *K = sm + Lds::oK, *V = sm + Lds::oV, *Pp = sm + Lds::oP, *W0 = sm + Lds::oW, *W1 = W0 + Lds::WT;
+    float *tot = sm + Lds::oT, *lamv = tot + 2 * COLS;      // half sums [2][COLS], e^E [COLS]
+
+    // the wave index as a scalar: the branch between the groups is then a scalar branch
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave % NW;
+    const bool aux = wave >= NW;
+    const int tid = threadIdx.x & (NT - 1);                 // index within the group
+    // (as in gk_walk)
+    auto fresh = [&]() { int t = tid; asm volatile("" : "+v"(t)); return t; };
+    const int slice = blockIdx.z % a.nsl;
+    const GRole& R = a.role[blockIdx.z / a.nsl];
+    const int rev = R.rev, vcol = slice * TV;               // first value column of this workgroup
+    const int kcol = aux ? KD / 2 : 0;                      // first key feature of this group
+    const GWalk s = find_walk(d, a, rev, SUM);
+    if (s.none) return;
+    const size_t sz = size_t(a.kd) * a.vd;
+    f32x16 S[KB];
+    _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) S[ib] = f32x16{0};
+    if (!SUM) {
+        const float* e = s.wseg > 0 ? R.bound + (s.slot0 + s.wseg) * sz : R.edge_in ? R.edge_in + size_t(s.walk.edge) * sz : nullptr;
+        if (e) state_load(S, e, R.trans, a.kd, a.vd, kcol, vcol + 32 * w, fresh() & 63);
+    }
+
+    // ---- work that both groups do
+    // this wave's part of the inter product, O^T[v][p] = sum_i S[i][v] x_p[i], the state blocks as A operands out of the
+    // accumulators
+    auto inter = [&](const float* X, int ld) {
+        const int l = fresh() & 63, n = l & 31, half = l >> 5;
+        f32x16 o = {0};
+        _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
+            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(X + n * ld + kcol + 32 * ib + 8 * g + 4 * half);
+                _Pragma("unroll") for (int j = 0; j < 4; ++j) o = mfma2(S[ib][4 * g + j], x[j], o);
+            }
+        return o;
+    };
+    // ... and its weight e^{E_p} (VEC 2; VEC 1 has it in the rows)
+    auto scale_inter = [&](f32x16& O) {
+        const int l = fresh() & 63, n = l & 31, half = l >> 5;
+        _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+            const f32x4 e = *reinterpret_cast<const f32x4*>(W0 + n * LW + 32 * w + 8 * g + 4 * half);
+            _Pragma("unroll") for (int j = 0; j < 4; ++j) O[4 * g + j] *= e[j];
+        }
+    };
+    // S[i][v] = lam S[i][v] + sum_t Y[t][i] (w_t Z[t][v]); the step's own sum is formed by itself, so the state sees one
+    // rounding per step instead of one per token
+    auto update = [&]() {
+        const float *Y = VEC == 1 ? W0 : K, *Z = VEC == 2 ? W0 : V;
+        const int ldy = VEC == 1 ? LW : LQ, ldz = VEC == 2 ? LW : LV;
+        float lam = 1.f;
+        if (VEC == 2) lam = lamv[32 * w + (fresh() & 31)];
+        _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) {
+            const int l = fresh() & 63, n = l & 31, half = l >> 5;
+            f32x16 U = {0};
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                const int t = hrow(x, half);
+                U = mfma2(Y[t * ldy + kcol + 32 * ib + n], Z[t * ldz + 32 * w + n], U);
+            }
+            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                f32x4 m = {lam, lam, lam, lam};
+                if (VEC == 1) m = *reinterpret_cast<const f32x4*>(lamv + kcol + 32 * ib + 8 * g + 4 * half);
+                _Pragma("unroll") for (int j = 0; j < 4; ++j) S[ib][4 * g + j] = fmaf(m[j], S[ib][4 * g + j], U[4 * g + j]);
+            }
+        }
+    };
+    auto block_store = [&](const f32x16& P) {  // a block of registers to this wave's place among the partials
+        const int lane = fresh() & 63;
+        _Pragma("unroll") for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<f32x4*>(Pp + w * 1024 + (g * 64 + lane) * 4) = f32x4{P[4 * g], P[4 * g + 1], P[4 * g + 2], P[4 * g + 3]};
+    };
+    // levels alternate between the two tiles: f(level, tile, other tile)
+    auto levels = [&](auto f) {
+        f(std::integral_constant<int, 16>{}, W1, W0);
+        f(std::integral_constant<int, 8>{}, W0, W1);
+        f(std::integral_constant<int, 4>{}, W1, W0);
+        f(std::integral_constant<int, 2>{}, W0, W1);
+        f(std::integral_constant<int, 1>{}, W1, W0);
+    };
+
+    if (aux) {
+        GTile<TIO, KD, NT> rq, rk;
+        GTile<TIO, TV, NT> rv;
+        // item = (column, half): the 16 transitions d_p INTO the positions of its half and, second half, the closing
+        // one.  Forward: the decay of the token itself; backward: that of the position before.
+        float dt[ITEMS][16], at[ITEMS][16], dn[ITEMS][16], closing[ITEMS], closing_n[ITEMS];
+        double gtot[ITEMS];
+        _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) gtot[i] = 0.0;
+        auto item_ok = [&](int t, int i) { return 2 * COLS >= NT * (i + 1) || t + NT * i < 2 * COLS; };
+        auto item_col = [&](int t, int i) { return (t + NT * i) % COLS; };
+        auto item_half = [&](int t, int i) { return (t + NT * i) / COLS; };
+
+        auto gload = [&](int kk) {
+            const int tid = fresh();
+            const ChunkPos p = walk_step(d, s, rev, kk);
+            const uint32_t kb = uint32_t(p.ts) * a.kd * sizeof(TIO), vb = uint32_t(p.ts) * a.vd * sizeof(TIO);
+            if (!SUM) rq.gload(static_cast<const TIO*>(R.xq) + p.tok0 * a.kd, kb, p.L, rev, tid);
+            rk.gload(static_cast<const TIO*>(R.xk) + p.tok0 * a.kd, kb, p.L, rev, tid);
+            rv.gload(static_cast<const TIO*>(R.xv) + p.tok0 * a.vd + vcol, vb, p.L, rev, tid);
+            {
+                const char* gb = reinterpret_cast<const char*>(a.g + p.tok0 * d.dk + (VEC == 2 ? vcol : 0));
+                const uint32_t grow = uint32_t(p.ts) * d.dk * 4;
+                _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) {
+                    if (!item_ok(tid, i)) continue;
+                    const uint32_t col = 4 * item_col(tid, i);
+                    const int h16 = 16 * item_half(tid, i);
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) {  // (what does not exist is zeroed when it is used)
+                        const int pos = h16 + x - rev, tok = min(max(rev ? p.L - 1 - pos : pos, 0), p.L - 1);
+                        dn[i][x] = *reinterpret_cast<const float*>(gb + uint32_t(tok) * grow + col);
+                    }
+                    closing_n[i] = *reinterpret_cast<const float*>(gb + col);
+                }
+            }
+        };
+        auto commit = [&](int L) {  // registers of this step -> LDS; decay tables
+            const int tid = fresh();
+            if (!SUM) rq.commit(Q, LQ, L, tid);
+            rk.commit(K, LQ, L, tid);
+            rv.commit(V, LV, L, tid);
+            {
+                _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) {
+                    if (!item_ok(tid, i)) continue;
+                    const int h = item_half(tid, i);
+                    double t = 0.0;
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                        const int pos = 16 * h + x - rev;
+                        dt[i][x] = pos >= 0 && pos < L ? dn[i][x] : 0.f;
+                        if (!SUM) at[i][x] = expf(dt[i][x]);
+                        t += double(dt[i][x]);
+                    }
+                    closing[i] = rev && L == GT && h ? closing_n[i] : 0.f;
+                    tot[h * COLS + item_col(tid, i)] = float(t + double(closing[i]));
+                }
+            }
+        };
         // ---- vector kind: writers of the weighted tiles (see the level scheme above)
-        auto each = [&](float* dst, auto&& weigh) {  // weigh(p, column, exponent sums' item) -> value
+        auto each = [&](auto&& f) {  // f(item, half, column)
             const int tid = fresh();
             _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) {
                 if (!item_ok(tid, i)) continue;
-                weigh(i, item_half(tid, i), item_col(tid, i), dst);
+                f(i, item_half(tid, i), item_col(tid, i));
             }
         };
-        auto write_start = [&](float* dst) {  // weight e^{E_p} from the start of the step; also e^E
-            each(dst, [&](int i, int h, int c, float* o) {
+        auto write_start = [&](float* o) {  // weight e^{E_p} from the start of the step; also e^E
+            each([&](int i, int h, int c) {
                 const float t0 = tot[c];
                 double e = h ? t0 : 0.0;
                 _Pragma("unroll") for (int x = 0; x < 16; ++x) {
@@ -334,11 +586,10 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
                     o[p * LW + c] = VEC == 1 ? Q[p * LQ + c] * wt : wt;
                 }
                 if (h == 0) lamv[c] = expf(t0 + tot[COLS + c]);
-                if (SUM && h == 0) gtot[i] += double(t0) + double(tot[COLS + c]);
             });
         };
-        auto write_end = [&](float* dst) {  // weight e^{E - E_p} to the end of the step, on the state update's operand
-            each(dst, [&](int i, int h, int c, float* o) {
+        auto write_end = [&](float* o) {  // weight e^{E - E_p} to the end of the step, on the state update's operand
+            each([&](int i, int h, int c) {
                 double e = h ? closing[i] : tot[COLS + c];
                 if (SUM && h == 0) {
                     lamv[c] = expf(tot[c] + tot[COLS + c]);
@@ -351,42 +602,73 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
                 }
             });
         };
-        auto write_level = [&](float* dst, auto lvc) {
+        auto write_level = [&](float* o, auto lvc) {  // products of at most 16 decays, from the reference outwards
             constexpr int lv = decltype(lvc)::value;
-            each(dst, [&](int i, int h, int c, float* o) {
+            each([&](int i, int h, int c) {
                 _Pragma("unroll") for (int b = 0; b < 16; b += lv) {
                     const bool odd = lv == 16 ? h != 0 : ((b / lv) & 1) != 0;
-                    float e[lv];
+                    float e[lv], prod = 1.f;
                     if (odd) {  // query side: from the block's start up to the position
-                        double sum = 0.0;
-                        _Pragma("unroll") for (int x = 0; x < lv; ++x) { sum += double(dt[i][b + x]); e[x] = float(sum); }
+                        _Pragma("unroll") for (int x = 0; x < lv; ++x) { prod *= at[i][b + x]; e[x] = prod; }
                     } else {    // key side: from the position to the block's end
-                        double sum = 0.0;
-                        _Pragma("unroll") for (int x = lv - 1; x >= 0; --x) { e[x] = float(sum); sum += double(dt[i][b + x]); }
+                        _Pragma("unroll") for (int x = lv - 1; x >= 0; --x) { e[x] = prod; prod *= at[i][b + x]; }
                     }
                     _Pragma("unroll") for (int x = 0; x < lv; ++x) {
                         const int p = 16 * h + b + x;
-                        const float wt = expf(e[x]);
-                        if (VEC == 1) o[p * LW + c] = (odd ? Q[p * LQ + c] : K[p * LQ + c]) * wt;
-                        else o[p * LW + c] = odd ? wt : V[p * LV + c] * wt;
+                        if (VEC == 1) o[p * LW + c] = (odd ? Q[p * LQ + c] : K[p * LQ + c]) * e[x];
+                        else o[p * LW + c] = odd ? e[x] : V[p * LV + c] * e[x];
                     }
                 }
             });
         };
 
-        f32x16 O;
-        // inter: O^T[v][p] = sum_i S[i][v] x_p[i], the state blocks as A operands out of the accumulators (two chains:
-        // half the roundings in a row, and an MFMA never waits for the one before it)
-        auto inter = [&](const float* X, int ld) {
-            const int l = fresh() & 63, n = l & 31, half = l >> 5;
-            f32x16 o[2] = {f32x16{0}, f32x16{0}};
-            _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
-                _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                    const f32x4 x = *reinterpret_cast<const f32x4*>(X + n * ld + 32 * ib + 8 * g + 4 * half);
-                    _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j & 1] = mfma2(S[ib][4 * g + j], x[j], o[j & 1]);
-                }
-            _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] = o[0][x] + o[1][x];
-        };
+        if (s.cnt > 0) gload(0);
+        for (int kk = 0; kk < s.cnt; ++kk) {
+            commit(walk_step(d, s, rev, kk).L);
+            __syncthreads();  // (A) rows and decay tables of this step are in LDS
+            gload(kk + 1);
+            if constexpr (SUM) {
+                write_end(W0);
+                __syncthreads();  // (B)
+                update();
+            } else if constexpr (VEC == 1) {
+                write_start(W0);
+                __syncthreads();  // (B) e^{E_p} x_p
+                const f32x16 O = inter(W0, LW);
+                write_level(W1, std::integral_constant<int, 16>{});
+                __syncthreads();  // (B2)
+                levels([&](auto lvc, float*, float* nxt) {
+                    constexpr int lv = decltype(lvc)::value;
+                    if constexpr (lv > 1) write_level(nxt, std::integral_constant<int, lv / 2>{});
+                    else write_end(nxt);
+                    __syncthreads();  // (L) next level's tile; after the last: score partials, weighted keys
+                });
+                __syncthreads();  // (M) the partials are spent
+                block_store(O);
+                update();
+            } else {
+                write_start(W0);
+                write_level(W1, std::integral_constant<int, 16>{});
+                f32x16 O = inter(Q, LQ);
+                __syncthreads();  // (B) score partials, first tiles
+                scale_inter(O);
+                __syncthreads();  // (B2) the partials and the first tile are spent
+                block_store(O);
+                levels([&](auto lvc, float*, float* nxt) {
+                    constexpr int lv = decltype(lvc)::value;
+                    if constexpr (lv > 1) write_level(nxt, std::integral_constant<int, lv / 2>{});
+                    else write_end(nxt);
+                    __syncthreads();  // (L) next level's tile; after the last: weighted values
+                });
+                update();
+            }
+            __syncthreads();  // (C) every read of this step's tiles is done
+        }
+        if (SUM && slice == 0) {
+            _Pragma("unroll") for (int i = 0; i < ITEMS; ++i)
+                if (item_ok(tid, i) && item_half(tid, i) == 0) R.gseg[(s.slot0 + s.wseg) * COLS + item_col(tid, i)] = gtot[i];
+        }
+    } else {
         // this wave's share (a range of features) of the block P^T[s][p] = y_s . x_p
         auto score_part = [&](const float* Y, const float* X, int ld) {
             const int l = fresh() & 63, n = l & 31, half = l >> 5;
@@ -398,11 +680,6 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
             }
             return P;
         };
-        auto part_store = [&](const f32x16& P) {
-            const int lane = fresh() & 63;
-            _Pragma("unroll") for (int g = 0; g < 4; ++g)
-                *reinterpret_cast<f32x4*>(Pp + w * 1024 + (g * 64 + lane) * 4) = f32x4{P[4 * g], P[4 * g + 1], P[4 * g + 2], P[4 * g + 3]};
-        };
         auto part_sum = [&]() {
             const int lane = fresh() & 63;
             f32x16 P;
@@ -413,8 +690,6 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
             }
             return P;
         };
-        auto prow = [&](int x) { return 8 * (x >> 2) + 4 * half + (x & 3); };  // row of result register x
-        auto hrow = [](int x, int half) { return 8 * (x >> 2) + 4 * half + (x & 3); };
         // sum_s Z[s][v] P^T[s][p]: the score block as B operand out of its registers
         auto intra = [&](const float* Z, int ld, const f32x16& P) {
             const int l = fresh() & 63, n = l & 31, half = l >> 5;
@@ -422,205 +697,109 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
             _Pragma("unroll") for (int x = 0; x < 16; ++x) acc = mfma2(Z[hrow(x, half) * ld + 32 * w + n], P[x], acc);
             return acc;
         };
-        auto add_to_O = [&](const f32x16& X) { _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] += X[x]; };
         auto diagonal = [&](const f32x16& P) {  // P[p][p] for this lane's position
             const int l = fresh() & 63;
             float t = 0.f;
             _Pragma("unroll") for (int x = 0; x < 16; ++x) t += hrow(x, l >> 5) == (l & 31) ? P[x] : 0.f;
             return t + __shfl_xor(t, 32, 64);
         };
-        // the pair (p, p) leaves the output's product with aux: it is the same number in q.dq and in k.dk and cancels
-        // in the decay gradient, exactly instead of to rounding
-        auto finish = [&](float pd) {
-            const int l = fresh() & 63, n = l & 31, half = l >> 5;
-            const int tok = rev ? L - 1 - n : n;           // token of this lane's position (n < L)
-            const size_t orow = cp.tok0 + size_t(n < L ? tok : 0) * cp.ts;
-            const size_t oel = orow * a.vd + vcol + 32 * w + 4 * half;  // + 8g: four consecutive output features
-            auto aux4 = [&](int g) { return load4(static_cast<const TIO*>(R.aux) + oel + 8 * g); };
-            if (R.xdot) {
-                if (VEC == 0) {
-                    float t = 0.f;
-                    _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                        const f32x4 q4 = aux4(g);
-                        _Pragma("unroll") for (int j = 0; j < 4; ++j) t += q4[j] * O[4 * g + j];
+        for (int kk = 0; kk < s.cnt; ++kk) {
+            const ChunkPos cp = walk_step(d, s, rev, kk);
+            const int L = cp.L;
+            f32x16 O, P;
+            float pd = 0.f;
+            f32x4 z[4];
+            __syncthreads();  // (A)
+            if constexpr (SUM) {
+                __syncthreads();  // (B)
+                update();
+            } else {
+                if constexpr (VEC == 1) {
+                    P = score_part(K, Q, LQ);
+                    {
+                        const int l = fresh() & 63;
+                        _Pragma("unroll") for (int x = 0; x < 16; ++x) P[x] = hrow(x, l >> 5) == (l & 31) ? P[x] : 0.f;
                     }
-                    t += __shfl_xor(t, 32, 64);
-                    if (half == 0) dred[w * GT + n] = t;
-                } else if (n < L) {
-                    float* x = R.xdot + (cp.wtok0 + tok) * a.vd + vcol + 32 * w + 4 * half;
-                    _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                        const f32x4 q4 = aux4(g);
-                        store4(x + 8 * g, f32x4{q4[0] * O[4 * g], q4[1] * O[4 * g + 1], q4[2] * O[4 * g + 2], q4[3] * O[4 * g + 3]});
-                    }
-                }
-            }
-            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                const f32x4 z = *reinterpret_cast<const f32x4*>(V + n * LV + 32 * w + 8 * g + 4 * half);
-                f32x4 o;
-                _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] = O[4 * g + j] + pd * z[j];
-                if (n < L) store4(static_cast<TIO*>(R.out) + oel + 8 * g, o);
-            }
-        };
-        // S[i][v] = lam(ib, x) S[i][v] + sum_t Y[t][i] (w_t Z[t][v]); the step's own sum is formed by itself, so the state
-        // sees one rounding per step instead of one per token
-        auto update = [&](const float* Y, int ldy, const float* Z, int ldz, const float* wt, auto&& lam) {
-            gload(kk + 1);  // the next step's rows: the update outlasts a trip to memory and has the registers
-            // (unconditional: behind a branch the old values would stay live through the whole step)
-            const int l = fresh() & 63, n = l & 31, half = l >> 5;
-            float z[16];
-            _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-                const int t = hrow(x, half);
-                z[x] = wt ? Z[t * ldz + 32 * w + n] * wt[t] : Z[t * ldz + 32 * w + n];
-            }
-            _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) {
-                f32x16 U = {0};
-                _Pragma("unroll") for (int x = 0; x < 16; ++x) U = mfma2(Y[hrow(x, half) * ldy + 32 * ib + n], z[x], U);
-                _Pragma("unroll") for (int x = 0; x < 16; ++x) S[ib][x] = fmaf(lam(ib, x), S[ib][x], U[x]);
-            }
-        };
-
-        if constexpr (VEC == 0) {
-            if (!SUM) {
-                part_store(score_part(K, Q, LQ));
-                if (d.kind != 0) {  // each wave its share of the weights, of pairs (r < n) only
-                    const int l = fresh() & 63, n = l & 31;
-                    const double bn = bs[n];
-                    _Pragma("unroll") for (int g = w; g < 4; g += NW) {
-                        f32x4 e;
-                        _Pragma("unroll") for (int j = 0; j < 4; ++j) {
-                            const int r = 8 * g + 4 * (l >> 5) + j;
-                            e[j] = r < n ? expf(float(bn - bs[r])) : 0.f;
+                    __syncthreads();  // (B)
+                    O = inter(W0, LW);
+                    __syncthreads();  // (B2)
+                    levels([&](auto lvc, float* cur, float*) {
+                        constexpr int lv = decltype(lvc)::value;
+                        const f32x16 G = score_part(cur, cur, LW);
+                        const int l = fresh() & 63, n = l & 31;
+                        _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                            const int r = hrow(x, l >> 5);
+                            if (r < n && (r ^ n) >= lv && (r ^ n) < 2 * lv) P[x] = G[x];
                         }
-                        *reinterpret_cast<f32x4*>(pw + (g * 64 + l) * 4) = e;
-                    }
+                        if constexpr (lv == 1) block_store(P);
+                        __syncthreads();  // (L)
+                    });
+                    P = part_sum();
+                    pd = diagonal(P);
+                    const int l = fresh() & 63;
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) P[x] = hrow(x, l >> 5) == (l & 31) ? 0.f : P[x];
+                    __syncthreads();  // (M)
+                    const f32x16 X = intra(V, LV, P);
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] += X[x];
+                } else {
+                    block_store(score_part(K, Q, LQ));
+                    O = inter(Q, LQ);
+                    __syncthreads();  // (B)
+                    scale_inter(O);
+                    P = part_sum();
+                    pd = diagonal(P);
+                    __syncthreads();  // (B2)
+                    levels([&](auto lvc, float* cur, float*) {
+                        constexpr int lv = decltype(lvc)::value;
+                        f32x16 G;
+                        const int l = fresh() & 63, n = l & 31, half = l >> 5;
+                        _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                            const int r = hrow(x, half);
+                            G[x] = r < n && (r ^ n) >= lv && (r ^ n) < 2 * lv ? P[x] : 0.f;
+                        }
+                        const f32x16 X = intra(cur, LW, G);
+                        _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                            const f32x4 e = *reinterpret_cast<const f32x4*>(cur + n * LW + 32 * w + 8 * g + 4 * half);
+                            _Pragma("unroll") for (int j = 0; j < 4; ++j) O[4 * g + j] += (n & lv) ? X[4 * g + j] * e[j] : 0.f;
+                        }
+                        __syncthreads();  // (L)
+                    });
                 }
-                inter(Q, LQ);
-                if (d.kind != 0) {
-                    const float e = wi[n];
-                    _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] *= e;
-                }
-                __syncthreads();  // (B) score partials
-                f32x16 P = part_sum();
-                const float pd = diagonal(P);
+                update();
                 const int l = fresh() & 63;
-                _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                    if (d.kind != 0) {
-                        const f32x4 e = *reinterpret_cast<const f32x4*>(pw + (g * 64 + l) * 4);
-                        _Pragma("unroll") for (int j = 0; j < 4; ++j) P[4 * g + j] *= e[j];
-                    } else {
-                        _Pragma("unroll") for (int j = 0; j < 4; ++j) P[4 * g + j] = 8 * g + 4 * (l >> 5) + j < (l & 31) ? P[4 * g + j] : 0.f;
-                    }
-                }
-                add_to_O(intra(V, LV, P));
-                finish(pd);
+                _Pragma("unroll") for (int g = 0; g < 4; ++g) z[g] = *reinterpret_cast<const f32x4*>(V + (l & 31) * LV + 32 * w + 8 * g + 4 * (l >> 5));
             }
-            const float lam = d.kind != 0 ? expf(float(bs[GT])) : 1.f;
-            update(K, LQ, V, LV, d.kind != 0 ? wo : nullptr, [&](int, int) { return lam; });
-        } else if constexpr (SUM) {
-            write_end(W);
-            __syncthreads();
-            update(W, LW, V, LV, nullptr, [&](int ib, int x) { return lamv[32 * ib + prow(x)]; });
-        } else {
-            float *W0 = W, *W1 = W + Lds::WT;
-            auto lev = [](auto f, float* x, float* y) {  // levels alternate between the two tiles
-                f(x, std::integral_constant<int, 16>{}, y);
-                f(y, std::integral_constant<int, 8>{}, x);
-                f(x, std::integral_constant<int, 4>{}, y);
-                f(y, std::integral_constant<int, 2>{}, x);
-                f(x, std::integral_constant<int, 1>{}, y);
-            };
-            if constexpr (VEC == 1) {
-                const f32x16 raw = score_part(K, Q, LQ);
-                f32x16 P;
-                _Pragma("unroll") for (int x = 0; x < 16; ++x) P[x] = prow(x) == n ? raw[x] : 0.f;
-                write_start(W0);
-                __syncthreads();
-                write_level(W1, std::integral_constant<int, 16>{});
-                inter(W0, LW);
-                __syncthreads();
-                lev([&](float* cur, auto lvc, float* nxt) {
-                    constexpr int lv = decltype(lvc)::value;
-                    if constexpr (lv > 1) write_level(nxt, std::integral_constant<int, lv / 2>{});
-                    else write_end(nxt);
-                    __builtin_amdgcn_sched_barrier(0);
-                    const f32x16 G = score_part(cur, cur, LW);
-                    const int l = fresh() & 63, n = l & 31;
-                    _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-                        const int r = hrow(x, l >> 5);
-                        if (r < n && (r ^ n) >= lv && (r ^ n) < 2 * lv) P[x] = G[x];
-                    }
-                    if constexpr (lv == 1) part_store(P);
-                    __syncthreads();
-                }, W1, W0);
-                P = part_sum();
-                const float pd = diagonal(P);
-                _Pragma("unroll") for (int x = 0; x < 16; ++x) P[x] = prow(x) == n ? 0.f : P[x];
-                add_to_O(intra(V, LV, P));
-                finish(pd);
-                update(W0, LW, V, LV, nullptr, [&](int ib, int x) { return lamv[32 * ib + prow(x)]; });
-            } else {
-                part_store(score_part(K, Q, LQ));
-                write_start(W0);
-                __syncthreads();
-                write_level(W1, std::integral_constant<int, 16>{});
-                inter(Q, LQ);
-                auto row4 = [&](const float* X, int n, int half, int g) {
-                    return *reinterpret_cast<const f32x4*>(X + n * LW + 32 * w + 8 * g + 4 * half);
-                };
+            __syncthreads();  // (C)
+            if constexpr (!SUM) {
+                // The output: the other group's half of the inter product, and the pair (p, p), which stays out of the
+                // product with aux: it is the same number in q.dq and in k.dk and cancels in the decay gradient, exactly
+                // instead of to rounding.
+                const int l = fresh() & 63, n = l & 31, half = l >> 5;
+                const int tok = rev ? L - 1 - n : n;           // token of this lane's position (n < L)
+                const size_t orow = cp.tok0 + size_t(n < L ? tok : 0) * cp.ts;
+                const size_t oel = orow * a.vd + vcol + 32 * w + 4 * half;  // + 8g: four consecutive output features
                 _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                    const f32x4 e = row4(W0, n, half, g);
-                    _Pragma("unroll") for (int j = 0; j < 4; ++j) O[4 * g + j] *= e[j];
+                    f32x4 o = *reinterpret_cast<const f32x4*>(Pp + w * 1024 + (g * 64 + l) * 4);
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] += O[4 * g + j];
+                    if (R.xdot) {
+                        const f32x4 q4 = load4(static_cast<const TIO*>(R.aux) + oel + 8 * g);
+                        f32x4 y;
+                        _Pragma("unroll") for (int j = 0; j < 4; ++j) y[j] = q4[j] * o[j];
+                        if (n < L) store4(R.xdot + (cp.wtok0 + tok) * a.vd + vcol + 32 * w + 4 * half + 8 * g, y);
+                    }
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] += pd * z[g][j];
+                    if (n < L) store4(static_cast<TIO*>(R.out) + oel + 8 * g, o);
                 }
-                const f32x16 P = part_sum();
-                const float pd = diagonal(P);
-                __syncthreads();
-                lev([&](float* cur, auto lvc, float* nxt) {
-                    constexpr int lv = decltype(lvc)::value;
-                    if constexpr (lv > 1) write_level(nxt, std::integral_constant<int, lv / 2>{});
-                    else write_end(nxt);
-                    __builtin_amdgcn_sched_barrier(0);
-                    f32x16 G;
-                    const int l = fresh() & 63, n = l & 31, half = l >> 5;
-                    _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-                        const int r = hrow(x, half);
-                        G[x] = r < n && (r ^ n) >= lv && (r ^ n) < 2 * lv ? P[x] : 0.f;
-                    }
-                    const f32x16 X = intra(cur, LW, G);
-                    _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                        const f32x4 e = row4(cur, n, half, g);
-                        _Pragma("unroll") for (int j = 0; j < 4; ++j) O[4 * g + j] += (n & lv) ? X[4 * g + j] * e[j] : 0.f;
-                    }
-                    __syncthreads();
-                }, W1, W0);
-                finish(pd);
-                const float lam = lamv[32 * w + n];
-                update(K, LQ, W0, LW, nullptr, [&](int, int) { return lam; });
             }
-        }
-        __syncthreads();  // (D) every read of this step's tiles is done
-        if (!SUM && VEC == 0 && R.xdot && tid < L) {
-            float t = 0.f;
-            _Pragma("unroll") for (int u = 0; u < NW; ++u) t += dred[u * GT + tid];
-            R.xdot[size_t(slice) * d.BH() * d.T + cp.wtok0 + (rev ? L - 1 - tid : tid)] = t;
         }
     }
 
-    if (SUM) {
-        state_store(R.bound + (s.slot0 + wseg + 1) * sz);
-        if (slice == 0 && d.kind != 0) {
-            if (VEC == 0) {
-                if (tid == 0) R.gseg[s.slot0 + wseg] = gtot[0];
-            } else {
-                _Pragma("unroll") for (int i = 0; i < ITEMS; ++i)
-                    if (item_ok(tid, i) && item_half(tid, i) == 0) R.gseg[(s.slot0 + wseg) * COLS + item_col(tid, i)] = gtot[i];
-            }
-        }
-        return;
-    }
-    if (empty_seq || wseg == s.nsq - 1) {
-        if (R.edge_out) state_store(R.edge_out + size_t(walk.edge) * sz);
-        if (R.end_slot && !empty_seq) state_store(R.bound + (s.slot0 + s.nsq) * sz);
-    }
+    float* e = nullptr;
+    if (SUM) e = R.bound + (s.slot0 + s.wseg + 1) * sz;
+    else if (s.empty || s.wseg == s.nsq - 1) e = R.edge_out ? R.edge_out + size_t(s.walk.edge) * sz : nullptr;
+    if (e) state_store(S, e, R.trans, a.kd, a.vd, kcol, vcol + 32 * w, fresh() & 63);
+    if (!SUM && R.end_slot && !s.empty && s.wseg == s.nsq - 1)
+        state_store(S, R.bound + (s.slot0 + s.nsq) * sz, R.trans, a.kd, a.vd, kcol, vcol + 32 * w, fresh() & 63);
 }
 
 // States at the segment boundaries of a sequence, in walk order: E_0 = edge_in, E_{s+1} = e^{g_s} E_s + U_s, in place (slot
@@ -855,23 +1034,25 @@ template <typename TIO, int KD, int TV, int VEC, bool SUM>
 hipError_t launch_walk(const Dims& d, GArgs a, int nroles, dim3 grid, hipStream_t st, int kid) {
     using Lds = GLds<KD, TV, VEC, SUM>;
     static_assert(Lds::bytes <= 160 * 1024, "LDS");
-    auto kernel = gk_walk<TIO, KD, TV, VEC, SUM>;
+    void (*kernel)(Dims, GArgs);
+    if constexpr (VEC == 0) kernel = gk_walk<TIO, KD, TV, SUM>;
+    else kernel = gk_walk_vec<TIO, KD, TV, VEC, SUM>;
     const hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), Lds::bytes);
     if (e != hipSuccess) return e;
     a.nsl = a.vd / TV;
     grid.z = nroles * a.nsl;
     ProfScope ps(kid, st);
-    hipLaunchKernelGGL(kernel, grid, dim3(2 * TV), Lds::bytes, st, d, a);
+    hipLaunchKernelGGL(kernel, grid, dim3(VEC == 0 ? 2 * TV : 4 * TV), Lds::bytes, st, d, a);
     return hipGetLastError();
 }
 // Key-role width kd keeps its whole state column block in one wave's registers; value-role widths of 128 and 256 go in
-// slices of 128 (fewer repeats of the scores), except where two more tiles of 256-wide weighted rows would not fit.
+// slices of 128 (fewer repeats of the scores), except the vector kind's with 256-wide keys (LDS, registers).
 template <typename TIO, int VEC, bool SUM>
 hipError_t walk_dims(const Dims& d, const GArgs& a, int nroles, dim3 grid, hipStream_t st, int kid) {
     const bool narrow = a.vd == 64;
     if (a.kd == 64) return narrow ? launch_walk<TIO, 64, 64, VEC, SUM>(d, a, nroles, grid, st, kid) : launch_walk<TIO, 64, 128, VEC, SUM>(d, a, nroles, grid, st, kid);
     if (a.kd == 128) return narrow ? launch_walk<TIO, 128, 64, VEC, SUM>(d, a, nroles, grid, st, kid) : launch_walk<TIO, 128, 128, VEC, SUM>(d, a, nroles, grid, st, kid);
-    if constexpr (VEC == 1) return launch_walk<TIO, 256, 64, VEC, SUM>(d, a, nroles, grid, st, kid);
+    if constexpr (VEC != 0) return launch_walk<TIO, 256, 64, VEC, SUM>(d, a, nroles, grid, st, kid);
     else return narrow ? launch_walk<TIO, 256, 64, VEC, SUM>(d, a, nroles, grid, st, kid) : launch_walk<TIO, 256, 128, VEC, SUM>(d, a, nroles, grid, st, kid);
 }
 template <typename TIO>
