@@ -1158,7 +1158,7 @@ hipError_t launch_delta_fwd_t(const Dims& d, const DeltaPrepArgs& pa, DeltaWalkA
         }
         {
             ProfScope ps(KID_DELTA_COMBINE, st);
-            hipLaunchKernelGGL(mk_delta_combine<false>, dim3(d.seqs()), block, kDeltaCombineLds, st, d, wa.edge_in, sumA, sumB, bound, sp.m, sp.nseg);
+            hipLaunchKernelGGL(mk_delta_combine<false>, dim3(D / 32, d.seqs()), block, kDeltaCombineLds, st, d, wa.edge_in, sumA, sumB, bound, sp.m, sp.nseg);
         }
         wa.bound = bound;
     }
@@ -1200,7 +1200,7 @@ hipError_t launch_delta_rwalk(const Dims& d, DeltaRevArgs ra, void* segws, hipSt
         }
         {
             ProfScope ps(KID_DELTA_COMBINE, st);
-            hipLaunchKernelGGL(mk_delta_combine<true>, dim3(d.seqs()), block, kDeltaCombineLds, st, d, ra.edge_in, sumA, sumB, bound, sp.m, sp.nseg);
+            hipLaunchKernelGGL(mk_delta_combine<true>, dim3(D / 32, d.seqs()), block, kDeltaCombineLds, st, d, ra.edge_in, sumA, sumB, bound, sp.m, sp.nseg);
         }
         ra.bound = bound;
     }

@@ -442,17 +442,11 @@ __global__ __launch_bounds__(512, 1) void mk_delta_walk8(Dims d, DeltaWalkArgs a
 // gradients), one workgroup per sequence, the product on the
 // matrix cores with both factors as bf16 head + remainder (three products; about 2^-16 relative).
 // LDS: A head | A remainder | E head | E remainder (128 x LD each).   grid: (seqs)
-constexpr int kDeltaCombineLds = 4 * D * LD * 2;
-__device__ __forceinline__ void delta_split_tile(uint16_t* hi, uint16_t* lo, const float* src, int tid) {
-    _Pragma("unroll") for (int it = 0; it < 16; ++it) {   // 128 x 128 floats by 256 threads, 4 at a time
-        const int p = tid + kThreads * it, row = p >> 5, c4 = p & 31;
-        const float4 x = src ? *reinterpret_cast<const float4*>(src + row * D + 4 * c4) : float4{0.f, 0.f, 0.f, 0.f};
-        const uint32_t h0 = pack2(x.x, x.y), h1 = pack2(x.z, x.w);
-        *reinterpret_cast<u32x2*>(hi + row * LD + 4 * c4) = u32x2{h0, h1};
-        *reinterpret_cast<u32x2*>(lo + row * LD + 4 * c4) =
-            u32x2{pack2(x.x - bf16_lo(h0), x.y - bf16_hi(h0)), pack2(x.z - bf16_lo(h1), x.w - bf16_hi(h1))};
-    }
-}
+// The value columns of E evolve independently: a workgroup chains 32 of them (grid: 4 x sequences), A and B of the next
+// segment requested while this one is multiplied.  Bound by the latency of that chain: 16 sequences of 2000 tokens in 16
+// segments, 0.144 ms with one workgroup per sequence and nothing requested ahead, 0.046 ms so.
+constexpr int LDE = 40;  // row stride of a 128 x 32 slice of E
+constexpr int kDeltaCombineLds = 2 * D * LD * 2 + 2 * D * LDE * 2;
 template <bool REV>
 __global__ __launch_bounds__(kThreads, 1) void mk_delta_combine(Dims d, const float* __restrict__ edge_in, const float* __restrict__ sumA,
                                                                 const float* __restrict__ sumB, float* __restrict__ bound, int m,
@@ -461,50 +455,70 @@ __global__ __launch_bounds__(kThreads, 1) void mk_delta_combine(Dims d, const fl
     uint16_t* Ah = reinterpret_cast<uint16_t*>(smem);
     uint16_t* Al = Ah + D * LD;
     uint16_t* Eh = Al + D * LD;
-    uint16_t* El = Eh + D * LD;
-    const int seq = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 31, half = lane >> 5;
+    uint16_t* El = Eh + D * LDE;
+    const int v0 = 32 * blockIdx.x, seq = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 31, half = lane >> 5;
     const SeqWalk walk = seq_walk(d, seq);
     const int nsq = max(1, (walk.n + m - 1) / m);
     const float* e0 = edge_in ? edge_in + size_t(seq) * D * D : nullptr;
     float* b = bound + size_t(seq) * nseg * D * D;
-    // the walk's first segment (REV: the last in time) starts from the edge state; the same as tiles
+    // the walk's first segment (REV: the last in time) starts from the edge state; the same as a tile
     float* b0 = b + size_t(REV ? nsq - 1 : 0) * D * D;
-    _Pragma("unroll") for (int it = 0; it < 16; ++it) {
-        const int p = tid + kThreads * it, row = p >> 5, c4 = p & 31;
-        *reinterpret_cast<float4*>(b0 + row * D + 4 * c4) = e0 ? *reinterpret_cast<const float4*>(e0 + row * D + 4 * c4) : float4{0.f, 0.f, 0.f, 0.f};
+    _Pragma("unroll") for (int it = 0; it < 4; ++it) {
+        const int p = tid + kThreads * it, row = p >> 3, c4 = p & 7;
+        const float4 x = e0 ? *reinterpret_cast<const float4*>(e0 + row * D + v0 + 4 * c4) : float4{0.f, 0.f, 0.f, 0.f};
+        *reinterpret_cast<float4*>(b0 + row * D + v0 + 4 * c4) = x;
+        const uint32_t h0 = pack2(x.x, x.y), h1 = pack2(x.z, x.w);
+        *reinterpret_cast<u32x2*>(Eh + row * LDE + 4 * c4) = u32x2{h0, h1};
+        *reinterpret_cast<u32x2*>(El + row * LDE + 4 * c4) =
+            u32x2{pack2(x.x - bf16_lo(h0), x.y - bf16_hi(h0)), pack2(x.z - bf16_lo(h1), x.w - bf16_hi(h1))};
     }
-    delta_split_tile(Eh, El, e0, tid);
+    if (nsq <= 1) return;
+    float4 ra[16];  // A of the next segment: 128 x 128 floats by 256 threads, 4 at a time
+    f32x16 rb;      // its B, at the result registers: rows 32 w .. + 31, this workgroup's columns
+    auto gload = [&](int st) {
+        const int s = REV ? nsq - 1 - min(st, nsq - 2) : min(st, nsq - 2);
+        const size_t slot = (size_t(seq) * nseg + s) * D * D;
+        _Pragma("unroll") for (int it = 0; it < 16; ++it) {
+            const int p = tid + kThreads * it;
+            ra[it] = *reinterpret_cast<const float4*>(sumA + slot + (p >> 5) * D + 4 * (p & 31));
+        }
+        _Pragma("unroll") for (int x = 0; x < 16; ++x)
+            rb[x] = sumB[slot + size_t(32 * wave + 8 * (x >> 2) + 4 * half + (x & 3)) * D + v0 + n];
+    };
+    gload(0);
     for (int st = 0; st + 1 < nsq; ++st) {
         const int s = REV ? nsq - 1 - st : st;   // the segment walked in this step; its end state enters segment s -+ 1
-        const size_t slot = (size_t(seq) * nseg + s) * D * D;
-        delta_split_tile(Ah, Al, sumA + slot, tid);
+        _Pragma("unroll") for (int it = 0; it < 16; ++it) {
+            const int p = tid + kThreads * it, row = p >> 5, c4 = p & 31;
+            const float4 x = ra[it];
+            const uint32_t h0 = pack2(x.x, x.y), h1 = pack2(x.z, x.w);
+            *reinterpret_cast<u32x2*>(Ah + row * LD + 4 * c4) = u32x2{h0, h1};
+            *reinterpret_cast<u32x2*>(Al + row * LD + 4 * c4) =
+                u32x2{pack2(x.x - bf16_lo(h0), x.y - bf16_hi(h0)), pack2(x.z - bf16_lo(h1), x.w - bf16_hi(h1))};
+        }
+        f32x16 acc = rb;
+        gload(st + 1);
         __syncthreads();  // A and E tiles are complete
-        // E'[i][v] = sum_j A[i][j] E[j][v] + B[i][v]; this wave: rows i in [32 w, 32 w + 32)
-        f32x16 acc[4];
-        _Pragma("unroll") for (int vb = 0; vb < 4; ++vb)
-            _Pragma("unroll") for (int x = 0; x < 16; ++x)
-                acc[vb][x] = sumB[slot + size_t(32 * wave + 8 * (x >> 2) + 4 * half + (x & 3)) * D + 32 * vb + n];
+        // E'[i][v] = sum_j A[i][j] E[j][v] + B[i][v]
         _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) {
             const bf16x8 ah = frag(Ah, LD, 32 * wave + n, 16 * ks + 8 * half), al = frag(Al, LD, 32 * wave + n, 16 * ks + 8 * half);
-            _Pragma("unroll") for (int vb = 0; vb < 4; ++vb) {
-                const bf16x8 eh = frag_tr(Eh, LD, 16 * ks, 32 * vb, lane), el = frag_tr(El, LD, 16 * ks, 32 * vb, lane);
-                acc[vb] = mfma(ah, eh, acc[vb]);
-                acc[vb] = mfma(ah, el, acc[vb]);
-                acc[vb] = mfma(al, eh, acc[vb]);
-            }
+            const bf16x8 eh = frag_tr(Eh, LDE, 16 * ks, 0, lane), el = frag_tr(El, LDE, 16 * ks, 0, lane);
+            acc = mfma(ah, eh, acc);
+            acc = mfma(ah, el, acc);
+            acc = mfma(al, eh, acc);
         }
-        __syncthreads();  // every wave has read E
+        __syncthreads();  // every wave has read A and E
         float* out = b + size_t(REV ? s - 1 : s + 1) * D * D;
-        _Pragma("unroll") for (int vb = 0; vb < 4; ++vb)
-            _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-                const int i = 32 * wave + 8 * (x >> 2) + 4 * half + (x & 3), v = 32 * vb + n;
-                const float e = acc[vb][x];
-                out[size_t(i) * D + v] = e;
-                const uint32_t h = pack2(e, 0.f);
-                Eh[i * LD + v] = uint16_t(h & 0xffffu);
-                El[i * LD + v] = uint16_t(pack2(e - bf16_lo(h), 0.f) & 0xffffu);
-            }
-        // the next delta_split_tile writes A only; the barrier at the top of the next step orders the E writes
+        _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+            const int i = 32 * wave + 8 * (x >> 2) + 4 * half + (x & 3);
+            const float e = acc[x];
+            out[size_t(i) * D + v0 + n] = e;
+            const uint32_t h = pack2(e, 0.f);
+            Eh[i * LDE + n] = uint16_t(h & 0xffffu);
+            El[i * LDE + n] = uint16_t(pack2(e - bf16_lo(h), 0.f) & 0xffffu);
+        }
+        // the barrier at the top of the next step orders the writes of A and E
     }
 }
 
