@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
         bf16x8 s[8], ds[8];
         u32x2 sr[8], dsr[8];  // remainder planes: 8-bit floats, still scaled by 2^8
     };
-    auto issue = [&](int vh, SliceRegs& r) {
+    auto issue_tiles = [&](int vh, SliceRegs& r) {
         _Pragma("unroll") for (int it = 0; it < 2; ++it) {
             int row, cpp;
             tile_rows(it, row, cpp);
@@ -422,16 +422,15 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
             r.tv[it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v + off));
             r.to[it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(d_o + off));
         }
-        // this wave's rows of S, dS (both token blocks read the same rows) and their 8-bit remainder planes
-        const size_t sbase = (pos.slot * nvh + vh) * D * D;
-        _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) {
-            const size_t soff = sbase + state_frag_off(wave, ks, lane);
-            r.s[ks] = *reinterpret_cast<const bf16x8*>(states + soff);
-            r.ds[ks] = *reinterpret_cast<const bf16x8*>(dstates + soff);
-            if (want_dg) {
-                r.sr[ks] = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(states_rem) + soff);
-                r.dsr[ks] = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(dstates_rem) + soff);
-            }
+    };
+    // this wave's rows of S, dS (both token blocks read the same rows) and their 8-bit remainder planes, k-step ks
+    auto issue_state = [&](int vh, int ks, SliceRegs& r) {
+        const size_t soff = (pos.slot * nvh + vh) * D * D + state_frag_off(wave, ks, lane);
+        r.s[ks] = *reinterpret_cast<const bf16x8*>(states + soff);
+        r.ds[ks] = *reinterpret_cast<const bf16x8*>(dstates + soff);
+        if (want_dg) {
+            r.sr[ks] = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(states_rem) + soff);
+            r.dsr[ks] = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(dstates_rem) + soff);
         }
     };
     auto commit = [&](const SliceRegs& r) {
@@ -458,7 +457,8 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
             tg[it][0] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(g + roff));
             tg[it][1] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(g + roff + 4));
         }
-        issue(0, sr0);
+        issue_tiles(0, sr0);
+        _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) issue_state(0, ks, sr0);
         _Pragma("unroll") for (int it = 0; it < 2; ++it) {
             int row, cpp;
             tile_rows(it, row, cpp);
@@ -493,13 +493,13 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
     f32x16 aq = {0}, aqr = {0}, ak = {0}, akr = {0};
     f32x16 z0 = {0}, z1 = {0};
     float zi = 0.f;
+    // The next slice takes the registers of this one as they are used up, so that no trip to memory stands between the
+    // slices (d_v = 256, 4 x 16 sequences of 4096: 0.648 -> 0.624 ms).
     for (int vh = 0; vh < nvh; ++vh) {
-        if (vh > 0) {
-            __syncthreads();  // the previous slice is consumed
-            issue(vh, sr0);
-        }
+        if (vh > 0) __syncthreads();  // the previous slice is consumed
         commit(sr0);
         __syncthreads();
+        if (vh + 1 < nvh) issue_tiles(vh + 1, sr0);
         _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) {
             const bf16x8 sf = sr0.s[ks], dsf = sr0.ds[ks];
             const bf16x8 dof = frag(T1, LD, t, 16 * ks + 8 * half), vf = frag(T0, LD, t, 16 * ks + 8 * half);
@@ -517,6 +517,7 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
                               (bf16_hi(a[p]) + kRem8Unscale * bf16_hi(ar[p])) * (bf16_hi(b[p]) + kRem8Unscale * bf16_hi(br[p]));
                 }
             }
+            if (vh + 1 < nvh) issue_state(vh + 1, ks, sr0);
         }
         if (wv < 4) {  // this wave's block of Z: rows of V and d_o as operands
             const int rowv = wv == 1 ? 32 + n : n;               // V row: wave 0, 2, 3: 0.., wave 1: 32..
