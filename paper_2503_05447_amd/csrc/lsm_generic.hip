@@ -803,7 +803,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
 }
 
 // States at the segment boundaries of a sequence, in walk order: E_0 = edge_in, E_{s+1} = e^{g_s} E_s + U_s, in place (slot
-// s+1 holds U_s on entry).  Elementwise, four elements per thread, eight slots requested ahead of the chain.
+// s+1 holds U_s on entry).  Elementwise, four elements per thread.
 // grid: (d_k d_v / 1024, sequences, directions)
 __global__ __launch_bounds__(256) void gk_scan(Dims d, GArgs a) {
     const GRole& R = a.role[blockIdx.z];
@@ -824,22 +824,30 @@ __global__ __launch_bounds__(256) void gk_scan(Dims d, GArgs a) {
     f32x4 E = {0.f, 0.f, 0.f, 0.f};
     if (R.edge_in) E = load4(R.edge_in + size_t(w.edge) * sz + e);
     float* b = R.bound + slot0 * sz + e;
-    constexpr int AHEAD = 8;
-    for (int s = 0; s + 1 < nsq; s += AHEAD) {
-        f32x4 u[AHEAD];
-        double gl[AHEAD];
-        _Pragma("unroll") for (int x = 0; x < AHEAD; ++x) {
-            const int t = min(s + x, nsq - 2);
-            u[x] = load4(b + size_t(t + 1) * sz);
-            gl[x] = d.kind == 0 ? 0.0 : R.gseg[(slot0 + t) * dkd + (dkd > 1 ? i : 0)];
+    // A batch of segments costs one memory latency: every load is issued before the first use.  The decays of the scalar
+    // kinds are the same for a whole workgroup and come through the scalar cache.
+    const double* gp = d.kind == 0 ? nullptr : R.gseg + slot0 * dkd;
+    auto chain = [&](auto vec) {
+        constexpr int AHEAD = 8;
+        for (int s = 0; s + 1 < nsq; s += AHEAD) {
+            f32x4 u[AHEAD];
+            double gl[AHEAD];
+            _Pragma("unroll") for (int x = 0; x < AHEAD; ++x) {
+                const int t = min(s + x, nsq - 2);
+                u[x] = load4(b + size_t(t + 1) * sz);
+                if constexpr (decltype(vec)::value) gl[x] = gp[size_t(t) * dkd + i];
+                else gl[x] = gp ? gp[t] : 0.0;
+            }
+            _Pragma("unroll") for (int x = 0; x < AHEAD; ++x) {
+                if (s + x >= nsq - 1) break;
+                const float lam = expf(float(gl[x]));
+                _Pragma("unroll") for (int c = 0; c < 4; ++c) E[c] = lam * E[c] + u[x][c];
+                store4(b + size_t(s + x + 1) * sz, E);
+            }
         }
-        _Pragma("unroll") for (int x = 0; x < AHEAD; ++x) {
-            if (s + x >= nsq - 1) break;
-            const float lam = expf(float(gl[x]));
-            _Pragma("unroll") for (int c = 0; c < 4; ++c) E[c] = lam * E[c] + u[x][c];
-            store4(b + size_t(s + x + 1) * sz, E);
-        }
-    }
+    };
+    if (d.kind == 3) chain(std::true_type{});
+    else chain(std::false_type{});
 }
 
 // Decay gradient of a segment: dg_t = sum_{u >= t in the segment} (q_u.dq_u - k_u.dk_u) + <S_end, dS_end>, S_end / dS_end the

@@ -902,12 +902,13 @@ __global__ __launch_bounds__(kThreads) void mk_bound_scan(Dims d, const float* _
     float* b = bound + slot * D * D + e;
     const float* gs = gseg + slot;
     float E = edge_in ? edge_in[edge_off(d, seq) + size_t(e / D) * D * d.vm + e % D] : 0.f;
-    // The contributions are read eight segments at a time before any of them is replaced: the reads of a batch do not
+    // The contributions are read a batch of segments at a time before any of them is replaced: the reads of a batch do not
     // depend on each other, only the recurrence does (read - update - write in turn pays one memory latency per segment).
-    constexpr int G = 8;
-    if (!REV) {
-        for (int s0 = 0; s0 + 1 < nsq; s0 += G) {
-            float u[G], w[G];
+    // 24 at a time while there are many, eight for the rest (4 sequences in 125 segments: 23 -> 18 us a launch).
+    auto batch = [&](auto size, int s0) {
+        constexpr int G = decltype(size)::value;
+        float u[G], w[G];
+        if (!REV) {
             _Pragma("unroll") for (int i = 0; i < G; ++i) {
                 const int s = min(s0 + i, nsq - 2);
                 u[i] = b[size_t(s + 1) * D * D];
@@ -918,11 +919,8 @@ __global__ __launch_bounds__(kThreads) void mk_bound_scan(Dims d, const float* _
                     E = __expf(w[i]) * E + u[i];
                     b[size_t(s0 + i + 1) * D * D] = E;
                 }
-        }
-    } else {
-        b[size_t(nsq - 1) * D * D] = E;
-        for (int s0 = nsq - 1; s0 >= skip; s0 -= G) {  // slots below skip - 1 are entered by no walk
-            float u[G], w[G];
+            return s0 + G;
+        } else {
             _Pragma("unroll") for (int i = 0; i < G; ++i) {
                 const int s = max(s0 - i, skip);
                 u[i] = b[size_t(s - 1) * D * D];
@@ -933,7 +931,17 @@ __global__ __launch_bounds__(kThreads) void mk_bound_scan(Dims d, const float* _
                     E = __expf(w[i]) * E + u[i];
                     b[size_t(s0 - i - 1) * D * D] = E;
                 }
+            return s0 - G;
         }
+    };
+    if (!REV) {
+        int s0 = 0;
+        while (nsq - 1 - s0 > 8) s0 = batch(std::integral_constant<int, 24>{}, s0);
+        while (s0 + 1 < nsq) s0 = batch(std::integral_constant<int, 8>{}, s0);
+    } else {
+        b[size_t(nsq - 1) * D * D] = E;
+        int s0 = nsq - 1;  // slots below skip - 1 are entered by no walk
+        while (s0 - skip >= 8) s0 = batch(std::integral_constant<int, 24>{}, s0);
+        while (s0 >= skip) s0 = batch(std::integral_constant<int, 8>{}, s0);
     }
 }
-
