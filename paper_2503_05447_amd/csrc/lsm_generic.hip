@@ -1123,7 +1123,7 @@ hipError_t bwd_t(const Dims& d, const BwdArgs& b) {
     if (want_dg) {
         const GDgArgs ga{w.xq, w.xk, w.bound_f, w.bound_r, b.d_mT, b.dg, w.dg_tok, gp.m, slots, extra, slices(d.dk, false)};
         {
-            ProfScope ps(KID_GEN_RSCAN, b.stream);
+            ProfScope ps(KID_GEN_DG, b.stream);
             hipLaunchKernelGGL(gk_dg, grid, dim3(256), 0, b.stream, d, ga);
         }
         if (d.kind == 1) {
