@@ -11,7 +11,10 @@
 // time with its state in matrix-core accumulators.  Where a launch has too few sequences a sequence is cut into
 // segments: gk_walk<SUM> (state update alone, from zero) leaves every segment's own contribution, gk_scan chains them,
 // and the walkers then run all segments in parallel.  The decay gradient needs, per token, q.dq and k.dk (left by the
-// two walkers) and, per segment, the product of the state and its gradient at the segment's end (gk_dg).
+// two walkers) and, per chunk, the product of the state and its gradient at the chunk's end: the dq walker leaves its state
+// there, the dk walker, launched after it, multiplies it with its own, and gk_dg sums backward from there.  (Summing back
+// from the end of a whole segment needs no state per chunk, but the roundings of q.dq and k.dk add up over the way: 2-norm
+// error 2.2e-6 against 3.6e-7 with segments of 2048 tokens and a decay of e^-0.02 a token.)
 //
 // Contractions are v_mfma_f32_32x32x2_f32: fp32 operands, fp32 accumulation, 1/16 of the bf16 rate but exact products,
 // and its operand layout is its result layout: lane l holds A[m = l%32][k = l/32], B[k = l/32][n = l%32], and result
@@ -20,13 +23,17 @@
 // matrix cores straight out of the accumulators and nothing is split or rounded on the way.
 //
 // Bound: the fp32 matrix rate (155 TFLOP/s measured; half of it reached at 4 x 16 sequences of 2047 fp32 tokens, d = 128,
-// scalar decay: forward walk 0.136 ms, the three gradient walks 0.39 ms) and, for the vector kind, as much vector work.
+// scalar decay: forward walk 0.136 ms, the three gradient walks 0.41 ms) and, for the vector kind, as much vector work.
 // Forward + backward against one-thread-per-element kernels on the vector ALU with a state per chunk in memory, which this
-// family replaced: that shape 11.6 -> 0.69 ms; bf16 vector decay, 4 x 8 sequences of 2048, d_k = 64, d_v = 128: 7.2 -> 0.445 ms;
-// forward alone, 32 sequences of 1777, d = 64: 0.262 -> 0.051 ms; 2 sequences of 256, d = 64: 0.110 -> 0.025 ms.  Distance to
-// 64-bit results: a half to equal (2-norm, every output).
+// family replaced: that shape 11.6 -> 0.72 ms; bf16 vector decay, 4 x 8 sequences of 2048, d_k = 64, d_v = 128: 7.2 -> 0.446 ms;
+// forward alone, 32 sequences of 1777, d = 64: 0.262 -> 0.051 ms; 2 sequences of 256, d = 64: 0.110 -> 0.025 ms.
+// Distance to 64-bit results against those kernels, 2-norm, weak to strong decays, 512 to 4096 tokens, chunks of 16 to 128: o, dq,
+// dk, dv and d_init_state 0.4 to 0.95 times (one case 1.08), dg 0.1 to 0.85 times (vector kind in chunks of 16: 1.04), the final
+// state 0.9 to 1.4 times (one rounding more: at most 3.7e-8 where it was 2.6e-8).
 #include "lsm_internal.h"
 
+#include <algorithm>
+#include <initializer_list>
 #include <mutex>
 #include <vector>
 
@@ -65,10 +72,13 @@ struct GRole {
     float* xdot;               // that product: scalar kinds [value slice][BH*T] (summed over the row), vector kind [BH*T][width]
     const float* edge_in;      // state the whole sequence starts from (walk order), [d_k][d_v] per sequence; NULL = zero
     float* edge_out;           // state it ends with; NULL = not wanted
-    float* bound;              // states at segment boundaries, one slot of [d_k][d_v] per segment
+    float* bound;              // states at segment boundaries, [d_k][d_v] each (bound_at)
     double* gseg;              // SUM: total log-decay of each segment ([slot], vector kind [slot][d_k])
     int rev, trans;            // walk backward in time; the walk's state is the transpose of the stored one
-    int end_slot;              // the walk's last state goes to the boundary slot after the last segment as well
+    int per;                   // 0: bound is numbered by segments; else by decay-gradient units, so many to a segment
+    int keep;                  // leave the state at the end of every unit in bound (1: but not the sequence's last, 2: all)
+    const float* dot;          // such states of the other direction: their products with this walk's state go to z,
+    double* z;                 //   [unit][width / 32] (one term per wave), vector kind [unit][2][width] (one per group)
 };
 struct GArgs {
     GRole role[3];
@@ -76,38 +86,53 @@ struct GArgs {
     int kd, vd;        // row widths of the key-role and value-role arrays
     int nsl;           // value slices (grid.z = role * nsl + slice)
     int m;             // segment length in units of Dims::gC tokens
-    int slots, extra;  // boundary slots per head (packed input) or per sequence; extra slots per sequence
+    int slots;         // boundary slots per head (packed input) or per sequence
+    int units;         // units of Dims::gC tokens per head (packed input) or per sequence
 };
+
+// Unit of the decay gradient: the tokens its sums run back over.
+__host__ __device__ __forceinline__ int dg_unit(const Dims& d) { return d.C < GT ? GT : d.C; }
+__host__ __device__ __forceinline__ int dg_per(const Dims& d) { return d.gC / dg_unit(d); }  // such units per unit of gC tokens
 
 // Segment `x` of the grid: packed input numbers the segments of all sequences of a head one after the other, sequence s
 // from its first unit / m + s on (units counted per sequence and at least one each, so that two never overlap).
-struct GSeg { SeqWalk w; int n, seg, nsq; size_t slot0; };
-__device__ __forceinline__ int seg_base(const Dims& d, int m, int extra, int s) {
-    return (m == 1 ? d.cstart[s] : d.cstart[s] / m + s) + extra * s;
+struct GSeg { SeqWalk w; int n, seg, nsq; size_t slot0, unit0; };
+__device__ __forceinline__ int seg_base(const Dims& d, int m, int s) { return m == 1 ? d.cstart[s] : d.cstart[s] / m + s; }
+// last sequence s with base(s) <= x (base ascending), 64 sequences at a time, one per lane
+template <typename F>
+__device__ __forceinline__ int last_seq(const Dims& d, int x, F base) {
+    int lo = -1;
+    for (int s0 = 0; s0 < d.nseq; s0 += 64) {
+        const int t = s0 + int(threadIdx.x & 63);
+        const uint64_t le = __ballot(t < d.nseq && base(min(t, d.nseq)) <= x);
+        lo += __popcll(le);
+        if (le != ~uint64_t(0)) break;
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
 }
-__device__ __forceinline__ GSeg find_seg(const Dims& d, int m, int slots, int extra, int x, int y) {
+__device__ __forceinline__ GSeg find_seg(const Dims& d, const GArgs& a, int x, int y) {
     GSeg r;
     if (!d.cu) {
         r.w = SeqWalk{y, y, 0, 0, 0, d.T};
         r.seg = x;
-        r.slot0 = size_t(y) * slots;
+        r.slot0 = size_t(y) * a.slots;
+        r.unit0 = size_t(y) * a.units;
     } else {
-        int lo = -1;  // last s whose base is <= x, 64 sequences at a time (one per lane)
-        for (int s0 = 0; s0 < d.nseq; s0 += 64) {
-            const int t = s0 + int(threadIdx.x & 63);
-            const uint64_t le = __ballot(t < d.nseq && seg_base(d, m, extra, min(t, d.nseq)) <= x);
-            lo += __popcll(le);
-            if (le != ~uint64_t(0)) break;
-        }
-        lo = __builtin_amdgcn_readfirstlane(lo);
+        const int lo = last_seq(d, x, [&](int s) { return seg_base(d, a.m, s); });
         r.w = SeqWalk{y, lo * d.H + y, 0, 0, d.cu[lo], d.cu[lo + 1]};
-        r.seg = x - seg_base(d, m, extra, lo);
-        r.slot0 = size_t(y) * slots + seg_base(d, m, extra, lo);
+        r.seg = x - seg_base(d, a.m, lo);
+        r.slot0 = size_t(y) * a.slots + seg_base(d, a.m, lo);
+        r.unit0 = size_t(y) * a.units + d.cstart[lo];
     }
+    r.unit0 *= dg_per(d);
     const int len = r.w.tend - r.w.tbeg;
     r.n = (len + GT - 1) / GT;
-    r.nsq = (len + d.gC * m - 1) / (d.gC * m);
+    r.nsq = (len + d.gC * a.m - 1) / (d.gC * a.m);
     return r;
+}
+// slot of the state that segment w >= 1 (walk order) starts from: the one at the end of the unit before it
+__device__ __forceinline__ size_t bound_at(int per, size_t slot0, size_t unit0, int w) {
+    return per ? unit0 + size_t(w) * per - 1 : slot0 + w;
 }
 __device__ __forceinline__ ChunkPos step_pos(const Dims& d, const SeqWalk& w, int k) {
     const int t0 = w.tbeg + k * GT;
@@ -173,20 +198,33 @@ __device__ __forceinline__ void state_store(const f32x16 (&S)[KB], float* e, int
             }
         }
 }
+// this lane's part of the product of two states: S and the stored one, transposed (elements as in state_load with trans)
+template <int KB>
+__device__ __forceinline__ double state_dot(const f32x16 (&S)[KB], const float* e, int kd, int kf, int vf, int lane) {
+    double z = 0.0;
+    e += size_t(vf + (lane & 31)) * kd + kf + 4 * (lane >> 5);
+    _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) {
+        f32x4 t[4];
+        _Pragma("unroll") for (int g = 0; g < 4; ++g) t[g] = load4(e + 32 * ib + 8 * g);
+        _Pragma("unroll") for (int x = 0; x < 16; ++x) z += double(t[x >> 2][x & 3]) * double(S[ib][x]);
+        asm volatile("" ::: "memory");  // one block's loads at a time: the registers are full
+    }
+    return z;
+}
 __device__ __forceinline__ int hrow(int x, int half) { return 8 * (x >> 2) + 4 * half + (x & 3); }  // row of result register x
 
 // What a workgroup walks.
 struct GWalk {
     SeqWalk walk;
-    size_t slot0;
-    int nsq, kbeg, kend, cnt, wseg;  // segments of the sequence; steps [kbeg, kend); segment index in walk order
+    size_t slot0, unit0;
+    int n, nsq, kbeg, kend, cnt, wseg;  // steps and segments of the sequence; steps [kbeg, kend); segment index in walk order
     bool empty;                      // packed input, an empty sequence: the state passes through
     bool none;                       // no work
 };
 __device__ __forceinline__ GWalk find_walk(const Dims& d, const GArgs& a, int rev, bool sum) {
-    const GSeg s = find_seg(d, a.m, a.slots, a.extra, blockIdx.x, blockIdx.y);
+    const GSeg s = find_seg(d, a, blockIdx.x, blockIdx.y);
     const int steps = a.m * (d.gC / GT), kbeg = s.seg * steps, kend = min(s.n, kbeg + steps);
-    GWalk g{s.w, s.slot0, s.nsq, kbeg, kend, max(kend - kbeg, 0), rev ? s.nsq - 1 - s.seg : s.seg, s.n == 0 && s.seg == 0, false};
+    GWalk g{s.w, s.slot0, s.unit0, s.n, s.nsq, kbeg, kend, max(kend - kbeg, 0), rev ? s.nsq - 1 - s.seg : s.seg, s.n == 0 && s.seg == 0, false};
     g.none = (s.seg >= s.nsq && !g.empty) || (sum && g.wseg >= s.nsq - 1);  // (nobody starts from the last segment's end)
     return g;
 }
@@ -197,6 +235,19 @@ __device__ __forceinline__ ChunkPos walk_step(const Dims& d, const GWalk& g, int
     ChunkPos p = step_pos(d, g.walk, rev ? g.kend - 1 - k : g.kbeg + k);
     if (kk >= g.cnt) p.L = 1;
     return p;
+}
+
+// decay-gradient unit that ends with the kk-th step, -1 if none does
+__device__ __forceinline__ int unit_end(const Dims& d, const GWalk& g, int rev, int kk) {
+    const int k = rev ? g.kend - 1 - kk : g.kbeg + kk, steps = dg_unit(d) / GT;
+    return (k + 1) % steps == 0 || k + 1 == g.n ? k / steps : -1;
+}
+// slot for the state after the kk-th step of a walk that keeps the units' states, -1 if that is not kept: at the end of a
+// segment the slot has the next segment's entry state already
+__device__ __forceinline__ long long keep_slot(const Dims& d, const GRole& R, const GWalk& g, int kk) {
+    if (!R.keep || (kk == g.cnt - 1 && (g.wseg < g.nsq - 1 || R.keep < 2))) return -1;
+    const int u = unit_end(d, g, R.rev, kk);
+    return u < 0 ? -1 : (long long)(g.unit0 + u);
 }
 
 // LDS of a walker, in floats.  Row strides == 4 mod 64 words: 16-byte row reads of 16 lanes tile the banks.
@@ -210,7 +261,7 @@ struct GLds {
     static constexpr int oK = SUM ? 0 : GT * LQ, oV = oK + GT * LQ, oP = oV + GT * LV, oW = oP + (SUM ? 0 : NW * 1024);
     static constexpr int oT = oW + WN * WT;
     static constexpr int tables = VEC == 0 ? 2 * 34 + 2 * GT : 3 * COLS;
-    static constexpr int oD = oT + tables, oE = oD + NW * GT, total = oE + (VEC == 0 && !SUM ? 1024 : 0);
+    static constexpr int oD = oT + tables, oE = oD + 2 * NW * GT, total = oE + (VEC == 0 && !SUM ? 1024 : 0);
     static constexpr int bytes = total * 4;
 };
 
@@ -226,7 +277,7 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
     float *Q = sm, *K = sm + Lds::oK, *V = sm + Lds::oV, *Pp = sm + Lds::oP;
     double* bs = reinterpret_cast<double*>(sm + Lds::oT);   // E_p [32], then the step's total
     float *wi = sm + Lds::oT + 68, *wo = wi + GT;           // e^{E_p}, e^{E - E_p}
-    float* dred = sm + Lds::oD;                             // [wave][32]: partial row products
+    double* dred = reinterpret_cast<double*>(sm + Lds::oD);  // [wave][32]: partial row products
     float* pw = sm + Lds::oE;                               // pair weights e^{E_n - E_r}, in the order of a score block's registers
 
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -242,7 +293,7 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
     f32x16 S[KB];
     _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) S[ib] = f32x16{0};
     if (!SUM) {
-        const float* e = s.wseg > 0 ? R.bound + (s.slot0 + s.wseg) * sz : R.edge_in ? R.edge_in + size_t(s.walk.edge) * sz : nullptr;
+        const float* e = s.wseg > 0 ? R.bound + bound_at(R.per, s.slot0, s.unit0, s.wseg) * sz : R.edge_in ? R.edge_in + size_t(s.walk.edge) * sz : nullptr;
         if (e) state_load(S, e, R.trans, a.kd, a.vd, 0, vcol + 32 * w, fresh() & 63);
     }
 
@@ -289,6 +340,16 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
     for (int kk = 0; kk < s.cnt; ++kk) {
         const ChunkPos cp = walk_step(d, s, rev, kk);
         const int L = cp.L;
+        if (!SUM && R.dot) {
+            const int u = unit_end(d, s, rev, kk);
+            if (u >= 0) {
+                const int lane = fresh() & 63;
+                double z = 0.0;  // (a sequence's last step starts from the edge state)
+                if (kk > 0 || s.wseg > 0 || R.edge_in) z = state_dot(S, R.dot + (s.unit0 + u) * sz, a.kd, 0, vcol + 32 * w, lane);
+                for (int off = 32; off > 0; off >>= 1) z += __shfl_xor(z, off, 64);
+                if (lane == 0) R.z[(s.unit0 + u) * (a.vd / 32) + vcol / 32 + w] = z;
+            }
+        }
         {
             const int tid = fresh();
             if (!SUM) rq.commit(Q, LQ, L, tid);
@@ -361,13 +422,13 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
             const int tok = rev ? L - 1 - n : n;           // token of this lane's position (n < L)
             const size_t orow = cp.tok0 + size_t(n < L ? tok : 0) * cp.ts;
             const size_t oel = orow * a.vd + vcol + 32 * w + 4 * half;  // + 8g: four consecutive output features
-            float t = 0.f;
+            double t = 0.0;
             _Pragma("unroll") for (int g = 0; g < 4; ++g) {
                 f32x4 o;
                 _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] = O[4 * g + j] + X[4 * g + j];
                 if (R.xdot) {
                     const f32x4 q4 = load4(static_cast<const TIO*>(R.aux) + oel + 8 * g);
-                    _Pragma("unroll") for (int j = 0; j < 4; ++j) t += q4[j] * o[j];
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) t += double(q4[j]) * double(o[j]);
                 }
                 const f32x4 z = *reinterpret_cast<const f32x4*>(V + n * LV + 32 * w + 8 * g + 4 * half);
                 _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] += pd * z[j];
@@ -394,20 +455,22 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
                 _Pragma("unroll") for (int x = 0; x < 16; ++x) S[ib][x] = fmaf(lam, S[ib][x], U[x]);
             }
         }
+        if (!SUM) {
+            const long long u = keep_slot(d, R, s, kk);
+            if (u >= 0) state_store(S, R.bound + u * sz, R.trans, a.kd, a.vd, 0, vcol + 32 * w, fresh() & 63);
+        }
         __syncthreads();  // (D) every read of this step's tiles is done
         if (!SUM && R.xdot && tid < L) {
-            float t = 0.f;
+            double t = 0.0;
             _Pragma("unroll") for (int u = 0; u < NW; ++u) t += dred[u * GT + tid];
-            R.xdot[size_t(slice) * d.BH() * d.T + cp.wtok0 + (rev ? L - 1 - tid : tid)] = t;
+            R.xdot[size_t(slice) * d.BH() * d.T + cp.wtok0 + (rev ? L - 1 - tid : tid)] = float(t);
         }
     }
 
     float* e = nullptr;
-    if (SUM) e = R.bound + (s.slot0 + s.wseg + 1) * sz;
+    if (SUM) e = R.bound + bound_at(R.per, s.slot0, s.unit0, s.wseg + 1) * sz;
     else if (s.empty || s.wseg == s.nsq - 1) e = R.edge_out ? R.edge_out + size_t(s.walk.edge) * sz : nullptr;
     if (e) state_store(S, e, R.trans, a.kd, a.vd, 0, vcol + 32 * w, fresh() & 63);
-    if (!SUM && R.end_slot && !s.empty && s.wseg == s.nsq - 1)
-        state_store(S, R.bound + (s.slot0 + s.nsq) * sz, R.trans, a.kd, a.vd, 0, vcol + 32 * w, fresh() & 63);
     if (SUM && slice == 0 && d.kind != 0 && tid == 0) R.gseg[s.slot0 + s.wseg] = gtot;
 }
 
@@ -452,7 +515,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
     f32x16 S[KB];
     _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) S[ib] = f32x16{0};
     if (!SUM) {
-        const float* e = s.wseg > 0 ? R.bound + (s.slot0 + s.wseg) * sz : R.edge_in ? R.edge_in + size_t(s.walk.edge) * sz : nullptr;
+        const float* e = s.wseg > 0 ? R.bound + bound_at(R.per, s.slot0, s.unit0, s.wseg) * sz : R.edge_in ? R.edge_in + size_t(s.walk.edge) * sz : nullptr;
         if (e) state_load(S, e, R.trans, a.kd, a.vd, kcol, vcol + 32 * w, fresh() & 63);
     }
 
@@ -497,6 +560,22 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                 _Pragma("unroll") for (int j = 0; j < 4; ++j) S[ib][4 * g + j] = fmaf(m[j], S[ib][4 * g + j], U[4 * g + j]);
             }
         }
+    };
+    // the product with the other direction's state at the unit end that the kk-th step starts from
+    auto unit_dot = [&](int kk) {
+        if (SUM || VEC != 2 || !R.dot) return;
+        const int u = unit_end(d, s, rev, kk);
+        if (u < 0) return;
+        const int l = fresh() & 63;
+        double z = 0.0;
+        if (kk > 0 || s.wseg > 0 || R.edge_in) z = state_dot(S, R.dot + (s.unit0 + u) * sz, a.kd, kcol, vcol + 32 * w, l);
+        z += __shfl_xor(z, 32, 64);
+        if (l < 32) R.z[((s.unit0 + u) * 2 + (aux ? 1 : 0)) * a.vd + vcol + 32 * w + l] = z;
+    };
+    auto unit_keep = [&](int kk) {
+        if (SUM || VEC != 2) return;
+        const long long u = keep_slot(d, R, s, kk);
+        if (u >= 0) state_store(S, R.bound + u * sz, R.trans, a.kd, a.vd, kcol, vcol + 32 * w, fresh() & 63);
     };
     auto block_store = [&](const f32x16& P) {  // a block of registers to this wave's place among the partials
         const int lane = fresh() & 63;
@@ -624,6 +703,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
 
         if (s.cnt > 0) gload(0);
         for (int kk = 0; kk < s.cnt; ++kk) {
+            unit_dot(kk);
             commit(walk_step(d, s, rev, kk).L);
             __syncthreads();  // (A) rows and decay tables of this step are in LDS
             gload(kk + 1);
@@ -662,6 +742,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                 });
                 update();
             }
+            unit_keep(kk);
             __syncthreads();  // (C) every read of this step's tiles is done
         }
         if (SUM && slice == 0) {
@@ -709,6 +790,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
             f32x16 O, P;
             float pd = 0.f;
             f32x4 z[4];
+            unit_dot(kk);
             __syncthreads();  // (A)
             if constexpr (SUM) {
                 __syncthreads();  // (B)
@@ -766,6 +848,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                     });
                 }
                 update();
+                unit_keep(kk);
                 const int l = fresh() & 63;
                 _Pragma("unroll") for (int g = 0; g < 4; ++g) z[g] = *reinterpret_cast<const f32x4*>(V + (l & 31) * LV + 32 * w + 8 * g + 4 * (l >> 5));
             }
@@ -795,11 +878,9 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
     }
 
     float* e = nullptr;
-    if (SUM) e = R.bound + (s.slot0 + s.wseg + 1) * sz;
+    if (SUM) e = R.bound + bound_at(R.per, s.slot0, s.unit0, s.wseg + 1) * sz;
     else if (s.empty || s.wseg == s.nsq - 1) e = R.edge_out ? R.edge_out + size_t(s.walk.edge) * sz : nullptr;
     if (e) state_store(S, e, R.trans, a.kd, a.vd, kcol, vcol + 32 * w, fresh() & 63);
-    if (!SUM && R.end_slot && !s.empty && s.wseg == s.nsq - 1)
-        state_store(S, R.bound + (s.slot0 + s.nsq) * sz, R.trans, a.kd, a.vd, kcol, vcol + 32 * w, fresh() & 63);
 }
 
 // States at the segment boundaries of a sequence, in walk order: E_0 = edge_in, E_{s+1} = e^{g_s} E_s + U_s, in place (slot
@@ -808,22 +889,24 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
 __global__ __launch_bounds__(256) void gk_scan(Dims d, GArgs a) {
     const GRole& R = a.role[blockIdx.z];
     const int q = blockIdx.y, sz = d.dk * d.dv;
-    int s0 = 0;
     SeqWalk w;
-    size_t slot0;
+    size_t slot0, unit0;
     if (!d.cu) {
         w = SeqWalk{q, q, 0, 0, 0, d.T};
         slot0 = size_t(q) * a.slots;
+        unit0 = size_t(q) * a.units;
     } else {
-        s0 = q / d.H;
-        w = SeqWalk{q % d.H, q, 0, 0, d.cu[s0], d.cu[s0 + 1]};
-        slot0 = size_t(q % d.H) * a.slots + seg_base(d, a.m, a.extra, s0);
+        const int s = q / d.H;
+        w = SeqWalk{q % d.H, q, 0, 0, d.cu[s], d.cu[s + 1]};
+        slot0 = size_t(q % d.H) * a.slots + seg_base(d, a.m, s);
+        unit0 = size_t(q % d.H) * a.units + d.cstart[s];
     }
+    unit0 *= dg_per(d);
     const int nsq = (w.tend - w.tbeg + d.gC * a.m - 1) / (d.gC * a.m);
     const int e = (blockIdx.x * 256 + threadIdx.x) * 4, i = e / d.dv, dkd = d.dkd();
     f32x4 E = {0.f, 0.f, 0.f, 0.f};
     if (R.edge_in) E = load4(R.edge_in + size_t(w.edge) * sz + e);
-    float* b = R.bound + slot0 * sz + e;
+    auto at = [&](int t) { return R.bound + bound_at(R.per, slot0, unit0, t) * sz + e; };
     // A batch of segments costs one memory latency: every load is issued before the first use.  The decays of the scalar
     // kinds are the same for a whole workgroup and come through the scalar cache.
     const double* gp = d.kind == 0 ? nullptr : R.gseg + slot0 * dkd;
@@ -834,7 +917,7 @@ __global__ __launch_bounds__(256) void gk_scan(Dims d, GArgs a) {
             double gl[AHEAD];
             _Pragma("unroll") for (int x = 0; x < AHEAD; ++x) {
                 const int t = min(s + x, nsq - 2);
-                u[x] = load4(b + size_t(t + 1) * sz);
+                u[x] = load4(at(t + 1));
                 if constexpr (decltype(vec)::value) gl[x] = gp[size_t(t) * dkd + i];
                 else gl[x] = gp ? gp[t] : 0.0;
             }
@@ -842,7 +925,7 @@ __global__ __launch_bounds__(256) void gk_scan(Dims d, GArgs a) {
                 if (s + x >= nsq - 1) break;
                 const float lam = expf(float(gl[x]));
                 _Pragma("unroll") for (int c = 0; c < 4; ++c) E[c] = lam * E[c] + u[x][c];
-                store4(b + size_t(s + x + 1) * sz, E);
+                store4(at(s + x + 1), E);
             }
         }
     };
@@ -850,78 +933,62 @@ __global__ __launch_bounds__(256) void gk_scan(Dims d, GArgs a) {
     else chain(std::false_type{});
 }
 
-// Decay gradient of a segment: dg_t = sum_{u >= t in the segment} (q_u.dq_u - k_u.dk_u) + <S_end, dS_end>, S_end / dS_end the
-// state and its gradient at the segment's end (vector kind: everything per key feature).  The per-token products come
-// from the dq and dk walkers without the pair (t, t), which is the same in both.  grid as the walkers' (one slice).
-struct GDgArgs { const float *xq, *xk, *bf, *br, *d_mT; float *dg, *dg_tok; int m, slots, extra, nslk; };
+// Decay gradient of a unit: dg_t = sum_{u >= t in the unit} (q_u.dq_u - k_u.dk_u) + <S_end, dS_end>, S_end / dS_end the
+// state and its gradient at the unit's end (vector kind: everything per key feature).  The per-token products come from
+// the dq and dk walkers without the pair (t, t), which is the same in both; the last term from the dk walker.
+// Scalar kinds: a wave per unit; vector kind: a workgroup.   grid: (ceil(units / 4) or units, heads or sequences)
+struct GDgArgs { const float *xq, *xk; const double* z; float *dg, *dg_tok; int units, nslk; };
 __global__ __launch_bounds__(256) void gk_dg(Dims d, GDgArgs a) {
-    __shared__ double cst[256];
     __shared__ double part[256];
-    const GSeg s = find_seg(d, a.m, a.slots, a.extra, blockIdx.x, blockIdx.y);
-    if (s.seg >= s.nsq) return;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, sz = d.dk * d.dv;
-    const bool last = s.seg == s.nsq - 1;
-    const float* S = a.bf + (s.slot0 + s.seg + 1) * sz;
-    const float* D = last ? (a.d_mT ? a.d_mT + size_t(s.w.edge) * sz : nullptr) : a.br + (s.slot0 + s.nsq - 1 - s.seg) * sz;
-    const int tb = s.w.tbeg + s.seg * a.m * d.gC, te = min(s.w.tend, tb + a.m * d.gC), len = te - tb;
-    const ChunkPos cp = chunk_pos_at(d, s.w.bh, tb, len, 0);
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), y = blockIdx.y, per = dg_per(d);
+    const int x = d.kind == 3 ? blockIdx.x : 4 * blockIdx.x + w;
+    if (x >= a.units * per) return;
+    int u = x, lo = 0, hi = d.T;
+    if (d.cu) {
+        const int s = last_seq(d, x, [&](int s) { return d.cstart[s] * per; });
+        u = x - d.cstart[s] * per;
+        lo = d.cu[s];
+        hi = d.cu[s + 1];
+    }
+    const int tb = lo + u * dg_unit(d), len = min(dg_unit(d), hi - tb);
+    if (len <= 0) return;
+    const ChunkPos cp = chunk_pos_at(d, y, tb, len, 0);
+    const size_t unit = size_t(y) * a.units * per + x;
     if (d.kind != 3) {
-        double z = 0.0;
-        if (D)
-            for (int e = tid * 4; e < sz; e += 1024) {
-                const f32x4 x = load4(S + e), y = load4(D + e);
-                z += double(x[0] * y[0] + x[1] * y[1]) + double(x[2] * y[2] + x[3] * y[3]);
-            }
-        part[tid] = z;
-        __syncthreads();
-        for (int h = 128; h > 0; h >>= 1) {
-            if (tid < h) part[tid] += part[tid + h];
-            __syncthreads();
-        }
-        if (w != 0) return;
-        double run = part[0];
+        double run = 0.0;
+        for (int i = 0; i < d.dk / 32; ++i) run += a.z[unit * (d.dk / 32) + i];
         const size_t plane = size_t(d.BH()) * d.T;
         for (int t0 = len - 1; t0 >= 0; t0 -= 64) {  // 64 tokens at a time, lane l = token t0 - l
             const int t = t0 - lane;
-            double x = 0.0;
+            double v = 0.0;
             if (t >= 0) {
                 const size_t row = cp.wtok0 + t;
-                for (int sl = 0; sl < a.nslk; ++sl) x += double(a.xq[sl * plane + row]) - double(a.xk[sl * plane + row]);
+                for (int sl = 0; sl < a.nslk; ++sl) v += double(a.xq[sl * plane + row]) - double(a.xk[sl * plane + row]);
             }
             for (int off = 1; off < 64; off <<= 1) {
-                const double y = __shfl_up(x, off, 64);
-                if (lane >= off) x += y;
+                const double o = __shfl_up(v, off, 64);
+                if (lane >= off) v += o;
             }
-            x += run;
+            v += run;
             if (t >= 0) {
-                if (d.kind == 2) a.dg[cp.tok0 + size_t(t) * cp.ts] = float(x);
-                else a.dg_tok[cp.wtok0 + t] = float(x);
+                if (d.kind == 2) a.dg[cp.tok0 + size_t(t) * cp.ts] = float(v);
+                else a.dg_tok[cp.wtok0 + t] = float(v);
             }
-            run = __shfl(x, 63, 64);
+            run = __shfl(v, 63, 64);
         }
         return;
     }
-    for (int i = w; i < d.dk; i += 4) {  // one key feature per wave
-        double z = 0.0;
-        if (D)
-            for (int c = lane * 4; c < d.dv; c += 256) {
-                const f32x4 x = load4(S + i * d.dv + c), y = load4(D + i * d.dv + c);
-                z += double(x[0] * y[0] + x[1] * y[1]) + double(x[2] * y[2] + x[3] * y[3]);
-            }
-        for (int off = 32; off > 0; off >>= 1) z += __shfl_xor(z, off, 64);
-        if (lane == 0) cst[i] = z;
-    }
     // feature i, group gr of the tokens: the group's sum first, then the suffix with the later groups' sums
-    const int i = tid % d.dk, ng = 256 / d.dk, gr = tid / d.dk, per = (len + ng - 1) / ng;
-    const int lo = min(len, gr * per), hi = min(len, lo + per);
+    const int i = tid % d.dk, ng = 256 / d.dk, gr = tid / d.dk, num = (len + ng - 1) / ng;
+    const int first = min(len, gr * num), end = min(len, first + num);
     const float *xq = a.xq + cp.wtok0 * d.dk + i, *xk = a.xk + cp.wtok0 * d.dk + i;
     double sum = 0.0;
-    _Pragma("unroll 8") for (int t = lo; t < hi; ++t) sum += double(xq[size_t(t) * d.dk]) - double(xk[size_t(t) * d.dk]);
+    _Pragma("unroll 8") for (int t = first; t < end; ++t) sum += double(xq[size_t(t) * d.dk]) - double(xk[size_t(t) * d.dk]);
     part[gr * d.dk + i] = sum;
     __syncthreads();
-    double run = cst[i];
-    for (int u = gr + 1; u < ng; ++u) run += part[u * d.dk + i];
-    _Pragma("unroll 8") for (int t = hi - 1; t >= lo; --t) {
+    double run = a.z[unit * 2 * d.dk + i] + a.z[(unit * 2 + 1) * d.dk + i];
+    for (int h = gr + 1; h < ng; ++h) run += part[h * d.dk + i];
+    _Pragma("unroll 8") for (int t = end - 1; t >= first; --t) {
         run += double(xq[size_t(t) * d.dk]) - double(xk[size_t(t) * d.dk]);
         a.dg[(cp.tok0 + size_t(t) * cp.ts) * d.dk + i] = float(run);
     }
@@ -961,7 +1028,7 @@ __global__ void k_chunk_starts(Dims d, int* __restrict__ cstart, int least) {
 // Segment plan: m units of gC tokens per segment.  Enough workgroups that the launch fills the chip with what fits on a
 // compute unit (two of the 128-wide walkers, four of the 64-wide ones), and no more boundary states than one per chunk of
 // the caller's chunk size, which is what lsm_chunk_fwd_workspace_bytes() has always reported.
-struct GPlan { int m, nseg, slots_f, slots_b; };
+struct GPlan { int m, nseg, units; };  // nseg: segments (and boundary slots), units: of gC tokens, per sequence or per head
 int slices(int width, bool narrow) { return narrow ? width / 64 : (width + 127) / 128; }
 GPlan gplan(const Dims& d) {
     const int units = (d.T + d.gC - 1) / d.gC, nsl = slices(d.dv, false), target = d.dv == 64 ? 1024 : 512;
@@ -972,45 +1039,47 @@ GPlan gplan(const Dims& d) {
         nseg = nseg > units ? units : nseg;
         p.m = (units + nseg - 1) / nseg;
         p.nseg = (units + p.m - 1) / p.m;
-        p.slots_f = p.nseg;
-        p.slots_b = p.nseg + 1;
+        p.units = units;
         return p;
     }
     const long long n = (long long)units + d.nseq, work = n * d.H * nsl;
     p.m = int((work + target - 1) / target);
     auto count = [&](int m) { return m == 1 ? int(n) : int(n / m) + d.nseq + 1; };
     while (count(p.m) > n) ++p.m;  // n: the chunks the workspace figure allows for
-    p.nseg = p.slots_f = count(p.m);
-    p.slots_b = p.slots_f + d.nseq;
+    p.nseg = count(p.m);
+    p.units = int(n);
     return p;
 }
 
-struct GWs { float *bound_f, *bound_r, *xq, *xk, *dg_tok; double *gseg_f, *gseg_r; size_t bytes; };
+struct GWs { float *bound_f, *bound_r, *xq, *xk, *dg_tok; double *gseg_f, *gseg_r, *z; size_t bytes; };
 GWs carve(const Dims& d, void* ws, bool bwd) {
     char* p = static_cast<char*>(ws);
     size_t off = 0;
     GWs w{};
     const GPlan gp = gplan(d);
     auto take = [&](size_t bytes) { char* r = p + off; off += align256(bytes); return r; };
-    const size_t slots = size_t(bwd ? gp.slots_b : gp.slots_f) * (d.nseq ? d.H : d.BH());
-    const bool bounds = bwd || gp.nseg > 1;
-    const size_t nb = bounds ? slots * d.dk * d.dv * 4 : 0, ng = bounds && d.kind != 0 ? slots * d.dkd() * 8 : 0;
-    w.bound_f = reinterpret_cast<float*>(take(nb));
+    const size_t rows = d.nseq ? d.H : d.BH(), slots = gp.nseg > 1 ? gp.nseg * rows : 0;
+    // backward: a state per decay-gradient unit, the segments' entry states among them
+    const size_t units = bwd && d.kind != 0 ? size_t(gp.units) * dg_per(d) * rows : 0;
+    const size_t st = size_t(d.dk) * d.dv * 4, ng = d.kind != 0 ? slots * d.dkd() * 8 : 0;
+    w.bound_f = reinterpret_cast<float*>(take((slots > units ? slots : units) * st));
     w.gseg_f = reinterpret_cast<double*>(take(ng));
     if (bwd) {
-        w.bound_r = reinterpret_cast<float*>(take(nb));
+        w.bound_r = reinterpret_cast<float*>(take(slots * st));
         w.gseg_r = reinterpret_cast<double*>(take(ng));
         const size_t tok = size_t(d.BH()) * d.T;
         const size_t nx = d.kind == 0 ? 0 : tok * (d.kind == 3 ? d.dk : slices(d.dk, false)) * 4;
         w.xq = reinterpret_cast<float*>(take(nx));
         w.xk = reinterpret_cast<float*>(take(nx));
+        w.z = reinterpret_cast<double*>(take(units * (d.kind == 3 ? 2 * d.dk : d.dk / 32) * 8));
         if (d.kind == 1) w.dg_tok = reinterpret_cast<float*>(take(tok * 4));
     }
     w.bytes = off;
     return w;
 }
 // The size the queries report: at least one fp32 state per chunk of the caller's chunk size (twice for the backward call)
-// and one running log-decay per token, as callers have always been told; the kernels above need less.
+// and one running log-decay per token, as callers have always been told; the kernels above need no more (but for packed
+// batches with more empty sequences than chunks).
 size_t reported(const Dims& d, bool bwd) {
     const size_t tok = size_t(d.BH()) * d.T, st = align256(size_t(d.BH()) * d.N * d.dk * d.dv * 4);
     size_t n = (d.kind != 0 ? align256(tok * d.dkd() * 8) : 0) + st;
@@ -1085,8 +1154,8 @@ hipError_t fwd_t(const Dims& d, const FwdArgs& f) {
     const GPlan gp = gplan(d);
     const dim3 grid(gp.nseg, d.nseq ? d.H : d.BH());
     GArgs a{};
-    a.g = f.g; a.kd = d.dk; a.vd = d.dv; a.m = gp.m; a.slots = gp.slots_f; a.extra = 0;
-    a.role[0] = GRole{f.q, f.k, f.v, nullptr, f.o, nullptr, f.m0, f.mT, w.bound_f, w.gseg_f, 0, 0, 0};
+    a.g = f.g; a.kd = d.dk; a.vd = d.dv; a.m = gp.m; a.slots = gp.nseg; a.units = gp.units;
+    a.role[0] = GRole{f.q, f.k, f.v, nullptr, f.o, nullptr, f.m0, f.mT, w.bound_f, w.gseg_f, 0, 0};
     if (gp.nseg > 1) {
         const hipError_t e = bounds<TIO>(d, a, 1, grid, f.stream);
         if (e != hipSuccess) return e;
@@ -1098,33 +1167,38 @@ template <typename TIO>
 hipError_t bwd_t(const Dims& d, const BwdArgs& b) {
     const GWs w = carve(d, b.ws, true);
     const GPlan gp = gplan(d);
-    const int slots = gp.slots_b, extra = 1;
-    const dim3 grid(d.nseq ? slots : gp.nseg, d.nseq ? d.H : d.BH());
+    const dim3 grid(gp.nseg, d.nseq ? d.H : d.BH());
     hipError_t e;
-    GArgs a{};
-    a.g = b.g; a.kd = d.dk; a.vd = d.dv; a.m = gp.m; a.slots = slots; a.extra = extra;
-    a.role[0] = GRole{nullptr, b.k, b.v, nullptr, nullptr, nullptr, b.m0, nullptr, w.bound_f, w.gseg_f, 0, 0, 0};
-    a.role[1] = GRole{nullptr, b.q, b.d_o, nullptr, nullptr, nullptr, b.d_mT, nullptr, w.bound_r, w.gseg_r, 1, 0, 0};
-    if (gp.nseg > 1 && (e = bounds<TIO>(d, a, 2, grid, b.stream)) != hipSuccess) return e;
     const bool want_dg = b.dg != nullptr;
+    const int per = want_dg ? gp.m * dg_per(d) : 0;
+    GArgs a{};
+    a.g = b.g; a.kd = d.dk; a.vd = d.dv; a.m = gp.m; a.slots = gp.nseg; a.units = gp.units;
+    a.role[0] = GRole{nullptr, b.k, b.v, nullptr, nullptr, nullptr, b.m0, nullptr, w.bound_f, w.gseg_f, 0, 0, per};
+    a.role[1] = GRole{nullptr, b.q, b.d_o, nullptr, nullptr, nullptr, b.d_mT, nullptr, w.bound_r, w.gseg_r, 1, 0};
+    if (gp.nseg > 1 && (e = bounds<TIO>(d, a, 2, grid, b.stream)) != hipSuccess) return e;
     float *xq = want_dg ? w.xq : nullptr, *xk = want_dg ? w.xk : nullptr;
-    const GRole dq{b.d_o, b.v, b.k, b.q, b.dq, xq, b.m0, nullptr, w.bound_f, nullptr, 0, 1, want_dg && b.d_mT != nullptr};
-    const GRole dk{b.v, b.d_o, b.q, b.k, b.dk, xk, b.d_mT, nullptr, w.bound_r, nullptr, 1, 1, 0};
-    const GRole dv{b.k, b.q, b.d_o, nullptr, b.dv, nullptr, b.d_mT, b.d_m0, w.bound_r, nullptr, 1, 0, 0};
-    a.kd = d.dv; a.vd = d.dk;
-    a.role[0] = dq; a.role[1] = dk; a.role[2] = dv;
-    const bool one = d.dk == d.dv && d.kind != 3;  // all three in one launch
-    if ((e = walks<TIO>(d, a, one ? 3 : 2, grid, b.stream)) != hipSuccess) return e;
-    if (!one) {
-        a.kd = d.dk; a.vd = d.dv;
-        a.role[0] = dv;
-        if ((e = walks<TIO>(d, a, 1, grid, b.stream)) != hipSuccess) return e;
+    const GRole dq{b.d_o, b.v, b.k, b.q, b.dq, xq, b.m0, nullptr, w.bound_f, nullptr, 0, 1, per, want_dg ? (b.d_mT ? 2 : 1) : 0};
+    const GRole dk{b.v, b.d_o, b.q, b.k, b.dk, xk, b.d_mT, nullptr, w.bound_r, nullptr, 1, 1, 0, 0, want_dg ? w.bound_f : nullptr, w.z};
+    const GRole dv{b.k, b.q, b.d_o, nullptr, b.dv, nullptr, b.d_mT, b.d_m0, w.bound_r, nullptr, 1, 0};
+    auto walk = [&](std::initializer_list<GRole> roles) {  // roles of one launch: the same widths
+        const bool grad = roles.begin()->trans != 0;
+        a.kd = grad ? d.dv : d.dk; a.vd = grad ? d.dk : d.dv;
+        std::copy(roles.begin(), roles.end(), a.role);
+        return walks<TIO>(d, a, int(roles.size()), grid, b.stream);
+    };
+    const bool one = d.dk == d.dv && d.kind != 3;  // one launch may hold dv as well
+    if (want_dg) {  // the dk walker reads what the dq walker leaves
+        if ((e = one ? walk({dq, dv}) : walk({dq})) != hipSuccess || (e = walk({dk})) != hipSuccess) return e;
+    } else if ((e = one ? walk({dq, dk, dv}) : walk({dq, dk})) != hipSuccess) {
+        return e;
     }
+    if (!one && (e = walk({dv})) != hipSuccess) return e;
     if (want_dg) {
-        const GDgArgs ga{w.xq, w.xk, w.bound_f, w.bound_r, b.d_mT, b.dg, w.dg_tok, gp.m, slots, extra, slices(d.dk, false)};
+        const GDgArgs ga{w.xq, w.xk, w.z, b.dg, w.dg_tok, gp.units, slices(d.dk, false)};
+        const int units = gp.units * dg_per(d);
         {
             ProfScope ps(KID_GEN_DG, b.stream);
-            hipLaunchKernelGGL(gk_dg, grid, dim3(256), 0, b.stream, d, ga);
+            hipLaunchKernelGGL(gk_dg, dim3(d.kind == 3 ? units : (units + 3) / 4, grid.y), dim3(256), 0, b.stream, d, ga);
         }
         if (d.kind == 1) {
             ProfScope ps(KID_HEAD_REDUCE, b.stream);

@@ -29,6 +29,30 @@ def test_segments_of_several_units(kind, shape):
     compare_case(x, chunk)
 
 
+@pytest.mark.parametrize("kind", [wl.KIND_SCALAR, wl.KIND_VECTOR])
+@pytest.mark.parametrize("chunk", [16, 64])
+def test_decay_gradient_error_does_not_grow_with_the_segment(kind, chunk):
+    """Four sequences alone are cut into segments of one unit; 256 copies of them (1024 recurrences) into one segment each.
+    Either way the decay gradient's sums run back over a chunk (at least 32 tokens), so its error against the oracle is the same but for
+    the rounding of the states they start from: a few percent (1.3 allowed).  Sums over the whole segment of 2048 tokens are
+    sqrt(2048 / 64) > 5 times as many roundings away."""
+    import torch
+    import paper_2503_05447_amd as pkg
+    from oracle import lsm_oracle_bwd
+    x = wl.make_inputs(1, 4, 2048, 64, 64, kind, dtype="f32", seed=2300 + kind, decay="weak", init_state=True, d_final=True)
+    want = lsm_oracle_bwd(x["q"], x["k"], x["v"], x["g"], kind, x["d_o"], x["m0"], x["d_mT"])["dg"]
+    t = to_device(x)
+    err = []
+    for copies in (1, 256):
+        c = {n: a.repeat(copies, *[1] * (a.dim() - 1)) for n, a in t.items()}
+        r = pkg.lsm_chunk_bwd(c["q"], c["k"], c["v"], c["g"], kind, c["d_o"], chunk, c["m0"], c["d_mT"])
+        torch.cuda.synchronize()
+        err.append(np.linalg.norm(host(r["dg"][-1:]) - want) / np.linalg.norm(want))
+        del c, r
+    print("dg 2-norm error: alone %.2e, one of 256 copies %.2e" % tuple(err))
+    assert err[1] <= 1.3 * err[0]
+
+
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("case", [("f32", 100, 64, 64, 64, 1), ("f32", 100, 64, 64, 128, 1), ("bf16", 40, 128, 128, 64, 1),
                                   ("bf16", 40, 128, 256, 64, 1), ("bf16", 3, 128, 128, 64, 1), ("bf16", 4, 128, 128, 64, 10)])
