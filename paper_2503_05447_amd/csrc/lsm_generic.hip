@@ -906,7 +906,9 @@ __global__ __launch_bounds__(256) void gk_scan(Dims d, GArgs a) {
     const int e = (blockIdx.x * 256 + threadIdx.x) * 4, i = e / d.dv, dkd = d.dkd();
     f32x4 E = {0.f, 0.f, 0.f, 0.f};
     if (R.edge_in) E = load4(R.edge_in + size_t(w.edge) * sz + e);
-    auto at = [&](int t) { return R.bound + bound_at(R.per, slot0, unit0, t) * sz + e; };
+    // bound_at() as a base and a stride (the rule itself in the loop: 11.8 -> 16.6 us, 28 segments of 32 sequences, d = 64)
+    const ptrdiff_t stride = ptrdiff_t(R.per ? R.per : 1) * sz;
+    float* b = R.bound + (R.per ? ptrdiff_t(unit0) - 1 : ptrdiff_t(slot0)) * sz + e;
     // A batch of segments costs one memory latency: every load is issued before the first use.  The decays of the scalar
     // kinds are the same for a whole workgroup and come through the scalar cache.
     const double* gp = d.kind == 0 ? nullptr : R.gseg + slot0 * dkd;
@@ -917,7 +919,7 @@ __global__ __launch_bounds__(256) void gk_scan(Dims d, GArgs a) {
             double gl[AHEAD];
             _Pragma("unroll") for (int x = 0; x < AHEAD; ++x) {
                 const int t = min(s + x, nsq - 2);
-                u[x] = load4(at(t + 1));
+                u[x] = load4(b + (t + 1) * stride);
                 if constexpr (decltype(vec)::value) gl[x] = gp[size_t(t) * dkd + i];
                 else gl[x] = gp ? gp[t] : 0.0;
             }
@@ -925,7 +927,7 @@ __global__ __launch_bounds__(256) void gk_scan(Dims d, GArgs a) {
                 if (s + x >= nsq - 1) break;
                 const float lam = expf(float(gl[x]));
                 _Pragma("unroll") for (int c = 0; c < 4; ++c) E[c] = lam * E[c] + u[x][c];
-                store4(at(s + x + 1), E);
+                store4(b + (s + x + 1) * stride, E);
             }
         }
     };
