@@ -28,8 +28,8 @@
 // family replaced: that shape 11.6 -> 0.72 ms; bf16 vector decay, 4 x 8 sequences of 2048, d_k = 64, d_v = 128: 7.2 -> 0.446 ms;
 // forward alone, 32 sequences of 1777, d = 64: 0.262 -> 0.051 ms; 2 sequences of 256, d = 64: 0.110 -> 0.025 ms.
 // Distance to 64-bit results against those kernels, 2-norm, weak to strong decays, 512 to 4096 tokens, chunks of 16 to 128: o, dq,
-// dk, dv and d_init_state 0.4 to 0.95 times (one case 1.08), dg 0.1 to 0.85 times (vector kind in chunks of 16: 1.04), the final
-// state 0.9 to 1.4 times (one rounding more: at most 3.7e-8 where it was 2.6e-8).
+// dk, dv and d_init_state 0.4 to 0.95 times (one case 1.09), dg 0.1 to 0.85 times (vector kind in chunks of 16: 1.04), the final
+// state 0.7 to 1.2 times (at most 5.5e-8 where it was 5.0e-8).
 #include "lsm_internal.h"
 
 #include <algorithm>
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
     extern __shared__ __align__(16) float sm[];
     float *Q = sm, *K = sm + Lds::oK, *V = sm + Lds::oV, *Pp = sm + Lds::oP;
     double* bs = reinterpret_cast<double*>(sm + Lds::oT);   // E_p [32], then the step's total
-    float *wi = sm + Lds::oT + 68, *wo = wi + GT;           // e^{E_p}, e^{E - E_p}
+    float *wi = sm + Lds::oT + 68, *wo = wi + GT;           // e^{E_p}, e^{E - E_p} (even positions, then odd ones)
     double* dred = reinterpret_cast<double*>(sm + Lds::oD);  // [wave][32]: partial row products
     float* pw = sm + Lds::oE;                               // pair weights e^{E_n - E_r}, in the order of a score block's registers
 
@@ -369,7 +369,7 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
             if (lane < GT) {
                 bs[n] = E;
                 wi[n] = expf(float(E));
-                wo[n] = expf(float(all - E));
+                wo[16 * (n & 1) + (n >> 1)] = expf(float(all - E));
                 if (n == 0) bs[GT] = all;
             }
             gtot += all;
@@ -441,17 +441,18 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
         }
         gload(kk + 1);  // the update outlasts a trip to memory and has the registers
         {   // S[i][v] = e^E S[i][v] + sum_t e^{E - E_t} y_t[i] z_t[v]; the step's own sum is formed by itself, so the state sees
-            // one rounding per step instead of one per token
+            // one rounding per step instead of one per token.  Tokens in order, the latest, which weigh most, last: what is added
+            // to them would round them again.
             const int lane = fresh() & 63, n = lane & 31, half = lane >> 5;
             float z[16];
             _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                const f32x4 e = *reinterpret_cast<const f32x4*>(wo + 8 * g + 4 * half);
-                _Pragma("unroll") for (int j = 0; j < 4; ++j) z[4 * g + j] = V[(8 * g + 4 * half + j) * LV + 32 * w + n] * e[j];
+                const f32x4 e = *reinterpret_cast<const f32x4*>(wo + 16 * half + 4 * g);
+                _Pragma("unroll") for (int j = 0; j < 4; ++j) z[4 * g + j] = V[(2 * (4 * g + j) + half) * LV + 32 * w + n] * e[j];
             }
             const float lam = expf(float(bs[GT]));
             _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) {
                 f32x16 U = {0};
-                _Pragma("unroll") for (int x = 0; x < 16; ++x) U = mfma2(K[hrow(x, half) * LQ + 32 * ib + n], z[x], U);
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) U = mfma2(K[(2 * x + half) * LQ + 32 * ib + n], z[x], U);
                 _Pragma("unroll") for (int x = 0; x < 16; ++x) S[ib][x] = fmaf(lam, S[ib][x], U[x]);
             }
         }
@@ -541,7 +542,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
         }
     };
     // S[i][v] = lam S[i][v] + sum_t Y[t][i] (w_t Z[t][v]); the step's own sum is formed by itself, so the state sees one
-    // rounding per step instead of one per token
+    // rounding per step instead of one per token (tokens in order: see gk_walk)
     auto update = [&]() {
         const float *Y = VEC == 1 ? W0 : K, *Z = VEC == 2 ? W0 : V;
         const int ldy = VEC == 1 ? LW : LQ, ldz = VEC == 2 ? LW : LV;
@@ -551,7 +552,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
             const int l = fresh() & 63, n = l & 31, half = l >> 5;
             f32x16 U = {0};
             _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-                const int t = hrow(x, half);
+                const int t = 2 * x + half;
                 U = mfma2(Y[t * ldy + kcol + 32 * ib + n], Z[t * ldz + 32 * w + n], U);
             }
             _Pragma("unroll") for (int g = 0; g < 4; ++g) {

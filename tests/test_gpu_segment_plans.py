@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import lsm_workloads as wl
-from lsm_testlib import check, compare_case, host, to_device
+from lsm_testlib import check, compare_case, gpu_forward, host, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -51,6 +51,23 @@ def test_decay_gradient_error_does_not_grow_with_the_segment(kind, chunk):
         del c, r
     print("dg 2-norm error: alone %.2e, one of 256 copies %.2e" % tuple(err))
     assert err[1] <= 1.3 * err[0]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("T", [511, 512])
+def test_final_state_is_rounded_once(T, d):
+    """Under a strong decay the last token makes up nearly all of the final state: one product, rounded once when it is added
+    (2-norm 2^-23 / sqrt(12) x 0.74 for mantissas spread evenly over their logarithm, 2.5e-8), last of the sum.  Anything that
+    is added after it rounds a second time: sqrt(2) as much, 3.6e-8.  The bound lies between, ragged last step or not."""
+    import torch
+    from oracle import lsm_oracle_fwd
+    x = wl.make_inputs(1, 16, T, d, d, wl.KIND_SCALAR, dtype="f32", seed=2400 + T + d, decay="strong4", init_state=True)
+    mT = gpu_forward(x, 64)[1]
+    torch.cuda.synchronize()
+    want = lsm_oracle_fwd(x["q"], x["k"], x["v"], x["g"], x["kind"], x["m0"])[1]
+    err = np.linalg.norm(host(mT) - want) / np.linalg.norm(want)
+    print("final state 2-norm error %.2e" % err)
+    assert err < 3.0e-8
 
 
 @pytest.mark.parametrize("kind", KINDS)
