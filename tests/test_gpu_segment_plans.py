@@ -53,6 +53,37 @@ def test_decay_gradient_error_does_not_grow_with_the_segment(kind, chunk):
     assert err[1] <= 1.3 * err[0]
 
 
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("case", [("f32", 64, 64, 64), ("f32", 128, 64, 64), ("f32", 64, 128, 16), ("bf16", 64, 64, 64), ("f32", 256, 64, 64)])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_non_finite_rows_do_not_reach_the_tokens_before_them(kind, case, value):
+    """One element of one token's q, k, v or d_o that is not finite, in the middle of a 32-token step: o and dq of earlier tokens
+    and dk and dv of later ones do not depend on it and come out bit for bit as without it; the token's own result is not finite."""
+    import torch
+    import paper_2503_05447_amd as pkg
+    dtype, dk, dv, chunk = case
+    T, s0, col = 97, 45, 37
+    x = wl.make_inputs(1, 2, T, dk, dv, kind, dtype=dtype, seed=2500, decay="weak", init_state=True, d_final=True)
+
+    def run(t):
+        o, _ = pkg.lsm_chunk_fwd(t["q"], t["k"], t["v"], t["g"], kind, chunk, t["m0"])
+        r = pkg.lsm_chunk_bwd(t["q"], t["k"], t["v"], t["g"], kind, t["d_o"], chunk, t["m0"], t["d_mT"])
+        return dict(r, o=o)
+    clean = run(to_device(x))
+    for name in ("q", "k", "v", "d_o"):
+        t = to_device(x)
+        t[name][:, :, s0, col] = value
+        got = run(t)
+        for out, keep in (("o", slice(0, s0)), ("dq", slice(0, s0)), ("dk", slice(s0 + 1, T)), ("dv", slice(s0 + 1, T))):
+            assert torch.equal(got[out][:, :, keep], clean[out][:, :, keep]), (name, out)
+        own = {"q": "o", "k": "o", "v": "o", "d_o": "dq"}[name]
+        assert not torch.isfinite(got[own][:, :, s0].float()).all(dim=-1).any(), name
+        if name == "v":  # one value column of o
+            other = [c for c in range(dv) if c != col]
+            assert torch.equal(got["o"][..., other], clean["o"][..., other])
+            assert not torch.isfinite(got["o"][:, :, s0:, col].float()).any()
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("T", [511, 512])
 def test_final_state_is_rounded_once(T, d):
