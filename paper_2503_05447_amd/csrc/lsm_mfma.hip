@@ -860,6 +860,12 @@ hipError_t vec_fwd(const Dims& d, const FwdArgs& a) {
 
 namespace {
 // ---- fused walkers: host side
+// Batch of the scan over segments.  Eight is the better one at most counts (us a launch, 8 against 24: 8 sequences in 17, 36, 55
+// segments 7.0, 10.9, 13.8 against 7.1, 11.6, 14.7; 4 in 126: 19.8 against 21.4; 64 in 8: 12.8 against 13.2).  Where the
+// segments are a multiple of 32, sequences lie a multiple of 2 MB apart and a batch of all of them falls on few memory channels:
+// the longer batch hides that (16 sequences in 32 segments 17.6 against 15.8, 12 in 32 13.9 against 13.1; 8 in 32 11.0 against 10.9,
+// 8 in 64 17.5 against 17.8).
+bool many_at_once(const Dims& d, const SegPlan& sp) { return !d.nseq && sp.nseg % 32 == 0 && d.seqs() > 8; }
 // entry states of the segments of one direction: summary pass, then the scan over segments
 template <bool REV>
 hipError_t walk_bounds(const Dims& d, hipStream_t st, const SegPlan& sp, const uint16_t* xk, const uint16_t* xv, const float* g,
@@ -890,7 +896,8 @@ hipError_t walk_bounds(const Dims& d, hipStream_t st, const SegPlan& sp, const u
         }
     }
     ProfScope ps(KID_WALK_SCAN, st);
-    hipLaunchKernelGGL(mk_bound_scan<REV>, dim3(D * D / kThreads, d.seqs()), block, 0, st, d, edge_in, bound, gseg, sp.m, sp.nseg, skip);
+    const auto scan = many_at_once(d, sp) ? mk_bound_scan<REV, true> : mk_bound_scan<REV, false>;
+    hipLaunchKernelGGL(scan, dim3(D * D / kThreads, d.seqs()), block, 0, st, d, edge_in, bound, gseg, sp.m, sp.nseg, skip);
     return hipSuccess;
 }
 

@@ -890,8 +890,11 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
 
 // Entry state of every segment from the segments' own contributions (left by the summary pass in the
 // slot of the segment that follows in walk order) and total log-decays: E' = e^{G} E + U, in walk order.
+// The contributions are read a batch of segments at a time before any of them is replaced: the reads of a batch do not
+// depend on each other, only the recurrence does (read - update - write in turn pays one memory latency per segment).
+// Eight at a time; MANY: 24 while there are that many left, which holds more registers (many_at_once).
 // grid: (128 * 128 / 256, seqs)
-template <bool REV>
+template <bool REV, bool MANY>
 __global__ __launch_bounds__(kThreads) void mk_bound_scan(Dims d, const float* __restrict__ edge_in, float* __restrict__ bound,
                                                           const float* __restrict__ gseg, int m, int nseg, int skip) {
     const int seq = blockIdx.y, e = blockIdx.x * kThreads + threadIdx.x;
@@ -902,9 +905,6 @@ __global__ __launch_bounds__(kThreads) void mk_bound_scan(Dims d, const float* _
     float* b = bound + slot * D * D + e;
     const float* gs = gseg + slot;
     float E = edge_in ? edge_in[edge_off(d, seq) + size_t(e / D) * D * d.vm + e % D] : 0.f;
-    // The contributions are read a batch of segments at a time before any of them is replaced: the reads of a batch do not
-    // depend on each other, only the recurrence does (read - update - write in turn pays one memory latency per segment).
-    // 24 at a time while there are many, eight for the rest (4 sequences in 125 segments: 23 -> 18 us a launch).
     auto batch = [&](auto size, int s0) {
         constexpr int G = decltype(size)::value;
         float u[G], w[G];
@@ -936,12 +936,14 @@ __global__ __launch_bounds__(kThreads) void mk_bound_scan(Dims d, const float* _
     };
     if (!REV) {
         int s0 = 0;
-        while (nsq - 1 - s0 > 8) s0 = batch(std::integral_constant<int, 24>{}, s0);
+        if constexpr (MANY)
+            while (nsq - 1 - s0 >= 24) s0 = batch(std::integral_constant<int, 24>{}, s0);
         while (s0 + 1 < nsq) s0 = batch(std::integral_constant<int, 8>{}, s0);
     } else {
         b[size_t(nsq - 1) * D * D] = E;
         int s0 = nsq - 1;  // slots below skip - 1 are entered by no walk
-        while (s0 - skip >= 8) s0 = batch(std::integral_constant<int, 24>{}, s0);
+        if constexpr (MANY)
+            while (s0 - skip + 1 >= 24) s0 = batch(std::integral_constant<int, 24>{}, s0);
         while (s0 >= skip) s0 = batch(std::integral_constant<int, 8>{}, s0);
     }
 }

@@ -29,6 +29,16 @@ def test_segments_of_several_units(kind, shape):
     compare_case(x, chunk)
 
 
+# the bf16 family's scan over segments: batches of eight, and of 24 (more than 8 sequences in 32 segments), either direction
+@pytest.mark.parametrize("kind", [wl.KIND_NONE, wl.KIND_HEAD, wl.KIND_SCALAR])
+@pytest.mark.parametrize("H,T", [(9, 2048), (9, 2000), (8, 2048), (9, 1088)])
+def test_scan_over_segments_in_batches(kind, H, T):
+    x = wl.make_inputs(1, H, T, 128, 128, kind, seed=2600 + T, decay="weak", init_state=True, d_final=True)
+    if kind == wl.KIND_HEAD:  # heads of one size, as in test_packed_batch_with_shared_segments
+        x["g"] = -np.linspace(0.05, 0.2, H, dtype=np.float32)
+    compare_case(x, 64)
+
+
 @pytest.mark.parametrize("kind", [wl.KIND_SCALAR, wl.KIND_VECTOR])
 @pytest.mark.parametrize("chunk", [16, 64])
 def test_decay_gradient_error_does_not_grow_with_the_segment(kind, chunk):
