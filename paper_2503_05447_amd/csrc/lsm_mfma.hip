@@ -307,7 +307,7 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
         // MODE 2 walks backward: it enters with the state of the last fine segment it covers
         const int nfine = (walk.n + sa.fine_m - 1) / sa.fine_m, per = sa.seg_m / sa.fine_m;
         const int f = MODE == 2 ? min(nfine, (seg + 1) * per) - 1 : seg * per;
-        const float* e = sa.seg_bound + (bound_slot(d, seq, sa.fine_m, sa.fine_n) + f) * D * D;
+        const float* e = sa.seg_bound + (bound_slot(d, walk, sa.fine_m, sa.fine_n) + f) * D * D;
         _Pragma("unroll") for (int r = 0; r < 16; ++r) {
             const int mm = 32 * mb + 8 * (r >> 2) + 4 * half + (r & 3), nn = 32 * nb + n;
             acc[r] = MODE == 0 ? e[mm * D + nn] : e[nn * D + mm];

@@ -305,7 +305,7 @@ __device__ __forceinline__ size_t edge_off(const Dims& d, int seq) { return (siz
 // REV: walk backward in time.  DEC: a decay is present.  SUMMARY: the state update alone, from a zero
 // state, result to a.bound / a.gseg.
 template <bool REV, bool DEC, bool SUMMARY, bool VSPLIT = false>
-__device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, int seq, int seg, unsigned char* smem) {
+__device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, const SeqWalk& walk, int seg, unsigned char* smem) {
     // LDS: SUMMARY: K | V | bs | wo;   else: Q | K | V | P head | P remainder | bs | wo
     uint16_t* Q = reinterpret_cast<uint16_t*>(smem);
     uint16_t* K = SUMMARY ? Q : Q + C * LD;
@@ -319,7 +319,6 @@ __device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, int 
     static_assert(!VSPLIT || SUMMARY, "two value planes: summary pass only");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 31, half = lane >> 5;
-    const SeqWalk walk = seq_walk(d, seq);
     const int nsq = (walk.n + a.m - 1) / a.m;  // segments of this sequence
     const int kbeg = seg * a.m, kend = min(walk.n, kbeg + a.m), cnt = kend - kbeg;
     const bool empty_seq = walk.n == 0 && seg == 0;  // packed input: the state passes through
@@ -334,8 +333,8 @@ __device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, int 
     f32x16 S[4];
     _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) S[ib] = f32x16{0};
     if (!SUMMARY) {
-        if (seg > 0) walk_state_load(S, a.bound + (bound_slot(d, seq, a.m, a.nseg) + seg) * D * D, false, wave, n, half);
-        else if (a.edge_in) walk_state_load(S, a.edge_in + edge_off(d, seq), false, wave, n, half, D * d.vm);
+        if (seg > 0) walk_state_load(S, a.bound + (bound_slot(d, walk, a.m, a.nseg) + seg) * D * D, false, wave, n, half);
+        else if (a.edge_in) walk_state_load(S, a.edge_in + edge_off(d, walk.edge), false, wave, n, half, D * d.vm);
     }
 
     TileRegs rq, rk, rv, rv2;
@@ -389,12 +388,12 @@ __device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, int 
 
     // ---- the state this walk ends with
     if (SUMMARY) {
-        const size_t slot = bound_slot(d, seq, a.m, a.nseg) + seg;
+        const size_t slot = bound_slot(d, walk, a.m, a.nseg) + seg;
         walk_state_store(S, a.bound + (REV ? slot - 1 : slot + 1) * D * D, false, wave, n, half);
         if (tid == 0) a.gseg[slot] = gtot;
         return;
     }
-    if (last && a.edge_out) walk_state_store(S, a.edge_out + edge_off(d, seq), false, wave, n, half, D * d.vm);
+    if (last && a.edge_out) walk_state_store(S, a.edge_out + edge_off(d, walk.edge), false, wave, n, half, D * d.vm);
 }
 
 // forward walker, or the summary pass of either direction (grid: segments x sequences)
@@ -402,7 +401,8 @@ template <bool REV, bool DEC, bool SUMMARY, bool VSPLIT = false>
 __global__ __launch_bounds__(kThreads, 2) void mk_walk(Dims d, WalkArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const SegIndex i = seg_index(d, a.m, blockIdx.x, blockIdx.y);
-    walk_body<REV, DEC, SUMMARY, VSPLIT>(d, a, i.seq, i.seg, smem);
+    if (i.seg < 0) return;
+    walk_body<REV, DEC, SUMMARY, VSPLIT>(d, a, i.walk, i.seg, smem);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -524,7 +524,9 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
     constexpr int NT = VSPLIT ? 256 : kGrad8Threads;  // threads that share the tile traffic
 
     const SegIndex si = seg_index(d, a.m, blockIdx.x, blockIdx.y);
-    const int seq = si.seq, seg = si.seg;
+    if (si.seg < 0) return;
+    const SeqWalk walk = si.walk;
+    const int seq = walk.edge, seg = si.seg;
     // the wave index as a scalar: the branch between the two groups is then a scalar branch (each group's barriers are
     // executed by its own waves only, whatever the compiler makes of the vector condition), and 32 * wave offsets are scalars
     const int tid = threadIdx.x, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave8 & 3;
@@ -543,7 +545,6 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             tt = 64 * wave + lane;
         }
     };
-    const SeqWalk walk = seq_walk(d, seq);
     const int kbeg = seg * a.m, kend = min(walk.n, kbeg + a.m), cnt = kend - kbeg;
     if (cnt <= 0) return;
 
@@ -632,7 +633,7 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
         {
             const int per = a.bound_per ? a.bound_per : 1;
             if (seg > 0)
-                walk_state_load(S, a.bound + (bound_slot(d, seq, a.m / per, a.bound_per ? a.bound_n : a.nseg) + seg * per) * D * D, true, wave, n, half);
+                walk_state_load(S, a.bound + (bound_slot(d, walk, a.m / per, a.bound_per ? a.bound_n : a.nseg) + seg * per) * D * D, true, wave, n, half);
             else if (a.edge_in) walk_state_load(S, a.edge_in + edge_off(d, seq), true, wave, n, half, D * d.vm);
         }
         float gval = 0.f;
@@ -901,7 +902,7 @@ __global__ __launch_bounds__(kThreads) void mk_bound_scan(Dims d, const float* _
     const SeqWalk walk = seq_walk(d, seq);
     const int nsq = (walk.n + m - 1) / m;
     if (nsq <= 1 && (!REV || nsq == 0)) return;  // forward, the first segment starts from edge_in itself
-    const size_t slot = bound_slot(d, seq, m, nseg);
+    const size_t slot = bound_slot(d, walk, m, nseg);
     float* b = bound + slot * D * D + e;
     const float* gs = gseg + slot;
     float E = edge_in ? edge_in[edge_off(d, seq) + size_t(e / D) * D * d.vm + e % D] : 0.f;
