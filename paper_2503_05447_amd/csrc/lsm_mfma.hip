@@ -21,8 +21,10 @@
 // read (frag_tr: lane = feature, 8 tokens), which needs no transposed copy.  Rounded products (scores,
 // decayed operands, states where it matters) are carried as a bf16 head plus a bf16 remainder and
 // cost two MFMAs.
+#include "../../include/lsm.h"
 #include "lsm_mfma_dev.h"
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <vector>
@@ -682,19 +684,28 @@ size_t even_slots(const Dims& d) {
 // A packed batch holds T tokens in all, not T per sequence: its segments are a 512th of all chunks.  Measured, forward,
 // d = 128: 8 sequences of 1 to 4096 tokens, 16 heads, 0.265 ms with the 37 chunks that the longest possible sequence would
 // be cut into and 0.093 with 6 (5: 0.097, 8: 0.094, 12: 0.123); 12 sequences of 500 to 5500, 32 heads, 0.35 -> 0.24.
+// A segment of one chunk, where the plan for equal sequences has longer ones, buys little for a scan twice as long: two, but
+// for batches that leave half of the chip idle (2 heads, 3432 + 11171 tokens: 52.3 us with one chunk, 41.6 with two; 8 heads, 608
+// + 785 + 767: 39.7 and 33.0; 2 heads, 12 sequences, 1483 tokens: 22.7 and 27.7).
 // The boundary states may take more than that plan's only where that one exceeds the built-in scratch of
-// lsm_chunk_fwd_noalloc, which so accepts what it always has.
+// lsm_chunk_fwd_noalloc, which so accepts what it always has: segments get longer until they fit, and from 512 recurrences
+// on, where that plan cuts nothing, a sequence is one segment.
 SegPlan seg_plan(const Dims& d) {
-    if (!d.nseq) return even_plan(d);
+    const SegPlan even_cut = even_plan(d);
+    if (!d.nseq) return even_cut;
     const int nmax = (d.T + C - 1) / C;
-    const size_t even = even_slots(d), state = size_t(D) * D * 4, kept = size_t(8) << 20;
-    const size_t most = even * state >= kept ? (even > 2048 ? even : 2048) : even;
+    const size_t even = even_slots(d), state = size_t(D) * D * 4;
+    const size_t most = even * state >= LSM_NOALLOC_SCRATCH_BYTES ? std::max(even, size_t(2048)) : even;
     // half a segment per sequence is left over on average: the workgroups that have work are to fit the chip at once
-    const long long work = (long long)d.N * d.H, wgs = kWalkTargetWgs - d.seqs() / 2 > 128 ? kWalkTargetWgs - d.seqs() / 2 : 128;
-    int m = int((work + wgs - 1) / wgs);
-    while (m < nmax && size_t(d.H) * head_slots(d, m) > most) ++m;
-    m = m > nmax ? nmax : m;
-    return SegPlan{m, (nmax + m - 1) / m};
+    const long long work = (long long)d.N * d.H, wgs = std::max(kWalkTargetWgs - d.seqs() / 2, 1);
+    long long m = (work + wgs - 1) / wgs;
+    if (work >= 128) m = std::max(m, (long long)std::min(2, even_cut.m));
+    if (size_t(d.H) * head_slots(d, int(m)) > most) {
+        const long long fit = (long long)(most / d.H) - d.nseq - 1;  // the least m with N / m <= fit
+        m = fit < 0 ? nmax : std::max(m, d.N / (fit + 1) + 1);
+    }
+    m = std::min(m, (long long)nmax);
+    return SegPlan{int(m), (nmax + int(m) - 1) / int(m)};
 }
 // boundary-state slots to allow for: what the plan needs, and no less than for sequences of equal length
 size_t bound_slots(const Dims& d, const SegPlan& sp) {

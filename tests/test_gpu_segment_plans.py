@@ -114,9 +114,9 @@ def test_final_state_is_rounded_once(T, d):
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("case", [("f32", 100, 64, 64, 64, 1), ("f32", 100, 64, 64, 128, 1), ("bf16", 40, 128, 128, 64, 1),
                                   ("bf16", 40, 128, 256, 64, 1), ("bf16", 3, 128, 128, 64, 1), ("bf16", 4, 128, 128, 64, 10),
-                                  ("bf16", 2, 128, 128, 64, 0), ("bf16", 8, 128, 128, 64, 0)])
+                                  ("bf16", 6, 128, 128, 64, 1), ("bf16", 2, 128, 128, 64, 0), ("bf16", 8, 128, 128, 64, 0)])
 def test_packed_batch_with_shared_segments(kind, case):
-    """Enough heads that a segment spans several chunks (the case of 3 heads: one chunk each; of 4 heads: several, and the
+    """Enough heads that a segment spans several chunks (the case of 3 heads: one chunk each; of 6: two; of 4: several, and the
     reverse scan in segments of them); empty sequences first, inside and last; sequences of one token.  times = 0: the batch
     seven times over, more sequences than a wave has lanes."""
     import torch
