@@ -294,7 +294,7 @@ struct GLds {
     static constexpr int WT = VEC == 0 ? 0 : GT * (COLS + 4), WN = VEC == 0 ? 0 : (SUM ? 1 : 2);
     static constexpr int oK = SUM ? 0 : GT * LQ, oV = oK + GT * LQ, oP = oV + GT * LV, oW = oP + (SUM ? 0 : NW * 1024);
     static constexpr int oT = oW + WN * WT;
-    static constexpr int tables = VEC == 0 ? 2 * 34 + 2 * GT : 3 * COLS;
+    static constexpr int tables = VEC == 0 ? 2 * 34 + 2 * GT : 5 * COLS;
     static constexpr int oD = oT + tables, oE = oD + 2 * NW * GT, total = oE + (VEC == 0 && !SUM ? 1024 : 0);
     static constexpr int bytes = total * 4;
 };
@@ -531,7 +531,8 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
     constexpr int ITEMS = (2 * COLS + NT - 1) / NT;
     extern __shared__ __align__(16) float sm[];
     float *Q = sm, *K = sm + Lds::oK, *V = sm + Lds::oV, *Pp = sm + Lds::oP, *W0 = sm + Lds::oW, *W1 = W0 + Lds::WT;
-    float *tot = sm + Lds::oT, *lamv = tot + 2 * COLS;      // half sums [2][COLS], e^E [COLS]
+    double* tot = reinterpret_cast<double*>(sm + Lds::oT);  // log-decay of either half of the step [2][COLS]
+    float* lamv = sm + Lds::oT + 4 * COLS;                  // e^E [COLS]
 
     // the wave index as a scalar: the branch between the groups is then a scalar branch
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave % NW;
@@ -676,7 +677,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                         t += double(dt[i][x]);
                     }
                     closing[i] = rev && L == GT && h ? closing_n[i] : 0.f;
-                    tot[h * COLS + item_col(tid, i)] = float(t + double(closing[i]));
+                    tot[h * COLS + item_col(tid, i)] = t + double(closing[i]);
                 }
             }
         };
@@ -690,7 +691,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
         };
         auto write_start = [&](float* o) {  // weight e^{E_p} from the start of the step; also e^E
             each([&](int i, int h, int c) {
-                const float t0 = tot[c];
+                const double t0 = tot[c];
                 double e = h ? t0 : 0.0;
                 _Pragma("unroll") for (int x = 0; x < 16; ++x) {
                     e += double(dt[i][x]);
@@ -698,15 +699,16 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                     const float wt = expf(float(e));
                     o[p * LW + c] = VEC == 1 ? Q[p * LQ + c] * wt : wt;
                 }
-                if (h == 0) lamv[c] = expf(t0 + tot[COLS + c]);
+                if (h == 0) lamv[c] = expf(float(t0 + tot[COLS + c]));
             });
         };
         auto write_end = [&](float* o) {  // weight e^{E - E_p} to the end of the step, on the state update's operand
             each([&](int i, int h, int c) {
-                double e = h ? closing[i] : tot[COLS + c];
+                double e = h ? double(closing[i]) : tot[COLS + c];
                 if (SUM && h == 0) {
-                    lamv[c] = expf(tot[c] + tot[COLS + c]);
-                    gtot[i] += double(tot[c]) + double(tot[COLS + c]);
+                    const double all = tot[c] + tot[COLS + c];
+                    lamv[c] = expf(float(all));
+                    gtot[i] += all;
                 }
                 _Pragma("unroll") for (int x = 15; x >= 0; --x) {
                     const int p = 16 * h + x;

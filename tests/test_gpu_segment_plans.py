@@ -63,6 +63,40 @@ def test_decay_gradient_error_does_not_grow_with_the_segment(kind, chunk):
     assert err[1] <= 1.3 * err[0]
 
 
+@pytest.mark.parametrize("T", [32, 33, 64, 512])
+@pytest.mark.parametrize("dk,dv", [(64, 64), (128, 128), (256, 64)])
+def test_vector_decay_sums_are_rounded_once(T, dk, dv):
+    """What a state alone contributes is e^{sum of log-decays} times it: the sum's one rounding to fp32 is the only one of its size.
+    The sums here are -64, -(64 + 2^-18) after the first 16 of 32 tokens from either end, and on, exactly representable, -(64 + 2^-17):
+    a half sum kept in fp32 comes out 2^-17 = 7.6e-6 off, and with it o, dq and both states.  Bound: expf (1 ulp), the matrix
+    products' and the state's roundings, together below 16 x 2^-24 = 9.5e-7."""
+    import torch
+    import paper_2503_05447_amd as pkg
+    H = 2 if T < 512 else 64
+    x = wl.make_inputs(1, H, T, dk, dv, wl.KIND_VECTOR, dtype="f32", seed=2800 + T, decay="zero", init_state=True, d_final=True)
+    g = x["g"]
+    g[:, :, 3:8] = -12.75
+    g[:, :, 10] = -(0.25 + 2.0 ** -18)   # sum of the first 16: -(64 + 2^-18)
+    if T > 16:
+        g[:, :, 16] = -2.0 ** -18
+    x["m0"] *= np.float32(2.0 ** 92)
+    x["v"][:] = 0
+    t = to_device(x)
+    o, mT = gpu_forward(x, 64, t)
+    dq = pkg.lsm_chunk_bwd(t["q"], t["k"], t["v"], t["g"], x["kind"], t["d_o"], 64, t["m0"], t["d_mT"])["dq"]
+    w = np.exp(np.cumsum(g.astype(np.float64), axis=2))
+    m0 = x["m0"].astype(np.float64)
+    for name, got, want in (("o", host(o), (x["q"].astype(np.float64) * w) @ m0), ("final_state", host(mT), w[:, :, -1, :, None] * m0),
+                            ("dq", host(dq), (x["d_o"].astype(np.float64) @ m0.swapaxes(2, 3)) * w)):
+        got, want = got[:, :, 20:], want[:, :, 20:]
+        if name == "final_state":
+            err = np.abs(got / want - 1).max()
+        else:
+            err = np.linalg.norm(got - want) / np.linalg.norm(want)
+        print(name, "%.2e" % err)
+        assert err < 16 * 2.0 ** -24, name
+
+
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("case", [("f32", 64, 64, 64), ("f32", 128, 64, 64), ("f32", 64, 128, 16), ("bf16", 64, 64, 64), ("f32", 256, 64, 64)])
 @pytest.mark.parametrize("value", [np.nan, np.inf])
