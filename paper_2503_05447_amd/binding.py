@@ -209,11 +209,19 @@ def _alloc_on(stream):
 _NO_CONTEXT = contextlib.nullcontext()
 
 
-def _stream_handle(stream):
-    if stream is not None:
-        return stream.cuda_stream
+@functools.lru_cache(maxsize=None)
+def _current_stream_handle():
+    """Function that returns the current stream's handle: without a Stream object where this torch can (the entry points are
+    not public), else through the public one."""
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    raw, device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
+
+
+def _stream_handle(stream):
+    return stream.cuda_stream if stream is not None else _current_stream_handle()()
 
 
 @functools.lru_cache(maxsize=256)

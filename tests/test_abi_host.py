@@ -192,3 +192,19 @@ def test_delta_rule_entry_points_reject_bad_arguments_before_any_launch():
     assert dbwd(gated, la=0x4200) == ERR_NULL       # d_log_alpha missing
     assert dbwd(ok, d_o=None) == ERR_NULL and dbwd(ok, dq=None) == ERR_NULL
     assert dbwd(ok, wsb=need_b - 1) == ERR_WS
+
+
+def test_current_stream_handle_without_the_private_entry_points(monkeypatch):
+    """A torch that lacks them: the handle comes from the public current_stream()."""
+    import types
+
+    import torch
+    for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.delattr(torch._C, n, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=0x1230))
+    binding._current_stream_handle.cache_clear()
+    try:
+        assert binding._stream_handle(None) == 0x1230
+    finally:
+        binding._current_stream_handle.cache_clear()
+    assert binding._stream_handle(types.SimpleNamespace(cuda_stream=0x4560)) == 0x4560
