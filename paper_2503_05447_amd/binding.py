@@ -210,18 +210,22 @@ _NO_CONTEXT = contextlib.nullcontext()
 
 
 @functools.lru_cache(maxsize=None)
-def _current_stream_handle():
-    """Function that returns the current stream's handle: without a Stream object where this torch can (the entry points are
-    not public), else through the public one."""
+def _raw_stream_calls():
+    """torch's calls for the current device and its current stream's handle without a Stream object; they are not public, None
+    where a torch lacks them."""
     import torch
     raw, device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
-    if raw is None or device is None:
-        return lambda: torch.cuda.current_stream().cuda_stream
-    return lambda: raw(device())
+    return (raw, device) if raw and device else (None, None)
 
 
 def _stream_handle(stream):
-    return stream.cuda_stream if stream is not None else _current_stream_handle()()
+    if stream is not None:
+        return stream.cuda_stream
+    raw, device = _raw_stream_calls()
+    if raw is not None:
+        return raw(device())
+    import torch
+    return torch.cuda.current_stream().cuda_stream
 
 
 @functools.lru_cache(maxsize=256)

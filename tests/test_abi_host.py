@@ -202,9 +202,9 @@ def test_current_stream_handle_without_the_private_entry_points(monkeypatch):
     for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
         monkeypatch.delattr(torch._C, n, raising=False)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=0x1230))
-    binding._current_stream_handle.cache_clear()
+    binding._raw_stream_calls.cache_clear()
     try:
         assert binding._stream_handle(None) == 0x1230
     finally:
-        binding._current_stream_handle.cache_clear()
+        binding._raw_stream_calls.cache_clear()
     assert binding._stream_handle(types.SimpleNamespace(cuda_stream=0x4560)) == 0x4560
