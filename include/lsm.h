@@ -106,7 +106,10 @@ typedef struct {
      * cu_seqlens (DEVICE pointer, n_seq + 1 ints, 16-byte aligned) holds the first token of each
      * sequence, cu_seqlens[0] = 0 <= ... <= cu_seqlens[n_seq] = T (content not checked).  Every
      * sequence is chunked on its own, so no chunk straddles a boundary; init_state, final_state and
-     * their gradients are then [n_seq,H,d_k,d_v].  The result equals n_seq separate calls.
+     * their gradients are then [n_seq,H,d_k,d_v].  The result equals n_seq separate calls up to
+     * rounding: how a sequence is cut into segments that run in parallel follows from the number of
+     * recurrences and tokens of the whole call, packed or not, so its last bits depend on what it is
+     * batched with (the same call gives the same bits).
      */
     int32_t  n_seq;
     int32_t  flags;       /* bitwise OR of lsm_flags; 0 = none                                   */
@@ -123,6 +126,8 @@ typedef struct {
  *   final_state NULL (not wanted) or [B,H,d_k,d_v] fp32: M_T             out
  *   workspace   device scratch of at least lsm_chunk_fwd_workspace_bytes(p); contents undefined after the call
  *   stream      hipStream_t, NULL = the default stream
+ * An element of q, k, v (or d_o) that is not finite reaches no result of a token before it (dk, dv: after it) on the
+ * kernels that compute in fp32 throughout (lsm_kernel_path(p) == 0); on the others it may reach every result of its chunk.
  * Returns an lsm_status.  On any error nothing has been enqueued, except for
  * LSM_ERR_LAUNCH, where earlier kernels of the call may have been.
  */

@@ -23,9 +23,9 @@
 // matrix cores straight out of the accumulators and nothing is split or rounded on the way.
 //
 // Bound: the fp32 matrix rate (155 TFLOP/s measured; half of it reached at 4 x 16 sequences of 2047 fp32 tokens, d = 128,
-// scalar decay: forward walk 0.136 ms, the three gradient walks 0.41 ms) and, for the vector kind, as much vector work.
+// scalar decay: forward walk 0.136 ms, the three gradient walks 0.46 ms) and, for the vector kind, as much vector work.
 // Forward + backward against one-thread-per-element kernels on the vector ALU with a state per chunk in memory, which this
-// family replaced: that shape 11.6 -> 0.72 ms; bf16 vector decay, 4 x 8 sequences of 2048, d_k = 64, d_v = 128: 7.2 -> 0.446 ms;
+// family replaced: that shape 11.6 -> 0.73 ms; bf16 vector decay, 4 x 8 sequences of 2048, d_k = 64, d_v = 128: 7.2 -> 0.443 ms;
 // forward alone, 32 sequences of 1777, d = 64: 0.262 -> 0.051 ms; 2 sequences of 256, d = 64: 0.110 -> 0.025 ms.
 // Distance to 64-bit results against those kernels, 2-norm, weak to strong decays, 512 to 4096 tokens, chunks of 16 to 128: o, dq,
 // dk, dv and d_init_state 0.4 to 0.95 times (one case 1.09), dg 0.1 to 0.85 times (vector kind in chunks of 16: 1.04), the final
@@ -717,7 +717,10 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                 }
             });
         };
-        auto write_level = [&](float* o, auto lvc) {  // products of at most 16 decays, from the reference outwards
+        // Products of at most 16 decays, from the reference outwards: a rounding per factor, where one exponential of the pair's
+        // difference has one for all and a rounded argument under strong decays.  Results are no further from 64 bits for it (512
+        // tokens, log-decays of -1e-3 to -20 a token: o and dv 0.4 to 0.9, dq and dk 0.5 to 1.0 times the error with exponentials).
+        auto write_level = [&](float* o, auto lvc) {
             constexpr int lv = decltype(lvc)::value;
             each([&](int i, int h, int c) {
                 _Pragma("unroll") for (int b = 0; b < 16; b += lv) {
@@ -1059,6 +1062,9 @@ __global__ void k_chunk_starts(Dims d, int* __restrict__ cstart, int least) {
 // Segment plan: m units of gC tokens per segment.  Enough workgroups that the launch fills the chip with what fits on a
 // compute unit (two of the 128-wide walkers, four of the 64-wide ones), and no more boundary states than one per chunk of
 // the caller's chunk size, which is what lsm_chunk_fwd_workspace_bytes() has always reported.
+// Half as many and twice as many workgroups, us a call: 32 sequences of 1777, d = 64, forward 72 / 55 / 55; 64 of 1024, d = 64, fp32,
+// 69 / 54 / 53; 32 of 2048, d_k = 64, d_v = 128, 85 / 71 / 82, vector kind with backward 544 / 439 / 479; 64 of 1000, d = 128, fp32,
+// 119 / 108 / 133.  Half is the better one for many short sequences (256 of 256, d = 128, fp32: 76 / 110 / 131).
 struct GPlan { int m, nseg, units; };  // nseg: segments (and boundary slots), units: of gC tokens, per sequence or per head
 int slices(int width, bool narrow) { return narrow ? width / 64 : (width + 127) / 128; }
 GPlan gplan(const Dims& d) {
@@ -1109,8 +1115,9 @@ GWs carve(const Dims& d, void* ws, bool bwd) {
     return w;
 }
 // The size the queries report: at least one fp32 state per chunk of the caller's chunk size (twice for the backward call)
-// and one running log-decay per token, as callers have always been told; the kernels above need no more (but for packed
-// batches with more empty sequences than chunks).
+// and one running log-decay per token, as callers have always been told (the forward figure also decides what fits the
+// built-in scratch of lsm_chunk_fwd_noalloc).  The forward kernels use less; the backward ones a state per decay-gradient unit
+// and per segment, and less than the figure too (but for packed batches with more empty sequences than chunks).
 size_t reported(const Dims& d, bool bwd) {
     const size_t tok = size_t(d.BH()) * d.T, st = align256(size_t(d.BH()) * d.N * d.dk * d.dv * 4);
     size_t n = (d.kind != 0 ? align256(tok * d.dkd() * 8) : 0) + st;

@@ -439,11 +439,10 @@ __global__ __launch_bounds__(512, 1) void mk_delta_walk8(Dims d, DeltaWalkArgs a
 }
 
 // Entry state of every segment: E_0 = M_0, E_{s+1} = A_s E_s + B_s (REV: from the last segment down, for the state
-// gradients), one workgroup per sequence, the product on the
-// matrix cores with both factors as bf16 head + remainder (three products; about 2^-16 relative).
-// LDS: A head | A remainder | E head | E remainder (128 x LD each).   grid: (seqs)
-// The value columns of E evolve independently: a workgroup chains 32 of them (grid: 4 x sequences), A and B of the next
-// segment requested while this one is multiplied.  Bound by the latency of that chain: 16 sequences of 2000 tokens in 16
+// gradients), the product on the matrix cores with both factors as bf16 head + remainder (three products; about 2^-16 relative).
+// LDS: A head | A remainder (128 x LD each) | E head | E remainder (128 x LDE each).   grid: (4, seqs)
+// The value columns of E evolve independently: a workgroup chains 32 of them, A and B of the next segment requested while
+// this one is multiplied.  Bound by the latency of that chain: 16 sequences of 2000 tokens in 16
 // segments, 0.144 ms with one workgroup per sequence and nothing requested ahead, 0.046 ms so.
 constexpr int LDE = 40;  // row stride of a 128 x 32 slice of E
 constexpr int kDeltaCombineLds = 2 * D * LD * 2 + 2 * D * LDE * 2;

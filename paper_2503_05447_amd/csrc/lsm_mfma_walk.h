@@ -396,7 +396,7 @@ __device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, cons
     if (last && a.edge_out) walk_state_store(S, a.edge_out + edge_off(d, walk.edge), false, wave, n, half, D * d.vm);
 }
 
-// forward walker, or the summary pass of either direction (grid: segments x sequences)
+// forward walker, or the summary pass of either direction (grid: segments x sequences; packed input: seg_index)
 template <bool REV, bool DEC, bool SUMMARY, bool VSPLIT = false>
 __global__ __launch_bounds__(kThreads, 2) void mk_walk(Dims d, WalkArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
