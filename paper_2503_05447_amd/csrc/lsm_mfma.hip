@@ -684,9 +684,11 @@ size_t even_slots(const Dims& d) {
 // A packed batch holds T tokens in all, not T per sequence: its segments are a 512th of all chunks.  Measured, forward,
 // d = 128: 8 sequences of 1 to 4096 tokens, 16 heads, 0.265 ms with the 37 chunks that the longest possible sequence would
 // be cut into and 0.093 with 6 (5: 0.097, 8: 0.094, 12: 0.123); 12 sequences of 500 to 5500, 32 heads, 0.35 -> 0.24.
-// A segment of one chunk, where the plan for equal sequences has longer ones, buys little for a scan twice as long: two, but
-// for batches that leave half of the chip idle (2 heads, 3432 + 11171 tokens: 52.3 us with one chunk, 41.6 with two; 8 heads, 608
-// + 785 + 767: 39.7 and 33.0; 2 heads, 12 sequences, 1483 tokens: 22.7 and 27.7).
+// A segment of one chunk, where the plan for equal sequences has longer ones, buys little for a scan twice as long: two, if the
+// sequences are long enough for the scan to count (32 chunks on average) and the batch for half of the chip.  One against two chunks,
+// forward / backward us: 2 heads, 3432 + 11171 tokens 52.7 / 112.3 against 43.1 / 88.6; 4 heads, 3000 + 2500 + 1200 42.7 / 86.6 against
+// 37.6 / 74.8; 2 heads, 2500 + 1700 + 3300 36.5 / 72.6 against 34.0 / 67.3; but 2 heads, 12 sequences of 1000 41.3 / 69.6 against
+// 38.5 / 78.3; 4 heads, 16 of 250 37.1 / 49.2 against 36.2 / 64.6.
 // The boundary states may take more than that plan's only where that one exceeds the built-in scratch of
 // lsm_chunk_fwd_noalloc, which so accepts what it always has: segments get longer until they fit, and from 512 recurrences
 // on, where that plan cuts nothing, a sequence is one segment.
@@ -699,7 +701,7 @@ SegPlan seg_plan(const Dims& d) {
     // half a segment per sequence is left over on average: the workgroups that have work are to fit the chip at once
     const long long work = (long long)d.N * d.H, wgs = std::max(kWalkTargetWgs - d.seqs() / 2, 1);
     long long m = (work + wgs - 1) / wgs;
-    if (work >= 128) m = std::max(m, (long long)std::min(2, even_cut.m));
+    if (nmax >= 32 * d.nseq && work >= 128) m = std::max(m, (long long)std::min(2, even_cut.m));
     if (size_t(d.H) * head_slots(d, int(m)) > most) {
         const long long fit = (long long)(most / d.H) - d.nseq - 1;  // the least m with N / m <= fit
         m = fit < 0 ? nmax : std::max(m, d.N / (fit + 1) + 1);

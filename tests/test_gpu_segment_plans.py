@@ -148,11 +148,11 @@ def test_final_state_is_rounded_once(T, d):
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("case", [("f32", 100, 64, 64, 64, 1), ("f32", 100, 64, 64, 128, 1), ("bf16", 40, 128, 128, 64, 1),
                                   ("bf16", 40, 128, 256, 64, 1), ("bf16", 3, 128, 128, 64, 1), ("bf16", 4, 128, 128, 64, 10),
-                                  ("bf16", 6, 128, 128, 64, 1), ("bf16", 2, 128, 128, 64, 0), ("bf16", 8, 128, 128, 64, 0),
+                                  ("bf16", 2, 128, 128, 64, 0), ("bf16", 8, 128, 128, 64, 0),
                                   ("bf16", 60, 64, 64, 64, 1), ("f32", 40, 256, 64, 64, 1), ("f32", 20, 128, 256, 64, 1),
                                   ("f32", 20, 64, 128, 16, 1), ("bf16", 30, 64, 128, 128, 1), ("f32", 5, 64, 64, 64, 0)])
 def test_packed_batch_with_shared_segments(kind, case):
-    """Enough heads that a segment spans several chunks (the case of 3 heads: one chunk each; of 6: two; of 4: several, and the
+    """Enough heads that a segment spans several chunks (the case of 3 heads: one chunk each; of 4 heads: several, and the
     reverse scan in segments of them); empty sequences first, inside and last; sequences of one token.  times = 0: the batch
     seven times over, more sequences than a wave has lanes."""
     import torch
@@ -207,6 +207,33 @@ def test_packed_batch_with_shared_segments(kind, case):
         tok = np.sqrt(np.mean(np.concatenate([np.atleast_1d(a) ** 2 for a in ref["dg_tok"]])))
         lim = {"f32": 1e-4, "bf16": 2e-2}[dtype] * np.maximum(np.abs(want), tok * np.sqrt(T))
         assert (np.abs(got - want) <= lim).all()
+
+
+@pytest.mark.parametrize("lens", [[2050, 2046], [1, 4095], [63, 65, 6016]])
+def test_packed_batch_of_few_long_sequences(lens):
+    """Either side of 32 chunks a sequence, where segments of one chunk become segments of two: against one call per sequence."""
+    import torch
+    import paper_2503_05447_amd as pkg
+    H, T, n = 4, sum(lens), len(lens)
+    x = wl.make_inputs(1, H, T, 128, 128, wl.KIND_SCALAR, seed=3000 + n, decay="default", init_state=False)
+    rng = np.random.default_rng(3001)
+    x["m0"] = (rng.standard_normal((n, H, 128, 128)) * 0.1).astype(np.float32)
+    x["d_mT"] = (rng.standard_normal((n, H, 128, 128)) * 0.1).astype(np.float32)
+    t = to_device(x)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    kw = {"cu_seqlens": torch.from_numpy(cu).to(t["q"].device)}
+    o, mT = pkg.lsm_chunk_fwd(t["q"], t["k"], t["v"], t["g"], wl.KIND_SCALAR, 64, t["m0"], **kw)
+    r = pkg.lsm_chunk_bwd(t["q"], t["k"], t["v"], t["g"], wl.KIND_SCALAR, t["d_o"], 64, t["m0"], t["d_mT"], **kw)
+    for s in range(n):
+        c = {m: t[m][:, :, cu[s]:cu[s + 1]].contiguous() for m in ("q", "k", "v", "g", "d_o")}
+        m0, dm = t["m0"][s:s + 1].contiguous(), t["d_mT"][s:s + 1].contiguous()
+        o1, mT1 = pkg.lsm_chunk_fwd(c["q"], c["k"], c["v"], c["g"], wl.KIND_SCALAR, 64, m0)
+        r1 = pkg.lsm_chunk_bwd(c["q"], c["k"], c["v"], c["g"], wl.KIND_SCALAR, c["d_o"], 64, m0, dm)
+        check("o", host(o[:, :, cu[s]:cu[s + 1]]), host(o1), "bf16")
+        check("final_state", host(mT[s:s + 1]), host(mT1), "bf16")
+        for m in ("dq", "dk", "dv", "dg"):
+            check(m, host(r[m][:, :, cu[s]:cu[s + 1]]), host(r1[m]), "bf16")
+        check("d_init_state", host(r["d_init_state"][s:s + 1]), host(r1["d_init_state"]), "bf16")
 
 
 @pytest.mark.parametrize("dtype,dk,dv", [("f32", 64, 64), ("f32", 128, 256), ("bf16", 64, 64), ("bf16", 128, 128), ("bf16", 128, 256)])
