@@ -689,6 +689,10 @@ size_t even_slots(const Dims& d) {
 // forward / backward us: 2 heads, 3432 + 11171 tokens 52.7 / 112.3 against 43.1 / 88.6; 4 heads, 3000 + 2500 + 1200 42.7 / 86.6 against
 // 37.6 / 74.8; 2 heads, 2500 + 1700 + 3300 36.5 / 72.6 against 34.0 / 67.3; but 2 heads, 12 sequences of 1000 41.3 / 69.6 against
 // 38.5 / 78.3; 4 heads, 16 of 250 37.1 / 49.2 against 36.2 / 64.6.
+// Sequences of up to four chunks on average stay whole if that leaves the batch for half of the chip: summary and scan cost more
+// than the chunks in a row.  Cut and whole: 16 heads, 12 sequences of 200 58 / 95 and 34 / 66; 32 heads, 4 of 100 37 / 51 and 23 /
+// 39; unequal ones are about even forward (32 heads, 400 + 107 + 80 + 213 41 / 59 and 43 / 88; 41 to 296 tokens, 7 of them, 52 / 86 and
+// 46 / 85), and with fewer workgroups cutting them is the better one (16 heads, 10 to 410 tokens, 6 of them, 39 / 63 and 43 / 73).
 // The boundary states may take more than that plan's only where that one exceeds the built-in scratch of
 // lsm_chunk_fwd_noalloc, which so accepts what it always has: segments get longer until they fit, and from 512 recurrences
 // on, where that plan cuts nothing, a sequence is one segment.
@@ -701,6 +705,8 @@ SegPlan seg_plan(const Dims& d) {
     // half a segment per sequence is left over on average: the workgroups that have work are to fit the chip at once
     const long long work = (long long)d.N * d.H, wgs = std::max(kWalkTargetWgs - d.seqs() / 2, 1);
     long long m = (work + wgs - 1) / wgs;
+    const int mean = (nmax + d.nseq - 1) / d.nseq;  // chunks of a sequence
+    if (mean <= 4 && work > 128 * mean) m = std::max(m, (long long)mean);
     if (nmax >= 32 * d.nseq && work >= 128) m = std::max(m, (long long)std::min(2, even_cut.m));
     if (size_t(d.H) * head_slots(d, int(m)) > most) {
         const long long fit = (long long)(most / d.H) - d.nseq - 1;  // the least m with N / m <= fit

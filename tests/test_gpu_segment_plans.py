@@ -148,7 +148,7 @@ def test_final_state_is_rounded_once(T, d):
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("case", [("f32", 100, 64, 64, 64, 1), ("f32", 100, 64, 64, 128, 1), ("bf16", 40, 128, 128, 64, 1),
                                   ("bf16", 40, 128, 256, 64, 1), ("bf16", 3, 128, 128, 64, 1), ("bf16", 4, 128, 128, 64, 10),
-                                  ("bf16", 2, 128, 128, 64, 0), ("bf16", 8, 128, 128, 64, 0),
+                                  ("bf16", 12, 128, 128, 64, 1), ("bf16", 2, 128, 128, 64, 0), ("bf16", 8, 128, 128, 64, 0),
                                   ("bf16", 60, 64, 64, 64, 1), ("f32", 40, 256, 64, 64, 1), ("f32", 20, 128, 256, 64, 1),
                                   ("f32", 20, 64, 128, 16, 1), ("bf16", 30, 64, 128, 128, 1), ("f32", 5, 64, 64, 64, 0)])
 def test_packed_batch_with_shared_segments(kind, case):
