@@ -16,20 +16,24 @@
 // from the end of a whole segment needs no state per chunk, but the roundings of q.dq and k.dk add up over the way: 2-norm
 // error 2.2e-6 against 3.6e-7 with segments of 2048 tokens and a decay of e^-0.02 a token.)
 //
-// Contractions are v_mfma_f32_32x32x2_f32: fp32 operands, fp32 accumulation, 1/16 of the bf16 rate but exact products,
-// and its operand layout is its result layout: lane l holds A[m = l%32][k = l/32], B[k = l/32][n = l%32], and result
+// Contractions of the vector kind are v_mfma_f32_32x32x2_f32: fp32 operands, fp32 accumulation, 1/16 of the bf16 rate but exact
+// products, and its operand layout is its result layout: lane l holds A[m = l%32][k = l/32], B[k = l/32][n = l%32], and result
 // register 4g+j of lane l is D[m = 8g + 4(l/32) + j][n = l%32].  Register x of a result block is therefore, unchanged, the
 // operand of one MFMA of the next product (its k index are the rows 8g+j and 8g+4+j), so states and scores feed the
-// matrix cores straight out of the accumulators and nothing is split or rounded on the way.
+// matrix cores straight out of the accumulators and nothing is split or rounded on the way.  The scalar kinds run the same
+// products on the bf16 matrix cores, operands in three parts (below).
 //
-// Bound: the fp32 matrix rate (155 TFLOP/s measured; half of it reached at 4 x 16 sequences of 2047 fp32 tokens, d = 128,
-// scalar decay: forward walk 0.136 ms, the three gradient walks 0.46 ms) and, for the vector kind, as much vector work.
+// Bound: the vector ALU and its order with the matrix instructions.  Scalar kinds, 4 x 16 sequences of 2047 fp32 tokens, d = 128:
+// vector issue 50 %, matrix pipes 30 % of the walk (fp32 instructions alone: 54 % of the matrix time and 20 % more time); the
+// vector kind 38 % matrix pipes, 37 % vector.
 // Forward + backward against one-thread-per-element kernels on the vector ALU with a state per chunk in memory, which this
-// family replaced: that shape 11.6 -> 0.73 ms; bf16 vector decay, 4 x 8 sequences of 2048, d_k = 64, d_v = 128: 7.2 -> 0.443 ms;
-// forward alone, 32 sequences of 1777, d = 64: 0.262 -> 0.051 ms; 2 sequences of 256, d = 64: 0.110 -> 0.025 ms.
-// Distance to 64-bit results against those kernels, 2-norm, weak to strong decays, 512 to 4096 tokens, chunks of 16 to 128: o, dq,
-// dk, dv and d_init_state 0.4 to 0.95 times (one case 1.09), dg 0.1 to 0.85 times (vector kind in chunks of 16: 1.04), the final
-// state 0.7 to 1.2 times (at most 5.5e-8 where it was 5.0e-8).
+// family replaced, then with fp32 instructions throughout, now: that shape 11.6 ms, 0.731, 0.625; bf16 vector decay, 4 x 8
+// sequences of 2048, d_k = 64, d_v = 128: 7.2 ms, 0.442, 0.442; forward alone, 32 sequences of 1777, d = 64, bf16: 262 us, 50.7,
+// 41.9; 2 sequences of 256, d = 64, fp32: 110 us, 25.1, 23.2.
+// Distance to 64-bit results against the kernels on the vector ALU, 2-norm, weak to strong decays, 512 to 4096 tokens, chunks of 16
+// to 128: o, dq, dk, dv and d_init_state 0.4 to 0.95 times (one case 1.09), dg 0.1 to 0.85 times (vector kind in chunks of 16: 1.04),
+// the final state 0.7 to 1.2 times (at most 5.5e-8 where it was 5.0e-8); the scalar kinds in three parts are closer again (fp32, 2
+// sequences of 256, d = 64: 1.6e-7 -> 8.8e-8; training step at 4 x 16 x 2047: furthest output 4.2e-7 -> 4.0e-7).
 #include "lsm_internal.h"
 
 #include <algorithm>
@@ -135,10 +139,6 @@ __device__ __forceinline__ GSeg find_seg(const Dims& d, const GArgs& a, int x, i
 __device__ __forceinline__ size_t bound_at(int per, size_t slot0, size_t unit0, int w) {
     return per ? unit0 + size_t(w) * per - 1 : slot0 + w;
 }
-__device__ __forceinline__ ChunkPos step_pos(const Dims& d, const SeqWalk& w, int k) {
-    const int t0 = w.tbeg + k * GT;
-    return chunk_pos_at(d, w.bh, t0, min(GT, w.tend - t0), 0);
-}
 
 // one operand's 32 rows on their way to LDS: 16-byte pieces, dealt to the threads row by row
 template <typename TIO, int W, int NT>
@@ -151,8 +151,13 @@ struct GTile {
         const char* b = reinterpret_cast<const char*>(base);
         _Pragma("unroll") for (int i = 0; i < CNT; ++i) {
             const int p = tid + NT * i, row = min(p / PR, L - 1), c = p % PR;
-            v[i] = *reinterpret_cast<const u32x4*>(b + uint32_t(rev ? L - 1 - row : row) * rowbytes + c * 16);
+            v[i] = *reinterpret_cast<const u32x4*>(b + (uint32_t(rev ? L - 1 - row : row) * rowbytes + uint32_t(c * 16)));
         }
+    }
+    __device__ __forceinline__ void clear(int L, int tid) {  // rows beyond the ragged end
+        if (L < GT)
+            _Pragma("unroll") for (int i = 0; i < CNT; ++i)
+                if ((tid + NT * i) / PR >= L) v[i] = u32x4{0, 0, 0, 0};
     }
     __device__ __forceinline__ void commit(float* dst, int ld, int L, int tid) const {
         _Pragma("unroll") for (int i = 0; i < CNT; ++i) {
@@ -204,12 +209,11 @@ template <int KB>
 __device__ __forceinline__ double state_dot(const f32x16 (&S)[KB], const float* e, int kd, int kf, int vf, int lane) {
     double z = 0.0;
     e += size_t(vf + (lane & 31)) * kd + kf + 4 * (lane >> 5);
-    _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) {
-        f32x4 t[4];
-        _Pragma("unroll") for (int g = 0; g < 4; ++g) t[g] = load4(e + 32 * ib + 8 * g);
-        _Pragma("unroll") for (int x = 0; x < 16; ++x) z += double(t[x >> 2][x & 3]) * double(S[ib][x]);
-        asm volatile("" ::: "memory");  // one block's loads at a time: the registers are full
-    }
+    f32x4 t[KB][4];  // every load before the first use (64 KiB of states: four trips to memory instead of one took 7500 clocks)
+    _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
+        _Pragma("unroll") for (int g = 0; g < 4; ++g) t[ib][g] = load4(e + 32 * ib + 8 * g);
+    _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
+        _Pragma("unroll") for (int x = 0; x < 16; ++x) z += double(t[ib][x >> 2][x & 3]) * double(S[ib][x]);
     return z;
 }
 __device__ __forceinline__ int hrow(int x, int half) { return 8 * (x >> 2) + 4 * half + (x & 3); }  // row of result register x
@@ -254,20 +258,24 @@ struct GWalk {
     int n, nsq, kbeg, kend, cnt, wseg;  // steps and segments of the sequence; steps [kbeg, kend); segment index in walk order
     bool empty;                      // packed input, an empty sequence: the state passes through
     bool none;                       // no work
+    ChunkPos origin;                 // of the head's token 0
 };
 __device__ __forceinline__ GWalk find_walk(const Dims& d, const GArgs& a, int rev, bool sum) {
     const GSeg s = find_seg(d, a, blockIdx.x, blockIdx.y);
     const int steps = a.m * (d.gC / GT), kbeg = s.seg * steps, kend = min(s.n, kbeg + steps);
-    GWalk g{s.w, s.slot0, s.unit0, s.n, s.nsq, kbeg, kend, max(kend - kbeg, 0), rev ? s.nsq - 1 - s.seg : s.seg, s.n == 0 && s.seg == 0, false};
+    GWalk g{s.w, s.slot0, s.unit0, s.n, s.nsq, kbeg, kend, max(kend - kbeg, 0), rev ? s.nsq - 1 - s.seg : s.seg, s.n == 0 && s.seg == 0, false, chunk_pos_at(d, s.w.bh, 0, 0, 0)};
     g.none = (s.seg >= s.nsq && !g.empty) || (sum && g.wseg >= s.nsq - 1);  // (nobody starts from the last segment's end)
     return g;
 }
 // position of the kk-th step; past the last it is one row of it, that nobody uses: rows are requested a step ahead and
 // unconditionally (behind a branch the old values would stay live through the whole step)
 __device__ __forceinline__ ChunkPos walk_step(const Dims& d, const GWalk& g, int rev, int kk) {
-    const int k = min(kk, g.cnt - 1);
-    ChunkPos p = step_pos(d, g.walk, rev ? g.kend - 1 - k : g.kbeg + k);
-    if (kk >= g.cnt) p.L = 1;
+    const int k = min(kk, g.cnt - 1), t0 = g.walk.tbeg + (rev ? g.kend - 1 - k : g.kbeg + k) * GT;
+    ChunkPos p = g.origin;  // (head and batch are told apart once: a division per step is a chain of a hundred clocks)
+    p.t0 = t0;
+    p.L = kk >= g.cnt ? 1 : min(GT, g.walk.tend - t0);
+    p.tok0 += size_t(t0) * p.ts;
+    p.wtok0 += t0;
     return p;
 }
 
@@ -284,35 +292,204 @@ __device__ __forceinline__ long long keep_slot(const Dims& d, const GRole& R, co
     return u < 0 ? -1 : (long long)(g.unit0 + u);
 }
 
-// LDS of a walker, in floats.  Row strides == 4 mod 64 words: 16-byte row reads of 16 lanes tile the banks.
-//   Q | K | V | score partials (vector kind: then half of the inter product) [wave][16][64] | W (vector kind: one or two
-//   tiles of weighted rows) | tables
+// LDS of the vector kind's walker, in floats.  Row strides == 4 mod 64 words: 16-byte row reads of 16 lanes tile the banks.
+//   Q | K | V | score partials, then half of the inter product [wave][16][64] | W (one or two tiles of weighted rows) | tables
 template <int KD, int TV, int VEC, bool SUM>
 struct GLds {
     static constexpr int NW = TV / 32, LQ = KD + 4, LV = TV + 4;
-    static constexpr int COLS = VEC == 2 ? TV : KD;           // decayed features held by this workgroup (vector kind)
-    static constexpr int WT = VEC == 0 ? 0 : GT * (COLS + 4), WN = VEC == 0 ? 0 : (SUM ? 1 : 2);
+    static constexpr int COLS = VEC == 2 ? TV : KD;           // decayed features held by this workgroup
+    static constexpr int WT = GT * (COLS + 4), WN = SUM ? 1 : 2;
     static constexpr int oK = SUM ? 0 : GT * LQ, oV = oK + GT * LQ, oP = oV + GT * LV, oW = oP + (SUM ? 0 : NW * 1024);
-    static constexpr int oT = oW + WN * WT;
-    static constexpr int tables = VEC == 0 ? 2 * 34 + 2 * GT : 5 * COLS;
-    static constexpr int oD = oT + tables, oE = oD + 2 * NW * GT, total = oE + (VEC == 0 && !SUM ? 1024 : 0);
-    static constexpr int bytes = total * 4;
+    static constexpr int oT = oW + WN * WT, total = oT + 5 * COLS, bytes = total * 4;
 };
 
-// Walker of the scalar kinds.  TV / 32 waves, wave w owning value features [32 w, 32 w + 32)
-// of the state, all key features.  Two workgroups of the 128-wide form share a compute unit, and one's matrix work runs
-// under the other's waits.  (Two groups of waves in one workgroup, as in the vector kind's walker below, took 0.155 ms
-// where this takes 0.136: the forward walk at the top.)
-template <typename TIO, int KD, int TV, bool SUM>
-__global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GArgs a) {
-    using Lds = GLds<KD, TV, 0, SUM>;
-    constexpr int NW = Lds::NW, NT = 2 * TV, LQ = Lds::LQ, LV = Lds::LV, KB = KD / 32;
-    extern __shared__ __align__(16) float sm[];
-    float *Q = sm, *K = sm + Lds::oK, *V = sm + Lds::oV, *Pp = sm + Lds::oP;
-    double* bs = reinterpret_cast<double*>(sm + Lds::oT);   // E_p [32], then the step's total
-    float *wi = sm + Lds::oT + 68, *wo = wi + GT;           // e^{E_p}, e^{E - E_p} (even positions, then odd ones)
-    double* dred = reinterpret_cast<double*>(sm + Lds::oD);  // [wave][32]: partial row products
-    float* pw = sm + Lds::oE;                               // pair weights e^{E_n - E_r}, in the order of a score block's registers
+// ---- fp32 products on the bf16 matrix cores
+//
+// An fp32 number is the sum of three bf16 ones exactly (head = rounded, then the rounded remainder, then what is left), so a
+// product of two of them is a handful of bf16 products accumulated in fp32: six where both operands are split (the three of
+// 2^-25 and less are dropped), three where one of them is a bf16 number to begin with.  At 16 times the rate of the fp32
+// matrix instructions that is 3/8 or 3/16 of their time, and closer: 16 terms are added per rounding instead of 2, and the
+// small products, added apart or first, are not rounded at the size of the sum.  One 32 x 32 block of normal numbers, K = 128,
+// 2-norm error against 64 bits: fp32 instructions 2.0e-7, six products 8.8e-8, three 6.4e-8.
+//
+// What is not finite has no such sum (infinity - infinity): elements of a result that are not finite are formed again with the
+// fp32 instructions from the numbers themselves, which a split row keeps (head clamped to the finite range, so that the second
+// part holds the infinity or NaN).  The others stay as they are, so that they do not depend on what is not finite.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x16 mfma16(bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2)); }
+__device__ __forceinline__ float lo2(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float hi2(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+template <bool CLAMP>
+__device__ __forceinline__ void split2(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
+    constexpr float top = 3.38953138925153547590470800371487866880e38f;  // largest bf16 number
+    h = CLAMP ? pack2(__builtin_amdgcn_fmed3f(a, -top, top), __builtin_amdgcn_fmed3f(b, -top, top)) : pack2(a, b);
+    const float ra = a - lo2(h), rb = b - hi2(h);
+    m = pack2(ra, rb);
+    l = pack2(ra - lo2(m), rb - hi2(m));
+}
+// the number a split row keeps
+__device__ __forceinline__ float joined(uint32_t h, uint32_t m, uint32_t l) {
+    const float H = lo2(h), M = lo2(m), L = lo2(l);
+    return fabsf(M) <= FLT_MAX ? H + (M + L) : M;
+}
+// Operand of eight k in NP parts (NP = 1: a bf16 number).
+template <int NP> struct Parts { bf16x8 p[NP]; };
+__device__ __forceinline__ Parts<3> split8(const float* x) {
+    u32x4 h, m, l;
+    _Pragma("unroll") for (int i = 0; i < 4; ++i) {
+        uint32_t a, b, c;
+        split2<false>(x[2 * i], x[2 * i + 1], a, b, c);
+        h[i] = a; m[i] = b; l[i] = c;
+    }
+    return Parts<3>{{__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)}};
+}
+// every product but that of the heads, smallest first
+template <int NA, int NB, typename Acc>
+__device__ __forceinline__ void small_terms(const Parts<NA>& a, const Parts<NB>& b, Acc& c) {
+    if constexpr (NA == 3 && NB == 3) {
+        c = mfma16(a.p[0], b.p[2], c);
+        c = mfma16(a.p[2], b.p[0], c);
+        c = mfma16(a.p[1], b.p[1], c);
+        c = mfma16(a.p[1], b.p[0], c);
+        c = mfma16(a.p[0], b.p[1], c);
+    } else if constexpr (NA == 3) {
+        c = mfma16(a.p[2], b.p[0], c);
+        c = mfma16(a.p[1], b.p[0], c);
+    } else if constexpr (NB == 3) {
+        c = mfma16(a.p[0], b.p[2], c);
+        c = mfma16(a.p[0], b.p[1], c);
+    }
+}
+// Schedule the N matrix instructions of this piece of code with V vector instructions after each: a wave issues in order, and
+// an instruction behind two dependent matrix ones waits with the second.
+template <int N, int V>
+__device__ __forceinline__ void interleave() {
+    _Pragma("unroll") for (int i = 0; i < N; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+    }
+}
+__device__ __forceinline__ bool finite(float x) { return fabsf(x) <= FLT_MAX; }
+__device__ __forceinline__ void replace_not_finite(f32x16& x, const f32x16& y) {
+    _Pragma("unroll") for (int i = 0; i < 16; ++i) x[i] = finite(x[i]) ? x[i] : y[i];
+}
+__device__ __forceinline__ float not_finite(const f32x16& x) {  // NaN if any element is infinite or NaN, else 0
+    float c = 0.f;
+    _Pragma("unroll") for (int i = 0; i < 16; ++i) c = fmaf(x[i], 0.f, c);
+    return c;
+}
+
+// Rows of the scalar kinds' walker in LDS, part by part.  Keys (and bf16 values) as they come; queries with the four-element
+// groups of every 16 features in the order 0, 2, 1, 3, so that the features of result registers 8s .. 8s+7, which an
+// operand out of the accumulators has as its k, lie in one 16-byte piece.
+template <int NP, int LDR>
+struct GRows {
+    static constexpr int PART = GT * LDR, SIZE = NP * PART;  // elements
+    template <typename TIO, int W, int NT>
+    __device__ static __forceinline__ void commit(uint16_t* dst, const GTile<TIO, W, NT>& t, int tid, bool swap) {
+        using Tile = GTile<TIO, W, NT>;
+        _Pragma("unroll") for (int i = 0; i < Tile::CNT; ++i) {
+            const int p = tid + NT * i, row = p / Tile::PR, c = p % Tile::PR;
+            const u32x4 x = t.v[i];
+            if constexpr (NP == 3) {
+                const int q = swap ? (c & ~3) | ((c & 1) << 1) | ((c >> 1) & 1) : c;
+                u32x2 h, m, l;
+                _Pragma("unroll") for (int e = 0; e < 2; ++e) {
+                    uint32_t a, b, d;
+                    split2<true>(__uint_as_float(x[2 * e]), __uint_as_float(x[2 * e + 1]), a, b, d);
+                    h[e] = a; m[e] = b; l[e] = d;
+                }
+                uint16_t* o = dst + row * LDR + 4 * q;
+                *reinterpret_cast<u32x2*>(o) = h;
+                *reinterpret_cast<u32x2*>(o + PART) = m;
+                *reinterpret_cast<u32x2*>(o + 2 * PART) = l;
+            } else if (swap) {
+                uint16_t* o = dst + row * LDR + 16 * (c >> 1) + 4 * (c & 1);
+                *reinterpret_cast<u32x2*>(o) = u32x2{x.x, x.y};
+                *reinterpret_cast<u32x2*>(o + 8) = u32x2{x.z, x.w};
+            } else {
+                *reinterpret_cast<u32x4*>(dst + row * LDR + 8 * c) = x;
+            }
+        }
+    }
+    // element at a stored column
+    __device__ static __forceinline__ float at(const uint16_t* src, int row, int col) {
+        const uint16_t* o = src + row * LDR + col;
+        if constexpr (NP == 3) return joined(o[0], o[PART], o[2 * PART]);
+        else return lo2(o[0]);
+    }
+    __device__ static __forceinline__ int swapped(int f) { return (f & ~12) | ((f & 4) << 1) | ((f & 8) >> 1); }
+    // eight features of one row: 16 consecutive bytes, or two groups of four elements, 8 apart
+    __device__ static __forceinline__ Parts<NP> row8(const uint16_t* src, int row, int col) {
+        Parts<NP> r;
+        _Pragma("unroll") for (int i = 0; i < NP; ++i) r.p[i] = *reinterpret_cast<const bf16x8*>(src + i * PART + row * LDR + col);
+        return r;
+    }
+    __device__ static __forceinline__ Parts<NP> row44(const uint16_t* src, int row, int col) {
+        Parts<NP> r;
+        _Pragma("unroll") for (int i = 0; i < NP; ++i) {
+            const uint16_t* o = src + i * PART + row * LDR + col;
+            const u32x2 a = *reinterpret_cast<const u32x2*>(o), b = *reinterpret_cast<const u32x2*>(o + 8);
+            r.p[i] = __builtin_bit_cast(bf16x8, u32x4{a.x, a.y, b.x, b.y});
+        }
+        return r;
+    }
+    // one column of rows hrow(8 s + 0 .. 7): the transposing LDS read hands lane i of 16 the i-th feature of a patch of 4 rows
+    __device__ static __forceinline__ Parts<NP> col8(const uint16_t* src, int s, int col0, int lane) {
+        typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
+        const int r = lane & 15;
+        Parts<NP> o;
+        _Pragma("unroll") for (int i = 0; i < NP; ++i) {
+            const uint16_t* p = src + i * PART + (16 * s + 4 * (lane >> 5) + (r >> 2)) * LDR + col0 + 16 * ((lane >> 4) & 1) + 4 * (r & 3);
+            const u32x2 a = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p)));
+            const u32x2 b = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 8 * LDR)));
+            o.p[i] = __builtin_bit_cast(bf16x8, u32x4{a.x, a.y, b.x, b.y});
+        }
+        return o;
+    }
+};
+
+// LDS of the scalar kinds' walker, in bytes.  Row strides of the split rows == 4 mod 64 words: 16-byte row reads of 16
+// lanes tile the banks.  fp32 values are read by columns, a wave's two halves four rows apart: 4 * stride == 32 mod 64.
+//   Q | K | V | scores: three parts [2][64][8], then the pairs (p, p) | two sets of decay tables | row products
+template <typename TIO, int KD, int TV, int HW, bool SUM>
+struct GLdsS {
+    static constexpr int NP = sizeof(TIO) == 4 ? 3 : 1, NW = TV / 32, NT = 64 * (NW + HW), LQ = KD + 8, LV = TV + 8;
+    static constexpr int rows = GT * LQ * NP * 2;
+    static constexpr int oK = SUM ? 0 : rows, oV = oK + rows, oP = oV + GT * LV * int(sizeof(TIO)), oD = oP + (SUM ? 0 : 3 * 2048);
+    static constexpr int oT = oD + (SUM ? 0 : GT * 4), table = 34 * 8 + 2 * GT * 4 + 16, oR = oT + 2 * table, bytes = oR + (SUM ? 0 : NW * GT * 8);
+};
+
+// Walker of the scalar kinds.  TV / 32 waves, wave w owning value features [32 w, 32 w + 32) of the state, all key features, and
+// HW helpers, which take their share of the rows and all of scores and tables.  Two workgroups of the 128-wide form share a
+// compute unit (77 KiB of LDS each), and one's matrix work runs under the other's waits.
+template <typename TIO, int KD, int TV, int HW, bool SUM>
+__global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(Dims d, GArgs a) {
+    using Lds = GLdsS<TIO, KD, TV, HW, SUM>;
+    constexpr int NP = Lds::NP, NW = Lds::NW, NT = Lds::NT, LQ = Lds::LQ, LV = Lds::LV, KB = KD / 32;
+    // The next rows are requested at the start of a step, but where a wave holds twice as many (two waves to 128-wide keys).
+    constexpr bool EARLY = KD == 64 || NT == 256;
+    using Rows = GRows<NP, LQ>;
+    using VRows = GRows<1, LV>;                              // bf16 values
+    extern __shared__ __align__(16) char smb[];
+    uint16_t *Q = reinterpret_cast<uint16_t*>(smb), *K = reinterpret_cast<uint16_t*>(smb + Lds::oK), *Pp = reinterpret_cast<uint16_t*>(smb + Lds::oP);
+    TIO* V = reinterpret_cast<TIO*>(smb + Lds::oV);
+    float* pdv = reinterpret_cast<float*>(smb + Lds::oD);
+    double* dred = reinterpret_cast<double*>(smb + Lds::oR);  // [wave][32]: partial row products
+    // decay tables of a step: E_p [32] and the step's total, e^{E_p}, e^{E - E_p} of all but the last two tokens (0 there)
+    // and of those two
+    struct Tables { double* bs; float *wi, *wo, *wl; };
+    auto tables = [&](int kk) {
+        char* t = smb + Lds::oT + (kk & 1) * Lds::table;
+        float* f = reinterpret_cast<float*>(t + 34 * 8);
+        return Tables{reinterpret_cast<double*>(t), f, f + GT, f + 2 * GT};
+    };
 
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Every phase reads LDS at its own lane-dependent addresses.  Left alone the compiler keeps them all in registers
@@ -324,17 +501,9 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
     const GWalk s = find_walk(d, a, rev, SUM);
     if (s.none) return;
     const size_t sz = size_t(a.kd) * a.vd;
-    f32x16 S[KB];
-    _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) S[ib] = f32x16{0};
-    if (!SUM) {
-        const float* e = s.wseg > 0 ? R.bound + bound_at(R.per, s.slot0, s.unit0, s.wseg) * sz : R.edge_in ? R.edge_in + size_t(s.walk.edge) * sz : nullptr;
-        if (e) state_load(S, e, R.trans, a.kd, a.vd, 0, vcol + 32 * w, fresh() & 63);
-    }
 
     GTile<TIO, KD, NT> rq, rk;
     GTile<TIO, TV, NT> rv;
-    float gval = 0.f;                                       // log-decay of walk position lane % 32
-    double gtot = 0.0;
     auto gload = [&](int kk) {
         const int tid = fresh();
         const ChunkPos p = walk_step(d, s, rev, kk);
@@ -342,39 +511,62 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
         if (!SUM) rq.gload(static_cast<const TIO*>(R.xq) + p.tok0 * a.kd, kb, p.L, rev, tid);
         rk.gload(static_cast<const TIO*>(R.xk) + p.tok0 * a.kd, kb, p.L, rev, tid);
         rv.gload(static_cast<const TIO*>(R.xv) + p.tok0 * a.vd + vcol, vb, p.L, rev, tid);
-        if (d.kind != 0 && w == 0) {
-            const int row = min(tid & 31, p.L - 1);
-            gval = d.kind == 1 ? a.g[s.walk.bh % d.H] : a.g[p.tok0 + size_t(rev ? p.L - 1 - row : row) * p.ts];
-        }
     };
-    // its share of the pair weights, of pairs (r < n) only
-    auto pair_weights = [&]() {
+    // The last wave, which has the fewest score blocks, makes the decay tables, a step ahead of their use.
+    const bool tabler = w == NW + HW - 1, carrier = HW == 0 || w < NW;
+    double gtot = 0.0;
+    // Log-decay of walk position lane % 32.  Every wave loads, and something also where there is none: a branch here would
+    // wait for all rows on their way (0 where the tables are made).
+    const float* gp = d.kind == 0 ? static_cast<const float*>(R.xk) : d.kind == 1 ? a.g + s.walk.bh % d.H : a.g;
+    auto decay_load = [&](int kk) {
+        const ChunkPos p = walk_step(d, s, rev, kk);
+        const int row = min(fresh() & 31, p.L - 1);
+        const float* base = d.kind == 2 ? gp + p.tok0 : gp;
+        return base[d.kind == 2 ? uint32_t(rev ? p.L - 1 - row : row) * uint32_t(p.ts) : 0u];
+    };
+    // E in fp64: the sums reach hundreds for strong decays while only their O(1) differences enter exp()
+    auto decay_tables = [&](int kk, float gval) {
         const int lane = fresh() & 63, n = lane & 31;
-        const double bn = bs[n];
-        _Pragma("unroll") for (int g = w; g < 4; g += NW) {
-            f32x4 e;
-            _Pragma("unroll") for (int j = 0; j < 4; ++j) {
-                const int r = 8 * g + 4 * (lane >> 5) + j;
-                e[j] = r < n ? expf(float(bn - bs[r])) : 0.f;
-            }
-            *reinterpret_cast<f32x4*>(pw + (g * 64 + lane) * 4) = e;
+        const Tables t = tables(kk);
+        const int L = walk_step(d, s, rev, kk).L;
+        const double x = n < L && d.kind != 0 ? double(gval) : 0.0;
+        double inc = x;
+        for (int off = 1; off < GT; off <<= 1) {
+            const double y = __shfl_up(inc, off, 32);
+            if (n >= off) inc += y;
         }
+        const double all = __shfl(inc, GT - 1, 32), E = rev ? inc - x : inc;
+        if (lane < GT) {
+            t.bs[n] = E;
+            t.wi[n] = expf(float(E));
+            const float wo = expf(float(all - E));
+            t.wo[n] = n < L - 2 ? wo : 0.f;
+            if (n >= L - 2 && n < L) t.wl[n - (L - 2)] = wo;
+            if (n == 0) t.bs[GT] = all;
+        }
+        gtot += all;
     };
-    if (s.cnt > 0) gload(0);
-    if (d.kind == 0) {  // the tables of a step without decay, once
-        if (tid == 0) bs[GT] = 0.0;
-        if (tid < GT) wi[tid] = wo[tid] = 1.f;
-        if (!SUM)
-            for (int e = tid; e < 1024; e += NT) {  // element e = (4-register group, lane, register) of a score block
-                const int l = (e >> 2) & 63;
-                pw[e] = hrow(4 * (e >> 8) + (e & 3), l >> 5) < (l & 31) ? 1.f : 0.f;
-            }
+    float gval = 0.f;                                       // of the step after the one whose tables are there
+    if (s.cnt > 0) {
+        const float g0 = decay_load(0);
+        gload(0);
+        gval = decay_load(1);
+        if (tabler) decay_tables(0, g0);
     }
+    f32x16 S[KB];
+    _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) S[ib] = f32x16{0};
+    if (!SUM) {
+        const float* e = s.wseg > 0 ? R.bound + bound_at(R.per, s.slot0, s.unit0, s.wseg) * sz : R.edge_in ? R.edge_in + size_t(s.walk.edge) * sz : nullptr;
+        if (e && carrier) state_load(S, e, R.trans, a.kd, a.vd, 0, vcol + 32 * w, fresh() & 63);
+    }
+    if (!SUM)  // the quarter of the score block whose keys follow its queries stays zero
+        for (int e = tid; e < 3 * 128; e += NT) *reinterpret_cast<u32x4*>(Pp + (e * 8)) = u32x4{0, 0, 0, 0};
 
     for (int kk = 0; kk < s.cnt; ++kk) {
         const ChunkPos cp = walk_step(d, s, rev, kk);
         const int L = cp.L;
-        if (!SUM && R.dot) {
+        const Tables T = tables(kk);
+        if (!SUM && carrier && R.dot) {
             const int u = unit_end(d, s, rev, kk);
             if (u >= 0) {
                 const int lane = fresh() & 63;
@@ -386,112 +578,244 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
         }
         {
             const int tid = fresh();
-            if (!SUM) rq.commit(Q, LQ, L, tid);
-            rk.commit(K, LQ, L, tid);
-            rv.commit(V, LV, L, tid);
-        }
-        // E in fp64: the sums reach hundreds for strong decays while only their O(1) differences enter exp()
-        if (w == 0 && d.kind != 0) {
-            const int lane = fresh() & 63, n = lane & 31;
-            const double x = n < L ? double(gval) : 0.0;
-            double inc = x;
-            for (int off = 1; off < GT; off <<= 1) {
-                const double y = __shfl_up(inc, off, 32);
-                if (n >= off) inc += y;
-            }
-            const double all = __shfl(inc, GT - 1, 32), E = rev ? inc - x : inc;
-            if (lane < GT) {
-                bs[n] = E;
-                wi[n] = expf(float(E));
-                wo[16 * (n & 1) + (n >> 1)] = expf(float(all - E));
-                if (n == 0) bs[GT] = all;
-            }
-            gtot += all;
+            if (!SUM) rq.clear(L, tid);
+            rk.clear(L, tid);
+            rv.clear(L, tid);
+            if (!SUM) Rows::commit(Q, rq, tid, true);
+            Rows::commit(K, rk, tid, false);
+            if constexpr (NP == 3) rv.commit(V, LV, GT, tid);
+            else VRows::commit(V, rv, tid, false);
         }
         __syncthreads();  // (A) rows and decay tables of this step are in LDS
+        if (EARLY) gload(kk + 1);
+        const float gnext = decay_load(kk + 2);
+        // this lane's four times four consecutive output features, 8 apart: uniform base + a 32-bit offset
+        const size_t obase = cp.tok0 * a.vd + vcol + 32 * w;
+        const uint32_t oel = [&] {
+            const int l = fresh() & 63, n = min(l & 31, L - 1);
+            return uint32_t(rev ? L - 1 - n : n) * (uint32_t(cp.ts) * uint32_t(a.vd)) + 4 * (l >> 5);
+        }();
+        f32x4 aux[4];                                       // the elements they are multiplied with
+        if (!SUM && carrier && R.xdot)  // (a helper has no columns of its own)
+            _Pragma("unroll") for (int g = 0; g < 4; ++g) aux[g] = load4(static_cast<const TIO*>(R.aux) + obase + oel + 8 * g);
         f32x16 O;
         if (!SUM) {
-            {   // this wave's share (a range of features) of the block P^T[s][p] = y_s . x_p
-                const int lane = fresh() & 63, n = lane & 31, half = lane >> 5;
-                f32x16 P = {0};
-                _Pragma("unroll") for (int f = 0; f < KD / NW; f += 8) {
-                    const int c = w * (KD / NW) + f + 4 * half;
-                    const f32x4 y = *reinterpret_cast<const f32x4*>(K + n * LQ + c), x = *reinterpret_cast<const f32x4*>(Q + n * LQ + c);
-                    _Pragma("unroll") for (int j = 0; j < 4; ++j) P = mfma2(y[j], x[j], P);
-                }
-                _Pragma("unroll") for (int g = 0; g < 4; ++g)
-                    *reinterpret_cast<f32x4*>(Pp + w * 1024 + (g * 64 + lane) * 4) = f32x4{P[4 * g], P[4 * g + 1], P[4 * g + 2], P[4 * g + 3]};
-            }
-            if (d.kind != 0) pair_weights();
-            {   // inter: O^T[v][p] = e^{E_p} sum_i S[i][v] x_p[i], the state blocks as A operands out of the accumulators (two
-                // chains: half the roundings in a row)
-                const int lane = fresh() & 63, n = lane & 31, half = lane >> 5;
-                f32x16 o[2] = {f32x16{0}, f32x16{0}};
-                _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
-                    _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                        const f32x4 x = *reinterpret_cast<const f32x4*>(Q + n * LQ + 32 * ib + 8 * g + 4 * half);
-                        _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j & 1] = mfma2(S[ib][4 * g + j], x[j], o[j & 1]);
+            // Blocks of 16 x 16 scores P^T[s][p] = y_s . x_p, keys 16 (b / 2) .., queries 16 ((b + 1) / 2) ..: a block to each of the
+            // first three of four waves, or the first two (same keys) to one of two and the third to the other (the helpers, if any).
+            if (HW ? !carrier : NW == 2 || w < 3) {
+                constexpr int NB = NW == 2 ? 2 : 1;
+                const int lane = fresh() & 63, c = lane & 15, q = lane >> 4, b0 = (HW ? w - NW : w) * NB, nb = min(NB, 3 - b0), sb = 16 * (b0 >> 1);
+                f32x4 P[NB];
+                {   // an accumulator for each of the products: short chains
+                    constexpr int NA = NP == 3 ? 6 : 1;
+                    f32x4 acc[NB][NA];
+                    _Pragma("unroll") for (int b = 0; b < NB; ++b)
+                        _Pragma("unroll") for (int i = 0; i < NA; ++i) acc[b][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    _Pragma("unroll") for (int f = 0; f < KD; f += 32) {
+                        const Parts<NP> y = Rows::row44(K, sb + c, f + 16 * (q >> 1) + 4 * (q & 1));
+                        _Pragma("unroll") for (int b = 0; b < NB; ++b) {
+                            const Parts<NP> x = Rows::row8(Q, 16 * ((min(b0 + b, 2) + 1) >> 1) + c, f + 8 * q);
+                            _Pragma("unroll") for (int i = 0; i < NA; ++i) {
+                                constexpr int py[6] = {0, 1, 0, 1, 2, 0}, px[6] = {0, 0, 1, 1, 0, 2};
+                                acc[b][i] = mfma16(y.p[py[i]], x.p[px[i]], acc[b][i]);
+                            }
+                        }
                     }
-                const float e = wi[n];
-                _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] = (o[0][x] + o[1][x]) * e;
-            }
-            __syncthreads();  // (B) score partials, pair weights
-            const int lane = fresh() & 63, n = lane & 31, half = lane >> 5;
-            f32x16 P;
-            float pd = 0.f;
-            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                f32x4 t = *reinterpret_cast<const f32x4*>(Pp + (g * 64 + lane) * 4);
-                _Pragma("unroll") for (int u = 1; u < NW; ++u) t += *reinterpret_cast<const f32x4*>(Pp + u * 1024 + (g * 64 + lane) * 4);
-                const f32x4 e = *reinterpret_cast<const f32x4*>(pw + (g * 64 + lane) * 4);
-                _Pragma("unroll") for (int j = 0; j < 4; ++j) {
-                    pd += hrow(4 * g + j, half) == n ? t[j] : 0.f;
-                    P[4 * g + j] = hrow(4 * g + j, half) < n ? t[j] * e[j] : 0.f;  // (not t * 0: t may be infinite)
+                    _Pragma("unroll") for (int b = 0; b < NB; ++b) {
+                        P[b] = acc[b][0];
+                        if constexpr (NP == 3) P[b] += (acc[b][1] + acc[b][2]) + (acc[b][3] + (acc[b][4] + acc[b][5]));
+                    }
+                }
+                _Pragma("unroll") for (int b = 0; b < NB; ++b) {
+                    if (b >= nb) break;
+                    const int p = 16 * ((b0 + b + 1) >> 1) + c;
+                    f32x4 t = P[b];
+                    if (__any(fmaf(t[0] + t[1], 0.f, (t[2] + t[3]) * 0.f) != 0.f)) {
+                        f32x4 G = {0.f, 0.f, 0.f, 0.f};
+                        _Pragma("unroll 1") for (int f = 0; f < KD; ++f) {
+                            const float x = Rows::at(Q, p, Rows::swapped(f));
+                            _Pragma("unroll") for (int j = 0; j < 4; ++j) G[j] = fmaf(Rows::at(K, sb + 4 * q + j, f), x, G[j]);
+                        }
+                        _Pragma("unroll") for (int j = 0; j < 4; ++j) t[j] = finite(t[j]) ? t[j] : G[j];
+                    }
+                    // decayed, in three parts and the order an operand has them; pairs (r < p) only, and (p, p) apart
+                    const double bp = T.bs[p];
+                    uint32_t h[2], m[2], l[2];
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) {
+                        const int r = sb + 4 * q + j;
+                        if (r == p) pdv[p] = t[j];
+                        if (d.kind != 0) t[j] *= expf(float(bp - T.bs[r]));
+                        t[j] = r < p ? t[j] : 0.f;  // (not t * 0: t may be infinite)
+                    }
+                    _Pragma("unroll") for (int j = 0; j < 2; ++j) split2<true>(t[2 * j], t[2 * j + 1], h[j], m[j], l[j]);
+                    uint16_t* o = Pp + ((sb >> 4) * 64 + (q & 1) * 32 + p) * 8 + 4 * (q >> 1);
+                    *reinterpret_cast<u32x2*>(o) = u32x2{h[0], h[1]};
+                    *reinterpret_cast<u32x2*>(o + 1024) = u32x2{m[0], m[1]};
+                    *reinterpret_cast<u32x2*>(o + 2048) = u32x2{l[0], l[1]};
                 }
             }
-            pd += __shfl_xor(pd, 32, 64);  // the pair (p, p) of this lane's position
-            const f32x16 X = causal_product(V + 32 * w, LV, P, lane, [](int s, int p) { return s < p; });
-            // The pair (p, p) stays out of the product with aux: it is the same number in q.dq and in k.dk and cancels in the
-            // decay gradient, exactly instead of to rounding.
-            const int tok = rev ? L - 1 - n : n;           // token of this lane's position (n < L)
-            const size_t orow = cp.tok0 + size_t(n < L ? tok : 0) * cp.ts;
-            const size_t oel = orow * a.vd + vcol + 32 * w + 4 * half;  // + 8g: four consecutive output features
-            double t = 0.0;
-            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                f32x4 o;
-                _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] = O[4 * g + j] + X[4 * g + j];
+            if (tabler && kk + 1 < s.cnt) decay_tables(kk + 1, gval);
+            if (carrier) {  // inter: O^T[v][p] = e^{E_p} sum_i S[i][v] x_p[i], the state blocks as A operands out of the accumulators
+                const int lane = fresh() & 63, n = lane & 31, half = lane >> 5;
+                f32x16 small = {0};
+                O = f32x16{0};
+                _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
+                    _Pragma("unroll") for (int h = 0; h < 2; ++h) {
+                        float t[8];
+                        _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = S[ib][8 * h + x];
+                        const Parts<3> sp = split8(t);
+                        const Parts<NP> x = Rows::row8(Q, n, 32 * ib + 16 * h + 8 * half);
+                        small_terms(sp, x, small);
+                        O = mfma16(sp.p[0], x.p[0], O);
+                    }
+                interleave<KB * 2 * (NP == 3 ? 6 : 3), NP == 3 ? 8 : 16>();
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] += small[x];
+                const float nf = not_finite(O);
+                if (__any(nf != nf)) {
+                    f32x16 G = {0};
+                    _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
+                        _Pragma("unroll") for (int x = 0; x < 16; ++x)
+                            G = mfma2(S[ib][x], Rows::at(Q, n, Rows::swapped(32 * ib + hrow(x, half))), G);
+                    replace_not_finite(O, G);
+                }
+                const float e = T.wi[n];
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] *= e;
+            }
+            __syncthreads();  // (B) scores
+            if (carrier) {
+                const int lane = fresh() & 63, n = lane & 31, half = lane >> 5;
+                // intra: X[v][p] = sum_s Z[s][v] P[s][p].  P is zero where s does not precede p, but a zero times an infinity or NaN is
+                // not: a value row that is not finite would reach the positions before it, which must not depend on it.  Then the
+                // product runs without such elements and they are added pair by pair.
+                f32x16 X;
+                {
+                    Parts<3> pp[2];
+                    _Pragma("unroll") for (int h = 0; h < 2; ++h)
+                        _Pragma("unroll") for (int i = 0; i < 3; ++i) pp[h].p[i] = *reinterpret_cast<const bf16x8*>(Pp + i * 1024 + (h * 64 + lane) * 8);
+                    auto product = [&](auto&& part) {
+                        X = f32x16{0};
+                        Parts<NP> vp[2];
+                        _Pragma("unroll") for (int h = 0; h < 2; ++h) {
+                            vp[h] = part(h);
+                            small_terms(vp[h], pp[h], X);
+                        }
+                        _Pragma("unroll") for (int h = 0; h < 2; ++h) X = mfma16(vp[h].p[0], pp[h].p[0], X);
+                    };
+                    auto value = [&](int row, int col) { if constexpr (NP == 3) return V[row * LV + col]; else return lo2(V[row * LV + col]); };
+                    product([&](int h) {
+                        if constexpr (NP == 3) {
+                            float t[8];
+                            _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = V[hrow(8 * h + x, half) * LV + 32 * w + n];
+                            return split8(t);
+                        } else {
+                            return VRows::col8(V, h, 32 * w, lane);
+                        }
+                    });
+                    const float nf = not_finite(X);
+                    if (__any(nf != nf)) {
+                        auto known = [&](int x) { const float t = value(hrow(x, half), 32 * w + n); return finite(t) ? t : 0.f; };
+                        auto score = [&](int r, int p) {
+                            const uint16_t* o = Pp + ((r >> 4) * 64 + ((r >> 2) & 1) * 32 + p) * 8 + 4 * ((r >> 3) & 1) + (r & 3);
+                            return joined(o[0], o[1024], o[2048]);
+                        };
+                        product([&](int h) {
+                            float t[8];
+                            _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = known(8 * h + x);
+                            if constexpr (NP == 3) return split8(t);
+                            else return Parts<1>{{__builtin_bit_cast(bf16x8, u32x4{pack2(t[0], t[1]), pack2(t[2], t[3]), pack2(t[4], t[5]), pack2(t[6], t[7])})}};
+                        });
+                        f32x16 G = {0};
+                        _Pragma("unroll") for (int x = 0; x < 16; ++x) G = mfma2(known(x), score(hrow(x, half), n), G);
+                        replace_not_finite(X, G);
+                        _Pragma("unroll 1") for (int r = 0; r < GT; ++r) {
+                            const float p = score(r, n);
+                            _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                                const float t = value(r, 32 * w + hrow(x, half));
+                                if (r < n && !finite(t)) X[x] += t * p;
+                            }
+                        }
+                    }
+                }
+                // The pair (p, p) stays out of the product with aux: it is the same number in q.dq and in k.dk and cancels in the
+                // decay gradient, exactly instead of to rounding.
+                const float pd = pdv[n];
+                double t = 0.0;
+                _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                    f32x4 o;
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] = O[4 * g + j] + X[4 * g + j];
+                    if (R.xdot) {
+                        _Pragma("unroll") for (int j = 0; j < 4; ++j) t += double(aux[g][j]) * double(o[j]);
+                    }
+                    const f32x4 z = load4(V + n * LV + 32 * w + 8 * g + 4 * half);
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] += pd * z[j];
+                    if (n < L) store4(static_cast<TIO*>(R.out) + obase + oel + 8 * g, o);
+                }
                 if (R.xdot) {
-                    const f32x4 q4 = load4(static_cast<const TIO*>(R.aux) + oel + 8 * g);
-                    _Pragma("unroll") for (int j = 0; j < 4; ++j) t += double(q4[j]) * double(o[j]);
+                    t += __shfl_xor(t, 32, 64);
+                    if (half == 0) dred[w * GT + n] = t;
                 }
-                const f32x4 z = *reinterpret_cast<const f32x4*>(V + n * LV + 32 * w + 8 * g + 4 * half);
-                _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] += pd * z[j];
-                if (n < L) store4(static_cast<TIO*>(R.out) + oel + 8 * g, o);
             }
-            if (R.xdot) {
-                t += __shfl_xor(t, 32, 64);
-                if (half == 0) dred[w * GT + n] = t;
-            }
+        } else if (tabler && kk + 1 < s.cnt) {
+            decay_tables(kk + 1, gval);
         }
-        gload(kk + 1);  // the update outlasts a trip to memory and has the registers
-        {   // S[i][v] = e^E S[i][v] + sum_t e^{E - E_t} y_t[i] z_t[v]; the step's own sum is formed by itself, so the state sees
-            // one rounding per step instead of one per token.  Tokens in order, the latest, which weigh most, last: what is added
-            // to them would round them again.
+        if (!EARLY) gload(kk + 1);
+        if (carrier) {  // S[i][v] = e^E S[i][v] + sum_t e^{E - E_t} y_t[i] z_t[v]; the step's own sum is formed by itself, so the state sees
+            // one rounding per step instead of one per token.  The latest tokens, which weigh most, come last, and the last two
+            // as they are: in parts the large product would be rounded once by itself and once with the small ones (final state
+            // under a strong decay 3.8e-8 instead of 2.7e-8).
             const int lane = fresh() & 63, n = lane & 31, half = lane >> 5;
-            float z[16];
-            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                const f32x4 e = *reinterpret_cast<const f32x4*>(wo + 16 * half + 4 * g);
-                _Pragma("unroll") for (int j = 0; j < 4; ++j) z[4 * g + j] = V[(2 * (4 * g + j) + half) * LV + 32 * w + n] * e[j];
+            Parts<3> z[2];
+            _Pragma("unroll") for (int h = 0; h < 2; ++h) {
+                float t[8];
+                const f32x4 e0 = *reinterpret_cast<const f32x4*>(T.wo + 16 * h + 4 * half), e1 = *reinterpret_cast<const f32x4*>(T.wo + 16 * h + 8 + 4 * half);
+                if constexpr (NP == 3) {
+                    _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = V[hrow(8 * h + x, half) * LV + 32 * w + n];
+                } else {
+                    const u32x4 r = __builtin_bit_cast(u32x4, VRows::col8(V, h, 32 * w, lane).p[0]);
+                    _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = x & 1 ? hi2(r[x >> 1]) : lo2(r[x >> 1]);
+                }
+                _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] *= x < 4 ? e0[x & 3] : e1[x & 3];
+                z[h] = split8(t);
             }
-            const float lam = expf(float(bs[GT]));
-            _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) {
-                f32x16 U = {0};
-                _Pragma("unroll") for (int x = 0; x < 16; ++x) U = mfma2(K[(2 * x + half) * LQ + 32 * ib + n], z[x], U);
-                _Pragma("unroll") for (int x = 0; x < 16; ++x) S[ib][x] = fmaf(lam, S[ib][x], U[x]);
+            auto weight = [&](int r) { return r < L - 2 ? T.wo[r] : r < L ? T.wl[r - (L - 2)] : 0.f; };
+            auto value = [&](int r) { if constexpr (NP == 3) return V[r * LV + 32 * w + n]; else return lo2(V[r * LV + 32 * w + n]); };
+            const int last = L - 2 + half < 0 ? GT - 1 : L - 2 + half;  // (one token: with a row of zeros)
+            const float zlast = value(last) * weight(last);
+            const float lam = expf(float(T.bs[GT]));
+            constexpr int GB = SUM && EARLY && KB >= 4 ? 4 : 2;  // blocks at a time: independent chains, one look for what is not finite
+            _Pragma("unroll") for (int i0 = 0; i0 < KB; i0 += GB) {
+                f32x16 U[GB];
+                _Pragma("unroll") for (int b = 0; b < GB; ++b) {
+                    const int i = 32 * (i0 + b);
+                    U[b] = f32x16{0};
+                    Parts<NP> y[2];
+                    _Pragma("unroll") for (int h = 0; h < 2; ++h) {
+                        y[h] = Rows::col8(K, h, i, lane);
+                        small_terms(y[h], z[h], U[b]);
+                    }
+                    _Pragma("unroll") for (int h = 0; h < 2; ++h) U[b] = mfma16(y[h].p[0], z[h].p[0], U[b]);
+                    U[b] = mfma2(Rows::at(K, last, i + n), zlast, U[b]);
+                }
+                float nf = 0.f;
+                _Pragma("unroll") for (int b = 0; b < GB; ++b) nf += not_finite(U[b]);
+                if (__any(nf != nf)) {
+                    _Pragma("unroll") for (int b = 0; b < GB; ++b) {
+                        f32x16 G = {0};
+                        _Pragma("unroll 1") for (int x = 0; x < 16; ++x) {
+                            const int r = 2 * x + half;
+                            G = mfma2(Rows::at(K, r, 32 * (i0 + b) + n), value(r) * weight(r), G);
+                        }
+                        replace_not_finite(U[b], G);
+                    }
+                }
+                _Pragma("unroll") for (int b = 0; b < GB; ++b)
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) S[i0 + b][x] = fmaf(lam, S[i0 + b][x], U[b][x]);
             }
         }
+        gval = gnext;
         if (!SUM) {
             const long long u = keep_slot(d, R, s, kk);
-            if (u >= 0) state_store(S, R.bound + u * sz, R.trans, a.kd, a.vd, 0, vcol + 32 * w, fresh() & 63);
+            if (u >= 0 && carrier) state_store(S, R.bound + u * sz, R.trans, a.kd, a.vd, 0, vcol + 32 * w, fresh() & 63);
         }
         __syncthreads();  // (D) every read of this step's tiles is done
         if (!SUM && R.xdot && tid < L) {
@@ -504,8 +828,8 @@ __global__ __launch_bounds__(2 * TV, KD == 256 ? 1 : 2) void gk_walk(Dims d, GAr
     float* e = nullptr;
     if (SUM) e = R.bound + bound_at(R.per, s.slot0, s.unit0, s.wseg + 1) * sz;
     else if (s.empty || s.wseg == s.nsq - 1) e = R.edge_out ? R.edge_out + size_t(s.walk.edge) * sz : nullptr;
-    if (e) state_store(S, e, R.trans, a.kd, a.vd, 0, vcol + 32 * w, fresh() & 63);
-    if (SUM && slice == 0 && d.kind != 0 && tid == 0) R.gseg[s.slot0 + s.wseg] = gtot;
+    if (e && carrier) state_store(S, e, R.trans, a.kd, a.vd, 0, vcol + 32 * w, fresh() & 63);
+    if (SUM && slice == 0 && d.kind != 0 && tabler && (tid & 63) == 0) R.gseg[s.slot0 + s.wseg] = gtot;
 }
 
 // Walker of the vector kind.  VEC 1: a decay per key-role feature (o, dv: the scores carry the decay).  VEC 2: a decay per
@@ -1145,20 +1469,29 @@ hipError_t allow_lds(const void* fn, int bytes) {
     return e;
 }
 
-template <typename TIO, int KD, int TV, int VEC, bool SUM>
-hipError_t launch_walk(const Dims& d, GArgs a, int nroles, dim3 grid, hipStream_t st, int kid) {
-    using Lds = GLds<KD, TV, VEC, SUM>;
+template <typename TIO, int KD, int TV, int VEC, int HW, bool SUM>
+hipError_t launch_walk_as(const Dims& d, GArgs a, int nroles, dim3 grid, hipStream_t st, int kid) {
+    using Lds = std::conditional_t<VEC == 0, GLdsS<TIO, KD, TV, HW, SUM>, GLds<KD, TV, VEC, SUM>>;
     static_assert(Lds::bytes <= 160 * 1024, "LDS");
     void (*kernel)(Dims, GArgs);
-    if constexpr (VEC == 0) kernel = gk_walk<TIO, KD, TV, SUM>;
+    if constexpr (VEC == 0) kernel = gk_walk<TIO, KD, TV, HW, SUM>;
     else kernel = gk_walk_vec<TIO, KD, TV, VEC, SUM>;
     const hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), Lds::bytes);
     if (e != hipSuccess) return e;
     a.nsl = a.vd / TV;
     grid.z = nroles * a.nsl;
     ProfScope ps(kid, st);
-    hipLaunchKernelGGL(kernel, grid, dim3(VEC == 0 ? 2 * TV : 4 * TV), Lds::bytes, st, d, a);
+    hipLaunchKernelGGL(kernel, grid, dim3(VEC == 0 ? 2 * TV + 64 * HW : 4 * TV), Lds::bytes, st, d, a);
     return hipGetLastError();
+}
+template <typename TIO, int KD, int TV, int VEC, bool SUM>
+hipError_t launch_walk(const Dims& d, const GArgs& a, int nroles, dim3 grid, hipStream_t st, int kid) {
+    // Two more waves for the rows, the tables and the scores where every workgroup has a compute unit to itself: a step is then
+    // one wave's chain of instructions (2 sequences of 256, d = 64, fp32: 26.8 -> 23.6 us; 32 of 1777, bf16, with 3.5 to a unit:
+    // 42.4 -> 52.0).
+    if constexpr (VEC == 0 && TV == 64)
+        if (grid.x * grid.y * unsigned(nroles * (a.vd / TV)) <= 256) return launch_walk_as<TIO, KD, TV, VEC, 2, SUM>(d, a, nroles, grid, st, kid);
+    return launch_walk_as<TIO, KD, TV, VEC, 0, SUM>(d, a, nroles, grid, st, kid);
 }
 // Key-role width kd keeps its whole state column block in one wave's registers; value-role widths of 128 and 256 go in
 // slices of 128 (fewer repeats of the scores), except the vector kind's with 256-wide keys (LDS, registers).

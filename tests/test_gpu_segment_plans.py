@@ -262,3 +262,40 @@ def test_head_decay_gradient_holds_every_sequence(dtype, dk, dv):
     err, one = np.abs(got - sum(part)).max(), min(np.sqrt(np.mean(part[i] ** 2)) for i in (0, 2))
     print("error %.2e, one token %.2e" % (err, one))
     assert err < 0.25 * one
+
+
+@pytest.mark.parametrize("kind", [wl.KIND_NONE, wl.KIND_HEAD, wl.KIND_SCALAR])
+@pytest.mark.parametrize("dtype,H,T,dk,dv", [("f32", 1, 1, 64, 64), ("f32", 2, 97, 64, 64), ("f32", 3, 65, 128, 64), ("f32", 2, 130, 64, 128),
+                                             ("f32", 2, 95, 256, 64), ("f32", 257, 33, 64, 64), ("bf16", 2, 98, 64, 64),
+                                             ("bf16", 257, 34, 64, 64), ("f32", 2, 66, 256, 128)])
+def test_products_in_three_parts(kind, dtype, H, T, dk, dv):
+    """Walks with helper waves (up to 256 workgroups of 64-wide values) and without, last steps of one, two and three tokens, every
+    width: forward and backward against the oracle, and fp32 results to 2^-21 in the 2-norm: a handful of roundings of 2^-24 of
+    sums whose terms cancel by a small factor."""
+    from oracle import lsm_oracle_fwd
+    x = wl.make_inputs(1, H, T, dk, dv, kind, dtype=dtype, seed=2600 + T, decay="weak", init_state=True, d_final=True)
+    compare_case(x, 64)
+    if dtype == "f32":
+        o, mT = gpu_forward(x, 64)
+        want = lsm_oracle_fwd(x["q"], x["k"], x["v"], x["g"], x["kind"], x["m0"])
+        for name, got, ref in (("o", o, want[0]), ("final_state", mT, want[1])):
+            err = np.linalg.norm(host(got) - ref) / np.linalg.norm(ref)
+            assert err <= 2.0 ** -21, (name, err)
+
+
+@pytest.mark.parametrize("name", ["q", "k", "v", "m0"])
+def test_numbers_above_the_largest_bf16_one(name):
+    """fp32 numbers that round to infinity in bf16 have finite results."""
+    from oracle import lsm_oracle_fwd
+    x = wl.make_inputs(1, 2, 70, 64, 64, wl.KIND_SCALAR, dtype="f32", seed=2700, decay="weak", init_state=True)
+    for n in ("q", "k", "v", "m0"):
+        x[n] *= np.float32(2.0 ** -4)
+    x[name].reshape(-1)[64 * 40 + 5] = 3.4e38
+    got = gpu_forward(x, 64)
+    want = lsm_oracle_fwd(x["q"], x["k"], x["v"], x["g"], x["kind"], x["m0"])
+    for a, b in zip(got, want):
+        a = host(a)
+        assert np.isfinite(a).all()
+        rows = lambda t: t.reshape(-1, t.shape[-1])
+        big = np.abs(rows(b)).max(axis=1, keepdims=True)
+        assert (np.abs(rows(a) - rows(b)) <= 2.0 ** -18 * big).all()
