@@ -305,16 +305,22 @@ struct GLds {
 
 // ---- fp32 products on the bf16 matrix cores
 //
-// An fp32 number is the sum of three bf16 ones exactly (head = rounded, then the rounded remainder, then what is left), so a
-// product of two of them is a handful of bf16 products accumulated in fp32: six where both operands are split (the three of
-// 2^-25 and less are dropped), three where one of them is a bf16 number to begin with.  At 16 times the rate of the fp32
-// matrix instructions that is 3/8 or 3/16 of their time, and closer: 16 terms are added per rounding instead of 2, and the
-// small products, added apart or first, are not rounded at the size of the sum.  One 32 x 32 block of normal numbers, K = 128,
-// 2-norm error against 64 bits: fp32 instructions 2.0e-7, six products 8.8e-8, three 6.4e-8.
+// An fp32 number of 2^-110 and more is the sum of three bf16 ones exactly (head = rounded, then the rounded remainder, then what
+// is left), so a product of two of them is a handful of bf16 products accumulated in fp32: six where both operands are split
+// (the three of 2^-25 and less are dropped), three where one of them is a bf16 number to begin with.  At 16 times the rate of
+// the fp32 matrix instructions that is 3/8 or 3/16 of their time, and closer: 16 terms are added per rounding instead of 2, and
+// the small products, added apart or first, are not rounded at the size of the sum.  One 32 x 32 block of normal numbers,
+// K = 128, 2-norm error against 64 bits: fp32 instructions 2.0e-7, six products 8.8e-8, three 6.4e-8.
 //
-// What is not finite has no such sum (infinity - infinity): elements of a result that are not finite are formed again with the
-// fp32 instructions from the numbers themselves, which a split row keeps (head clamped to the finite range, so that the second
-// part holds the infinity or NaN).  The others stay as they are, so that they do not depend on what is not finite.
+// Below that the last parts, or their low bits, would be under the smallest bf16 number.  So what is split is 2^24 times the
+// operand, which gives every normal number three parts that are normal, and the result's factor is taken out of the sum: the
+// same bits, over the whole range of fp32.  Cost, forward + backward, fp32, 4 x 16 sequences of 2047, d = 128: 598 -> 614 us;
+// forward, bf16, 32 sequences of 1777, d = 64: 44.2 -> 45.4.
+//
+// What is not finite has no such sum (infinity - infinity), and 2^24 times a number of 2^104 and more is not: elements of a result
+// that are not finite are formed again with the fp32 instructions from the numbers themselves (rows and states from where they
+// came from, a score from its parts, which then hold its bits).  The others stay as they are, so that they do not depend on
+// what is not finite.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -325,26 +331,21 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) { return __
 __device__ __forceinline__ uint32_t pack2(float lo, float hi) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2)); }
 __device__ __forceinline__ float lo2(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi2(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-template <bool CLAMP>
+constexpr float kUp = 0x1p24f, kDown = 0x1p-24f;  // factor of an operand before it is split
 __device__ __forceinline__ void split2(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
-    constexpr float top = 3.38953138925153547590470800371487866880e38f;  // largest bf16 number
-    h = CLAMP ? pack2(__builtin_amdgcn_fmed3f(a, -top, top), __builtin_amdgcn_fmed3f(b, -top, top)) : pack2(a, b);
+    h = pack2(a, b);
     const float ra = a - lo2(h), rb = b - hi2(h);
     m = pack2(ra, rb);
     l = pack2(ra - lo2(m), rb - hi2(m));
 }
-// the number a split row keeps
-__device__ __forceinline__ float joined(uint32_t h, uint32_t m, uint32_t l) {
-    const float H = lo2(h), M = lo2(m), L = lo2(l);
-    return fabsf(M) <= FLT_MAX ? H + (M + L) : M;
-}
-// Operand of eight k in NP parts (NP = 1: a bf16 number).
+__device__ __forceinline__ float joined(uint32_t h, uint32_t m, uint32_t l) { return lo2(h) + (lo2(m) + lo2(l)); }
+// Operand of eight k in NP parts (NP = 1: a bf16 number, without a factor).
 template <int NP> struct Parts { bf16x8 p[NP]; };
 __device__ __forceinline__ Parts<3> split8(const float* x) {
     u32x4 h, m, l;
     _Pragma("unroll") for (int i = 0; i < 4; ++i) {
         uint32_t a, b, c;
-        split2<false>(x[2 * i], x[2 * i + 1], a, b, c);
+        split2(x[2 * i], x[2 * i + 1], a, b, c);
         h[i] = a; m[i] = b; l[i] = c;
     }
     return Parts<3>{{__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)}};
@@ -402,7 +403,7 @@ struct GRows {
                 u32x2 h, m, l;
                 _Pragma("unroll") for (int e = 0; e < 2; ++e) {
                     uint32_t a, b, d;
-                    split2<true>(__uint_as_float(x[2 * e]), __uint_as_float(x[2 * e + 1]), a, b, d);
+                    split2(__uint_as_float(x[2 * e]) * kUp, __uint_as_float(x[2 * e + 1]) * kUp, a, b, d);
                     h[e] = a; m[e] = b; l[e] = d;
                 }
                 uint16_t* o = dst + row * LDR + 4 * q;
@@ -418,7 +419,7 @@ struct GRows {
             }
         }
     }
-    // element at a stored column
+    // element at a stored column (with its factor)
     __device__ static __forceinline__ float at(const uint16_t* src, int row, int col) {
         const uint16_t* o = src + row * LDR + col;
         if constexpr (NP == 3) return joined(o[0], o[PART], o[2 * PART]);
@@ -482,7 +483,7 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
     TIO* V = reinterpret_cast<TIO*>(smb + Lds::oV);
     float* pdv = reinterpret_cast<float*>(smb + Lds::oD);
     double* dred = reinterpret_cast<double*>(smb + Lds::oR);  // [wave][32]: partial row products
-    // decay tables of a step: E_p [32] and the step's total, e^{E_p}, e^{E - E_p} of all but the last two tokens (0 there)
+    // decay tables of a step: E_p [32] and the step's total, e^{E_p}, 2^24 e^{E - E_p} of all but the last two tokens (0 there)
     // and of those two
     struct Tables { double* bs; float *wi, *wo, *wl; };
     auto tables = [&](int kk) {
@@ -491,6 +492,8 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
         return Tables{reinterpret_cast<double*>(t), f, f + GT, f + 2 * GT};
     };
 
+    // factors to take out of a product of scores (rows x rows) and of any other (rows x what is split in registers)
+    constexpr float kScores = NP == 3 ? kDown * kDown : 1.f, kRows = NP == 3 ? kDown * kDown : kDown;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Every phase reads LDS at its own lane-dependent addresses.  Left alone the compiler keeps them all in registers
     // across the loop (over a hundred); with the thread id hidden at the start of a phase it recomputes that phase's few.
@@ -511,6 +514,12 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
         if (!SUM) rq.gload(static_cast<const TIO*>(R.xq) + p.tok0 * a.kd, kb, p.L, rev, tid);
         rk.gload(static_cast<const TIO*>(R.xk) + p.tok0 * a.kd, kb, p.L, rev, tid);
         rv.gload(static_cast<const TIO*>(R.xv) + p.tok0 * a.vd + vcol, vb, p.L, rev, tid);
+    };
+    // an element of a row as it came, row < L
+    auto number = [&](const void* x, const ChunkPos& p, int row, int col) {
+        const TIO* e = static_cast<const TIO*>(x) + (p.tok0 + size_t(rev ? p.L - 1 - row : row) * p.ts) * a.kd + col;
+        if constexpr (NP == 3) return *e;
+        else return lo2(*e);
     };
     // The last wave, which has the fewest score blocks, makes the decay tables, a step ahead of their use.
     const bool tabler = w == NW + HW - 1, carrier = HW == 0 || w < NW;
@@ -539,7 +548,7 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
         if (lane < GT) {
             t.bs[n] = E;
             t.wi[n] = expf(float(E));
-            const float wo = expf(float(all - E));
+            const float wo = expf(float(all - E)) * kUp;
             t.wo[n] = n < L - 2 ? wo : 0.f;
             if (n >= L - 2 && n < L) t.wl[n - (L - 2)] = wo;
             if (n == 0) t.bs[GT] = all;
@@ -630,11 +639,13 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
                     if (b >= nb) break;
                     const int p = 16 * ((b0 + b + 1) >> 1) + c;
                     f32x4 t = P[b];
-                    if (__any(fmaf(t[0] + t[1], 0.f, (t[2] + t[3]) * 0.f) != 0.f)) {
+                    const bool again = __any(fmaf(t[0] + t[1], 0.f, (t[2] + t[3]) * 0.f) != 0.f);
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) t[j] *= kScores;
+                    if (again) {
                         f32x4 G = {0.f, 0.f, 0.f, 0.f};
                         _Pragma("unroll 1") for (int f = 0; f < KD; ++f) {
-                            const float x = Rows::at(Q, p, Rows::swapped(f));
-                            _Pragma("unroll") for (int j = 0; j < 4; ++j) G[j] = fmaf(Rows::at(K, sb + 4 * q + j, f), x, G[j]);
+                            const float x = number(R.xq, cp, min(p, L - 1), f);
+                            _Pragma("unroll") for (int j = 0; j < 4; ++j) G[j] = fmaf(number(R.xk, cp, min(sb + 4 * q + j, L - 1), f), x, G[j]);
                         }
                         _Pragma("unroll") for (int j = 0; j < 4; ++j) t[j] = finite(t[j]) ? t[j] : G[j];
                     }
@@ -647,7 +658,16 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
                         if (d.kind != 0) t[j] *= expf(float(bp - T.bs[r]));
                         t[j] = r < p ? t[j] : 0.f;  // (not t * 0: t may be infinite)
                     }
-                    _Pragma("unroll") for (int j = 0; j < 2; ++j) split2<true>(t[2 * j], t[2 * j + 1], h[j], m[j], l[j]);
+                    const f32x4 u = t * kUp;
+                    _Pragma("unroll") for (int j = 0; j < 2; ++j) split2(u[2 * j], u[2 * j + 1], h[j], m[j], l[j]);
+                    if (__any(fmaf(u[0] + u[1], 0.f, (u[2] + u[3]) * 0.f) != 0.f))  // its bits instead of parts
+                        _Pragma("unroll") for (int j = 0; j < 4; ++j)
+                            if (!finite(u[j])) {
+                                const uint32_t word = __float_as_uint(t[j]), at = 16 * (j & 1), keep = 0xffff0000u >> at;
+                                h[j >> 1] = (h[j >> 1] & keep) | (0x7f80u << at);
+                                m[j >> 1] = (m[j >> 1] & keep) | ((word >> 16) << at);
+                                l[j >> 1] = (l[j >> 1] & keep) | ((word & 0xffffu) << at);
+                            }
                     uint16_t* o = Pp + ((sb >> 4) * 64 + (q & 1) * 32 + p) * 8 + 4 * (q >> 1);
                     *reinterpret_cast<u32x2*>(o) = u32x2{h[0], h[1]};
                     *reinterpret_cast<u32x2*>(o + 1024) = u32x2{m[0], m[1]};
@@ -662,7 +682,7 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
                 _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
                     _Pragma("unroll") for (int h = 0; h < 2; ++h) {
                         float t[8];
-                        _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = S[ib][8 * h + x];
+                        _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = S[ib][8 * h + x] * kUp;
                         const Parts<3> sp = split8(t);
                         const Parts<NP> x = Rows::row8(Q, n, 32 * ib + 16 * h + 8 * half);
                         small_terms(sp, x, small);
@@ -670,15 +690,15 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
                     }
                 interleave<KB * 2 * (NP == 3 ? 6 : 3), NP == 3 ? 8 : 16>();
                 _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] += small[x];
-                const float nf = not_finite(O);
+                const float nf = not_finite(O), e = T.wi[n];
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] *= kRows;
                 if (__any(nf != nf)) {
                     f32x16 G = {0};
                     _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
                         _Pragma("unroll") for (int x = 0; x < 16; ++x)
-                            G = mfma2(S[ib][x], Rows::at(Q, n, Rows::swapped(32 * ib + hrow(x, half))), G);
+                            G = mfma2(S[ib][x], number(R.xq, cp, min(n, L - 1), 32 * ib + hrow(x, half)), G);
                     replace_not_finite(O, G);
                 }
-                const float e = T.wi[n];
                 _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] *= e;
             }
             __syncthreads();  // (B) scores
@@ -688,6 +708,7 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
                 // not: a value row that is not finite would reach the positions before it, which must not depend on it.  Then the
                 // product runs without such elements and they are added pair by pair.
                 f32x16 X;
+                float xs = kRows;                           // the factor to take out of X
                 {
                     Parts<3> pp[2];
                     _Pragma("unroll") for (int h = 0; h < 2; ++h)
@@ -705,7 +726,7 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
                     product([&](int h) {
                         if constexpr (NP == 3) {
                             float t[8];
-                            _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = V[hrow(8 * h + x, half) * LV + 32 * w + n];
+                            _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = V[hrow(8 * h + x, half) * LV + 32 * w + n] * kUp;
                             return split8(t);
                         } else {
                             return VRows::col8(V, h, 32 * w, lane);
@@ -716,16 +737,20 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
                         auto known = [&](int x) { const float t = value(hrow(x, half), 32 * w + n); return finite(t) ? t : 0.f; };
                         auto score = [&](int r, int p) {
                             const uint16_t* o = Pp + ((r >> 4) * 64 + ((r >> 2) & 1) * 32 + p) * 8 + 4 * ((r >> 3) & 1) + (r & 3);
-                            return joined(o[0], o[1024], o[2048]);
+                            return (o[0] & 0x7f80) == 0x7f80 ? __uint_as_float(uint32_t(o[1024]) << 16 | o[2048]) : joined(o[0], o[1024], o[2048]) * kDown;
                         };
                         product([&](int h) {
                             float t[8];
                             _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = known(8 * h + x);
-                            if constexpr (NP == 3) return split8(t);
-                            else return Parts<1>{{__builtin_bit_cast(bf16x8, u32x4{pack2(t[0], t[1]), pack2(t[2], t[3]), pack2(t[4], t[5]), pack2(t[6], t[7])})}};
+                            if constexpr (NP == 3) {
+                                _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] *= kUp;
+                                return split8(t);
+                            } else return Parts<1>{{__builtin_bit_cast(bf16x8, u32x4{pack2(t[0], t[1]), pack2(t[2], t[3]), pack2(t[4], t[5]), pack2(t[6], t[7])})}};
                         });
                         f32x16 G = {0};
                         _Pragma("unroll") for (int x = 0; x < 16; ++x) G = mfma2(known(x), score(hrow(x, half), n), G);
+                        _Pragma("unroll") for (int x = 0; x < 16; ++x) X[x] *= kRows;
+                        xs = 1.f;
                         replace_not_finite(X, G);
                         _Pragma("unroll 1") for (int r = 0; r < GT; ++r) {
                             const float p = score(r, n);
@@ -742,7 +767,7 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
                 double t = 0.0;
                 _Pragma("unroll") for (int g = 0; g < 4; ++g) {
                     f32x4 o;
-                    _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] = O[4 * g + j] + X[4 * g + j];
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] = fmaf(X[4 * g + j], xs, O[4 * g + j]);
                     if (R.xdot) {
                         _Pragma("unroll") for (int j = 0; j < 4; ++j) t += double(aux[g][j]) * double(o[j]);
                     }
@@ -797,13 +822,17 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
                     U[b] = mfma2(Rows::at(K, last, i + n), zlast, U[b]);
                 }
                 float nf = 0.f;
-                _Pragma("unroll") for (int b = 0; b < GB; ++b) nf += not_finite(U[b]);
+                _Pragma("unroll") for (int b = 0; b < GB; ++b) {
+                    nf += not_finite(U[b]);
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) U[b][x] *= kRows;
+                }
                 if (__any(nf != nf)) {
                     _Pragma("unroll") for (int b = 0; b < GB; ++b) {
                         f32x16 G = {0};
                         _Pragma("unroll 1") for (int x = 0; x < 16; ++x) {
                             const int r = 2 * x + half;
-                            G = mfma2(Rows::at(K, r, 32 * (i0 + b) + n), value(r) * weight(r), G);
+                            const float y = number(R.xk, cp, min(r, L - 1), 32 * (i0 + b) + n);
+                            G = mfma2(r < L ? y : 0.f, value(r) * (weight(r) * kDown), G);
                         }
                         replace_not_finite(U[b], G);
                     }

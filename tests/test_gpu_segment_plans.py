@@ -299,3 +299,59 @@ def test_numbers_above_the_largest_bf16_one(name):
         rows = lambda t: t.reshape(-1, t.shape[-1])
         big = np.abs(rows(b)).max(axis=1, keepdims=True)
         assert (np.abs(rows(a) - rows(b)) <= 2.0 ** -18 * big).all()
+
+
+def two_norm_error(got, want):
+    return np.linalg.norm(host(got) - want) / np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("exponent", [-116, -124])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("name", ["q", "k", "v", "m0", "d_o"])
+def test_numbers_below_the_smallest_bf16_parts(name, d, exponent):
+    """A bf16 number ends at 2^-133, the three parts of an fp32 number of 2^-110 and less would be cut there.  One operand is scaled
+    down, others up, so that all results are normal numbers; the bound is that of test_products_in_three_parts, and the family's
+    1e-4 for the decay gradient, whose terms cancel."""
+    import torch
+    from oracle import lsm_oracle_bwd, lsm_oracle_fwd
+    from lsm_testlib import gpu_backward
+    x = wl.make_inputs(1, 2, 99, d, d, wl.KIND_SCALAR, dtype="f32", seed=2750 + d, decay="weak", init_state=True, init_std=8.0)
+    small, up = 2.0 ** exponent, 2.0 ** 20
+    scale = {"q": dict(q=small, v=up, m0=up, d_o=up), "k": dict(k=small, v=up, m0=small, d_o=up),
+             "v": dict(v=small, k=up, m0=small * up, d_o=up), "m0": dict(m0=small, v=0.0, q=up, d_o=up),
+             "d_o": dict(d_o=small, q=up, k=up, v=up, m0=up)}[name]
+    for n, f in scale.items():
+        x[n] = (x[n].astype(np.float64) * f).astype(np.float32)
+    o, mT = gpu_forward(x, 64)
+    r = gpu_backward(x, 64)
+    torch.cuda.synchronize()
+    o_ref, mT_ref = lsm_oracle_fwd(x["q"], x["k"], x["v"], x["g"], x["kind"], x["m0"])
+    ref = lsm_oracle_bwd(x["q"], x["k"], x["v"], x["g"], x["kind"], x["d_o"], x["m0"], None)
+    errs = {}
+    for n, got, want in [("o", o, o_ref), ("final_state", mT, mT_ref), ("d_init_state", r["d_init_state"], ref["d_m0"])] + \
+            [(n, r[n], ref[n]) for n in ("dq", "dk", "dv", "dg")]:
+        if want.any():
+            errs[n] = two_norm_error(got, want)
+    print(" ".join("%s %.1e" % e for e in errs.items()))
+    for n, e in errs.items():
+        assert e <= (1e-4 if n == "dg" else 2.0 ** -21), (n, e)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("where", ["scores", "values", "state"])
+def test_what_a_strong_decay_leaves_keeps_its_bits(where, dtype):
+    """Only the first five tokens have values, and one token decays by e^-84 = 2^-121.2: what they leave is the whole result of the
+    tokens after it.  scores: those of the pairs across it, values: their weighted rows that enter the state, state: the running
+    state of the steps after.  The bound is that of test_products_in_three_parts (bf16 elements: of the state, which is fp32)."""
+    from oracle import lsm_oracle_fwd
+    T, cut = (32, 6) if where != "state" else (99, 40)
+    x = wl.make_inputs(1, 2, T, 64, 64, wl.KIND_SCALAR, dtype=dtype, seed=2760, decay="zero")
+    x["g"][:, :, cut] = -84.0
+    x["v"][:, :, 5:] = 0
+    for n, f in {"scores": dict(v=2.0 ** 20), "values": dict(k=2.0 ** 20), "state": dict(k=8.0, v=8.0, q=2.0 ** 20)}[where].items():
+        x[n] *= np.float32(f)
+    o, mT = gpu_forward(x, 64)
+    o_ref, mT_ref = lsm_oracle_fwd(x["q"], x["k"], x["v"], x["g"], x["kind"], None)
+    errs = [two_norm_error(mT, mT_ref)] + ([two_norm_error(o[:, :, cut:], o_ref[:, :, cut:])] if dtype == "f32" else [])
+    print(where, " ".join("%.1e" % e for e in errs))
+    assert max(errs) <= 2.0 ** -21
