@@ -389,9 +389,15 @@ __device__ __forceinline__ float not_finite(const f32x16& x) {  // NaN if any el
 // Rows of the scalar kinds' walker in LDS, part by part.  Keys (and bf16 values) as they come; queries with the four-element
 // groups of every 16 features in the order 0, 2, 1, 3, so that the features of result registers 8s .. 8s+7, which an
 // operand out of the accumulators has as its k, lie in one 16-byte piece.
-template <int NP, int LDR>
+// Rows follow one another 16 bytes apart, so that reads of 16 lanes tile the banks, or (XCH, 64-wide rows) without a gap, the
+// 16-byte pieces of a row exchanged instead: 16 rows' pieces of one column, and 4 x 32 bytes of 8 rows, lie in different banks.
+template <int NP, int RW, bool XCH>
 struct GRows {
-    static constexpr int PART = GT * LDR, SIZE = NP * PART;  // elements
+    static_assert(!XCH || RW == 64, "eight pieces to a row");
+    static constexpr int LDR = XCH ? RW : RW + 8, PART = GT * LDR;  // elements
+    __device__ static __forceinline__ int pos(int row, int col) {
+        return row * LDR + (XCH ? col ^ (((row & 6) | ((row >> 3) & 1)) << 3) : col);
+    }
     template <typename TIO, int W, int NT>
     __device__ static __forceinline__ void commit(uint16_t* dst, const GTile<TIO, W, NT>& t, int tid, bool swap) {
         using Tile = GTile<TIO, W, NT>;
@@ -406,22 +412,22 @@ struct GRows {
                     split2(__uint_as_float(x[2 * e]) * kUp, __uint_as_float(x[2 * e + 1]) * kUp, a, b, d);
                     h[e] = a; m[e] = b; l[e] = d;
                 }
-                uint16_t* o = dst + row * LDR + 4 * q;
+                uint16_t* o = dst + pos(row, 4 * q);
                 *reinterpret_cast<u32x2*>(o) = h;
                 *reinterpret_cast<u32x2*>(o + PART) = m;
                 *reinterpret_cast<u32x2*>(o + 2 * PART) = l;
             } else if (swap) {
-                uint16_t* o = dst + row * LDR + 16 * (c >> 1) + 4 * (c & 1);
-                *reinterpret_cast<u32x2*>(o) = u32x2{x.x, x.y};
-                *reinterpret_cast<u32x2*>(o + 8) = u32x2{x.z, x.w};
+                const int f = 16 * (c >> 1) + 4 * (c & 1);
+                *reinterpret_cast<u32x2*>(dst + pos(row, f)) = u32x2{x.x, x.y};
+                *reinterpret_cast<u32x2*>(dst + pos(row, f + 8)) = u32x2{x.z, x.w};
             } else {
-                *reinterpret_cast<u32x4*>(dst + row * LDR + 8 * c) = x;
+                *reinterpret_cast<u32x4*>(dst + pos(row, 8 * c)) = x;
             }
         }
     }
     // element at a stored column (with its factor)
     __device__ static __forceinline__ float at(const uint16_t* src, int row, int col) {
-        const uint16_t* o = src + row * LDR + col;
+        const uint16_t* o = src + pos(row, col);
         if constexpr (NP == 3) return joined(o[0], o[PART], o[2 * PART]);
         else return lo2(o[0]);
     }
@@ -429,14 +435,14 @@ struct GRows {
     // eight features of one row: 16 consecutive bytes, or two groups of four elements, 8 apart
     __device__ static __forceinline__ Parts<NP> row8(const uint16_t* src, int row, int col) {
         Parts<NP> r;
-        _Pragma("unroll") for (int i = 0; i < NP; ++i) r.p[i] = *reinterpret_cast<const bf16x8*>(src + i * PART + row * LDR + col);
+        _Pragma("unroll") for (int i = 0; i < NP; ++i) r.p[i] = *reinterpret_cast<const bf16x8*>(src + i * PART + pos(row, col));
         return r;
     }
     __device__ static __forceinline__ Parts<NP> row44(const uint16_t* src, int row, int col) {
         Parts<NP> r;
         _Pragma("unroll") for (int i = 0; i < NP; ++i) {
-            const uint16_t* o = src + i * PART + row * LDR + col;
-            const u32x2 a = *reinterpret_cast<const u32x2*>(o), b = *reinterpret_cast<const u32x2*>(o + 8);
+            const uint16_t* o = src + i * PART;
+            const u32x2 a = *reinterpret_cast<const u32x2*>(o + pos(row, col)), b = *reinterpret_cast<const u32x2*>(o + pos(row, col + 8));
             r.p[i] = __builtin_bit_cast(bf16x8, u32x4{a.x, a.y, b.x, b.y});
         }
         return r;
@@ -444,25 +450,35 @@ struct GRows {
     // one column of rows hrow(8 s + 0 .. 7): the transposing LDS read hands lane i of 16 the i-th feature of a patch of 4 rows
     __device__ static __forceinline__ Parts<NP> col8(const uint16_t* src, int s, int col0, int lane) {
         typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-        const int r = lane & 15;
+        const int r = lane & 15, row = 16 * s + 4 * (lane >> 5) + (r >> 2), col = col0 + 16 * ((lane >> 4) & 1) + 4 * (r & 3);
         Parts<NP> o;
         _Pragma("unroll") for (int i = 0; i < NP; ++i) {
-            const uint16_t* p = src + i * PART + (16 * s + 4 * (lane >> 5) + (r >> 2)) * LDR + col0 + 16 * ((lane >> 4) & 1) + 4 * (r & 3);
-            const u32x2 a = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p)));
-            const u32x2 b = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 8 * LDR)));
+            const uint16_t* p = src + i * PART;
+            const u32x2 a = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + pos(row, col))));
+            const u32x2 b = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + pos(row + 8, col))));
             o.p[i] = __builtin_bit_cast(bf16x8, u32x4{a.x, a.y, b.x, b.y});
         }
         return o;
     }
 };
 
-// LDS of the scalar kinds' walker, in bytes.  Row strides of the split rows == 4 mod 64 words: 16-byte row reads of 16
-// lanes tile the banks.  fp32 values are read by columns, a wave's two halves four rows apart: 4 * stride == 32 mod 64.
+// LDS of the scalar kinds' walker, in bytes.  fp32 values are read by columns, a wave's two halves four rows apart, and four
+// columns at a time by rows: either 4 * stride == 32 mod 64 words, or (XCH) no gap and 8-column pieces exchanged by the row's bits
+// 1 to 3, bit 2 between the halves of the row.
 //   Q | K | V | scores: three parts [2][64][8], then the pairs (p, p) | two sets of decay tables | row products
+// XCH for fp32, 64 x 64, without helpers: four workgroups fit on a compute unit, the number that the segment plan counts on (with
+// gaps 44736 bytes and three, three quarters of a grid and then the rest: forward, 64 sequences of 1024 63 -> 54 us, 1024 of 512
+// 219 -> 165; forward + backward, 64 of 1024, 198 -> 177).  With helpers the exchange only costs instructions (23.7 -> 24.3 us for 2
+// sequences of 256).
 template <typename TIO, int KD, int TV, int HW, bool SUM>
 struct GLdsS {
-    static constexpr int NP = sizeof(TIO) == 4 ? 3 : 1, NW = TV / 32, NT = 64 * (NW + HW), LQ = KD + 8, LV = TV + 8;
-    static constexpr int rows = GT * LQ * NP * 2;
+    static constexpr int NP = sizeof(TIO) == 4 ? 3 : 1, NW = TV / 32, NT = 64 * (NW + HW);
+    static constexpr bool XCH = NP == 3 && KD == 64 && TV == 64 && HW == 0;
+    using Rows = GRows<NP, KD, XCH>;
+    static constexpr int LV = XCH ? TV : TV + 8, rows = NP * Rows::PART * 2;
+    __device__ static __forceinline__ int vpos(int row, int col) {
+        return row * LV + (XCH ? col ^ (((row >> 2) & 1) << 5 | ((row >> 3) & 1) << 4 | ((row >> 1) & 1) << 3) : col);
+    }
     static constexpr int oK = SUM ? 0 : rows, oV = oK + rows, oP = oV + GT * LV * int(sizeof(TIO)), oD = oP + (SUM ? 0 : 3 * 2048);
     static constexpr int oT = oD + (SUM ? 0 : GT * 4), table = 34 * 8 + 2 * GT * 4 + 16, oR = oT + 2 * table, bytes = oR + (SUM ? 0 : NW * GT * 8);
 };
@@ -473,11 +489,11 @@ struct GLdsS {
 template <typename TIO, int KD, int TV, int HW, bool SUM>
 __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(Dims d, GArgs a) {
     using Lds = GLdsS<TIO, KD, TV, HW, SUM>;
-    constexpr int NP = Lds::NP, NW = Lds::NW, NT = Lds::NT, LQ = Lds::LQ, LV = Lds::LV, KB = KD / 32;
+    constexpr int NP = Lds::NP, NW = Lds::NW, NT = Lds::NT, KB = KD / 32;
     // The next rows are requested at the start of a step, but where a wave holds twice as many (two waves to 128-wide keys).
     constexpr bool EARLY = KD == 64 || NT == 256;
-    using Rows = GRows<NP, LQ>;
-    using VRows = GRows<1, LV>;                              // bf16 values
+    using Rows = typename Lds::Rows;
+    using VRows = GRows<1, TV, false>;                      // bf16 values
     extern __shared__ __align__(16) char smb[];
     uint16_t *Q = reinterpret_cast<uint16_t*>(smb), *K = reinterpret_cast<uint16_t*>(smb + Lds::oK), *Pp = reinterpret_cast<uint16_t*>(smb + Lds::oP);
     TIO* V = reinterpret_cast<TIO*>(smb + Lds::oV);
@@ -592,7 +608,11 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
             rv.clear(L, tid);
             if (!SUM) Rows::commit(Q, rq, tid, true);
             Rows::commit(K, rk, tid, false);
-            if constexpr (NP == 3) rv.commit(V, LV, GT, tid);
+            if constexpr (NP == 3)
+                _Pragma("unroll") for (int i = 0; i < rv.CNT; ++i) {
+                    const int p = tid + NT * i;
+                    *reinterpret_cast<u32x4*>(V + Lds::vpos(p / rv.PR, 4 * (p % rv.PR))) = rv.v[i];
+                }
             else VRows::commit(V, rv, tid, false);
         }
         __syncthreads();  // (A) rows and decay tables of this step are in LDS
@@ -722,11 +742,11 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
                         }
                         _Pragma("unroll") for (int h = 0; h < 2; ++h) X = mfma16(vp[h].p[0], pp[h].p[0], X);
                     };
-                    auto value = [&](int row, int col) { if constexpr (NP == 3) return V[row * LV + col]; else return lo2(V[row * LV + col]); };
+                    auto value = [&](int row, int col) { if constexpr (NP == 3) return V[Lds::vpos(row, col)]; else return lo2(V[Lds::vpos(row, col)]); };
                     product([&](int h) {
                         if constexpr (NP == 3) {
                             float t[8];
-                            _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = V[hrow(8 * h + x, half) * LV + 32 * w + n] * kUp;
+                            _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = V[Lds::vpos(hrow(8 * h + x, half), 32 * w + n)] * kUp;
                             return split8(t);
                         } else {
                             return VRows::col8(V, h, 32 * w, lane);
@@ -771,7 +791,7 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
                     if (R.xdot) {
                         _Pragma("unroll") for (int j = 0; j < 4; ++j) t += double(aux[g][j]) * double(o[j]);
                     }
-                    const f32x4 z = load4(V + n * LV + 32 * w + 8 * g + 4 * half);
+                    const f32x4 z = load4(V + Lds::vpos(n, 32 * w + 8 * g + 4 * half));
                     _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] += pd * z[j];
                     if (n < L) store4(static_cast<TIO*>(R.out) + obase + oel + 8 * g, o);
                 }
@@ -794,7 +814,7 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
                 float t[8];
                 const f32x4 e0 = *reinterpret_cast<const f32x4*>(T.wo + 16 * h + 4 * half), e1 = *reinterpret_cast<const f32x4*>(T.wo + 16 * h + 8 + 4 * half);
                 if constexpr (NP == 3) {
-                    _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = V[hrow(8 * h + x, half) * LV + 32 * w + n];
+                    _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = V[Lds::vpos(hrow(8 * h + x, half), 32 * w + n)];
                 } else {
                     const u32x4 r = __builtin_bit_cast(u32x4, VRows::col8(V, h, 32 * w, lane).p[0]);
                     _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = x & 1 ? hi2(r[x >> 1]) : lo2(r[x >> 1]);
@@ -803,7 +823,7 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
                 z[h] = split8(t);
             }
             auto weight = [&](int r) { return r < L - 2 ? T.wo[r] : r < L ? T.wl[r - (L - 2)] : 0.f; };
-            auto value = [&](int r) { if constexpr (NP == 3) return V[r * LV + 32 * w + n]; else return lo2(V[r * LV + 32 * w + n]); };
+            auto value = [&](int r) { if constexpr (NP == 3) return V[Lds::vpos(r, 32 * w + n)]; else return lo2(V[Lds::vpos(r, 32 * w + n)]); };
             const int last = L - 2 + half < 0 ? GT - 1 : L - 2 + half;  // (one token: with a row of zeros)
             const float zlast = value(last) * weight(last);
             const float lam = expf(float(T.bs[GT]));
@@ -1415,9 +1435,10 @@ __global__ void k_chunk_starts(Dims d, int* __restrict__ cstart, int least) {
 // Segment plan: m units of gC tokens per segment.  Enough workgroups that the launch fills the chip with what fits on a
 // compute unit (two of the 128-wide walkers, four of the 64-wide ones), and no more boundary states than one per chunk of
 // the caller's chunk size, which is what lsm_chunk_fwd_workspace_bytes() has always reported.
-// Half as many and twice as many workgroups, us a call: 32 sequences of 1777, d = 64, forward 72 / 55 / 55; 64 of 1024, d = 64, fp32,
-// 69 / 54 / 53; 32 of 2048, d_k = 64, d_v = 128, 85 / 71 / 82, vector kind with backward 544 / 439 / 479; 64 of 1000, d = 128, fp32,
-// 119 / 108 / 133.  Half is the better one for many short sequences (256 of 256, d = 128, fp32: 76 / 110 / 131).
+// Half as many, as many and twice as many workgroups, us a call: 32 sequences of 1777, d = 64, forward 52 / 47 / 47; 64 of 1024,
+// d = 64, fp32, 62 / 52 / 52; 32 of 2048, d_k = 64, d_v = 128, 68 / 54 / 68, vector kind with backward 544 / 439 / 479; 64 of 1000,
+// d = 128, fp32, 111 / 94 / 117.  Half is the better one for many short sequences (256 of 256, d = 128, fp32: 66 / 95 / 115).
+// (Of the scalar kinds' fp32 walkers with 128- and 256-wide keys two and one fit; the plan counts four for every 64-wide value.)
 struct GPlan { int m, nseg, units; };  // nseg: segments (and boundary slots), units: of gC tokens, per sequence or per head
 int slices(int width, bool narrow) { return narrow ? width / 64 : (width + 127) / 128; }
 GPlan gplan(const Dims& d) {
@@ -1498,6 +1519,7 @@ hipError_t allow_lds(const void* fn, int bytes) {
     return e;
 }
 
+static_assert(GLdsS<float, 64, 64, 0, false>::bytes <= 40 * 1024, "four workgroups to a compute unit: gplan");
 template <typename TIO, int KD, int TV, int VEC, int HW, bool SUM>
 hipError_t launch_walk_as(const Dims& d, GArgs a, int nroles, dim3 grid, hipStream_t st, int kid) {
     using Lds = std::conditional_t<VEC == 0, GLdsS<TIO, KD, TV, HW, SUM>, GLds<KD, TV, VEC, SUM>>;
@@ -1516,8 +1538,9 @@ hipError_t launch_walk_as(const Dims& d, GArgs a, int nroles, dim3 grid, hipStre
 template <typename TIO, int KD, int TV, int VEC, bool SUM>
 hipError_t launch_walk(const Dims& d, const GArgs& a, int nroles, dim3 grid, hipStream_t st, int kid) {
     // Two more waves for the rows, the tables and the scores where every workgroup has a compute unit to itself: a step is then
-    // one wave's chain of instructions (2 sequences of 256, d = 64, fp32: 26.8 -> 23.6 us; 32 of 1777, bf16, with 3.5 to a unit:
-    // 42.4 -> 52.0).
+    // one wave's chain of instructions.  us a call without and with them: 2 sequences of 256, fp32, d = 64 26.8 / 23.6, 128-wide keys
+    // 39.9 / 33.9, 256-wide 57.3 / 49.0, their training steps 112 / 99 and 148 / 131; 8 of 2000, fp32 52 / 46 and 71 / 60, bf16 44 / 41 and
+    // 56 / 51.  With 3.5 workgroups to a unit (32 of 1777, bf16, d = 64) 42.4 / 52.0.
     if constexpr (VEC == 0 && TV == 64)
         if (grid.x * grid.y * unsigned(nroles * (a.vd / TV)) <= 256) return launch_walk_as<TIO, KD, TV, VEC, 2, SUM>(d, a, nroles, grid, st, kid);
     return launch_walk_as<TIO, KD, TV, VEC, 0, SUM>(d, a, nroles, grid, st, kid);
