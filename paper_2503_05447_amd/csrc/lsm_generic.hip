@@ -317,7 +317,7 @@ struct GLds {
 // same bits, over the whole range of fp32.  Cost, forward + backward, fp32, 4 x 16 sequences of 2047, d = 128: 598 -> 614 us;
 // forward, bf16, 32 sequences of 1777, d = 64: 44.2 -> 45.4.
 //
-// What is not finite has no such sum (infinity - infinity), and 2^24 times a number of 2^104 and more is not: elements of a result
+// What is not finite has no such sum (infinity - infinity), and 2^24 times a number of 2^104 and more is not finite: elements of a result
 // that are not finite are formed again with the fp32 instructions from the numbers themselves (rows and states from where they
 // came from, a score from its parts, which then hold its bits).  The others stay as they are, so that they do not depend on
 // what is not finite.
@@ -680,9 +680,10 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
                     }
                     const f32x4 u = t * kUp;
                     _Pragma("unroll") for (int j = 0; j < 2; ++j) split2(u[2 * j], u[2 * j + 1], h[j], m[j], l[j]);
-                    if (__any(fmaf(u[0] + u[1], 0.f, (u[2] + u[3]) * 0.f) != 0.f))  // its bits instead of parts
+                    auto fits = [&](int j) { return fabsf(t[j]) < 0x1p103f; };  // (to 2^104 the head could round to infinity)
+                    if (__any(!(fits(0) && fits(1) && fits(2) && fits(3))))     // its bits instead of parts
                         _Pragma("unroll") for (int j = 0; j < 4; ++j)
-                            if (!finite(u[j])) {
+                            if (!fits(j)) {
                                 const uint32_t word = __float_as_uint(t[j]), at = 16 * (j & 1), keep = 0xffff0000u >> at;
                                 h[j >> 1] = (h[j >> 1] & keep) | (0x7f80u << at);
                                 m[j >> 1] = (m[j >> 1] & keep) | ((word >> 16) << at);

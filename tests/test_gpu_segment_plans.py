@@ -355,3 +355,28 @@ def test_what_a_strong_decay_leaves_keeps_its_bits(where, dtype):
     errs = [two_norm_error(mT, mT_ref)] + ([two_norm_error(o[:, :, cut:], o_ref[:, :, cut:])] if dtype == "f32" else [])
     print(where, " ".join("%.1e" % e for e in errs))
     assert max(errs) <= 2.0 ** -21
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
+@pytest.mark.parametrize("where", ["q", "v", "d_o", "scores", "state", "results"])
+def test_numbers_that_outgrow_the_factor(where, dtype, d):
+    """Operands from 2^104 and results from 2^80 on are infinite once they are 2^24 and 2^48 times as large: they are formed again from
+    the numbers themselves (scores: from their bits).  Bounds: fp32 as in test_products_in_three_parts; bf16 results carry their own
+    rounding, 2^-9 at most, and that of the scores of the adjoint."""
+    import torch
+    from lsm_testlib import gpu_backward, oracle_all
+    x = wl.make_inputs(1, 2, 99, d, d, wl.KIND_SCALAR, dtype=dtype, seed=2770 + d, decay="weak", init_state=True)
+    power = {"q": dict(q=106, k=-20, v=-20, m0=-40), "v": dict(v=106, k=-30, m0=76), "d_o": dict(d_o=106, q=-20, k=-20, v=-20),
+             "scores": dict(q=55, k=55, v=-100, m0=-45), "state": dict(m0=110, q=-100), "results": dict(q=50, k=30, v=10, m0=40)}[where]
+    for n, p in power.items():
+        x[n] *= np.float32(2.0 ** p)
+    o, mT = gpu_forward(x, 64)
+    r = gpu_backward(x, 64)
+    torch.cuda.synchronize()
+    o_ref, mT_ref, ref = oracle_all(x)
+    errs = {n: two_norm_error(got, want) for n, got, want in
+            [("o", o, o_ref), ("final_state", mT, mT_ref), ("d_init_state", r["d_init_state"], ref["d_m0"])] +
+            [(n, r[n], ref[n]) for n in ("dq", "dk", "dv", "dg")]}
+    print(" ".join("%s %.1e" % e for e in errs.items()))
+    for n, e in errs.items():
+        assert e <= (1e-4 if n == "dg" else 2.0 ** -8 if dtype == "bf16" and n in ("o", "dq", "dk", "dv") else 2.0 ** -21), (n, e)
