@@ -1,6 +1,8 @@
 """The walkers at the sizes where their segment plans change.  fp32 walkers (every shape outside the bf16 family): one
 32-token step and its edges, one and several segments, segments of several units.  Both families: packed batches, whose
 boundary slots and workgroups are numbered across sequences.  Against the fp64 oracle, tolerances of the parity tests."""
+import itertools
+
 import numpy as np
 import pytest
 
@@ -101,12 +103,13 @@ def test_vector_decay_sums_are_rounded_once(T, dk, dv):
 @pytest.mark.parametrize("case", [("f32", 64, 64, 64), ("f32", 128, 64, 64), ("f32", 64, 128, 16), ("bf16", 64, 64, 64), ("f32", 256, 64, 64)])
 @pytest.mark.parametrize("value", [np.nan, np.inf])
 def test_non_finite_rows_do_not_reach_the_tokens_before_them(kind, case, value):
-    """One element of one token's q, k, v or d_o that is not finite, in the middle of a 32-token step: o and dq of earlier tokens
-    and dk and dv of later ones do not depend on it and come out bit for bit as without it; the token's own result is not finite."""
+    """One element of one token's q, k, v or d_o that is not finite, in the middle of a 32-token step, its first or one of its last two
+    tokens, alone in the last step: o and dq of earlier tokens and dk and dv of later ones do not depend on it and come out bit for bit
+    as without it; the token's own result is not finite."""
     import torch
     import paper_2503_05447_amd as pkg
     dtype, dk, dv, chunk = case
-    T, s0, col = 97, 45, 37
+    T, col = 97, 37
     x = wl.make_inputs(1, 2, T, dk, dv, kind, dtype=dtype, seed=2500, decay="weak", init_state=True, d_final=True)
 
     def run(t):
@@ -114,7 +117,7 @@ def test_non_finite_rows_do_not_reach_the_tokens_before_them(kind, case, value):
         r = pkg.lsm_chunk_bwd(t["q"], t["k"], t["v"], t["g"], kind, t["d_o"], chunk, t["m0"], t["d_mT"])
         return dict(r, o=o)
     clean = run(to_device(x))
-    for name in ("q", "k", "v", "d_o"):
+    for name, s0 in itertools.product(("q", "k", "v", "d_o"), (45, 64, 94, 95, 96)):
         t = to_device(x)
         t[name][:, :, s0, col] = value
         got = run(t)
@@ -265,7 +268,8 @@ def test_head_decay_gradient_holds_every_sequence(dtype, dk, dv):
 
 
 @pytest.mark.parametrize("kind", [wl.KIND_NONE, wl.KIND_HEAD, wl.KIND_SCALAR])
-@pytest.mark.parametrize("dtype,H,T,dk,dv", [("f32", 1, 1, 64, 64), ("f32", 2, 97, 64, 64), ("f32", 3, 65, 128, 64), ("f32", 2, 130, 64, 128),
+@pytest.mark.parametrize("dtype,H,T,dk,dv", [("f32", 1, 1, 64, 64), ("f32", 2, 97, 64, 64), ("f32", 2, 35, 64, 64), ("bf16", 2, 99, 128, 64),
+                                             ("f32", 257, 35, 128, 64), ("f32", 3, 65, 128, 64), ("f32", 2, 130, 64, 128),
                                              ("f32", 2, 95, 256, 64), ("f32", 257, 33, 64, 64), ("bf16", 2, 98, 64, 64),
                                              ("bf16", 257, 34, 64, 64), ("f32", 2, 66, 256, 128)])
 def test_products_in_three_parts(kind, dtype, H, T, dk, dv):
@@ -380,3 +384,32 @@ def test_numbers_that_outgrow_the_factor(where, dtype, d):
     print(" ".join("%s %.1e" % e for e in errs.items()))
     for n, e in errs.items():
         assert e <= (1e-4 if n == "dg" else 2.0 ** -8 if dtype == "bf16" and n in ("o", "dq", "dk", "dv") else 2.0 ** -21), (n, e)
+
+
+@pytest.mark.parametrize("kind", [wl.KIND_NONE, wl.KIND_SCALAR])
+@pytest.mark.parametrize("dtype,dk,dv", [("f32", 64, 64), ("f32", 128, 64), ("f32", 64, 128), ("bf16", 64, 64), ("bf16", 128, 64)])
+def test_helper_waves_leave_the_same_bits(dtype, dk, dv, kind):
+    """20 units of 64 tokens and 16 heads: a packed call has more than 256 workgroups, whose 64-wide walks have no helper waves, each
+    of the separate calls has fewer; the segments are of one unit in either, and so are all sums."""
+    import torch
+    import paper_2503_05447_amd as pkg
+    lens, H = [300, 64, 129, 33, 257, 99, 1], 16
+    T, n = sum(lens), len(lens)
+    x = wl.make_inputs(1, H, T, dk, dv, kind, dtype=dtype, seed=2950, decay="weak")
+    rng = np.random.default_rng(2951)
+    x["m0"] = (rng.standard_normal((n, H, dk, dv)) * 0.1).astype(np.float32)
+    x["d_mT"] = (rng.standard_normal((n, H, dk, dv)) * 0.1).astype(np.float32)
+    t = to_device(x)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+
+    def run(c, m0, dm, **kw):
+        o, mT = pkg.lsm_chunk_fwd(c["q"], c["k"], c["v"], c["g"], kind, 64, m0, **kw)
+        return dict(pkg.lsm_chunk_bwd(c["q"], c["k"], c["v"], c["g"], kind, c["d_o"], 64, m0, dm, **kw), o=o, final_state=mT)
+    whole = run(t, t["m0"], t["d_mT"], cu_seqlens=torch.from_numpy(cu).to(t["q"].device))
+    for s in range(n):
+        part = {m: None if t[m] is None else t[m][:, :, cu[s]:cu[s + 1]].contiguous() for m in ("q", "k", "v", "g", "d_o")}
+        alone = run(part, t["m0"][s:s + 1].contiguous(), t["d_mT"][s:s + 1].contiguous())
+        for m, got in alone.items():
+            if got is not None:
+                want = whole[m][s:s + 1] if m in ("final_state", "d_init_state") else whole[m][:, :, cu[s]:cu[s + 1]]
+                assert torch.equal(got, want), (m, s)
