@@ -24,12 +24,12 @@
 // products on the bf16 matrix cores, operands in three parts (below).
 //
 // Bound: the vector ALU and its order with the matrix instructions.  Scalar kinds, 4 x 16 sequences of 2047 fp32 tokens, d = 128:
-// vector issue 50 %, matrix pipes 30 % of the walk (fp32 instructions alone: 54 % of the matrix time and 20 % more time); the
+// vector issue 55 %, matrix pipes 30 % of the walk (fp32 instructions alone: matrix pipes 54 %, the whole step 18 % longer); the
 // vector kind 38 % matrix pipes, 37 % vector.
 // Forward + backward against one-thread-per-element kernels on the vector ALU with a state per chunk in memory, which this
-// family replaced, then with fp32 instructions throughout, now: that shape 11.6 ms, 0.731, 0.625; bf16 vector decay, 4 x 8
+// family replaced, then with fp32 instructions throughout, now: that shape 11.6 ms, 0.731, 0.621; bf16 vector decay, 4 x 8
 // sequences of 2048, d_k = 64, d_v = 128: 7.2 ms, 0.442, 0.442; forward alone, 32 sequences of 1777, d = 64, bf16: 262 us, 50.7,
-// 41.9; 2 sequences of 256, d = 64, fp32: 110 us, 25.1, 23.2.
+// 43.5; 2 sequences of 256, d = 64, fp32: 110 us, 25.1, 23.6.
 // Distance to 64-bit results against the kernels on the vector ALU, 2-norm, weak to strong decays, 512 to 4096 tokens, chunks of 16
 // to 128: o, dq, dk, dv and d_init_state 0.4 to 0.95 times (one case 1.09), dg 0.1 to 0.85 times (vector kind in chunks of 16: 1.04),
 // the final state 0.7 to 1.2 times (at most 5.5e-8 where it was 5.0e-8); the scalar kinds in three parts are closer again (fp32, 2
@@ -221,8 +221,8 @@ __device__ __forceinline__ int hrow(int x, int half) { return 8 * (x >> 2) + 4 *
 // X[v][p] = sum_s Z[s][v] P[s][p]: the score block as B operand out of its registers, `z` at value feature 0 of this wave.
 // P is zero where s does not precede p, but a zero times an infinity or NaN is not: a value row that is not finite would
 // reach the positions before it, which must not depend on it.  Where the block holds one (seen on the operands as they are
-// loaded) the matrix product runs without such elements and they are added pair by pair, ok(s, p) only.  With the check,
-// forward + backward: fp32, 4 x 16 sequences of 2047, d = 128, 728 -> 732 us; bf16 vector decay, 4 x 8 of 2048, d_k = 64, 444 -> 442.
+// loaded) the matrix product runs without such elements and they are added pair by pair, ok(s, p) only.  The check costs nothing:
+// forward + backward, bf16 vector decay, 4 x 8 sequences of 2048, d_k = 64, without and with it 444 / 442 us.
 template <typename Ok>
 __device__ __forceinline__ f32x16 causal_product(const float* z, int ld, const f32x16& P, int lane, Ok ok) {
     const int n = lane & 31, half = lane >> 5;
@@ -314,8 +314,9 @@ struct GLds {
 //
 // Below that the last parts, or their low bits, would be under the smallest bf16 number.  So what is split is 2^24 times the
 // operand, which gives every normal number three parts that are normal, and the result's factor is taken out of the sum: the
-// same bits, over the whole range of fp32.  Cost, forward + backward, fp32, 4 x 16 sequences of 2047, d = 128: 598 -> 614 us;
-// forward, bf16, 32 sequences of 1777, d = 64: 44.2 -> 45.4.
+// same bits, over the whole range of fp32.  Cost, forward + backward, fp32, 4 x 16 sequences of 2047, d = 128: 605 -> 621 us;
+// forward, bf16, 32 sequences of 1777, d = 64: 42.2 -> 43.5; at most 7 % (forward + backward, bf16, 32 of 1777, d_k = 64, d_v = 128:
+// 191 -> 205; with fp32 instructions throughout 296).
 //
 // What is not finite has no such sum (infinity - infinity), and 2^24 times a number of 2^104 and more is not finite: elements of a result
 // that are not finite are formed again with the fp32 instructions from the numbers themselves (rows and states from where they
@@ -950,7 +951,8 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
         }
     };
     // S[i][v] = lam S[i][v] + sum_t Y[t][i] (w_t Z[t][v]); the step's own sum is formed by itself, so the state sees one
-    // rounding per step instead of one per token (tokens in order: see gk_walk)
+    // rounding per step instead of one per token (tokens in order, the latest, which weigh most, last: what is added to them would
+    // round them again)
     auto update = [&]() {
         const float *Y = VEC == 1 ? W0 : K, *Z = VEC == 2 ? W0 : V;
         const int ldy = VEC == 1 ? LW : LQ, ldz = VEC == 2 ? LW : LV;
