@@ -888,25 +888,16 @@ bool many_at_once(const Dims& d, const SegPlan& sp) { return !d.nseq && sp.nseg 
 // entry states of the segments of one direction: summary pass, then the scan over segments
 template <bool REV>
 hipError_t walk_bounds(const Dims& d, hipStream_t st, const SegPlan& sp, const uint16_t* xk, const uint16_t* xv, const float* g,
-                       const float* edge_in, float* bound, float* gseg, int skip = 1, const uint16_t* xv_lo = nullptr) {
+                       const float* edge_in, float* bound, float* gseg, int skip = 1) {
     if (sp.nseg <= 1) return hipSuccess;
     WalkArgs a{};
-    a.xk = xk; a.xv = xv; a.g = g; a.bound = bound; a.gseg = gseg; a.m = sp.m; a.nseg = sp.nseg; a.skip = skip; a.xv_lo = xv_lo;
+    a.xk = xk; a.xv = xv; a.g = g; a.bound = bound; a.gseg = gseg; a.m = sp.m; a.nseg = sp.nseg; a.skip = skip;
     hipError_t e;
     const dim3 grid(walk_grid_x(d, sp.m, sp.nseg), walk_grid_y(d)), block(kThreads);
     {
         ProfScope ps(KID_WALK_SUMMARY, st);
         constexpr int lds = walk_lds(true);
-        if (xv_lo) {  // values in two planes (delta-rule backward; forward direction only)
-            constexpr int lds2 = lds + C * LD * 2;
-            if (d.kind == 0) {
-                if ((e = allow_lds(mk_walk<REV, false, true, true>, lds2)) != hipSuccess) return e;
-                hipLaunchKernelGGL((mk_walk<REV, false, true, true>), grid, block, lds2, st, d, a);
-            } else {
-                if ((e = allow_lds(mk_walk<REV, true, true, true>, lds2)) != hipSuccess) return e;
-                hipLaunchKernelGGL((mk_walk<REV, true, true, true>), grid, block, lds2, st, d, a);
-            }
-        } else if (d.kind == 0) {
+if (d.kind == 0) {
             if ((e = allow_lds(mk_walk<REV, false, true>, lds)) != hipSuccess) return e;
             hipLaunchKernelGGL((mk_walk<REV, false, true>), grid, block, lds, st, d, a);
         } else {
@@ -953,11 +944,12 @@ hipError_t walk_fwd(const Dims& d0, const FwdArgs& a) {
 }
 
 hipError_t launch_walk_grad(const Dims& d, const SegPlan& sp, const GradArgs& ga, hipStream_t st) {
-    const dim3 grid(walk_grid_x(d, sp.m, sp.nseg), walk_grid_y(d)), block(kGrad8Threads);
+    const dim3 block(kGrad8Threads);
     hipError_t e;
     ProfScope ps(KID_WALK_GRAD, st);
-    if (ga.v_lo) {  // values in two planes (delta-rule backward)
+    if (ga.v_lo) {  // delta-rule backward: values in two planes, the delta walkers' segments
         constexpr int lds = walk_grad_lds(true);
+        const dim3 grid(sp.nseg, d.seqs());
         if (d.kind == 0) {
             if ((e = allow_lds(mk_walk_grad<false, false, true>, lds)) != hipSuccess) return e;
             hipLaunchKernelGGL((mk_walk_grad<false, false, true>), grid, block, lds, st, d, ga);
@@ -967,6 +959,7 @@ hipError_t launch_walk_grad(const Dims& d, const SegPlan& sp, const GradArgs& ga
         }
         return hipSuccess;
     }
+    const dim3 grid(walk_grid_x(d, sp.m, sp.nseg), walk_grid_y(d));
     // d_v = 256: pass 0 leaves dq and dk in the partial planes (WIDE 1), pass 1 adds them to its own (WIDE 2)
     const int wide = d.vm == 1 ? 0 : (d.vs == 0 ? 1 : 2);
     auto launch = [&](auto kernel) -> hipError_t {
@@ -1127,6 +1120,9 @@ size_t delta_seg_bytes(const Dims& d) {
     const SegPlan sp = delta_plan(d);
     return sp.nseg > 1 ? 3 * align256(size_t(d.seqs()) * sp.nseg * D * D * 4) : 0;
 }
+const float* delta_entries(const Dims& d, const void* segws) {
+    return reinterpret_cast<const float*>(static_cast<const char*>(segws) + delta_seg_bytes(d) / 3 * 2);
+}
 }  // namespace
 // Dims::save: the forward call also leaves T^T and the pseudo-values in the workspace, laid out as the backward call
 // carves it, and the backward call does not run the prep and the walk again.
@@ -1196,33 +1192,27 @@ hipError_t launch_delta_fwd(const Dims& d, const DeltaPrepArgs& pa, DeltaWalkArg
     return d.kind == 0 ? launch_delta_fwd_t<false>(d, pa, wa, segws, stream) : launch_delta_fwd_t<true>(d, pa, wa, segws, stream);
 }
 
+// segf: the forward walk's summaries (its factors, transposed, are the reverse walk's)
 template <bool DEC>
-hipError_t launch_delta_rwalk(const Dims& d, DeltaRevArgs ra, void* segws, hipStream_t st) {
+hipError_t launch_delta_rwalk(const Dims& d, DeltaRevArgs ra, const void* segf, void* segws, hipStream_t st) {
     hipError_t e;
     const SegPlan sp = delta_plan(d);
     const dim3 grid(sp.nseg, d.seqs()), block(kThreads);
-    if ((e = allow_lds(mk_delta_rwalk<DEC, 0>, kDeltaRevLds)) != hipSuccess) return e;
+    if ((e = allow_lds(mk_delta_rwalk<DEC, false>, kDeltaRevLds)) != hipSuccess) return e;
     ra.m = sp.m;
     ra.nseg = sp.nseg;
     if (sp.nseg > 1) {
         const size_t one = align256(size_t(d.seqs()) * sp.nseg * D * D * 4);
-        float* sumA = reinterpret_cast<float*>(segws);
-        float* sumB = reinterpret_cast<float*>(static_cast<char*>(segws) + one);
-        float* bound = reinterpret_cast<float*>(static_cast<char*>(segws) + 2 * one);
-        if ((e = allow_lds(mk_delta_rwalk<DEC, 1>, kDeltaRevLds)) != hipSuccess) return e;
-        if ((e = allow_lds(mk_delta_rwalk<DEC, 2>, kDeltaRevLds)) != hipSuccess) return e;
+        const float* sumA = reinterpret_cast<const float*>(segf);
+        float* sumB = reinterpret_cast<float*>(segws);
+        float* bound = reinterpret_cast<float*>(static_cast<char*>(segws) + one);
+        if ((e = allow_lds(mk_delta_rwalk<DEC, true>, kDeltaRevLds)) != hipSuccess) return e;
         if ((e = allow_lds(mk_delta_combine<true>, kDeltaCombineLds)) != hipSuccess) return e;
         {
             ProfScope ps(KID_DELTA_SUMMARY, st);
             DeltaRevArgs sa = ra;
             sa.sum = sumB;
-            hipLaunchKernelGGL((mk_delta_rwalk<DEC, 1>), grid, block, kDeltaRevLds, st, d, sa);
-        }
-        {
-            ProfScope ps(KID_DELTA_SUMMARY, st);
-            DeltaRevArgs sa = ra;
-            sa.sum = sumA;
-            hipLaunchKernelGGL((mk_delta_rwalk<DEC, 2>), grid, block, kDeltaRevLds, st, d, sa);
+            hipLaunchKernelGGL((mk_delta_rwalk<DEC, true>), grid, block, kDeltaRevLds, st, d, sa);
         }
         {
             ProfScope ps(KID_DELTA_COMBINE, st);
@@ -1231,16 +1221,15 @@ hipError_t launch_delta_rwalk(const Dims& d, DeltaRevArgs ra, void* segws, hipSt
         ra.bound = bound;
     }
     ProfScope ps(KID_DELTA_RWALK, st);
-    hipLaunchKernelGGL((mk_delta_rwalk<DEC, 0>), grid, block, kDeltaRevLds, st, d, ra);
+    hipLaunchKernelGGL((mk_delta_rwalk<DEC, false>), grid, block, kDeltaRevLds, st, d, ra);
     return hipSuccess;
 }
 
 struct DeltaWs {
-    uint16_t *what, *tt, *usave, *usave_l, *dstates, *du_h, *du_l, *dw_h, *dw_l;
+    uint16_t *what, *tt, *usave, *usave_l, *dstates, *w_h, *w_l;
     float* uhat;
-    void* walk;   // bound_f, gseg_f of the gradient walker
     void* seg;    // segment summaries and entry states of the delta walker
-    void* seg_r;  // the same for the reverse walker
+    void* seg_r;  // the same for the reverse walker, without factors of its own
     size_t bytes;
 };
 DeltaWs carve_delta(const Dims& d, void* ws) {
@@ -1255,16 +1244,12 @@ DeltaWs carve_delta(const Dims& d, void* ws) {
     w.usave = reinterpret_cast<uint16_t*>(take(rows * D * 2));
     w.usave_l = reinterpret_cast<uint16_t*>(take(rows * D * 2));
     w.dstates = reinterpret_cast<uint16_t*>(take(size_t(d.BH()) * d.N * D * D * 2));
-    w.du_h = reinterpret_cast<uint16_t*>(take(rows * D * 2));
-    w.du_l = reinterpret_cast<uint16_t*>(take(rows * D * 2));
-    w.dw_h = reinterpret_cast<uint16_t*>(take(rows * D * 2));
-    w.dw_l = reinterpret_cast<uint16_t*>(take(rows * D * 2));
-    w.walk = p + off;
-    off += carve_walk(d, nullptr, false).bytes;
+    w.w_h = reinterpret_cast<uint16_t*>(take(rows * D * 2));
+    w.w_l = reinterpret_cast<uint16_t*>(take(rows * D * 2));
     w.seg = p + off;
     off += delta_seg_bytes(d);
     w.seg_r = p + off;
-    off += delta_seg_bytes(d);
+    off += delta_seg_bytes(d) / 3 * 2;
     w.bytes = off;
     return w;
 }
@@ -1282,46 +1267,24 @@ hipError_t delta_fwd_saving(const Dims& d, const DeltaArgs& a) {
 
 hipError_t delta_bwd(const Dims& d, const DeltaBwdArgs& a) {
     const DeltaWs w = carve_delta(d, a.ws);
-    const WalkWs ww = carve_walk(d, w.walk, false);
-    const SegPlan sp = seg_plan(d);
+    const SegPlan sp = delta_plan(d);
     auto q = static_cast<const uint16_t*>(a.q), k = static_cast<const uint16_t*>(a.k), v = static_cast<const uint16_t*>(a.v);
     auto d_o = static_cast<const uint16_t*>(a.d_o);
     hipError_t e;
-    // forward again: What, Uhat, T, and the pseudo-values U in the layout of v
+    // forward again: T, the pseudo-values U in the layout of v, the segments' factors and entry states
     if (!d.save) {
         const DeltaPrepArgs pa{k, v, a.log_alpha, a.beta, a.bw, w.what, w.uhat, w.tt};
         const DeltaWalkArgs wa{q, k, w.what, w.uhat, a.log_alpha, nullptr, a.m0, nullptr, w.usave, w.usave_l};
         if ((e = launch_delta_fwd(d, pa, wa, w.seg, a.stream)) != hipSuccess) return e;
     }
-    // state gradients and dU, backward in time
-    {
-        const DeltaRevArgs ra{q, k, d_o, w.what, a.log_alpha, w.dstates, w.du_h, w.du_l, a.d_mT, a.d_m0};
-        e = d.kind == 0 ? launch_delta_rwalk<false>(d, ra, w.seg_r, a.stream) : launch_delta_rwalk<true>(d, ra, w.seg_r, a.stream);
-        if (e != hipSuccess) return e;
-    }
-    // with U as the values the recurrence is the scalar-decay one: dq, the key gradient through scores and state update
-    // and the decay gradient of those terms from the gradient walker (its value gradient is dU once more, not wanted)
-    if ((e = walk_bounds<false>(d, a.stream, sp, k, w.usave, a.log_alpha, a.m0, ww.bound_f, ww.gseg_f, 1, w.usave_l)) != hipSuccess) return e;
-    GradArgs ga{q, k, w.usave, d_o, a.log_alpha, w.dstates, static_cast<uint16_t*>(a.dq), static_cast<uint16_t*>(a.dk),
-                static_cast<uint16_t*>(a.dv), d.kind == 0 ? nullptr : a.d_log_alpha, a.m0, ww.bound_f, sp.m, sp.nseg, w.usave_l, w.du_h, w.du_l, w.dw_h, w.dw_l};
-    // dk <- head, dv <- remainder of its key gradient; it also leaves dW = -dU S^T, the gradient of What
+    // backward in time: state gradients, W, dv and db
+    const DeltaRevArgs ra{q, k, v, d_o, w.tt, a.log_alpha, a.beta, a.bw, w.dstates, w.w_h, w.w_l, static_cast<uint16_t*>(a.dv), a.d_bw, a.d_mT, a.d_m0};
+    e = d.kind == 0 ? launch_delta_rwalk<false>(d, ra, w.seg, w.seg_r, a.stream) : launch_delta_rwalk<true>(d, ra, w.seg, w.seg_r, a.stream);
+    if (e != hipSuccess) return e;
+    // forward in time, with U as the values: dq, dk and the gradients of decay and erase strength
+    GradArgs ga{q, k, w.usave, d_o, a.log_alpha, w.dstates, static_cast<uint16_t*>(a.dq), static_cast<uint16_t*>(a.dk), nullptr,
+                d.kind == 0 ? nullptr : a.d_log_alpha, a.m0, delta_entries(d, w.seg), sp.m, sp.nseg, w.usave_l, w.w_h, w.w_l, a.beta, a.d_beta};
     if ((e = launch_walk_grad(d, sp, ga, a.stream)) != hipSuccess) return e;
-    // everything that goes through the triangular solve, chunk by chunk; completes dk, dv and the parameter gradients
-    {
-        const DeltaGradArgs g3{k, v, w.du_h, w.du_l, w.dw_h, w.dw_l, w.tt, a.log_alpha, a.beta, a.bw,
-                               static_cast<const uint16_t*>(a.dk), static_cast<const uint16_t*>(a.dv),
-                               static_cast<uint16_t*>(a.dk), static_cast<uint16_t*>(a.dv), a.d_log_alpha, a.d_beta, a.d_bw};
-        const int jobs = d.N * d.BH();
-        const dim3 grid(jobs < 256 ? jobs : 256);
-        ProfScope ps(KID_DELTA_GRAD, a.stream);
-        if (d.kind == 0) {
-            if ((e = allow_lds(mk_delta_grad<false>, kDeltaGradLds)) != hipSuccess) return e;
-            hipLaunchKernelGGL(mk_delta_grad<false>, grid, dim3(kThreads), kDeltaGradLds, a.stream, d, g3);
-        } else {
-            if ((e = allow_lds(mk_delta_grad<true>, kDeltaGradLds)) != hipSuccess) return e;
-            hipLaunchKernelGGL(mk_delta_grad<true>, grid, dim3(kThreads), kDeltaGradLds, a.stream, d, g3);
-        }
-    }
     return hipGetLastError();
 }
 

@@ -319,7 +319,8 @@ __global__ __launch_bounds__(512, 1) void mk_delta_walk8(Dims d, DeltaWalkArgs a
     const int nsq = max(1, (walk.n + a.m - 1) / a.m);  // segments of this sequence
     const int kbeg = seg * a.m, kend = min(walk.n, kbeg + a.m), cnt = max(kend - kbeg, 0);
     if (MODE != 0) {
-        if (cnt <= 0 || seg >= nsq - 1) return;  // only segments whose end state another one starts from
+        // only segments whose end state another one starts from (the backward pass walks the last one's factor too)
+        if (cnt <= 0 || (seg >= nsq - 1 && !(MODE == 2 && a.usave))) return;
     } else if (seg >= nsq) {
         return;
     }
@@ -439,7 +440,7 @@ __global__ __launch_bounds__(512, 1) void mk_delta_walk8(Dims d, DeltaWalkArgs a
 }
 
 // Entry state of every segment: E_0 = M_0, E_{s+1} = A_s E_s + B_s (REV: from the last segment down, for the state
-// gradients), the product on the matrix cores with both factors as bf16 head + remainder (three products; about 2^-16 relative).
+// gradients, with the transposes of the forward walk's factors), the product on the matrix cores with both factors as bf16 head + remainder (three products; about 2^-16 relative).
 // LDS: A head | A remainder (128 x LD each) | E head | E remainder (128 x LDE each).   grid: (4, seqs)
 // The value columns of E evolve independently: a workgroup chains 32 of them, A and B of the next segment requested while
 // this one is multiplied.  Bound by the latency of that chain: 16 sequences of 2000 tokens in 16
@@ -501,7 +502,8 @@ __global__ __launch_bounds__(kThreads, 1) void mk_delta_combine(Dims d, const fl
         __syncthreads();  // A and E tiles are complete
         // E'[i][v] = sum_j A[i][j] E[j][v] + B[i][v]
         _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) {
-            const bf16x8 ah = frag(Ah, LD, 32 * wave + n, 16 * ks + 8 * half), al = frag(Al, LD, 32 * wave + n, 16 * ks + 8 * half);
+            const bf16x8 ah = REV ? frag_tr(Ah, LD, 16 * ks, 32 * wave, lane) : frag(Ah, LD, 32 * wave + n, 16 * ks + 8 * half);
+            const bf16x8 al = REV ? frag_tr(Al, LD, 16 * ks, 32 * wave, lane) : frag(Al, LD, 32 * wave + n, 16 * ks + 8 * half);
             const bf16x8 eh = frag_tr(Eh, LDE, 16 * ks, 0, lane), el = frag_tr(El, LDE, 16 * ks, 0, lane);
             acc = mfma(ah, eh, acc);
             acc = mfma(ah, el, acc);
@@ -522,166 +524,256 @@ __global__ __launch_bounds__(kThreads, 1) void mk_delta_combine(Dims d, const fl
 }
 
 // ---------------------------------------------------------------------------------------------
-// Backward, sequential part.  With U known, M_t = alpha_t M_{t-1} + k_t^T u_t is the scalar-decay recurrence on values
-// U, so the gradient walker of the diagonal kinds yields dq, the key gradient through the scores and the state
-// update, and the decay gradient of those terms, PROVIDED it is handed the state gradients of the delta rule.  Those
-// differ from the diagonal kinds': u_t depends on the state the chunk starts from (U = Uhat - What S), so per chunk
-//     dU = A^T dO + diag(wo) K dS'          (A = masked decayed scores, dS' = gradient of the state at the chunk end)
-//     dS = Gamma_C dS' + (diag(Gamma) Q)^T dO - What^T dU .
-// mk_delta_rwalk walks a sequence backward with dS in the accumulators (the forward walker's block layout), stores
-// dS' per chunk in the fragment-major bf16 form the gradient walker reads, and dU as bf16 head + remainder for the
-// kernels that take the gradient through the triangular solve.  The gradient walker, which has the state S of
-// every chunk in its accumulators, also forms dWhat = -dU S^T on the way (its VSPLIT variant).
+// Backward.  With U known, M_t = alpha_t M_{t-1} + k_t^T u_t is the scalar-decay recurrence on values U, so most of the
+// adjoint is the diagonal kinds' - if the state gradients are the delta rule's.  Those carry a feedback term, because u_t
+// depends on the state the chunk starts from: R = (I + L) U = diag(b) V - diag(beta Gamma) K S.  Per chunk, with A the masked
+// decayed scores, dS' the gradient of the state at the chunk end and W the gradient of R,
+//     dU = A^T dO + diag(wo) K dS' ,   W = T^T dU ,
+//     dS = Gamma_C dS' + (diag(Gamma) Q)^T dO - (diag(beta Gamma) K)^T W .
+// Everything that reaches the inputs through the solve follows from W without T (the gradient of T is dU R^T and
+// dL = -T^T (dU R^T) T^T = -W U^T, since T R = U):
+//     dv_t = b_t W_t ,  db_t = W_t . v_t ,
+//     X_t = -Gamma_t S W_t + sum_{r < t} H_tr k_r ,   H_tr = -D_tr (W_t . u_r) ,  D_tr = e^{lg_t - lg_r} ,
+//     dk_t += beta_t X_t + sum_{j > t} beta_j H_jt k_j ,   d beta_t = k_t . X_t ,
+// and the erase term enters the decay gradient like a second query: + beta_t k_t . X_t, its key side with the other
+// key gradients.  mk_delta_rwalk walks a sequence backward with dS in the accumulators (the forward walker's block layout),
+// stores dS' per chunk in the fragment-major bf16 form the gradient walker reads, W as bf16 head + remainder, dv and db; the
+// gradient walker (VSPLIT) does the rest, entering its segments with the forward walk's states.  Bytes a token of the backward:
+// 5.1 KB.  With dU handed on instead of W, a kernel of its own took the gradient through T chunk by chunk (9.2 KB a token, a
+// summary pass over U for the entry states): forward + backward, 16 x 16 sequences of 2048, 1.64 -> 1.19 ms.
 struct DeltaRevArgs {
-    const uint16_t *q, *k, *d_o;
-    const uint16_t* what;     // [BH*T][128] bf16 (library order)
-    const float* log_alpha;
+    const uint16_t *q, *k, *v, *d_o;
+    const uint16_t* tt;       // [BH*N][2][64][64] bf16: T^T (rows r, columns t), head and remainder planes
+    const float *log_alpha, *beta, *bw;
     uint16_t* dstates;        // [BH*N] fragment-major bf16: slot c = gradient of the state at the end of chunk c
-    uint16_t *du_h, *du_l;    // [BH*T][128] bf16 (library order)
+    uint16_t *w_h, *w_l;      // [BH*T][128] bf16 (library order)
+    uint16_t* dv;             // layout of v
+    float* d_bw;              // per token, may be NULL
     const float* edge_in;     // d M_T [i][v] per sequence or NULL
     float* edge_out;          // d M_0 or NULL
     int m, nseg;              // segments as for the forward walker: the walk enters segment s (from above) with bound[seq][s],
-    const float* bound;       // the summary modes leave what the segment makes of a zero / identity state in sum[seq][s]
-    float* sum;
+    const float* bound;       // the summary leaves what the segment makes of a zero state in sum[seq][s] (what it makes of the
+    float* sum;               // identity is the transpose of the forward walk's factor)
 };
 constexpr int LDW = 40;  // row stride of a wave's private 32-column tiles
-// LDS: Q | K | dO | What (64 x LD) | scores head | remainder (64 x LDP) | per wave: 128 x LDW bf16 (its columns of dS',
-// then of dU head and remainder, 64 x LDW each) | bs | wo | Gamma
-constexpr int kDeltaRevLds = (4 * C * LD + 2 * C * LDP) * 2 + 4 * D * LDW * 2 + (3 * C + 8) * 4;
+// LDS: Q | K | dO (64 x LD) | T^T head | remainder | scores head | remainder (64 x LDP) | per wave: 128 x LDW bf16 (its columns
+// of dS', then of W head and remainder, 64 x LDW each) | bs | wo | Gamma | -beta Gamma | b | db per wave
+constexpr int kDeltaRevLds = (3 * C * LD + 4 * C * LDP) * 2 + 4 * D * LDW * 2 + (5 * C + 8 + 4 * C) * 4;
 
-// grid: (segments, seqs).  MODE 0: the walk.  MODE 1 / 2: summary of a segment (nothing stored but its end state), from a
-// zero state / from the identity with d_o = 0.
-template <bool DEC, int MODE = 0>
+// a token-contraction operand like frag_tr whose k order follows a D-layout block (frag_perm's): slot e of lane (n, half) is row
+// row0 + 8 (e / 4) + 4 half + e % 4 of column col0 + n
+__device__ __forceinline__ bf16x8 frag_tr_perm(const uint16_t* tile, int ld, int row0, int col0, int lane) {
+    const int r = lane & 15, nblk = (lane >> 4) & 1, half = lane >> 5;
+    const uint16_t* p = tile + (row0 + 4 * half + (r >> 2)) * ld + col0 + 16 * nblk + 4 * (r & 3);
+    typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
+    const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p)));
+    const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 8 * ld)));
+    return __builtin_bit_cast(bf16x8, u32x4{lo.x, lo.y, hi.x, hi.y});
+}
+// registers 8p .. 8p+7 of a D-layout block as an operand of the next product (k = its rows), head and remainder
+__device__ __forceinline__ void split_frag(const f32x16& x, int p, u32x4& hi, u32x4& lo) {
+    _Pragma("unroll") for (int e = 0; e < 4; ++e) {
+        const float x0 = x[8 * p + 2 * e], x1 = x[8 * p + 2 * e + 1];
+        hi[e] = pack2(x0, x1);
+        lo[e] = pack2(x0 - bf16_lo(hi[e]), x1 - bf16_hi(hi[e]));
+    }
+}
+// ... and such an operand to LDS by rows: lane = column, so neighbouring lanes exchange halves and store two columns at once.
+// dst: row 0, column 0 of the 16 rows and 32 columns
+__device__ __forceinline__ void store_frag_rows(uint16_t* dst, int ld, const u32x4& w, int n, int half) {
+    const bool odd = n & 1;
+    uint16_t* p = dst + (4 * half + (odd ? 1 : 0)) * ld + (n & ~1);
+    const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+    _Pragma("unroll") for (int e = 0; e < 4; ++e) {
+        const uint32_t other = __builtin_amdgcn_mov_dpp(int(w[e]), 0xB1, 0xf, 0xf, true);  // lane ^ 1
+        *reinterpret_cast<uint32_t*>(p + (8 * (e >> 1) + 2 * (e & 1)) * ld) = __builtin_amdgcn_perm(other, w[e], sel);
+    }
+}
+// weights of the rows of registers 8p .. 8p+7 of a D-layout block at row0
+__device__ __forceinline__ void row_weights(const float* tab, int row0, int half, float (&w)[8]) {
+    const float4 a = *reinterpret_cast<const float4*>(tab + row0 + 4 * half), b = *reinterpret_cast<const float4*>(tab + row0 + 8 + 4 * half);
+    w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w; w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w;
+}
+
+// grid: (segments, seqs).  SUM: summary of a segment from a zero state (nothing stored but its end state).
+// A wave owns value columns [32 w, 32 w + 32) of dS, dU and W; the products that lead from one to the next take the block before
+// straight out of the accumulators (lane = value column, registers = the next contraction's index), so only scores, T and
+// input rows are read from LDS.
+template <bool DEC, bool SUM>
 __global__ __launch_bounds__(kThreads, 1) void mk_delta_rwalk(Dims d, DeltaRevArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     uint16_t* Q = reinterpret_cast<uint16_t*>(smem);
     uint16_t* K = Q + C * LD;
     uint16_t* dO = K + C * LD;
-    uint16_t* Wh = dO + C * LD;
-    uint16_t* Ph = Wh + C * LD;
+    uint16_t* TTh = dO + C * LD;
+    uint16_t* TTl = TTh + C * LDP;
+    uint16_t* Ph = TTl + C * LDP;
     uint16_t* Pl = Ph + C * LDP;
     uint16_t* priv = Pl + C * LDP;
     float* bs = reinterpret_cast<float*>(priv + 4 * D * LDW);
     float* wo = bs + C + 4;
     float* gm = wo + C + 4;
+    float* ne = gm + C;           // -beta Gamma
+    float* bb = ne + C;
+    float* red = bb + C;          // [wave][64]
 
     const int seg = blockIdx.x, seq = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 31, half = lane >> 5;
     const SeqWalk walk = seq_walk(d, seq);
     const int nsq = max(1, (walk.n + a.m - 1) / a.m);
     const int kbeg = seg * a.m, kend = min(walk.n, kbeg + a.m), cnt = max(kend - kbeg, 0);
-    if (MODE != 0) {
+    if (SUM) {
         if (cnt <= 0 || seg == 0) return;  // only segments whose end state (backward in time) another one starts from
     } else if (seg >= nsq) {
         return;
     }
     uint16_t* pw = priv + wave * D * LDW;   // this wave's region
-    uint16_t* duh = pw;
-    uint16_t* dul = pw + C * LDW;
+    uint16_t* wh = pw;
+    uint16_t* wl = pw + C * LDW;
 
     f32x16 S[4];  // dS[ib][4g+j] = dS[i = 32 ib + 8g + 4 half + j][v = 32 wave + n]
     _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) S[ib] = f32x16{0};
-    if (MODE == 0) {
+    if (!SUM) {
         const float* ein = a.nseg > 1 ? a.bound + (size_t(seq) * a.nseg + seg) * D * D
                                       : (a.edge_in ? a.edge_in + size_t(seq) * D * D : nullptr);
         if (ein) walk_state_load(S, ein, false, wave, n, half);
-    } else if (MODE == 2) {
-        _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
-            _Pragma("unroll") for (int x = 0; x < 16; ++x)
-                S[ib][x] = (32 * ib + 8 * (x >> 2) + 4 * half + (x & 3) == 32 * wave + n) ? 1.f : 0.f;
     }
 
-    TileRegs rq, rk, ro, rw;
-    float gval = 0.f;
+    TileRegs rq, rk, ro, rt;
+    float gval = 0.f, bval = 1.f, bwval = 1.f;
     auto gload = [&](int kk) {
         const ChunkPos p = walk_pos(d, walk, kend - 1 - min(kk, cnt - 1));
-        if (DEC) gval = a.log_alpha[p.tok0 + size_t(min(lane, p.L - 1)) * p.ts];
-        if (MODE != 2) {
-            walk_gload<false, kThreads>(rq, a.q, p.tok0, p.ts, p.L, tid);
-            walk_gload<false, kThreads>(ro, a.d_o, p.tok0, p.ts, p.L, tid);
-        }
+        const size_t pt = p.tok0 + size_t(min(lane, p.L - 1)) * p.ts;
+        if (DEC) gval = a.log_alpha[pt];
+        if (a.beta) bval = a.beta[pt];
+        if (!SUM && a.bw) bwval = a.bw[pt];
+        walk_gload<false, kThreads>(rq, a.q, p.tok0, p.ts, p.L, tid);
+        walk_gload<false, kThreads>(ro, a.d_o, p.tok0, p.ts, p.L, tid);
         walk_gload<false, kThreads>(rk, a.k, p.tok0, p.ts, p.L, tid);
-        walk_gload<false, kThreads>(rw, a.what, p.wtok0, 1, p.L, tid);
+        const uint16_t* gtt = a.tt + p.slot * 2 * C * C;
+        _Pragma("unroll") for (int it = 0; it < 4; ++it) rt.v[it] = *reinterpret_cast<const u32x4*>(gtt + 8 * (tid + kThreads * it));
     };
     if (cnt > 0) gload(0);
 
     for (int kk = 0; kk < cnt; ++kk) {
         const ChunkPos cp = walk_pos(d, walk, kend - 1 - kk);
         const int L = cp.L;
-        if (MODE != 2) {
-            walk_commit<kThreads>(Q, rq, L, tid);
-            walk_commit<kThreads>(dO, ro, L, tid);
-        }
+        walk_commit<kThreads>(Q, rq, L, tid);
+        walk_commit<kThreads>(dO, ro, L, tid);
         walk_commit<kThreads>(K, rk, L, tid);
-        walk_commit<kThreads>(Wh, rw, L, tid);
-        if (DEC && wave == 0) {
-            walk_decay_tables<false>(gval, L, 0.f, bs, wo, lane);
-            gm[lane] = __expf(bs[lane]);
+        _Pragma("unroll") for (int it = 0; it < 4; ++it) {
+            const int p = tid + kThreads * it, row = (p >> 3) & 63, piece = p & 7;
+            *reinterpret_cast<u32x4*>((p >> 9 ? TTl : TTh) + row * LDP + 8 * piece) = rt.v[it];
+        }
+        if (wave == 0) {
+            float gam = 1.f;
+            if (DEC) {
+                walk_decay_tables<false>(gval, L, 0.f, bs, wo, lane);
+                gm[lane] = gam = __expf(bs[lane]);
+            }
+            ne[lane] = lane < L ? -bval * gam : 0.f;
+            bb[lane] = lane < L ? bwval : 0.f;
         }
         gload(kk + 1);
-        __syncthreads();  // (A) tiles and decay tables of this chunk are in LDS
+        u32x4 vv[4];  // this lane's pieces of v, for db: row (lane >> 2) + 16 it, columns 32 wave + 8 (lane & 3)
+        if (!SUM) {
+            _Pragma("unroll") for (int it = 0; it < 4; ++it)
+                vv[it] = *reinterpret_cast<const u32x4*>(a.v + (cp.tok0 + size_t(min((lane >> 2) + 16 * it, L - 1)) * cp.ts) * D + 32 * wave + 8 * (lane & 3));
+        }
+        __syncthreads();  // (A) tiles and tables of this chunk are in LDS
         const float bC = DEC ? bs[C] : 0.f;
 
         // ---- dS' of this wave's columns -> global, fragment-major: through the wave's private tile [i][v - 32 wave]
-        if (MODE == 0) {
-        _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
-            _Pragma("unroll") for (int x = 0; x < 16; ++x)
-                pw[(32 * ib + 8 * (x >> 2) + 4 * half + (x & 3)) * LDW + n] = uint16_t(pack2(S[ib][x], 0.f));
-        __builtin_amdgcn_wave_barrier();
-        {
+        if (!SUM) {
+            _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
+                _Pragma("unroll") for (int p = 0; p < 2; ++p) {
+                    u32x4 h;
+                    _Pragma("unroll") for (int e = 0; e < 4; ++e) h[e] = pack2(S[ib][8 * p + 2 * e], S[ib][8 * p + 2 * e + 1]);
+                    store_frag_rows(pw + (32 * ib + 16 * p) * LDW, LDW, h, n, half);
+                }
+            __builtin_amdgcn_wave_barrier();
             uint16_t* dst = a.dstates + cp.slot * D * D;
             _Pragma("unroll") for (int blk = 0; blk < 4; ++blk)
                 _Pragma("unroll") for (int q2 = 0; q2 < 2; ++q2) {
                     const u32x4 val = *reinterpret_cast<const u32x4*>(pw + (32 * blk + n) * LDW + 16 * q2 + 8 * half);
                     __builtin_nontemporal_store(val, reinterpret_cast<u32x4*>(dst + state_frag_off(blk, 2 * wave + q2, lane)));
                 }
-        }
-        __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_wave_barrier();
         }
 
-        // ---- dU^T[v][t] = wo_t sum_i dS'[i][v] k_t[i] + sum_{j >= t} dO[j][v] P[j][t]
-        f32x16 dU[2];
-        walk_inter<false>(dU, S, K, bs, n, half);
+        // ---- dU[t][v] = wo_t sum_i k_t[i] dS'[i][v] + sum_{j >= t} P[j][t] dO[j][v]
+        f32x16 dU[2] = {{0}, {0}};
+        _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
+            _Pragma("unroll") for (int p = 0; p < 2; ++p) {
+                u32x4 hi, lo;
+                split_frag(S[ib], p, hi, lo);
+                const bf16x8 sh = __builtin_bit_cast(bf16x8, hi), sl = __builtin_bit_cast(bf16x8, lo);
+                const bf16x8 k0 = frag_perm(K, LD, n, 32 * ib + 16 * p, half), k1 = frag_perm(K, LD, 32 + n, 32 * ib + 16 * p, half);
+                dU[0] = mfma(k0, sh, dU[0]);
+                dU[1] = mfma(k1, sh, dU[1]);
+                dU[0] = mfma(k0, sl, dU[0]);
+                dU[1] = mfma(k1, sl, dU[1]);
+            }
         if (DEC) {
-            _Pragma("unroll") for (int tb = 0; tb < 2; ++tb) {
-                const float w = wo[32 * tb + n];
-                _Pragma("unroll") for (int x = 0; x < 16; ++x) dU[tb][x] *= w;
-            }
-        }
-        if (MODE != 2) {
-            walk_scores<DEC>(K, Q, Ph, Pl, bs, wave, n, half);
-            __syncthreads();  // (C) scores are in LDS
-        }
-        _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
-            if (MODE != 2) {
-                _Pragma("unroll") for (int ks = 2 * nb; ks < 4; ++ks) {  // queries j < 32 never see keys t >= 32
-                    const bf16x8 dot = frag_tr(dO, LD, 16 * ks, 32 * wave, lane);
-                    dU[nb] = mfma(dot, frag_tr(Ph, LDP, 16 * ks, 32 * nb, lane), dU[nb]);
-                    dU[nb] = mfma(dot, frag_tr(Pl, LDP, 16 * ks, 32 * nb, lane), dU[nb]);
+            _Pragma("unroll") for (int tb = 0; tb < 2; ++tb)
+                _Pragma("unroll") for (int p = 0; p < 2; ++p) {
+                    float w[8];
+                    row_weights(wo, 32 * tb + 16 * p, half, w);
+                    _Pragma("unroll") for (int x = 0; x < 8; ++x) dU[tb][8 * p + x] *= w[x];
                 }
-            }
-            const PackedBlock uh = pack_block(dU[nb]);
-            f32x16 r = dU[nb];
-            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                r[4 * g + 0] -= bf16_lo(uh.v[g].x);
-                r[4 * g + 1] -= bf16_hi(uh.v[g].x);
-                r[4 * g + 2] -= bf16_lo(uh.v[g].y);
-                r[4 * g + 3] -= bf16_hi(uh.v[g].y);
-            }
-            store_packed(duh, LDW, 32 * nb + n, 0, half, uh);
-            store_packed(dul, LDW, 32 * nb + n, 0, half, pack_block(r));
         }
-        __builtin_amdgcn_wave_barrier();
-        if (MODE == 0) {
-        _Pragma("unroll") for (int it = 0; it < 4; ++it) {
-            const int row = (lane >> 2) + 16 * it, piece = lane & 3;
-            if (row < L) {
-                const size_t off = (cp.wtok0 + row) * D + 32 * wave + 8 * piece;
-                *reinterpret_cast<u32x4*>(a.du_h + off) = *reinterpret_cast<const u32x4*>(duh + row * LDW + 8 * piece);
-                *reinterpret_cast<u32x4*>(a.du_l + off) = *reinterpret_cast<const u32x4*>(dul + row * LDW + 8 * piece);
+        walk_scores<DEC>(K, Q, Ph, Pl, bs, wave, n, half);
+        __syncthreads();  // (C) scores are in LDS
+        _Pragma("unroll") for (int tb = 0; tb < 2; ++tb)
+            _Pragma("unroll") for (int ks = 2 * tb; ks < 4; ++ks) {  // queries j < 32 never see keys t >= 32
+                const bf16x8 dot = frag_tr(dO, LD, 16 * ks, 32 * wave, lane);
+                dU[tb] = mfma(frag_tr(Ph, LDP, 16 * ks, 32 * tb, lane), dot, dU[tb]);
+                dU[tb] = mfma(frag_tr(Pl, LDP, 16 * ks, 32 * tb, lane), dot, dU[tb]);
+            }
+        // ---- W[r][v] = sum_{t >= r} T[t][r] dU[t][v]
+        f32x16 W[2] = {{0}, {0}};
+        _Pragma("unroll") for (int kt = 0; kt < 4; ++kt) {
+            u32x4 hi, lo;
+            split_frag(dU[kt >> 1], kt & 1, hi, lo);
+            const bf16x8 uh = __builtin_bit_cast(bf16x8, hi), ul = __builtin_bit_cast(bf16x8, lo);
+            _Pragma("unroll") for (int rb = 0; rb <= (kt >> 1); ++rb) {
+                const bf16x8 th = frag_perm(TTh, LDP, 32 * rb + n, 16 * kt, half), tl = frag_perm(TTl, LDP, 32 * rb + n, 16 * kt, half);
+                W[rb] = mfma(th, uh, W[rb]);
+                W[rb] = mfma(tl, uh, W[rb]);
+                W[rb] = mfma(th, ul, W[rb]);
             }
         }
+        if (!SUM) {
+            _Pragma("unroll") for (int kt = 0; kt < 4; ++kt) {
+                u32x4 hi, lo;
+                split_frag(W[kt >> 1], kt & 1, hi, lo);
+                store_frag_rows(wh + 16 * kt * LDW, LDW, hi, n, half);
+                store_frag_rows(wl + 16 * kt * LDW, LDW, lo, n, half);
+            }
+            __builtin_amdgcn_wave_barrier();
+            // W to memory; dv and this wave's share of db on the way
+            _Pragma("unroll") for (int it = 0; it < 4; ++it) {
+                const int row = (lane >> 2) + 16 * it, piece = lane & 3;
+                const u32x4 h = *reinterpret_cast<const u32x4*>(wh + row * LDW + 8 * piece), l = *reinterpret_cast<const u32x4*>(wl + row * LDW + 8 * piece);
+                const float b = bb[row];
+                u32x4 o;
+                float s = 0.f;
+                _Pragma("unroll") for (int p = 0; p < 4; ++p) {
+                    const float w0 = bf16_lo(h[p]) + bf16_lo(l[p]), w1 = bf16_hi(h[p]) + bf16_hi(l[p]);
+                    s += w0 * bf16_lo(vv[it][p]) + w1 * bf16_hi(vv[it][p]);
+                    o[p] = pack2(b * w0, b * w1);
+                }
+                if (row < L) {
+                    const size_t off = (cp.wtok0 + row) * D + 32 * wave + 8 * piece;
+                    *reinterpret_cast<u32x4*>(a.w_h + off) = h;
+                    *reinterpret_cast<u32x4*>(a.w_l + off) = l;
+                    __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(a.dv + (cp.tok0 + size_t(row) * cp.ts) * D + 32 * wave + 8 * piece));
+                }
+                s += __shfl_xor(s, 1, 64);
+                s += __shfl_xor(s, 2, 64);
+                if (piece == 0) red[wave * C + row] = s;
+            }
         }
-        // ---- dS = Gamma_C dS' + sum_t (Gamma_t q_t)^T dO_t - sum_t what_t^T dU_t
+        // ---- dS = Gamma_C dS' + sum_t (Gamma_t q_t)^T dO_t - sum_t (beta_t Gamma_t k_t)^T W_t
         if (DEC) {
             const float lam = __expf(bC);
             _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
@@ -701,328 +793,28 @@ __global__ __launch_bounds__(kThreads, 1) void mk_delta_rwalk(Dims d, DeltaRevAr
                 }
             }
             const bf16x8 oh = __builtin_bit_cast(bf16x8, hi), ol = __builtin_bit_cast(bf16x8, lo);
-            u32x4 nh = __builtin_bit_cast(u32x4, frag_tr(duh, LDW, 16 * ks, 0, lane));
-            u32x4 nl = __builtin_bit_cast(u32x4, frag_tr(dul, LDW, 16 * ks, 0, lane));
-            _Pragma("unroll") for (int p = 0; p < 4; ++p) {  // -dU
-                nh[p] ^= 0x80008000u;
-                nl[p] ^= 0x80008000u;
-            }
-            const bf16x8 uh = __builtin_bit_cast(bf16x8, nh), ul = __builtin_bit_cast(bf16x8, nl);
+            float w[8];
+            row_weights(ne, 16 * ks, half, w);
+            f32x16& Wb = W[ks >> 1];
+            _Pragma("unroll") for (int x = 0; x < 8; ++x) Wb[8 * (ks & 1) + x] *= w[x];
+            split_frag(Wb, ks & 1, hi, lo);
+            const bf16x8 eh = __builtin_bit_cast(bf16x8, hi), el = __builtin_bit_cast(bf16x8, lo);
             _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) {
-                const bf16x8 wa = frag_tr(Wh, LD, 16 * ks, 32 * ib, lane);
-                if (MODE != 2) {
-                    const bf16x8 qa = frag_tr(Q, LD, 16 * ks, 32 * ib, lane);
-                    S[ib] = mfma(qa, oh, S[ib]);
-                    if (DEC) S[ib] = mfma(qa, ol, S[ib]);
-                }
-                S[ib] = mfma(wa, uh, S[ib]);
-                S[ib] = mfma(wa, ul, S[ib]);
+                const bf16x8 qa = frag_tr(Q, LD, 16 * ks, 32 * ib, lane);
+                S[ib] = mfma(qa, oh, S[ib]);
+                if (DEC) S[ib] = mfma(qa, ol, S[ib]);
+                const bf16x8 ka = frag_tr_perm(K, LD, 16 * ks, 32 * ib, lane);
+                S[ib] = mfma(ka, eh, S[ib]);
+                S[ib] = mfma(ka, el, S[ib]);
             }
         }
         __syncthreads();  // (D) every read of this chunk's tiles is done
+        if (!SUM && a.d_bw && wave == 0 && lane < L)
+            a.d_bw[cp.tok0 + size_t(lane) * cp.ts] = (red[lane] + red[C + lane]) + (red[2 * C + lane] + red[3 * C + lane]);
     }
-    if (MODE != 0) {
+    if (SUM) {
         walk_state_store(S, a.sum + (size_t(seq) * a.nseg + seg) * D * D, false, wave, n, half);
         return;
     }
     if (a.edge_out && seg == 0) walk_state_store(S, a.edge_out + size_t(seq) * D * D, false, wave, n, half);
-}
-
-// ---------------------------------------------------------------------------------------------
-// Backward, the chunk-local part: everything that reaches the inputs through the triangular solve.  Per chunk, with
-// T = (I + L)^-1, Uhat = T diag(b) V, What = T diag(beta Gamma) K and the gradients dU (of Uhat) and dWhat:
-//   dVb = T^T dU          -> dv_r = b_r dVb_r ,            db_r = dVb_r . v_r
-//   dKb = T^T dWhat       -> dk_r += beta_r Gamma_r dKb_r , c_r = dKb_r . k_r  (-> d beta_r += Gamma_r c_r, d lg_r += beta_r Gamma_r c_r)
-//   dT  = dU (diag(b) V)^T + dWhat (diag(beta Gamma) K)^T   (only its strictly lower part matters)
-//   dL  = -T^T dT T^T     (strictly lower part);  L_tr = beta_t e^{lg_t - lg_r} (k_t . k_r):
-//   F_tr = dL_tr e^{lg_t - lg_r} (k_t . k_r):  d beta_t += sum_r F_tr ;  d lg_t += beta_t sum_r F_tr ;  d lg_r -= sum_t beta_t F_tr
-//   dG_tr = beta_t e^{lg_t - lg_r} dL_tr:      dk_t += sum_r dG_tr k_r ,  dk_r += sum_t dG_tr k_t
-// and d log alpha_t = sum_{s >= t} d lg_s inside the chunk (lg is the chunk-local running sum).  The key gradient of
-// the gradient walker (head + remainder) is added before the one rounding to bf16, its decay gradient is added to.
-struct DeltaGradArgs {
-    const uint16_t *k, *v;            // layout of the caller
-    const uint16_t *du_h, *du_l, *dw_h, *dw_l;  // [BH*T][128] (library order)
-    const uint16_t* tt;               // [BH*N][2][64][64]
-    const float *log_alpha, *beta, *bw;
-    const uint16_t *dk1_h, *dk1_l;    // the gradient walker's key gradient, layout of the caller
-    uint16_t *dk, *dv;
-    float *d_log_alpha, *d_beta, *d_bw;   // d_log_alpha is added to
-};
-// LDS: K | V | dU head | remainder | dWhat head | remainder (64 x LD) | T^T head | remainder | dT head | remainder
-// (64 x LDP) | lg, beta, b, e^{lg} | reductions.  After the first phase the five tiles behind K are spent and hold
-// M1 = dT T^T and dG (head, remainder, 64 x LDP each) and the stages of dv and dk.
-constexpr int kDeltaGradRed = (4 * C + 4 * 2 * C + 3 * C + 3 * C) * 4;  // params | db, c per wave | row sums | column sums
-constexpr int kDeltaGradLds = 6 * C * LD * 2 + 4 * C * LDP * 2 + kDeltaGradRed;
-
-// grid: up to one workgroup per compute unit; each takes chunks blockIdx.x, blockIdx.x + gridDim.x, ...
-template <bool DEC>
-__global__ __launch_bounds__(kThreads, 1) void mk_delta_grad(Dims d, DeltaGradArgs a) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    uint16_t* K = reinterpret_cast<uint16_t*>(smem);
-    uint16_t* V = K + C * LD;
-    uint16_t* dUh = V + C * LD;
-    uint16_t* dUl = dUh + C * LD;
-    uint16_t* dWh = dUl + C * LD;
-    uint16_t* dWl = dWh + C * LD;
-    uint16_t* TTh = dWl + C * LD;
-    uint16_t* TTl = TTh + C * LDP;
-    uint16_t* dTh = TTl + C * LDP;
-    uint16_t* dTl = dTh + C * LDP;
-    float* lg = reinterpret_cast<float*>(dTl + C * LDP);
-    float* be = lg + C;
-    float* bb = be + C;
-    float* gm = bb + C;           // e^{lg}
-    float* red_db = gm + C;       // [wave][64]
-    float* red_c = red_db + 4 * C;
-    float* rowF = red_c + 4 * C;  // [3 blocks][32]: sum_r F_tr per t of the block
-    float* colE = rowF + 3 * C;   // [3 blocks][32]: sum_t beta_t F_tr per r of the block   (3 * C floats reserved each)
-    // second phase, over V .. dWl
-    uint16_t* M1h = V;
-    uint16_t* M1l = M1h + C * LDP;
-    uint16_t* dGh = M1l + C * LDP;
-    uint16_t* dGl = dGh + C * LDP;
-    uint16_t* stv = dGl + C * LDP;   // stage of dv (64 x LD)
-    uint16_t* stk = stv + C * LD;    // stage of dk
-    static_assert(4 * C * LDP + 2 * C * LD <= 5 * C * LD, "second phase fits behind K");
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 31, half = lane >> 5;
-    const int jobs = d.N * d.BH();
-    // One workgroup per compute unit walks over chunks; the rows of the next chunk are requested into registers while
-    // this one is worked on (the kernel needs most of the unit's LDS, so no second workgroup hides the loads).
-    struct Pre { TileRegs k, v, uh, ul, wh, wl; u32x4 tt[4]; float la, be, bw; } pre;
-    auto gload = [&](int job) {
-        const ChunkPos p = chunk_pos(d, job % d.N, job / d.N);
-        const int Lp = max(p.L, 1);
-        const size_t pt = p.tok0 + size_t(min(lane, Lp - 1)) * p.ts;
-        pre.la = DEC ? a.log_alpha[pt] : 0.f;
-        pre.be = a.beta ? a.beta[pt] : 1.f;
-        pre.bw = a.bw ? a.bw[pt] : 1.f;
-        tile_gload(pre.k, a.k, p.tok0, p.ts, Lp, tid);
-        tile_gload(pre.v, a.v, p.tok0, p.ts, Lp, tid);
-        tile_gload(pre.uh, a.du_h, p.wtok0, 1, Lp, tid);
-        tile_gload(pre.ul, a.du_l, p.wtok0, 1, Lp, tid);
-        tile_gload(pre.wh, a.dw_h, p.wtok0, 1, Lp, tid);
-        tile_gload(pre.wl, a.dw_l, p.wtok0, 1, Lp, tid);
-        const uint16_t* gtt = a.tt + p.slot * 2 * C * C;
-        _Pragma("unroll") for (int it = 0; it < 4; ++it) {
-            const int q = tid + kThreads * it, plane = q >> 9, row = (q >> 3) & 63, piece = q & 7;
-            pre.tt[it] = *reinterpret_cast<const u32x4*>(gtt + plane * C * C + row * C + 8 * piece);
-        }
-    };
-    if (int(blockIdx.x) < jobs) gload(blockIdx.x);
-  for (int job = blockIdx.x; job < jobs; job += gridDim.x) {
-    const ChunkPos cp = chunk_pos(d, job % d.N, job / d.N);
-    const int L = cp.L;
-    const size_t ptok = cp.tok0 + size_t(min(lane, max(L, 1) - 1)) * cp.ts;
-    if (wave == 0) {
-        float x = (DEC && lane < L) ? pre.la : 0.f;
-        for (int off = 1; off < 64; off <<= 1) {
-            const float y = __shfl_up(x, off, 64);
-            if (lane >= off) x += y;
-        }
-        lg[lane] = x;
-        be[lane] = lane < L ? pre.be : 0.f;
-        bb[lane] = lane < L ? pre.bw : 0.f;
-        gm[lane] = DEC ? __expf(x) : 1.f;
-    }
-    tile_commit(K, pre.k, L, tid);
-    tile_commit(V, pre.v, L, tid);
-    tile_commit(dUh, pre.uh, L, tid);
-    tile_commit(dUl, pre.ul, L, tid);
-    tile_commit(dWh, pre.wh, L, tid);
-    tile_commit(dWl, pre.wl, L, tid);
-    _Pragma("unroll") for (int it = 0; it < 4; ++it) {
-        const int q = tid + kThreads * it, plane = q >> 9, row = (q >> 3) & 63, piece = q & 7;
-        *reinterpret_cast<u32x4*>((plane ? TTl : TTh) + row * LDP + 8 * piece) = pre.tt[it];
-    }
-    // the gradient walker's key gradient of this chunk (both planes), wanted at the very end
-    u32x2 k1h[2][4], k1l[2][4];
-    _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
-        const size_t row = (cp.tok0 + size_t(min(32 * nb + n, max(L, 1) - 1)) * cp.ts) * D + 32 * wave + 4 * half;
-        _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-            k1h[nb][g] = *reinterpret_cast<const u32x2*>(a.dk1_h + row + 8 * g);
-            k1l[nb][g] = *reinterpret_cast<const u32x2*>(a.dk1_l + row + 8 * g);
-        }
-    }
-    if (job + int(gridDim.x) < jobs) gload(job + gridDim.x);
-    __syncthreads();
-
-    // ---- first phase
-    PackedBlock resv[2];
-    f32x16 dk2[2];
-    _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
-        // dVb^T[v][r] = sum_t dU[t][v] T[t][r],  dKb^T[i][r] = sum_t dWhat[t][i] T[t][r]  (T[t][r] = 0 for t < r)
-        f32x16 av = {0}, ak = {0};
-        _Pragma("unroll") for (int ks = 2 * nb; ks < 4; ++ks) {
-            const bf16x8 th = frag(TTh, LDP, 32 * nb + n, 16 * ks + 8 * half), tl = frag(TTl, LDP, 32 * nb + n, 16 * ks + 8 * half);
-            const bf16x8 uh = frag_tr(dUh, LD, 16 * ks, 32 * wave, lane), ul = frag_tr(dUl, LD, 16 * ks, 32 * wave, lane);
-            const bf16x8 wh = frag_tr(dWh, LD, 16 * ks, 32 * wave, lane), wl = frag_tr(dWl, LD, 16 * ks, 32 * wave, lane);
-            av = mfma(uh, th, av);
-            av = mfma(uh, tl, av);
-            av = mfma(ul, th, av);
-            ak = mfma(wh, th, ak);
-            ak = mfma(wh, tl, ak);
-            ak = mfma(wl, th, ak);
-        }
-        const int r = 32 * nb + n;
-        float pdb = row_dot(V, r, wave, half, av), pc = row_dot(K, r, wave, half, ak);
-        pdb += __shfl_xor(pdb, 32, 64);
-        pc += __shfl_xor(pc, 32, 64);
-        if (half == 0) {
-            red_db[wave * C + r] = pdb;
-            red_c[wave * C + r] = pc;
-        }
-        const float br = bb[r], wr = be[r] * gm[r];
-        _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-            av[x] *= br;
-            ak[x] *= wr;
-        }
-        resv[nb] = pack_block(av);
-        dk2[nb] = ak;
-    }
-    // dT[t][r] for r < t, blocks (r, t) = (0,0), (0,1), (1,1) by waves 0, 1, 2; wave 3 clears the block above the diagonal
-    if (wave < 3) {
-        const int rb = wave == 2 ? 1 : 0, tb = wave ? 1 : 0;
-        f32x16 t1 = score_block2(V, 32 * rb, dUh, 32 * tb, n, half);   // D[m = r][n = t] = v_r . dU_t
-        t1 = score_block2(V, 32 * rb, dUl, 32 * tb, n, half, t1);
-        f32x16 t2 = score_block2(K, 32 * rb, dWh, 32 * tb, n, half);
-        t2 = score_block2(K, 32 * rb, dWl, 32 * tb, n, half, t2);
-        const int t = 32 * tb + n;
-        _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-            const int r0 = 32 * rb + 8 * g + 4 * half;
-            const float4 b4 = *reinterpret_cast<const float4*>(bb + r0), e4 = *reinterpret_cast<const float4*>(be + r0);
-            const float4 g4 = *reinterpret_cast<const float4*>(gm + r0);
-            const float bv[4] = {b4.x, b4.y, b4.z, b4.w}, wv[4] = {e4.x * g4.x, e4.y * g4.y, e4.z * g4.z, e4.w * g4.w};
-            _Pragma("unroll") for (int j = 0; j < 4; ++j)
-                t1[4 * g + j] = (r0 + j < t) ? t1[4 * g + j] * bv[j] + t2[4 * g + j] * wv[j] : 0.f;
-        }
-        store_block_t_split(dTh, dTl, LDP, t, 32 * rb, half, t1);
-    } else {
-        _Pragma("unroll") for (int it = 0; it < 2; ++it) {   // rows t < 32, columns r >= 32
-            const int p = lane + 64 * it, row = p >> 2, piece = p & 3;
-            *reinterpret_cast<u32x4*>(dTh + row * LDP + 32 + 8 * piece) = u32x4{0, 0, 0, 0};
-            *reinterpret_cast<u32x4*>(dTl + row * LDP + 32 + 8 * piece) = u32x4{0, 0, 0, 0};
-        }
-    }
-    __syncthreads();  // first phase done: the tiles behind K are spent, dT is complete
-
-    // ---- M1[t][r] = sum_r' dT[t][r'] T[r][r'], blocks (r, t) = (0,0), (0,1), (1,1); kept as a tile [t][r]
-    if (wave < 3) {
-        const int mb = wave == 2 ? 1 : 0, nb = wave ? 1 : 0;
-        f32x16 m1 = {0};
-        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
-            if (ks >= 2 * (mb + 1)) break;  // r' <= r
-            const bf16x8 ah = frag_tr(TTh, LDP, 16 * ks, 32 * mb, lane), al = frag_tr(TTl, LDP, 16 * ks, 32 * mb, lane);  // T[r][r']
-            const bf16x8 bh_ = frag(dTh, LDP, 32 * nb + n, 16 * ks + 8 * half), bl = frag(dTl, LDP, 32 * nb + n, 16 * ks + 8 * half);
-            m1 = mfma(ah, bh_, m1);
-            m1 = mfma(ah, bl, m1);
-            m1 = mfma(al, bh_, m1);
-        }
-        store_block_t_split(M1h, M1l, LDP, 32 * nb + n, 32 * mb, half, m1);
-    } else {
-        _Pragma("unroll") for (int it = 0; it < 2; ++it) {   // rows t' < 32, columns r >= 32: never contribute
-            const int p = lane + 64 * it, row = p >> 2, piece = p & 3;
-            *reinterpret_cast<u32x4*>(M1h + row * LDP + 32 + 8 * piece) = u32x4{0, 0, 0, 0};
-            *reinterpret_cast<u32x4*>(M1l + row * LDP + 32 + 8 * piece) = u32x4{0, 0, 0, 0};
-            *reinterpret_cast<u32x4*>(dGh + row * LDP + 32 + 8 * piece) = u32x4{0, 0, 0, 0};
-            *reinterpret_cast<u32x4*>(dGl + row * LDP + 32 + 8 * piece) = u32x4{0, 0, 0, 0};
-        }
-    }
-    __syncthreads();
-    // ---- dL[t][r] = -sum_t' T[t'][t] M1[t'][r], then F, the row and column sums, and dG as a tile [t][r]
-    if (wave < 3) {
-        const int mb = wave == 2 ? 1 : 0, nb = wave ? 1 : 0;
-        f32x16 dl = {0};
-        _Pragma("unroll") for (int ks = 2 * nb; ks < 4; ++ks) {  // t' >= t
-            const bf16x8 ah = frag_tr(M1h, LDP, 16 * ks, 32 * mb, lane), al = frag_tr(M1l, LDP, 16 * ks, 32 * mb, lane);  // M1[t'][r]
-            const bf16x8 bh_ = frag(TTh, LDP, 32 * nb + n, 16 * ks + 8 * half), bl = frag(TTl, LDP, 32 * nb + n, 16 * ks + 8 * half);  // T[t'][t]
-            dl = mfma(ah, bh_, dl);
-            dl = mfma(ah, bl, dl);
-            dl = mfma(al, bh_, dl);
-        }
-        const f32x16 G = score_block2(K, 32 * mb, K, 32 * nb, n, half);  // D[m = r][n = t] = k_r . k_t
-        const int t = 32 * nb + n;
-        const float bt = be[t], lt = lg[t];
-        float rs = 0.f;
-        f32x16 dg;
-        float cs[16];
-        _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-            const int r0 = 32 * mb + 8 * g + 4 * half;
-            const float4 l4 = *reinterpret_cast<const float4*>(lg + r0);
-            const float lr[4] = {l4.x, l4.y, l4.z, l4.w};
-            _Pragma("unroll") for (int j = 0; j < 4; ++j) {
-                const float dec = DEC ? __expf(lt - lr[j]) : 1.f;
-                const float dlv = (r0 + j < t) ? -dl[4 * g + j] * dec : 0.f;   // dL_tr e^{lg_t - lg_r}
-                const float f = dlv * G[4 * g + j];
-                rs += f;
-                cs[4 * g + j] = bt * f;
-                dg[4 * g + j] = bt * dlv;
-            }
-        }
-        rs += __shfl_xor(rs, 32, 64);
-        if (half == 0) rowF[wave * 32 + n] = rs;
-        if (DEC) {  // column sums over the 32 tokens t of the block, for each r
-            _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-                float v_ = cs[x];
-                for (int off = 16; off > 0; off >>= 1) v_ += __shfl_xor(v_, off, 64);
-                cs[x] = v_;
-            }
-            if (n == 0) {
-                _Pragma("unroll") for (int x = 0; x < 16; ++x) colE[wave * 32 + 8 * (x >> 2) + 4 * half + (x & 3)] = cs[x];
-            }
-        }
-        store_block_t_split(dGh, dGl, LDP, t, 32 * mb, half, dg);
-    }
-    __syncthreads();
-    // ---- dk^T[i][t] = dk2[i][t] + sum_r K^T[i][r] (dG[t][r] + dG[r][t]) + the gradient walker's part
-    _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
-        f32x16 acc = dk2[nb];
-        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
-            const bf16x8 kt = frag_tr(K, LD, 16 * ks, 32 * wave, lane);
-            if (ks < 2 * (nb + 1)) {  // r < t
-                acc = mfma(kt, frag(dGh, LDP, 32 * nb + n, 16 * ks + 8 * half), acc);
-                acc = mfma(kt, frag(dGl, LDP, 32 * nb + n, 16 * ks + 8 * half), acc);
-            }
-            if (ks >= 2 * nb) {       // r > t
-                acc = mfma(kt, frag_tr(dGh, LDP, 16 * ks, 32 * nb, lane), acc);
-                acc = mfma(kt, frag_tr(dGl, LDP, 16 * ks, 32 * nb, lane), acc);
-            }
-        }
-        const int t = 32 * nb + n;
-        _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-            const u32x2 h = k1h[nb][g], l = k1l[nb][g];
-            acc[4 * g + 0] += bf16_lo(h.x) + bf16_lo(l.x);
-            acc[4 * g + 1] += bf16_hi(h.x) + bf16_hi(l.x);
-            acc[4 * g + 2] += bf16_lo(h.y) + bf16_lo(l.y);
-            acc[4 * g + 3] += bf16_hi(h.y) + bf16_hi(l.y);
-        }
-        store_packed(stk, LD, t, 32 * wave, half, pack_block(acc));
-        store_packed(stv, LD, t, 32 * wave, half, resv[nb]);
-    }
-    __syncthreads();
-    store_tile(a.dk, stk, cp.tok0, cp.ts, L, tid);
-    store_tile(a.dv, stv, cp.tok0, cp.ts, L, tid);
-    // ---- per-token parameters (wave 0, lane = token)
-    if (wave == 0) {
-        const int t = lane;
-        const float cb = (red_c[t] + red_c[C + t]) + (red_c[2 * C + t] + red_c[3 * C + t]);
-        const float db = (red_db[t] + red_db[C + t]) + (red_db[2 * C + t] + red_db[3 * C + t]);
-        // row sums of F: t < 32 from block 0; t >= 32 from blocks 1 and 2.  Column sums: r < 32 from blocks 0 and 1; r >= 32 from block 2.
-        const float rf = t < 32 ? rowF[t] : rowF[32 + (t - 32)] + rowF[64 + (t - 32)];
-        if (a.d_bw && t < L) a.d_bw[ptok] = db;
-        if (a.d_beta && t < L) a.d_beta[ptok] = gm[t] * cb + rf;
-        if (DEC) {
-            const float ce = t < 32 ? colE[t] + colE[32 + t] : colE[64 + (t - 32)];
-            float dlg = be[t] * gm[t] * cb + be[t] * rf - ce;
-            if (t >= L) dlg = 0.f;
-            float sfx = dlg;  // suffix sum over tokens >= t
-            for (int off = 1; off < 64; off <<= 1) {
-                const float y = __shfl_down(sfx, off, 64);
-                if (t + off < 64) sfx += y;
-            }
-            if (t < L) a.d_log_alpha[ptok] += sfx;
-        }
-    }
-    __syncthreads();  // the stages and the reductions are read; the next chunk may overwrite them
-  }
 }

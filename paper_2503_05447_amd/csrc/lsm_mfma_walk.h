@@ -28,7 +28,6 @@ struct WalkArgs {
     float* gseg;           // [slot]: total log-decay of each segment (SUMMARY writes)
     int m, nseg;           // chunks per segment, segments per sequence (upper bound for packed input)
     int skip;              // SUMMARY, REV: segments [0, skip) feed no other walk and are left out (at least 1)
-    const uint16_t* xv_lo; // VSPLIT (summary pass only): remainder plane of the value-role rows
 };
 
 // tile rows in walk order: row r holds token r (forward) or token L-1-r (backward); rows >= L are zero.
@@ -304,7 +303,7 @@ __device__ __forceinline__ void walk_state_store(const f32x16 (&S)[4], float* e,
 __device__ __forceinline__ size_t edge_off(const Dims& d, int seq) { return (size_t(seq) * D * d.vm + d.vs) * D; }
 // REV: walk backward in time.  DEC: a decay is present.  SUMMARY: the state update alone, from a zero
 // state, result to a.bound / a.gseg.
-template <bool REV, bool DEC, bool SUMMARY, bool VSPLIT = false>
+template <bool REV, bool DEC, bool SUMMARY>
 __device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, const SeqWalk& walk, int seg, unsigned char* smem) {
     // LDS: SUMMARY: K | V | bs | wo;   else: Q | K | V | P head | P remainder | bs | wo
     uint16_t* Q = reinterpret_cast<uint16_t*>(smem);
@@ -315,8 +314,6 @@ __device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, cons
     float* bs = reinterpret_cast<float*>(SUMMARY ? V + C * LD : Pl + C * LDP);  // beta[64], then b_C
     float* wo = bs + C + 4;                                                      // e^{b_C - beta}[64]
     uint16_t* stage = Q;
-    uint16_t* V2 = reinterpret_cast<uint16_t*>(smem + walk_lds(SUMMARY));  // VSPLIT only
-    static_assert(!VSPLIT || SUMMARY, "two value planes: summary pass only");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 31, half = lane >> 5;
     const int nsq = (walk.n + a.m - 1) / a.m;  // segments of this sequence
@@ -337,7 +334,7 @@ __device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, cons
         else if (a.edge_in) walk_state_load(S, a.edge_in + edge_off(d, walk.edge), false, wave, n, half, D * d.vm);
     }
 
-    TileRegs rq, rk, rv, rv2;
+    TileRegs rq, rk, rv;
     float gval = 0.f, gtot = 0.f;
     // The summary pass visits the chunks of its segment in the order opposite to the walk (a sum: each
     // chunk's weights carry the decay of the chunks that follow it in walk order), so that the walker,
@@ -352,7 +349,6 @@ __device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, cons
         if (!SUMMARY) walk_gload<REV, kThreads>(rq, a.xq, p.tok0, p.ts, p.L, tid);
         walk_gload<REV, kThreads>(rk, a.xk, p.tok0, p.ts, p.L, tid);
         walk_gload<REV, kThreads>(rv, a.xv, p.vtok0, p.vts, p.L, tid);
-        if (VSPLIT) walk_gload<REV, kThreads>(rv2, a.xv_lo, p.vtok0, p.vts, p.L, tid);
     };
     if (cnt > 0) gload(0);
 
@@ -363,7 +359,6 @@ __device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, cons
         if (!SUMMARY) walk_commit<kThreads>(Q, rq, L, tid);
         walk_commit<kThreads>(K, rk, L, tid);
         walk_commit<kThreads>(V, rv, L, tid);
-        if (VSPLIT) walk_commit<kThreads>(V2, rv2, L, tid);
         if (DEC && wave == 0) gtot += walk_decay_tables<REV>(gval, L, SUMMARY ? gtot : 0.f, bs, wo, lane);
         gload(kk + 1);
         __syncthreads();  // (A) tiles and decay tables of this chunk are in LDS
@@ -379,8 +374,7 @@ __device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, cons
                 store_packed(stage, LD, 32 * jb + n, 32 * wave, half, pack_block(O[jb]));
             }
         }
-        if (VSPLIT) walk_update_vsplit<DEC, !SUMMARY>(S, K, V, V2, wo, bC, wave, lane, half);
-        else walk_update<DEC, !SUMMARY>(S, K, V, wo, bC, wave, lane, half);
+        walk_update<DEC, !SUMMARY>(S, K, V, wo, bC, wave, lane, half);
         __syncthreads();  // (D) the output stage is complete and every read of this chunk's tiles is done
         // every thread reads back exactly the stage pieces that its own next walk_commit overwrites: no barrier
         if (!SUMMARY) walk_store<REV>(a.out, stage, cp.vtok0, cp.vts, L, tid);
@@ -397,12 +391,12 @@ __device__ __forceinline__ void walk_body(const Dims& d, const WalkArgs& a, cons
 }
 
 // forward walker, or the summary pass of either direction (grid: segments x sequences; packed input: seg_index)
-template <bool REV, bool DEC, bool SUMMARY, bool VSPLIT = false>
+template <bool REV, bool DEC, bool SUMMARY>
 __global__ __launch_bounds__(kThreads, 2) void mk_walk(Dims d, WalkArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const SegIndex i = seg_index(d, a.m, blockIdx.x, blockIdx.y);
     if (i.seg < 0) return;
-    walk_body<REV, DEC, SUMMARY, VSPLIT>(d, a, i.walk, i.seg, smem);
+    walk_body<REV, DEC, SUMMARY>(d, a, i.walk, i.seg, smem);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -433,11 +427,11 @@ struct GradArgs {
     const float* edge_in;     // M_0 [i][v] per sequence or NULL
     const float* bound;       // entry states of the segments but the first ([i][v]) when nseg > 1
     int m, nseg;
-    const uint16_t* v_lo;     // VSPLIT: remainder plane of the values (same layout as v)
-    // VSPLIT: dU (head, remainder; [BH*T][128] in the library's own order) and the product dW = -dU S^T of every chunk with
-    // the state it starts from (head, remainder, same order)
-    const uint16_t *du_h, *du_l;
-    uint16_t *dw_h, *dw_l;
+    // VSPLIT: remainder plane of the values (same layout as v); W, the gradient of the delta rule's right-hand side, head and
+    // remainder ([BH*T][128] in the library's own order); erase strength per token (NULL = 1) and its gradient (may be NULL)
+    const uint16_t *v_lo, *w_h, *w_l;
+    const float* beta;
+    float* d_beta;
     // the entry states may be kept at a finer grain than this walk's segments: bound is numbered for bound_n segments per sequence,
     // one per m / bound_per chunks, and segment s enters with slot s * bound_per (0: same grain, nseg slots)
     int bound_per, bound_n;
@@ -446,12 +440,18 @@ struct GradArgs {
     // the second adds them to its own before the one rounding
     uint16_t* part[4];
 };
-// VSPLIT (the delta-rule backward, whose values are the pseudo-values U = head + remainder): the values enter
-// every product with both planes; the value gradient is not formed (it is the caller's dU once more) and its
-// output receives the remainder of the key gradient instead (dk = head, dv = remainder).  The area of the dS rows
-// holds the two planes of dU instead, and the walker also leaves dW = -dU S^T (the gradient of the delta rule's
-// What), staged through the d_o tile and the second value tile.
-__host__ __device__ constexpr int walk_grad_lds(bool vsplit) { return kWalkGradLds + (vsplit ? C * LD * 2 : 0); }
+// VSPLIT (the delta-rule backward, whose values are the pseudo-values U = head + remainder): the values enter every product with
+// both planes, the value gradient is not formed (the reverse walk leaves it), and the erase term adds a second set of scores
+// and a second query-side gradient (the formulas stand before mk_delta_rwalk):
+//   H_tr = -D_tr (W_t . u_r) , r < t ,   X_t = -e^{b_t} S W_t + sum_r H_tr k_r ,   d beta_t = k_t . X_t ,
+//   dk_t += beta_t X_t + sum_{j > t} beta_j H_jt k_j ,   dg as for a second query with gradient beta_t X_t.
+// The area of As holds beta H; that of the dS rows the two planes of W, then beta X (fp32), which the group that has the rest
+// of dk adds before the one rounding.  d beta takes the score part as row sums of H * (K K^T), unscaled (beta may be 0).
+// A segment is one of the reverse walk's, entry states from the forward walk's chain of segments.
+constexpr int LDX = D + 4;  // floats per row of the stage of beta X
+constexpr int kWalkGradSplitExtra = C * LD * 2 + (C + 3 * 32 + 4 * C) * 4;  // second value tile | beta | row sums | k . X per wave
+__host__ __device__ constexpr int walk_grad_lds(bool vsplit) { return kWalkGradLds + (vsplit ? kWalkGradSplitExtra : 0); }
+static_assert(walk_grad_lds(true) <= 160 * 1024 && C * LDX * 4 <= 2 * C * LD * 2, "LDS; the stage of beta X fits the planes of W");
 
 // inter product of the state with rows kept in two planes (head Qh, remainder Ql), the state blocks converted once:
 // O^T[i][t] = sum_v S[i][v] (Qh + Ql)[t][v], remainder x remainder left out
@@ -482,17 +482,17 @@ __device__ __forceinline__ void walk_inter_split(f32x16 (&O)[2], const f32x16 (&
 // Gradient walker kernel: eight waves, two per SIMD.  The work of a chunk is split by function, not by data, so that
 // neither group needs the other's registers:
 //   waves 0..3 (wave w: key features i in [32w, 32w+32)) carry the state; they form dq (inter part from the state, intra
-//              part from G), <S, dS>, with VSPLIT dW, and move the state on;
+//              part from G), <S, dS>, with VSPLIT X, and move the state on;
 //   waves 4..7 (wave w: the same i slice for dk, value features v in [32w, 32w+32) for dv) hold the dS rows of the chunk;
 //              they compute the score blocks (G, As), dk and dv.
 // Each group runs a loop of its own with the same four barriers per chunk, so a SIMD always has one wave of either
 // kind to issue from: the matrix, vector and LDS work of the two overlap instead of queueing behind one wave's waits.
 // Plain case: all 512 threads share the tile traffic (global -> registers -> LDS, stage -> global), and the carrier
 // waves read dS for <S, dS> at the (i, v) of their state registers from the LDS rows.
-// VSPLIT: the carrier waves' registers are full (state, dq, dW), so the other group moves most of the tiles; the carrier
-// waves form <S, dS> (dS by loads of their own from the fragment-major array, which the other group has just pulled
-// into L2: the LDS area of the dS rows holds dU) and dW before barrier (2), and dq and the state update after it, so
-// that the accumulators of dW and dq never coexist.
+// VSPLIT: the carrier waves' registers are full (state, dq, X), so the other group moves most of the tiles; the carrier
+// waves form the state part of X before barrier (2), then complete and park it, then dq, the state update and <S, dS> (dS by
+// loads of their own from the fragment-major array, which the other group has just pulled into L2: the LDS area of the
+// dS rows holds W), so that the accumulators of X and dq never coexist.
 constexpr int kGrad8Threads = 512;
 
 // WIDE: 0 the only pass; 1 the first of two value-slice passes (dq, dk to the partial planes); 2 the second
@@ -514,16 +514,18 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
     float* red = wo + C + 4;         // [i slice][2][64]: q.dq, k.dk partial sums over the slice
     float* zred = red + 4 * 2 * 64;  // [i slice]: partial <S, dS>
     uint16_t* V2 = reinterpret_cast<uint16_t*>(smem + kWalkGradLds);  // VSPLIT only
-    uint16_t* dUh = dSt;             // VSPLIT: 64 x LD each, over the dS rows
-    uint16_t* dUl = dSt + C * LD;
-    uint16_t* Wl = Ah;               // VSPLIT (no As): stage of the remainder plane of dW, 64 x LD
+    uint16_t* Wh = dSt;              // VSPLIT: 64 x LD each, over the dS rows
+    uint16_t* Wl = dSt + C * LD;
+    float* Xs = reinterpret_cast<float*>(dSt);                          // ... and, once they are spent, beta X [64][LDX]
+    float* be = reinterpret_cast<float*>(smem + kWalkGradLds + C * LD * 2);  // VSPLIT: beta [64]
+    float* rowF = be + C;            // [block][32]: sum_r H_tr (k_t . k_r) over the block's keys
+    float* redx = rowF + 3 * 32;     // [i slice][64]: k . X without the scores' share
     uint16_t* Lq = Gh;               // WIDE == 1: stages of the remainder planes of dq and dk (G and As are spent after (3))
     uint16_t* Lk = Ah;
     static_assert(2 * C * LDP >= C * LD, "a 64 x LD stage fits the area of G");
-    static_assert(2 * C * LDP >= C * LD, "the dW stage fits the area of As");
     constexpr int NT = VSPLIT ? 256 : kGrad8Threads;  // threads that share the tile traffic
 
-    const SegIndex si = seg_index(d, a.m, blockIdx.x, blockIdx.y);
+    const SegIndex si = VSPLIT ? SegIndex{seq_walk(d, blockIdx.y), int(blockIdx.x)} : seg_index(d, a.m, blockIdx.x, blockIdx.y);
     if (si.seg < 0) return;
     const SeqWalk walk = si.walk;
     const int seq = walk.edge, seg = si.seg;
@@ -548,10 +550,10 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
     const int kbeg = seg * a.m, kend = min(walk.n, kbeg + a.m), cnt = kend - kbeg;
     if (cnt <= 0) return;
 
-    // VSPLIT: the carrier group moves the head plane of dU in, and d_o when it has no decay tables to keep (measured:
-    // with them it is the slower group already); the other group moves the other tiles in and all but the head of dW out
+    // VSPLIT: the carrier group moves the head plane of W in, and d_o when it has no decay tables to keep (measured:
+    // with them it is the slower group already); the other group moves the other tiles in and the gradients out
     constexpr bool kCarrierMovesDo = !DEC;
-    TileRegs tq, tk, tv, to, tv2, tdh, tdl;
+    TileRegs tq, tk, tv, to, tv2, twh, twl;
     auto gload_tiles = [&](const ChunkPos& p, bool first_group) {
         if (!VSPLIT || !first_group) {
             walk_gload<false, NT>(tq, a.q, p.tok0, p.ts, p.L, tt);
@@ -559,10 +561,10 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             walk_gload<false, NT>(tv, a.v, p.vtok0, p.vts, p.L, tt);
         }
         if (!VSPLIT || first_group == kCarrierMovesDo) walk_gload<false, NT>(to, a.d_o, p.vtok0, p.vts, p.L, tt);
-        if (VSPLIT && first_group) walk_gload<false, NT>(tdh, a.du_h, p.wtok0, 1, p.L, tt);
+        if (VSPLIT && first_group) walk_gload<false, NT>(twh, a.w_h, p.wtok0, 1, p.L, tt);
         if (VSPLIT && !first_group) {
             walk_gload<false, NT>(tv2, a.v_lo, p.vtok0, p.vts, p.L, tt);
-            walk_gload<false, NT>(tdl, a.du_l, p.wtok0, 1, p.L, tt);
+            walk_gload<false, NT>(twl, a.w_l, p.wtok0, 1, p.L, tt);
         }
     };
     auto commit_tiles = [&](int L, bool first_group) {
@@ -572,16 +574,15 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             walk_commit<NT>(V, tv, L, tt);
         }
         if (!VSPLIT || first_group == kCarrierMovesDo) walk_commit<NT>(dO, to, L, tt);
-        if (VSPLIT && first_group) walk_commit<NT>(dUh, tdh, L, tt);
+        if (VSPLIT && first_group) walk_commit<NT>(Wh, twh, L, tt);
         if (VSPLIT && !first_group) {
             walk_commit<NT>(V2, tv2, L, tt);
-            walk_commit<NT>(dUl, tdl, L, tt);
+            walk_commit<NT>(Wl, twl, L, tt);
         }
     };
     auto store_tiles = [&](const ChunkPos& cp, bool first_group) {
         // Every thread reads back exactly the stage pieces that its own next commit overwrites: no barrier between this and
-        // the next chunk's commit.  (VSPLIT: the head of dW is staged over the plane of dU that the carrier group commits,
-        // so that group stores it; the stage of the remainder is next written after barrier (1).)
+        // the next chunk's commit.
         if (!VSPLIT || !first_group) {
             if (WIDE == 1) {  // head and remainder of this pass's dq and dk, for the second pass
                 walk_store<false, NT>(a.part[0], Q, cp.wtok0, 1, cp.L, tt);
@@ -592,10 +593,8 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
                 walk_store<false, NT>(a.dq, Q, cp.tok0, cp.ts, cp.L, tt);
                 walk_store<false, NT>(a.dk, K, cp.tok0, cp.ts, cp.L, tt);
             }
-            walk_store<false, NT>(a.dv, V, cp.vtok0, cp.vts, cp.L, tt);
+            if (!VSPLIT) walk_store<false, NT>(a.dv, V, cp.vtok0, cp.vts, cp.L, tt);
         }
-        if (VSPLIT && first_group) walk_store<false, NT>(a.dw_h, dUh, cp.wtok0, 1, cp.L, tt);
-        if (VSPLIT && !first_group) walk_store<false, NT>(a.dw_l, Wl, cp.wtok0, 1, cp.L, tt);
     };
     // WIDE == 2: the first pass's share of a gradient block (lane = token 32 nb + n, registers = this wave's 32 features)
     struct Part { u32x2 h[4], l[4]; };
@@ -632,13 +631,15 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
         _Pragma("unroll") for (int vb = 0; vb < 4; ++vb) S[vb] = f32x16{0};
         {
             const int per = a.bound_per ? a.bound_per : 1;
-            if (seg > 0)
+            if (VSPLIT && a.nseg > 1) walk_state_load(S, a.bound + (size_t(seq) * a.nseg + seg) * D * D, true, wave, n, half);
+            else if (!VSPLIT && seg > 0)
                 walk_state_load(S, a.bound + (bound_slot(d, walk, a.m / per, a.bound_per ? a.bound_n : a.nseg) + seg * per) * D * D, true, wave, n, half);
             else if (a.edge_in) walk_state_load(S, a.edge_in + edge_off(d, seq), true, wave, n, half, D * d.vm);
         }
-        float gval = 0.f;
+        float gval = 0.f, bval = 1.f;
         auto gload = [&](int kk) {
             const ChunkPos p = walk_pos(d, walk, kbeg + min(kk, cnt - 1));
+            if (VSPLIT && a.beta) bval = a.beta[p.tok0 + size_t(min(lane, p.L - 1)) * p.ts];
             if (DEC) gval = a.g[d.kind == 1 ? size_t(walk.bh % d.H) : p.tok0 + size_t(min(lane, p.L - 1)) * p.ts];
             gload_tiles(p, true);
         };
@@ -659,7 +660,7 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
                 if (WANT_DG) {
                     float pq = row_dot(Q, tok, wave, half, aq[nb]);
                     pq += __shfl_xor(pq, 32, 64);
-                    if (half == 0) red[(wave * 2 + 0) * 64 + tok] = pq;
+                    if (half == 0) red[(wave * 2 + 0) * 64 + tok] = VSPLIT ? pq + red[(wave * 2 + 0) * 64 + tok] : pq;
                 }
                 if (WIDE == 2) part_add(aq[nb], pt[nb]);  // after the decay gradient took this pass's own share
                 if (WIDE == 1) {
@@ -692,19 +693,23 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             fresh();
             commit_tiles(L, true);
             if (DEC && wave8 == 0) walk_decay_tables<false>(gval, L, 0.f, bs, wo, lane);
+            if (VSPLIT && wave8 == 0) be[lane] = lane < L ? bval : 0.f;
             __syncthreads();  // (1) tiles, dS rows and decay tables of this chunk are in LDS
             fresh();
             const float bC = DEC ? bs[C] : 0.f;
             f32x16 aq[2];
-            PackedBlock resw[2], resq[2], resql[2];
+            PackedBlock resq[2], resql[2];
             if (VSPLIT) {
-                // dW^T[i][t] = -sum_v S[i][v] dU[t][v]; the remainder plane is staged at once (nobody else uses its area)
-                f32x16 dw[2];
-                walk_inter_split(dw, S, dUh, dUl, n, half);
+                // X^T[i][t], the state's share: -e^{b_t} sum_v S[i][v] W[t][v]
+                walk_inter_split(aq, S, Wh, Wl, n, half);
                 _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
-                    _Pragma("unroll") for (int x = 0; x < 16; ++x) dw[nb][x] = -dw[nb][x];
-                    resw[nb] = split_block(dw[nb]);
-                    store_packed(Wl, LD, 32 * nb + n, 32 * wave, half, pack_block(dw[nb]));
+                    const int tok = 32 * nb + n;
+                    const float w = DEC ? -__expf(bs[tok]) : -1.f, b = be[tok];
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) aq[nb][x] *= w;
+                    float px = row_dot(K, tok, wave, half, aq[nb]);
+                    px += __shfl_xor(px, 32, 64);
+                    if (half == 0) redx[wave * 64 + tok] = px;
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) aq[nb][x] *= b;
                 }
             } else {
                 walk_inter<DEC>(aq, S, dO, bs, n, half);
@@ -719,8 +724,23 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             __syncthreads();  // (2) G and As are in LDS
             fresh();
             if (VSPLIT) {
-                // the planes of dU are dead: the head of dW is staged over the first
-                _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) store_packed(dUh, LD, 32 * nb + n, 32 * wave, half, resw[nb]);
+                // beta X is complete with beta H, and parked over the planes of W, which are spent
+                _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
+                    const int tok = 32 * nb + n;
+                    _Pragma("unroll") for (int ks = 0; ks < 2 * (nb + 1); ++ks) {
+                        const bf16x8 kt = frag_tr(K, LD, 16 * ks, 32 * wave, lane);
+                        aq[nb] = mfma(kt, frag(Ah, LDP, tok, 16 * ks + 8 * half), aq[nb]);
+                        aq[nb] = mfma(kt, frag(Al, LDP, tok, 16 * ks + 8 * half), aq[nb]);
+                    }
+                    if (WANT_DG) {
+                        float px = row_dot(K, tok, wave, half, aq[nb]);
+                        px += __shfl_xor(px, 32, 64);
+                        if (half == 0) red[(wave * 2 + 0) * 64 + tok] = px;
+                    }
+                    _Pragma("unroll") for (int g = 0; g < 4; ++g)
+                        *reinterpret_cast<float4*>(Xs + tok * LDX + 32 * wave + 8 * g + 4 * half) =
+                            float4{aq[nb][4 * g], aq[nb][4 * g + 1], aq[nb][4 * g + 2], aq[nb][4 * g + 3]};
+                }
                 walk_inter<DEC>(aq, S, dO, bs, n, half);
                 dq_intra(aq, resq, resql, cp);
                 fresh();
@@ -745,6 +765,11 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             __syncthreads();  // (4)
             fresh();
             store_tiles(cp, true);
+            if (VSPLIT && a.d_beta && wave8 == 1 && lane < L) {
+                const float x = (redx[lane] + redx[64 + lane]) + (redx[128 + lane] + redx[192 + lane]);
+                // row sums: t < 32 from block (0,0); t >= 32 from blocks (1,0) and (1,1)
+                a.d_beta[cp.tok0 + size_t(lane) * cp.ts] = x + (lane < 32 ? rowF[lane] : rowF[lane] + rowF[32 + lane]);
+            }
             if (WANT_DG && wave8 == 0) {
                 // fixed-order sums over the four feature slices, then the reverse in-chunk running sum
                 float w = 0.f;
@@ -786,6 +811,25 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             walk_mask<DEC>(P, 32 * prb, 32 * pjb + n, bs, half);
             store_block_t_split(isG ? Gh : Ah, isG ? Gl : Al, LDP, 32 * pjb + n, 32 * prb, half, P);
         };
+        // VSPLIT: a block of H, with its row sums against K K^T; what is kept is beta H
+        auto erase_score = [&](int bi) {
+            const int pjb = bi ? 1 : 0, prb = bi == 2 ? 1 : 0, t = 32 * pjb + n;
+            f32x16 P = score_block2(V, 32 * prb, Wh, 32 * pjb, n, half);  // D[m = r][n = t] = u_r . W_t
+            P = score_block2(V2, 32 * prb, Wh, 32 * pjb, n, half, P);
+            P = score_block2(V, 32 * prb, Wl, 32 * pjb, n, half, P);
+            walk_mask<DEC>(P, 32 * prb, t, bs, half);
+            const f32x16 G = score_block2(K, 32 * prb, K, 32 * pjb, n, half);
+            const float b = be[t];
+            float rs = 0.f;
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                P[x] = 32 * prb + 8 * (x >> 2) + 4 * half + (x & 3) == t ? 0.f : -P[x];  // a key does not erase itself
+                rs += P[x] * G[x];
+                P[x] *= b;
+            }
+            rs += __shfl_xor(rs, 32, 64);
+            if (half == 0) rowF[32 * bi + n] = rs;
+            store_block_t_split(Ah, Al, LDP, t, 32 * prb, half, P);
+        };
         gload(0);
         for (int kk = 0; kk < cnt; ++kk) {
             const ChunkPos cp = walk_pos(d, walk, kbeg + kk);
@@ -801,7 +845,11 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             fresh();
             // G = (dO V^T) * D first (the other group waits for it at (2)), then As = (Q K^T) * D, which only dv needs
             if (VSPLIT) {
-                if (wave < 3) score(true, wave);
+                if (wave < 3) {
+                    erase_score(wave);
+                } else {
+                    _Pragma("unroll 1") for (int bi = 0; bi < 3; ++bi) score(true, bi);
+                }
             } else {
                 if (wave < 3) score(true, wave);
                 else score(false, 0);
@@ -849,16 +897,18 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
                     const bf16x8 qt = frag_tr(Q, LD, 16 * ks, 32 * wave, lane);
                     ak[nb] = mfma(qt, frag_tr(Gh, LDP, 16 * ks, 32 * nb, lane), ak[nb]);  // B[k = j][n = r] = G[j][r]
                     ak[nb] = mfma(qt, frag_tr(Gl, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
+                    if (VSPLIT) {  // the same with beta H and the keys in the query's place
+                        const bf16x8 kt = frag_tr(K, LD, 16 * ks, 32 * wave, lane);
+                        ak[nb] = mfma(kt, frag_tr(Ah, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
+                        ak[nb] = mfma(kt, frag_tr(Al, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
+                    }
                 }
                 if (WANT_DG) {
                     float pk = row_dot(K, tok, wave, half, ak[nb]);
                     pk += __shfl_xor(pk, 32, 64);
                     if (half == 0) red[(wave * 2 + 1) * 64 + tok] = pk;
                 }
-                if (VSPLIT) {  // the key gradient leaves as head + remainder (the caller adds to it before rounding)
-                    resk[nb] = split_block(ak[nb]);
-                    resv[nb] = pack_block(ak[nb]);
-                } else {
+                if (!VSPLIT) {
                     if (WIDE == 2) part_add(ak[nb], pt[nb]);
                     if (WIDE == 1) {
                         resk[nb] = split_block(ak[nb]);
@@ -878,8 +928,18 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             __syncthreads();  // (3)
             fresh();
             _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
+                if (VSPLIT) {  // the other group's beta X, before the one rounding
+                    _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                        const float4 x = *reinterpret_cast<const float4*>(Xs + (32 * nb + n) * LDX + 32 * wave + 8 * g + 4 * half);
+                        ak[nb][4 * g] += x.x;
+                        ak[nb][4 * g + 1] += x.y;
+                        ak[nb][4 * g + 2] += x.z;
+                        ak[nb][4 * g + 3] += x.w;
+                    }
+                    resk[nb] = pack_block(ak[nb]);
+                }
                 store_packed(K, LD, 32 * nb + n, 32 * wave, half, resk[nb]);
-                store_packed(V, LD, 32 * nb + n, 32 * wave, half, resv[nb]);
+                if (!VSPLIT) store_packed(V, LD, 32 * nb + n, 32 * wave, half, resv[nb]);
                 if (WIDE == 1) store_packed(Lk, LD, 32 * nb + n, 32 * wave, half, reskl[nb]);
             }
             __syncthreads();  // (4)

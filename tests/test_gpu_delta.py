@@ -142,10 +142,12 @@ def run_bwd_and_check(x, layout=0):
 # (B, H, T): one chunk; a ragged chunk; several chunks; eleven chunks (every chunk a segment of the gradient walker);
 # 40 sequences of 24 chunks (segments of two chunks)
 BWD_SHAPES = [(1, 2, 64), (2, 2, 37), (2, 3, 200), (1, 3, 700), (5, 8, 1500)]
+# every sequence one segment (from 192 sequences on): whole chunks, a ragged tail of one token, one ragged chunk
+WHOLE_SHAPES = [(6, 32, 128), (8, 25, 129), (6, 32, 50)]
 
 
 @pytest.mark.parametrize("gated", [False, True])
-@pytest.mark.parametrize("shape", BWD_SHAPES)
+@pytest.mark.parametrize("shape", BWD_SHAPES + WHOLE_SHAPES)
 def test_delta_backward_matches_oracle(shape, gated):
     B, H, T = shape
     x = wl.make_delta_inputs(B, H, T, 128, 128, gated, seed=5100 + T + int(gated), init_state=True, d_final=True)
