@@ -1120,6 +1120,7 @@ size_t delta_seg_bytes(const Dims& d) {
     const SegPlan sp = delta_plan(d);
     return sp.nseg > 1 ? 3 * align256(size_t(d.seqs()) * sp.nseg * D * D * 4) : 0;
 }
+size_t delta_t_bytes(const Dims& d) { return align256(size_t(d.BH()) * d.N * kDeltaT * 2); }
 const float* delta_entries(const Dims& d, const void* segws) {
     return reinterpret_cast<const float*>(static_cast<const char*>(segws) + delta_seg_bytes(d) / 3 * 2);
 }
@@ -1128,7 +1129,7 @@ const float* delta_entries(const Dims& d, const void* segws) {
 // carves it, and the backward call does not run the prep and the walk again.
 size_t delta_fwd_workspace(const Dims& d) {
     if (d.save) return carve_delta_bytes(d);
-    return align256(size_t(d.BH()) * d.T * D * 2) + align256(size_t(d.BH()) * d.T * D * 4) + delta_seg_bytes(d);
+    return delta_t_bytes(d) + delta_seg_bytes(d);
 }
 namespace {
 hipError_t launch_delta_fwd(const Dims& d, const DeltaPrepArgs& pa, DeltaWalkArgs wa, void* segws, hipStream_t stream);
@@ -1136,13 +1137,11 @@ hipError_t launch_delta_fwd(const Dims& d, const DeltaPrepArgs& pa, DeltaWalkArg
 hipError_t delta_fwd_saving(const Dims& d, const DeltaArgs& a);
 hipError_t delta_fwd(const Dims& d, const DeltaArgs& a) {
     if (d.save) return delta_fwd_saving(d, a);
-    char* p = static_cast<char*>(a.ws);
-    uint16_t* what = reinterpret_cast<uint16_t*>(p);
-    float* uhat = reinterpret_cast<float*>(p + align256(size_t(d.BH()) * d.T * D * 2));
+    uint16_t* tt = static_cast<uint16_t*>(a.ws);
     auto q = static_cast<const uint16_t*>(a.q), k = static_cast<const uint16_t*>(a.k), v = static_cast<const uint16_t*>(a.v);
-    const DeltaPrepArgs pa{k, v, a.log_alpha, a.beta, a.bw, what, uhat, nullptr};
-    const DeltaWalkArgs wa{q, k, what, uhat, a.log_alpha, static_cast<uint16_t*>(a.o), a.m0, a.mT, nullptr, nullptr};
-    return launch_delta_fwd(d, pa, wa, p + align256(size_t(d.BH()) * d.T * D * 2) + align256(size_t(d.BH()) * d.T * D * 4), a.stream);
+    const DeltaPrepArgs pa{k, a.log_alpha, a.beta, tt};
+    const DeltaWalkArgs wa{q, k, v, tt, a.log_alpha, a.beta, a.bw, static_cast<uint16_t*>(a.o), a.m0, a.mT, nullptr, nullptr};
+    return launch_delta_fwd(d, pa, wa, static_cast<char*>(a.ws) + delta_t_bytes(d), a.stream);
 }
 namespace {
 template <bool DEC>
@@ -1226,8 +1225,7 @@ hipError_t launch_delta_rwalk(const Dims& d, DeltaRevArgs ra, const void* segf, 
 }
 
 struct DeltaWs {
-    uint16_t *what, *tt, *usave, *usave_l, *dstates, *w_h, *w_l;
-    float* uhat;
+    uint16_t *tt, *usave, *usave_l, *dstates, *w_h, *w_l;
     void* seg;    // segment summaries and entry states of the delta walker
     void* seg_r;  // the same for the reverse walker, without factors of its own
     size_t bytes;
@@ -1238,9 +1236,7 @@ DeltaWs carve_delta(const Dims& d, void* ws) {
     auto take = [&](size_t bytes) { char* r = p + off; off += align256(bytes); return r; };
     const size_t rows = size_t(d.BH()) * d.T;
     DeltaWs w{};
-    w.what = reinterpret_cast<uint16_t*>(take(rows * D * 2));
-    w.uhat = reinterpret_cast<float*>(take(rows * D * 4));
-    w.tt = reinterpret_cast<uint16_t*>(take(size_t(d.BH()) * d.N * 2 * C * C * 2));
+    w.tt = reinterpret_cast<uint16_t*>(take(delta_t_bytes(d)));
     w.usave = reinterpret_cast<uint16_t*>(take(rows * D * 2));
     w.usave_l = reinterpret_cast<uint16_t*>(take(rows * D * 2));
     w.dstates = reinterpret_cast<uint16_t*>(take(size_t(d.BH()) * d.N * D * D * 2));
@@ -1260,8 +1256,8 @@ size_t delta_bwd_workspace(const Dims& d) { return carve_delta(d, nullptr).bytes
 hipError_t delta_fwd_saving(const Dims& d, const DeltaArgs& a) {
     const DeltaWs w = carve_delta(d, a.ws);
     auto q = static_cast<const uint16_t*>(a.q), k = static_cast<const uint16_t*>(a.k), v = static_cast<const uint16_t*>(a.v);
-    const DeltaPrepArgs pa{k, v, a.log_alpha, a.beta, a.bw, w.what, w.uhat, w.tt};
-    const DeltaWalkArgs wa{q, k, w.what, w.uhat, a.log_alpha, static_cast<uint16_t*>(a.o), a.m0, a.mT, w.usave, w.usave_l};
+    const DeltaPrepArgs pa{k, a.log_alpha, a.beta, w.tt};
+    const DeltaWalkArgs wa{q, k, v, w.tt, a.log_alpha, a.beta, a.bw, static_cast<uint16_t*>(a.o), a.m0, a.mT, w.usave, w.usave_l};
     return launch_delta_fwd(d, pa, wa, w.seg, a.stream);
 }
 
@@ -1273,8 +1269,8 @@ hipError_t delta_bwd(const Dims& d, const DeltaBwdArgs& a) {
     hipError_t e;
     // forward again: T, the pseudo-values U in the layout of v, the segments' factors and entry states
     if (!d.save) {
-        const DeltaPrepArgs pa{k, v, a.log_alpha, a.beta, a.bw, w.what, w.uhat, w.tt};
-        const DeltaWalkArgs wa{q, k, w.what, w.uhat, a.log_alpha, nullptr, a.m0, nullptr, w.usave, w.usave_l};
+        const DeltaPrepArgs pa{k, a.log_alpha, a.beta, w.tt};
+        const DeltaWalkArgs wa{q, k, v, w.tt, a.log_alpha, a.beta, a.bw, nullptr, a.m0, nullptr, w.usave, w.usave_l};
         if ((e = launch_delta_fwd(d, pa, wa, w.seg, a.stream)) != hipSuccess) return e;
     }
     // backward in time: state gradients, W, dv and db

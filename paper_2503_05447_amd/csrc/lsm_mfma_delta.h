@@ -1,4 +1,4 @@
-// Delta-rule rows of the paper's Table 1 (DeltaNet, Gated DeltaNet), forward, chunkwise: bf16 operands, fp32
+// Delta-rule rows of the paper's Table 1 (DeltaNet, Gated DeltaNet), chunkwise: bf16 operands, fp32
 // accumulation, chunk = 64, d_k = d_v = 128.  Included by lsm_mfma.hip after lsm_mfma_walk.h.
 //
 // Both rows are  M_t = alpha_t (I - beta_t k_t^T k_t) M_{t-1} + b_t k_t^T v_t ,  o_t = q_t M_t  (DeltaNet:
@@ -7,17 +7,19 @@
 // the update reads M_t = alpha_t M_{t-1} + k_t^T u_t: the per-token scalar-decay recurrence of Eq. 5 with u in
 // the place of v, which the chunk walker already evaluates.  Inside a chunk that starts from the state S, with
 // Gamma_t = prod_{s <= t} alpha_s, the pseudo-values solve the unit lower-triangular system
-//     (I + L) U = diag(b) V - diag(beta Gamma) K S ,   L_tr = beta_t (Gamma_t / Gamma_r) (k_t . k_r) ,  r < t
-// so U = Uhat - What S with  T = (I + L)^-1 ,  Uhat = T diag(b) V ,  What = T diag(beta Gamma) K  (the chunkwise
-// form published for the delta rule; the paper itself gives no algorithm for these rows).
-//   mk_delta_prep  (one workgroup per chunk, all chunks in parallel): L from K K^T on the matrix cores, T by
-//                  forward substitution in fp32 inside 32 x 32 diagonal blocks and a block product below them,
-//                  Uhat (fp32) and What (bf16) to the workspace.
-//   mk_delta_walk8 (one workgroup per sequence or segment): the forward chunk walker with one more product per chunk,
-//                  U = Uhat - What S from the state in the accumulators; U (as bf16 head + remainder) then plays the
-//                  value tile's part in the intra-chunk product and in the state update.
+//     (I + L) U = R ,  R = diag(b) V - diag(beta Gamma) K S ,   L_tr = beta_t (Gamma_t / Gamma_r) (k_t . k_r) ,  r < t
+// (the chunkwise form published for the delta rule; the paper itself gives no algorithm for these rows).
+//   mk_delta_prep  (one workgroup per chunk, all chunks in parallel): L from K K^T on the matrix cores, T = (I + L)^-1 by
+//                  forward substitution in fp32 inside 32 x 32 diagonal blocks and a block product below them.
+//   mk_delta_walk8 (one workgroup per sequence or segment): the forward chunk walker with two more products per chunk,
+//                  K S from the state in the accumulators and U = T R; U then plays the values' part in the
+//                  intra-chunk product and in the state update.
+// T is all that is handed from one to the other.  (T diag(b) V in fp32 and T diag(beta Gamma) K in bf16, formed by the first kernel,
+// make the walk's chain one product shorter and cost 1.3 KB of traffic a token and the rounding of the latter: 16 x 16
+// sequences of 2048, keeping U, 209 + 251 us; this 74 + 198.  Final state without a decay, 2-norm error 4.6e-4 -> 4.0e-6.)
 // Every value column of the state evolves on its own (the erase term acts on the key side only), so a wave
-// keeps its 128 x 32 slice of S and its 32 columns of U to itself.
+// keeps its 128 x 32 slice of S and its 32 columns of R and U to itself, in registers throughout: lane = value column,
+// registers = the index that the next product contracts.
 // Segments.  The state a segment of chunks ends with is an affine function of the state it starts from, S' = A S + B,
 // with a dense d_k x d_k factor A (the product of the chunks' erase-and-decay factors), not a decayed sum.  Because
 // the value columns evolve independently, A is what the same walk makes of the identity when the values are zero,
@@ -26,33 +28,68 @@
 // each sequence on the matrix cores, and the walker proper then runs all segments in parallel.
 #pragma once
 
-constexpr int LDU = D + 4;   // floats per row of an fp32 [64][128] tile in LDS
 constexpr int LDD = 36;      // floats per row of a 32 x 32 diagonal block of L
 constexpr int LDT = 40;      // elements per row of a 32 x 32 bf16 tile
-// LDS of mk_delta_prep (two workgroups per compute unit):
-//   K tile | R1: the four planes of T^T scaled by columns (64 x LDP bf16 each), later the Uhat stage (fp32)
-//          | R2: diagonal blocks of L (fp32; later R^T head, remainder), L_10 head, remainder, T_00^T and T_11^T head,
-//                remainder (32 x LDT bf16 each); later the V tile
-//          | log Gamma, beta, b
-constexpr int kDeltaR1 = 4 * C * LDP * 2;
-constexpr int kDeltaR2 = 2 * 32 * LDD * 4 + 6 * 32 * LDT * 2;
-static_assert(kDeltaR1 >= C * LDU * 4 && kDeltaR2 >= C * LD * 2 && 2 * 32 * LDD * 4 >= 2 * 32 * LDT * 2, "tenants fit");
-constexpr int kDeltaPrepLds = C * LD * 2 + kDeltaR1 + kDeltaR2 + 3 * C * 4;
+// T^T (rows r, columns t) of a chunk in memory, bf16 head and remainder: the rows r < 32 of either plane (64 columns), then the
+// rows r >= 32 (columns 32 .. 63; the others are zero and not kept)
+constexpr int kDeltaT = 2 * 32 * 64 + 2 * 32 * 32;
+// its 16-byte pieces in that order: place of piece p in a pair of tiles [2][64][LDP]
+__device__ __forceinline__ int delta_t_place(int p) {
+    const int q = p - 512;
+    return p < 512 ? ((p >> 8) * C + ((p >> 3) & 31)) * LDP + 8 * (p & 7) : ((q >> 7) * C + 32 + ((q >> 2) & 31)) * LDP + 32 + 8 * (q & 3);
+}
+// LDS of mk_delta_prep (four workgroups per compute unit): K tile, later L: diagonal blocks (fp32; later R^T head, remainder),
+// L_10 head, remainder | T^T head, remainder (64 x LDP) | log Gamma, beta
+constexpr int kDeltaPrepLds = C * LD * 2 + 2 * C * LDP * 2 + 2 * C * 4;
+static_assert(2 * 32 * LDD * 4 + 2 * 32 * LDT * 2 <= C * LD * 2 && 2 * 32 * LDD * 4 >= 2 * 32 * LDT * 2, "tenants fit");
 
 struct DeltaPrepArgs {
-    const uint16_t *k, *v;
-    const float *log_alpha, *beta, *bw;  // per token ([B,H,T], or [B,T,H] for the token-major layout); NULL = 1
-    uint16_t* what;                      // [BH*T][128] bf16
-    float* uhat;                         // [BH*T][128] fp32
-    uint16_t* tt;                        // NULL, or [BH*N][2][64][64] bf16: T^T (rows r, columns t), head and remainder planes
+    const uint16_t* k;
+    const float *log_alpha, *beta;  // per token ([B,H,T], or [B,T,H] for the token-major layout); NULL = 1
+    uint16_t* tt;                   // [BH*N][kDeltaT]
 };
 
+// a token-contraction operand like frag_tr whose k order follows a D-layout block (frag_perm's): slot e of lane (n, half) is row
+// row0 + 8 (e / 4) + 4 half + e % 4 of column col0 + n
+__device__ __forceinline__ bf16x8 frag_tr_perm(const uint16_t* tile, int ld, int row0, int col0, int lane) {
+    const int r = lane & 15, nblk = (lane >> 4) & 1, half = lane >> 5;
+    const uint16_t* p = tile + (row0 + 4 * half + (r >> 2)) * ld + col0 + 16 * nblk + 4 * (r & 3);
+    typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
+    const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p)));
+    const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 8 * ld)));
+    return __builtin_bit_cast(bf16x8, u32x4{lo.x, lo.y, hi.x, hi.y});
+}
+// registers 8p .. 8p+7 of a D-layout block as an operand of the next product (k = its rows), head and remainder
+__device__ __forceinline__ void split_frag(const f32x16& x, int p, u32x4& hi, u32x4& lo) {
+    _Pragma("unroll") for (int e = 0; e < 4; ++e) {
+        const float x0 = x[8 * p + 2 * e], x1 = x[8 * p + 2 * e + 1];
+        hi[e] = pack2(x0, x1);
+        lo[e] = pack2(x0 - bf16_lo(hi[e]), x1 - bf16_hi(hi[e]));
+    }
+}
+// ... and such an operand to LDS by rows: lane = column, so neighbouring lanes exchange halves and store two columns at once.
+// dst: row 0, column 0 of the 16 rows and 32 columns
+__device__ __forceinline__ void store_frag_rows(uint16_t* dst, int ld, const u32x4& w, int n, int half) {
+    const bool odd = n & 1;
+    uint16_t* p = dst + (4 * half + (odd ? 1 : 0)) * ld + (n & ~1);
+    const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+    _Pragma("unroll") for (int e = 0; e < 4; ++e) {
+        const uint32_t other = __builtin_amdgcn_mov_dpp(int(w[e]), 0xB1, 0xf, 0xf, true);  // lane ^ 1
+        *reinterpret_cast<uint32_t*>(p + (8 * (e >> 1) + 2 * (e & 1)) * ld) = __builtin_amdgcn_perm(other, w[e], sel);
+    }
+}
+// weights of the rows of registers 8p .. 8p+7 of a D-layout block at row0 - 16p
+__device__ __forceinline__ void row_weights(const float* tab, int row0, int half, float (&w)[8]) {
+    const float4 a = *reinterpret_cast<const float4*>(tab + row0 + 4 * half), b = *reinterpret_cast<const float4*>(tab + row0 + 8 + 4 * half);
+    w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w; w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w;
+}
+
 // 32 consecutive fp32 values -> one 32-element bf16 row, head and remainder
-__device__ __forceinline__ void delta_row_split(uint16_t* hi, uint16_t* lo, const float (&x)[32], float scale) {
+__device__ __forceinline__ void delta_row_split(uint16_t* hi, uint16_t* lo, const float (&x)[32]) {
     _Pragma("unroll") for (int i = 0; i < 4; ++i) {
         u32x4 h, l;
         _Pragma("unroll") for (int p = 0; p < 4; ++p) {
-            const float x0 = x[8 * i + 2 * p] * scale, x1 = x[8 * i + 2 * p + 1] * scale;
+            const float x0 = x[8 * i + 2 * p], x1 = x[8 * i + 2 * p + 1];
             h[p] = pack2(x0, x1);
             l[p] = pack2(x0 - bf16_lo(h[p]), x1 - bf16_hi(h[p]));
         }
@@ -63,54 +100,46 @@ __device__ __forceinline__ void delta_row_split(uint16_t* hi, uint16_t* lo, cons
 
 // grid: (N, BH).  T = (I + L)^-1 in two levels: the two 32 x 32 diagonal blocks by forward substitution in fp32
 // (one wave, lane = block and column), the block below the diagonal as T_10 = -T_11 L_10 T_00 on the matrix cores
-// with every factor as bf16 head + remainder.  T is kept transposed and already scaled by columns (b_r for Uhat,
-// beta_r Gamma_r for What), so every lane writes whole 16-byte row pieces.
+// with every factor as bf16 head + remainder.  T is kept transposed, so every lane writes whole 16-byte row pieces.
+// Bound: one wave's chain of the substitution (2.4 us of 5); four workgroups to a compute unit run beside each other.
 template <bool DEC>
-__global__ __launch_bounds__(kThreads, 2) void mk_delta_prep(Dims d, DeltaPrepArgs a) {
+__global__ __launch_bounds__(kThreads, 4) void mk_delta_prep(Dims d, DeltaPrepArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     uint16_t* Kt = reinterpret_cast<uint16_t*>(smem);
-    unsigned char* r1 = reinterpret_cast<unsigned char*>(Kt + C * LD);
-    uint16_t* TbTh = reinterpret_cast<uint16_t*>(r1);  // (T diag(b))^T [r][t], head and remainder
-    uint16_t* TbTl = TbTh + C * LDP;
-    uint16_t* TwTh = TbTl + C * LDP;                   // (T diag(beta Gamma))^T
-    uint16_t* TwTl = TwTh + C * LDP;
-    float* Ust = reinterpret_cast<float*>(r1);
-    unsigned char* r2 = r1 + kDeltaR1;
-    float* Ld = reinterpret_cast<float*>(r2);                              // [2][32][LDD]: L_00, L_11
-    uint16_t* RTh = reinterpret_cast<uint16_t*>(r2);                       // over L_00, L_11 once they are spent
+    float* Ld = reinterpret_cast<float*>(smem);                            // [2][32][LDD]: L_00, L_11
+    uint16_t* RTh = reinterpret_cast<uint16_t*>(smem);                     // over L_00, L_11 once they are spent
     uint16_t* RTl = RTh + 32 * LDT;
-    uint16_t* L10h = reinterpret_cast<uint16_t*>(r2 + 2 * 32 * LDD * 4);   // L_10 [t'][r]
+    uint16_t* L10h = reinterpret_cast<uint16_t*>(smem + 2 * 32 * LDD * 4); // L_10 [t'][r]
     uint16_t* L10l = L10h + 32 * LDT;
-    uint16_t* TTh = L10l + 32 * LDT;                                       // [2] x (head, remainder): T_00^T, T_11^T, [c][t']
-    uint16_t* Vt = reinterpret_cast<uint16_t*>(r2);
-    float* lg = reinterpret_cast<float*>(r2 + kDeltaR2);  // log Gamma_t
+    uint16_t* Th = Kt + C * LD;                                            // T^T [r][t]
+    uint16_t* Tl = Th + C * LDP;
+    float* lg = reinterpret_cast<float*>(Tl + C * LDP);                    // log Gamma_t
     float* be = lg + C;
-    float* bb = be + C;
 
     const int c = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 31, half = lane >> 5;
     const ChunkPos cp = chunk_pos(d, c, bh);
     const int L = cp.L;
     if (L <= 0) return;
+    TileRegs rk;
+    tile_gload(rk, a.k, cp.tok0, cp.ts, L, tid);
     if (wave == 0) {
         const size_t ptok = cp.tok0 + size_t(min(lane, L - 1)) * cp.ts;
         float x = (DEC && lane < L) ? a.log_alpha[ptok] : 0.f;
-        const float bet = a.beta ? a.beta[ptok] : 1.f, bwt = a.bw ? a.bw[ptok] : 1.f;
+        const float bet = a.beta ? a.beta[ptok] : 1.f;
         for (int off = 1; off < 64; off <<= 1) {
             const float y = __shfl_up(x, off, 64);
             if (lane >= off) x += y;
         }
         lg[lane] = x;
-        be[lane] = lane < L ? bet : 0.f;  // rows beyond the ragged end: no erase, no write
-        bb[lane] = lane < L ? bwt : 0.f;
+        be[lane] = lane < L ? bet : 0.f;  // rows beyond the ragged end: no erase
     }
-    TileRegs rv;
-    tile_gload(rv, a.v, cp.tok0, cp.ts, L, tid);  // held in registers until the solve has freed its LDS
-    load_tile(Kt, a.k, cp.tok0, cp.ts, L, tid);
+    tile_commit(Kt, rk, L, tid);
     __syncthreads();
     // ---- L[t][r] = beta_t e^{lg_t - lg_r} (k_t . k_r) for r < t, else 0: blocks (r, t) = (0,0), (0,1), (1,1)
+    f32x16 G;
+    const int rb = wave == 2 ? 1 : 0, tb = wave ? 1 : 0;
     if (wave < 3) {
-        const int rb = wave == 2 ? 1 : 0, tb = wave ? 1 : 0;
-        f32x16 G = score_block2(Kt, 32 * rb, Kt, 32 * tb, n, half);  // D[m = r][n = t]
+        G = score_block2(Kt, 32 * rb, Kt, 32 * tb, n, half);  // D[m = r][n = t]
         const int t = 32 * tb + n;
         const float bt = be[t], lt = lg[t];
         _Pragma("unroll") for (int g = 0; g < 4; ++g) {
@@ -121,6 +150,9 @@ __global__ __launch_bounds__(kThreads, 2) void mk_delta_prep(Dims d, DeltaPrepAr
                 G[4 * g + j] = r < t ? bt * (DEC ? __expf(lt - lrv[j]) : 1.f) * G[4 * g + j] : 0.f;
             }
         }
+    }
+    __syncthreads();  // the K tile is spent
+    if (wave < 3) {
         if (rb == tb) {  // diagonal block, fp32 [t'][r']
             float* dst = Ld + rb * 32 * LDD + n * LDD;
             _Pragma("unroll") for (int g = 0; g < 4; ++g)
@@ -147,28 +179,13 @@ __global__ __launch_bounds__(kThreads, 2) void mk_delta_prep(Dims d, DeltaPrepAr
             }
             X[t] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
         }
-        const float bcol = bb[lane], wcol = be[lane] * (DEC ? __expf(lg[lane]) : 1.f);  // lane = this column's token
-        uint16_t* tt = TTh + blk * 2 * 32 * LDT;
-        delta_row_split(tt + cc * LDT, tt + 32 * LDT + cc * LDT, X, 1.f);
-        delta_row_split(TbTh + lane * LDP + 32 * blk, TbTl + lane * LDP + 32 * blk, X, bcol);
-        delta_row_split(TwTh + lane * LDP + 32 * blk, TwTl + lane * LDP + 32 * blk, X, wcol);
-        uint16_t* gtt = a.tt ? a.tt + cp.slot * 2 * C * C : nullptr;  // the backward pass wants T itself
-        if (gtt) {
-            delta_row_split(gtt + lane * C + 32 * blk, gtt + C * C + lane * C + 32 * blk, X, 1.f);
-            if (blk) {  // T[t][r] = 0 for t < 32 <= r
-                _Pragma("unroll") for (int i = 0; i < 4; ++i) {
-                    *reinterpret_cast<u32x4*>(gtt + lane * C + 8 * i) = u32x4{0, 0, 0, 0};
-                    *reinterpret_cast<u32x4*>(gtt + C * C + lane * C + 8 * i) = u32x4{0, 0, 0, 0};
-                }
-            }
-        }
+        delta_row_split(Th + lane * LDP + 32 * blk, Tl + lane * LDP + 32 * blk, X);
         __builtin_amdgcn_wave_barrier();  // LDS serves one wave's accesses in order: what follows reads what was just written
         // ---- R[r][t] = sum_t' L_10[t'][r] T_11[t][t'], kept as R^T [t][r]
-        const uint16_t *T00h = TTh, *T00l = TTh + 32 * LDT, *T11h = TTh + 2 * 32 * LDT, *T11l = TTh + 3 * 32 * LDT;
         f32x16 R = {0};
         _Pragma("unroll") for (int ks = 0; ks < 2; ++ks) {
             const bf16x8 ah = frag_tr(L10h, LDT, 16 * ks, 0, lane), al = frag_tr(L10l, LDT, 16 * ks, 0, lane);
-            const bf16x8 bh_ = frag_tr(T11h, LDT, 16 * ks, 0, lane), bl = frag_tr(T11l, LDT, 16 * ks, 0, lane);
+            const bf16x8 bh_ = frag_tr(Th, LDP, 32 + 16 * ks, 32, lane), bl = frag_tr(Tl, LDP, 32 + 16 * ks, 32, lane);
             R = mfma(ah, bh_, R);
             R = mfma(ah, bl, R);
             R = mfma(al, bh_, R);
@@ -176,67 +193,30 @@ __global__ __launch_bounds__(kThreads, 2) void mk_delta_prep(Dims d, DeltaPrepAr
         __builtin_amdgcn_wave_barrier();
         store_block_t_split(RTh, RTl, LDT, n, 0, half, R);  // over the diagonal blocks of L, which are spent
         __builtin_amdgcn_wave_barrier();
-        // ---- T_10[t][c] = -sum_r R^T[t][r] T_00[r][c], scaled by this lane's column and stored transposed
+        // ---- T_10[t][c] = -sum_r R^T[t][r] T_00[r][c]
         f32x16 T10 = {0};
         _Pragma("unroll") for (int ks = 0; ks < 2; ++ks) {
             const bf16x8 ah = frag(RTh, LDT, n, 16 * ks + 8 * half), al = frag(RTl, LDT, n, 16 * ks + 8 * half);
-            const bf16x8 bh_ = frag(T00h, LDT, n, 16 * ks + 8 * half), bl = frag(T00l, LDT, n, 16 * ks + 8 * half);
+            const bf16x8 bh_ = frag(Th, LDP, n, 16 * ks + 8 * half), bl = frag(Tl, LDP, n, 16 * ks + 8 * half);
             T10 = mfma(ah, bh_, T10);
             T10 = mfma(ah, bl, T10);
             T10 = mfma(al, bh_, T10);
         }
-        const float b0 = bb[n], w0 = be[n] * (DEC ? __expf(lg[n]) : 1.f);  // column c = n of the first block
-        f32x16 Tb, Tw;
-        _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-            Tb[x] = -T10[x] * b0;
-            Tw[x] = -T10[x] * w0;
-        }
-        store_block_t_split(TbTh, TbTl, LDP, n, 32, half, Tb);  // rows c, columns 32 + t
-        store_block_t_split(TwTh, TwTl, LDP, n, 32, half, Tw);
-        if (gtt) {
-            _Pragma("unroll") for (int x = 0; x < 16; ++x) Tb[x] = -T10[x];
-            store_block_t_split(gtt, gtt + C * C, C, n, 32, half, Tb);
-        }
+        _Pragma("unroll") for (int x = 0; x < 16; ++x) T10[x] = -T10[x];
+        store_block_t_split(Th, Tl, LDP, n, 32, half, T10);  // rows c, columns 32 + t
     }
-    __syncthreads();  // T is complete; the small tiles are spent
-    tile_commit(Vt, rv, L, tid);
-    __syncthreads();
-    // ---- What^T[c][t] = sum_r K[r][c] Tw[t][r],  Uhat^T[c][t] = sum_r V[r][c] Tb[t][r]; this wave: features 32 w ..
-    f32x16 Wt[2] = {{0}, {0}}, Ut[2] = {{0}, {0}};
-    _Pragma("unroll") for (int nb = 0; nb < 2; ++nb)
-        _Pragma("unroll") for (int ks = 0; ks < 2 * (nb + 1); ++ks) {  // T is lower triangular
-            const bf16x8 ka = frag_tr(Kt, LD, 16 * ks, 32 * wave, lane), va = frag_tr(Vt, LD, 16 * ks, 32 * wave, lane);
-            Wt[nb] = mfma(ka, frag_tr(TwTh, LDP, 16 * ks, 32 * nb, lane), Wt[nb]);
-            Wt[nb] = mfma(ka, frag_tr(TwTl, LDP, 16 * ks, 32 * nb, lane), Wt[nb]);
-            Ut[nb] = mfma(va, frag_tr(TbTh, LDP, 16 * ks, 32 * nb, lane), Ut[nb]);
-            Ut[nb] = mfma(va, frag_tr(TbTl, LDP, 16 * ks, 32 * nb, lane), Ut[nb]);
-        }
-    __syncthreads();  // every read of the tiles and of the planes is done
-    _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
-        store_packed(Kt, LD, 32 * nb + n, 32 * wave, half, pack_block(Wt[nb]));
-        _Pragma("unroll") for (int g = 0; g < 4; ++g)
-            *reinterpret_cast<float4*>(Ust + (32 * nb + n) * LDU + 32 * wave + 8 * g + 4 * half) =
-                float4{Ut[nb][4 * g], Ut[nb][4 * g + 1], Ut[nb][4 * g + 2], Ut[nb][4 * g + 3]};
-    }
-    __syncthreads();
-    _Pragma("unroll") for (int it = 0; it < 4; ++it) {
-        const int p = tid + kThreads * it, row = p >> 4, cpp = p & 15;
-        if (row < L)
-            *reinterpret_cast<u32x4*>(a.what + (cp.wtok0 + row) * D + cpp * 8) = *reinterpret_cast<const u32x4*>(Kt + row * LD + cpp * 8);
-    }
-    _Pragma("unroll") for (int it = 0; it < 8; ++it) {
-        const int p = tid + kThreads * it, row = p >> 5, c4 = p & 31;
-        if (row < L)
-            *reinterpret_cast<float4*>(a.uhat + (cp.wtok0 + row) * D + c4 * 4) = *reinterpret_cast<const float4*>(Ust + row * LDU + c4 * 4);
+    __syncthreads();  // T is complete
+    _Pragma("unroll") for (int it = 0; it < 3; ++it) {
+        const int p = tid + kThreads * it;
+        *reinterpret_cast<u32x4*>(a.tt + cp.slot * kDeltaT + 8 * p) = *reinterpret_cast<const u32x4*>(Th + delta_t_place(p));
     }
 }
 
 // ---- the walker
 struct DeltaWalkArgs {
-    const uint16_t *q, *k;
-    const uint16_t* what;   // [BH*T][128]
-    const float* uhat;      // [BH*T][128]
-    const float* log_alpha;
+    const uint16_t *q, *k, *v;
+    const uint16_t* tt;     // [BH*N][kDeltaT]
+    const float *log_alpha, *beta, *bw;  // per token, NULL = 1
     uint16_t* out;
     const float* edge_in;   // M_0 [i][v] per sequence or NULL
     float* edge_out;        // M_T or NULL
@@ -247,72 +227,52 @@ struct DeltaWalkArgs {
     const float* bound;
     float* sum;
 };
-// The pseudo-values are kept as bf16 head + remainder: a single rounding of u_t would show in o_t at the size of
-// an output ulp wherever one token dominates the read-out (strong decay), which the diagonal kinds never pay
-// because their values are inputs.
-// intra: O^T[v][j] += sum_{r <= j} U^T[v][r] P[j][r] for the query block jb (remainder x remainder left out)
-__device__ __forceinline__ void delta_intra(f32x16& O, int jb, const uint16_t* Vh, const uint16_t* Vl, const uint16_t* Ph,
-                                            const uint16_t* Pl, int w4, int lane, int n, int half) {
-    const int j = 32 * jb + n;
-    _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
-        if (ks >= 2 * (jb + 1)) break;  // keys r >= 32 never reach queries j < 32
-        const bf16x8 vh = frag_tr(Vh, LD, 16 * ks, 32 * w4, lane), vl = frag_tr(Vl, LD, 16 * ks, 32 * w4, lane);
-        const bf16x8 ph = frag(Ph, LDP, j, 16 * ks + 8 * half);
-        O = mfma(vh, ph, O);
-        O = mfma(vl, ph, O);
-        O = mfma(vh, frag(Pl, LDP, j, 16 * ks + 8 * half), O);
-    }
-}
-struct TileRegsF { float4 v[8]; };
-__device__ __forceinline__ void tilef_gload(TileRegsF& r, const float* src, size_t tok0, int L, int tid) {
-    _Pragma("unroll") for (int it = 0; it < 8; ++it) {
-        const int p = tid + kThreads * it, row = min(p >> 5, L - 1), c4 = p & 31;
-        r.v[it] = *reinterpret_cast<const float4*>(src + (tok0 + row) * D + c4 * 4);
-    }
-}
-__device__ __forceinline__ void tilef_commit(float* dst, const TileRegsF& r, int L, int tid) {
-    _Pragma("unroll") for (int it = 0; it < 8; ++it) {
-        const int p = tid + kThreads * it, row = p >> 5, c4 = p & 31;
-        const float keep = row < L ? 1.f : 0.f;
-        *reinterpret_cast<float4*>(dst + row * LDU + c4 * 4) = float4{r.v[it].x * keep, r.v[it].y * keep, r.v[it].z * keep, r.v[it].w * keep};
-    }
-}
 
 // The walk (MODE 0), and the summaries of a segment for the cut into segments: the state part of the walk alone, from a
 // zero state (MODE 1: the segment's own contribution B) or from the identity with zero values (MODE 2: its transfer
 // matrix A).  grid: (segments, seqs).  Eight waves, two per SIMD, split by function:
-//   waves 0..3 carry the state (wave w: value columns [32w, 32w+32)): both inter products, the pseudo-values, the intra
+//   waves 0..3 carry the state (wave w: value columns [32w, 32w+32)): both inter products, R and U, the intra
 //              part of the output and the state update - the chain that every chunk has to go through in order;
 //   waves 4..7 do everything that does not need the state: all tile traffic (global -> registers -> LDS one chunk ahead,
-//              output stage and pseudo-values -> global), the decay tables, the three score blocks.
-// A chunk has two phases.  In the first the carrier waves read Q, What and Uhat (inter products, pseudo-values) while the
-// others compute the scores and store the previous chunk's output; in the second the carrier waves read only the scores,
-// K and their own pseudo-values (intra part, state update), so the others overwrite Q, What and Uhat with the next
-// chunk's rows and rebuild the decay tables (two sets, used in turn) meanwhile.  Only K, which both phases read, is
-// committed between two chunks.  The output has a stage of its own for the same reason.
-// LDS: Q | K | U head | U remainder | What | output stage (64 x LD bf16 each) | Uhat (64 x LDU fp32) | scores head |
-// scores remainder (64 x LDP) | two sets of (bs, wo)
-constexpr int kDeltaTab = 2 * C + 8;
-constexpr int kDeltaWalk8Lds = (6 * C * LD + 2 * C * LDP) * 2 + C * LDU * 4 + 2 * kDeltaTab * 4;
+//              output and pseudo-values -> global), the tables, the three score blocks.
+// A chunk has two phases.  In the first the carrier waves read Q, K, V and T (inter products, R, U) while the others compute
+// the scores and store the previous chunk's results; in the second the carrier waves read only the scores and K (intra
+// part, state update), so the others overwrite Q, V, T and the K tile of the chunk before with the next chunk's rows and rebuild the
+// tables (K and the tables in two sets, used in turn) meanwhile: two barriers a chunk.
+// The pseudo-values are kept as bf16 head + remainder: a single rounding of u_t would show in o_t at the size of
+// an output ulp wherever one token dominates the read-out (strong decay), which the diagonal kinds never pay
+// because their values are inputs.  R is split the same way, products of two remainders are left out.
+// LDS: Q | K (two sets) | V | output stage | U head stage | U remainder stage (64 x LD bf16 each) | T^T head | remainder |
+// scores head | scores remainder (64 x LDP) | two sets of (bs, wo, -beta Gamma, b)
+constexpr int kDeltaTab = 4 * C + 4;
+constexpr int kDeltaWalk8Lds = (7 * C * LD + 4 * C * LDP) * 2 + 2 * kDeltaTab * 4;
 static_assert(kDeltaWalk8Lds <= 160 * 1024, "one workgroup's LDS");
 
 template <bool DEC, int MODE>
 __global__ __launch_bounds__(512, 1) void mk_delta_walk8(Dims d, DeltaWalkArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     uint16_t* Q = reinterpret_cast<uint16_t*>(smem);
-    uint16_t* K = Q + C * LD;
-    uint16_t* V = K + C * LD;    // pseudo-values U of this chunk, bf16 head
-    uint16_t* Vl = V + C * LD;   // and remainder
-    uint16_t* Wh = Vl + C * LD;
-    uint16_t* stage = Wh + C * LD;
-    float* Uh = reinterpret_cast<float*>(stage + C * LD);
-    uint16_t* Ph = reinterpret_cast<uint16_t*>(Uh + C * LDU);
+    uint16_t* K2 = Q + C * LD;   // [2]
+    uint16_t* V = K2 + 2 * C * LD;
+    uint16_t* stage = V + C * LD;
+    uint16_t* Us = stage + C * LD;
+    uint16_t* Usl = Us + C * LD;
+    uint16_t* Th = Usl + C * LD;
+    uint16_t* Tl = Th + C * LDP;
+    uint16_t* Ph = Tl + C * LDP;
     uint16_t* Pl = Ph + C * LDP;
-    float* tab = reinterpret_cast<float*>(Pl + C * LDP);  // [2][kDeltaTab]: bs (65), wo (64) of the chunks of either parity
+    float* tab = reinterpret_cast<float*>(Pl + C * LDP);  // [2][kDeltaTab]: bs (65), wo, ne, bb (64) of the chunks of either parity
 
     // the wave index as a scalar: the branch between the two groups is a scalar branch
     const int seg = blockIdx.x, seq = blockIdx.y, tid = threadIdx.x, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lane = tid & 63, wave = wave8 & 3, n = lane & 31, half = lane >> 5;
+    const int wave = wave8 & 3;
+    int lane = tid & 63, n = lane & 31, half = lane >> 5;
+    // (as in mk_walk_grad: a phase's lane-dependent LDS addresses are formed in the phase, not kept across the loop)
+    auto fresh = [&]() {
+        asm volatile("" : "+v"(lane));
+        n = lane & 31;
+        half = lane >> 5;
+    };
     const int t256 = tid & 255;
     const bool carrier = wave8 < 4;
     const SeqWalk walk = seq_walk(d, seq);
@@ -338,104 +298,174 @@ __global__ __launch_bounds__(512, 1) void mk_delta_walk8(Dims d, DeltaWalkArgs a
                     S[ib][x] = (32 * ib + 8 * (x >> 2) + 4 * half + (x & 3) == 32 * wave + n) ? 1.f : 0.f;
         }
         for (int kk = 0; kk < cnt; ++kk) {
+            const uint16_t* K = K2 + (kk & 1) * C * LD;
             const float* bs = tab + (kk & 1) * kDeltaTab;
-            const float* wo = bs + C + 4;
-            __syncthreads();  // (A) the tiles and the decay tables of this chunk are in LDS
-            const float bC = DEC ? bs[C] : 0.f;
-            // pseudo-values of this wave's value columns: U^T[v][t] = Uhat[t][v] - sum_i S[i][v] What[t][i]; the inter part
-            // of the output comes out of the same pass over the state blocks (one conversion to bf16 head + remainder)
-            f32x16 O[2];
-            {
-                f32x16 Wacc[2];
-                walk_inter_pair<DEC, MODE == 0>(Wacc, O, S, Wh, Q, bs, n, half);
-                _Pragma("unroll") for (int tb = 0; tb < 2; ++tb) {
-                    f32x16 u;
-                    _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                        const float4 uh = MODE == 2 ? float4{0.f, 0.f, 0.f, 0.f}
-                                                    : *reinterpret_cast<const float4*>(Uh + (32 * tb + n) * LDU + 32 * wave + 8 * g + 4 * half);
-                        u[4 * g + 0] = uh.x - Wacc[tb][4 * g + 0];
-                        u[4 * g + 1] = uh.y - Wacc[tb][4 * g + 1];
-                        u[4 * g + 2] = uh.z - Wacc[tb][4 * g + 2];
-                        u[4 * g + 3] = uh.w - Wacc[tb][4 * g + 3];
+            const float *wo = bs + C + 4, *ne = wo + C, *bb = ne + C;
+            __syncthreads();  // (A) the tiles and the tables of this chunk are in LDS
+            fresh();
+            // both inter products with one conversion of the state blocks: R[t][v] = sum_i k_t[i] S[i][v], O^T[v][j] = sum_i S[i][v] q_j[i]
+            f32x16 R[2] = {{0}, {0}}, O[2] = {{0}, {0}};
+            _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
+                _Pragma("unroll") for (int p = 0; p < 2; ++p) {
+                    u32x4 hi, lo;
+                    split_frag(S[ib], p, hi, lo);
+                    const bf16x8 sh = __builtin_bit_cast(bf16x8, hi), sl = __builtin_bit_cast(bf16x8, lo);
+                    const bf16x8 k0 = frag_perm(K, LD, n, 32 * ib + 16 * p, half), k1 = frag_perm(K, LD, 32 + n, 32 * ib + 16 * p, half);
+                    R[0] = mfma(k0, sh, R[0]);
+                    R[1] = mfma(k1, sh, R[1]);
+                    R[0] = mfma(k0, sl, R[0]);
+                    R[1] = mfma(k1, sl, R[1]);
+                    if (MODE == 0) {
+                        const bf16x8 q0 = frag_perm(Q, LD, n, 32 * ib + 16 * p, half), q1 = frag_perm(Q, LD, 32 + n, 32 * ib + 16 * p, half);
+                        O[0] = mfma(sh, q0, O[0]);
+                        O[1] = mfma(sh, q1, O[1]);
+                        O[0] = mfma(sl, q0, O[0]);
+                        O[1] = mfma(sl, q1, O[1]);
                     }
-                    const PackedBlock uh = pack_block(u);
-                    _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                        u[4 * g + 0] -= bf16_lo(uh.v[g].x);
-                        u[4 * g + 1] -= bf16_hi(uh.v[g].x);
-                        u[4 * g + 2] -= bf16_lo(uh.v[g].y);
-                        u[4 * g + 3] -= bf16_hi(uh.v[g].y);
-                    }
-                    store_packed(V, LD, 32 * tb + n, 32 * wave, half, uh);
-                    store_packed(Vl, LD, 32 * tb + n, 32 * wave, half, pack_block(u));
+                }
+            if (DEC && MODE == 0) {
+                _Pragma("unroll") for (int jb = 0; jb < 2; ++jb) {
+                    const float w = __expf(bs[32 * jb + n]);
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) O[jb][x] *= w;
                 }
             }
-            __syncthreads();  // (C) scores are in LDS; Q, What and Uhat are spent (this wave's columns of U are its own)
+            fresh();
+            // R = b V - beta Gamma K S, U = T R
+            f32x16 U[2] = {{0}, {0}};
+            _Pragma("unroll") for (int kr = 0; kr < 4; ++kr) {
+                f32x16& Rb = R[kr >> 1];
+                const int x0 = 8 * (kr & 1);
+                float w[8], wv[8];
+                row_weights(ne, 16 * kr, half, w);
+                _Pragma("unroll") for (int x = 0; x < 8; ++x) Rb[x0 + x] *= w[x];
+                if (MODE != 2) {
+                    row_weights(bb, 16 * kr, half, wv);
+                    const u32x4 v8 = __builtin_bit_cast(u32x4, frag_tr_perm(V, LD, 16 * kr, 32 * wave, lane));
+                    _Pragma("unroll") for (int e = 0; e < 4; ++e) {
+                        Rb[x0 + 2 * e] = fmaf(wv[2 * e], bf16_lo(v8[e]), Rb[x0 + 2 * e]);
+                        Rb[x0 + 2 * e + 1] = fmaf(wv[2 * e + 1], bf16_hi(v8[e]), Rb[x0 + 2 * e + 1]);
+                    }
+                }
+                u32x4 hi, lo;
+                split_frag(Rb, kr & 1, hi, lo);
+                const bf16x8 rh = __builtin_bit_cast(bf16x8, hi), rl = __builtin_bit_cast(bf16x8, lo);
+                _Pragma("unroll") for (int tb = kr >> 1; tb < 2; ++tb) {
+                    const bf16x8 th = frag_tr_perm(Th, LDP, 16 * kr, 32 * tb, lane), tl = frag_tr_perm(Tl, LDP, 16 * kr, 32 * tb, lane);
+                    U[tb] = mfma(th, rh, U[tb]);
+                    U[tb] = mfma(tl, rh, U[tb]);
+                    U[tb] = mfma(th, rl, U[tb]);
+                }
+            }
+            u32x4 uh[4], ul[4];
+            _Pragma("unroll") for (int kr = 0; kr < 4; ++kr) split_frag(U[kr >> 1], kr & 1, uh[kr], ul[kr]);
+            __syncthreads();  // (C) scores are in LDS; Q, V and T are spent
+            fresh();
             if (MODE == 0) {
+                // O^T[v][j] += sum_{r <= j} U^T[v][r] P[j][r]
                 _Pragma("unroll") for (int jb = 0; jb < 2; ++jb) {
-                    delta_intra(O[jb], jb, V, Vl, Ph, Pl, wave, lane, n, half);
+                    _Pragma("unroll") for (int kr = 0; kr < 2 * (jb + 1); ++kr) {  // keys r >= 32 never reach queries j < 32
+                        const bf16x8 ph = frag_perm(Ph, LDP, 32 * jb + n, 16 * kr, half), pl = frag_perm(Pl, LDP, 32 * jb + n, 16 * kr, half);
+                        const bf16x8 h = __builtin_bit_cast(bf16x8, uh[kr]), l = __builtin_bit_cast(bf16x8, ul[kr]);
+                        O[jb] = mfma(h, ph, O[jb]);
+                        O[jb] = mfma(l, ph, O[jb]);
+                        O[jb] = mfma(h, pl, O[jb]);
+                    }
                     store_packed(stage, LD, 32 * jb + n, 32 * wave, half, pack_block(O[jb]));
                 }
+                if (a.usave) {
+                    _Pragma("unroll") for (int kr = 0; kr < 4; ++kr) {
+                        store_frag_rows(Us + 16 * kr * LD + 32 * wave, LD, uh[kr], n, half);
+                        store_frag_rows(Usl + 16 * kr * LD + 32 * wave, LD, ul[kr], n, half);
+                    }
+                }
             }
-            walk_update_vsplit<DEC, true>(S, K, V, Vl, wo, bC, wave, lane, half);
-            __syncthreads();  // (D) the output stage is complete and every read of K and of the pseudo-values is done
+            fresh();
+            // S[i][v] = e^{b_C} S[i][v] + sum_t k_t[i] (wo_t U[t][v])
+            if (DEC) {
+                const float lam = __expf(bs[C]);
+                _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) S[ib][x] *= lam;
+            }
+            _Pragma("unroll") for (int kr = 0; kr < 4; ++kr) {
+                u32x4 hi = uh[kr], lo = ul[kr];
+                if (DEC) {
+                    float w[8];
+                    row_weights(wo, 16 * kr, half, w);
+                    _Pragma("unroll") for (int x = 0; x < 8; ++x) U[kr >> 1][8 * (kr & 1) + x] *= w[x];
+                    split_frag(U[kr >> 1], kr & 1, hi, lo);
+                }
+                const bf16x8 h = __builtin_bit_cast(bf16x8, hi), l = __builtin_bit_cast(bf16x8, lo);
+                bf16x8 ka[4];
+                _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) ka[ib] = frag_tr_perm(K, LD, 16 * kr, 32 * ib, lane);
+                _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) S[ib] = mfma(ka[ib], h, S[ib]);
+                _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) S[ib] = mfma(ka[ib], l, S[ib]);
+            }
         }
+        __syncthreads();  // (E) the last chunk's results are staged
         if (MODE != 0) walk_state_store(S, a.sum + (size_t(seq) * a.nseg + seg) * D * D, false, wave, n, half);
         else if (a.edge_out && seg == nsq - 1) walk_state_store(S, a.edge_out + size_t(seq) * D * D, false, wave, n, half);
     } else {
-        TileRegs rq, rk, rw;
-        TileRegsF ru;
-        float gval = 0.f;
+        TileRegs rq, rk, rv;
+        u32x4 rt[3];
+        float gval = 0.f, bval = 1.f, bwval = 1.f;
         auto pos = [&](int kk) { return walk_pos(d, walk, kbeg + min(kk, cnt - 1)); };
-        auto gload_main = [&](int kk) {  // the rows of the first phase, and the log-decays
+        auto gload = [&](int kk) {
             const ChunkPos p = pos(kk);
-            if (DEC) gval = a.log_alpha[p.tok0 + size_t(min(lane, p.L - 1)) * p.ts];
+            const size_t pt = p.tok0 + size_t(min(lane, p.L - 1)) * p.ts;
+            if (DEC) gval = a.log_alpha[pt];
+            if (a.beta) bval = a.beta[pt];
+            if (MODE != 2 && a.bw) bwval = a.bw[pt];
             if (MODE == 0) walk_gload<false, kThreads>(rq, a.q, p.tok0, p.ts, p.L, t256);
-            walk_gload<false, kThreads>(rw, a.what, p.wtok0, 1, p.L, t256);
-            if (MODE != 2) tilef_gload(ru, a.uhat, p.wtok0, p.L, t256);
+            walk_gload<false, kThreads>(rk, a.k, p.tok0, p.ts, p.L, t256);
+            if (MODE != 2) walk_gload<false, kThreads>(rv, a.v, p.tok0, p.ts, p.L, t256);
+            _Pragma("unroll") for (int it = 0; it < 3; ++it)
+                rt[it] = *reinterpret_cast<const u32x4*>(a.tt + p.slot * kDeltaT + 8 * (t256 + kThreads * it));
         };
-        auto commit_main = [&](int kk) {  // ... into LDS, with the decay tables of that chunk
+        auto commit = [&](int kk) {
             const int L = pos(kk).L;
             if (MODE == 0) walk_commit<kThreads>(Q, rq, L, t256);
-            walk_commit<kThreads>(Wh, rw, L, t256);
-            if (MODE != 2) tilef_commit(Uh, ru, L, t256);
+            walk_commit<kThreads>(K2 + (kk & 1) * C * LD, rk, L, t256);
+            if (MODE != 2) walk_commit<kThreads>(V, rv, L, t256);
+            _Pragma("unroll") for (int it = 0; it < 3; ++it) *reinterpret_cast<u32x4*>(Th + delta_t_place(t256 + kThreads * it)) = rt[it];
             float* bs = tab + (kk & 1) * kDeltaTab;
-            if (DEC && wave == 0) walk_decay_tables<false>(gval, L, 0.f, bs, bs + C + 4, lane);
+            float *wo = bs + C + 4, *ne = wo + C, *bb = ne + C;
+            if (wave == 0) {
+                float gam = 1.f;
+                if (DEC) {
+                    walk_decay_tables<false>(gval, L, 0.f, bs, wo, lane);
+                    gam = __expf(bs[lane]);
+                }
+                ne[lane] = lane < L ? -bval * gam : 0.f;
+                bb[lane] = lane < L ? bwval : 0.f;
+            }
         };
-        auto gload_k = [&](int kk) {
+        auto store = [&](int kk) {  // a chunk's output and pseudo-values
             const ChunkPos p = pos(kk);
-            walk_gload<false, kThreads>(rk, a.k, p.tok0, p.ts, p.L, t256);
+            if (a.out) walk_store<false, kThreads>(a.out, stage, p.tok0, p.ts, p.L, t256);
+            if (a.usave) {
+                walk_store<false, kThreads>(a.usave, Us, p.tok0, p.ts, p.L, t256);
+                walk_store<false, kThreads>(a.usave_l, Usl, p.tok0, p.ts, p.L, t256);
+            }
         };
         if (cnt > 0) {
-            gload_main(0);
-            gload_k(0);
-            commit_main(0);
-            if (cnt > 1) gload_main(1);
+            gload(0);
+            commit(0);
+            if (cnt > 1) gload(1);
         }
         for (int kk = 0; kk < cnt; ++kk) {
-            const ChunkPos cp = pos(kk);
-            walk_commit<kThreads>(K, rk, cp.L, t256);
             __syncthreads();  // (A)
-            if (kk + 1 < cnt) gload_k(kk + 1);
-            if (MODE == 0) walk_scores<DEC>(K, Q, Ph, Pl, tab + (kk & 1) * kDeltaTab, wave, n, half);
-            if (MODE == 0 && kk > 0 && a.out) {  // the previous chunk's output
-                const ChunkPos pp = pos(kk - 1);
-                walk_store<false, kThreads>(a.out, stage, pp.tok0, pp.ts, pp.L, t256);
+            if (MODE == 0) {
+                walk_scores<DEC>(K2 + (kk & 1) * C * LD, Q, Ph, Pl, tab + (kk & 1) * kDeltaTab, wave, n, half);
+                if (kk > 0) store(kk - 1);
             }
             __syncthreads();  // (C)
             if (kk + 1 < cnt) {
-                commit_main(kk + 1);
-                if (kk + 2 < cnt) gload_main(kk + 2);
+                commit(kk + 1);
+                if (kk + 2 < cnt) gload(kk + 2);
             }
-            if (MODE == 0 && a.usave) {
-                walk_store<false, kThreads>(a.usave, V, cp.tok0, cp.ts, cp.L, t256);
-                walk_store<false, kThreads>(a.usave_l, Vl, cp.tok0, cp.ts, cp.L, t256);
-            }
-            __syncthreads();  // (D)
         }
-        if (MODE == 0 && cnt > 0 && a.out) {
-            const ChunkPos pp = pos(cnt - 1);
-            walk_store<false, kThreads>(a.out, stage, pp.tok0, pp.ts, pp.L, t256);
-        }
+        __syncthreads();  // (E)
+        if (MODE == 0 && cnt > 0) store(cnt - 1);
     }
 }
 
@@ -543,7 +573,7 @@ __global__ __launch_bounds__(kThreads, 1) void mk_delta_combine(Dims d, const fl
 // summary pass over U for the entry states): forward + backward, 16 x 16 sequences of 2048, 1.64 -> 1.19 ms.
 struct DeltaRevArgs {
     const uint16_t *q, *k, *v, *d_o;
-    const uint16_t* tt;       // [BH*N][2][64][64] bf16: T^T (rows r, columns t), head and remainder planes
+    const uint16_t* tt;       // [BH*N][kDeltaT]
     const float *log_alpha, *beta, *bw;
     uint16_t* dstates;        // [BH*N] fragment-major bf16: slot c = gradient of the state at the end of chunk c
     uint16_t *w_h, *w_l;      // [BH*T][128] bf16 (library order)
@@ -559,41 +589,6 @@ constexpr int LDW = 40;  // row stride of a wave's private 32-column tiles
 // LDS: Q | K | dO (64 x LD) | T^T head | remainder | scores head | remainder (64 x LDP) | per wave: 128 x LDW bf16 (its columns
 // of dS', then of W head and remainder, 64 x LDW each) | bs | wo | Gamma | -beta Gamma | b | db per wave
 constexpr int kDeltaRevLds = (3 * C * LD + 4 * C * LDP) * 2 + 4 * D * LDW * 2 + (5 * C + 8 + 4 * C) * 4;
-
-// a token-contraction operand like frag_tr whose k order follows a D-layout block (frag_perm's): slot e of lane (n, half) is row
-// row0 + 8 (e / 4) + 4 half + e % 4 of column col0 + n
-__device__ __forceinline__ bf16x8 frag_tr_perm(const uint16_t* tile, int ld, int row0, int col0, int lane) {
-    const int r = lane & 15, nblk = (lane >> 4) & 1, half = lane >> 5;
-    const uint16_t* p = tile + (row0 + 4 * half + (r >> 2)) * ld + col0 + 16 * nblk + 4 * (r & 3);
-    typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-    const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p)));
-    const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 8 * ld)));
-    return __builtin_bit_cast(bf16x8, u32x4{lo.x, lo.y, hi.x, hi.y});
-}
-// registers 8p .. 8p+7 of a D-layout block as an operand of the next product (k = its rows), head and remainder
-__device__ __forceinline__ void split_frag(const f32x16& x, int p, u32x4& hi, u32x4& lo) {
-    _Pragma("unroll") for (int e = 0; e < 4; ++e) {
-        const float x0 = x[8 * p + 2 * e], x1 = x[8 * p + 2 * e + 1];
-        hi[e] = pack2(x0, x1);
-        lo[e] = pack2(x0 - bf16_lo(hi[e]), x1 - bf16_hi(hi[e]));
-    }
-}
-// ... and such an operand to LDS by rows: lane = column, so neighbouring lanes exchange halves and store two columns at once.
-// dst: row 0, column 0 of the 16 rows and 32 columns
-__device__ __forceinline__ void store_frag_rows(uint16_t* dst, int ld, const u32x4& w, int n, int half) {
-    const bool odd = n & 1;
-    uint16_t* p = dst + (4 * half + (odd ? 1 : 0)) * ld + (n & ~1);
-    const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
-    _Pragma("unroll") for (int e = 0; e < 4; ++e) {
-        const uint32_t other = __builtin_amdgcn_mov_dpp(int(w[e]), 0xB1, 0xf, 0xf, true);  // lane ^ 1
-        *reinterpret_cast<uint32_t*>(p + (8 * (e >> 1) + 2 * (e & 1)) * ld) = __builtin_amdgcn_perm(other, w[e], sel);
-    }
-}
-// weights of the rows of registers 8p .. 8p+7 of a D-layout block at row0
-__device__ __forceinline__ void row_weights(const float* tab, int row0, int half, float (&w)[8]) {
-    const float4 a = *reinterpret_cast<const float4*>(tab + row0 + 4 * half), b = *reinterpret_cast<const float4*>(tab + row0 + 8 + 4 * half);
-    w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w; w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w;
-}
 
 // grid: (segments, seqs).  SUM: summary of a segment from a zero state (nothing stored but its end state).
 // A wave owns value columns [32 w, 32 w + 32) of dS, dU and W; the products that lead from one to the next take the block before
@@ -638,7 +633,8 @@ __global__ __launch_bounds__(kThreads, 1) void mk_delta_rwalk(Dims d, DeltaRevAr
         if (ein) walk_state_load(S, ein, false, wave, n, half);
     }
 
-    TileRegs rq, rk, ro, rt;
+    TileRegs rq, rk, ro;
+    u32x4 rt[3];
     float gval = 0.f, bval = 1.f, bwval = 1.f;
     auto gload = [&](int kk) {
         const ChunkPos p = walk_pos(d, walk, kend - 1 - min(kk, cnt - 1));
@@ -649,8 +645,7 @@ __global__ __launch_bounds__(kThreads, 1) void mk_delta_rwalk(Dims d, DeltaRevAr
         walk_gload<false, kThreads>(rq, a.q, p.tok0, p.ts, p.L, tid);
         walk_gload<false, kThreads>(ro, a.d_o, p.tok0, p.ts, p.L, tid);
         walk_gload<false, kThreads>(rk, a.k, p.tok0, p.ts, p.L, tid);
-        const uint16_t* gtt = a.tt + p.slot * 2 * C * C;
-        _Pragma("unroll") for (int it = 0; it < 4; ++it) rt.v[it] = *reinterpret_cast<const u32x4*>(gtt + 8 * (tid + kThreads * it));
+        _Pragma("unroll") for (int it = 0; it < 3; ++it) rt[it] = *reinterpret_cast<const u32x4*>(a.tt + p.slot * kDeltaT + 8 * (tid + kThreads * it));
     };
     if (cnt > 0) gload(0);
 
@@ -660,10 +655,7 @@ __global__ __launch_bounds__(kThreads, 1) void mk_delta_rwalk(Dims d, DeltaRevAr
         walk_commit<kThreads>(Q, rq, L, tid);
         walk_commit<kThreads>(dO, ro, L, tid);
         walk_commit<kThreads>(K, rk, L, tid);
-        _Pragma("unroll") for (int it = 0; it < 4; ++it) {
-            const int p = tid + kThreads * it, row = (p >> 3) & 63, piece = p & 7;
-            *reinterpret_cast<u32x4*>((p >> 9 ? TTl : TTh) + row * LDP + 8 * piece) = rt.v[it];
-        }
+        _Pragma("unroll") for (int it = 0; it < 3; ++it) *reinterpret_cast<u32x4*>(TTh + delta_t_place(tid + kThreads * it)) = rt[it];
         if (wave == 0) {
             float gam = 1.f;
             if (DEC) {

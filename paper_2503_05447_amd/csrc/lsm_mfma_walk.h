@@ -140,43 +140,6 @@ __device__ __forceinline__ void walk_inter(f32x16 (&O)[2], const f32x16 (&S)[4],
         }
     }
 }
-// two inter products against the same state with one conversion of its blocks: Oa^T = S^T A^T (unscaled), Ob^T = e^{beta} S^T B^T
-template <bool DEC, bool WANT_B>
-__device__ __forceinline__ void walk_inter_pair(f32x16 (&Oa)[2], f32x16 (&Ob)[2], const f32x16 (&S)[4], const uint16_t* A, const uint16_t* B,
-                                                const float* bs, int n, int half) {
-    _Pragma("unroll") for (int jb = 0; jb < 2; ++jb) {
-        Oa[jb] = f32x16{0};
-        Ob[jb] = f32x16{0};
-    }
-    _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
-        _Pragma("unroll") for (int p = 0; p < 2; ++p) {
-            u32x4 hi, lo;
-            _Pragma("unroll") for (int e = 0; e < 4; ++e) {
-                const float x0 = S[ib][8 * p + 2 * e], x1 = S[ib][8 * p + 2 * e + 1];
-                hi[e] = pack2(x0, x1);
-                lo[e] = pack2(x0 - bf16_lo(hi[e]), x1 - bf16_hi(hi[e]));
-            }
-            const bf16x8 sh = __builtin_bit_cast(bf16x8, hi), sl = __builtin_bit_cast(bf16x8, lo);
-            const bf16x8 a0 = frag_perm(A, LD, n, 32 * ib + 16 * p, half), a1 = frag_perm(A, LD, 32 + n, 32 * ib + 16 * p, half);
-            Oa[0] = mfma(sh, a0, Oa[0]);
-            Oa[1] = mfma(sh, a1, Oa[1]);
-            Oa[0] = mfma(sl, a0, Oa[0]);
-            Oa[1] = mfma(sl, a1, Oa[1]);
-            if (WANT_B) {
-                const bf16x8 b0 = frag_perm(B, LD, n, 32 * ib + 16 * p, half), b1 = frag_perm(B, LD, 32 + n, 32 * ib + 16 * p, half);
-                Ob[0] = mfma(sh, b0, Ob[0]);
-                Ob[1] = mfma(sh, b1, Ob[1]);
-                Ob[0] = mfma(sl, b0, Ob[0]);
-                Ob[1] = mfma(sl, b1, Ob[1]);
-            }
-        }
-    if (DEC && WANT_B) {
-        _Pragma("unroll") for (int jb = 0; jb < 2; ++jb) {
-            const float w = __expf(bs[32 * jb + n]);
-            _Pragma("unroll") for (int x = 0; x < 16; ++x) Ob[jb][x] *= w;
-        }
-    }
-}
 // scores: each of the three 32 x 32 blocks on or below the diagonal by one wave (w4 = 0: (0,0), 1: (1,0),
 // 2: (1,1)), mask and decay on its accumulators, handed to the others through LDS as head + remainder
 template <bool DEC>
@@ -235,38 +198,6 @@ __device__ __forceinline__ void walk_update(f32x16 (&S)[4], const uint16_t* K, c
         }
     }
 }
-// the same state update with the values in two planes (head + remainder; the pseudo-values of the delta rule), the
-// weighted slice split again into head + remainder in registers
-template <bool DEC, bool SCALE>
-__device__ __forceinline__ void walk_update_vsplit(f32x16 (&S)[4], const uint16_t* K, const uint16_t* Vh, const uint16_t* Vl,
-                                             const float* wo, float bC, int w4, int lane, int half) {
-    if (DEC && SCALE) {
-        const float lam = __expf(bC);
-        _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
-            _Pragma("unroll") for (int x = 0; x < 16; ++x) S[ib][x] *= lam;
-    }
-    _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
-        const u32x4 rh = __builtin_bit_cast(u32x4, frag_tr(Vh, LD, 16 * ks, 32 * w4, lane));
-        const u32x4 rl = __builtin_bit_cast(u32x4, frag_tr(Vl, LD, 16 * ks, 32 * w4, lane));
-        u32x4 hi = rh, lo = rl;
-        if (DEC) {
-            const float4 w0 = *reinterpret_cast<const float4*>(wo + 16 * ks + 8 * half);
-            const float4 w1 = *reinterpret_cast<const float4*>(wo + 16 * ks + 8 * half + 4);
-            const float w[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-            _Pragma("unroll") for (int p = 0; p < 4; ++p) {
-                const float x0 = (bf16_lo(rh[p]) + bf16_lo(rl[p])) * w[2 * p], x1 = (bf16_hi(rh[p]) + bf16_hi(rl[p])) * w[2 * p + 1];
-                hi[p] = pack2(x0, x1);
-                lo[p] = pack2(x0 - bf16_lo(hi[p]), x1 - bf16_hi(hi[p]));
-            }
-        }
-        const bf16x8 vh = __builtin_bit_cast(bf16x8, hi), vl = __builtin_bit_cast(bf16x8, lo);
-        bf16x8 ka[4];
-        _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) ka[ib] = frag_tr(K, LD, 16 * ks, 32 * ib, lane);
-        _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) S[ib] = mfma(ka[ib], vh, S[ib]);
-        _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) S[ib] = mfma(ka[ib], vl, S[ib]);
-    }
-}
-
 // chunk-local decay tables by one wave: beta (inclusive running sum of the log-decays in walk order, exclusive
 // when walking backward), b_C, and the weights wo = e^{b_C - beta + extra} of the state update
 template <bool REV>
