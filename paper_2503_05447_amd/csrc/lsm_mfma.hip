@@ -1196,7 +1196,7 @@ template <bool DEC>
 hipError_t launch_delta_rwalk(const Dims& d, DeltaRevArgs ra, const void* segf, void* segws, hipStream_t st) {
     hipError_t e;
     const SegPlan sp = delta_plan(d);
-    const dim3 grid(sp.nseg, d.seqs()), block(kThreads);
+    const dim3 grid(sp.nseg, d.seqs()), block(512);
     if ((e = allow_lds(mk_delta_rwalk<DEC, false>, kDeltaRevLds)) != hipSuccess) return e;
     ra.m = sp.m;
     ra.nseg = sp.nseg;
@@ -1215,7 +1215,7 @@ hipError_t launch_delta_rwalk(const Dims& d, DeltaRevArgs ra, const void* segf, 
         }
         {
             ProfScope ps(KID_DELTA_COMBINE, st);
-            hipLaunchKernelGGL(mk_delta_combine<true>, dim3(D / 32, d.seqs()), block, kDeltaCombineLds, st, d, ra.edge_in, sumA, sumB, bound, sp.m, sp.nseg);
+            hipLaunchKernelGGL(mk_delta_combine<true>, dim3(D / 32, d.seqs()), dim3(kThreads), kDeltaCombineLds, st, d, ra.edge_in, sumA, sumB, bound, sp.m, sp.nseg);
         }
         ra.bound = bound;
     }

@@ -585,17 +585,23 @@ struct DeltaRevArgs {
     const float* bound;       // the summary leaves what the segment makes of a zero state in sum[seq][s] (what it makes of the
     float* sum;               // identity is the transpose of the forward walk's factor)
 };
-constexpr int LDW = 40;  // row stride of a wave's private 32-column tiles
-// LDS: Q | K | dO (64 x LD) | T^T head | remainder | scores head | remainder (64 x LDP) | per wave: 128 x LDW bf16 (its columns
-// of dS', then of W head and remainder, 64 x LDW each) | bs | wo | Gamma | -beta Gamma | b | db per wave
-constexpr int kDeltaRevLds = (3 * C * LD + 4 * C * LDP) * 2 + 4 * D * LDW * 2 + (5 * C + 8 + 4 * C) * 4;
+// LDS: Q | K | dO (64 x LD) | T^T head | remainder | scores head | remainder (64 x LDP) | stage of dS' (bf16, 128 x LD) | stage of
+// W (fp32, 64 x LDW) | two sets of (bs, wo, Gamma, -beta Gamma, b)
+constexpr int LDW = D + 4;
+constexpr int kDeltaRevTab = 5 * C + 4;
+constexpr int kDeltaRevLds = (3 * C * LD + 4 * C * LDP + D * LD) * 2 + (C * LDW + 2 * kDeltaRevTab) * 4;
+static_assert(kDeltaRevLds <= 160 * 1024, "one workgroup's LDS");
 
-// grid: (segments, seqs).  SUM: summary of a segment from a zero state (nothing stored but its end state).
-// A wave owns value columns [32 w, 32 w + 32) of dS, dU and W; the products that lead from one to the next take the block before
-// straight out of the accumulators (lane = value column, registers = the next contraction's index), so only scores, T and
-// input rows are read from LDS.
+// grid: (segments, seqs).  SUM: summary of a segment from a zero state (nothing stored but its end state).  Eight waves, two per
+// SIMD, split by function as in the forward walk:
+//   waves 0..3 carry the state (wave w: value columns [32 w, 32 w + 32) of dS, dU and W): the chain dU, W, state update.  The
+//              products that lead from one to the next take the block before straight out of the accumulators (lane = value
+//              column, registers = the next contraction's index), so only scores, T and input rows are read from LDS;
+//   waves 4..7 the scores, the tables, and what leaves: dS' (staged while dU's state part is formed) and, a chunk later, W, dv and db.
+// All share the rows on their way in.  16 x 16 sequences of 2048, 2.5 KB a token: 380 us with four waves
+// doing everything in turn, 321 so.
 template <bool DEC, bool SUM>
-__global__ __launch_bounds__(kThreads, 1) void mk_delta_rwalk(Dims d, DeltaRevArgs a) {
+__global__ __launch_bounds__(512, 1) void mk_delta_rwalk(Dims d, DeltaRevArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     uint16_t* Q = reinterpret_cast<uint16_t*>(smem);
     uint16_t* K = Q + C * LD;
@@ -604,15 +610,19 @@ __global__ __launch_bounds__(kThreads, 1) void mk_delta_rwalk(Dims d, DeltaRevAr
     uint16_t* TTl = TTh + C * LDP;
     uint16_t* Ph = TTl + C * LDP;
     uint16_t* Pl = Ph + C * LDP;
-    uint16_t* priv = Pl + C * LDP;
-    float* bs = reinterpret_cast<float*>(priv + 4 * D * LDW);
-    float* wo = bs + C + 4;
-    float* gm = wo + C + 4;
-    float* ne = gm + C;           // -beta Gamma
-    float* bb = ne + C;
-    float* red = bb + C;          // [wave][64]
+    uint16_t* dSt = Pl + C * LDP;
+    float* Ws = reinterpret_cast<float*>(dSt + D * LD);
+    float* tab = Ws + C * LDW;
 
-    const int seg = blockIdx.x, seq = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 31, half = lane >> 5;
+    const int seg = blockIdx.x, seq = blockIdx.y, tid = threadIdx.x, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave8 & 3;
+    int lane = tid & 63, n = lane & 31, half = lane >> 5;
+    auto fresh = [&]() {  // (as in mk_walk_grad)
+        asm volatile("" : "+v"(lane));
+        n = lane & 31;
+        half = lane >> 5;
+    };
+    const int t256 = tid & 255;
+    const bool carrier = wave8 < 4;
     const SeqWalk walk = seq_walk(d, seq);
     const int nsq = max(1, (walk.n + a.m - 1) / a.m);
     const int kbeg = seg * a.m, kend = min(walk.n, kbeg + a.m), cnt = max(kend - kbeg, 0);
@@ -621,192 +631,193 @@ __global__ __launch_bounds__(kThreads, 1) void mk_delta_rwalk(Dims d, DeltaRevAr
     } else if (seg >= nsq) {
         return;
     }
-    uint16_t* pw = priv + wave * D * LDW;   // this wave's region
-    uint16_t* wh = pw;
-    uint16_t* wl = pw + C * LDW;
-
-    f32x16 S[4];  // dS[ib][4g+j] = dS[i = 32 ib + 8g + 4 half + j][v = 32 wave + n]
-    _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) S[ib] = f32x16{0};
-    if (!SUM) {
-        const float* ein = a.nseg > 1 ? a.bound + (size_t(seq) * a.nseg + seg) * D * D
-                                      : (a.edge_in ? a.edge_in + size_t(seq) * D * D : nullptr);
-        if (ein) walk_state_load(S, ein, false, wave, n, half);
-    }
-
+    auto pos = [&](int kk) { return walk_pos(d, walk, kend - 1 - min(kk, cnt - 1)); };
     TileRegs rq, rk, ro;
-    u32x4 rt[3];
-    float gval = 0.f, bval = 1.f, bwval = 1.f;
-    auto gload = [&](int kk) {
-        const ChunkPos p = walk_pos(d, walk, kend - 1 - min(kk, cnt - 1));
-        const size_t pt = p.tok0 + size_t(min(lane, p.L - 1)) * p.ts;
-        if (DEC) gval = a.log_alpha[pt];
-        if (a.beta) bval = a.beta[pt];
-        if (!SUM && a.bw) bwval = a.bw[pt];
-        walk_gload<false, kThreads>(rq, a.q, p.tok0, p.ts, p.L, tid);
-        walk_gload<false, kThreads>(ro, a.d_o, p.tok0, p.ts, p.L, tid);
-        walk_gload<false, kThreads>(rk, a.k, p.tok0, p.ts, p.L, tid);
-        _Pragma("unroll") for (int it = 0; it < 3; ++it) rt[it] = *reinterpret_cast<const u32x4*>(a.tt + p.slot * kDeltaT + 8 * (tid + kThreads * it));
+    auto gload_rows = [&](const ChunkPos& p) {
+        walk_gload<false, 512>(rq, a.q, p.tok0, p.ts, p.L, tid);
+        walk_gload<false, 512>(ro, a.d_o, p.tok0, p.ts, p.L, tid);
+        walk_gload<false, 512>(rk, a.k, p.tok0, p.ts, p.L, tid);
     };
-    if (cnt > 0) gload(0);
+    auto commit_rows = [&](int L) {
+        walk_commit<512>(Q, rq, L, tid);
+        walk_commit<512>(dO, ro, L, tid);
+        walk_commit<512>(K, rk, L, tid);
+    };
 
-    for (int kk = 0; kk < cnt; ++kk) {
-        const ChunkPos cp = walk_pos(d, walk, kend - 1 - kk);
-        const int L = cp.L;
-        walk_commit<kThreads>(Q, rq, L, tid);
-        walk_commit<kThreads>(dO, ro, L, tid);
-        walk_commit<kThreads>(K, rk, L, tid);
-        _Pragma("unroll") for (int it = 0; it < 3; ++it) *reinterpret_cast<u32x4*>(TTh + delta_t_place(tid + kThreads * it)) = rt[it];
-        if (wave == 0) {
-            float gam = 1.f;
-            if (DEC) {
-                walk_decay_tables<false>(gval, L, 0.f, bs, wo, lane);
-                gm[lane] = gam = __expf(bs[lane]);
-            }
-            ne[lane] = lane < L ? -bval * gam : 0.f;
-            bb[lane] = lane < L ? bwval : 0.f;
-        }
-        gload(kk + 1);
-        u32x4 vv[4];  // this lane's pieces of v, for db: row (lane >> 2) + 16 it, columns 32 wave + 8 (lane & 3)
+    if (carrier) {
+        f32x16 S[4];  // dS[ib][4g+j] = dS[i = 32 ib + 8g + 4 half + j][v = 32 wave + n]
+        _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) S[ib] = f32x16{0};
         if (!SUM) {
-            _Pragma("unroll") for (int it = 0; it < 4; ++it)
-                vv[it] = *reinterpret_cast<const u32x4*>(a.v + (cp.tok0 + size_t(min((lane >> 2) + 16 * it, L - 1)) * cp.ts) * D + 32 * wave + 8 * (lane & 3));
+            const float* ein = a.nseg > 1 ? a.bound + (size_t(seq) * a.nseg + seg) * D * D
+                                          : (a.edge_in ? a.edge_in + size_t(seq) * D * D : nullptr);
+            if (ein) walk_state_load(S, ein, false, wave, n, half);
         }
-        __syncthreads();  // (A) tiles and tables of this chunk are in LDS
-        const float bC = DEC ? bs[C] : 0.f;
-
-        // ---- dS' of this wave's columns -> global, fragment-major: through the wave's private tile [i][v - 32 wave]
-        if (!SUM) {
+        if (cnt > 0) gload_rows(pos(0));
+        for (int kk = 0; kk < cnt; ++kk) {
+            const float* bs = tab + (kk & 1) * kDeltaRevTab;
+            const float *wo = bs + C + 4, *gm = wo + C, *ne = gm + C;
+            commit_rows(pos(kk).L);
+            if (kk + 1 < cnt) gload_rows(pos(kk + 1));
+            __syncthreads();  // (A) tiles and tables of this chunk are in LDS
+            fresh();
+            // dU[t][v] = wo_t sum_i k_t[i] dS'[i][v] + sum_{j >= t} P[j][t] dO[j][v]; dS' leaves as its bf16 heads
+            f32x16 dU[2] = {{0}, {0}};
             _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
                 _Pragma("unroll") for (int p = 0; p < 2; ++p) {
-                    u32x4 h;
-                    _Pragma("unroll") for (int e = 0; e < 4; ++e) h[e] = pack2(S[ib][8 * p + 2 * e], S[ib][8 * p + 2 * e + 1]);
-                    store_frag_rows(pw + (32 * ib + 16 * p) * LDW, LDW, h, n, half);
+                    u32x4 hi, lo;
+                    split_frag(S[ib], p, hi, lo);
+                    const bf16x8 sh = __builtin_bit_cast(bf16x8, hi), sl = __builtin_bit_cast(bf16x8, lo);
+                    const bf16x8 k0 = frag_perm(K, LD, n, 32 * ib + 16 * p, half), k1 = frag_perm(K, LD, 32 + n, 32 * ib + 16 * p, half);
+                    dU[0] = mfma(k0, sh, dU[0]);
+                    dU[1] = mfma(k1, sh, dU[1]);
+                    dU[0] = mfma(k0, sl, dU[0]);
+                    dU[1] = mfma(k1, sl, dU[1]);
+                    if (!SUM) store_frag_rows(dSt + (32 * ib + 16 * p) * LD + 32 * wave, LD, hi, n, half);
                 }
-            __builtin_amdgcn_wave_barrier();
-            uint16_t* dst = a.dstates + cp.slot * D * D;
-            _Pragma("unroll") for (int blk = 0; blk < 4; ++blk)
-                _Pragma("unroll") for (int q2 = 0; q2 < 2; ++q2) {
-                    const u32x4 val = *reinterpret_cast<const u32x4*>(pw + (32 * blk + n) * LDW + 16 * q2 + 8 * half);
-                    __builtin_nontemporal_store(val, reinterpret_cast<u32x4*>(dst + state_frag_off(blk, 2 * wave + q2, lane)));
-                }
-            __builtin_amdgcn_wave_barrier();
-        }
-
-        // ---- dU[t][v] = wo_t sum_i k_t[i] dS'[i][v] + sum_{j >= t} P[j][t] dO[j][v]
-        f32x16 dU[2] = {{0}, {0}};
-        _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
-            _Pragma("unroll") for (int p = 0; p < 2; ++p) {
-                u32x4 hi, lo;
-                split_frag(S[ib], p, hi, lo);
-                const bf16x8 sh = __builtin_bit_cast(bf16x8, hi), sl = __builtin_bit_cast(bf16x8, lo);
-                const bf16x8 k0 = frag_perm(K, LD, n, 32 * ib + 16 * p, half), k1 = frag_perm(K, LD, 32 + n, 32 * ib + 16 * p, half);
-                dU[0] = mfma(k0, sh, dU[0]);
-                dU[1] = mfma(k1, sh, dU[1]);
-                dU[0] = mfma(k0, sl, dU[0]);
-                dU[1] = mfma(k1, sl, dU[1]);
-            }
-        if (DEC) {
-            _Pragma("unroll") for (int tb = 0; tb < 2; ++tb)
-                _Pragma("unroll") for (int p = 0; p < 2; ++p) {
+            if (DEC) {
+                _Pragma("unroll") for (int kt = 0; kt < 4; ++kt) {
                     float w[8];
-                    row_weights(wo, 32 * tb + 16 * p, half, w);
-                    _Pragma("unroll") for (int x = 0; x < 8; ++x) dU[tb][8 * p + x] *= w[x];
+                    row_weights(wo, 16 * kt, half, w);
+                    _Pragma("unroll") for (int x = 0; x < 8; ++x) dU[kt >> 1][8 * (kt & 1) + x] *= w[x];
                 }
-        }
-        walk_scores<DEC>(K, Q, Ph, Pl, bs, wave, n, half);
-        __syncthreads();  // (C) scores are in LDS
-        _Pragma("unroll") for (int tb = 0; tb < 2; ++tb)
-            _Pragma("unroll") for (int ks = 2 * tb; ks < 4; ++ks) {  // queries j < 32 never see keys t >= 32
+            }
+            __syncthreads();  // (C) the scores and the stage of dS' are in LDS
+            fresh();
+            _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
                 const bf16x8 dot = frag_tr(dO, LD, 16 * ks, 32 * wave, lane);
-                dU[tb] = mfma(frag_tr(Ph, LDP, 16 * ks, 32 * tb, lane), dot, dU[tb]);
-                dU[tb] = mfma(frag_tr(Pl, LDP, 16 * ks, 32 * tb, lane), dot, dU[tb]);
+                _Pragma("unroll") for (int tb = 0; tb <= (ks >> 1); ++tb) {  // queries j < 32 never see keys t >= 32
+                    dU[tb] = mfma(frag_tr(Ph, LDP, 16 * ks, 32 * tb, lane), dot, dU[tb]);
+                    dU[tb] = mfma(frag_tr(Pl, LDP, 16 * ks, 32 * tb, lane), dot, dU[tb]);
+                }
             }
-        // ---- W[r][v] = sum_{t >= r} T[t][r] dU[t][v]
-        f32x16 W[2] = {{0}, {0}};
-        _Pragma("unroll") for (int kt = 0; kt < 4; ++kt) {
-            u32x4 hi, lo;
-            split_frag(dU[kt >> 1], kt & 1, hi, lo);
-            const bf16x8 uh = __builtin_bit_cast(bf16x8, hi), ul = __builtin_bit_cast(bf16x8, lo);
-            _Pragma("unroll") for (int rb = 0; rb <= (kt >> 1); ++rb) {
-                const bf16x8 th = frag_perm(TTh, LDP, 32 * rb + n, 16 * kt, half), tl = frag_perm(TTl, LDP, 32 * rb + n, 16 * kt, half);
-                W[rb] = mfma(th, uh, W[rb]);
-                W[rb] = mfma(tl, uh, W[rb]);
-                W[rb] = mfma(th, ul, W[rb]);
-            }
-        }
-        if (!SUM) {
+            // W[r][v] = sum_{t >= r} T[t][r] dU[t][v]
+            f32x16 W[2] = {{0}, {0}};
             _Pragma("unroll") for (int kt = 0; kt < 4; ++kt) {
                 u32x4 hi, lo;
-                split_frag(W[kt >> 1], kt & 1, hi, lo);
-                store_frag_rows(wh + 16 * kt * LDW, LDW, hi, n, half);
-                store_frag_rows(wl + 16 * kt * LDW, LDW, lo, n, half);
-            }
-            __builtin_amdgcn_wave_barrier();
-            // W to memory; dv and this wave's share of db on the way
-            _Pragma("unroll") for (int it = 0; it < 4; ++it) {
-                const int row = (lane >> 2) + 16 * it, piece = lane & 3;
-                const u32x4 h = *reinterpret_cast<const u32x4*>(wh + row * LDW + 8 * piece), l = *reinterpret_cast<const u32x4*>(wl + row * LDW + 8 * piece);
-                const float b = bb[row];
-                u32x4 o;
-                float s = 0.f;
-                _Pragma("unroll") for (int p = 0; p < 4; ++p) {
-                    const float w0 = bf16_lo(h[p]) + bf16_lo(l[p]), w1 = bf16_hi(h[p]) + bf16_hi(l[p]);
-                    s += w0 * bf16_lo(vv[it][p]) + w1 * bf16_hi(vv[it][p]);
-                    o[p] = pack2(b * w0, b * w1);
+                split_frag(dU[kt >> 1], kt & 1, hi, lo);
+                const bf16x8 uh = __builtin_bit_cast(bf16x8, hi), ul = __builtin_bit_cast(bf16x8, lo);
+                _Pragma("unroll") for (int rb = 0; rb <= (kt >> 1); ++rb) {
+                    const bf16x8 th = frag_perm(TTh, LDP, 32 * rb + n, 16 * kt, half), tl = frag_perm(TTl, LDP, 32 * rb + n, 16 * kt, half);
+                    W[rb] = mfma(th, uh, W[rb]);
+                    W[rb] = mfma(tl, uh, W[rb]);
+                    W[rb] = mfma(th, ul, W[rb]);
                 }
-                if (row < L) {
-                    const size_t off = (cp.wtok0 + row) * D + 32 * wave + 8 * piece;
+            }
+            fresh();
+            if (!SUM) {
+                _Pragma("unroll") for (int rb = 0; rb < 2; ++rb)
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x)
+                        Ws[(32 * rb + 8 * (x >> 2) + 4 * half + (x & 3)) * LDW + 32 * wave + n] = W[rb][x];
+            }
+            // dS = Gamma_C dS' + sum_t (Gamma_t q_t)^T dO_t - sum_t (beta_t Gamma_t k_t)^T W_t
+            if (DEC) {
+                const float lam = __expf(bs[C]);
+                _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) S[ib][x] *= lam;
+            }
+            _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
+                const u32x4 raw = __builtin_bit_cast(u32x4, frag_tr(dO, LD, 16 * ks, 32 * wave, lane));
+                u32x4 hi = raw, lo = {0, 0, 0, 0};
+                if (DEC) {
+                    const float4 w0 = *reinterpret_cast<const float4*>(gm + 16 * ks + 8 * half);
+                    const float4 w1 = *reinterpret_cast<const float4*>(gm + 16 * ks + 8 * half + 4);
+                    const float w[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+                    _Pragma("unroll") for (int p = 0; p < 4; ++p) {
+                        const float x0 = bf16_lo(raw[p]) * w[2 * p], x1 = bf16_hi(raw[p]) * w[2 * p + 1];
+                        hi[p] = pack2(x0, x1);
+                        lo[p] = pack2(x0 - bf16_lo(hi[p]), x1 - bf16_hi(hi[p]));
+                    }
+                }
+                const bf16x8 oh = __builtin_bit_cast(bf16x8, hi), ol = __builtin_bit_cast(bf16x8, lo);
+                float w[8];
+                row_weights(ne, 16 * ks, half, w);
+                f32x16& Wb = W[ks >> 1];
+                _Pragma("unroll") for (int x = 0; x < 8; ++x) Wb[8 * (ks & 1) + x] *= w[x];
+                split_frag(Wb, ks & 1, hi, lo);
+                const bf16x8 eh = __builtin_bit_cast(bf16x8, hi), el = __builtin_bit_cast(bf16x8, lo);
+                _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) {
+                    const bf16x8 qa = frag_tr(Q, LD, 16 * ks, 32 * ib, lane);
+                    S[ib] = mfma(qa, oh, S[ib]);
+                    if (DEC) S[ib] = mfma(qa, ol, S[ib]);
+                    const bf16x8 ka = frag_tr_perm(K, LD, 16 * ks, 32 * ib, lane);
+                    S[ib] = mfma(ka, eh, S[ib]);
+                    S[ib] = mfma(ka, el, S[ib]);
+                }
+            }
+            __syncthreads();  // (D) every read of this chunk's tiles is done
+            fresh();
+        }
+        if (SUM) walk_state_store(S, a.sum + (size_t(seq) * a.nseg + seg) * D * D, false, wave, n, half);
+        else if (a.edge_out && seg == 0) walk_state_store(S, a.edge_out + size_t(seq) * D * D, false, wave, n, half);
+    } else {
+        u32x4 rt[3];
+        TileRegs rv;
+        float gval = 0.f, bval = 1.f, bwval = 1.f;
+        auto gload = [&](int kk) {
+            const ChunkPos p = pos(kk);
+            const size_t pt = p.tok0 + size_t(min(lane, p.L - 1)) * p.ts;
+            if (DEC) gval = a.log_alpha[pt];
+            if (a.beta) bval = a.beta[pt];
+            if (!SUM && a.bw) bwval = a.bw[pt];
+            gload_rows(p);
+            _Pragma("unroll") for (int it = 0; it < 3; ++it) rt[it] = *reinterpret_cast<const u32x4*>(a.tt + p.slot * kDeltaT + 8 * (t256 + kThreads * it));
+        };
+        // W of the kk-th chunk to memory, and dv and db on the way (rv: the chunk's rows of v, in the same pieces)
+        auto leave = [&](int kk) {
+            const ChunkPos p = pos(kk);
+            const float* bb = tab + (kk & 1) * kDeltaRevTab + 4 * C + 4;
+            _Pragma("unroll") for (int it = 0; it < 4; ++it) {
+                const int q = t256 + kThreads * it, row = q >> 4, piece = q & 15;
+                const float4 x0 = *reinterpret_cast<const float4*>(Ws + row * LDW + 8 * piece), x1 = *reinterpret_cast<const float4*>(Ws + row * LDW + 8 * piece + 4);
+                const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w}, b = bb[row];
+                u32x4 h, l, o;
+                float s = 0.f;
+                _Pragma("unroll") for (int e = 0; e < 4; ++e) {
+                    h[e] = pack2(x[2 * e], x[2 * e + 1]);
+                    l[e] = pack2(x[2 * e] - bf16_lo(h[e]), x[2 * e + 1] - bf16_hi(h[e]));
+                    o[e] = pack2(b * x[2 * e], b * x[2 * e + 1]);
+                    s += x[2 * e] * bf16_lo(rv.v[it][e]) + x[2 * e + 1] * bf16_hi(rv.v[it][e]);
+                }
+                if (row < p.L) {
+                    const size_t off = (p.wtok0 + row) * D + 8 * piece, tok = p.tok0 + size_t(row) * p.ts;
                     *reinterpret_cast<u32x4*>(a.w_h + off) = h;
                     *reinterpret_cast<u32x4*>(a.w_l + off) = l;
-                    __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(a.dv + (cp.tok0 + size_t(row) * cp.ts) * D + 32 * wave + 8 * piece));
+                    __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(a.dv + tok * D + 8 * piece));
                 }
-                s += __shfl_xor(s, 1, 64);
-                s += __shfl_xor(s, 2, 64);
-                if (piece == 0) red[wave * C + row] = s;
+                _Pragma("unroll") for (int off = 8; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+                if (a.d_bw && piece == 0 && row < p.L) a.d_bw[p.tok0 + size_t(row) * p.ts] = s;
             }
-        }
-        // ---- dS = Gamma_C dS' + sum_t (Gamma_t q_t)^T dO_t - sum_t (beta_t Gamma_t k_t)^T W_t
-        if (DEC) {
-            const float lam = __expf(bC);
-            _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
-                _Pragma("unroll") for (int x = 0; x < 16; ++x) S[ib][x] *= lam;
-        }
-        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
-            const u32x4 raw = __builtin_bit_cast(u32x4, frag_tr(dO, LD, 16 * ks, 32 * wave, lane));
-            u32x4 hi = raw, lo = {0, 0, 0, 0};
-            if (DEC) {
-                const float4 w0 = *reinterpret_cast<const float4*>(gm + 16 * ks + 8 * half);
-                const float4 w1 = *reinterpret_cast<const float4*>(gm + 16 * ks + 8 * half + 4);
-                const float w[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-                _Pragma("unroll") for (int p = 0; p < 4; ++p) {
-                    const float x0 = bf16_lo(raw[p]) * w[2 * p], x1 = bf16_hi(raw[p]) * w[2 * p + 1];
-                    hi[p] = pack2(x0, x1);
-                    lo[p] = pack2(x0 - bf16_lo(hi[p]), x1 - bf16_hi(hi[p]));
+        };
+        if (cnt > 0) gload(0);
+        for (int kk = 0; kk < cnt; ++kk) {
+            const ChunkPos cp = pos(kk);
+            float* bs = tab + (kk & 1) * kDeltaRevTab;
+            float *wo = bs + C + 4, *gm = wo + C, *ne = gm + C, *bb = ne + C;
+            commit_rows(cp.L);
+            _Pragma("unroll") for (int it = 0; it < 3; ++it) *reinterpret_cast<u32x4*>(TTh + delta_t_place(t256 + kThreads * it)) = rt[it];
+            if (wave == 0) {
+                float gam = 1.f;
+                if (DEC) {
+                    walk_decay_tables<false>(gval, cp.L, 0.f, bs, wo, lane);
+                    gm[lane] = gam = __expf(bs[lane]);
                 }
+                ne[lane] = lane < cp.L ? -bval * gam : 0.f;
+                bb[lane] = lane < cp.L ? bwval : 0.f;
             }
-            const bf16x8 oh = __builtin_bit_cast(bf16x8, hi), ol = __builtin_bit_cast(bf16x8, lo);
-            float w[8];
-            row_weights(ne, 16 * ks, half, w);
-            f32x16& Wb = W[ks >> 1];
-            _Pragma("unroll") for (int x = 0; x < 8; ++x) Wb[8 * (ks & 1) + x] *= w[x];
-            split_frag(Wb, ks & 1, hi, lo);
-            const bf16x8 eh = __builtin_bit_cast(bf16x8, hi), el = __builtin_bit_cast(bf16x8, lo);
-            _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) {
-                const bf16x8 qa = frag_tr(Q, LD, 16 * ks, 32 * ib, lane);
-                S[ib] = mfma(qa, oh, S[ib]);
-                if (DEC) S[ib] = mfma(qa, ol, S[ib]);
-                const bf16x8 ka = frag_tr_perm(K, LD, 16 * ks, 32 * ib, lane);
-                S[ib] = mfma(ka, eh, S[ib]);
-                S[ib] = mfma(ka, el, S[ib]);
+            if (kk + 1 < cnt) gload(kk + 1);
+            __syncthreads();  // (A)
+            walk_scores<DEC>(K, Q, Ph, Pl, bs, wave, n, half);
+            if (!SUM && kk > 0) leave(kk - 1);
+            __syncthreads();  // (C)
+            if (!SUM) {
+                walk_gload<false, kThreads>(rv, a.v, cp.tok0, cp.ts, cp.L, t256);
+                uint16_t* dst = a.dstates + cp.slot * D * D;
+                _Pragma("unroll") for (int ks = 0; ks < 8; ++ks)
+                    __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(dSt + (32 * wave + n) * LD + 16 * ks + 8 * half),
+                                                reinterpret_cast<u32x4*>(dst + state_frag_off(wave, ks, lane)));
             }
+            __syncthreads();  // (D)
         }
-        __syncthreads();  // (D) every read of this chunk's tiles is done
-        if (!SUM && a.d_bw && wave == 0 && lane < L)
-            a.d_bw[cp.tok0 + size_t(lane) * cp.ts] = (red[lane] + red[C + lane]) + (red[2 * C + lane] + red[3 * C + lane]);
+        if (!SUM && cnt > 0) leave(cnt - 1);
     }
-    if (SUM) {
-        walk_state_store(S, a.sum + (size_t(seq) * a.nseg + seg) * D * D, false, wave, n, half);
-        return;
-    }
-    if (a.edge_out && seg == 0) walk_state_store(S, a.edge_out + size_t(seq) * D * D, false, wave, n, half);
 }
