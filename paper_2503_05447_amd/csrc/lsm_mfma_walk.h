@@ -379,17 +379,26 @@ struct GradArgs {
 // The area of As holds beta H; that of the dS rows the two planes of W, then beta X (fp32), which the group that has the rest
 // of dk adds before the one rounding.  d beta takes the score part as row sums of H * (K K^T), unscaled (beta may be 0).
 // A segment is one of the reverse walk's, entry states from the forward walk's chain of segments.
-constexpr int LDX = D + 4;  // floats per row of the stage of beta X
+constexpr int LDX = 34;  // floats per row of a wave's 64 x 32 part of the stage of beta X
 constexpr int kWalkGradSplitExtra = C * LD * 2 + (C + 3 * 32 + 4 * C) * 4;  // second value tile | beta | row sums | k . X per wave
 __host__ __device__ constexpr int walk_grad_lds(bool vsplit) { return kWalkGradLds + (vsplit ? kWalkGradSplitExtra : 0); }
-static_assert(walk_grad_lds(true) <= 160 * 1024 && C * LDX * 4 <= 2 * C * LD * 2, "LDS; the stage of beta X fits the planes of W");
+static_assert(walk_grad_lds(true) <= 160 * 1024 && C * LDX * 4 <= 32 * LD * 2, "LDS; a wave's beta X fits half of a plane of W");
+// a D-layout block whose lanes are tokens (tok, and its row of 128 elements) to memory as bf16, 16 bytes a lane: the halves of a
+// wave exchange theirs as in state_store_direct
+__device__ __forceinline__ void store_tokens_direct(uint16_t* row, bool ok, int wave, int half, const f32x16& x) {
+    const PackedBlock p = pack_block(x);
+    _Pragma("unroll") for (int q = 0; q < 2; ++q) {
+        const auto s0 = __builtin_amdgcn_permlane32_swap(p.v[2 * q].x, p.v[2 * q + 1].x, false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(p.v[2 * q].y, p.v[2 * q + 1].y, false, false);
+        if (ok) *reinterpret_cast<u32x4*>(row + 32 * wave + 16 * q + 8 * half) = u32x4{s0[0], s1[0], s0[1], s1[1]};
+    }
+}
 
-// inter product of the state with rows kept in two planes (head Qh, remainder Ql), the state blocks converted once:
-// O^T[i][t] = sum_v S[i][v] (Qh + Ql)[t][v], remainder x remainder left out
-__device__ __forceinline__ void walk_inter_split(f32x16 (&O)[2], const f32x16 (&S)[4], const uint16_t* Qh, const uint16_t* Ql, int n,
-                                                 int half) {
-    O[0] = f32x16{0};
-    O[1] = f32x16{0};
+// two inter products with one conversion of the state blocks: X^T[i][t] = sum_v S[i][v] (Wh + Wl)[t][v] (remainder x remainder
+// left out) and O^T[i][t] = sum_v S[i][v] Q[t][v]
+__device__ __forceinline__ void walk_inter_pair(f32x16 (&X)[2], f32x16 (&O)[2], const f32x16 (&S)[4], const uint16_t* Wh, const uint16_t* Wl,
+                                                const uint16_t* Q, int n, int half) {
+    _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) X[nb] = O[nb] = f32x16{0};
     _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
         _Pragma("unroll") for (int p = 0; p < 2; ++p) {
             u32x4 hi, lo;
@@ -399,15 +408,41 @@ __device__ __forceinline__ void walk_inter_split(f32x16 (&O)[2], const f32x16 (&
                 lo[e] = pack2(x0 - bf16_lo(hi[e]), x1 - bf16_hi(hi[e]));
             }
             const bf16x8 sh = __builtin_bit_cast(bf16x8, hi), sl = __builtin_bit_cast(bf16x8, lo);
-            const bf16x8 qh0 = frag_perm(Qh, LD, n, 32 * ib + 16 * p, half), qh1 = frag_perm(Qh, LD, 32 + n, 32 * ib + 16 * p, half);
-            const bf16x8 ql0 = frag_perm(Ql, LD, n, 32 * ib + 16 * p, half), ql1 = frag_perm(Ql, LD, 32 + n, 32 * ib + 16 * p, half);
-            O[0] = mfma(sh, qh0, O[0]);
-            O[1] = mfma(sh, qh1, O[1]);
-            O[0] = mfma(sl, qh0, O[0]);
-            O[1] = mfma(sl, qh1, O[1]);
-            O[0] = mfma(sh, ql0, O[0]);
-            O[1] = mfma(sh, ql1, O[1]);
+            _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
+                const bf16x8 wh = frag_perm(Wh, LD, 32 * nb + n, 32 * ib + 16 * p, half);
+                const bf16x8 wl = frag_perm(Wl, LD, 32 * nb + n, 32 * ib + 16 * p, half);
+                const bf16x8 q = frag_perm(Q, LD, 32 * nb + n, 32 * ib + 16 * p, half);
+                X[nb] = mfma(sh, wh, X[nb]);
+                O[nb] = mfma(sh, q, O[nb]);
+                X[nb] = mfma(sl, wh, X[nb]);
+                O[nb] = mfma(sl, q, O[nb]);
+                X[nb] = mfma(sh, wl, X[nb]);
+            }
         }
+}
+
+// score_block2 with rows in two planes: (A + A2)[m] . B[n], and with B2 (A + A2) . (B + B2) without remainder x remainder; the
+// remainders' products apart, so that the chains are short
+__device__ __forceinline__ f32x16 score_block_split(const uint16_t* Am, const uint16_t* Am2, int m0, const uint16_t* Bm, const uint16_t* Bm2,
+                                                    int n0, int n, int half) {
+    f32x16 acc = {0}, rem = {0};
+    _Pragma("unroll") for (int h4 = 0; h4 < 2; ++h4) {
+        bf16x8 a[4], a2[4], b[4], b2[4];
+        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
+            const int col = 16 * (4 * h4 + ks) + 8 * half;
+            a[ks] = frag(Am, LD, m0 + n, col);
+            b[ks] = frag(Bm, LD, n0 + n, col);
+            a2[ks] = frag(Am2, LD, m0 + n, col);
+            if (Bm2) b2[ks] = frag(Bm2, LD, n0 + n, col);
+        }
+        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
+            acc = mfma(a[ks], b[ks], acc);
+            rem = mfma(a2[ks], b[ks], rem);
+            if (Bm2) rem = mfma(a[ks], b2[ks], rem);
+        }
+    }
+    _Pragma("unroll") for (int x = 0; x < 16; ++x) acc[x] += rem[x];
+    return acc;
 }
 
 // Gradient walker kernel: eight waves, two per SIMD.  The work of a chunk is split by function, not by data, so that
@@ -416,14 +451,15 @@ __device__ __forceinline__ void walk_inter_split(f32x16 (&O)[2], const f32x16 (&
 //              part from G), <S, dS>, with VSPLIT X, and move the state on;
 //   waves 4..7 (wave w: the same i slice for dk, value features v in [32w, 32w+32) for dv) hold the dS rows of the chunk;
 //              they compute the score blocks (G, As), dk and dv.
-// Each group runs a loop of its own with the same four barriers per chunk, so a SIMD always has one wave of either
+// Each group runs a loop of its own with the same barriers per chunk, so a SIMD always has one wave of either
 // kind to issue from: the matrix, vector and LDS work of the two overlap instead of queueing behind one wave's waits.
 // Plain case: all 512 threads share the tile traffic (global -> registers -> LDS, stage -> global), and the carrier
 // waves read dS for <S, dS> at the (i, v) of their state registers from the LDS rows.
-// VSPLIT: the carrier waves' registers are full (state, dq, X), so the other group moves most of the tiles; the carrier
-// waves form the state part of X before barrier (2), then complete and park it, then dq, the state update and <S, dS> (dS by
-// loads of their own from the fragment-major array, which the other group has just pulled into L2: the LDS area of the
-// dS rows holds W), so that the accumulators of X and dq never coexist.
+// VSPLIT: the other group moves most of the tiles; the carrier waves form the state's part of X and dq with one conversion of the
+// state before barrier (2), then park beta X, complete dq, move the state on and take <S, dS> (dS by loads of their own from the
+// fragment-major array, which the other group has just pulled into L2: the LDS area of the dS rows holds W); the other group
+// forms the scores before (2) and all of dk, X's scores' share included, after it.  16 x 16 sequences of 2048, 2.8 KB a token: 514 us
+// with X completed by the carrier waves and one group moving all tiles but one, 470 so.
 constexpr int kGrad8Threads = 512;
 
 // WIDE: 0 the only pass; 1 the first of two value-slice passes (dq, dk to the partial planes); 2 the second
@@ -447,7 +483,9 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
     uint16_t* V2 = reinterpret_cast<uint16_t*>(smem + kWalkGradLds);  // VSPLIT only
     uint16_t* Wh = dSt;              // VSPLIT: 64 x LD each, over the dS rows
     uint16_t* Wl = dSt + C * LD;
-    float* Xs = reinterpret_cast<float*>(dSt);                          // ... and, once they are spent, beta X [64][LDX]
+    // ... and, once they are spent, beta X: a wave's [64][LDX] over the rows of W that the wave of the same index among the others
+    // writes next
+    float* Xs = reinterpret_cast<float*>(dSt) + (int(threadIdx.x >> 6) & 3) * (32 * LD / 2);
     float* be = reinterpret_cast<float*>(smem + kWalkGradLds + C * LD * 2);  // VSPLIT: beta [64]
     float* rowF = be + C;            // [block][32]: sum_r H_tr (k_t . k_r) over the block's keys
     float* redx = rowF + 3 * 32;     // [i slice][64]: k . X without the scores' share
@@ -481,51 +519,56 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
     const int kbeg = seg * a.m, kend = min(walk.n, kbeg + a.m), cnt = kend - kbeg;
     if (cnt <= 0) return;
 
-    // VSPLIT: the carrier group moves the head plane of W in, and d_o when it has no decay tables to keep (measured:
-    // with them it is the slower group already); the other group moves the other tiles in and the gradients out
-    constexpr bool kCarrierMovesDo = !DEC;
-    TileRegs tq, tk, tv, to, tv2, twh, twl;
+    // VSPLIT: the carrier group moves q, k and d_o in, the other group the planes of U and W; the gradients leave from the
+    // registers.  Requests are made after (2), under the products.  (One group moving all but a tile, between the chunks: 2300 clocks
+    // to issue, 2200 to commit, of 24500.)
+    // Wave w of the other group moves rows 32 (w % 2) .. + 31 of the head (w < 2) or remainder plane of W.
+    TileRegs tq, tk, tv, to, tv2;
+    u32x4 tw[8];
     auto gload_tiles = [&](const ChunkPos& p, bool first_group) {
-        if (!VSPLIT || !first_group) {
+        if (!VSPLIT || first_group) {
             walk_gload<false, NT>(tq, a.q, p.tok0, p.ts, p.L, tt);
             walk_gload<false, NT>(tk, a.k, p.tok0, p.ts, p.L, tt);
-            walk_gload<false, NT>(tv, a.v, p.vtok0, p.vts, p.L, tt);
         }
-        if (!VSPLIT || first_group == kCarrierMovesDo) walk_gload<false, NT>(to, a.d_o, p.vtok0, p.vts, p.L, tt);
-        if (VSPLIT && first_group) walk_gload<false, NT>(twh, a.w_h, p.wtok0, 1, p.L, tt);
+        if (!VSPLIT || !first_group) walk_gload<false, NT>(tv, a.v, p.vtok0, p.vts, p.L, tt);
+        if (!VSPLIT || first_group) walk_gload<false, NT>(to, a.d_o, p.vtok0, p.vts, p.L, tt);
         if (VSPLIT && !first_group) {
             walk_gload<false, NT>(tv2, a.v_lo, p.vtok0, p.vts, p.L, tt);
-            walk_gload<false, NT>(twl, a.w_l, p.wtok0, 1, p.L, tt);
+            const uint16_t* w = (wave < 2 ? a.w_h : a.w_l) + p.wtok0 * D;
+            _Pragma("unroll") for (int it = 0; it < 8; ++it)
+                tw[it] = *reinterpret_cast<const u32x4*>(w + min(32 * (wave & 1) + 4 * it + (lane >> 4), p.L - 1) * D + 8 * (lane & 15));
         }
     };
     auto commit_tiles = [&](int L, bool first_group) {
-        if (!VSPLIT || !first_group) {
+        if (VSPLIT && !first_group) {
+            _Pragma("unroll") for (int it = 0; it < 8; ++it) {
+                const int row = 32 * (wave & 1) + 4 * it + (lane >> 4);
+                const uint32_t keep = row < L ? 0xffffffffu : 0u;
+                *reinterpret_cast<u32x4*>((wave < 2 ? Wh : Wl) + row * LD + 8 * (lane & 15)) =
+                    u32x4{tw[it].x & keep, tw[it].y & keep, tw[it].z & keep, tw[it].w & keep};
+            }
+        }
+        if (!VSPLIT || first_group) {
             walk_commit<NT>(Q, tq, L, tt);
             walk_commit<NT>(K, tk, L, tt);
-            walk_commit<NT>(V, tv, L, tt);
         }
-        if (!VSPLIT || first_group == kCarrierMovesDo) walk_commit<NT>(dO, to, L, tt);
-        if (VSPLIT && first_group) walk_commit<NT>(Wh, twh, L, tt);
-        if (VSPLIT && !first_group) {
-            walk_commit<NT>(V2, tv2, L, tt);
-            walk_commit<NT>(Wl, twl, L, tt);
-        }
+        if (!VSPLIT || !first_group) walk_commit<NT>(V, tv, L, tt);
+        if (!VSPLIT || first_group) walk_commit<NT>(dO, to, L, tt);
+        if (VSPLIT && !first_group) walk_commit<NT>(V2, tv2, L, tt);
     };
-    auto store_tiles = [&](const ChunkPos& cp, bool first_group) {
+    auto store_tiles = [&](const ChunkPos& cp) {
         // Every thread reads back exactly the stage pieces that its own next commit overwrites: no barrier between this and
         // the next chunk's commit.
-        if (!VSPLIT || !first_group) {
-            if (WIDE == 1) {  // head and remainder of this pass's dq and dk, for the second pass
-                walk_store<false, NT>(a.part[0], Q, cp.wtok0, 1, cp.L, tt);
-                walk_store<false, NT>(a.part[1], Lq, cp.wtok0, 1, cp.L, tt);
-                walk_store<false, NT>(a.part[2], K, cp.wtok0, 1, cp.L, tt);
-                walk_store<false, NT>(a.part[3], Lk, cp.wtok0, 1, cp.L, tt);
-            } else {
-                walk_store<false, NT>(a.dq, Q, cp.tok0, cp.ts, cp.L, tt);
-                walk_store<false, NT>(a.dk, K, cp.tok0, cp.ts, cp.L, tt);
-            }
-            if (!VSPLIT) walk_store<false, NT>(a.dv, V, cp.vtok0, cp.vts, cp.L, tt);
+        if (WIDE == 1) {  // head and remainder of this pass's dq and dk, for the second pass
+            walk_store<false, NT>(a.part[0], Q, cp.wtok0, 1, cp.L, tt);
+            walk_store<false, NT>(a.part[1], Lq, cp.wtok0, 1, cp.L, tt);
+            walk_store<false, NT>(a.part[2], K, cp.wtok0, 1, cp.L, tt);
+            walk_store<false, NT>(a.part[3], Lk, cp.wtok0, 1, cp.L, tt);
+        } else {
+            walk_store<false, NT>(a.dq, Q, cp.tok0, cp.ts, cp.L, tt);
+            walk_store<false, NT>(a.dk, K, cp.tok0, cp.ts, cp.L, tt);
         }
+        walk_store<false, NT>(a.dv, V, cp.vtok0, cp.vts, cp.L, tt);
     };
     // WIDE == 2: the first pass's share of a gradient block (lane = token 32 nb + n, registers = this wave's 32 features)
     struct Part { u32x2 h[4], l[4]; };
@@ -591,7 +634,7 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
                 if (WANT_DG) {
                     float pq = row_dot(Q, tok, wave, half, aq[nb]);
                     pq += __shfl_xor(pq, 32, 64);
-                    if (half == 0) red[(wave * 2 + 0) * 64 + tok] = VSPLIT ? pq + red[(wave * 2 + 0) * 64 + tok] : pq;
+                    if (half == 0) red[(wave * 2 + 0) * 64 + tok] = pq;
                 }
                 if (WIDE == 2) part_add(aq[nb], pt[nb]);  // after the decay gradient took this pass's own share
                 if (WIDE == 1) {
@@ -628,19 +671,22 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             __syncthreads();  // (1) tiles, dS rows and decay tables of this chunk are in LDS
             fresh();
             const float bC = DEC ? bs[C] : 0.f;
-            f32x16 aq[2];
+            f32x16 aq[2], ax[2];
             PackedBlock resq[2], resql[2];
             if (VSPLIT) {
-                // X^T[i][t], the state's share: -e^{b_t} sum_v S[i][v] W[t][v]
-                walk_inter_split(aq, S, Wh, Wl, n, half);
+                // X^T[i][t] and dq^T[i][t], the state's share: -e^{b_t} sum_v S[i][v] W[t][v], e^{b_t} sum_v S[i][v] dO[t][v]
+                walk_inter_pair(ax, aq, S, Wh, Wl, dO, n, half);
                 _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
                     const int tok = 32 * nb + n;
-                    const float w = DEC ? -__expf(bs[tok]) : -1.f, b = be[tok];
-                    _Pragma("unroll") for (int x = 0; x < 16; ++x) aq[nb][x] *= w;
-                    float px = row_dot(K, tok, wave, half, aq[nb]);
+                    const float w = DEC ? __expf(bs[tok]) : 1.f, b = be[tok];
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                        if (DEC) aq[nb][x] *= w;
+                        ax[nb][x] *= -w;
+                    }
+                    float px = row_dot(K, tok, wave, half, ax[nb]);
                     px += __shfl_xor(px, 32, 64);
                     if (half == 0) redx[wave * 64 + tok] = px;
-                    _Pragma("unroll") for (int x = 0; x < 16; ++x) aq[nb][x] *= b;
+                    _Pragma("unroll") for (int x = 0; x < 16; ++x) ax[nb][x] *= b;
                 }
             } else {
                 walk_inter<DEC>(aq, S, dO, bs, n, half);
@@ -655,25 +701,34 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             __syncthreads();  // (2) G and As are in LDS
             fresh();
             if (VSPLIT) {
-                // beta X is complete with beta H, and parked over the planes of W, which are spent
-                _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
-                    const int tok = 32 * nb + n;
-                    _Pragma("unroll") for (int ks = 0; ks < 2 * (nb + 1); ++ks) {
-                        const bf16x8 kt = frag_tr(K, LD, 16 * ks, 32 * wave, lane);
-                        aq[nb] = mfma(kt, frag(Ah, LDP, tok, 16 * ks + 8 * half), aq[nb]);
-                        aq[nb] = mfma(kt, frag(Al, LDP, tok, 16 * ks + 8 * half), aq[nb]);
-                    }
-                    if (WANT_DG) {
-                        float px = row_dot(K, tok, wave, half, aq[nb]);
-                        px += __shfl_xor(px, 32, 64);
-                        if (half == 0) red[(wave * 2 + 0) * 64 + tok] = px;
-                    }
-                    _Pragma("unroll") for (int g = 0; g < 4; ++g)
-                        *reinterpret_cast<float4*>(Xs + tok * LDX + 32 * wave + 8 * g + 4 * half) =
-                            float4{aq[nb][4 * g], aq[nb][4 * g + 1], aq[nb][4 * g + 2], aq[nb][4 * g + 3]};
+                // (a chain of few products: every operand is requested before anything is written to LDS)
+                bf16x8 kt[4], gh[6], gl[6];
+                _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) kt[ks] = frag_tr(K, LD, 16 * ks, 32 * wave, lane);
+                _Pragma("unroll") for (int i = 0; i < 6; ++i) {
+                    const int off = (i < 2 ? n : 32 + n) * LDP + 16 * (i < 2 ? i : i - 2) + 8 * half;
+                    gh[i] = *reinterpret_cast<const bf16x8*>(Gh + off);
+                    gl[i] = *reinterpret_cast<const bf16x8*>(Gl + off);
                 }
-                walk_inter<DEC>(aq, S, dO, bs, n, half);
-                dq_intra(aq, resq, resql, cp);
+                _Pragma("unroll") for (int i = 0; i < 6; ++i) {
+                    aq[i < 2 ? 0 : 1] = mfma(kt[i < 2 ? i : i - 2], gh[i], aq[i < 2 ? 0 : 1]);
+                    aq[i < 2 ? 0 : 1] = mfma(kt[i < 2 ? i : i - 2], gl[i], aq[i < 2 ? 0 : 1]);
+                }
+                if (WANT_DG) {
+                    float pq[2];
+                    _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) pq[nb] = row_dot(Q, 32 * nb + n, wave, half, aq[nb]);
+                    _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
+                        pq[nb] += __shfl_xor(pq[nb], 32, 64);
+                        if (half == 0) red[(wave * 2 + 0) * 64 + 32 * nb + n] = pq[nb];
+                    }
+                }
+                // the planes of W are spent: beta X (without the scores' share) is parked over them for the group that has dk
+                _Pragma("unroll") for (int nb = 0; nb < 2; ++nb)
+                    _Pragma("unroll") for (int g = 0; g < 4; ++g)
+                        _Pragma("unroll") for (int h = 0; h < 2; ++h)
+                            *reinterpret_cast<float2*>(Xs + (32 * nb + n) * LDX + 8 * g + 4 * half + 2 * h) = float2{ax[nb][4 * g + 2 * h], ax[nb][4 * g + 2 * h + 1]};
+                _Pragma("unroll") for (int nb = 0; nb < 2; ++nb)
+                    store_tokens_direct(a.dq + (cp.tok0 + size_t(32 * nb + n) * cp.ts) * D, 32 * nb + n < L, wave, half, aq[nb]);
+                if (kk + 1 < cnt) gload(kk + 1);
                 fresh();
                 if (WANT_DG) {
                     const uint16_t* dS = a.dstates + cp.slot * D * D;
@@ -683,29 +738,29 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
                 }
                 walk_update<DEC, true, true>(S, V, K, wo, bC, wave, lane, half, V2);
                 if (WANT_DG) state_dot(dsz);
-                if (kk + 1 < cnt) gload(kk + 1);
             } else {
                 dq_intra(aq, resq, resql, cp);
             }
             __syncthreads();  // (3) every wave is done with the tiles
             fresh();
-            _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
-                store_packed(Q, LD, 32 * nb + n, 32 * wave, half, resq[nb]);
-                if (WIDE == 1) store_packed(Lq, LD, 32 * nb + n, 32 * wave, half, resql[nb]);
+            if (!VSPLIT) {
+                _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
+                    store_packed(Q, LD, 32 * nb + n, 32 * wave, half, resq[nb]);
+                    if (WIDE == 1) store_packed(Lq, LD, 32 * nb + n, 32 * wave, half, resql[nb]);
+                }
+                __syncthreads();  // (4)
+                store_tiles(cp);
             }
-            __syncthreads();  // (4)
-            fresh();
-            store_tiles(cp, true);
-            if (VSPLIT && a.d_beta && wave8 == 1 && lane < L) {
-                const float x = (redx[lane] + redx[64 + lane]) + (redx[128 + lane] + redx[192 + lane]);
-                // row sums: t < 32 from block (0,0); t >= 32 from blocks (1,0) and (1,1)
-                a.d_beta[cp.tok0 + size_t(lane) * cp.ts] = x + (lane < 32 ? rowF[lane] : rowF[lane] + rowF[32 + lane]);
-            }
+            auto kx = [&]() {  // k_t . X_t; row sums of the scores' share: t < 32 from block (0,0); t >= 32 from (1,0) and (1,1)
+                return (redx[lane] + redx[64 + lane]) + (redx[128 + lane] + redx[192 + lane]) + (lane < 32 ? rowF[lane] : rowF[lane] + rowF[32 + lane]);
+            };
+            if (VSPLIT && a.d_beta && wave8 == 1 && lane < L) a.d_beta[cp.tok0 + size_t(lane) * cp.ts] = kx();
             if (WANT_DG && wave8 == 0) {
                 // fixed-order sums over the four feature slices, then the reverse in-chunk running sum
                 float w = 0.f;
                 const float z = (zred[0] + zred[1]) + (zred[2] + zred[3]);
                 _Pragma("unroll") for (int wv = 0; wv < 4; ++wv) w += red[(wv * 2 + 0) * 64 + tid] - red[(wv * 2 + 1) * 64 + tid];
+                if (VSPLIT) w += be[tid] * kx();
                 float sfx = w;  // suffix sum of w over tokens >= tid
                 for (int off = 1; off < 64; off <<= 1) {
                     const float y = __shfl_down(sfx, off, 64);
@@ -727,7 +782,7 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
         bf16x8 dsfrag[8];
         auto gload = [&](int kk) {
             const ChunkPos p = walk_pos(d, walk, kbeg + min(kk, cnt - 1));
-            gload_tiles(p, false);
+            if (!VSPLIT) gload_tiles(p, false);
             // rows i in [32w, 32w+32) of dS: A operands [m = i][k = v]
             const uint16_t* dS = a.dstates + p.slot * D * D;
             _Pragma("unroll") for (int ks = 0; ks < 8; ++ks)
@@ -737,17 +792,16 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
         auto score = [&](bool isG, int bi) {
             const int pjb = bi ? 1 : 0, prb = bi == 2 ? 1 : 0;
             // D[m = r][n = j] = v_r . d_o_j  or  k_r . q_j
-            f32x16 P = isG ? score_block2(V, 32 * prb, dO, 32 * pjb, n, half) : score_block2(K, 32 * prb, Q, 32 * pjb, n, half);
-            if (VSPLIT && isG) P = score_block2(V2, 32 * prb, dO, 32 * pjb, n, half, P);
+            f32x16 P = !isG ? score_block2(K, 32 * prb, Q, 32 * pjb, n, half)
+                       : VSPLIT ? score_block_split(V, V2, 32 * prb, dO, nullptr, 32 * pjb, n, half)
+                                : score_block2(V, 32 * prb, dO, 32 * pjb, n, half);
             walk_mask<DEC>(P, 32 * prb, 32 * pjb + n, bs, half);
             store_block_t_split(isG ? Gh : Ah, isG ? Gl : Al, LDP, 32 * pjb + n, 32 * prb, half, P);
         };
         // VSPLIT: a block of H, with its row sums against K K^T; what is kept is beta H
         auto erase_score = [&](int bi) {
             const int pjb = bi ? 1 : 0, prb = bi == 2 ? 1 : 0, t = 32 * pjb + n;
-            f32x16 P = score_block2(V, 32 * prb, Wh, 32 * pjb, n, half);  // D[m = r][n = t] = u_r . W_t
-            P = score_block2(V2, 32 * prb, Wh, 32 * pjb, n, half, P);
-            P = score_block2(V, 32 * prb, Wl, 32 * pjb, n, half, P);
+            f32x16 P = score_block_split(V, V2, 32 * prb, Wh, Wl, 32 * pjb, n, half);  // D[m = r][n = t] = u_r . W_t
             walk_mask<DEC>(P, 32 * prb, t, bs, half);
             const f32x16 G = score_block2(K, 32 * prb, K, 32 * pjb, n, half);
             const float b = be[t];
@@ -761,6 +815,7 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             if (half == 0) rowF[32 * bi + n] = rs;
             store_block_t_split(Ah, Al, LDP, t, 32 * prb, half, P);
         };
+        if (VSPLIT) gload_tiles(walk_pos(d, walk, kbeg), false);
         gload(0);
         for (int kk = 0; kk < cnt; ++kk) {
             const ChunkPos cp = walk_pos(d, walk, kbeg + kk);
@@ -777,6 +832,7 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             // G = (dO V^T) * D first (the other group waits for it at (2)), then As = (Q K^T) * D, which only dv needs
             if (VSPLIT) {
                 if (wave < 3) {
+                    if (kk + 1 < cnt) gload_tiles(walk_pos(d, walk, kbeg + kk + 1), false);
                     erase_score(wave);
                 } else {
                     _Pragma("unroll 1") for (int bi = 0; bi < 3; ++bi) score(true, bi);
@@ -788,18 +844,21 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             }
             // inter parts: dk^T[i][r] from the dS rows in registers, dv^T[v][r] from the transposed read of the LDS rows
             f32x16 ak[2] = {{0}, {0}}, av[2] = {{0}, {0}};
-            _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
-                const int tok = 32 * nb + n;
-                _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) ak[nb] = mfma(dsfrag[ks], frag(V, LD, tok, 16 * ks + 8 * half), ak[nb]);
-                if (VSPLIT) {
-                    _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) ak[nb] = mfma(dsfrag[ks], frag(V2, LD, tok, 16 * ks + 8 * half), ak[nb]);
+            auto dk_inter = [&]() {
+                _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
+                    const int tok = 32 * nb + n;
+                    _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) ak[nb] = mfma(dsfrag[ks], frag(V, LD, tok, 16 * ks + 8 * half), ak[nb]);
+                    if (VSPLIT) {
+                        _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) ak[nb] = mfma(dsfrag[ks], frag(V2, LD, tok, 16 * ks + 8 * half), ak[nb]);
+                    }
+                    if (DEC) {
+                        const float wk = wo[tok];
+                        _Pragma("unroll") for (int x = 0; x < 16; ++x) ak[nb][x] *= wk;
+                    }
                 }
-                if (DEC) {
-                    const float wk = wo[tok];
-                    _Pragma("unroll") for (int x = 0; x < 16; ++x) ak[nb][x] *= wk;
-                }
-            }
-            if (kk + 1 < cnt) gload(kk + 1);  // the dS registers are free
+                if (kk + 1 < cnt) gload(kk + 1);  // the dS registers are free
+            };
+            if (!VSPLIT) dk_inter();
             if (!VSPLIT) {
                 _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) {
                     const bf16x8 dst = frag_tr(dSt, LD, 16 * ks, 32 * wave, lane);  // dS^T[v][i], i = 16 ks + ..
@@ -815,67 +874,95 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
             }
             __syncthreads();  // (2) G and As are in LDS
             fresh();
+            if (VSPLIT) {
+                if (wave == 3 && kk + 1 < cnt) gload_tiles(walk_pos(d, walk, kbeg + kk + 1), false);
+                dk_inter();
+            }
             PackedBlock resk[2], resv[2], reskl[2];
             Part pt[2];
             if (WIDE == 2) {
                 part_load(pt[0], a.part[2], a.part[3], cp, 0);
                 part_load(pt[1], a.part[2], a.part[3], cp, 1);
             }
-            _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
+            if (VSPLIT) {
+                // dk^T[i][r] += sum_{j>=r} Q^T[i][j] G[j][r], the same with beta H and the keys in the query's place, then, after the
+                // decay gradient took the key side, the scores' share of beta X
+                bf16x8 qt[4], kt[4];
+                _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
+                    qt[ks] = frag_tr(Q, LD, 16 * ks, 32 * wave, lane);
+                    kt[ks] = frag_tr(K, LD, 16 * ks, 32 * wave, lane);
+                }
+                float pk[2] = {0.f, 0.f};
+                _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
+                    _Pragma("unroll") for (int ks = 2 * nb; ks < 4; ++ks) {
+                        ak[nb] = mfma(qt[ks], frag_tr(Gh, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
+                        ak[nb] = mfma(qt[ks], frag_tr(Gl, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
+                        ak[nb] = mfma(kt[ks], frag_tr(Ah, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
+                        ak[nb] = mfma(kt[ks], frag_tr(Al, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
+                    }
+                    if (WANT_DG) pk[nb] = row_dot(K, 32 * nb + n, wave, half, ak[nb]);
+                    _Pragma("unroll") for (int ks = 0; ks < 2 * (nb + 1); ++ks) {
+                        ak[nb] = mfma(kt[ks], frag(Ah, LDP, 32 * nb + n, 16 * ks + 8 * half), ak[nb]);
+                        ak[nb] = mfma(kt[ks], frag(Al, LDP, 32 * nb + n, 16 * ks + 8 * half), ak[nb]);
+                    }
+                }
+                if (WANT_DG) {
+                    _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
+                        pk[nb] += __shfl_xor(pk[nb], 32, 64);
+                        if (half == 0) red[(wave * 2 + 1) * 64 + 32 * nb + n] = pk[nb];
+                    }
+                }
+            }
+            _Pragma("unroll") for (int nb = 0; nb < (VSPLIT ? 0 : 2); ++nb) {
                 const int tok = 32 * nb + n;
                 // dk^T[i][r] += sum_{j>=r} Q^T[i][j] G[j][r]: queries j < 32 never see keys r >= 32
                 _Pragma("unroll") for (int ks = 2 * nb; ks < 4; ++ks) {
                     const bf16x8 qt = frag_tr(Q, LD, 16 * ks, 32 * wave, lane);
                     ak[nb] = mfma(qt, frag_tr(Gh, LDP, 16 * ks, 32 * nb, lane), ak[nb]);  // B[k = j][n = r] = G[j][r]
                     ak[nb] = mfma(qt, frag_tr(Gl, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
-                    if (VSPLIT) {  // the same with beta H and the keys in the query's place
-                        const bf16x8 kt = frag_tr(K, LD, 16 * ks, 32 * wave, lane);
-                        ak[nb] = mfma(kt, frag_tr(Ah, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
-                        ak[nb] = mfma(kt, frag_tr(Al, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
-                    }
                 }
                 if (WANT_DG) {
                     float pk = row_dot(K, tok, wave, half, ak[nb]);
                     pk += __shfl_xor(pk, 32, 64);
                     if (half == 0) red[(wave * 2 + 1) * 64 + tok] = pk;
                 }
-                if (!VSPLIT) {
-                    if (WIDE == 2) part_add(ak[nb], pt[nb]);
-                    if (WIDE == 1) {
-                        resk[nb] = split_block(ak[nb]);
-                        reskl[nb] = pack_block(ak[nb]);
-                    } else {
-                        resk[nb] = pack_block(ak[nb]);
-                    }
-                    // dv^T[v][r] += sum_{j>=r} dO^T[v][j] As[j][r]
-                    _Pragma("unroll") for (int ks = 2 * nb; ks < 4; ++ks) {
-                        const bf16x8 dot = frag_tr(dO, LD, 16 * ks, 32 * wave, lane);
-                        av[nb] = mfma(dot, frag_tr(Ah, LDP, 16 * ks, 32 * nb, lane), av[nb]);  // B[k = j][n = r] = As[j][r]
-                        av[nb] = mfma(dot, frag_tr(Al, LDP, 16 * ks, 32 * nb, lane), av[nb]);
-                    }
-                    resv[nb] = pack_block(av[nb]);
+                if (WIDE == 2) part_add(ak[nb], pt[nb]);
+                if (WIDE == 1) {
+                    resk[nb] = split_block(ak[nb]);
+                    reskl[nb] = pack_block(ak[nb]);
+                } else {
+                    resk[nb] = pack_block(ak[nb]);
                 }
+                // dv^T[v][r] += sum_{j>=r} dO^T[v][j] As[j][r]
+                _Pragma("unroll") for (int ks = 2 * nb; ks < 4; ++ks) {
+                    const bf16x8 dot = frag_tr(dO, LD, 16 * ks, 32 * wave, lane);
+                    av[nb] = mfma(dot, frag_tr(Ah, LDP, 16 * ks, 32 * nb, lane), av[nb]);  // B[k = j][n = r] = As[j][r]
+                    av[nb] = mfma(dot, frag_tr(Al, LDP, 16 * ks, 32 * nb, lane), av[nb]);
+                }
+                resv[nb] = pack_block(av[nb]);
             }
             __syncthreads();  // (3)
             fresh();
-            _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
-                if (VSPLIT) {  // the other group's beta X, before the one rounding
-                    _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                        const float4 x = *reinterpret_cast<const float4*>(Xs + (32 * nb + n) * LDX + 32 * wave + 8 * g + 4 * half);
-                        ak[nb][4 * g] += x.x;
-                        ak[nb][4 * g + 1] += x.y;
-                        ak[nb][4 * g + 2] += x.z;
-                        ak[nb][4 * g + 3] += x.w;
-                    }
-                    resk[nb] = pack_block(ak[nb]);
+            if (VSPLIT) {  // with the other group's beta X, before the one rounding (the wave's own next rows of W come over it)
+                _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
+                    const int tok = 32 * nb + n;
+                    _Pragma("unroll") for (int g = 0; g < 4; ++g)
+                        _Pragma("unroll") for (int h = 0; h < 2; ++h) {
+                            const float2 x = *reinterpret_cast<const float2*>(Xs + tok * LDX + 8 * g + 4 * half + 2 * h);
+                            ak[nb][4 * g + 2 * h] += x.x;
+                            ak[nb][4 * g + 2 * h + 1] += x.y;
+                        }
+                    store_tokens_direct(a.dk + (cp.tok0 + size_t(tok) * cp.ts) * D, tok < L, wave, half, ak[nb]);
                 }
-                store_packed(K, LD, 32 * nb + n, 32 * wave, half, resk[nb]);
-                if (!VSPLIT) store_packed(V, LD, 32 * nb + n, 32 * wave, half, resv[nb]);
-                if (WIDE == 1) store_packed(Lk, LD, 32 * nb + n, 32 * wave, half, reskl[nb]);
+            } else {
+                _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
+                    store_packed(K, LD, 32 * nb + n, 32 * wave, half, resk[nb]);
+                    store_packed(V, LD, 32 * nb + n, 32 * wave, half, resv[nb]);
+                    if (WIDE == 1) store_packed(Lk, LD, 32 * nb + n, 32 * wave, half, reskl[nb]);
+                }
+                __syncthreads();  // (4)
+                store_tiles(cp);
             }
-            __syncthreads();  // (4)
-            fresh();
-            store_tiles(cp, false);
         }
     }
 }
