@@ -432,7 +432,7 @@ __global__ __launch_bounds__(512, 1) void mk_delta_walk8(Dims d, DeltaWalkArgs a
             if (wave == 0) {
                 float gam = 1.f;
                 if (DEC) {
-                    walk_decay_tables<false>(gval, L, 0.f, bs, wo, lane);
+                    walk_decay_tables<false, false>(gval, L, 0.f, bs, wo, lane);
                     gam = __expf(bs[lane]);
                 }
                 ne[lane] = lane < L ? -bval * gam : 0.f;
@@ -798,7 +798,7 @@ __global__ __launch_bounds__(512, 1) void mk_delta_rwalk(Dims d, DeltaRevArgs a)
             if (wave == 0) {
                 float gam = 1.f;
                 if (DEC) {
-                    walk_decay_tables<false>(gval, cp.L, 0.f, bs, wo, lane);
+                    walk_decay_tables<false, false>(gval, cp.L, 0.f, bs, wo, lane);
                     gm[lane] = gam = __expf(bs[lane]);
                 }
                 ne[lane] = lane < cp.L ? -bval * gam : 0.f;

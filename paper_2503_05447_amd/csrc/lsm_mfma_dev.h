@@ -55,6 +55,20 @@ __device__ __forceinline__ bf16x8 frag_tr(const uint16_t* tile, int ld, int row0
     return __builtin_bit_cast(bf16x8, v);
 }
 
+// The same for contractions whose two operands are both read so, in a k order of their own that both share: slot e of half h is
+// token row0 + 4 (e % 4) + e / 4 + 2 h (tr4_at: where a table of per-token weights has it).  A patch's four rows are four rows
+// apart, 16 words mod 64 with either row stride, and so in different banks; consecutive rows share half of theirs.  (Gradient walker of
+// the delta rule: conflict clocks 5900 -> 2500 a chunk, LDS busy 13500 -> 9700; training steps of the scalar kinds 1 % shorter.)
+__device__ __forceinline__ bf16x8 frag_tr4(const uint16_t* tile, int ld, int row0, int col0, int lane) {
+    const int r = lane & 15, nblk = (lane >> 4) & 1, half = lane >> 5;
+    const uint16_t* p = tile + (row0 + 2 * half + 4 * (r >> 2)) * ld + col0 + 16 * nblk + 4 * (r & 3);
+    typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
+    const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p)));
+    const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + ld)));
+    return __builtin_bit_cast(bf16x8, u32x4{lo.x, lo.y, hi.x, hi.y});
+}
+__device__ __forceinline__ int tr4_at(int t) { return (t & ~15) | (4 * (t & 2)) | (4 * (t & 1)) | ((t >> 2) & 3); }
+
 // write a D-layout block as 8-byte pieces: dst[(n)][m0 + 8g + 4half + 0..3], row stride ld
 __device__ __forceinline__ void store_block_t(uint16_t* dst, int ld, int nrow, int m0, int half, const f32x16& d) {
     _Pragma("unroll") for (int g = 0; g < 4; ++g) {

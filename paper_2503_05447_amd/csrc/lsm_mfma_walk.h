@@ -163,7 +163,7 @@ __device__ __forceinline__ void walk_intra(f32x16& O, int jb, const uint16_t* V,
     }
 }
 // state: S[i][v] = e^{b_C} S[i][v] + sum_t K^T[i][t] (wo_t V[t][v]); the weighted value slice of this wave is
-// split into head + remainder in registers.  SCALE = false: the weights already carry every decay.
+// split into head + remainder in registers (wo in tr4_at order).  SCALE = false: the weights already carry every decay.
 // K2 (KSPLIT): remainder plane of the key-role tile (remainder x remainder is left out).
 template <bool DEC, bool SCALE, bool KSPLIT = false>
 __device__ __forceinline__ void walk_update(f32x16 (&S)[4], const uint16_t* K, const uint16_t* V, const float* wo, float bC, int w4,
@@ -174,7 +174,7 @@ __device__ __forceinline__ void walk_update(f32x16 (&S)[4], const uint16_t* K, c
             _Pragma("unroll") for (int x = 0; x < 16; ++x) S[ib][x] *= lam;
     }
     _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
-        const u32x4 raw = __builtin_bit_cast(u32x4, frag_tr(V, LD, 16 * ks, 32 * w4, lane));
+        const u32x4 raw = __builtin_bit_cast(u32x4, frag_tr4(V, LD, 16 * ks, 32 * w4, lane));
         u32x4 hi = raw, lo = {0, 0, 0, 0};
         if (DEC) {
             const float4 w0 = *reinterpret_cast<const float4*>(wo + 16 * ks + 8 * half);
@@ -188,19 +188,20 @@ __device__ __forceinline__ void walk_update(f32x16 (&S)[4], const uint16_t* K, c
         }
         const bf16x8 vh = __builtin_bit_cast(bf16x8, hi), vl = __builtin_bit_cast(bf16x8, lo);
         bf16x8 ka[4];
-        _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) ka[ib] = frag_tr(K, LD, 16 * ks, 32 * ib, lane);
+        _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) ka[ib] = frag_tr4(K, LD, 16 * ks, 32 * ib, lane);
         _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) S[ib] = mfma(ka[ib], vh, S[ib]);
         if (DEC) {
             _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) S[ib] = mfma(ka[ib], vl, S[ib]);
         }
         if (KSPLIT) {
-            _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) S[ib] = mfma(frag_tr(K2, LD, 16 * ks, 32 * ib, lane), vh, S[ib]);
+            _Pragma("unroll") for (int ib = 0; ib < 4; ++ib) S[ib] = mfma(frag_tr4(K2, LD, 16 * ks, 32 * ib, lane), vh, S[ib]);
         }
     }
 }
 // chunk-local decay tables by one wave: beta (inclusive running sum of the log-decays in walk order, exclusive
 // when walking backward), b_C, and the weights wo = e^{b_C - beta + extra} of the state update
-template <bool REV>
+// (TR4: wo in tr4_at order)
+template <bool REV, bool TR4 = true>
 __device__ __forceinline__ float walk_decay_tables(float gval, int L, float extra, float* bs, float* wo, int lane) {
     const float x = lane < L ? gval : 0.f;
     float inc = x;
@@ -210,7 +211,7 @@ __device__ __forceinline__ float walk_decay_tables(float gval, int L, float extr
     }
     const float bC = __shfl(inc, 63, 64), beta = REV ? inc - x : inc;
     bs[lane] = beta;
-    wo[lane] = __expf(bC - beta + extra);
+    wo[TR4 ? tr4_at(lane) : lane] = __expf(bC - beta + extra);
     if (lane == 0) bs[C] = bC;
     return bC;
 }
@@ -459,7 +460,7 @@ __device__ __forceinline__ f32x16 score_block_split(const uint16_t* Am, const ui
 // state before barrier (2), then park beta X, complete dq, move the state on and take <S, dS> (dS by loads of their own from the
 // fragment-major array, which the other group has just pulled into L2: the LDS area of the dS rows holds W); the other group
 // forms the scores before (2) and all of dk, X's scores' share included, after it.  16 x 16 sequences of 2048, 2.8 KB a token: 514 us
-// with X completed by the carrier waves and one group moving all tiles but one, 470 so.
+// with X completed by the carrier waves and one group moving all tiles but one, 470, 455 with frag_tr4's order, so.
 constexpr int kGrad8Threads = 512;
 
 // WIDE: 0 the only pass; 1 the first of two value-slice passes (dq, dk to the partial planes); 2 the second
@@ -852,7 +853,7 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
                         _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) ak[nb] = mfma(dsfrag[ks], frag(V2, LD, tok, 16 * ks + 8 * half), ak[nb]);
                     }
                     if (DEC) {
-                        const float wk = wo[tok];
+                        const float wk = wo[tr4_at(tok)];
                         _Pragma("unroll") for (int x = 0; x < 16; ++x) ak[nb][x] *= wk;
                     }
                 }
@@ -867,7 +868,7 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
                 }
                 if (DEC) {
                     _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
-                        const float wk = wo[32 * nb + n];
+                        const float wk = wo[tr4_at(32 * nb + n)];
                         _Pragma("unroll") for (int x = 0; x < 16; ++x) av[nb][x] *= wk;
                     }
                 }
@@ -889,21 +890,22 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
                 // decay gradient took the key side, the scores' share of beta X
                 bf16x8 qt[4], kt[4];
                 _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
-                    qt[ks] = frag_tr(Q, LD, 16 * ks, 32 * wave, lane);
-                    kt[ks] = frag_tr(K, LD, 16 * ks, 32 * wave, lane);
+                    qt[ks] = frag_tr4(Q, LD, 16 * ks, 32 * wave, lane);
+                    kt[ks] = frag_tr4(K, LD, 16 * ks, 32 * wave, lane);
                 }
                 float pk[2] = {0.f, 0.f};
                 _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
                     _Pragma("unroll") for (int ks = 2 * nb; ks < 4; ++ks) {
-                        ak[nb] = mfma(qt[ks], frag_tr(Gh, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
-                        ak[nb] = mfma(qt[ks], frag_tr(Gl, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
-                        ak[nb] = mfma(kt[ks], frag_tr(Ah, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
-                        ak[nb] = mfma(kt[ks], frag_tr(Al, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
+                        ak[nb] = mfma(qt[ks], frag_tr4(Gh, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
+                        ak[nb] = mfma(qt[ks], frag_tr4(Gl, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
+                        ak[nb] = mfma(kt[ks], frag_tr4(Ah, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
+                        ak[nb] = mfma(kt[ks], frag_tr4(Al, LDP, 16 * ks, 32 * nb, lane), ak[nb]);
                     }
                     if (WANT_DG) pk[nb] = row_dot(K, 32 * nb + n, wave, half, ak[nb]);
                     _Pragma("unroll") for (int ks = 0; ks < 2 * (nb + 1); ++ks) {
-                        ak[nb] = mfma(kt[ks], frag(Ah, LDP, 32 * nb + n, 16 * ks + 8 * half), ak[nb]);
-                        ak[nb] = mfma(kt[ks], frag(Al, LDP, 32 * nb + n, 16 * ks + 8 * half), ak[nb]);
+                        const bf16x8 kn = frag_tr(K, LD, 16 * ks, 32 * wave, lane);
+                        ak[nb] = mfma(kn, frag(Ah, LDP, 32 * nb + n, 16 * ks + 8 * half), ak[nb]);
+                        ak[nb] = mfma(kn, frag(Al, LDP, 32 * nb + n, 16 * ks + 8 * half), ak[nb]);
                     }
                 }
                 if (WANT_DG) {
