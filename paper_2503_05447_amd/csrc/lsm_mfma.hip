@@ -278,22 +278,24 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
     uint16_t* stage = tiles + 2 * kStateTile;                    // [32 * LD]: the untransposed copy, if any
     // The four workgroups of a sequence read the same A-side rows.  Workgroups are dealt to the 8
     // XCDs round-robin by linear id, so the id is decoded such that those four share an XCD (and
-    // its L2): id = xcd + 8 * (4 * (seq / 8) + nb), seq = xcd + 8 * (seq / 8).
+    // its L2): id = xcd + 8 * (4 * (seq / 8) + nb), seq = xcd + 8 * (seq / 8).  The value slices of a sequence, which
+    // read the same B-side rows, do too.
     int nb, seq;
+    const int vhc = VEC ? sa.vh_count : 1;
     const int nsegs = sa.seg_n > 1 ? sa.seg_n : 1, seg = wg_id / (wg_count / nsegs);
     {
-        const int nwg = wg_count / nsegs, id = wg_id % nwg, full = (nwg / 32) * 32;  // 32 = 8 XCDs x 4 blocks
+        const int nwg = wg_count / nsegs, id = wg_id % nwg, full = nwg / (32 * vhc) * (32 * vhc);  // 32 = 8 XCDs x 4 blocks
         if (id < full) {
-            const int xcd = id & 7, slot = id >> 3;
+            const int xcd = id & 7, slot = id >> 3, u = slot >> 2;
             nb = slot & 3;
-            seq = xcd + 8 * (slot >> 2);
+            seq = (xcd + 8 * (u / vhc)) * vhc + u % vhc;
         } else {  // tail when the number of sequences is not a multiple of 8
             nb = (id - full) & 3;
             seq = (full >> 2) + ((id - full) >> 2);
         }
     }
-    const int vh = VEC ? seq % sa.vh_count : 0, nvh = VEC ? sa.vh_count : 1;
-    const SeqWalk walk = seq_walk(d, VEC ? seq / sa.vh_count : seq);
+    const int vh = seq % vhc, nvh = vhc;
+    const SeqWalk walk = seq_walk(d, seq / vhc);
     const int kbeg = nsegs > 1 ? seg * sa.seg_m : 0, kend = nsegs > 1 ? min(walk.n, kbeg + sa.seg_m) : walk.n;
     if (seg > 0 && kend <= kbeg) return;  // a sequence shorter than this segment's start
     const int cnt = kend - kbeg;  // chunks to walk
@@ -385,9 +387,9 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
         // acc[m][n] += sum_t A[t][32mb + m] * Bw[t][n]: both operands read token-major out of LDS
         const uint16_t *ta = bufA(k), *tb = bufB(k);
         _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
-            const bf16x8 fa = frag_tr(ta, LD, 16 * ks, 32 * mb, lane);
-            acc = mfma(fa, frag_tr(tb, LDB, 16 * ks, 0, lane), acc);
-            if (DEC) acc = mfma(fa, frag_tr(tb + C * LDB, LDB, 16 * ks, 0, lane), acc);
+            const bf16x8 fa = frag_tr4(ta, LD, 16 * ks, 32 * mb, lane);
+            acc = mfma(fa, frag_tr4(tb, LDB, 16 * ks, 0, lane), acc);
+            if (DEC) acc = mfma(fa, frag_tr4(tb + C * LDB, LDB, 16 * ks, 0, lane), acc);
         }
         __syncthreads();  // every wave is done with the tiles of chunk k
         state_to_lds<DEC, VEC>(rw, bufA(k), bufB(k), tid);  // chunk k+2; read again two barriers from now
@@ -870,7 +872,7 @@ hipError_t vec_fwd(const Dims& d, const FwdArgs& a) {
     {
         ProfScope ps(KID_MFMA_OUTPUT, a.stream);
         if ((e = allow_lds(mk_output_vec<false>, kOutVecLds)) != hipSuccess) return e;
-        hipLaunchKernelGGL(mk_output_vec<false>, dim3(d.N, d.BH(), nvh), dim3(kThreads), kOutVecLds, a.stream, d, w.qhat_hi, w.qhat_lo, v,
+        hipLaunchKernelGGL(mk_output_vec<false>, dim3(d.N * nvh, d.BH()), dim3(kThreads), kOutVecLds, a.stream, d, w.qhat_hi, w.qhat_lo, v,
                            w.p_hi, w.p_lo, w.states_t, static_cast<uint16_t*>(a.o));
     }
     return hipGetLastError();
@@ -1068,7 +1070,7 @@ hipError_t vec_bwd(const Dims& d, const BwdArgs& a) {
     {
         ProfScope ps(KID_MFMA_VEC_DV, a.stream);
         if ((e = allow_lds(mk_output_vec<true>, kOutVecLds)) != hipSuccess) return e;
-        hipLaunchKernelGGL(mk_output_vec<true>, dim3(d.N, d.BH(), nvh), dim3(kThreads), kOutVecLds, a.stream, d, w.khat_hi,
+        hipLaunchKernelGGL(mk_output_vec<true>, dim3(d.N * nvh, d.BH()), dim3(kThreads), kOutVecLds, a.stream, d, w.khat_hi,
                            w.khat_lo, d_o, w.p_hi, w.p_lo, w.dstates_t, static_cast<uint16_t*>(a.dv));
     }
     {

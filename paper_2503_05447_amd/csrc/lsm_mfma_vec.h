@@ -282,7 +282,9 @@ __device__ __forceinline__ void load_scores(uint16_t* dst, const uint16_t* src, 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Output of one chunk for one 128-wide slice of the value dimension (grid: N x BH x d_v/128):
+// Output of one chunk for one 128-wide slice of the value dimension (grid: N d_v/128 x BH; the slices of a chunk, which read the
+// same qhat and P, are eight workgroups apart, on the same die and at the same time; d_v = 256, 4 x 16 sequences of 4096, with one
+// slice after all chunks of the other 161 us, this 129, the value gradient's 217 and 204):
 //   O^T[v][j] = sum_i S^T[v][i] qhat_j[i] + sum_{r<=j} V^T[v][r] P[j][r]
 // with qhat and P from mk_vec_prep.  Wave w owns 32 value columns.
 // DV = true computes with the same structure the value gradient
@@ -306,7 +308,8 @@ __global__ __launch_bounds__(kThreads, 2) void mk_output_vec(Dims d, const uint1
     uint16_t* Ph = V + C * LD;
     uint16_t* Pl = Ph + C * LDP;
 
-    const int c = blockIdx.x, bh = blockIdx.y, vh = blockIdx.z, nvh = gridDim.z;
+    const int nvh = d.dv / D, bh = blockIdx.y, x = blockIdx.x, whole = int(gridDim.x) / (8 * nvh) * (8 * nvh);
+    const int vh = x < whole ? (x >> 3) % nvh : (x - whole) % nvh, c = x < whole ? 8 * (x / (8 * nvh)) + (x & 7) : x / nvh;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const ChunkPos pos = chunk_pos(d, c, bh);
     const int L = pos.L;
@@ -344,9 +347,9 @@ __global__ __launch_bounds__(kThreads, 2) void mk_output_vec(Dims d, const uint1
             }
         } else {
             _Pragma("unroll") for (int ks = 2 * jb; ks < 4; ++ks) {  // queries j < 32 never see keys r >= 32
-                const bf16x8 vt = frag_tr(V, LD, 16 * ks, 32 * wave, lane);
-                acc = mfma(vt, frag_tr(Ph, LDP, 16 * ks, 32 * jb, lane), acc);  // B[k = j][n = r] = P[j][r]
-                acc = mfma(vt, frag_tr(Pl, LDP, 16 * ks, 32 * jb, lane), acc);
+                const bf16x8 vt = frag_tr4(V, LD, 16 * ks, 32 * wave, lane);
+                acc = mfma(vt, frag_tr4(Ph, LDP, 16 * ks, 32 * jb, lane), acc);  // B[k = j][n = r] = P[j][r]
+                acc = mfma(vt, frag_tr4(Pl, LDP, 16 * ks, 32 * jb, lane), acc);
             }
         }
         res[jb] = pack_block(acc);
