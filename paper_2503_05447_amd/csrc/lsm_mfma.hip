@@ -96,11 +96,9 @@ __global__ __launch_bounds__(64) void mk_decay_prep(Dims d, const float* __restr
 // a single token dominates is visible.
 constexpr int LDB = 40;  // row stride (elements) of a 64 x 32 B-side slice in LDS
 // LDS: 2 x (A tile 64 x LD | B slice head 64 x LDB | B slice remainder 64 x LDB) for chunks k+1, k+2
-//      | one 32 x LD stage for the scans that also store a block untransposed (the transposed order
-//        leaves straight from the registers, see state_store_direct)
+// (the state leaves straight from the registers, see state_store_direct)
 constexpr int kStateTile = C * LD + 2 * C * LDB;
-constexpr int kStateLdsNone = 2 * kStateTile * 2;                  // transposed stores only
-constexpr int kStateLdsPlain = (2 * kStateTile + 32 * LD) * 2;     // with the stage of an untransposed copy
+constexpr int kStateLds = 2 * kStateTile * 2;
 
 struct StateRegs {  // one thread's share of a chunk on its way from global memory to LDS
     u32x4 a[4], b, blo;  // blo: remainder plane of the B slice (vector decay: both planes arrive precomputed)
@@ -119,7 +117,6 @@ struct StateArgs {
     const uint16_t* xb_lo;  // remainder plane of the decayed B-side operand
     int a_stride;           // row stride (elements) of the A-side operand = d_v
     int vh_count;           // 128-wide value slices per (b,h); each is scanned as a sequence of its own
-    uint16_t* states_twin;  // MODE 2 only: second copy of the head, untransposed (dS^T [v][i]), or NULL
     // scan cut into segments (seg_n > 1; grid = seg_n times the plain one): segment s walks chunks
     // [s seg_m, (s+1) seg_m) from the state in seg_bound, which holds fp32 [i][v] entry states at a finer grain
     // (one per fine_m chunks, numbered by bound_slot(); slot f = the state the walk enters fine segment f with)
@@ -198,23 +195,7 @@ __device__ __forceinline__ void state_to_lds(const StateRegs& r, uint16_t* bufA,
 __device__ __forceinline__ size_t state_frag_off(int blk, int ks, int lane) {
     return (size_t(blk * 8 + ks) * 64 + lane) * 8;
 }
-// One wave's staged 32 x 32 block -> global memory.  Stage row r = row r of the stored block `rowblk`,
-// stage columns 32 mb .. +31 = its columns 32 colblk .. +31.  The wave reads back only what it staged
-// itself, and LDS serves a wave's accesses in order: no barrier.
-template <bool STREAM = true>
-__device__ __forceinline__ void state_store(uint16_t* dst, const uint16_t* stage, int mb, int rowblk, int colblk,
-                                            int lane) {
-    _Pragma("unroll") for (int it = 0; it < 2; ++it) {
-        const int piece = 2 * it + (lane >> 5), ksl = piece >> 1, hf = piece & 1, r = lane & 31;
-        const u32x4 val = *reinterpret_cast<const u32x4*>(stage + r * LD + 32 * mb + 16 * ksl + 8 * hf);
-        u32x4* p = reinterpret_cast<u32x4*>(dst + state_frag_off(rowblk, 2 * colblk + ksl, 32 * hf + r));
-        // written once, read by a later kernel: keep it from displacing the shared input tiles in L2
-        if (STREAM) __builtin_nontemporal_store(val, p);
-        else *p = val;
-    }
-}
-
-// The same block -> global memory without LDS, for the transposed order (stored row = the lane's column
+// A 32 x 32 block -> global memory without LDS, in the transposed order (stored row = the lane's column
 // n, stored columns = the block's rows m).  In D layout lanes l and l + 32 hold complementary halves
 // (4 + 4 rows) of every group of 8 rows; one v_permlane32_swap per dword hands each lane a whole group:
 // the lower lanes the even groups, the upper lanes the odd ones, i.e. exactly the 16 bytes that lane
@@ -257,11 +238,8 @@ __device__ __forceinline__ void state_store_direct_split8(uint16_t* dst, uint8_t
 // head and a remainder plane and is always the B side, so that a state column n is one key feature i
 // and e^{b_C[i]} is one factor per lane; the A side is a 128-wide slice of the value-sized operand
 // (row stride d_v), each slice being scanned like a sequence of its own.
-//   MODE 3 (VEC only): forward states with the operands of MODE 1, stored S^T [v][i] like MODE 0.
-//   MODE 2 with VEC: states_twin, when given, receives a second copy dS^T [v][i] (for the dv kernel).
-//   SAVE (MODE 3 only): the forward scan also leaves what the backward pass needs of it, the states in
-//   the order MODE 1 stores them (S [i][v], into states_twin) and their 8-bit remainder plane (states_rem).
-template <int MODE, bool DEC, bool REM, bool VEC, bool SAVE = false>
+// MODE 1 then serves the forward pass too: one copy of the states, S [i][v], for all of their readers.
+template <int MODE, bool DEC, bool VEC>
 __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& sa, int wg_id, int wg_count,
                                                 unsigned char* smem) {
     const uint16_t* __restrict__ xa = sa.xa;
@@ -271,11 +249,9 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
     const float* __restrict__ lam = sa.lam;
     uint16_t* __restrict__ states = sa.states;
     uint16_t* __restrict__ states_rem = sa.states_rem;
-    uint16_t* __restrict__ states_twin = sa.states_twin;
     const float* __restrict__ edge_in = sa.edge_in;
     float* __restrict__ edge_out = sa.edge_out;
     uint16_t* tiles = reinterpret_cast<uint16_t*>(smem);         // [2][kStateTile]
-    uint16_t* stage = tiles + 2 * kStateTile;                    // [32 * LD]: the untransposed copy, if any
     // The four workgroups of a sequence read the same A-side rows.  Workgroups are dealt to the 8
     // XCDs round-robin by linear id, so the id is decoded such that those four share an XCD (and
     // its L2): id = xcd + 8 * (4 * (seq / 8) + nb), seq = xcd + 8 * (seq / 8).  The value slices of a sequence, which
@@ -367,19 +343,9 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
     // would wait for the load issued in the same iteration.
     auto iteration = [&](int k, StateRegs& rw, StateRegs& rl) {
         gload(k + 4, rl);
-        // stage the state this chunk starts from (MODE 2: the gradient this chunk ends with)
-        uint16_t* sh = stage;
-        constexpr bool kTwin = VEC && MODE == 2;  // second copy, untransposed
-        if (MODE == 3 || (kTwin && states_twin)) {
-            _Pragma("unroll") for (int x = 0; x < 16; ++x)
-                sh[(8 * (x >> 2) + 4 * half + (x & 3)) * LD + 32 * mb + n] = uint16_t(pack2(acc[x], 0.f));
-        }
-        // the transposed order needs no staging: registers -> global memory
-        if (MODE != 3 || SAVE) {
-            uint16_t* tdst = (MODE == 3 ? states_twin : states) + slot(k);
-            if (states_rem) state_store_direct_split8(tdst, reinterpret_cast<uint8_t*>(states_rem) + slot(k), nb, mb, lane, acc);
-            else state_store_direct(tdst, nb, mb, lane, acc);
-        }
+        // the state this chunk starts from (MODE 2: the gradient this chunk ends with): registers -> global memory
+        if (states_rem) state_store_direct_split8(states + slot(k), reinterpret_cast<uint8_t*>(states_rem) + slot(k), nb, mb, lane, acc);
+        else state_store_direct(states + slot(k), nb, mb, lane, acc);
         if (DEC) {
             const float lam_cur = rw.lam;
             _Pragma("unroll") for (int x = 0; x < 16; ++x) acc[x] *= lam_cur;
@@ -393,9 +359,6 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
         }
         __syncthreads();  // every wave is done with the tiles of chunk k
         state_to_lds<DEC, VEC>(rw, bufA(k), bufB(k), tid);  // chunk k+2; read again two barriers from now
-        // the untransposed copy: stage row = state row m (block mb), stage columns = state columns (block nb)
-        if (MODE == 3) state_store<false>(states + slot(k), sh, mb, mb, nb, lane);
-        if (kTwin && states_twin) state_store(states_twin + slot(k), sh, mb, mb, nb, lane);
     };
     int k = 0;
     for (; k + 2 < cnt; k += 3) {
@@ -416,10 +379,10 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
     }
 }
 
-template <int MODE, bool DEC, bool SAVE = false>
+template <int MODE, bool DEC>
 __global__ __launch_bounds__(kThreads) void mk_state_seq(Dims d, StateArgs sa) {
     extern __shared__ __align__(16) unsigned char smem[];
-    state_scan_body<MODE, DEC, false, false, SAVE>(d, sa, blockIdx.x, gridDim.x, smem);
+    state_scan_body<MODE, DEC, false>(d, sa, blockIdx.x, gridDim.x, smem);
 }
 
 
@@ -586,25 +549,18 @@ __global__ void mk_head_reduce(Dims d, const float* __restrict__ dg_tok, float* 
     if (threadIdx.x == 0) dg[h] = part[0];
 }
 
-// the forward state scan of the vector decay kind
-template <int MODE, bool SAVE = false>
+// vector decay kind: forward states (MODE 1) or the reverse scan of state gradients (MODE 2)
+template <int MODE>
 __global__ __launch_bounds__(kThreads) void mk_state_vec(Dims d, StateArgs sa) {
     extern __shared__ __align__(16) unsigned char smem[];
-    state_scan_body<MODE, true, false, true, SAVE>(d, sa, blockIdx.x, gridDim.x, smem);
+    state_scan_body<MODE, true, true>(d, sa, blockIdx.x, gridDim.x, smem);
 }
 
-// the reverse scan alone (the states come from the forward call)
-__global__ __launch_bounds__(kThreads) void mk_state_vec_rev(Dims d, StateArgs sa) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    state_scan_body<2, true, true, true>(d, sa, blockIdx.x, gridDim.x, smem);
-}
-
-// both scans of the backward pass, vector decay kind (REM: also the remainder plane of S)
-template <bool REM>
+// both scans of the backward pass
 __global__ __launch_bounds__(kThreads) void mk_state_pair_vec(Dims d, StateArgs s1, StateArgs s2) {
     extern __shared__ __align__(16) unsigned char smem[];
-    if (blockIdx.y == 0) state_scan_body<1, true, REM, true>(d, s1, blockIdx.x, gridDim.x, smem);
-    else state_scan_body<2, true, REM, true>(d, s2, blockIdx.x, gridDim.x, smem);
+    if (blockIdx.y == 0) state_scan_body<1, true, true>(d, s1, blockIdx.x, gridDim.x, smem);
+    else state_scan_body<2, true, true>(d, s2, blockIdx.x, gridDim.x, smem);
 }
 
 #include "lsm_mfma_vec.h"
@@ -612,8 +568,7 @@ __global__ __launch_bounds__(kThreads) void mk_state_pair_vec(Dims d, StateArgs 
 #include "lsm_mfma_delta.h"
 
 struct Ws {
-    uint16_t *states, *dstates, *states_rem, *dstates_t, *dstates_rem;
-    uint16_t* states_t;  // what the forward output kernel reads (S^T [v][i]); = states unless the states are saved
+    uint16_t *states, *dstates, *states_rem, *dstates_rem;
     float *dg_tok, *wdec, *winc, *lam;
     // vector decay: decayed operand planes [BH*T][128], chunk decay totals [BH*N][128], scores [BH*N][64][64]
     uint16_t *khat_hi, *khat_lo, *qhat_hi, *qhat_lo, *p_hi, *p_lo;
@@ -621,8 +576,7 @@ struct Ws {
     size_t bytes;
 };
 
-// With saved states (d.save) the forward and the backward call share one workspace: the backward
-// carving, followed by the plane of transposed states that only the forward call uses.
+// With saved states (d.save) the forward and the backward call share one workspace: the backward carving.
 Ws carve(const Dims& d, void* ws, bool bwd) {
     char* p = static_cast<char*>(ws);
     size_t off = 0;
@@ -635,11 +589,9 @@ Ws carve(const Dims& d, void* ws, bool bwd) {
     const size_t st = align256(size_t(d.BH()) * (d.dv / D) * d.N * D * D * 2) + kSkew;
     if (d.save) bwd = true;
     w.states = reinterpret_cast<uint16_t*>(p + off); off += st;
-    w.states_t = w.states;
     if (d.kind == 3) {
         if (bwd) {
             w.dstates = reinterpret_cast<uint16_t*>(p + off); off += st;
-            w.dstates_t = reinterpret_cast<uint16_t*>(p + off); off += st;
             w.states_rem = reinterpret_cast<uint16_t*>(p + off); off += align256(st / 2) + kSkew;  // one byte per element
             w.dstates_rem = reinterpret_cast<uint16_t*>(p + off); off += align256(st / 2) + kSkew;
         }
@@ -649,7 +601,6 @@ Ws carve(const Dims& d, void* ws, bool bwd) {
         w.p_hi = reinterpret_cast<uint16_t*>(p + off); off += sc;
         w.p_lo = reinterpret_cast<uint16_t*>(p + off); off += sc;
         w.lamv = reinterpret_cast<float*>(p + off); off += align256(size_t(d.BH()) * d.N * D * 4);
-        if (d.save) { w.states_t = reinterpret_cast<uint16_t*>(p + off); off += st; }
         w.bytes = off;
         return w;
     }
@@ -661,7 +612,6 @@ Ws carve(const Dims& d, void* ws, bool bwd) {
         w.lam = reinterpret_cast<float*>(p + off); off += align256(size_t(d.BH()) * d.N * 4);
     }
     if (bwd && d.kind == 1) { w.dg_tok = reinterpret_cast<float*>(p + off); off += align256(size_t(d.BH()) * d.N * 4); }  // per-chunk sums
-    if (d.save) { w.states_t = reinterpret_cast<uint16_t*>(p + off); off += st; }
     w.bytes = off;
     return w;
 }
@@ -822,7 +772,7 @@ namespace {
 template <int MODE>
 hipError_t launch_state(const Dims& d, hipStream_t st, const StateArgs& sa) {
     const dim3 sgrid(D / 32 * d.seqs() * (sa.seg_n > 1 ? sa.seg_n : 1)), block(kThreads);
-    const int lds = kStateLdsNone;
+    const int lds = kStateLds;
     hipError_t e;
     if (d.kind == 0) {
         if ((e = allow_lds(mk_state_seq<MODE, false>, lds)) != hipSuccess) return e;
@@ -858,22 +808,15 @@ hipError_t vec_fwd(const Dims& d, const FwdArgs& a) {
     if ((e = launch_vec_prep(d, a.stream, q, k, a.g, w)) != hipSuccess) return e;
     {
         ProfScope ps(KID_MFMA_STATE, a.stream);
-        if ((e = allow_lds(mk_state_vec<3>, kStateLdsPlain)) != hipSuccess) return e;
-        const dim3 sgrid(D / 32 * d.seqs() * nvh);
-        if (d.save) {
-            if ((e = allow_lds(mk_state_vec<3, true>, kStateLdsPlain)) != hipSuccess) return e;
-            StateArgs sa{v, w.khat_hi, nullptr, w.lamv, w.states_t, w.states_rem, a.m0, a.mT, w.khat_lo, d.dv, nvh, w.states};
-            hipLaunchKernelGGL((mk_state_vec<3, true>), sgrid, dim3(kThreads), kStateLdsPlain, a.stream, d, sa);
-        } else {
-            StateArgs sa{v, w.khat_hi, nullptr, w.lamv, w.states, nullptr, a.m0, a.mT, w.khat_lo, d.dv, nvh};
-            hipLaunchKernelGGL(mk_state_vec<3>, sgrid, dim3(kThreads), kStateLdsPlain, a.stream, d, sa);
-        }
+        if ((e = allow_lds(mk_state_vec<1>, kStateLds)) != hipSuccess) return e;
+        const StateArgs sa{v, w.khat_hi, nullptr, w.lamv, w.states, d.save ? w.states_rem : nullptr, a.m0, a.mT, w.khat_lo, d.dv, nvh};
+        hipLaunchKernelGGL(mk_state_vec<1>, dim3(D / 32 * d.seqs() * nvh), dim3(kThreads), kStateLds, a.stream, d, sa);
     }
     {
         ProfScope ps(KID_MFMA_OUTPUT, a.stream);
         if ((e = allow_lds(mk_output_vec<false>, kOutVecLds)) != hipSuccess) return e;
         hipLaunchKernelGGL(mk_output_vec<false>, dim3(d.N * nvh, d.BH()), dim3(kThreads), kOutVecLds, a.stream, d, w.qhat_hi, w.qhat_lo, v,
-                           w.p_hi, w.p_lo, w.states_t, static_cast<uint16_t*>(a.o));
+                           w.p_hi, w.p_lo, w.states, static_cast<uint16_t*>(a.o));
     }
     return hipGetLastError();
 }
@@ -1049,29 +992,24 @@ hipError_t vec_bwd(const Dims& d, const BwdArgs& a) {
     if (d.save) {  // the decayed operand planes, the scores and the states are the forward call's
         ProfScope ps(KID_MFMA_DSTATE, a.stream);
         const StateArgs s2{d_o, w.qhat_hi, nullptr, w.lamv, w.dstates, a.dg ? w.dstates_rem : nullptr, a.d_mT, a.d_m0,
-                           w.qhat_lo, d.dv, nvh, w.dstates_t};
-        if ((e = allow_lds(mk_state_vec_rev, kStateLdsPlain)) != hipSuccess) return e;
-        hipLaunchKernelGGL(mk_state_vec_rev, dim3(D / 32 * d.seqs() * nvh), dim3(kThreads), kStateLdsPlain, a.stream, d, s2);
+                           w.qhat_lo, d.dv, nvh};
+        if ((e = allow_lds(mk_state_vec<2>, kStateLds)) != hipSuccess) return e;
+        hipLaunchKernelGGL(mk_state_vec<2>, dim3(D / 32 * d.seqs() * nvh), dim3(kThreads), kStateLds, a.stream, d, s2);
     } else {
         ProfScope ps(KID_MFMA_STATE_BWD, a.stream);
         const StateArgs s1{v, w.khat_hi, nullptr, w.lamv, w.states, a.dg ? w.states_rem : nullptr, a.m0, nullptr,
                            w.khat_lo, d.dv, nvh};
         const StateArgs s2{d_o, w.qhat_hi, nullptr, w.lamv, w.dstates, a.dg ? w.dstates_rem : nullptr, a.d_mT, a.d_m0,
-                           w.qhat_lo, d.dv, nvh, w.dstates_t};
+                           w.qhat_lo, d.dv, nvh};
         const dim3 sgrid(D / 32 * d.seqs() * nvh, 2);
-        if (a.dg) {
-            if ((e = allow_lds(mk_state_pair_vec<true>, kStateLdsPlain)) != hipSuccess) return e;
-            hipLaunchKernelGGL(mk_state_pair_vec<true>, sgrid, dim3(kThreads), kStateLdsPlain, a.stream, d, s1, s2);
-        } else {
-            if ((e = allow_lds(mk_state_pair_vec<false>, kStateLdsPlain)) != hipSuccess) return e;
-            hipLaunchKernelGGL(mk_state_pair_vec<false>, sgrid, dim3(kThreads), kStateLdsPlain, a.stream, d, s1, s2);
-        }
+        if ((e = allow_lds(mk_state_pair_vec, kStateLds)) != hipSuccess) return e;
+        hipLaunchKernelGGL(mk_state_pair_vec, sgrid, dim3(kThreads), kStateLds, a.stream, d, s1, s2);
     }
     {
         ProfScope ps(KID_MFMA_VEC_DV, a.stream);
         if ((e = allow_lds(mk_output_vec<true>, kOutVecLds)) != hipSuccess) return e;
         hipLaunchKernelGGL(mk_output_vec<true>, dim3(d.N * nvh, d.BH()), dim3(kThreads), kOutVecLds, a.stream, d, w.khat_hi,
-                           w.khat_lo, d_o, w.p_hi, w.p_lo, w.dstates_t, static_cast<uint16_t*>(a.dv));
+                           w.khat_lo, d_o, w.p_hi, w.p_lo, w.dstates, static_cast<uint16_t*>(a.dv));
     }
     {
         ProfScope ps(KID_MFMA_GRAD, a.stream);

@@ -253,17 +253,7 @@ __global__ __launch_bounds__(kThreads, 2) void mk_vec_prep(Dims d, const uint16_
     }
 }
 
-// 64 x 128 bf16 tile out of rows of `stride` elements starting at column `col0`; rows >= L zero
-__device__ __forceinline__ void load_tile_strided(uint16_t* dst, const uint16_t* src, size_t tok0, int ts, int L, int stride,
-                                                  int col0, int tid) {
-    _Pragma("unroll") for (int it = 0; it < 4; ++it) {
-        const int p = tid + kThreads * it, row = p >> 4, cp = p & 15;
-        const u32x4 v = __builtin_nontemporal_load(
-            reinterpret_cast<const u32x4*>(src + (tok0 + size_t(min(row, L - 1)) * ts) * stride + col0 + cp * 8));
-        const uint32_t keep = row < L ? 0xffffffffu : 0u;
-        *reinterpret_cast<u32x4*>(dst + row * LD + cp * 8) = u32x4{v.x & keep, v.y & keep, v.z & keep, v.w & keep};
-    }
-}
+// LDS tile rows [0, L) -> rows of `stride` elements starting at column `col0`
 __device__ __forceinline__ void store_tile_strided(uint16_t* dst, const uint16_t* src, size_t tok0, int ts, int L, int stride,
                                                    int col0, int tid) {
     _Pragma("unroll") for (int it = 0; it < 4; ++it) {
@@ -273,14 +263,6 @@ __device__ __forceinline__ void store_tile_strided(uint16_t* dst, const uint16_t
                                         reinterpret_cast<u32x4*>(dst + (tok0 + size_t(row) * ts) * stride + col0 + cp * 8));
     }
 }
-// 64 x 64 bf16 matrix (dense rows) -> LDS tile with row stride LDP
-__device__ __forceinline__ void load_scores(uint16_t* dst, const uint16_t* src, int tid) {
-    _Pragma("unroll") for (int it = 0; it < 2; ++it) {
-        const int p = tid + kThreads * it, row = p >> 3, cp = p & 7;
-        *reinterpret_cast<u32x4*>(dst + row * LDP + cp * 8) = *reinterpret_cast<const u32x4*>(src + row * C + cp * 8);
-    }
-}
-
 // ---------------------------------------------------------------------------------------------
 // Output of one chunk for one 128-wide slice of the value dimension (grid: N d_v/128 x BH; the slices of a chunk, which read the
 // same qhat and P, are eight workgroups apart, on the same die and at the same time; d_v = 256, 4 x 16 sequences of 4096, with one
@@ -289,9 +271,14 @@ __device__ __forceinline__ void load_scores(uint16_t* dst, const uint16_t* src, 
 // with qhat and P from mk_vec_prep.  Wave w owns 32 value columns.
 // DV = true computes with the same structure the value gradient
 //   dv^T[v][r] = sum_i dS^T[v][i] khat_r[i] + sum_{j>=r} dO^T[v][j] P[j][r]
-// (states = dS^T, qhat = khat, v = d_o; P is read through the LDS transpose read).
+// (states = dS, qhat = khat, v = d_o; P is read through the LDS transpose read).
+// The states lie in memory with their key features as rows, as mk_grad_vec reads them; here the key features are contracted, so the
+// slice passes through LDS first, rows of 128 values over V and P, and comes back by columns.  With a second, transposed copy of every
+// state for these two kernels alone, and their rows requested tile by tile: d_v = 256, 4 x 16 sequences of 4096, scans 214 and
+// 209 us, output 129, value gradient 204; this 176, 156, 118, 115.
 // LDS: qhat head (later the O stage) | qhat remainder | V slice | P head | P remainder
 constexpr int kOutVecLds = 3 * C * LD * 2 + 2 * C * LDP * 2;
+static_assert(D * LD <= C * LD + 2 * C * LDP, "a state slice fits the area of V and P");
 
 template <bool DV>
 __global__ __launch_bounds__(kThreads, 2) void mk_output_vec(Dims d, const uint16_t* __restrict__ qhat,
@@ -318,17 +305,37 @@ __global__ __launch_bounds__(kThreads, 2) void mk_output_vec(Dims d, const uint1
     const int ts = pos.ts;
     const int n = lane & 31, half = lane >> 5;
 
-    const uint16_t* St = states + (pos.slot * nvh + vh) * D * D;
-    bf16x8 sfrag[8];
-    _Pragma("unroll") for (int ks = 0; ks < 8; ++ks)
-        sfrag[ks] = *reinterpret_cast<const bf16x8*>(St + state_frag_off(wave, ks, lane));
-
-    load_tile(Q, qhat, wtok0, 1, L, tid);  // the library's own planes
-    load_tile(Ql, qhat_lo, wtok0, 1, L, tid);
-    load_tile_strided(V, v, tok0, ts, L, d.dv, D * vh, tid);
+    // every row is requested before the first wait
+    const uint16_t* Sg = states + (pos.slot * nvh + vh) * D * D;
+    uint16_t* St = V;  // [128][LD]
+    u32x4 rs[8], rv[4], rp[4];
+    TileRegs rq, rl;
+    _Pragma("unroll") for (int it = 0; it < 8; ++it) rs[it] = *reinterpret_cast<const u32x4*>(Sg + 8 * (tid + kThreads * it));
+    tile_gload(rq, qhat, wtok0, 1, L, tid);  // the library's own planes
+    tile_gload(rl, qhat_lo, wtok0, 1, L, tid);
     const size_t poff = pos.slot * C * C;
-    load_scores(Ph, p_hi + poff, tid);
-    load_scores(Pl, p_lo + poff, tid);
+    _Pragma("unroll") for (int it = 0; it < 4; ++it) {
+        const int p = tid + kThreads * it, row = p >> 4, cp = p & 15;
+        rv[it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v + (tok0 + size_t(min(row, L - 1)) * ts) * d.dv + D * vh + cp * 8));
+        rp[it] = *reinterpret_cast<const u32x4*>((it < 2 ? p_hi : p_lo) + poff + 8 * (tid + kThreads * (it & 1)));
+    }
+    _Pragma("unroll") for (int it = 0; it < 8; ++it) {  // fragment order: 32 rows of 8 values each, state_frag_off
+        const int p = tid + kThreads * it, l = p & 63;
+        *reinterpret_cast<u32x4*>(St + (32 * (p >> 9) + (l & 31)) * LD + 16 * ((p >> 6) & 7) + 8 * (l >> 5)) = rs[it];
+    }
+    tile_commit(Q, rq, L, tid);
+    tile_commit(Ql, rl, L, tid);
+    __syncthreads();
+    bf16x8 sfrag[8];
+    _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) sfrag[ks] = frag_tr(St, LD, 16 * ks, 32 * wave, lane);
+    __syncthreads();  // the state slice is in registers; V and P take its place
+    _Pragma("unroll") for (int it = 0; it < 4; ++it) {
+        const int p = tid + kThreads * it, row = p >> 4, cp = p & 15;
+        const uint32_t keep = row < L ? 0xffffffffu : 0u;
+        *reinterpret_cast<u32x4*>(V + row * LD + cp * 8) = u32x4{rv[it].x & keep, rv[it].y & keep, rv[it].z & keep, rv[it].w & keep};
+        const int q = tid + kThreads * (it & 1);
+        *reinterpret_cast<u32x4*>((it < 2 ? Ph : Pl) + (q >> 3) * LDP + 8 * (q & 7)) = rp[it];
+    }
     __syncthreads();
 
     PackedBlock res[2];
