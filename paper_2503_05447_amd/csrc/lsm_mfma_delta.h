@@ -59,25 +59,6 @@ __device__ __forceinline__ bf16x8 frag_tr_perm(const uint16_t* tile, int ld, int
     const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 8 * ld)));
     return __builtin_bit_cast(bf16x8, u32x4{lo.x, lo.y, hi.x, hi.y});
 }
-// registers 8p .. 8p+7 of a D-layout block as an operand of the next product (k = its rows), head and remainder
-__device__ __forceinline__ void split_frag(const f32x16& x, int p, u32x4& hi, u32x4& lo) {
-    _Pragma("unroll") for (int e = 0; e < 4; ++e) {
-        const float x0 = x[8 * p + 2 * e], x1 = x[8 * p + 2 * e + 1];
-        hi[e] = pack2(x0, x1);
-        lo[e] = pack2(x0 - bf16_lo(hi[e]), x1 - bf16_hi(hi[e]));
-    }
-}
-// ... and such an operand to LDS by rows: lane = column, so neighbouring lanes exchange halves and store two columns at once.
-// dst: row 0, column 0 of the 16 rows and 32 columns
-__device__ __forceinline__ void store_frag_rows(uint16_t* dst, int ld, const u32x4& w, int n, int half) {
-    const bool odd = n & 1;
-    uint16_t* p = dst + (4 * half + (odd ? 1 : 0)) * ld + (n & ~1);
-    const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
-    _Pragma("unroll") for (int e = 0; e < 4; ++e) {
-        const uint32_t other = __builtin_amdgcn_mov_dpp(int(w[e]), 0xB1, 0xf, 0xf, true);  // lane ^ 1
-        *reinterpret_cast<uint32_t*>(p + (8 * (e >> 1) + 2 * (e & 1)) * ld) = __builtin_amdgcn_perm(other, w[e], sel);
-    }
-}
 // weights of the rows of registers 8p .. 8p+7 of a D-layout block at row0 - 16p
 __device__ __forceinline__ void row_weights(const float* tab, int row0, int half, float (&w)[8]) {
     const float4 a = *reinterpret_cast<const float4*>(tab + row0 + 4 * half), b = *reinterpret_cast<const float4*>(tab + row0 + 8 + 4 * half);

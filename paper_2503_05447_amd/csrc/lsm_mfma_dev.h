@@ -94,16 +94,28 @@ __device__ __forceinline__ void store_block_t_split(uint16_t* hi, uint16_t* lo, 
 // one term of the decay gradient), so it is kept as 8-bit floats (1-5-2), scaled by 2^8 to stay clear
 // of their underflow: x = head + 2^-8 * rem8 to about 2^-12 relative, in three bytes per element.
 constexpr float kRem8Scale = 256.f, kRem8Unscale = 1.f / 256.f;
-typedef float f32x2v __attribute__((ext_vector_type(2)));
-// 8 such bytes -> bf16 operand (exact: the 8-bit values have two mantissa bits); still scaled by 2^8
+// 8 such bytes -> bf16 operand, the scale taken out (exact: the 8-bit values have two mantissa bits)
 __device__ __forceinline__ bf16x8 rem8_to_bf16(u32x2 raw) {
     u32x4 v;
     _Pragma("unroll") for (int p = 0; p < 2; ++p) {
-        const f32x2v a = __builtin_amdgcn_cvt_pk_f32_bf8(int(raw[p]), false), b = __builtin_amdgcn_cvt_pk_f32_bf8(int(raw[p]), true);
-        v[2 * p] = pack2(a.x, a.y);
-        v[2 * p + 1] = pack2(b.x, b.y);
+        v[2 * p] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8(raw[p], kRem8Unscale, false));
+        v[2 * p + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8(raw[p], kRem8Unscale, true));
     }
     return __builtin_bit_cast(bf16x8, v);
+}
+// running sum over the lanes of each half of a wave (lane 31 of a half has the total): four steps inside rows of 16, then the first
+// row's total to the second; an addition each, where a shuffle through LDS takes three more instructions and its latency
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float lanes_below(float x) {
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, int(__float_as_uint(x)), CTRL, ROWS, 0xf, ROWS == 0xf));
+}
+__device__ __forceinline__ float half_prefix(float x) {
+    x += lanes_below<0x111, 0xf>(x);  // row_shr:1, 2, 4, 8
+    x += lanes_below<0x112, 0xf>(x);
+    x += lanes_below<0x114, 0xf>(x);
+    x += lanes_below<0x118, 0xf>(x);
+    x += lanes_below<0x142, 0xa>(x);  // row_bcast:15
+    return x;
 }
 
 // 64 x 128 bf16 tile: global rows [tok0, tok0+L) -> LDS (row stride LD), rows >= L zero
@@ -157,5 +169,24 @@ __device__ __forceinline__ void store_packed(uint16_t* dst, int ld, int nrow, in
         *reinterpret_cast<u32x2*>(dst + nrow * ld + m0 + 8 * g + 4 * half) = p.v[g];
 }
 
+// registers 8p .. 8p+7 of a D-layout block as an operand of the next product (k = its rows), head and remainder
+__device__ __forceinline__ void split_frag(const f32x16& x, int p, u32x4& hi, u32x4& lo) {
+    _Pragma("unroll") for (int e = 0; e < 4; ++e) {
+        const float x0 = x[8 * p + 2 * e], x1 = x[8 * p + 2 * e + 1];
+        hi[e] = pack2(x0, x1);
+        lo[e] = pack2(x0 - bf16_lo(hi[e]), x1 - bf16_hi(hi[e]));
+    }
+}
+// ... and such an operand to LDS by rows: lane = column, so neighbouring lanes exchange halves and store two columns at once.
+// dst: row 0, column 0 of the 16 rows and 32 columns
+__device__ __forceinline__ void store_frag_rows(uint16_t* dst, int ld, const u32x4& w, int n, int half) {
+    const bool odd = n & 1;
+    uint16_t* p = dst + (4 * half + (odd ? 1 : 0)) * ld + (n & ~1);
+    const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+    _Pragma("unroll") for (int e = 0; e < 4; ++e) {
+        const uint32_t other = __builtin_amdgcn_mov_dpp(int(w[e]), 0xB1, 0xf, 0xf, true);  // lane ^ 1
+        *reinterpret_cast<uint32_t*>(p + (8 * (e >> 1) + 2 * (e & 1)) * ld) = __builtin_amdgcn_perm(other, w[e], sel);
+    }
+}
 }  // namespace
 }  // namespace lsm

@@ -368,7 +368,8 @@ __global__ __launch_bounds__(kThreads, 2) void mk_output_vec(Dims d, const uint1
 }
 
 // ---------------------------------------------------------------------------------------------
-// dq, dk and the decay gradient of one chunk (grid: N x BH), vector decay kind.
+// dq, dk and the decay gradient, chunk by chunk (grid: up to one workgroup per compute unit; each takes every gridDim.x-th chunk and
+// requests the next one's rows and states while it works on this one), vector decay kind.
 //   dA[j][r] = d_o_j . v_r  (r <= j),   Z[u][t] = dA[max(u,t)][min(u,t)]  (symmetric, 64 x 64)
 //   dq_j[i] = e^{b_j[i]} sum_v S[i][v] d_o_j[v]           + sum_{r<j} dA[j][r] k_r[i] e^{b_j[i]-b_r[i]} + dA[j][j] k_j[i]
 //   dk_r[i] = e^{b_C[i]-b_r[i]} sum_v dS[i][v] v_r[v]     + sum_{j>r} dA[j][r] q_j[i] e^{b_j[i]-b_r[i]} + dA[r][r] q_r[i]
@@ -381,6 +382,9 @@ __global__ __launch_bounds__(kThreads, 2) void mk_output_vec(Dims d, const uint1
 // and the long per-element weight arithmetic of one overlaps the waits of the other.  Z is built
 // once (waves 0..3: one 32 x 32 block each), summed over the 128-wide value slices, and kept in LDS
 // as bf16 head + remainder.
+// Bound: vector issue in the levels (25700 of 61500 clocks a chunk), a chunk's 393 KB (d_v = 256) in the inter parts (18000; 42000 at
+// the rate of a copy for all of it).  d_v = 256, 4 x 16 sequences of 4096: 630 us with a workgroup per chunk (its first rows waited for, 17000
+// of 76000 clocks), running sums by shuffles (7000) and <S, dS> on the vector ALU; 530 so.
 // LDS: b | Q | K | T0 (V slice, then W head, then dq stage) | T1 (d_o slice, W remainder, dk stage)
 //      | Z head | Z remainder | diagonal of dA | <S,dS> per feature | exchange between the two token blocks
 //      | second level-tile buffer (head, remainder)        -- 155 KiB in all
@@ -412,45 +416,61 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
     float* xch = zl + D;                                 // [3][4][32]: block-1 totals of the running sum, tail sums of both blocks
     uint16_t* W1 = reinterpret_cast<uint16_t*>(xch + 3 * 4 * 32);  // second level-tile buffer: head | remainder
 
-    const int c = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int wave = wv & 3, nb = wv >> 2;  // feature block, token block
-    const ChunkPos pos = chunk_pos(d, c, bh);
-    const int L = pos.L;
-    if (L <= 0) return;  // packed input: the grid is sized for an upper bound of the chunk count
-    const size_t tok0 = pos.tok0;
-    const int ts = pos.ts;
-    const int n = lane & 31, half = lane >> 5;
-    const int t = 32 * nb + n;  // this lane's token
+    // the wave index as a scalar: matrix instructions do not look at the lane mask, so a branch around them has to be a scalar one
+    int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wv & 3, nb = wv >> 2;  // feature block, token block
+    int n = lane & 31, half = lane >> 5;
+    // this lane's token, backward over the lanes: the decay gradient's running sum from the last token on is then one over the lanes
+    int t = 32 * nb + 31 - n;
+    // (as in mk_walk_grad: a phase's lane-dependent addresses are formed in the phase, not kept across the chunks)
+    auto fresh = [&]() {
+        asm volatile("" : "+v"(lane));
+        tid = 64 * wv + lane;
+        n = lane & 31;
+        half = lane >> 5;
+        t = 32 * nb + 31 - n;
+    };
     const int nvh = d.dv / D;
     const bool want_dg = dg != nullptr;  // then states_rem and dstates_rem are present
+
+    const int jobs = d.N * d.BH();
+    auto job_pos = [&](int job) { return chunk_pos(d, job % d.N, job / d.N); };
+    // this workgroup's next chunk from `job` on (packed input: N is an upper bound of the chunk count)
+    auto next_job = [&](int job, ChunkPos& p) {
+        for (; job < jobs; job += gridDim.x) {
+            p = job_pos(job);
+            if (p.L > 0) break;
+        }
+        return job;
+    };
 
     // 64 x 128 tiles move as 1024 16-byte pieces, two per thread
     auto tile_rows = [&](int it, int& row, int& cpp) { const int p = tid + NT * it; row = p >> 4; cpp = p & 15; };
     struct SliceRegs {
         u32x4 tv[2], to[2];
-        bf16x8 s[8], ds[8];
-        u32x2 sr[8], dsr[8];  // remainder planes: 8-bit floats, still scaled by 2^8
+        bf16x8 s[4], ds[4];   // four k-steps ahead (eight: 48 registers more, which the loop over chunks would spill)
+        u32x2 sr[4], dsr[4];  // remainder planes: 8-bit floats
     };
-    auto issue_tiles = [&](int vh, SliceRegs& r) {
+    auto issue_tiles = [&](const ChunkPos& p, int vh, SliceRegs& r) {
         _Pragma("unroll") for (int it = 0; it < 2; ++it) {
             int row, cpp;
             tile_rows(it, row, cpp);
-            const size_t off = (tok0 + size_t(min(row, L - 1)) * ts) * d.dv + D * vh + cpp * 8;
+            const size_t off = (p.tok0 + size_t(min(row, p.L - 1)) * p.ts) * d.dv + D * vh + cpp * 8;
             r.tv[it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v + off));
             r.to[it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(d_o + off));
         }
     };
     // this wave's rows of S, dS (both token blocks read the same rows) and their 8-bit remainder planes, k-step ks
-    auto issue_state = [&](int vh, int ks, SliceRegs& r) {
-        const size_t soff = (pos.slot * nvh + vh) * D * D + state_frag_off(wave, ks, lane);
-        r.s[ks] = *reinterpret_cast<const bf16x8*>(states + soff);
-        r.ds[ks] = *reinterpret_cast<const bf16x8*>(dstates + soff);
+    auto issue_state = [&](const ChunkPos& p, int vh, int ks, SliceRegs& r) {
+        const size_t soff = (p.slot * nvh + vh) * D * D + state_frag_off(wave, ks, lane);
+        r.s[ks & 3] = *reinterpret_cast<const bf16x8*>(states + soff);
+        r.ds[ks & 3] = *reinterpret_cast<const bf16x8*>(dstates + soff);
         if (want_dg) {
-            r.sr[ks] = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(states_rem) + soff);
-            r.dsr[ks] = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(dstates_rem) + soff);
+            r.sr[ks & 3] = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(states_rem) + soff);
+            r.dsr[ks & 3] = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(dstates_rem) + soff);
         }
     };
-    auto commit = [&](const SliceRegs& r) {
+    auto commit = [&](const SliceRegs& r, int L) {
         _Pragma("unroll") for (int it = 0; it < 2; ++it) {
             int row, cpp;
             tile_rows(it, row, cpp);
@@ -459,35 +479,45 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
             *reinterpret_cast<u32x4*>(T1 + row * LD + cpp * 8) = u32x4{r.to[it].x & keep, r.to[it].y & keep, r.to[it].z & keep, r.to[it].w & keep};
         }
     };
-    // ---- q, k, g and the first value slice: every load issued before the first wait
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    struct RowRegs { u32x4 q[2], k[2]; f32x4 g[2][2]; } in;
+    auto issue_rows = [&](const ChunkPos& p) {
+        _Pragma("unroll") for (int it = 0; it < 2; ++it) {
+            int row, cpp;
+            tile_rows(it, row, cpp);
+            const size_t roff = (p.tok0 + size_t(min(row, p.L - 1)) * p.ts) * D + cpp * 8;
+            in.q[it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(q + roff));
+            in.k[it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k + roff));
+            in.g[it][0] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(g + roff));
+            in.g[it][1] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(g + roff + 4));
+        }
+    };
     SliceRegs sr0;
-    {
-        u32x4 tq[2], tk[2];
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
-        f32x4 tg[2][2];
-        _Pragma("unroll") for (int it = 0; it < 2; ++it) {
-            int row, cpp;
-            tile_rows(it, row, cpp);
-            const size_t roff = (tok0 + size_t(min(row, L - 1)) * ts) * D + cpp * 8;
-            tq[it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(q + roff));
-            tk[it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k + roff));
-            tg[it][0] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(g + roff));
-            tg[it][1] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(g + roff + 4));
-        }
-        issue_tiles(0, sr0);
-        _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) issue_state(0, ks, sr0);
-        _Pragma("unroll") for (int it = 0; it < 2; ++it) {
-            int row, cpp;
-            tile_rows(it, row, cpp);
-            const uint32_t keep = row < L ? 0xffffffffu : 0u;
-            const float kf = row < L ? 1.f : 0.f;
-            *reinterpret_cast<u32x4*>(Qr + row * LD + cpp * 8) = u32x4{tq[it].x & keep, tq[it].y & keep, tq[it].z & keep, tq[it].w & keep};
-            *reinterpret_cast<u32x4*>(Kr + row * LD + cpp * 8) = u32x4{tk[it].x & keep, tk[it].y & keep, tk[it].z & keep, tk[it].w & keep};
-            *reinterpret_cast<float4*>(bt + row * LDF + cpp * 8) = float4{tg[it][0].x * kf, tg[it][0].y * kf, tg[it][0].z * kf, tg[it][0].w * kf};
-            *reinterpret_cast<float4*>(bt + row * LDF + cpp * 8 + 4) = float4{tg[it][1].x * kf, tg[it][1].y * kf, tg[it][1].z * kf, tg[it][1].w * kf};
-        }
+    ChunkPos pos{}, ahead{};
+    int job = next_job(blockIdx.x, pos);
+    if (job >= jobs) return;
+    issue_rows(pos);
+    issue_tiles(pos, 0, sr0);
+    _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) issue_state(pos, 0, ks, sr0);
+  for (; job < jobs; pos = ahead) {
+    const int L = pos.L, ts = pos.ts;
+    const size_t tok0 = pos.tok0;
+    ahead = pos;
+    job = next_job(job + gridDim.x, ahead);
+    if (job >= jobs) ahead = pos;
+    fresh();
+    _Pragma("unroll") for (int it = 0; it < 2; ++it) {
+        int row, cpp;
+        tile_rows(it, row, cpp);
+        const uint32_t keep = row < L ? 0xffffffffu : 0u;
+        const float kf = row < L ? 1.f : 0.f;
+        *reinterpret_cast<u32x4*>(Qr + row * LD + cpp * 8) = u32x4{in.q[it].x & keep, in.q[it].y & keep, in.q[it].z & keep, in.q[it].w & keep};
+        *reinterpret_cast<u32x4*>(Kr + row * LD + cpp * 8) = u32x4{in.k[it].x & keep, in.k[it].y & keep, in.k[it].z & keep, in.k[it].w & keep};
+        *reinterpret_cast<float4*>(bt + row * LDF + cpp * 8) = float4{in.g[it][0].x * kf, in.g[it][0].y * kf, in.g[it][0].z * kf, in.g[it][0].w * kf};
+        *reinterpret_cast<float4*>(bt + row * LDF + cpp * 8 + 4) = float4{in.g[it][1].x * kf, in.g[it][1].y * kf, in.g[it][1].z * kf, in.g[it][1].w * kf};
     }
     __syncthreads();
+    fresh();
     {   // inclusive scan of g along tokens: one feature column per thread, four quarters of 16 tokens
         const int i = tid & 127, hq = tid >> 7;
         float run = 0.f;
@@ -508,33 +538,35 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
     // aqr, akr: contributions of the remainder planes of S and dS; they enter the decay gradient only, so
     // that dq and dk do not depend on whether it is asked for
     f32x16 aq = {0}, aqr = {0}, ak = {0}, akr = {0};
-    f32x16 z0 = {0}, z1 = {0};
-    float zi = 0.f;
+    f32x16 z0 = {0};  // waves 0..3: Z; waves 4..7: S dS^T
     // The next slice takes the registers of this one as they are used up, so that no trip to memory stands between the
     // slices (d_v = 256, 4 x 16 sequences of 4096: 0.648 -> 0.624 ms).
     for (int vh = 0; vh < nvh; ++vh) {
         if (vh > 0) __syncthreads();  // the previous slice is consumed
-        commit(sr0);
+        fresh();
+        commit(sr0, L);
         __syncthreads();
-        if (vh + 1 < nvh) issue_tiles(vh + 1, sr0);
+        fresh();
+        if (vh + 1 < nvh) issue_tiles(pos, vh + 1, sr0);
         _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) {
-            const bf16x8 sf = sr0.s[ks], dsf = sr0.ds[ks];
+            const bf16x8 sf = sr0.s[ks & 3], dsf = sr0.ds[ks & 3];
             const bf16x8 dof = frag(T1, LD, t, 16 * ks + 8 * half), vf = frag(T0, LD, t, 16 * ks + 8 * half);
             aq = mfma(sf, dof, aq);
             ak = mfma(dsf, vf, ak);
             if (want_dg) {
-                const bf16x8 srf = rem8_to_bf16(sr0.sr[ks]), dsrf = rem8_to_bf16(sr0.dsr[ks]);
+                const bf16x8 srf = rem8_to_bf16(sr0.sr[ks & 3]), dsrf = rem8_to_bf16(sr0.dsr[ks & 3]);
                 aqr = mfma(srf, dof, aqr);
                 akr = mfma(dsrf, vf, akr);
-                if (nb == 0) {  // <S, dS> over this lane's share of row i = 32 wave + n
-                    const u32x4 a = __builtin_bit_cast(u32x4, sf), ar = __builtin_bit_cast(u32x4, srf);
-                    const u32x4 b = __builtin_bit_cast(u32x4, dsf), br = __builtin_bit_cast(u32x4, dsrf);
-                    _Pragma("unroll") for (int p = 0; p < 4; ++p)
-                        zi += (bf16_lo(a[p]) + kRem8Unscale * bf16_lo(ar[p])) * (bf16_lo(b[p]) + kRem8Unscale * bf16_lo(br[p])) +
-                              (bf16_hi(a[p]) + kRem8Unscale * bf16_hi(ar[p])) * (bf16_hi(b[p]) + kRem8Unscale * bf16_hi(br[p]));
+                // <S, dS> of every key feature, the diagonal of S dS^T (on the vector ALU: 60 instructions a k-step)
+                if (nb == 1) {
+                    z0 = mfma(srf, dsrf, z0);
+                    z0 = mfma(srf, dsf, z0);
+                    z0 = mfma(sf, dsrf, z0);
+                    z0 = mfma(sf, dsf, z0);
                 }
             }
-            if (vh + 1 < nvh) issue_state(vh + 1, ks, sr0);
+            if (ks < 4) issue_state(pos, vh, ks + 4, sr0);
+            else if (vh + 1 < nvh) issue_state(pos, vh + 1, ks - 4, sr0);
         }
         if (wv < 4) {  // this wave's block of Z: rows of V and d_o as operands
             const int rowv = wv == 1 ? 32 + n : n;               // V row: wave 0, 2, 3: 0.., wave 1: 32..
@@ -543,18 +575,30 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
                 const bf16x8 fv = frag(T0, LD, rowv, 16 * ks + 8 * half), fo = frag(T1, LD, rowo, 16 * ks + 8 * half);
                 if (wv == 3) z0 = mfma(fo, fv, z0);              // D[m][n] = d_o_{32+m} . v_n
                 else z0 = mfma(fv, fo, z0);                      // D[m][n] = v_m . d_o_n
-                if (wv < 2) z1 = mfma(fo, fv, z1);               // D[m][n] = d_o_m . v_n
             }
         }
     }
+    fresh();
     if (wv < 4) {  // Z[u][t] -> LDS rows t, head and remainder; diagonal of dA
         const int ub = (wv == 1 || wv == 3) ? 1 : 0, tb = (wv == 1 || wv == 2) ? 1 : 0;
         if (wv < 2) {
-            _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-                const int m = 8 * (x >> 2) + 4 * half + (x & 3);
-                if (m == n) zd[32 * wv + n] = z0[x];
-                z0[x] = m <= n ? z0[x] : z1[x];
+            // the other triangle is the transpose: the block once by columns, a lane's pieces of it back by rows
+            _Pragma("unroll") for (int p = 0; p < 2; ++p) {
+                u32x4 h, l;
+                split_frag(z0, p, h, l);
+                store_frag_rows(Zh + (32 * wv + 16 * p) * LDP + 32 * wv, LDP, h, n, half);
+                store_frag_rows(Zl + (32 * wv + 16 * p) * LDP + 32 * wv, LDP, l, n, half);
             }
+            __builtin_amdgcn_wave_barrier();
+            _Pragma("unroll") for (int x = 0; x < 16; ++x)
+                if (8 * (x >> 2) + 4 * half + (x & 3) == n) zd[32 * wv + n] = z0[x];
+            _Pragma("unroll") for (int g4 = 0; g4 < 4; ++g4) {
+                const int m0 = 8 * g4 + 4 * half, off = (32 * wv + n) * LDP + 32 * wv + m0;
+                const u32x2 h = *reinterpret_cast<const u32x2*>(Zh + off), l = *reinterpret_cast<const u32x2*>(Zl + off);
+                const float y[4] = {bf16_lo(h.x) + bf16_lo(l.x), bf16_hi(h.x) + bf16_hi(l.x), bf16_lo(h.y) + bf16_lo(l.y), bf16_hi(h.y) + bf16_hi(l.y)};
+                _Pragma("unroll") for (int j = 0; j < 4; ++j) z0[4 * g4 + j] = m0 + j <= n ? z0[4 * g4 + j] : y[j];
+            }
+            __builtin_amdgcn_wave_barrier();
         }
         store_block_t_split(Zh, Zl, LDP, 32 * tb + n, 32 * ub, half, z0);
     }
@@ -571,13 +615,15 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
             const int x = 4 * gq + jj;
             const float wq = __expf(bb[jj]), wk = __expf(cc[jj] - bb[jj]);
             aq[x] *= wq;
-            aqr[x] *= wq * kRem8Unscale;
+            aqr[x] *= wq;
             ak[x] *= wk;
-            akr[x] *= wk * kRem8Unscale;
+            akr[x] *= wk;
             xk[x] = kf[jj] * (ak[x] + akr[x]);
         }
     }
-    if (want_dg && nb == 0) {
+    if (want_dg && nb == 1) {
+        float zi = 0.f;
+        _Pragma("unroll") for (int x = 0; x < 16; ++x) zi += 8 * (x >> 2) + 4 * half + (x & 3) == n ? z0[x] : 0.f;
         zi += __shfl_xor(zi, 32, 64);
         if (half == 0) zl[32 * wave + n] = zi;
     }
@@ -586,12 +632,13 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
     // token blocks 0 and 1) take the two halves of an iteration in opposite order: while one builds
     // the tile of the next level (exponentials on the vector ALU) the other contracts the current one
     // (LDS reads, MFMA), instead of both queueing for the same unit.
-    const int cp = tid & 15, r0 = tid >> 4;  // W rows r0 and r0 + 32, features 8 cp .. + 7
     auto Wh = [&](int lv) { return (lv & 1) ? W1 : T0; };
     auto Wl = [&](int lv) { return (lv & 1) ? W1 + C * LD : T1; };
     auto build = [&](int lv) {
         const int ls = 5 - lv;
         uint16_t *wh = Wh(lv), *wl = Wl(lv);
+        fresh();
+        const int cp = tid & 15, r0 = tid >> 4;  // W rows r0 and r0 + 32, features 8 cp .. + 7
         _Pragma("unroll") for (int it = 0; it < 2; ++it) {
             const int row = r0 + 32 * it;
             bool qside;
@@ -611,6 +658,7 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
     auto contract = [&](int lv) {
         const int ls = 5 - lv;
         const uint16_t *wh = Wh(lv), *wl = Wl(lv);
+        fresh();
         const int ub = ls == 5 ? 1 - nb : nb;  // the partners of level 32 sit in the other 32-block
         f32x16 X = {0};
         _Pragma("unroll") for (int s2 = 0; s2 < 2; ++s2) {
@@ -641,15 +689,19 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
             const float bb[4] = {b4.x, b4.y, b4.z, b4.w}, rr[4] = {r4.x, r4.y, r4.z, r4.w};
             _Pragma("unroll") for (int jj = 0; jj < 4; ++jj) {
                 const int x = 4 * gq + jj;
-                const float val = X[x] * level_weight(bb[jj], rr[jj], sl);
-                aq[x] += qside ? val : 0.f;
-                ak[x] += qside ? 0.f : val;
+                const float w = level_weight(bb[jj], rr[jj], sl);
+                aq[x] = fmaf(X[x], qside ? w : 0.f, aq[x]);
+                ak[x] = fmaf(X[x], qside ? 0.f : w, ak[x]);
             }
         }
     };
     __syncthreads();  // Z complete, V / d_o slices consumed
     build(0);
     __syncthreads();
+    // the next chunk's rows, under the levels (the last chunk's once more where there is none: behind a branch the registers'
+    // old contents would stay live)
+    issue_rows(ahead);
+    issue_tiles(ahead, 0, sr0);
     _Pragma("unroll") for (int lv = 0; lv < 6; ++lv) {
         if (nb == 0) {
             if (lv < 5) build(lv + 1);
@@ -661,6 +713,7 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
         __syncthreads();  // the next tile is complete, this one is free again
     }
     // ---- diagonal pairs, then the decay gradient from the unrounded accumulators
+    fresh();
     f32x16 wd;
     {
         const float dd = zd[t];
@@ -681,19 +734,13 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
     // (the barrier that ends the level loop: every wave is done with the level tiles)
     store_packed(T0, LD, t, 32 * wave, half, pack_block(aq));
     store_packed(T1, LD, t, 32 * wave, half, pack_block(ak));
+    fresh();
     if (want_dg) {
-        // per feature (register): inclusive suffix sum over this wave's 32 tokens (lanes of one half), the
-        // sum of this wave's tail terms; both go to the other token block through LDS
-        _Pragma("unroll") for (int off = 1; off < 32; off <<= 1) {
-            _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-                const float y = __shfl_down(wd[x], off, 32);
-                wd[x] += (n + off < 32) ? y : 0.f;
-            }
-        }
-        _Pragma("unroll") for (int off = 1; off < 32; off <<= 1) {
-            _Pragma("unroll") for (int x = 0; x < 16; ++x) xk[x] += __shfl_xor(xk[x], off, 32);
-        }
-        if (n == 0) {
+        // per feature (register): running sum over this wave's 32 tokens, the last one first, and the sum of this
+        // wave's tail terms; both go to the other token block through LDS
+        _Pragma("unroll") for (int x = 0; x < 16; ++x) wd[x] = half_prefix(wd[x]);
+        _Pragma("unroll") for (int x = 0; x < 16; ++x) xk[x] = half_prefix(xk[x]);
+        if (n == 31) {
             _Pragma("unroll") for (int x = 0; x < 16; ++x) {
                 const int f = 8 * (x >> 2) + 4 * half + (x & 3);
                 if (nb == 1) xch[(0 * 4 + wave) * 32 + f] = wd[x];   // total of token block 1
@@ -702,6 +749,7 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
         }
     }
     __syncthreads();  // stages and exchange complete; b no longer needed as weights
+    fresh();
     {
         int row, cpp;
         _Pragma("unroll") for (int it = 0; it < 2; ++it) {
@@ -720,11 +768,11 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
             const int col = 32 * wave + 8 * gq + 4 * half;
             const float4 c4 = *reinterpret_cast<const float4*>(bt + 63 * LDF + col);
             const float4 z4 = *reinterpret_cast<const float4*>(zl + col);
-            const float cc[4] = {c4.x, c4.y, c4.z, c4.w}, zz[4] = {z4.x, z4.y, z4.z, z4.w};
+            const float cc[4] = {c4.x, c4.y, c4.z, c4.w}, zf[4] = {z4.x, z4.y, z4.z, z4.w};
             _Pragma("unroll") for (int jj = 0; jj < 4; ++jj) {
                 const int x = 4 * gq + jj, f = 8 * gq + 4 * half + jj;
                 // tail over all 64 tokens (block 0 first), the state term, and for block 0 the running sum of block 1
-                add[x] = (xch[(1 * 4 + wave) * 32 + f] + xch[(2 * 4 + wave) * 32 + f]) + __expf(cc[jj]) * zz[jj] +
+                add[x] = (xch[(1 * 4 + wave) * 32 + f] + xch[(2 * 4 + wave) * 32 + f]) + __expf(cc[jj]) * zf[jj] +
                          (nb == 0 ? xch[(0 * 4 + wave) * 32 + f] : 0.f);
             }
         }
@@ -734,10 +782,15 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
                 float4{wd[4 * gq] + add[4 * gq], wd[4 * gq + 1] + add[4 * gq + 1], wd[4 * gq + 2] + add[4 * gq + 2],
                        wd[4 * gq + 3] + add[4 * gq + 3]};
         __syncthreads();
+        fresh();
         _Pragma("unroll") for (int it = 0; it < 4; ++it) {
             const int p = tid + NT * it, row = p >> 5, c4 = p & 31;
             if (row < L)
                 *reinterpret_cast<float4*>(dg + (tok0 + size_t(row) * ts) * D + 4 * c4) = *reinterpret_cast<const float4*>(bt + row * LDF + 4 * c4);
         }
     }
+    // the next chunk's first states, in the registers of the accumulators
+    _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) issue_state(ahead, 0, ks, sr0);
+    __syncthreads();  // the stages are read
+  }
 }

@@ -170,3 +170,29 @@ def test_packed_input_with_an_empty_sequence(case):
         for key in ("dq", "dk", "dv", "dg"):
             assert torch.equal(r[key][:, :, lo:hi], r_s[key]), key
         assert torch.equal(r["d_init_state"][s_:s_ + 1], r_s["d_init_state"])
+
+
+@pytest.mark.parametrize("dv", [128, 256])
+@pytest.mark.parametrize("lens", [[700], [130, 70, 0, 500]])
+def test_vector_kind_more_chunks_than_workgroups(dv, lens):
+    """The gradient kernel takes chunks in turn once there are more than 256 (330 and more here, the packed batch with chunk
+    indices that hold none between them): every head comes out bit for bit as among so few that each chunk has a workgroup."""
+    import torch
+    import paper_2503_05447_amd as pkg
+    kind, H, T, n = wl.KIND_VECTOR, 30, sum(lens), len(lens)
+    x = wl.make_inputs(1, H, T, 128, dv, kind, dtype="bf16", seed=990 + n, decay="weak")
+    rng = np.random.default_rng(991)
+    x["m0"] = (rng.standard_normal((n, H, 128, dv)) * 0.1).astype(np.float32)
+    x["d_mT"] = (rng.standard_normal((n, H, 128, dv)) * 0.1).astype(np.float32)
+    t = to_device(x)
+    cu = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).to(t["q"].device) if n > 1 else None
+
+    def run(lo, hi):
+        h = {k_: t[k_][:, lo:hi].contiguous() for k_ in ("q", "k", "v", "g", "m0", "d_o", "d_mT")}
+        return pkg.lsm_chunk_bwd(h["q"], h["k"], h["v"], h["g"], kind, h["d_o"], 64, h["m0"], h["d_mT"], cu_seqlens=cu)
+    whole = run(0, H)
+    for lo in range(0, H, 10):
+        part = run(lo, lo + 10)
+        torch.cuda.synchronize()
+        for key in ("dq", "dk", "dv", "dg", "d_init_state"):
+            assert torch.equal(whole[key][:, lo:lo + 10], part[key]), (key, lo)
