@@ -251,6 +251,11 @@ __device__ __forceinline__ f32x16 causal_product(const float* z, int ld, const f
     return X;
 }
 
+// Have a block in its registers here.  Left alone the compiler puts what is added to a block in every phase off until the block is
+// used, phases later, and keeps the operands instead: gk_walk_vec's outputs, five levels of them, went through scratch memory,
+// behind every store before (20000 of 43000 clocks a step, bf16, d_k = 64, d_v = 128).
+__device__ __forceinline__ void formed(f32x16& x) { asm volatile("" : "+v"(x)); }
+
 // What a workgroup walks.
 struct GWalk {
     SeqWalk walk;
@@ -1221,6 +1226,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                             const int r = hrow(x, l >> 5);
                             if (r < n && (r ^ n) >= lv && (r ^ n) < 2 * lv) P[x] = G[x];
                         }
+                        formed(P);
                         if constexpr (lv == 1) block_store(P);
                         __syncthreads();  // (L)
                     });
@@ -1231,6 +1237,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                     __syncthreads();  // (M)
                     const f32x16 X = causal_product(V + 32 * w, LV, P, fresh() & 63, [](int s, int p) { return s < p; });
                     _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] += X[x];
+                    formed(O);
                 } else {
                     block_store(score_part(K, Q, LQ));
                     O = inter(Q, LQ);
@@ -1252,6 +1259,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                             const f32x4 e = *reinterpret_cast<const f32x4*>(cur + n * LW + 32 * w + 8 * g + 4 * half);
                             _Pragma("unroll") for (int j = 0; j < 4; ++j) O[4 * g + j] += (n & lv) ? X[4 * g + j] * e[j] : 0.f;
                         }
+                        formed(O);
                         __syncthreads();  // (L)
                     });
                 }
