@@ -16,7 +16,7 @@
 // from the end of a whole segment needs no state per chunk, but the roundings of q.dq and k.dk add up over the way: 2-norm
 // error 2.2e-6 against 3.6e-7 with segments of 2048 tokens and a decay of e^-0.02 a token.)
 //
-// Contractions of the vector kind are v_mfma_f32_32x32x2_f32: fp32 operands, fp32 accumulation, 1/16 of the bf16 rate but exact
+// Contractions of the vector kind are v_mfma_f32_32x32x2_f32 (but where bf16 rows enter as they came, see gk_walk_vec): fp32 operands, fp32 accumulation, 1/16 of the bf16 rate but exact
 // products, and its operand layout is its result layout: lane l holds A[m = l%32][k = l/32], B[k = l/32][n = l%32], and result
 // register 4g+j of lane l is D[m = 8g + 4(l/32) + j][n = l%32].  Register x of a result block is therefore, unchanged, the
 // operand of one MFMA of the next product (its k index are the rows 8g+j and 8g+4+j), so states and scores feed the
@@ -25,10 +25,10 @@
 //
 // Bound: the vector ALU and its order with the matrix instructions.  Scalar kinds, 4 x 16 sequences of 2047 fp32 tokens, d = 128:
 // vector issue 55 %, matrix pipes 30 % of the walk (fp32 instructions alone: matrix pipes 54 %, the whole step 18 % longer); the
-// vector kind 38 % matrix pipes, 37 % vector.
+// vector kind its chain of phases: 26000 to 28000 clocks a step, of which each of the two groups works some 20000.
 // Forward + backward against one-thread-per-element kernels on the vector ALU with a state per chunk in memory, which this
 // family replaced, then with fp32 instructions throughout, now: that shape 11.6 ms, 0.731, 0.621; bf16 vector decay, 4 x 8
-// sequences of 2048, d_k = 64, d_v = 128: 7.2 ms, 0.442, 0.442; forward alone, 32 sequences of 1777, d = 64, bf16: 262 us, 50.7,
+// sequences of 2048, d_k = 64, d_v = 128: 7.2 ms, 0.442, 0.380; forward alone, 32 sequences of 1777, d = 64, bf16: 262 us, 50.7,
 // 43.5; 2 sequences of 256, d = 64, fp32: 110 us, 25.1, 23.6.
 // Distance to 64-bit results against the kernels on the vector ALU, 2-norm, weak to strong decays, 512 to 4096 tokens, chunks of 16
 // to 128: o, dq, dk, dv and d_init_state 0.4 to 0.95 times (one case 1.09), dg 0.1 to 0.85 times (vector kind in chunks of 16: 1.04),
@@ -62,6 +62,13 @@ __device__ __forceinline__ uint32_t bf16_bits(float x) {  // round to nearest ev
 __device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 __device__ __forceinline__ f32x4 load4(const uint16_t* p) {
     const u32x2 w = *reinterpret_cast<const u32x2*>(p);
+    return f32x4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u)};
+}
+// the same in two steps: as they lie in memory, then as numbers
+__device__ __forceinline__ f32x4 load4raw(const float* p) { return load4(p); }
+__device__ __forceinline__ u32x2 load4raw(const uint16_t* p) { return *reinterpret_cast<const u32x2*>(p); }
+__device__ __forceinline__ f32x4 numbers4(f32x4 v) { return v; }
+__device__ __forceinline__ f32x4 numbers4(u32x2 w) {
     return f32x4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u)};
 }
 __device__ __forceinline__ void store4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
@@ -218,33 +225,36 @@ __device__ __forceinline__ double state_dot(const f32x16 (&S)[KB], const float* 
 }
 __device__ __forceinline__ int hrow(int x, int half) { return 8 * (x >> 2) + 4 * half + (x & 3); }  // row of result register x
 
-// X[v][p] = sum_s Z[s][v] P[s][p]: the score block as B operand out of its registers, `z` at value feature 0 of this wave.
+// X[v][p] = sum_s Z[s][v] P[s][p]: the score block as B operand out of its registers.
 // P is zero where s does not precede p, but a zero times an infinity or NaN is not: a value row that is not finite would
-// reach the positions before it, which must not depend on it.  Where the block holds one (seen on the operands as they are
+// reach the positions before it, which must not depend on it (z(s, v): value feature v of this wave).  Where the block holds one (seen on the operands as they are
 // loaded) the matrix product runs without such elements and they are added pair by pair, ok(s, p) only.  The check costs nothing:
 // forward + backward, bf16 vector decay, 4 x 8 sequences of 2048, d_k = 64, without and with it 444 / 442 us.
-template <typename Ok>
-__device__ __forceinline__ f32x16 causal_product(const float* z, int ld, const f32x16& P, int lane, Ok ok) {
+// LV: a level's block (0: any): rows on its odd side are zero, and where that can be told from the register alone they are left out.
+template <int LV, typename Z, typename Ok>
+__device__ __forceinline__ f32x16 causal_product(Z&& z, const f32x16& P, int lane, Ok ok) {
     const int n = lane & 31, half = lane >> 5;
+    constexpr int skip = LV == 4 ? 0 : LV;  // (register x: row 8 (x / 4) + 4 half + x % 4)
     f32x16 X = {0};
     float chk = 0.f;
     _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-        const float t = z[hrow(x, half) * ld + n];
+        if (hrow(x, 0) & skip) continue;
+        const float t = z(hrow(x, half), n);
         chk = fmaf(t, 0.f, chk);
         X = mfma2(t, P[x], X);
     }
     if (__any(chk != chk)) {
         X = f32x16{0};
         _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-            const float t = z[hrow(x, half) * ld + n];
+            if (hrow(x, 0) & skip) continue;
+            const float t = z(hrow(x, half), n);
             X = mfma2(fabsf(t) <= FLT_MAX ? t : 0.f, P[x], X);
         }
         _Pragma("unroll 1") for (int s = 0; s < GT; ++s) {
             const float p = __shfl(P[4 * (s >> 3) + (s & 3)], n + 8 * (s & 4), 64);  // P[s][n]
-            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                const f32x4 t = *reinterpret_cast<const f32x4*>(z + s * ld + 8 * g + 4 * half);
-                _Pragma("unroll") for (int j = 0; j < 4; ++j)
-                    if (ok(s, n) && !(fabsf(t[j]) <= FLT_MAX)) X[4 * g + j] += t[j] * p;
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                const float t = z(s, hrow(x, half));
+                if (ok(s, n) && !(fabsf(t) <= FLT_MAX)) X[x] += t * p;
             }
         }
     }
@@ -299,12 +309,15 @@ __device__ __forceinline__ long long keep_slot(const Dims& d, const GRole& R, co
 
 // LDS of the vector kind's walker, in floats.  Row strides == 4 mod 64 words: 16-byte row reads of 16 lanes tile the banks.
 //   Q | K | V | score partials, then half of the inter product [wave][16][64] | W (one or two tiles of weighted rows) | tables
-template <int KD, int TV, int VEC, bool SUM>
+// bf16 elements: the rows that enter products as they came stay bf16 (GRows), keys and queries of VEC 2, values of the summary.
+template <typename TIO, int KD, int TV, int VEC, bool SUM>
 struct GLds {
+    static constexpr bool RAW = sizeof(TIO) == 2 && (VEC == 2 || SUM);
     static constexpr int NW = TV / 32, LQ = KD + 4, LV = TV + 4;
     static constexpr int COLS = VEC == 2 ? TV : KD;           // decayed features held by this workgroup
+    static constexpr int QK = RAW && VEC == 2 ? GT * (KD + 8) / 2 : GT * LQ, VT = RAW && VEC == 1 ? GT * (TV + 8) / 2 : GT * LV;
     static constexpr int WT = GT * (COLS + 4), WN = SUM ? 1 : 2;
-    static constexpr int oK = SUM ? 0 : GT * LQ, oV = oK + GT * LQ, oP = oV + GT * LV, oW = oP + (SUM ? 0 : NW * 1024);
+    static constexpr int oK = SUM ? 0 : QK, oV = oK + QK, oP = oV + VT, oW = oP + (SUM ? 0 : NW * 1024);
     static constexpr int oT = oW + WN * WT, total = oT + 5 * COLS, bytes = total * 4;
 };
 
@@ -906,11 +919,18 @@ __global__ __launch_bounds__(2 * TV + 64 * HW, KD == 256 ? 1 : 2) void gk_walk(D
 // comments of both number.
 template <typename TIO, int KD, int TV, int VEC, bool SUM>
 __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d, GArgs a) {
-    using Lds = GLds<KD, TV, VEC, SUM>;
+    using Lds = GLds<TIO, KD, TV, VEC, SUM>;
+    constexpr bool RAW = Lds::RAW;
+    using KRows = GRows<1, KD, false>;  // bf16 rows as they came: queries with the groups of four exchanged, keys and values in order
+    using VRows = GRows<1, TV, false>;
     constexpr int NW = Lds::NW, NT = 2 * TV, LQ = Lds::LQ, LV = Lds::LV, KB = KD / 64, COLS = Lds::COLS, LW = COLS + 4;
     constexpr int ITEMS = (2 * COLS + NT - 1) / NT;
     extern __shared__ __align__(16) float sm[];
     float *Q = sm, *K = sm + Lds::oK, *V = sm + Lds::oV, *Pp = sm + Lds::oP, *W0 = sm + Lds::oW, *W1 = W0 + Lds::WT;
+    uint16_t *Qb = reinterpret_cast<uint16_t*>(Q), *Kb = reinterpret_cast<uint16_t*>(K), *Vb = reinterpret_cast<uint16_t*>(V);
+    // element of a value or key row, as the kernel has them
+    auto value = [&](int row, int col) { if constexpr (RAW && VEC == 1) return VRows::at(Vb, row, col); else return V[row * LV + col]; };
+    auto key = [&](int row, int col) { if constexpr (RAW && VEC == 2) return KRows::at(Kb, row, col); else return K[row * LQ + col]; };
     double* tot = reinterpret_cast<double*>(sm + Lds::oT);  // log-decay of either half of the step [2][COLS]
     float* lamv = sm + Lds::oT + 4 * COLS;                  // e^E [COLS]
 
@@ -936,16 +956,45 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
 
     // ---- work that both groups do
     // this wave's part of the inter product, O^T[v][p] = sum_i S[i][v] x_p[i], the state blocks as A operands out of the
-    // accumulators
+    // accumulators; bf16 rows as they came (VEC 2): the state in three parts, as the scalar kinds have it.  (bf16, d_k = 64, d_v = 128,
+    // 4 x 8 sequences of 2048, the dq and dk walkers with fp32 instructions 80 us; with this, the update's weighted values in
+    // parts, the scores' products single and the levels' empty rows left out 63; distance of dg to 64 bits 3.2e-7 -> 2.4e-7.  For o
+    // and dv, where rows are weighted too, the split costs what it saves: 77 -> 94 us, not done; the summary 38 -> 37.)
     auto inter = [&](const float* X, int ld) {
         const int l = fresh() & 63, n = l & 31, half = l >> 5;
         f32x16 o = {0};
-        _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
-            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-                const f32x4 x = *reinterpret_cast<const f32x4*>(X + n * ld + kcol + 32 * ib + 8 * g + 4 * half);
-                _Pragma("unroll") for (int j = 0; j < 4; ++j) o = mfma2(S[ib][4 * g + j], x[j], o);
-            }
-        return o;
+        auto exact = [&]() {
+            f32x16 o = {0};
+            _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
+                _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                    f32x4 x;
+                    const int c = kcol + 32 * ib + 8 * g + 4 * half;
+                    if constexpr (RAW && VEC == 2) {
+                        _Pragma("unroll") for (int j = 0; j < 4; ++j) x[j] = KRows::at(Qb, n, KRows::swapped(c + j));
+                    } else x = *reinterpret_cast<const f32x4*>(X + n * ld + c);
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) o = mfma2(S[ib][4 * g + j], x[j], o);
+                }
+            return o;
+        };
+        if constexpr (RAW && VEC == 2) {
+            f32x16 small = {0};
+            _Pragma("unroll") for (int ib = 0; ib < KB; ++ib)
+                _Pragma("unroll") for (int h = 0; h < 2; ++h) {
+                    float t[8];
+                    _Pragma("unroll") for (int x = 0; x < 8; ++x) t[x] = S[ib][8 * h + x] * kUp;
+                    const Parts<3> sp = split8(t);
+                    const Parts<1> x = KRows::row8(Qb, n, kcol + 32 * ib + 16 * h + 8 * half);
+                    small_terms(sp, x, small);
+                    o = mfma16(sp.p[0], x.p[0], o);
+                }
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) o[x] += small[x];
+            const float nf = not_finite(o);
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) o[x] *= kDown;
+            if (__any(nf != nf)) replace_not_finite(o, exact());
+            return o;
+        } else {
+            return exact();
+        }
     };
     // ... and its weight e^{E_p} (VEC 2; VEC 1 has it in the rows)
     auto scale_inter = [&](f32x16& O) {
@@ -957,18 +1006,58 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
     };
     // S[i][v] = lam S[i][v] + sum_t Y[t][i] (w_t Z[t][v]); the step's own sum is formed by itself, so the state sees one
     // rounding per step instead of one per token (tokens in order, the latest, which weigh most, last: what is added to them would
-    // round them again)
-    auto update = [&]() {
-        const float *Y = VEC == 1 ? W0 : K, *Z = VEC == 2 ? W0 : V;
-        const int ldy = VEC == 1 ? LW : LQ, ldz = VEC == 2 ? LW : LV;
+    // round them again).  bf16 elements: the weighted side in three parts, the last two tokens apart, as the scalar kinds have it.
+    auto update = [&](int L) {
+        auto left = [&](int t, int i) { if constexpr (VEC == 1) return W0[t * LW + i]; else return key(t, i); };
+        auto right = [&](int t, int v) { if constexpr (VEC == 2) return W0[t * LW + v]; else return value(t, v); };
         float lam = 1.f;
         if (VEC == 2) lam = lamv[32 * w + (fresh() & 31)];
+        Parts<3> zp[2];                                     // VEC 2: this wave's weighted values
+        auto weighted = [&](const float* col, int h, int half) {  // eight tokens of a column of W0, the last two of the step left out
+            float t[8];
+            _Pragma("unroll") for (int x = 0; x < 8; ++x) {
+                const int r = hrow(8 * h + x, half);
+                t[x] = r < L - 2 ? col[r * LW] * kUp : 0.f;
+            }
+            return split8(t);
+        };
+        if constexpr (RAW && VEC == 2) {
+            const int l = fresh() & 63;
+            _Pragma("unroll") for (int h = 0; h < 2; ++h) zp[h] = weighted(W0 + 32 * w + (l & 31), h, l >> 5);
+        }
         _Pragma("unroll") for (int ib = 0; ib < KB; ++ib) {
             const int l = fresh() & 63, n = l & 31, half = l >> 5;
             f32x16 U = {0};
-            _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-                const int t = 2 * x + half;
-                U = mfma2(Y[t * ldy + kcol + 32 * ib + n], Z[t * ldz + 32 * w + n], U);
+            auto exact = [&]() {
+                f32x16 U = {0};
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) U = mfma2(left(2 * x + half, kcol + 32 * ib + n), right(2 * x + half, 32 * w + n), U);
+                return U;
+            };
+            if constexpr (RAW) {
+                if constexpr (VEC == 1) {
+                    Parts<3> yp[2];
+                    _Pragma("unroll") for (int h = 0; h < 2; ++h) {
+                        yp[h] = weighted(W0 + kcol + 32 * ib + n, h, half);
+                        const Parts<1> v = VRows::col8(Vb, h, 32 * w, l);
+                        small_terms(yp[h], v, U);
+                    }
+                    _Pragma("unroll") for (int h = 0; h < 2; ++h) U = mfma16(yp[h].p[0], VRows::col8(Vb, h, 32 * w, l).p[0], U);
+                } else {
+                    Parts<1> y[2];
+                    _Pragma("unroll") for (int h = 0; h < 2; ++h) {
+                        y[h] = KRows::col8(Kb, h, kcol + 32 * ib, l);
+                        small_terms(y[h], zp[h], U);
+                    }
+                    _Pragma("unroll") for (int h = 0; h < 2; ++h) U = mfma16(y[h].p[0], zp[h].p[0], U);
+                }
+                const int last = L - 2 + half < 0 ? GT - 1 : L - 2 + half;  // (one token: with a row of zeros)
+                const float y = left(last, kcol + 32 * ib + n), z = right(last, 32 * w + n);
+                U = mfma2(VEC == 1 ? y * kUp : y, VEC == 2 ? z * kUp : z, U);
+                const float nf = not_finite(U);
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) U[x] *= kDown;
+                if (__any(nf != nf)) replace_not_finite(U, exact());
+            } else {
+                U = exact();
             }
             _Pragma("unroll") for (int g = 0; g < 4; ++g) {
                 f32x4 m = {lam, lam, lam, lam};
@@ -1043,9 +1132,21 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
         };
         auto commit = [&](int L) {  // registers of this step -> LDS; decay tables
             const int tid = fresh();
-            if (!SUM) rq.commit(Q, LQ, L, tid);
-            rk.commit(K, LQ, L, tid);
-            rv.commit(V, LV, L, tid);
+            if constexpr (RAW && VEC == 2) {
+                rq.clear(L, tid);
+                rk.clear(L, tid);
+                KRows::commit(Qb, rq, tid, true);
+                KRows::commit(Kb, rk, tid, false);
+            } else {
+                if (!SUM) rq.commit(Q, LQ, L, tid);
+                rk.commit(K, LQ, L, tid);
+            }
+            if constexpr (RAW && VEC == 1) {
+                rv.clear(L, tid);
+                VRows::commit(Vb, rv, tid, false);
+            } else {
+                rv.commit(V, LV, L, tid);
+            }
             {
                 _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) {
                     if (!item_ok(tid, i)) continue;
@@ -1124,13 +1225,14 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
         if (s.cnt > 0) gload(0);
         for (int kk = 0; kk < s.cnt; ++kk) {
             unit_dot(kk);
-            commit(walk_step(d, s, rev, kk).L);
+            const int L = walk_step(d, s, rev, kk).L;
+            commit(L);
             __syncthreads();  // (A) rows and decay tables of this step are in LDS
             gload(kk + 1);
             if constexpr (SUM) {
                 write_end(W0);
                 __syncthreads();  // (B)
-                update();
+                update(L);
             } else if constexpr (VEC == 1) {
                 write_start(W0);
                 __syncthreads();  // (B) e^{E_p} x_p
@@ -1145,7 +1247,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                 });
                 __syncthreads();  // (M) the partials are spent
                 block_store(O);
-                update();
+                update(L);
             } else {
                 write_start(W0);
                 write_level(W1, std::integral_constant<int, 16>{});
@@ -1160,7 +1262,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                     else write_end(nxt);
                     __syncthreads();  // (L) next level's tile; after the last: weighted values
                 });
-                update();
+                update(L);
             }
             unit_keep(kk);
             __syncthreads();  // (C) every read of this step's tiles is done
@@ -1178,6 +1280,16 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                 const int c = w * (KD / NW) + f + 4 * half;
                 const f32x4 y = *reinterpret_cast<const f32x4*>(Y + n * ld + c), x = *reinterpret_cast<const f32x4*>(X + n * ld + c);
                 _Pragma("unroll") for (int j = 0; j < 4; ++j) P = mfma2(y[j], x[j], P);
+            }
+            return P;
+        };
+        // the same from bf16 rows as they came: every product exact
+        auto score_raw = [&]() {
+            const int l = fresh() & 63, n = l & 31, half = l >> 5;
+            f32x16 P = {0};
+            _Pragma("unroll") for (int f = 0; f < KD / NW; f += 16) {
+                const int c = w * (KD / NW) + f;
+                P = mfma16(KRows::row44(Kb, n, c + 4 * half).p[0], KRows::row8(Qb, n, c + 8 * half).p[0], P);
             }
             return P;
         };
@@ -1205,9 +1317,16 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
             f32x4 z[4];
             unit_dot(kk);
             __syncthreads();  // (A)
+            // the elements that the output is multiplied with, requested before this step's stores: a load waits for the stores before it
+            decltype(load4raw(static_cast<const TIO*>(R.aux))) q4[4];
+            if (!SUM && R.xdot) {
+                const int l = fresh() & 63, n = min(l & 31, L - 1);
+                const size_t row = (cp.tok0 + size_t(rev ? L - 1 - n : n) * cp.ts) * a.vd + vcol + 32 * w + 4 * (l >> 5);
+                _Pragma("unroll") for (int g = 0; g < 4; ++g) q4[g] = load4raw(static_cast<const TIO*>(R.aux) + row + 8 * g);
+            }
             if constexpr (SUM) {
                 __syncthreads();  // (B)
-                update();
+                update(L);
             } else {
                 if constexpr (VEC == 1) {
                     P = score_part(K, Q, LQ);
@@ -1235,11 +1354,12 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                     const int l = fresh() & 63;
                     _Pragma("unroll") for (int x = 0; x < 16; ++x) P[x] = hrow(x, l >> 5) == (l & 31) ? 0.f : P[x];
                     __syncthreads();  // (M)
-                    const f32x16 X = causal_product(V + 32 * w, LV, P, fresh() & 63, [](int s, int p) { return s < p; });
+                    const f32x16 X = causal_product<0>([&](int s, int v) { return V[s * LV + 32 * w + v]; }, P, fresh() & 63, [](int s, int p) { return s < p; });
                     _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] += X[x];
                     formed(O);
                 } else {
-                    block_store(score_part(K, Q, LQ));
+                    if constexpr (RAW) block_store(score_raw());
+                    else block_store(score_part(K, Q, LQ));
                     O = inter(Q, LQ);
                     __syncthreads();  // (B)
                     scale_inter(O);
@@ -1254,7 +1374,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                             const int r = hrow(x, half);
                             G[x] = r < n && (r ^ n) >= lv && (r ^ n) < 2 * lv ? P[x] : 0.f;
                         }
-                        const f32x16 X = causal_product(cur + 32 * w, LW, G, l, [](int r, int p) { return r < p && (r ^ p) >= lv && (r ^ p) < 2 * lv; });
+                        const f32x16 X = causal_product<lv>([&](int s, int v) { return cur[s * LW + 32 * w + v]; }, G, l, [](int r, int p) { return r < p && (r ^ p) >= lv && (r ^ p) < 2 * lv; });
                         _Pragma("unroll") for (int g = 0; g < 4; ++g) {
                             const f32x4 e = *reinterpret_cast<const f32x4*>(cur + n * LW + 32 * w + 8 * g + 4 * half);
                             _Pragma("unroll") for (int j = 0; j < 4; ++j) O[4 * g + j] += (n & lv) ? X[4 * g + j] * e[j] : 0.f;
@@ -1263,7 +1383,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                         __syncthreads();  // (L)
                     });
                 }
-                update();
+                update(L);
                 unit_keep(kk);
                 const int l = fresh() & 63;
                 _Pragma("unroll") for (int g = 0; g < 4; ++g) z[g] = *reinterpret_cast<const f32x4*>(V + (l & 31) * LV + 32 * w + 8 * g + 4 * (l >> 5));
@@ -1281,9 +1401,9 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                     f32x4 o = *reinterpret_cast<const f32x4*>(Pp + w * 1024 + (g * 64 + l) * 4);
                     _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] += O[4 * g + j];
                     if (R.xdot) {
-                        const f32x4 q4 = load4(static_cast<const TIO*>(R.aux) + oel + 8 * g);
+                        const f32x4 q = numbers4(q4[g]);
                         f32x4 y;
-                        _Pragma("unroll") for (int j = 0; j < 4; ++j) y[j] = q4[j] * o[j];
+                        _Pragma("unroll") for (int j = 0; j < 4; ++j) y[j] = q[j] * o[j];
                         if (n < L) store4(R.xdot + (cp.wtok0 + tok) * a.vd + vcol + 32 * w + 4 * half + 8 * g, y);
                     }
                     _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] += pd * z[g][j];
@@ -1533,7 +1653,7 @@ hipError_t allow_lds(const void* fn, int bytes) {
 static_assert(GLdsS<float, 64, 64, 0, false>::bytes <= 40 * 1024, "four workgroups to a compute unit: gplan");
 template <typename TIO, int KD, int TV, int VEC, int HW, bool SUM>
 hipError_t launch_walk_as(const Dims& d, GArgs a, int nroles, dim3 grid, hipStream_t st, int kid) {
-    using Lds = std::conditional_t<VEC == 0, GLdsS<TIO, KD, TV, HW, SUM>, GLds<KD, TV, VEC, SUM>>;
+    using Lds = std::conditional_t<VEC == 0, GLdsS<TIO, KD, TV, HW, SUM>, GLds<TIO, KD, TV, VEC, SUM>>;
     static_assert(Lds::bytes <= 160 * 1024, "LDS");
     void (*kernel)(Dims, GArgs);
     if constexpr (VEC == 0) kernel = gk_walk<TIO, KD, TV, HW, SUM>;

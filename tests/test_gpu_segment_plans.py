@@ -413,3 +413,25 @@ def test_helper_waves_leave_the_same_bits(dtype, dk, dv, kind):
             if got is not None:
                 want = whole[m][s:s + 1] if m in ("final_state", "d_init_state") else whole[m][:, :, cu[s]:cu[s + 1]]
                 assert torch.equal(got, want), (m, s)
+
+
+@pytest.mark.parametrize("dk,dv", [(64, 64), (64, 128), (256, 64)])
+@pytest.mark.parametrize("T,power", [(1, {}), (2, {}), (34, {}), (99, {}), (99, dict(v=106, k=-30, m0=76)), (99, dict(d_o=106, q=-20, k=-20, v=-20)),
+                                     (99, dict(m0=110, q=-100)), (99, dict(v=-112, m0=-116))])
+def test_vector_decay_bf16_rows_as_they_came(T, power, dk, dv):
+    """bf16 rows enter the gradient walkers' products unsplit, state and weighted rows in three parts of 2^24 times the number: one
+    and two tokens (the last two of a step go apart), a ragged step, numbers that outgrow the factor and such as fall below the
+    parts of a bf16 number.  Bounds: bf16 results one rounding (2^-9 at most) and the adjoint's, fp32 ones as in
+    test_numbers_that_outgrow_the_factor."""
+    import torch
+    from lsm_testlib import gpu_backward, oracle_all
+    x = wl.make_inputs(1, 2, T, dk, dv, wl.KIND_VECTOR, dtype="bf16", seed=2900 + T + dk, decay="weak", init_state=True, d_final=True)
+    for n, p in power.items():
+        x[n] *= np.float32(2.0 ** p)
+    r = gpu_backward(x, 64)
+    torch.cuda.synchronize()
+    ref = oracle_all(x)[2]
+    errs = {n: two_norm_error(r[m], ref[n]) for n, m in [("dq", "dq"), ("dk", "dk"), ("dv", "dv"), ("dg", "dg"), ("d_m0", "d_init_state")]}
+    print(" ".join("%s %.1e" % e for e in errs.items()))
+    for n, e in errs.items():
+        assert e <= (1e-4 if n == "dg" else 2.0 ** -21 if n == "d_m0" else 2.0 ** -8), (n, e)
