@@ -28,7 +28,7 @@
 // vector kind its chain of phases: 26000 to 28000 clocks a step, of which each of the two groups works some 20000.
 // Forward + backward against one-thread-per-element kernels on the vector ALU with a state per chunk in memory, which this
 // family replaced, then with fp32 instructions throughout, now: that shape 11.6 ms, 0.731, 0.621; bf16 vector decay, 4 x 8
-// sequences of 2048, d_k = 64, d_v = 128: 7.2 ms, 0.442, 0.380; forward alone, 32 sequences of 1777, d = 64, bf16: 262 us, 50.7,
+// sequences of 2048, d_k = 64, d_v = 128: 7.2 ms, 0.442, 0.357; forward alone, 32 sequences of 1777, d = 64, bf16: 262 us, 50.7,
 // 43.5; 2 sequences of 256, d = 64, fp32: 110 us, 25.1, 23.6.
 // Distance to 64-bit results against the kernels on the vector ALU, 2-norm, weak to strong decays, 512 to 4096 tokens, chunks of 16
 // to 128: o, dq, dk, dv and d_init_state 0.4 to 0.95 times (one case 1.09), dg 0.1 to 0.85 times (vector kind in chunks of 16: 1.04),
@@ -225,21 +225,21 @@ __device__ __forceinline__ double state_dot(const f32x16 (&S)[KB], const float* 
 }
 __device__ __forceinline__ int hrow(int x, int half) { return 8 * (x >> 2) + 4 * half + (x & 3); }  // row of result register x
 
-// X[v][p] = sum_s Z[s][v] P[s][p]: the score block as B operand out of its registers.
+// X[v][p] = sum_s Z[s][v] P[s][p]: the score block as B operand out of its registers, `z` at value feature 0 of this wave.
 // P is zero where s does not precede p, but a zero times an infinity or NaN is not: a value row that is not finite would
-// reach the positions before it, which must not depend on it (z(s, v): value feature v of this wave).  Where the block holds one (seen on the operands as they are
+// reach the positions before it, which must not depend on it.  Where the block holds one (seen on the operands as they are
 // loaded) the matrix product runs without such elements and they are added pair by pair, ok(s, p) only.  The check costs nothing:
 // forward + backward, bf16 vector decay, 4 x 8 sequences of 2048, d_k = 64, without and with it 444 / 442 us.
 // LV: a level's block (0: any): rows on its odd side are zero, and where that can be told from the register alone they are left out.
-template <int LV, typename Z, typename Ok>
-__device__ __forceinline__ f32x16 causal_product(Z&& z, const f32x16& P, int lane, Ok ok) {
+template <int LV, typename Ok>
+__device__ __forceinline__ f32x16 causal_product(const float* z, int ld, const f32x16& P, int lane, Ok ok) {
     const int n = lane & 31, half = lane >> 5;
     constexpr int skip = LV == 4 ? 0 : LV;  // (register x: row 8 (x / 4) + 4 half + x % 4)
     f32x16 X = {0};
     float chk = 0.f;
     _Pragma("unroll") for (int x = 0; x < 16; ++x) {
         if (hrow(x, 0) & skip) continue;
-        const float t = z(hrow(x, half), n);
+        const float t = z[hrow(x, half) * ld + n];
         chk = fmaf(t, 0.f, chk);
         X = mfma2(t, P[x], X);
     }
@@ -247,14 +247,15 @@ __device__ __forceinline__ f32x16 causal_product(Z&& z, const f32x16& P, int lan
         X = f32x16{0};
         _Pragma("unroll") for (int x = 0; x < 16; ++x) {
             if (hrow(x, 0) & skip) continue;
-            const float t = z(hrow(x, half), n);
+            const float t = z[hrow(x, half) * ld + n];
             X = mfma2(fabsf(t) <= FLT_MAX ? t : 0.f, P[x], X);
         }
         _Pragma("unroll 1") for (int s = 0; s < GT; ++s) {
             const float p = __shfl(P[4 * (s >> 3) + (s & 3)], n + 8 * (s & 4), 64);  // P[s][n]
-            _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-                const float t = z(s, hrow(x, half));
-                if (ok(s, n) && !(fabsf(t) <= FLT_MAX)) X[x] += t * p;
+            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                const f32x4 t = *reinterpret_cast<const f32x4*>(z + s * ld + 8 * g + 4 * half);
+                _Pragma("unroll") for (int j = 0; j < 4; ++j)
+                    if (ok(s, n) && !(fabsf(t[j]) <= FLT_MAX)) X[4 * g + j] += t[j] * p;
             }
         }
     }
@@ -263,7 +264,8 @@ __device__ __forceinline__ f32x16 causal_product(Z&& z, const f32x16& P, int lan
 
 // Have a block in its registers here.  Left alone the compiler puts what is added to a block in every phase off until the block is
 // used, phases later, and keeps the operands instead: gk_walk_vec's outputs, five levels of them, went through scratch memory,
-// behind every store before (20000 of 43000 clocks a step, bf16, d_k = 64, d_v = 128).
+// behind every store before (20000 of 43000 clocks a step, bf16, d_k = 64, d_v = 128).  (o and dv of 64-wide values never did, and run
+// 1 to 2 % longer with it: not there.)
 __device__ __forceinline__ void formed(f32x16& x) { asm volatile("" : "+v"(x)); }
 
 // What a workgroup walks.
@@ -309,16 +311,21 @@ __device__ __forceinline__ long long keep_slot(const Dims& d, const GRole& R, co
 
 // LDS of the vector kind's walker, in floats.  Row strides == 4 mod 64 words: 16-byte row reads of 16 lanes tile the banks.
 //   Q | K | V | score partials, then half of the inter product [wave][16][64] | W (one or two tiles of weighted rows) | tables
-// bf16 elements: the rows that enter products as they came stay bf16 (GRows), keys and queries of VEC 2, values of the summary.
+// bf16 elements: the rows that enter products as they came stay bf16 (GRows), keys and queries of VEC 2, values of
+// the summary (64-wide ones not: forward, 8 sequences of 2000, d = 64, 43.5 -> 46 us).
 template <typename TIO, int KD, int TV, int VEC, bool SUM>
 struct GLds {
-    static constexpr bool RAW = sizeof(TIO) == 2 && (VEC == 2 || SUM);
+    static constexpr bool RAW = sizeof(TIO) == 2 && (VEC == 2 || (SUM && TV == 128));
     static constexpr int NW = TV / 32, LQ = KD + 4, LV = TV + 4;
     static constexpr int COLS = VEC == 2 ? TV : KD;           // decayed features held by this workgroup
     static constexpr int QK = RAW && VEC == 2 ? GT * (KD + 8) / 2 : GT * LQ, VT = RAW && VEC == 1 ? GT * (TV + 8) / 2 : GT * LV;
     static constexpr int WT = GT * (COLS + 4), WN = SUM ? 1 : 2;
     static constexpr int oK = SUM ? 0 : QK, oV = oK + QK, oP = oV + VT, oW = oP + (SUM ? 0 : NW * 1024);
-    static constexpr int oT = oW + WN * WT, total = oT + 5 * COLS, bytes = total * 4;
+    // a decayed feature's 32 positions are dealt to 2 threads of the group that weighs rows, or to 4 where there are as many: then the
+    // sums of four pieces, and their products for the level whose blocks are two pieces (d_k = 64, d_v = 128,
+    // 4 x 8 sequences of 2048, with 2: o and dv walkers 77 us, summary 37; with 4: 71 and 33)
+    static constexpr int PIECES = 4 * COLS <= 2 * TV ? 4 : 2;
+    static constexpr int oT = oW + WN * WT, total = oT + (PIECES == 4 ? 17 : 5) * COLS, bytes = total * 4;
 };
 
 // ---- fp32 products on the bf16 matrix cores
@@ -924,15 +931,16 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
     using KRows = GRows<1, KD, false>;  // bf16 rows as they came: queries with the groups of four exchanged, keys and values in order
     using VRows = GRows<1, TV, false>;
     constexpr int NW = Lds::NW, NT = 2 * TV, LQ = Lds::LQ, LV = Lds::LV, KB = KD / 64, COLS = Lds::COLS, LW = COLS + 4;
-    constexpr int ITEMS = (2 * COLS + NT - 1) / NT;
+    constexpr int PIECES = Lds::PIECES, LEN = GT / PIECES, ITEMS = (PIECES * COLS + NT - 1) / NT;
     extern __shared__ __align__(16) float sm[];
     float *Q = sm, *K = sm + Lds::oK, *V = sm + Lds::oV, *Pp = sm + Lds::oP, *W0 = sm + Lds::oW, *W1 = W0 + Lds::WT;
     uint16_t *Qb = reinterpret_cast<uint16_t*>(Q), *Kb = reinterpret_cast<uint16_t*>(K), *Vb = reinterpret_cast<uint16_t*>(V);
     // element of a value or key row, as the kernel has them
     auto value = [&](int row, int col) { if constexpr (RAW && VEC == 1) return VRows::at(Vb, row, col); else return V[row * LV + col]; };
     auto key = [&](int row, int col) { if constexpr (RAW && VEC == 2) return KRows::at(Kb, row, col); else return K[row * LQ + col]; };
-    double* tot = reinterpret_cast<double*>(sm + Lds::oT);  // log-decay of either half of the step [2][COLS]
-    float* lamv = sm + Lds::oT + 4 * COLS;                  // e^E [COLS]
+    double* tot = reinterpret_cast<double*>(sm + Lds::oT);  // log-decay of the pieces of the step [PIECES][COLS]
+    float* lamv = sm + Lds::oT + 2 * PIECES * COLS;         // e^E [COLS]
+    float *fwdp = lamv + COLS, *bwdp = fwdp + 4 * COLS;     // four pieces: products of a piece's decays from either end [4][COLS]
 
     // the wave index as a scalar: the branch between the groups is then a scalar branch
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave % NW;
@@ -1099,14 +1107,14 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
     if (aux) {
         GTile<TIO, KD, NT> rq, rk;
         GTile<TIO, TV, NT> rv;
-        // item = (column, half): the 16 transitions d_p INTO the positions of its half and, second half, the closing
+        // item = (column, piece): the transitions d_p INTO the positions of its piece and, last piece, the closing
         // one.  Forward: the decay of the token itself; backward: that of the position before.
-        float dt[ITEMS][16], at[ITEMS][16], dn[ITEMS][16], closing[ITEMS], closing_n[ITEMS];
+        float dt[ITEMS][LEN], at[ITEMS][LEN], dn[ITEMS][LEN], closing[ITEMS], closing_n[ITEMS];
         double gtot[ITEMS];
         _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) gtot[i] = 0.0;
-        auto item_ok = [&](int t, int i) { return 2 * COLS >= NT * (i + 1) || t + NT * i < 2 * COLS; };
+        auto item_ok = [&](int t, int i) { return PIECES * COLS >= NT * (i + 1) || t + NT * i < PIECES * COLS; };
         auto item_col = [&](int t, int i) { return (t + NT * i) % COLS; };
-        auto item_half = [&](int t, int i) { return (t + NT * i) / COLS; };
+        auto item_piece = [&](int t, int i) { return (t + NT * i) / COLS; };
 
         auto gload = [&](int kk) {
             const int tid = fresh();
@@ -1121,9 +1129,9 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                 _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) {
                     if (!item_ok(tid, i)) continue;
                     const uint32_t col = 4 * item_col(tid, i);
-                    const int h16 = 16 * item_half(tid, i);
-                    _Pragma("unroll") for (int x = 0; x < 16; ++x) {  // (what does not exist is zeroed when it is used)
-                        const int pos = h16 + x - rev, tok = min(max(rev ? p.L - 1 - pos : pos, 0), p.L - 1);
+                    const int p0 = LEN * item_piece(tid, i);
+                    _Pragma("unroll") for (int x = 0; x < LEN; ++x) {  // (what does not exist is zeroed when it is used)
+                        const int pos = p0 + x - rev, tok = min(max(rev ? p.L - 1 - pos : pos, 0), p.L - 1);
                         dn[i][x] = *reinterpret_cast<const float*>(gb + uint32_t(tok) * grow + col);
                     }
                     closing_n[i] = *reinterpret_cast<const float*>(gb + col);
@@ -1150,50 +1158,64 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
             {
                 _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) {
                     if (!item_ok(tid, i)) continue;
-                    const int h = item_half(tid, i);
+                    const int h = item_piece(tid, i);
                     double t = 0.0;
-                    _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-                        const int pos = 16 * h + x - rev;
+                    _Pragma("unroll") for (int x = 0; x < LEN; ++x) {
+                        const int pos = LEN * h + x - rev;
                         dt[i][x] = pos >= 0 && pos < L ? dn[i][x] : 0.f;
                         if (!SUM) at[i][x] = expf(dt[i][x]);
                         t += double(dt[i][x]);
                     }
-                    closing[i] = rev && L == GT && h ? closing_n[i] : 0.f;
+                    closing[i] = rev && L == GT && h == PIECES - 1 ? closing_n[i] : 0.f;
                     tot[h * COLS + item_col(tid, i)] = t + double(closing[i]);
+                    if constexpr (!SUM && PIECES == 4) {
+                        float f = 1.f, b = 1.f;
+                        _Pragma("unroll") for (int x = 0; x < LEN; ++x) f *= at[i][x];
+                        _Pragma("unroll") for (int x = LEN - 1; x >= 0; --x) b *= at[i][x];
+                        fwdp[h * COLS + item_col(tid, i)] = f;
+                        bwdp[h * COLS + item_col(tid, i)] = b;
+                    }
                 }
             }
         };
         // ---- vector kind: writers of the weighted tiles (see the level scheme above)
-        auto each = [&](auto&& f) {  // f(item, half, column)
+        auto each = [&](auto&& f) {  // f(item, piece, column)
             const int tid = fresh();
             _Pragma("unroll") for (int i = 0; i < ITEMS; ++i) {
                 if (!item_ok(tid, i)) continue;
-                f(i, item_half(tid, i), item_col(tid, i));
+                f(i, item_piece(tid, i), item_col(tid, i));
             }
         };
         auto write_start = [&](float* o) {  // weight e^{E_p} from the start of the step; also e^E
             each([&](int i, int h, int c) {
-                const double t0 = tot[c];
-                double e = h ? t0 : 0.0;
-                _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                double all = 0.0, e = 0.0;
+                _Pragma("unroll") for (int u = 0; u < PIECES; ++u) {
+                    const double t = tot[u * COLS + c];
+                    if (u < h) e += t;
+                    all += t;
+                }
+                _Pragma("unroll") for (int x = 0; x < LEN; ++x) {
                     e += double(dt[i][x]);
-                    const int p = 16 * h + x;
+                    const int p = LEN * h + x;
                     const float wt = expf(float(e));
                     o[p * LW + c] = VEC == 1 ? Q[p * LQ + c] * wt : wt;
                 }
-                if (h == 0) lamv[c] = expf(float(t0 + tot[COLS + c]));
+                if (h == 0) lamv[c] = expf(float(all));
             });
         };
         auto write_end = [&](float* o) {  // weight e^{E - E_p} to the end of the step, on the state update's operand
             each([&](int i, int h, int c) {
-                double e = h ? double(closing[i]) : tot[COLS + c];
+                double e = 0.0;
+                _Pragma("unroll") for (int u = PIECES - 1; u > 0; --u)
+                    if (u > h) e += tot[u * COLS + c];
+                if (h == PIECES - 1) e = double(closing[i]);
                 if (SUM && h == 0) {
-                    const double all = tot[c] + tot[COLS + c];
+                    const double all = tot[c] + e;
                     lamv[c] = expf(float(all));
                     gtot[i] += all;
                 }
-                _Pragma("unroll") for (int x = 15; x >= 0; --x) {
-                    const int p = 16 * h + x;
+                _Pragma("unroll") for (int x = LEN - 1; x >= 0; --x) {
+                    const int p = LEN * h + x;
                     o[p * LW + c] = (VEC == 1 ? K[p * LQ + c] : V[p * LV + c]) * expf(float(e));
                     e += double(dt[i][x]);
                 }
@@ -1205,16 +1227,19 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
         auto write_level = [&](float* o, auto lvc) {
             constexpr int lv = decltype(lvc)::value;
             each([&](int i, int h, int c) {
-                _Pragma("unroll") for (int b = 0; b < 16; b += lv) {
-                    const bool odd = lv == 16 ? h != 0 : ((b / lv) & 1) != 0;
-                    float e[lv], prod = 1.f;
+                constexpr int B = lv < LEN ? lv : LEN;      // positions of a block in this piece
+                _Pragma("unroll") for (int b = 0; b < LEN; b += B) {
+                    const int first = LEN * h + b;
+                    const bool odd = B == lv && LEN % (2 * lv) == 0 ? ((b / lv) & 1) != 0 : ((first / lv) & 1) != 0;
+                    float e[B], prod = 1.f;
+                    if (lv > LEN && (h & 1) == (odd ? 1 : 0)) prod = odd ? fwdp[(h - 1) * COLS + c] : bwdp[(h + 1) * COLS + c];
                     if (odd) {  // query side: from the block's start up to the position
-                        _Pragma("unroll") for (int x = 0; x < lv; ++x) { prod *= at[i][b + x]; e[x] = prod; }
+                        _Pragma("unroll") for (int x = 0; x < B; ++x) { prod *= at[i][b + x]; e[x] = prod; }
                     } else {    // key side: from the position to the block's end
-                        _Pragma("unroll") for (int x = lv - 1; x >= 0; --x) { e[x] = prod; prod *= at[i][b + x]; }
+                        _Pragma("unroll") for (int x = B - 1; x >= 0; --x) { e[x] = prod; prod *= at[i][b + x]; }
                     }
-                    _Pragma("unroll") for (int x = 0; x < lv; ++x) {
-                        const int p = 16 * h + b + x;
+                    _Pragma("unroll") for (int x = 0; x < B; ++x) {
+                        const int p = first + x;
                         if (VEC == 1) o[p * LW + c] = (odd ? Q[p * LQ + c] : K[p * LQ + c]) * e[x];
                         else o[p * LW + c] = odd ? e[x] : V[p * LV + c] * e[x];
                     }
@@ -1269,7 +1294,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
         }
         if (SUM && slice == 0) {
             _Pragma("unroll") for (int i = 0; i < ITEMS; ++i)
-                if (item_ok(tid, i) && item_half(tid, i) == 0) R.gseg[(s.slot0 + s.wseg) * COLS + item_col(tid, i)] = gtot[i];
+                if (item_ok(tid, i) && item_piece(tid, i) == 0) R.gseg[(s.slot0 + s.wseg) * COLS + item_col(tid, i)] = gtot[i];
         }
     } else {
         // this wave's share (a range of features) of the block P^T[s][p] = y_s . x_p
@@ -1319,7 +1344,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
             __syncthreads();  // (A)
             // the elements that the output is multiplied with, requested before this step's stores: a load waits for the stores before it
             decltype(load4raw(static_cast<const TIO*>(R.aux))) q4[4];
-            if (!SUM && R.xdot) {
+            if (VEC == 2 && R.xdot) {  // (dq and dk only)
                 const int l = fresh() & 63, n = min(l & 31, L - 1);
                 const size_t row = (cp.tok0 + size_t(rev ? L - 1 - n : n) * cp.ts) * a.vd + vcol + 32 * w + 4 * (l >> 5);
                 _Pragma("unroll") for (int g = 0; g < 4; ++g) q4[g] = load4raw(static_cast<const TIO*>(R.aux) + row + 8 * g);
@@ -1345,7 +1370,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                             const int r = hrow(x, l >> 5);
                             if (r < n && (r ^ n) >= lv && (r ^ n) < 2 * lv) P[x] = G[x];
                         }
-                        formed(P);
+                        if constexpr (TV == 128) formed(P);
                         if constexpr (lv == 1) block_store(P);
                         __syncthreads();  // (L)
                     });
@@ -1354,9 +1379,9 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                     const int l = fresh() & 63;
                     _Pragma("unroll") for (int x = 0; x < 16; ++x) P[x] = hrow(x, l >> 5) == (l & 31) ? 0.f : P[x];
                     __syncthreads();  // (M)
-                    const f32x16 X = causal_product<0>([&](int s, int v) { return V[s * LV + 32 * w + v]; }, P, fresh() & 63, [](int s, int p) { return s < p; });
+                    const f32x16 X = causal_product<0>(V + 32 * w, LV, P, fresh() & 63, [](int s, int p) { return s < p; });
                     _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] += X[x];
-                    formed(O);
+                    if constexpr (TV == 128) formed(O);
                 } else {
                     if constexpr (RAW) block_store(score_raw());
                     else block_store(score_part(K, Q, LQ));
@@ -1374,7 +1399,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                             const int r = hrow(x, half);
                             G[x] = r < n && (r ^ n) >= lv && (r ^ n) < 2 * lv ? P[x] : 0.f;
                         }
-                        const f32x16 X = causal_product<lv>([&](int s, int v) { return cur[s * LW + 32 * w + v]; }, G, l, [](int r, int p) { return r < p && (r ^ p) >= lv && (r ^ p) < 2 * lv; });
+                        const f32x16 X = causal_product<lv>(cur + 32 * w, LW, G, l, [](int r, int p) { return r < p && (r ^ p) >= lv && (r ^ p) < 2 * lv; });
                         _Pragma("unroll") for (int g = 0; g < 4; ++g) {
                             const f32x4 e = *reinterpret_cast<const f32x4*>(cur + n * LW + 32 * w + 8 * g + 4 * half);
                             _Pragma("unroll") for (int j = 0; j < 4; ++j) O[4 * g + j] += (n & lv) ? X[4 * g + j] * e[j] : 0.f;
@@ -1400,7 +1425,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                 _Pragma("unroll") for (int g = 0; g < 4; ++g) {
                     f32x4 o = *reinterpret_cast<const f32x4*>(Pp + w * 1024 + (g * 64 + l) * 4);
                     _Pragma("unroll") for (int j = 0; j < 4; ++j) o[j] += O[4 * g + j];
-                    if (R.xdot) {
+                    if (VEC == 2 && R.xdot) {
                         const f32x4 q = numbers4(q4[g]);
                         f32x4 y;
                         _Pragma("unroll") for (int j = 0; j < 4; ++j) y[j] = q[j] * o[j];
