@@ -14,7 +14,9 @@
 //   mk_delta_walk8 (one workgroup per sequence or segment): the forward chunk walker with two more products per chunk,
 //                  K S from the state in the accumulators and U = T R; U then plays the values' part in the
 //                  intra-chunk product and in the state update.
-// T is all that is handed from one to the other.  (T diag(b) V in fp32 and T diag(beta Gamma) K in bf16, formed by the first kernel,
+// T is all that is handed from one to the other, without its diagonal: U = R + (T - I) R, in reverse W = dU + (T - I)^T dU, so that
+// R and dU, split for the products, are not rounded where they stand for themselves.  (2-norm errors with T whole, 16 x 16
+// sequences of 2048: d beta 8.8e-6, d b 3.5e-6, final state 3.6e-6; so 8.2e-6, 2.5e-6, 2.7e-6.)  (T diag(b) V in fp32 and T diag(beta Gamma) K in bf16, formed by the first kernel,
 // make the walk's chain one product shorter and cost 1.3 KB of traffic a token and the rounding of the latter: 16 x 16
 // sequences of 2048, keeping U, 209 + 251 us; this 74 + 198.  Final state without a decay, 2-norm error 4.6e-4 -> 4.0e-6.)
 // Every value column of the state evolves on its own (the erase term acts on the key side only), so a wave
@@ -31,7 +33,7 @@
 constexpr int LDD = 36;      // floats per row of a 32 x 32 diagonal block of L
 constexpr int LDT = 40;      // elements per row of a 32 x 32 bf16 tile
 // T^T (rows r, columns t) of a chunk in memory, bf16 head and remainder: the rows r < 32 of either plane (64 columns), then the
-// rows r >= 32 (columns 32 .. 63; the others are zero and not kept)
+// rows r >= 32 (columns 32 .. 63; the others are zero and not kept); zeros in the place of the ones on the diagonal
 constexpr int kDeltaT = 2 * 32 * 64 + 2 * 32 * 32;
 // its 16-byte pieces in that order: place of piece p in a pair of tiles [2][64][LDP]
 __device__ __forceinline__ int delta_t_place(int p) {
@@ -185,8 +187,9 @@ __global__ __launch_bounds__(kThreads, 4) void mk_delta_prep(Dims d, DeltaPrepAr
         }
         _Pragma("unroll") for (int x = 0; x < 16; ++x) T10[x] = -T10[x];
         store_block_t_split(Th, Tl, LDP, n, 32, half, T10);  // rows c, columns 32 + t
+        Th[lane * LDP + lane] = 0;  // (after this wave's last read of T; the remainder of a 1 is zero)
     }
-    __syncthreads();  // T is complete
+    __syncthreads();  // T - I is complete
     _Pragma("unroll") for (int it = 0; it < 3; ++it) {
         const int p = tid + kThreads * it;
         *reinterpret_cast<u32x4*>(a.tt + cp.slot * kDeltaT + 8 * p) = *reinterpret_cast<const u32x4*>(Th + delta_t_place(p));
@@ -311,8 +314,7 @@ __global__ __launch_bounds__(512, 1) void mk_delta_walk8(Dims d, DeltaWalkArgs a
                 }
             }
             fresh();
-            // R = b V - beta Gamma K S, U = T R
-            f32x16 U[2] = {{0}, {0}};
+            // R = b V - beta Gamma K S, U = R + (T - I) R: what is not multiplied is not split either
             _Pragma("unroll") for (int kr = 0; kr < 4; ++kr) {
                 f32x16& Rb = R[kr >> 1];
                 const int x0 = 8 * (kr & 1);
@@ -327,8 +329,12 @@ __global__ __launch_bounds__(512, 1) void mk_delta_walk8(Dims d, DeltaWalkArgs a
                         Rb[x0 + 2 * e + 1] = fmaf(wv[2 * e + 1], bf16_hi(v8[e]), Rb[x0 + 2 * e + 1]);
                     }
                 }
+            }
+            // (U[1] = R[1] here, as U[0], spills 6 registers with a decay: 16 x 16 sequences of 2048 257 us, this 251)
+            f32x16 U[2] = {R[0], f32x16{0}};
+            _Pragma("unroll") for (int kr = 0; kr < 4; ++kr) {
                 u32x4 hi, lo;
-                split_frag(Rb, kr & 1, hi, lo);
+                split_frag(R[kr >> 1], kr & 1, hi, lo);
                 const bf16x8 rh = __builtin_bit_cast(bf16x8, hi), rl = __builtin_bit_cast(bf16x8, lo);
                 _Pragma("unroll") for (int tb = kr >> 1; tb < 2; ++tb) {
                     const bf16x8 th = frag_tr_perm(Th, LDP, 16 * kr, 32 * tb, lane), tl = frag_tr_perm(Tl, LDP, 16 * kr, 32 * tb, lane);
@@ -337,6 +343,7 @@ __global__ __launch_bounds__(512, 1) void mk_delta_walk8(Dims d, DeltaWalkArgs a
                     U[tb] = mfma(th, rl, U[tb]);
                 }
             }
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) U[1][x] += R[1][x];
             u32x4 uh[4], ul[4];
             _Pragma("unroll") for (int kr = 0; kr < 4; ++kr) split_frag(U[kr >> 1], kr & 1, uh[kr], ul[kr]);
             __syncthreads();  // (C) scores are in LDS; Q, V and T are spent
@@ -671,8 +678,8 @@ __global__ __launch_bounds__(512, 1) void mk_delta_rwalk(Dims d, DeltaRevArgs a)
                     dU[tb] = mfma(frag_tr(Pl, LDP, 16 * ks, 32 * tb, lane), dot, dU[tb]);
                 }
             }
-            // W[r][v] = sum_{t >= r} T[t][r] dU[t][v]
-            f32x16 W[2] = {{0}, {0}};
+            // W[r][v] = dU[r][v] + sum_{t > r} T[t][r] dU[t][v]
+            f32x16 W[2] = {dU[0], dU[1]};
             _Pragma("unroll") for (int kt = 0; kt < 4; ++kt) {
                 u32x4 hi, lo;
                 split_frag(dU[kt >> 1], kt & 1, hi, lo);

@@ -289,6 +289,59 @@ def test_delta_packed_sequences_equal_separate_calls(gated, keep):
         assert torch.equal(r["d_init_state"][s_:s_ + 1], r_s["d_init_state"]), s_
 
 
+def half_unit(x):
+    """Largest distance of a number of x's binade to its bf16 head and remainder: the head is within 2^(e-8), that rest within half
+    a unit of its own eight bits."""
+    return 2.0 ** (np.floor(np.log2(np.maximum(np.abs(x), 1e-30))) - 17)
+
+
+def nearly_orthogonal(seed):
+    """One chunk, 16 recurrences: token t's key is feature 64 + t and a bit of feature 0, which couples the tokens by 2^-12."""
+    x = wl.make_delta_inputs(2, 8, 64, 128, 128, False, seed=seed, tie_b=False, d_final=True)
+    k = np.zeros((2, 8, 64, 128), np.float32)
+    k[..., np.arange(64), 64 + np.arange(64)] = 1.0
+    k[..., 0] = c = wl.bf16_round(np.float32(0.0157))
+    x["k"] = k
+    x["d_mT"] = wl.bf16_round(x["d_mT"])
+    x["q"], x["d_o"] = np.zeros_like(x["q"]), np.zeros_like(x["d_o"])
+    return x, float(c) ** 2
+
+
+def test_delta_pseudo_values_are_rounded_once():
+    """Rows 64 + t of the final state are u_t, which is kept as a bf16 head and remainder: no further from the exact one than that,
+    the coupling's share of three such roundings (T, R, remainder times remainder) and 24 of fp32 (two for each matrix product)."""
+    import torch
+    import paper_2503_05447_amd as pkg
+    from oracle import delta_oracle_fwd
+    x, coupling = nearly_orthogonal(6100)
+    t = dev(x)
+    _, mT = pkg.lsm_delta_fwd(t["q"], t["k"], t["v"], None, t["beta"], t["b"])
+    torch.cuda.synchronize()
+    u = delta_oracle_fwd(x["q"], x["k"], x["v"], None, x["beta"], x["b"], None)[1][:, :, 64:]
+    over = np.abs(host(mT)[:, :, 64:] - u) / (half_unit(u) + 64 * coupling * 3 * half_unit(np.abs(u).max()) + 24 * 2.0 ** -24 * np.abs(u))
+    print("pseudo-values: %.3f of the bound" % over.max())
+    assert over.max() <= 1.0
+
+
+def test_delta_gradients_of_the_right_hand_side_are_rounded_once():
+    """Rows 64 + t of d_init_state are d_mT - beta_t W_t (no queries): beta W is multiplied as a bf16 head and remainder, d_mT is bf16
+    already.  Bound as for the pseudo-values."""
+    import torch
+    import paper_2503_05447_amd as pkg
+    from oracle import delta_oracle_bwd
+    x, coupling = nearly_orthogonal(6200)
+    t = dev(x)
+    d_o, d_mT = torch.from_numpy(x["d_o"]).to(t["q"].device).to(torch.bfloat16), torch.from_numpy(x["d_mT"]).to(t["q"].device)
+    r = pkg.lsm_delta_bwd(t["q"], t["k"], t["v"], d_o, None, t["beta"], t["b"], None, d_mT)
+    torch.cuda.synchronize()
+    ref = delta_oracle_bwd(x["q"], x["k"], x["v"], x["d_o"], None, x["beta"], x["b"], None, x["d_mT"])["d_m0"][:, :, 64:]
+    w = x["d_mT"][:, :, 64:].astype(np.float64) - ref
+    over = np.abs(host(r["d_init_state"])[:, :, 64:] - ref) / (half_unit(w) + 64 * coupling * 3 * half_unit(np.abs(w).max()) +
+                                                               24 * 2.0 ** -24 * (np.abs(w) + np.abs(ref)))
+    print("gradients of the right-hand side: %.3f of the bound" % over.max())
+    assert over.max() <= 1.0
+
+
 def test_delta_rejects_what_it_does_not_serve():
     import torch
     import paper_2503_05447_amd as pkg
