@@ -342,6 +342,37 @@ def test_delta_gradients_of_the_right_hand_side_are_rounded_once():
     assert over.max() <= 1.0
 
 
+def one_chunk(T):
+    z = lambda *s: np.zeros((1, 1, T) + s, np.float32)
+    return dict(B=1, H=1, T=T, dk=128, dv=128, q=z(128), k=z(128), v=z(128), d_o=z(128), m0=None, d_mT=None, log_alpha=None,
+                beta=None, b=np.ones((1, 1, T), np.float32))
+
+
+def backward_of(x):
+    import torch
+    import paper_2503_05447_amd as pkg
+    from oracle import delta_oracle_bwd
+    t = dev(x)
+    d_o = torch.from_numpy(x["d_o"]).to(t["q"].device).to(torch.bfloat16)
+    r = pkg.lsm_delta_bwd(t["q"], t["k"], t["v"], d_o, t["log_alpha"], t["beta"], t["b"])
+    torch.cuda.synchronize()
+    return r, delta_oracle_bwd(x["q"], x["k"], x["v"], x["d_o"], x["log_alpha"], x["beta"], x["b"], None, None)
+
+
+def test_delta_decay_gradient_keeps_what_is_small_beside_the_diagonal():
+    """Token 0's k.dk is 1.5 2^23 from its own query, less 63 erase terms of 2^-6, a quarter of a unit for every 16 tokens.  q.dq has
+    the same large number; what is left, a unit, is the decay gradient's.  Bound: one rounding of k.dk, and those of W (2^-17 each)."""
+    x = one_chunk(64)
+    t = np.arange(1, 64)
+    x["log_alpha"] = np.zeros((1, 1, 64), np.float32)
+    x["k"][0, 0, 0, 0], x["q"][0, 0, 0, 0], x["d_o"][0, 0, 0, 0], x["v"][0, 0, 0, 0] = 1.0, 2.0 ** 12, 1.5 * 2.0 ** 11, 1.0
+    x["k"][0, 0, t, t], x["k"][0, 0, t, 0], x["q"][0, 0, t, t], x["d_o"][0, 0, t, 0] = 1.0, 2.0 ** -6, 1.0, 1.0
+    r, ref = backward_of(x)
+    err = np.abs(host(r["d_log_alpha"]) - ref["d_log_alpha"]).max()
+    print("decay gradient: off by %.3f units of k.dk" % err)
+    assert err <= 0.5 + 64 * 2.0 ** -6 * 2.0 ** -17
+
+
 def test_delta_rejects_what_it_does_not_serve():
     import torch
     import paper_2503_05447_amd as pkg
