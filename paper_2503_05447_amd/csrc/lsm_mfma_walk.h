@@ -422,8 +422,9 @@ __device__ __forceinline__ void walk_inter_pair(f32x16 (&X)[2], f32x16 (&O)[2], 
         }
 }
 
-// score_block2 with rows in two planes: (A + A2)[m] . B[n], and with B2 (A + A2) . (B + B2) without remainder x remainder; the
-// remainders' products apart, so that the chains are short
+// score_block2 with rows in two planes: (A + A2)[m] . B[n], and with B2 (A + A2) . (B + B2); the remainders' products apart, so that
+// the chains are short.  (The product of two remainders is as large as the rounding of either row: d beta, 16 x 16 sequences of
+// 2048, 2-norm 8.1e-6 without it, 7.7e-6; backward 655 and 658 us.)
 __device__ __forceinline__ f32x16 score_block_split(const uint16_t* Am, const uint16_t* Am2, int m0, const uint16_t* Bm, const uint16_t* Bm2,
                                                     int n0, int n, int half) {
     f32x16 acc = {0}, rem = {0};
@@ -439,7 +440,10 @@ __device__ __forceinline__ f32x16 score_block_split(const uint16_t* Am, const ui
         _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
             acc = mfma(a[ks], b[ks], acc);
             rem = mfma(a2[ks], b[ks], rem);
-            if (Bm2) rem = mfma(a[ks], b2[ks], rem);
+            if (Bm2) {
+                rem = mfma(a2[ks], b2[ks], rem);
+                rem = mfma(a[ks], b2[ks], rem);
+            }
         }
     }
     _Pragma("unroll") for (int x = 0; x < 16; ++x) acc[x] += rem[x];

@@ -373,6 +373,24 @@ def test_delta_decay_gradient_keeps_what_is_small_beside_the_diagonal():
     assert err <= 0.5 + 64 * 2.0 ** -6 * 2.0 ** -17
 
 
+def test_delta_erase_gradient_has_the_product_of_the_remainders():
+    """d beta_1 = -W_1 . u_0, both 1 + 255 2^-16, exact as a bf16 head and remainder: the product of the remainders is 2^-16 of it, and
+    nothing else is rounded but fp32 sums."""
+    x = one_chunk(2)
+    x["beta"] = np.full((1, 1, 2), 0.5, np.float32)
+    x["k"][0, 0, :, 0] = 1.0
+    x["k"][0, 0, 1, 1] = 1.0
+    x["b"][0, 0, 0] = 1.0 + 255 * 2.0 ** -16
+    x["v"][0, 0, 0, 0] = x["d_o"][0, 0, 1, 0] = x["q"][0, 0, 1, 0] = 1.0
+    x["q"][0, 0, 1, 1] = 255 * 2.0 ** -16
+    r, ref = backward_of(x)
+    want = float(ref["d_beta"][0, 0, 1])
+    assert abs(want + (1.0 + 255 * 2.0 ** -16) ** 2) < 1e-12
+    err = abs(float(r["d_beta"][0, 0, 1]) - want)
+    print("erase gradient: relative error %.2e" % (err / abs(want)))
+    assert err <= 2.0 ** -20 * abs(want)
+
+
 def test_delta_rejects_what_it_does_not_serve():
     import torch
     import paper_2503_05447_amd as pkg
