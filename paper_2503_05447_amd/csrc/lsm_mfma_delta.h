@@ -263,8 +263,8 @@ __global__ __launch_bounds__(512, 1) void mk_delta_walk8(Dims d, DeltaWalkArgs a
     const int nsq = max(1, (walk.n + a.m - 1) / a.m);  // segments of this sequence
     const int kbeg = seg * a.m, kend = min(walk.n, kbeg + a.m), cnt = max(kend - kbeg, 0);
     if (MODE != 0) {
-        // only segments whose end state another one starts from (the backward pass walks the last one's factor too)
-        if (cnt <= 0 || (seg >= nsq - 1 && !(MODE == 2 && a.usave))) return;
+        // only segments whose end state another one starts from (backward in time the last one's factor is wanted too)
+        if (nsq == 1 || cnt <= 0 || (seg == nsq - 1 && !(MODE == 2 && a.usave))) return;
     } else if (seg >= nsq) {
         return;
     }

@@ -391,6 +391,32 @@ def test_delta_erase_gradient_has_the_product_of_the_remainders():
     assert err <= 2.0 ** -20 * abs(want)
 
 
+def test_delta_packed_factors_of_cut_sequences_only():
+    """The factors of the segments ([sequence][segment][128][128] fp32, five such planes before the workspace's end) are formed for the
+    sequences that are cut, and for none of a single segment."""
+    import torch
+    import paper_2503_05447_amd as pkg
+    lens, H = [1500, 40, 200, 64, 900], 8
+    seqs, total = len(lens) * H, sum(lens)
+    chunks = -(-total // 64)
+    m = -(-chunks // min(-(-256 // seqs), chunks))
+    nseg, own = -(-chunks // m), [-(-n // (64 * m)) for n in lens]
+    assert sorted(set(own)) == [1, 3, 4]
+    x = wl.make_delta_inputs(1, H, total, 128, 128, False, seed=6300)
+    t = dev(x)
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32, device=t["q"].device)
+    ws = pkg.lsm_delta_workspace(t["q"], t["k"], t["v"], None, cu_seqlens=cu)
+    ws.fill_(0xff)
+    pkg.lsm_delta_fwd(t["q"], t["k"], t["v"], None, t["beta"], t["b"], cu_seqlens=cu, workspace=ws, save_states=True)
+    torch.cuda.synchronize()
+    plane = seqs * nseg * 65536
+    factors = ws[ws.numel() - 5 * plane:ws.numel() - 4 * plane].reshape(seqs, nseg, 65536)
+    written = (factors != 0xff).any(2).cpu().numpy()
+    for s in range(seqs):
+        n = own[s // H]
+        assert written[s].tolist() == [i < n and n > 1 for i in range(nseg)], (s, n)
+
+
 def test_delta_rejects_what_it_does_not_serve():
     import torch
     import paper_2503_05447_amd as pkg
