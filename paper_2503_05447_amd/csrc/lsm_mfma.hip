@@ -895,9 +895,9 @@ hipError_t launch_walk_grad(const Dims& d, const SegPlan& sp, const GradArgs& ga
     const dim3 block(kGrad8Threads);
     hipError_t e;
     ProfScope ps(KID_WALK_GRAD, st);
-    if (ga.v_lo) {  // delta-rule backward: values in two planes, the delta walkers' segments
+    const dim3 grid(walk_grid_x(d, sp.m, sp.nseg), walk_grid_y(d));
+    if (ga.v_lo) {  // delta-rule backward: values in two planes
         constexpr int lds = walk_grad_lds(true);
-        const dim3 grid(sp.nseg, d.seqs());
         if (d.kind == 0) {
             if ((e = allow_lds(mk_walk_grad<false, false, true>, lds)) != hipSuccess) return e;
             hipLaunchKernelGGL((mk_walk_grad<false, false, true>), grid, block, lds, st, d, ga);
@@ -907,7 +907,6 @@ hipError_t launch_walk_grad(const Dims& d, const SegPlan& sp, const GradArgs& ga
         }
         return hipSuccess;
     }
-    const dim3 grid(walk_grid_x(d, sp.m, sp.nseg), walk_grid_y(d));
     // d_v = 256: pass 0 leaves dq and dk in the partial planes (WIDE 1), pass 1 adds them to its own (WIDE 2)
     const int wide = d.vm == 1 ? 0 : (d.vs == 0 ? 1 : 2);
     auto launch = [&](auto kernel) -> hipError_t {
@@ -1064,6 +1063,20 @@ size_t delta_seg_bytes(const Dims& d) {
     const SegPlan sp = delta_plan(d);
     return sp.nseg > 1 ? 3 * align256(size_t(d.seqs()) * sp.nseg * D * D * 4) : 0;
 }
+// Segments of the gradient walker.  It needs no summary of its own: the forward walk leaves its state wherever a segment begins
+// (64 KB each), so they are shorter than the other walkers' where that fills the last round of workgroups, of which a compute
+// unit holds one, better.  Packed sequences are unequal, and delta_plan() makes one segment of most: there by the chunks there are.
+// Forward + backward in the delta walkers' segments and so, us: 320 sequences of 2048 1338 and 1282, 144 of 2048 1017 and
+// 1020 (with a decay 1192 and 1148), 288 of 1024 657 and 656 (776 and 727); packed, 16 heads, 8 of 1000 359 and 332, one of 4000 with
+// 17 of 200 1093 and 745, 200 to 4000, 6 of them, 1142 and 933; but 32 heads, 20 to 1200, 12 of them, 410 and 440 (few are longer
+// than the segment of 11 chunks, and none much).
+SegPlan delta_grad_plan(const Dims& d) {
+    const SegPlan sp = delta_plan(d), fine = seg_plan(d);
+    auto cost = [&](const SegPlan& p) { return (long long)(size_t(d.seqs()) * p.nseg + 255) / 256 * p.m; };  // chunks one after the other
+    return d.nseq || cost(fine) < cost(sp) ? fine : sp;
+}
+bool delta_grad_apart(const Dims& d) { return d.nseq || delta_grad_plan(d).m != delta_plan(d).m; }
+size_t delta_entry_bytes(const Dims& d) { return delta_grad_apart(d) ? align256(bound_slots(d, delta_grad_plan(d)) * D * D * 4) : 0; }
 size_t delta_t_bytes(const Dims& d) { return align256(size_t(d.BH()) * d.N * kDeltaT * 2); }
 const float* delta_entries(const Dims& d, const void* segws) {
     return reinterpret_cast<const float*>(static_cast<const char*>(segws) + delta_seg_bytes(d) / 3 * 2);
@@ -1170,6 +1183,7 @@ hipError_t launch_delta_rwalk(const Dims& d, DeltaRevArgs ra, const void* segf, 
 
 struct DeltaWs {
     uint16_t *tt, *usave, *usave_l, *dstates, *w_h, *w_l;
+    float* entries;  // entry states of the gradient walker's segments, NULL: those of the delta walker's
     void* seg;    // segment summaries and entry states of the delta walker
     void* seg_r;  // the same for the reverse walker, without factors of its own
     size_t bytes;
@@ -1186,6 +1200,7 @@ DeltaWs carve_delta(const Dims& d, void* ws) {
     w.dstates = reinterpret_cast<uint16_t*>(take(size_t(d.BH()) * d.N * D * D * 2));
     w.w_h = reinterpret_cast<uint16_t*>(take(rows * D * 2));
     w.w_l = reinterpret_cast<uint16_t*>(take(rows * D * 2));
+    if (delta_entry_bytes(d)) w.entries = reinterpret_cast<float*>(take(delta_entry_bytes(d)));
     w.seg = p + off;
     off += delta_seg_bytes(d);
     w.seg_r = p + off;
@@ -1194,6 +1209,12 @@ DeltaWs carve_delta(const Dims& d, void* ws) {
     return w;
 }
 size_t carve_delta_bytes(const Dims& d) { return carve_delta(d, nullptr).bytes; }
+void delta_leave_entries(const Dims& d, const DeltaWs& w, DeltaWalkArgs& wa) {
+    const SegPlan gp = delta_grad_plan(d);
+    wa.entries = w.entries;
+    wa.em = gp.m;
+    wa.en = gp.nseg;
+}
 }  // namespace
 size_t delta_bwd_workspace(const Dims& d) { return carve_delta(d, nullptr).bytes; }
 
@@ -1201,20 +1222,22 @@ hipError_t delta_fwd_saving(const Dims& d, const DeltaArgs& a) {
     const DeltaWs w = carve_delta(d, a.ws);
     auto q = static_cast<const uint16_t*>(a.q), k = static_cast<const uint16_t*>(a.k), v = static_cast<const uint16_t*>(a.v);
     const DeltaPrepArgs pa{k, a.log_alpha, a.beta, w.tt};
-    const DeltaWalkArgs wa{q, k, v, w.tt, a.log_alpha, a.beta, a.bw, static_cast<uint16_t*>(a.o), a.m0, a.mT, w.usave, w.usave_l};
+    DeltaWalkArgs wa{q, k, v, w.tt, a.log_alpha, a.beta, a.bw, static_cast<uint16_t*>(a.o), a.m0, a.mT, w.usave, w.usave_l};
+    delta_leave_entries(d, w, wa);
     return launch_delta_fwd(d, pa, wa, w.seg, a.stream);
 }
 
 hipError_t delta_bwd(const Dims& d, const DeltaBwdArgs& a) {
     const DeltaWs w = carve_delta(d, a.ws);
-    const SegPlan sp = delta_plan(d);
+    const SegPlan sp = delta_grad_plan(d);
     auto q = static_cast<const uint16_t*>(a.q), k = static_cast<const uint16_t*>(a.k), v = static_cast<const uint16_t*>(a.v);
     auto d_o = static_cast<const uint16_t*>(a.d_o);
     hipError_t e;
     // forward again: T, the pseudo-values U in the layout of v, the segments' factors and entry states
     if (!d.save) {
         const DeltaPrepArgs pa{k, a.log_alpha, a.beta, w.tt};
-        const DeltaWalkArgs wa{q, k, v, w.tt, a.log_alpha, a.beta, a.bw, nullptr, a.m0, nullptr, w.usave, w.usave_l};
+        DeltaWalkArgs wa{q, k, v, w.tt, a.log_alpha, a.beta, a.bw, nullptr, a.m0, nullptr, w.usave, w.usave_l};
+        delta_leave_entries(d, w, wa);
         if ((e = launch_delta_fwd(d, pa, wa, w.seg, a.stream)) != hipSuccess) return e;
     }
     // backward in time: state gradients, W, dv and db
@@ -1223,7 +1246,8 @@ hipError_t delta_bwd(const Dims& d, const DeltaBwdArgs& a) {
     if (e != hipSuccess) return e;
     // forward in time, with U as the values: dq, dk and the gradients of decay and erase strength
     GradArgs ga{q, k, w.usave, d_o, a.log_alpha, w.dstates, static_cast<uint16_t*>(a.dq), static_cast<uint16_t*>(a.dk), nullptr,
-                d.kind == 0 ? nullptr : a.d_log_alpha, a.m0, delta_entries(d, w.seg), sp.m, sp.nseg, w.usave_l, w.w_h, w.w_l, a.beta, a.d_beta};
+                d.kind == 0 ? nullptr : a.d_log_alpha, a.m0, delta_grad_apart(d) ? w.entries : delta_entries(d, w.seg), sp.m, sp.nseg,
+                w.usave_l, w.w_h, w.w_l, a.beta, a.d_beta};
     if ((e = launch_walk_grad(d, sp, ga, a.stream)) != hipSuccess) return e;
     return hipGetLastError();
 }

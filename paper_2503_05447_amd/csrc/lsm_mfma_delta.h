@@ -210,6 +210,10 @@ struct DeltaWalkArgs {
     int m, nseg;
     const float* bound;
     float* sum;
+    // the gradient walker's entry states, where its segments are not this walk's (NULL: they are): the state before every em-th
+    // chunk of a sequence, slots as bound_slot() numbers them for en segments a sequence
+    float* entries;
+    int em, en;
 };
 
 // The walk (MODE 0), and the summaries of a segment for the cut into segments: the state part of the walk alone, from a
@@ -285,6 +289,11 @@ __global__ __launch_bounds__(512, 1) void mk_delta_walk8(Dims d, DeltaWalkArgs a
             const uint16_t* K = K2 + (kk & 1) * C * LD;
             const float* bs = tab + (kk & 1) * kDeltaTab;
             const float *wo = bs + C + 4, *ne = wo + C, *bb = ne + C;
+            if (MODE == 0 && a.entries) {
+                const int k = kbeg + kk;
+                if (k > 0 && k % a.em == 0)
+                    walk_state_store(S, a.entries + (bound_slot(d, walk, a.em, a.en) + k / a.em) * D * D, false, wave, n, half);
+            }
             __syncthreads();  // (A) the tiles and the tables of this chunk are in LDS
             fresh();
             // both inter products with one conversion of the state blocks: R[t][v] = sum_i k_t[i] S[i][v], O^T[v][j] = sum_i S[i][v] q_j[i]

@@ -379,7 +379,7 @@ struct GradArgs {
 //   dk_t += beta_t X_t + sum_{j > t} beta_j H_jt k_j ,   dg as for a second query with gradient beta_t X_t.
 // The area of As holds beta H; that of the dS rows the two planes of W, then beta X (fp32), which the group that has the rest
 // of dk adds before the one rounding.  d beta takes the score part as row sums of H * (K K^T), unscaled (beta may be 0).
-// A segment is one of the reverse walk's, entry states from the forward walk's chain of segments.
+// Entry states of the segments come from the forward walk (delta_grad_plan).
 constexpr int LDX = 34;  // floats per row of a wave's 64 x 32 part of the stage of beta X
 constexpr int kWalkGradSplitExtra = C * LD * 2 + (C + 3 * 32 + 4 * C) * 4;  // second value tile | beta | row sums | k . X per wave
 __host__ __device__ constexpr int walk_grad_lds(bool vsplit) { return kWalkGradLds + (vsplit ? kWalkGradSplitExtra : 0); }
@@ -499,7 +499,7 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
     static_assert(2 * C * LDP >= C * LD, "a 64 x LD stage fits the area of G");
     constexpr int NT = VSPLIT ? 256 : kGrad8Threads;  // threads that share the tile traffic
 
-    const SegIndex si = VSPLIT ? SegIndex{seq_walk(d, blockIdx.y), int(blockIdx.x)} : seg_index(d, a.m, blockIdx.x, blockIdx.y);
+    const SegIndex si = seg_index(d, a.m, blockIdx.x, blockIdx.y);
     if (si.seg < 0) return;
     const SeqWalk walk = si.walk;
     const int seq = walk.edge, seg = si.seg;
@@ -610,8 +610,7 @@ __global__ __launch_bounds__(kGrad8Threads, 1) void mk_walk_grad(Dims d, GradArg
         _Pragma("unroll") for (int vb = 0; vb < 4; ++vb) S[vb] = f32x16{0};
         {
             const int per = a.bound_per ? a.bound_per : 1;
-            if (VSPLIT && a.nseg > 1) walk_state_load(S, a.bound + (size_t(seq) * a.nseg + seg) * D * D, true, wave, n, half);
-            else if (!VSPLIT && seg > 0)
+            if (seg > 0)
                 walk_state_load(S, a.bound + (bound_slot(d, walk, a.m / per, a.bound_per ? a.bound_n : a.nseg) + seg * per) * D * D, true, wave, n, half);
             else if (a.edge_in) walk_state_load(S, a.edge_in + edge_off(d, seq), true, wave, n, half, D * d.vm);
         }

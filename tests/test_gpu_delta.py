@@ -144,10 +144,12 @@ def run_bwd_and_check(x, layout=0):
 BWD_SHAPES = [(1, 2, 64), (2, 2, 37), (2, 3, 200), (1, 3, 700), (5, 8, 1500)]
 # every sequence one segment (from 192 sequences on): whole chunks, a ragged tail of one token, one ragged chunk
 WHOLE_SHAPES = [(6, 32, 128), (8, 25, 129), (6, 32, 50)]
+# the gradient walker's segments shorter than the other walkers': two in each of theirs, and two where those have one
+FINER_SHAPES = [(9, 16, 500), (18, 16, 200)]
 
 
 @pytest.mark.parametrize("gated", [False, True])
-@pytest.mark.parametrize("shape", BWD_SHAPES + WHOLE_SHAPES)
+@pytest.mark.parametrize("shape", BWD_SHAPES + WHOLE_SHAPES + FINER_SHAPES)
 def test_delta_backward_matches_oracle(shape, gated):
     B, H, T = shape
     x = wl.make_delta_inputs(B, H, T, 128, 128, gated, seed=5100 + T + int(gated), init_state=True, d_final=True)
@@ -415,6 +417,45 @@ def test_delta_packed_factors_of_cut_sequences_only():
     for s in range(seqs):
         n = own[s // H]
         assert written[s].tolist() == [i < n and n > 1 for i in range(nseg)], (s, n)
+
+
+@pytest.mark.parametrize("gated", [False, True])
+def test_delta_packed_segments_of_several_chunks(gated):
+    """Sequences of one segment and of two beside each other, in segments of 13 chunks, the gradient walker's of 2 chunks: against the
+    oracle sequence by sequence (calls of their own are cut otherwise)."""
+    import torch
+    import paper_2503_05447_amd as pkg
+    from oracle import delta_oracle_bwd, delta_oracle_fwd
+    lens, H = [1500, 40, 0, 700, 64, 130], 16
+    T, n = sum(lens), len(lens)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    x = wl.make_delta_inputs(1, H, T, 128, 128, gated, seed=6400 + int(gated), tie_b=False, decay="weak")
+    rng = np.random.default_rng(6401)
+    x["m0"] = (rng.standard_normal((n, H, 128, 128)) * 0.1).astype(np.float32)
+    x["d_mT"] = (rng.standard_normal((n, H, 128, 128)) * 0.1).astype(np.float32)
+    t = dev(x)
+    d_o, d_mT = torch.from_numpy(x["d_o"]).to(t["q"].device).to(torch.bfloat16), torch.from_numpy(x["d_mT"]).to(t["q"].device)
+    cu_d = torch.from_numpy(cu).to(t["q"].device)
+    pars = (t["log_alpha"], t["beta"], t["b"], t["m0"])
+    o, mT = pkg.lsm_delta_fwd(t["q"], t["k"], t["v"], *pars, cu_seqlens=cu_d)
+    r = pkg.lsm_delta_bwd(t["q"], t["k"], t["v"], d_o, *pars, d_mT, cu_seqlens=cu_d)
+    torch.cuda.synchronize()
+    for s_, (lo, hi) in enumerate(zip(cu[:-1], cu[1:])):
+        if hi == lo:
+            assert torch.equal(mT[s_], t["m0"][s_]) and torch.equal(r["d_init_state"][s_], d_mT[s_])
+            continue
+        cut = lambda a: None if a is None else np.ascontiguousarray(a[:, :, lo:hi])
+        args = [cut(x[m]) for m in ("q", "k", "v")]
+        par = [cut(x[m]) for m in ("log_alpha", "beta", "b")]
+        o_ref, mT_ref = delta_oracle_fwd(*args, *par, x["m0"][s_:s_ + 1])
+        ref = delta_oracle_bwd(*args, cut(x["d_o"]), *par, x["m0"][s_:s_ + 1], x["d_mT"][s_:s_ + 1])
+        errs = dict(o=rel_err(host(o[:, :, lo:hi]), o_ref, BF16_HALF_ULP), final_state=rel_err(host(mT[s_:s_ + 1]), mT_ref),
+                    d_init_state=rel_err(host(r["d_init_state"][s_:s_ + 1]), ref["d_m0"]))
+        for m in ("dq", "dk", "dv", "d_log_alpha", "d_beta", "d_b"):
+            if ref[m] is not None:
+                errs[m] = rel_err(host(r[m][:, :, lo:hi]), ref[m], BF16_HALF_ULP if m in ("dq", "dk", "dv") else 0.0)
+        print("packed, %d tokens: %s" % (hi - lo, " ".join("%s %.1e" % e for e in errs.items())), flush=True)
+        assert max(errs.values()) <= TOL, errs
 
 
 def test_delta_rejects_what_it_does_not_serve():
