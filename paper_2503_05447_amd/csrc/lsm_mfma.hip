@@ -98,7 +98,7 @@ constexpr int LDB = 40;  // row stride (elements) of a 64 x 32 B-side slice in L
 // LDS: 2 x (A tile 64 x LD | B slice head 64 x LDB | B slice remainder 64 x LDB) for chunks k+1, k+2
 // (the state leaves straight from the registers, see state_store_direct)
 constexpr int kStateTile = C * LD + 2 * C * LDB;
-constexpr int kStateLds = 2 * kStateTile * 2;
+constexpr int kStateLds = 2 * kStateTile * 2, kStateLdsT = kStateLds + 2 * 32 * 4;  // (T: and the decays of chunks k+1, k+2)
 
 struct StateRegs {  // one thread's share of a chunk on its way from global memory to LDS
     u32x4 a[4], b, blo;  // blo: remainder plane of the B slice (vector decay: both planes arrive precomputed)
@@ -200,6 +200,9 @@ __device__ __forceinline__ size_t state_frag_off(int blk, int ks, int lane) {
 // (4 + 4 rows) of every group of 8 rows; one v_permlane32_swap per dword hands each lane a whole group:
 // the lower lanes the even groups, the upper lanes the odd ones, i.e. exactly the 16 bytes that lane
 // 32 hf + n of fragment (rowblk, 2 mb + q) holds, and a wave stores one contiguous KiB per instruction.
+// CACHED: the next kernel reads the states out of the caches (vec_fwd), else they go past them.  (Not an argument: of two stores
+// behind a branch the compiler makes one, without the hint.)
+template <bool CACHED = false>
 __device__ __forceinline__ void state_store_direct(uint16_t* dst, int rowblk, int mb, int lane, const f32x16& acc) {
     _Pragma("unroll") for (int q = 0; q < 2; ++q) {
         const uint32_t a0 = pack2(acc[8 * q + 0], acc[8 * q + 1]), a1 = pack2(acc[8 * q + 2], acc[8 * q + 3]);
@@ -207,7 +210,9 @@ __device__ __forceinline__ void state_store_direct(uint16_t* dst, int rowblk, in
         const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
         const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
         const u32x4 val = {s0[0], s1[0], s0[1], s1[1]};
-        __builtin_nontemporal_store(val, reinterpret_cast<u32x4*>(dst + state_frag_off(rowblk, 2 * mb + q, lane)));
+        u32x4* p = reinterpret_cast<u32x4*>(dst + state_frag_off(rowblk, 2 * mb + q, lane));
+        if constexpr (CACHED) *p = val;
+        else __builtin_nontemporal_store(val, p);
     }
 }
 // with the 8-bit remainder plane: (x - head) * 2^8 as an 8-bit float, same element order, one byte each
@@ -239,7 +244,10 @@ __device__ __forceinline__ void state_store_direct_split8(uint16_t* dst, uint8_t
 // and e^{b_C[i]} is one factor per lane; the A side is a 128-wide slice of the value-sized operand
 // (row stride d_v), each slice being scanned like a sequence of its own.
 // MODE 1 then serves the forward pass too: one copy of the states, S [i][v], for all of their readers.
-template <int MODE, bool DEC, bool VEC>
+// TRANS (MODE 1, VEC): the operands change places, so that a state column is a value feature and the states leave as S^T [v][i],
+// the order in which the output kernel, the only reader where nothing is kept, has its operand.  The decays are then one per
+// register and come from LDS.  (2: by plain stores)
+template <int MODE, bool DEC, bool VEC, int TRANS = 0>
 __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& sa, int wg_id, int wg_count,
                                                 unsigned char* smem) {
     const uint16_t* __restrict__ xa = sa.xa;
@@ -252,6 +260,7 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
     const float* __restrict__ edge_in = sa.edge_in;
     float* __restrict__ edge_out = sa.edge_out;
     uint16_t* tiles = reinterpret_cast<uint16_t*>(smem);         // [2][kStateTile]
+    float* lamt = reinterpret_cast<float*>(tiles + 2 * kStateTile);  // TRANS: [2][32]
     // The four workgroups of a sequence read the same A-side rows.  Workgroups are dealt to the 8
     // XCDs round-robin by linear id, so the id is decoded such that those four share an XCD (and
     // its L2): id = xcd + 8 * (4 * (seq / 8) + nb), seq = xcd + 8 * (seq / 8).  The value slices of a sequence, which
@@ -281,23 +290,23 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
     const int erow = VEC ? sa.a_stride : D * d.vm;  // row stride of the fp32 edge states [i][v]
     const int vcol = VEC ? D * vh : D * d.vs;       // first value column of this scan in the value-sized arrays
 
-    // acc[4g+j] = state element (m = 32mb + 8g + 4half + j, n = 32nb + lane%32); MODE 0: m = i, else m = v
+    // acc[4g+j] = state element (m = 32mb + 8g + 4half + j, n = 32nb + lane%32); MODE 0: m = i, else m = v; TRANS: mb and nb, which
+    // stay the operands' blocks, the other way round
     f32x16 acc = {0};
+    auto edge_at = [&](int x, int row) {  // acc[x] in an edge state [i][v]
+        const int mm = 8 * (x >> 2) + 4 * half + (x & 3);
+        if (TRANS) return (32 * nb + mm) * row + 32 * mb + n;
+        return MODE == 0 ? (32 * mb + mm) * row + 32 * nb + n : (32 * nb + n) * row + 32 * mb + mm;
+    };
     if (nsegs > 1 && walk.n > 0) {
         // MODE 2 walks backward: it enters with the state of the last fine segment it covers
         const int nfine = (walk.n + sa.fine_m - 1) / sa.fine_m, per = sa.seg_m / sa.fine_m;
         const int f = MODE == 2 ? min(nfine, (seg + 1) * per) - 1 : seg * per;
         const float* e = sa.seg_bound + (bound_slot(d, walk, sa.fine_m, sa.fine_n) + f) * D * D;
-        _Pragma("unroll") for (int r = 0; r < 16; ++r) {
-            const int mm = 32 * mb + 8 * (r >> 2) + 4 * half + (r & 3), nn = 32 * nb + n;
-            acc[r] = MODE == 0 ? e[mm * D + nn] : e[nn * D + mm];
-        }
+        _Pragma("unroll") for (int x = 0; x < 16; ++x) acc[x] = e[edge_at(x, D)];
     } else if (edge_in) {
         const float* e = edge_in + size_t(walk.edge) * D * erow + vcol;
-        _Pragma("unroll") for (int r = 0; r < 16; ++r) {
-            const int mm = 32 * mb + 8 * (r >> 2) + 4 * half + (r & 3), nn = 32 * nb + n;
-            acc[r] = MODE == 0 ? e[mm * erow + nn] : e[nn * erow + mm];
-        }
+        _Pragma("unroll") for (int x = 0; x < 16; ++x) acc[x] = e[edge_at(x, erow)];
     }
     const int first = MODE == 2 ? kend - 1 : kbeg, step = MODE == 2 ? -1 : 1;
     // the state this walk ends with leaves through edge_out only where the walk ends the sequence
@@ -308,7 +317,7 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
     const uint16_t* xav = xa + vcol;
     auto gload = [&](int kc, StateRegs& r) {
         // the kc-th chunk of the walk (clamped at the end); it goes to LDS during iteration kc - 2
-        const int c = first + step * min(kc, cnt - 1), clam = first + step * min(max(kc - 2, 0), cnt - 1);
+        const int c = first + step * min(kc, cnt - 1), clam = TRANS ? c : first + step * min(max(kc - 2, 0), cnt - 1);
         state_gload<DEC, VEC>(d, xav, xb, xb_lo, wts, lam, sa.a_stride, walk_pos(d, walk, c),
                               size_t(walk.bh) * d.N + walk.c0 + clam, 32 * nb, tid, r);
     };
@@ -319,20 +328,18 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
     if (cnt <= 0) {  // an empty sequence of a packed input: the state passes through
         if (edge_out) {
             float* e = edge_out + size_t(walk.edge) * D * erow + vcol;
-            _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-                const int mm = 32 * mb + 8 * (x >> 2) + 4 * half + (x & 3), nn = 32 * nb + n;
-                if (MODE == 0) e[mm * erow + nn] = acc[x];
-                else e[nn * erow + mm] = acc[x];
-            }
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) e[edge_at(x, erow)] = acc[x];
         }
         return;
     }
     gload(0, r0);
     if (cnt > 1) gload(1, r1);
-    state_to_lds<DEC, VEC>(r0, bufA(0), bufB(0), tid);
-    if (cnt > 1) {
-        state_to_lds<DEC, VEC>(r1, bufA(1), bufB(1), tid);
-    }
+    auto to_lds = [&](int k, const StateRegs& r) {
+        state_to_lds<DEC, VEC>(r, bufA(k), bufB(k), tid);
+        if (TRANS && tid < 32) lamt[32 * (k & 1) + tid] = r.lam;
+    };
+    to_lds(0, r0);
+    if (cnt > 1) to_lds(1, r1);
     gload(2, r0);
     gload(3, r1);
     __syncthreads();
@@ -344,9 +351,18 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
     auto iteration = [&](int k, StateRegs& rw, StateRegs& rl) {
         gload(k + 4, rl);
         // the state this chunk starts from (MODE 2: the gradient this chunk ends with): registers -> global memory
-        if (states_rem) state_store_direct_split8(states + slot(k), reinterpret_cast<uint8_t*>(states_rem) + slot(k), nb, mb, lane, acc);
+        if (TRANS) state_store_direct<TRANS == 2>(states + slot(k), mb, nb, lane, acc);
+        else if (states_rem) state_store_direct_split8(states + slot(k), reinterpret_cast<uint8_t*>(states_rem) + slot(k), nb, mb, lane, acc);
         else state_store_direct(states + slot(k), nb, mb, lane, acc);
-        if (DEC) {
+        if (TRANS) {
+            _Pragma("unroll") for (int g = 0; g < 4; ++g) {
+                const float4 l = *reinterpret_cast<const float4*>(lamt + 32 * (k & 1) + 8 * g + 4 * half);
+                acc[4 * g] *= l.x;
+                acc[4 * g + 1] *= l.y;
+                acc[4 * g + 2] *= l.z;
+                acc[4 * g + 3] *= l.w;
+            }
+        } else if (DEC) {
             const float lam_cur = rw.lam;
             _Pragma("unroll") for (int x = 0; x < 16; ++x) acc[x] *= lam_cur;
         }
@@ -354,11 +370,15 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
         const uint16_t *ta = bufA(k), *tb = bufB(k);
         _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
             const bf16x8 fa = frag_tr4(ta, LD, 16 * ks, 32 * mb, lane);
-            acc = mfma(fa, frag_tr4(tb, LDB, 16 * ks, 0, lane), acc);
-            if (DEC) acc = mfma(fa, frag_tr4(tb + C * LDB, LDB, 16 * ks, 0, lane), acc);
+            const bf16x8 fb = frag_tr4(tb, LDB, 16 * ks, 0, lane);
+            acc = TRANS ? mfma(fb, fa, acc) : mfma(fa, fb, acc);
+            if (DEC) {
+                const bf16x8 fl = frag_tr4(tb + C * LDB, LDB, 16 * ks, 0, lane);
+                acc = TRANS ? mfma(fl, fa, acc) : mfma(fa, fl, acc);
+            }
         }
         __syncthreads();  // every wave is done with the tiles of chunk k
-        state_to_lds<DEC, VEC>(rw, bufA(k), bufB(k), tid);  // chunk k+2; read again two barriers from now
+        to_lds(k, rw);  // chunk k+2; read again two barriers from now
     };
     int k = 0;
     for (; k + 2 < cnt; k += 3) {
@@ -371,11 +391,7 @@ __device__ __forceinline__ void state_scan_body(const Dims& d, const StateArgs& 
     __syncthreads();
     if (edge_out) {
         float* e = edge_out + size_t(walk.edge) * D * erow + vcol;
-        _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-            const int mm = 32 * mb + 8 * (x >> 2) + 4 * half + (x & 3), nn = 32 * nb + n;
-            if (MODE == 0) e[mm * erow + nn] = acc[x];
-            else e[nn * erow + mm] = acc[x];
-        }
+        _Pragma("unroll") for (int x = 0; x < 16; ++x) e[edge_at(x, erow)] = acc[x];
     }
 }
 
@@ -549,11 +565,11 @@ __global__ void mk_head_reduce(Dims d, const float* __restrict__ dg_tok, float* 
     if (threadIdx.x == 0) dg[h] = part[0];
 }
 
-// vector decay kind: forward states (MODE 1) or the reverse scan of state gradients (MODE 2)
-template <int MODE>
+// vector decay kind: forward states (MODE 1; TRANS: for the output kernel alone) or the reverse scan of state gradients (MODE 2)
+template <int MODE, int TRANS = 0>
 __global__ __launch_bounds__(kThreads) void mk_state_vec(Dims d, StateArgs sa) {
     extern __shared__ __align__(16) unsigned char smem[];
-    state_scan_body<MODE, true, true>(d, sa, blockIdx.x, gridDim.x, smem);
+    state_scan_body<MODE, true, true, TRANS>(d, sa, blockIdx.x, gridDim.x, smem);
 }
 
 // both scans of the backward pass
@@ -811,14 +827,21 @@ hipError_t vec_fwd(const Dims& d, const FwdArgs& a) {
     if ((e = launch_vec_prep(d, a.stream, q, k, a.g, w)) != hipSuccess) return e;
     {
         ProfScope ps(KID_MFMA_STATE, a.stream);
-        if ((e = allow_lds(mk_state_vec<1>, kStateLds)) != hipSuccess) return e;
+        // Nothing kept: the states are for the output kernel alone, in its order, and where they fit the last-level cache (256 MB)
+        // by plain stores.  As a keeping call has them and so, scan + output us: d_v = 128, 4 x 16 sequences of 1024 26 + 21 and
+        // 25 + 19, of 4096 86 + 80 and 86 + 70; d_v = 256, of 4096 (268 MB) 143 + 115, by plain stores 142 + 121.
+        const bool cached = size_t(d.BH()) * nvh * d.N * D * D * 2 < size_t(256) << 20;
+        const auto scan = d.save ? mk_state_vec<1> : cached ? mk_state_vec<1, 2> : mk_state_vec<1, 1>;
+        const int lds = d.save ? kStateLds : kStateLdsT;
+        if ((e = allow_lds(scan, lds)) != hipSuccess) return e;
         const StateArgs sa{v, w.khat_hi, nullptr, w.lamv, w.states, d.save ? w.states_rem : nullptr, a.m0, a.mT, w.khat_lo, d.dv, nvh};
-        hipLaunchKernelGGL(mk_state_vec<1>, dim3(D / 32 * d.seqs() * nvh), dim3(kThreads), kStateLds, a.stream, d, sa);
+        hipLaunchKernelGGL(scan, dim3(D / 32 * d.seqs() * nvh), dim3(kThreads), lds, a.stream, d, sa);
     }
     {
         ProfScope ps(KID_MFMA_OUTPUT, a.stream);
-        if ((e = allow_lds(mk_output_vec<false>, kOutVecLds)) != hipSuccess) return e;
-        hipLaunchKernelGGL(mk_output_vec<false>, dim3(d.N * nvh, d.BH()), dim3(kThreads), kOutVecLds, a.stream, d, w.qhat_hi, w.qhat_lo, v,
+        const auto output = d.save ? mk_output_vec<false> : mk_output_vec<false, true>;
+        if ((e = allow_lds(output, kOutVecLds)) != hipSuccess) return e;
+        hipLaunchKernelGGL(output, dim3(d.N * nvh, d.BH()), dim3(kThreads), kOutVecLds, a.stream, d, w.qhat_hi, w.qhat_lo, v,
                            w.p_hi, w.p_lo, w.states, static_cast<uint16_t*>(a.o));
     }
     return hipGetLastError();

@@ -272,7 +272,8 @@ __device__ __forceinline__ void store_tile_strided(uint16_t* dst, const uint16_t
 // DV = true computes with the same structure the value gradient
 //   dv^T[v][r] = sum_i dS^T[v][i] khat_r[i] + sum_{j>=r} dO^T[v][j] P[j][r]
 // (states = dS, qhat = khat, v = d_o; P is read through the LDS transpose read).
-// The states lie in memory with their key features as rows, as mk_grad_vec reads them; here the key features are contracted, so the
+// TRANS: the states lie in memory with their value features as rows, this kernel's operand as it is (a forward call that keeps nothing).
+// Else they lie with their key features as rows, as mk_grad_vec reads them; here the key features are contracted, so the
 // slice passes through LDS first, rows of 128 values over V and P, and comes back by columns.  With a second, transposed copy of every
 // state for these two kernels alone, and their rows requested tile by tile: d_v = 256, 4 x 16 sequences of 4096, scans 214 and
 // 209 us, output 129, value gradient 204; this 176, 156, 118, 115.
@@ -280,7 +281,7 @@ __device__ __forceinline__ void store_tile_strided(uint16_t* dst, const uint16_t
 constexpr int kOutVecLds = 3 * C * LD * 2 + 2 * C * LDP * 2;
 static_assert(D * LD <= C * LD + 2 * C * LDP, "a state slice fits the area of V and P");
 
-template <bool DV>
+template <bool DV, bool TRANS = false>
 __global__ __launch_bounds__(kThreads, 2) void mk_output_vec(Dims d, const uint16_t* __restrict__ qhat,
                                                              const uint16_t* __restrict__ qhat_lo,
                                                              const uint16_t* __restrict__ v,
@@ -310,7 +311,8 @@ __global__ __launch_bounds__(kThreads, 2) void mk_output_vec(Dims d, const uint1
     uint16_t* St = V;  // [128][LD]
     u32x4 rs[8], rv[4], rp[4];
     TileRegs rq, rl;
-    _Pragma("unroll") for (int it = 0; it < 8; ++it) rs[it] = *reinterpret_cast<const u32x4*>(Sg + 8 * (tid + kThreads * it));
+    _Pragma("unroll") for (int it = 0; it < 8; ++it)
+        rs[it] = *reinterpret_cast<const u32x4*>(Sg + (TRANS ? state_frag_off(wave, it, lane) : size_t(8 * (tid + kThreads * it))));
     tile_gload(rq, qhat, wtok0, 1, L, tid);  // the library's own planes
     tile_gload(rl, qhat_lo, wtok0, 1, L, tid);
     const size_t poff = pos.slot * C * C;
@@ -319,16 +321,22 @@ __global__ __launch_bounds__(kThreads, 2) void mk_output_vec(Dims d, const uint1
         rv[it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v + (tok0 + size_t(min(row, L - 1)) * ts) * d.dv + D * vh + cp * 8));
         rp[it] = *reinterpret_cast<const u32x4*>((it < 2 ? p_hi : p_lo) + poff + 8 * (tid + kThreads * (it & 1)));
     }
-    _Pragma("unroll") for (int it = 0; it < 8; ++it) {  // fragment order: 32 rows of 8 values each, state_frag_off
-        const int p = tid + kThreads * it, l = p & 63;
-        *reinterpret_cast<u32x4*>(St + (32 * (p >> 9) + (l & 31)) * LD + 16 * ((p >> 6) & 7) + 8 * (l >> 5)) = rs[it];
+    bf16x8 sfrag[8];
+    if (!TRANS) {
+        _Pragma("unroll") for (int it = 0; it < 8; ++it) {  // fragment order: 32 rows of 8 values each, state_frag_off
+            const int p = tid + kThreads * it, l = p & 63;
+            *reinterpret_cast<u32x4*>(St + (32 * (p >> 9) + (l & 31)) * LD + 16 * ((p >> 6) & 7) + 8 * (l >> 5)) = rs[it];
+        }
     }
     tile_commit(Q, rq, L, tid);
     tile_commit(Ql, rl, L, tid);
-    __syncthreads();
-    bf16x8 sfrag[8];
-    _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) sfrag[ks] = frag_tr(St, LD, 16 * ks, 32 * wave, lane);
-    __syncthreads();  // the state slice is in registers; V and P take its place
+    if (!TRANS) {
+        __syncthreads();
+        _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) sfrag[ks] = frag_tr(St, LD, 16 * ks, 32 * wave, lane);
+        __syncthreads();  // the state slice is in registers; V and P take its place
+    } else {
+        _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) sfrag[ks] = __builtin_bit_cast(bf16x8, rs[ks]);
+    }
     _Pragma("unroll") for (int it = 0; it < 4; ++it) {
         const int p = tid + kThreads * it, row = p >> 4, cp = p & 15;
         const uint32_t keep = row < L ? 0xffffffffu : 0u;

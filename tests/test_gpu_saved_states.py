@@ -107,3 +107,29 @@ def test_flag_is_inert_where_nothing_is_kept(kind):
         assert torch.equal(r[key], r0[key]), key
     if kind != wl.KIND_NONE:
         assert torch.equal(r["dg"], r0["dg"])
+
+
+@pytest.mark.parametrize("dv", [128, 256])
+@pytest.mark.parametrize("lens", [[1], [63, 0, 65, 200], [129], [300]])
+def test_vector_kind_forward_is_the_same_with_and_without_keeping(lens, dv):
+    """A call that keeps nothing scans with the operands' places exchanged and leaves its states in another order: the same products,
+    the same roundings, bit for bit, over one to five chunks (the register sets of the scan turn after three), ragged ends, an empty
+    sequence and carried states."""
+    import torch
+    import paper_2503_05447_amd as pkg
+    T, n, H = sum(lens), len(lens), 3
+    x = wl.make_inputs(1, H, T, 128, dv, wl.KIND_VECTOR, dtype="bf16", seed=1600 + T + dv, decay="weak")
+    x["m0"] = (np.random.default_rng(6).standard_normal((n, H, 128, dv)) * 0.1).astype(np.float32)
+    x["d_mT"] = None
+    t = to_device(x)
+    cu = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).to(t["q"].device) if n > 1 else None
+    args = (t["q"], t["k"], t["v"], t["g"], wl.KIND_VECTOR, 64, t["m0"])
+    ws = pkg.lsm_chunk_workspace(*args[:5], cu_seqlens=cu, save_states=True)
+    o, mT = pkg.lsm_chunk_fwd(*args, cu_seqlens=cu)
+    o2, mT2 = pkg.lsm_chunk_fwd(*args, cu_seqlens=cu, workspace=ws, save_states=True)
+    torch.cuda.synchronize()
+    assert torch.equal(o, o2) and torch.equal(mT, mT2)
+    if n == 1:
+        o_ref, mT_ref, _ = oracle_all(x, backward=False)
+        check("o", host(o), o_ref, "bf16")
+        check("final_state", host(mT), mT_ref, "bf16")
