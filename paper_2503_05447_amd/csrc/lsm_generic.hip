@@ -264,8 +264,8 @@ __device__ __forceinline__ f32x16 causal_product(const float* z, int ld, const f
 
 // Have a block in its registers here.  Left alone the compiler puts what is added to a block in every phase off until the block is
 // used, phases later, and keeps the operands instead: gk_walk_vec's outputs, five levels of them, went through scratch memory,
-// behind every store before (20000 of 43000 clocks a step, bf16, d_k = 64, d_v = 128).  (o and dv of 64-wide values never did, and run
-// 1 to 2 % longer with it: not there.)
+// behind every store before (20000 of 43000 clocks a step, bf16, d_k = 64, d_v = 128).  (o and dv of 64-wide values: with 256 decayed
+// features 2 to 4 % shorter with it, fp32, 4 x 8 sequences of 2048 forward 507 and 486 us; with fewer up to 2 % longer, not there.)
 __device__ __forceinline__ void formed(f32x16& x) { asm volatile("" : "+v"(x)); }
 
 // What a workgroup walks.
@@ -1115,6 +1115,9 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
         auto item_ok = [&](int t, int i) { return PIECES * COLS >= NT * (i + 1) || t + NT * i < PIECES * COLS; };
         auto item_col = [&](int t, int i) { return (t + NT * i) % COLS; };
         auto item_piece = [&](int t, int i) { return (t + NT * i) / COLS; };
+        // (Two pieces have forms of their own: that a piece number is then 0 or 1 is not known to the compiler, and the
+        // general ones spill 14 to 28 registers more with 256 decayed features; fp32, d_v = 64, 4 x 8 sequences of 2048, forward 507 us, so
+        // and with the outputs formed() 486; d_k = 128 311 and 306.)
 
         auto gload = [&](int kk) {
             const int tid = fresh();
@@ -1166,7 +1169,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                         if (!SUM) at[i][x] = expf(dt[i][x]);
                         t += double(dt[i][x]);
                     }
-                    closing[i] = rev && L == GT && h == PIECES - 1 ? closing_n[i] : 0.f;
+                    closing[i] = rev && L == GT && (PIECES == 2 ? h != 0 : h == PIECES - 1) ? closing_n[i] : 0.f;
                     tot[h * COLS + item_col(tid, i)] = t + double(closing[i]);
                     if constexpr (!SUM && PIECES == 4) {
                         float f = 1.f, b = 1.f;
@@ -1188,11 +1191,15 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
         };
         auto write_start = [&](float* o) {  // weight e^{E_p} from the start of the step; also e^E
             each([&](int i, int h, int c) {
-                double all = 0.0, e = 0.0;
-                _Pragma("unroll") for (int u = 0; u < PIECES; ++u) {
-                    const double t = tot[u * COLS + c];
-                    if (u < h) e += t;
-                    all += t;
+                const double t0 = tot[c];
+                double all = 0.0, e = h ? t0 : 0.0;
+                if constexpr (PIECES == 4) {
+                    e = 0.0;
+                    _Pragma("unroll") for (int u = 0; u < PIECES; ++u) {
+                        const double t = tot[u * COLS + c];
+                        if (u < h) e += t;
+                        all += t;
+                    }
                 }
                 _Pragma("unroll") for (int x = 0; x < LEN; ++x) {
                     e += double(dt[i][x]);
@@ -1200,15 +1207,20 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                     const float wt = expf(float(e));
                     o[p * LW + c] = VEC == 1 ? Q[p * LQ + c] * wt : wt;
                 }
-                if (h == 0) lamv[c] = expf(float(all));
+                if (h == 0) lamv[c] = expf(float(PIECES == 4 ? all : t0 + tot[COLS + c]));
             });
         };
         auto write_end = [&](float* o) {  // weight e^{E - E_p} to the end of the step, on the state update's operand
             each([&](int i, int h, int c) {
-                double e = 0.0;
-                _Pragma("unroll") for (int u = PIECES - 1; u > 0; --u)
-                    if (u > h) e += tot[u * COLS + c];
-                if (h == PIECES - 1) e = double(closing[i]);
+                double e;
+                if constexpr (PIECES == 2) {
+                    e = h ? double(closing[i]) : tot[COLS + c];
+                } else {
+                    e = 0.0;
+                    _Pragma("unroll") for (int u = PIECES - 1; u > 0; --u)
+                        if (u > h) e += tot[u * COLS + c];
+                    if (h == PIECES - 1) e = double(closing[i]);
+                }
                 if (SUM && h == 0) {
                     const double all = tot[c] + e;
                     lamv[c] = expf(float(all));
@@ -1230,7 +1242,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                 constexpr int B = lv < LEN ? lv : LEN;      // positions of a block in this piece
                 _Pragma("unroll") for (int b = 0; b < LEN; b += B) {
                     const int first = LEN * h + b;
-                    const bool odd = B == lv && LEN % (2 * lv) == 0 ? ((b / lv) & 1) != 0 : ((first / lv) & 1) != 0;
+                    const bool odd = PIECES == 2 && lv == 16 ? h != 0 : B == lv && LEN % (2 * lv) == 0 ? ((b / lv) & 1) != 0 : ((first / lv) & 1) != 0;
                     float e[B], prod = 1.f;
                     if (lv > LEN && (h & 1) == (odd ? 1 : 0)) prod = odd ? fwdp[(h - 1) * COLS + c] : bwdp[(h + 1) * COLS + c];
                     if (odd) {  // query side: from the block's start up to the position
@@ -1370,7 +1382,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                             const int r = hrow(x, l >> 5);
                             if (r < n && (r ^ n) >= lv && (r ^ n) < 2 * lv) P[x] = G[x];
                         }
-                        if constexpr (TV == 128) formed(P);
+                        if constexpr (TV == 128 || KD == 256) formed(P);
                         if constexpr (lv == 1) block_store(P);
                         __syncthreads();  // (L)
                     });
@@ -1381,7 +1393,7 @@ __global__ __launch_bounds__(4 * TV, KD == 256 ? 1 : 2) void gk_walk_vec(Dims d,
                     __syncthreads();  // (M)
                     const f32x16 X = causal_product<0>(V + 32 * w, LV, P, fresh() & 63, [](int s, int p) { return s < p; });
                     _Pragma("unroll") for (int x = 0; x < 16; ++x) O[x] += X[x];
-                    if constexpr (TV == 128) formed(O);
+                    if constexpr (TV == 128 || KD == 256) formed(O);
                 } else {
                     if constexpr (RAW) block_store(score_raw());
                     else block_store(score_part(K, Q, LQ));
