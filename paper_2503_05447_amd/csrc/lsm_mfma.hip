@@ -617,9 +617,6 @@ Ws carve(const Dims& d, void* ws, bool bwd) {
         w.p_hi = reinterpret_cast<uint16_t*>(p + off); off += sc;
         w.p_lo = reinterpret_cast<uint16_t*>(p + off); off += sc;
         w.lamv = reinterpret_cast<float*>(p + off); off += align256(size_t(d.BH()) * d.N * D * 4);
-        // Keeping states needs no more than recomputing them since both orders are read from one copy; the size query's
-        // promise that a buffer for keeping is the larger one (it covers every call of either sort) stands.
-        if (d.save) off += kSkew;
         w.bytes = off;
         return w;
     }
