@@ -321,9 +321,9 @@ struct GLds {
     static constexpr int QK = RAW && VEC == 2 ? GT * (KD + 8) / 2 : GT * LQ, VT = RAW && VEC == 1 ? GT * (TV + 8) / 2 : GT * LV;
     static constexpr int WT = GT * (COLS + 4), WN = SUM ? 1 : 2;
     static constexpr int oK = SUM ? 0 : QK, oV = oK + QK, oP = oV + VT, oW = oP + (SUM ? 0 : NW * 1024);
-    // a decayed feature's 32 positions are dealt to 2 threads of the group that weighs rows, or to 4 where there are as many: then the
-    // sums of four pieces, and their products for the level whose blocks are two pieces (d_k = 64, d_v = 128,
-    // 4 x 8 sequences of 2048, with 2: o and dv walkers 77 us, summary 37; with 4: 71 and 33)
+    // a decayed feature's 32 positions are dealt to 2 threads of the group that weighs rows, or to 4 where there are as many (of the
+    // supported shapes d_k = 64, d_v = 128 alone: o and dv, and the summary): then the sums of four pieces, and their products for the
+    // level whose blocks are two pieces (4 x 8 sequences of 2048, with 2: o and dv walkers 77 us, summary 37; with 4: 71 and 33)
     static constexpr int PIECES = 4 * COLS <= 2 * TV ? 4 : 2;
     static constexpr int oT = oW + WN * WT, total = oT + (PIECES == 4 ? 17 : 5) * COLS, bytes = total * 4;
 };

@@ -865,7 +865,7 @@ hipError_t walk_bounds(const Dims& d, hipStream_t st, const SegPlan& sp, const u
     {
         ProfScope ps(KID_WALK_SUMMARY, st);
         constexpr int lds = walk_lds(true);
-if (d.kind == 0) {
+        if (d.kind == 0) {
             if ((e = allow_lds(mk_walk<REV, false, true>, lds)) != hipSuccess) return e;
             hipLaunchKernelGGL((mk_walk<REV, false, true>), grid, block, lds, st, d, a);
         } else {

@@ -118,19 +118,8 @@ __device__ __forceinline__ float half_prefix(float x) {
     return x;
 }
 
-// 64 x 128 bf16 tile: global rows [tok0, tok0+L) -> LDS (row stride LD), rows >= L zero
-// (tok0 = row of the first token in src, ts = rows between consecutive tokens)
-__device__ __forceinline__ void load_tile(uint16_t* dst, const uint16_t* src, size_t tok0, int ts, int L, int tid) {
-    _Pragma("unroll") for (int it = 0; it < 4; ++it) {
-        const int p = tid + kThreads * it, row = p >> 4, cp = p & 15;
-        // uniform base (scalar registers) + a 32-bit byte offset per lane
-        const uint32_t off = (uint32_t(min(row, L - 1)) * uint32_t(ts) * D + cp * 8) * 2;
-        const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(src + tok0 * D) + off));
-        const uint32_t keep = row < L ? 0xffffffffu : 0u;  // branch-free: a branch around a load drains the load queue
-        *reinterpret_cast<u32x4*>(dst + row * LD + cp * 8) = u32x4{v.x & keep, v.y & keep, v.z & keep, v.w & keep};
-    }
-}
-// the same in two steps: global -> registers (no operation on the loaded values), registers -> LDS
+// 64 x 128 bf16 tile: global rows [tok0, tok0+L) -> registers (no operation on the loaded values) -> LDS (row stride LD), rows >= L
+// zero (tok0 = row of the first token in src, ts = rows between consecutive tokens)
 struct TileRegs { u32x4 v[4]; };
 __device__ __forceinline__ void tile_gload(TileRegs& r, const uint16_t* src, size_t tok0, int ts, int L, int tid) {
     _Pragma("unroll") for (int it = 0; it < 4; ++it) {

@@ -507,298 +507,298 @@ __global__ __launch_bounds__(kGradVecThreads, 1) void mk_grad_vec(Dims d, const 
     issue_rows(pos);
     issue_tiles(pos, 0, sr0);
     _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) issue_state(pos, 0, ks, sr0);
-  for (; job < jobs; pos = ahead) {
-    const int L = pos.L, ts = pos.ts;
-    const size_t tok0 = pos.tok0;
-    ahead = pos;
-    job = next_job(job + gridDim.x, ahead);
-    if (job >= jobs) ahead = pos;
-    fresh();
-    _Pragma("unroll") for (int it = 0; it < 2; ++it) {
-        int row, cpp;
-        tile_rows(it, row, cpp);
-        const uint32_t keep = row < L ? 0xffffffffu : 0u;
-        const float kf = row < L ? 1.f : 0.f;
-        *reinterpret_cast<u32x4*>(Qr + row * LD + cpp * 8) = u32x4{in.q[it].x & keep, in.q[it].y & keep, in.q[it].z & keep, in.q[it].w & keep};
-        *reinterpret_cast<u32x4*>(Kr + row * LD + cpp * 8) = u32x4{in.k[it].x & keep, in.k[it].y & keep, in.k[it].z & keep, in.k[it].w & keep};
-        *reinterpret_cast<float4*>(bt + row * LDF + cpp * 8) = float4{in.g[it][0].x * kf, in.g[it][0].y * kf, in.g[it][0].z * kf, in.g[it][0].w * kf};
-        *reinterpret_cast<float4*>(bt + row * LDF + cpp * 8 + 4) = float4{in.g[it][1].x * kf, in.g[it][1].y * kf, in.g[it][1].z * kf, in.g[it][1].w * kf};
-    }
-    __syncthreads();
-    fresh();
-    {   // inclusive scan of g along tokens: one feature column per thread, four quarters of 16 tokens
-        const int i = tid & 127, hq = tid >> 7;
-        float run = 0.f;
-        for (int r = 16 * hq; r < 16 * hq + 16; ++r) {
-            run += bt[r * LDF + i];
-            bt[r * LDF + i] = run;
+    for (; job < jobs; pos = ahead) {
+        const int L = pos.L, ts = pos.ts;
+        const size_t tok0 = pos.tok0;
+        ahead = pos;
+        job = next_job(job + gridDim.x, ahead);
+        if (job >= jobs) ahead = pos;
+        fresh();
+        _Pragma("unroll") for (int it = 0; it < 2; ++it) {
+            int row, cpp;
+            tile_rows(it, row, cpp);
+            const uint32_t keep = row < L ? 0xffffffffu : 0u;
+            const float kf = row < L ? 1.f : 0.f;
+            *reinterpret_cast<u32x4*>(Qr + row * LD + cpp * 8) = u32x4{in.q[it].x & keep, in.q[it].y & keep, in.q[it].z & keep, in.q[it].w & keep};
+            *reinterpret_cast<u32x4*>(Kr + row * LD + cpp * 8) = u32x4{in.k[it].x & keep, in.k[it].y & keep, in.k[it].z & keep, in.k[it].w & keep};
+            *reinterpret_cast<float4*>(bt + row * LDF + cpp * 8) = float4{in.g[it][0].x * kf, in.g[it][0].y * kf, in.g[it][0].z * kf, in.g[it][0].w * kf};
+            *reinterpret_cast<float4*>(bt + row * LDF + cpp * 8 + 4) = float4{in.g[it][1].x * kf, in.g[it][1].y * kf, in.g[it][1].z * kf, in.g[it][1].w * kf};
         }
         __syncthreads();
-        float base = 0.f;
-        for (int qq = 0; qq < hq; ++qq) base += bt[(16 * qq + 15) * LDF + i];
+        fresh();
+        {   // inclusive scan of g along tokens: one feature column per thread, four quarters of 16 tokens
+            const int i = tid & 127, hq = tid >> 7;
+            float run = 0.f;
+            for (int r = 16 * hq; r < 16 * hq + 16; ++r) {
+                run += bt[r * LDF + i];
+                bt[r * LDF + i] = run;
+            }
+            __syncthreads();
+            float base = 0.f;
+            for (int qq = 0; qq < hq; ++qq) base += bt[(16 * qq + 15) * LDF + i];
+            __syncthreads();
+            if (hq > 0)
+                for (int r = 16 * hq; r < 16 * hq + 16; ++r) bt[r * LDF + i] += base;
+        }
         __syncthreads();
-        if (hq > 0)
-            for (int r = 16 * hq; r < 16 * hq + 16; ++r) bt[r * LDF + i] += base;
-    }
-    __syncthreads();
 
-    // ---- inter parts and Z, slice by slice of the value dimension
-    // aqr, akr: contributions of the remainder planes of S and dS; they enter the decay gradient only, so
-    // that dq and dk do not depend on whether it is asked for
-    f32x16 aq = {0}, aqr = {0}, ak = {0}, akr = {0};
-    f32x16 z0 = {0};  // waves 0..3: Z; waves 4..7: S dS^T
-    // The next slice takes the registers of this one as they are used up, so that no trip to memory stands between the
-    // slices (d_v = 256, 4 x 16 sequences of 4096: 0.648 -> 0.624 ms).
-    for (int vh = 0; vh < nvh; ++vh) {
-        if (vh > 0) __syncthreads();  // the previous slice is consumed
-        fresh();
-        commit(sr0, L);
-        __syncthreads();
-        fresh();
-        if (vh + 1 < nvh) issue_tiles(pos, vh + 1, sr0);
-        _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) {
-            const bf16x8 sf = sr0.s[ks & 3], dsf = sr0.ds[ks & 3];
-            const bf16x8 dof = frag(T1, LD, t, 16 * ks + 8 * half), vf = frag(T0, LD, t, 16 * ks + 8 * half);
-            aq = mfma(sf, dof, aq);
-            ak = mfma(dsf, vf, ak);
-            if (want_dg) {
-                const bf16x8 srf = rem8_to_bf16(sr0.sr[ks & 3]), dsrf = rem8_to_bf16(sr0.dsr[ks & 3]);
-                aqr = mfma(srf, dof, aqr);
-                akr = mfma(dsrf, vf, akr);
-                // <S, dS> of every key feature, the diagonal of S dS^T (on the vector ALU: 60 instructions a k-step)
-                if (nb == 1) {
-                    z0 = mfma(srf, dsrf, z0);
-                    z0 = mfma(srf, dsf, z0);
-                    z0 = mfma(sf, dsrf, z0);
-                    z0 = mfma(sf, dsf, z0);
+        // ---- inter parts and Z, slice by slice of the value dimension
+        // aqr, akr: contributions of the remainder planes of S and dS; they enter the decay gradient only, so
+        // that dq and dk do not depend on whether it is asked for
+        f32x16 aq = {0}, aqr = {0}, ak = {0}, akr = {0};
+        f32x16 z0 = {0};  // waves 0..3: Z; waves 4..7: S dS^T
+        // The next slice takes the registers of this one as they are used up, so that no trip to memory stands between the
+        // slices (d_v = 256, 4 x 16 sequences of 4096: 0.648 -> 0.624 ms).
+        for (int vh = 0; vh < nvh; ++vh) {
+            if (vh > 0) __syncthreads();  // the previous slice is consumed
+            fresh();
+            commit(sr0, L);
+            __syncthreads();
+            fresh();
+            if (vh + 1 < nvh) issue_tiles(pos, vh + 1, sr0);
+            _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) {
+                const bf16x8 sf = sr0.s[ks & 3], dsf = sr0.ds[ks & 3];
+                const bf16x8 dof = frag(T1, LD, t, 16 * ks + 8 * half), vf = frag(T0, LD, t, 16 * ks + 8 * half);
+                aq = mfma(sf, dof, aq);
+                ak = mfma(dsf, vf, ak);
+                if (want_dg) {
+                    const bf16x8 srf = rem8_to_bf16(sr0.sr[ks & 3]), dsrf = rem8_to_bf16(sr0.dsr[ks & 3]);
+                    aqr = mfma(srf, dof, aqr);
+                    akr = mfma(dsrf, vf, akr);
+                    // <S, dS> of every key feature, the diagonal of S dS^T (on the vector ALU: 60 instructions a k-step)
+                    if (nb == 1) {
+                        z0 = mfma(srf, dsrf, z0);
+                        z0 = mfma(srf, dsf, z0);
+                        z0 = mfma(sf, dsrf, z0);
+                        z0 = mfma(sf, dsf, z0);
+                    }
+                }
+                if (ks < 4) issue_state(pos, vh, ks + 4, sr0);
+                else if (vh + 1 < nvh) issue_state(pos, vh + 1, ks - 4, sr0);
+            }
+            if (wv < 4) {  // this wave's block of Z: rows of V and d_o as operands
+                const int rowv = wv == 1 ? 32 + n : n;               // V row: wave 0, 2, 3: 0.., wave 1: 32..
+                const int rowo = wv == 0 ? n : 32 + n;               // d_o row: wave 0: 0.., else 32..
+                _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) {
+                    const bf16x8 fv = frag(T0, LD, rowv, 16 * ks + 8 * half), fo = frag(T1, LD, rowo, 16 * ks + 8 * half);
+                    if (wv == 3) z0 = mfma(fo, fv, z0);              // D[m][n] = d_o_{32+m} . v_n
+                    else z0 = mfma(fv, fo, z0);                      // D[m][n] = v_m . d_o_n
                 }
             }
-            if (ks < 4) issue_state(pos, vh, ks + 4, sr0);
-            else if (vh + 1 < nvh) issue_state(pos, vh + 1, ks - 4, sr0);
         }
-        if (wv < 4) {  // this wave's block of Z: rows of V and d_o as operands
-            const int rowv = wv == 1 ? 32 + n : n;               // V row: wave 0, 2, 3: 0.., wave 1: 32..
-            const int rowo = wv == 0 ? n : 32 + n;               // d_o row: wave 0: 0.., else 32..
-            _Pragma("unroll") for (int ks = 0; ks < 8; ++ks) {
-                const bf16x8 fv = frag(T0, LD, rowv, 16 * ks + 8 * half), fo = frag(T1, LD, rowo, 16 * ks + 8 * half);
-                if (wv == 3) z0 = mfma(fo, fv, z0);              // D[m][n] = d_o_{32+m} . v_n
-                else z0 = mfma(fv, fo, z0);                      // D[m][n] = v_m . d_o_n
-            }
-        }
-    }
-    fresh();
-    if (wv < 4) {  // Z[u][t] -> LDS rows t, head and remainder; diagonal of dA
-        const int ub = (wv == 1 || wv == 3) ? 1 : 0, tb = (wv == 1 || wv == 2) ? 1 : 0;
-        if (wv < 2) {
-            // the other triangle is the transpose: the block once by columns, a lane's pieces of it back by rows
-            _Pragma("unroll") for (int p = 0; p < 2; ++p) {
-                u32x4 h, l;
-                split_frag(z0, p, h, l);
-                store_frag_rows(Zh + (32 * wv + 16 * p) * LDP + 32 * wv, LDP, h, n, half);
-                store_frag_rows(Zl + (32 * wv + 16 * p) * LDP + 32 * wv, LDP, l, n, half);
-            }
-            __builtin_amdgcn_wave_barrier();
-            _Pragma("unroll") for (int x = 0; x < 16; ++x)
-                if (8 * (x >> 2) + 4 * half + (x & 3) == n) zd[32 * wv + n] = z0[x];
-            _Pragma("unroll") for (int g4 = 0; g4 < 4; ++g4) {
-                const int m0 = 8 * g4 + 4 * half, off = (32 * wv + n) * LDP + 32 * wv + m0;
-                const u32x2 h = *reinterpret_cast<const u32x2*>(Zh + off), l = *reinterpret_cast<const u32x2*>(Zl + off);
-                const float y[4] = {bf16_lo(h.x) + bf16_lo(l.x), bf16_hi(h.x) + bf16_hi(l.x), bf16_lo(h.y) + bf16_lo(l.y), bf16_hi(h.y) + bf16_hi(l.y)};
-                _Pragma("unroll") for (int j = 0; j < 4; ++j) z0[4 * g4 + j] = m0 + j <= n ? z0[4 * g4 + j] : y[j];
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-        store_block_t_split(Zh, Zl, LDP, 32 * tb + n, 32 * ub, half, z0);
-    }
-    // weights of the inter parts; the part of dg that needs dk^{inter}
-    f32x16 xk = {0};
-    _Pragma("unroll") for (int gq = 0; gq < 4; ++gq) {
-        const int col = 32 * wave + 8 * gq + 4 * half;
-        const float4 b4 = *reinterpret_cast<const float4*>(bt + t * LDF + col);
-        const float4 c4 = *reinterpret_cast<const float4*>(bt + 63 * LDF + col);
-        const float bb[4] = {b4.x, b4.y, b4.z, b4.w}, cc[4] = {c4.x, c4.y, c4.z, c4.w};
-        const u32x2 kk = *reinterpret_cast<const u32x2*>(Kr + t * LD + col);
-        const float kf[4] = {bf16_lo(kk.x), bf16_hi(kk.x), bf16_lo(kk.y), bf16_hi(kk.y)};
-        _Pragma("unroll") for (int jj = 0; jj < 4; ++jj) {
-            const int x = 4 * gq + jj;
-            const float wq = __expf(bb[jj]), wk = __expf(cc[jj] - bb[jj]);
-            aq[x] *= wq;
-            aqr[x] *= wq;
-            ak[x] *= wk;
-            akr[x] *= wk;
-            xk[x] = kf[jj] * (ak[x] + akr[x]);
-        }
-    }
-    if (want_dg && nb == 1) {
-        float zi = 0.f;
-        _Pragma("unroll") for (int x = 0; x < 16; ++x) zi += 8 * (x >> 2) + 4 * half + (x & 3) == n ? z0[x] : 0.f;
-        zi += __shfl_xor(zi, 32, 64);
-        if (half == 0) zl[32 * wave + n] = zi;
-    }
-
-    // ---- levels.  The level tiles are double-buffered, and the two waves of a SIMD (same features,
-    // token blocks 0 and 1) take the two halves of an iteration in opposite order: while one builds
-    // the tile of the next level (exponentials on the vector ALU) the other contracts the current one
-    // (LDS reads, MFMA), instead of both queueing for the same unit.
-    auto Wh = [&](int lv) { return (lv & 1) ? W1 : T0; };
-    auto Wl = [&](int lv) { return (lv & 1) ? W1 + C * LD : T1; };
-    auto build = [&](int lv) {
-        const int ls = 5 - lv;
-        uint16_t *wh = Wh(lv), *wl = Wl(lv);
         fresh();
-        const int cp = tid & 15, r0 = tid >> 4;  // W rows r0 and r0 + 32, features 8 cp .. + 7
-        _Pragma("unroll") for (int it = 0; it < 2; ++it) {
-            const int row = r0 + 32 * it;
-            bool qside;
-            const int ref = level_ref(row, ls, qside);
-            const float sl = level_sign(qside);
-            float b[8], br[8], w[8];
-            decay_row8(bt, row, cp * 8, b);
-            decay_row8(bt, ref, cp * 8, br);
-            _Pragma("unroll") for (int e = 0; e < 8; ++e) w[e] = level_weight(b[e], br[e], sl);
-            const u32x4 raw = *reinterpret_cast<const u32x4*>((qside ? Qr : Kr) + row * LD + cp * 8);
-            u32x4 hi, lo;
-            weigh8(raw, w, hi, &lo);
-            *reinterpret_cast<u32x4*>(wh + row * LD + cp * 8) = hi;
-            *reinterpret_cast<u32x4*>(wl + row * LD + cp * 8) = lo;
-        }
-    };
-    auto contract = [&](int lv) {
-        const int ls = 5 - lv;
-        const uint16_t *wh = Wh(lv), *wl = Wl(lv);
-        fresh();
-        const int ub = ls == 5 ? 1 - nb : nb;  // the partners of level 32 sit in the other 32-block
-        f32x16 X = {0};
-        _Pragma("unroll") for (int s2 = 0; s2 < 2; ++s2) {
-            const int u0 = 32 * ub + 16 * s2;
-            const int xr = (u0 + 8 * half) ^ t;
-            u32x4 mask;
-            _Pragma("unroll") for (int p = 0; p < 4; ++p)
-                mask[p] = ((((xr ^ (2 * p)) >> ls) == 1) ? 0xffffu : 0u) | ((((xr ^ (2 * p + 1)) >> ls) == 1) ? 0xffff0000u : 0u);
-            u32x4 zh = *reinterpret_cast<const u32x4*>(Zh + t * LDP + u0 + 8 * half);
-            u32x4 zlo = *reinterpret_cast<const u32x4*>(Zl + t * LDP + u0 + 8 * half);
-            _Pragma("unroll") for (int p = 0; p < 4; ++p) {
-                zh[p] &= mask[p];
-                zlo[p] &= mask[p];
+        if (wv < 4) {  // Z[u][t] -> LDS rows t, head and remainder; diagonal of dA
+            const int ub = (wv == 1 || wv == 3) ? 1 : 0, tb = (wv == 1 || wv == 2) ? 1 : 0;
+            if (wv < 2) {
+                // the other triangle is the transpose: the block once by columns, a lane's pieces of it back by rows
+                _Pragma("unroll") for (int p = 0; p < 2; ++p) {
+                    u32x4 h, l;
+                    split_frag(z0, p, h, l);
+                    store_frag_rows(Zh + (32 * wv + 16 * p) * LDP + 32 * wv, LDP, h, n, half);
+                    store_frag_rows(Zl + (32 * wv + 16 * p) * LDP + 32 * wv, LDP, l, n, half);
+                }
+                __builtin_amdgcn_wave_barrier();
+                _Pragma("unroll") for (int x = 0; x < 16; ++x)
+                    if (8 * (x >> 2) + 4 * half + (x & 3) == n) zd[32 * wv + n] = z0[x];
+                _Pragma("unroll") for (int g4 = 0; g4 < 4; ++g4) {
+                    const int m0 = 8 * g4 + 4 * half, off = (32 * wv + n) * LDP + 32 * wv + m0;
+                    const u32x2 h = *reinterpret_cast<const u32x2*>(Zh + off), l = *reinterpret_cast<const u32x2*>(Zl + off);
+                    const float y[4] = {bf16_lo(h.x) + bf16_lo(l.x), bf16_hi(h.x) + bf16_hi(l.x), bf16_lo(h.y) + bf16_lo(l.y), bf16_hi(h.y) + bf16_hi(l.y)};
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) z0[4 * g4 + j] = m0 + j <= n ? z0[4 * g4 + j] : y[j];
+                }
+                __builtin_amdgcn_wave_barrier();
             }
-            const bf16x8 bzh = __builtin_bit_cast(bf16x8, zh), bzl = __builtin_bit_cast(bf16x8, zlo);
-            const bf16x8 ah = frag_tr(wh, LD, u0, 32 * wave, lane), al = frag_tr(wl, LD, u0, 32 * wave, lane);
-            X = mfma(ah, bzh, X);
-            X = mfma(ah, bzl, X);
-            X = mfma(al, bzh, X);
+            store_block_t_split(Zh, Zl, LDP, 32 * tb + n, 32 * ub, half, z0);
         }
-        bool qside;
-        const int ref = level_ref(t, ls, qside);
-        const float sl = level_sign(qside);
+        // weights of the inter parts; the part of dg that needs dk^{inter}
+        f32x16 xk = {0};
         _Pragma("unroll") for (int gq = 0; gq < 4; ++gq) {
             const int col = 32 * wave + 8 * gq + 4 * half;
             const float4 b4 = *reinterpret_cast<const float4*>(bt + t * LDF + col);
-            const float4 r4 = *reinterpret_cast<const float4*>(bt + ref * LDF + col);
-            const float bb[4] = {b4.x, b4.y, b4.z, b4.w}, rr[4] = {r4.x, r4.y, r4.z, r4.w};
-            _Pragma("unroll") for (int jj = 0; jj < 4; ++jj) {
-                const int x = 4 * gq + jj;
-                const float w = level_weight(bb[jj], rr[jj], sl);
-                aq[x] = fmaf(X[x], qside ? w : 0.f, aq[x]);
-                ak[x] = fmaf(X[x], qside ? 0.f : w, ak[x]);
-            }
-        }
-    };
-    __syncthreads();  // Z complete, V / d_o slices consumed
-    build(0);
-    __syncthreads();
-    // the next chunk's rows, under the levels (the last chunk's once more where there is none: behind a branch the registers'
-    // old contents would stay live)
-    issue_rows(ahead);
-    issue_tiles(ahead, 0, sr0);
-    _Pragma("unroll") for (int lv = 0; lv < 6; ++lv) {
-        if (nb == 0) {
-            if (lv < 5) build(lv + 1);
-            contract(lv);
-        } else {
-            contract(lv);
-            if (lv < 5) build(lv + 1);
-        }
-        __syncthreads();  // the next tile is complete, this one is free again
-    }
-    // ---- diagonal pairs, then the decay gradient from the unrounded accumulators
-    fresh();
-    f32x16 wd;
-    {
-        const float dd = zd[t];
-        _Pragma("unroll") for (int gq = 0; gq < 4; ++gq) {
-            const int col = 32 * wave + 8 * gq + 4 * half;
-            const u32x2 qq = *reinterpret_cast<const u32x2*>(Qr + t * LD + col);
+            const float4 c4 = *reinterpret_cast<const float4*>(bt + 63 * LDF + col);
+            const float bb[4] = {b4.x, b4.y, b4.z, b4.w}, cc[4] = {c4.x, c4.y, c4.z, c4.w};
             const u32x2 kk = *reinterpret_cast<const u32x2*>(Kr + t * LD + col);
-            const float qf[4] = {bf16_lo(qq.x), bf16_hi(qq.x), bf16_lo(qq.y), bf16_hi(qq.y)};
             const float kf[4] = {bf16_lo(kk.x), bf16_hi(kk.x), bf16_lo(kk.y), bf16_hi(kk.y)};
             _Pragma("unroll") for (int jj = 0; jj < 4; ++jj) {
                 const int x = 4 * gq + jj;
-                aq[x] += dd * kf[jj];
-                ak[x] += dd * qf[jj];
-                wd[x] = qf[jj] * (aq[x] + aqr[x]) - kf[jj] * (ak[x] + akr[x]);
+                const float wq = __expf(bb[jj]), wk = __expf(cc[jj] - bb[jj]);
+                aq[x] *= wq;
+                aqr[x] *= wq;
+                ak[x] *= wk;
+                akr[x] *= wk;
+                xk[x] = kf[jj] * (ak[x] + akr[x]);
             }
         }
-    }
-    // (the barrier that ends the level loop: every wave is done with the level tiles)
-    store_packed(T0, LD, t, 32 * wave, half, pack_block(aq));
-    store_packed(T1, LD, t, 32 * wave, half, pack_block(ak));
-    fresh();
-    if (want_dg) {
-        // per feature (register): running sum over this wave's 32 tokens, the last one first, and the sum of this
-        // wave's tail terms; both go to the other token block through LDS
-        _Pragma("unroll") for (int x = 0; x < 16; ++x) wd[x] = half_prefix(wd[x]);
-        _Pragma("unroll") for (int x = 0; x < 16; ++x) xk[x] = half_prefix(xk[x]);
-        if (n == 31) {
-            _Pragma("unroll") for (int x = 0; x < 16; ++x) {
-                const int f = 8 * (x >> 2) + 4 * half + (x & 3);
-                if (nb == 1) xch[(0 * 4 + wave) * 32 + f] = wd[x];   // total of token block 1
-                xch[((1 + nb) * 4 + wave) * 32 + f] = xk[x];           // tail sum of this block
-            }
+        if (want_dg && nb == 1) {
+            float zi = 0.f;
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) zi += 8 * (x >> 2) + 4 * half + (x & 3) == n ? z0[x] : 0.f;
+            zi += __shfl_xor(zi, 32, 64);
+            if (half == 0) zl[32 * wave + n] = zi;
         }
-    }
-    __syncthreads();  // stages and exchange complete; b no longer needed as weights
-    fresh();
-    {
-        int row, cpp;
-        _Pragma("unroll") for (int it = 0; it < 2; ++it) {
-            tile_rows(it, row, cpp);
-            if (row < L) {
-                __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(T0 + row * LD + cpp * 8),
-                                            reinterpret_cast<u32x4*>(dq + (tok0 + size_t(row) * ts) * D + cpp * 8));
-                __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(T1 + row * LD + cpp * 8),
-                                            reinterpret_cast<u32x4*>(dk + (tok0 + size_t(row) * ts) * D + cpp * 8));
+
+        // ---- levels.  The level tiles are double-buffered, and the two waves of a SIMD (same features,
+        // token blocks 0 and 1) take the two halves of an iteration in opposite order: while one builds
+        // the tile of the next level (exponentials on the vector ALU) the other contracts the current one
+        // (LDS reads, MFMA), instead of both queueing for the same unit.
+        auto Wh = [&](int lv) { return (lv & 1) ? W1 : T0; };
+        auto Wl = [&](int lv) { return (lv & 1) ? W1 + C * LD : T1; };
+        auto build = [&](int lv) {
+            const int ls = 5 - lv;
+            uint16_t *wh = Wh(lv), *wl = Wl(lv);
+            fresh();
+            const int cp = tid & 15, r0 = tid >> 4;  // W rows r0 and r0 + 32, features 8 cp .. + 7
+            _Pragma("unroll") for (int it = 0; it < 2; ++it) {
+                const int row = r0 + 32 * it;
+                bool qside;
+                const int ref = level_ref(row, ls, qside);
+                const float sl = level_sign(qside);
+                float b[8], br[8], w[8];
+                decay_row8(bt, row, cp * 8, b);
+                decay_row8(bt, ref, cp * 8, br);
+                _Pragma("unroll") for (int e = 0; e < 8; ++e) w[e] = level_weight(b[e], br[e], sl);
+                const u32x4 raw = *reinterpret_cast<const u32x4*>((qside ? Qr : Kr) + row * LD + cp * 8);
+                u32x4 hi, lo;
+                weigh8(raw, w, hi, &lo);
+                *reinterpret_cast<u32x4*>(wh + row * LD + cp * 8) = hi;
+                *reinterpret_cast<u32x4*>(wl + row * LD + cp * 8) = lo;
             }
-        }
-    }
-    if (want_dg) {
-        float add[16];
-        _Pragma("unroll") for (int gq = 0; gq < 4; ++gq) {
-            const int col = 32 * wave + 8 * gq + 4 * half;
-            const float4 c4 = *reinterpret_cast<const float4*>(bt + 63 * LDF + col);
-            const float4 z4 = *reinterpret_cast<const float4*>(zl + col);
-            const float cc[4] = {c4.x, c4.y, c4.z, c4.w}, zf[4] = {z4.x, z4.y, z4.z, z4.w};
-            _Pragma("unroll") for (int jj = 0; jj < 4; ++jj) {
-                const int x = 4 * gq + jj, f = 8 * gq + 4 * half + jj;
-                // tail over all 64 tokens (block 0 first), the state term, and for block 0 the running sum of block 1
-                add[x] = (xch[(1 * 4 + wave) * 32 + f] + xch[(2 * 4 + wave) * 32 + f]) + __expf(cc[jj]) * zf[jj] +
-                         (nb == 0 ? xch[(0 * 4 + wave) * 32 + f] : 0.f);
+        };
+        auto contract = [&](int lv) {
+            const int ls = 5 - lv;
+            const uint16_t *wh = Wh(lv), *wl = Wl(lv);
+            fresh();
+            const int ub = ls == 5 ? 1 - nb : nb;  // the partners of level 32 sit in the other 32-block
+            f32x16 X = {0};
+            _Pragma("unroll") for (int s2 = 0; s2 < 2; ++s2) {
+                const int u0 = 32 * ub + 16 * s2;
+                const int xr = (u0 + 8 * half) ^ t;
+                u32x4 mask;
+                _Pragma("unroll") for (int p = 0; p < 4; ++p)
+                    mask[p] = ((((xr ^ (2 * p)) >> ls) == 1) ? 0xffffu : 0u) | ((((xr ^ (2 * p + 1)) >> ls) == 1) ? 0xffff0000u : 0u);
+                u32x4 zh = *reinterpret_cast<const u32x4*>(Zh + t * LDP + u0 + 8 * half);
+                u32x4 zlo = *reinterpret_cast<const u32x4*>(Zl + t * LDP + u0 + 8 * half);
+                _Pragma("unroll") for (int p = 0; p < 4; ++p) {
+                    zh[p] &= mask[p];
+                    zlo[p] &= mask[p];
+                }
+                const bf16x8 bzh = __builtin_bit_cast(bf16x8, zh), bzl = __builtin_bit_cast(bf16x8, zlo);
+                const bf16x8 ah = frag_tr(wh, LD, u0, 32 * wave, lane), al = frag_tr(wl, LD, u0, 32 * wave, lane);
+                X = mfma(ah, bzh, X);
+                X = mfma(ah, bzl, X);
+                X = mfma(al, bzh, X);
             }
-        }
-        __syncthreads();  // every wave has read b and the exchange area: b becomes the dg stage
-        _Pragma("unroll") for (int gq = 0; gq < 4; ++gq)
-            *reinterpret_cast<float4*>(bt + t * LDF + 32 * wave + 8 * gq + 4 * half) =
-                float4{wd[4 * gq] + add[4 * gq], wd[4 * gq + 1] + add[4 * gq + 1], wd[4 * gq + 2] + add[4 * gq + 2],
-                       wd[4 * gq + 3] + add[4 * gq + 3]};
+            bool qside;
+            const int ref = level_ref(t, ls, qside);
+            const float sl = level_sign(qside);
+            _Pragma("unroll") for (int gq = 0; gq < 4; ++gq) {
+                const int col = 32 * wave + 8 * gq + 4 * half;
+                const float4 b4 = *reinterpret_cast<const float4*>(bt + t * LDF + col);
+                const float4 r4 = *reinterpret_cast<const float4*>(bt + ref * LDF + col);
+                const float bb[4] = {b4.x, b4.y, b4.z, b4.w}, rr[4] = {r4.x, r4.y, r4.z, r4.w};
+                _Pragma("unroll") for (int jj = 0; jj < 4; ++jj) {
+                    const int x = 4 * gq + jj;
+                    const float w = level_weight(bb[jj], rr[jj], sl);
+                    aq[x] = fmaf(X[x], qside ? w : 0.f, aq[x]);
+                    ak[x] = fmaf(X[x], qside ? 0.f : w, ak[x]);
+                }
+            }
+        };
+        __syncthreads();  // Z complete, V / d_o slices consumed
+        build(0);
         __syncthreads();
-        fresh();
-        _Pragma("unroll") for (int it = 0; it < 4; ++it) {
-            const int p = tid + NT * it, row = p >> 5, c4 = p & 31;
-            if (row < L)
-                *reinterpret_cast<float4*>(dg + (tok0 + size_t(row) * ts) * D + 4 * c4) = *reinterpret_cast<const float4*>(bt + row * LDF + 4 * c4);
+        // the next chunk's rows, under the levels (the last chunk's once more where there is none: behind a branch the registers'
+        // old contents would stay live)
+        issue_rows(ahead);
+        issue_tiles(ahead, 0, sr0);
+        _Pragma("unroll") for (int lv = 0; lv < 6; ++lv) {
+            if (nb == 0) {
+                if (lv < 5) build(lv + 1);
+                contract(lv);
+            } else {
+                contract(lv);
+                if (lv < 5) build(lv + 1);
+            }
+            __syncthreads();  // the next tile is complete, this one is free again
         }
+        // ---- diagonal pairs, then the decay gradient from the unrounded accumulators
+        fresh();
+        f32x16 wd;
+        {
+            const float dd = zd[t];
+            _Pragma("unroll") for (int gq = 0; gq < 4; ++gq) {
+                const int col = 32 * wave + 8 * gq + 4 * half;
+                const u32x2 qq = *reinterpret_cast<const u32x2*>(Qr + t * LD + col);
+                const u32x2 kk = *reinterpret_cast<const u32x2*>(Kr + t * LD + col);
+                const float qf[4] = {bf16_lo(qq.x), bf16_hi(qq.x), bf16_lo(qq.y), bf16_hi(qq.y)};
+                const float kf[4] = {bf16_lo(kk.x), bf16_hi(kk.x), bf16_lo(kk.y), bf16_hi(kk.y)};
+                _Pragma("unroll") for (int jj = 0; jj < 4; ++jj) {
+                    const int x = 4 * gq + jj;
+                    aq[x] += dd * kf[jj];
+                    ak[x] += dd * qf[jj];
+                    wd[x] = qf[jj] * (aq[x] + aqr[x]) - kf[jj] * (ak[x] + akr[x]);
+                }
+            }
+        }
+        // (the barrier that ends the level loop: every wave is done with the level tiles)
+        store_packed(T0, LD, t, 32 * wave, half, pack_block(aq));
+        store_packed(T1, LD, t, 32 * wave, half, pack_block(ak));
+        fresh();
+        if (want_dg) {
+            // per feature (register): running sum over this wave's 32 tokens, the last one first, and the sum of this
+            // wave's tail terms; both go to the other token block through LDS
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) wd[x] = half_prefix(wd[x]);
+            _Pragma("unroll") for (int x = 0; x < 16; ++x) xk[x] = half_prefix(xk[x]);
+            if (n == 31) {
+                _Pragma("unroll") for (int x = 0; x < 16; ++x) {
+                    const int f = 8 * (x >> 2) + 4 * half + (x & 3);
+                    if (nb == 1) xch[(0 * 4 + wave) * 32 + f] = wd[x];   // total of token block 1
+                    xch[((1 + nb) * 4 + wave) * 32 + f] = xk[x];           // tail sum of this block
+                }
+            }
+        }
+        __syncthreads();  // stages and exchange complete; b no longer needed as weights
+        fresh();
+        {
+            int row, cpp;
+            _Pragma("unroll") for (int it = 0; it < 2; ++it) {
+                tile_rows(it, row, cpp);
+                if (row < L) {
+                    __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(T0 + row * LD + cpp * 8),
+                                                reinterpret_cast<u32x4*>(dq + (tok0 + size_t(row) * ts) * D + cpp * 8));
+                    __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(T1 + row * LD + cpp * 8),
+                                                reinterpret_cast<u32x4*>(dk + (tok0 + size_t(row) * ts) * D + cpp * 8));
+                }
+            }
+        }
+        if (want_dg) {
+            float add[16];
+            _Pragma("unroll") for (int gq = 0; gq < 4; ++gq) {
+                const int col = 32 * wave + 8 * gq + 4 * half;
+                const float4 c4 = *reinterpret_cast<const float4*>(bt + 63 * LDF + col);
+                const float4 z4 = *reinterpret_cast<const float4*>(zl + col);
+                const float cc[4] = {c4.x, c4.y, c4.z, c4.w}, zf[4] = {z4.x, z4.y, z4.z, z4.w};
+                _Pragma("unroll") for (int jj = 0; jj < 4; ++jj) {
+                    const int x = 4 * gq + jj, f = 8 * gq + 4 * half + jj;
+                    // tail over all 64 tokens (block 0 first), the state term, and for block 0 the running sum of block 1
+                    add[x] = (xch[(1 * 4 + wave) * 32 + f] + xch[(2 * 4 + wave) * 32 + f]) + __expf(cc[jj]) * zf[jj] +
+                             (nb == 0 ? xch[(0 * 4 + wave) * 32 + f] : 0.f);
+                }
+            }
+            __syncthreads();  // every wave has read b and the exchange area: b becomes the dg stage
+            _Pragma("unroll") for (int gq = 0; gq < 4; ++gq)
+                *reinterpret_cast<float4*>(bt + t * LDF + 32 * wave + 8 * gq + 4 * half) =
+                    float4{wd[4 * gq] + add[4 * gq], wd[4 * gq + 1] + add[4 * gq + 1], wd[4 * gq + 2] + add[4 * gq + 2],
+                           wd[4 * gq + 3] + add[4 * gq + 3]};
+            __syncthreads();
+            fresh();
+            _Pragma("unroll") for (int it = 0; it < 4; ++it) {
+                const int p = tid + NT * it, row = p >> 5, c4 = p & 31;
+                if (row < L)
+                    *reinterpret_cast<float4*>(dg + (tok0 + size_t(row) * ts) * D + 4 * c4) = *reinterpret_cast<const float4*>(bt + row * LDF + 4 * c4);
+            }
+        }
+        // the next chunk's first states, in the registers of the accumulators
+        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) issue_state(ahead, 0, ks, sr0);
+        __syncthreads();  // the stages are read
     }
-    // the next chunk's first states, in the registers of the accumulators
-    _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) issue_state(ahead, 0, ks, sr0);
-    __syncthreads();  // the stages are read
-  }
 }

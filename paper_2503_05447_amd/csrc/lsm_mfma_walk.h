@@ -95,8 +95,8 @@ __host__ __device__ constexpr int walk_lds(bool summary) {
 
 // D[m][n] = sum_f Am[m0 + m][f] * Bm[n0 + n][f] over the 128 features of two row-major LDS tiles, the
 // fragments requested four k-steps at a time (a lower register peak than all sixteen at once)
-__device__ __forceinline__ f32x16 score_block2(const uint16_t* Am, int m0, const uint16_t* Bm, int n0, int n, int half,
-                                               f32x16 acc = f32x16{0}) {
+__device__ __forceinline__ f32x16 score_block2(const uint16_t* Am, int m0, const uint16_t* Bm, int n0, int n, int half) {
+    f32x16 acc = {0};
     _Pragma("unroll") for (int h4 = 0; h4 < 2; ++h4) {
         bf16x8 fa[4], fb[4];
         _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {
@@ -120,11 +120,7 @@ __device__ __forceinline__ void walk_inter(f32x16 (&O)[2], const f32x16 (&S)[4],
     _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
         _Pragma("unroll") for (int p = 0; p < 2; ++p) {
             u32x4 hi, lo;
-            _Pragma("unroll") for (int e = 0; e < 4; ++e) {
-                const float x0 = S[ib][8 * p + 2 * e], x1 = S[ib][8 * p + 2 * e + 1];
-                hi[e] = pack2(x0, x1);
-                lo[e] = pack2(x0 - bf16_lo(hi[e]), x1 - bf16_hi(hi[e]));
-            }
+            split_frag(S[ib], p, hi, lo);
             const bf16x8 sh = __builtin_bit_cast(bf16x8, hi), sl = __builtin_bit_cast(bf16x8, lo);
             const bf16x8 qf0 = frag_perm(Q, LD, n, 32 * ib + 16 * p, half);
             const bf16x8 qf1 = frag_perm(Q, LD, 32 + n, 32 * ib + 16 * p, half);
@@ -345,7 +341,8 @@ __global__ __launch_bounds__(kThreads, 2) void mk_walk(Dims d, WalkArgs a) {
 // S enters its product as bf16 head + remainder taken from the fp32 accumulators, so the q.dq term of the decay
 // gradient sees no state rounding.  G and As are each computed once per workgroup, one wave per 32 x 32 block, and
 // parked as head + remainder in areas of their own; the dS rows, which arrive as the A operands of the dk inter part,
-// also go to LDS for the contractions over i.  One workgroup per compute unit, four barriers per chunk.
+// also go to LDS for the contractions over i.  One workgroup per compute unit, four barriers per chunk
+// (VSPLIT: three, its gradients leave from the registers).
 // LDS: Q | K | V | dO (64 x LD; at the end the stages of dq, dk, dv) | G head | G remainder | As head |
 //      As remainder (64 x LDP each) | dS rows (128 x LD) | bs | wo | red (4 x 2 x 64) | zred
 constexpr int kWalkGradLds = (4 * C * LD + 4 * C * LDP + D * LD) * 2 + (2 * C + 8) * 4 + 4 * 64 * 2 * 4 + 64;
@@ -403,11 +400,7 @@ __device__ __forceinline__ void walk_inter_pair(f32x16 (&X)[2], f32x16 (&O)[2], 
     _Pragma("unroll") for (int ib = 0; ib < 4; ++ib)
         _Pragma("unroll") for (int p = 0; p < 2; ++p) {
             u32x4 hi, lo;
-            _Pragma("unroll") for (int e = 0; e < 4; ++e) {
-                const float x0 = S[ib][8 * p + 2 * e], x1 = S[ib][8 * p + 2 * e + 1];
-                hi[e] = pack2(x0, x1);
-                lo[e] = pack2(x0 - bf16_lo(hi[e]), x1 - bf16_hi(hi[e]));
-            }
+            split_frag(S[ib], p, hi, lo);
             const bf16x8 sh = __builtin_bit_cast(bf16x8, hi), sl = __builtin_bit_cast(bf16x8, lo);
             _Pragma("unroll") for (int nb = 0; nb < 2; ++nb) {
                 const bf16x8 wh = frag_perm(Wh, LD, 32 * nb + n, 32 * ib + 16 * p, half);
