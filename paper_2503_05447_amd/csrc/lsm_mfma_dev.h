@@ -69,15 +69,7 @@ __device__ __forceinline__ bf16x8 frag_tr4(const uint16_t* tile, int ld, int row
 }
 __device__ __forceinline__ int tr4_at(int t) { return (t & ~15) | (4 * (t & 2)) | (4 * (t & 1)) | ((t >> 2) & 3); }
 
-// write a D-layout block as 8-byte pieces: dst[(n)][m0 + 8g + 4half + 0..3], row stride ld
-__device__ __forceinline__ void store_block_t(uint16_t* dst, int ld, int nrow, int m0, int half, const f32x16& d) {
-    _Pragma("unroll") for (int g = 0; g < 4; ++g) {
-        u32x2 v = {pack2(d[4 * g + 0], d[4 * g + 1]), pack2(d[4 * g + 2], d[4 * g + 3])};
-        *reinterpret_cast<u32x2*>(dst + nrow * ld + m0 + 8 * g + 4 * half) = v;
-    }
-}
-
-// same, as a bf16 head in `hi` and the bf16 remainder in `lo` (x = hi + lo to ~2^-17)
+// write a D-layout block as 8-byte pieces: [n][m0 + 8g + 4half + 0..3], row stride ld, as a bf16 head in `hi` and the bf16 remainder in `lo` (x = hi + lo to ~2^-17)
 __device__ __forceinline__ void store_block_t_split(uint16_t* hi, uint16_t* lo, int ld, int nrow, int m0, int half,
                                                     const f32x16& d) {
     _Pragma("unroll") for (int g = 0; g < 4; ++g) {
