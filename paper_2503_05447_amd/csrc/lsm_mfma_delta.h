@@ -339,7 +339,8 @@ __global__ __launch_bounds__(512, 1) void mk_delta_walk8(Dims d, DeltaWalkArgs a
                     }
                 }
             }
-            // (U[1] = R[1] here, as U[0], spills 6 registers with a decay: 16 x 16 sequences of 2048 257 us, this 251)
+            // (U[1] = R[1] here, as U[0], spills 6 registers with a decay: 16 x 16 sequences of 2048, forward, 257 us, this 251; and with
+            // U[0] complete before the later rows are split 247)
             f32x16 U[2] = {R[0], f32x16{0}};
             _Pragma("unroll") for (int kr = 0; kr < 4; ++kr) {
                 u32x4 hi, lo;
@@ -351,6 +352,7 @@ __global__ __launch_bounds__(512, 1) void mk_delta_walk8(Dims d, DeltaWalkArgs a
                     U[tb] = mfma(tl, rh, U[tb]);
                     U[tb] = mfma(th, rl, U[tb]);
                 }
+                if (kr == 1) asm volatile("" : "+v"(U[0]));
             }
             _Pragma("unroll") for (int x = 0; x < 16; ++x) U[1][x] += R[1][x];
             u32x4 uh[4], ul[4];
