@@ -278,9 +278,8 @@ def delta_bench(steps, warmup, check):
             th = B * H * T
             ab = th * (4 * 256 + 4 * 2)   # q, k, v, o in bf16; two per-token parameters
             abb = th * (7 * 256 + 4 * 4)  # backward: q, k, v, d_o read, dq, dk, dv written; parameters and their gradients
-            # chunk-dense flops per token-head: scores, A U, Q S, state update (as the diagonal kinds) + K K^T,
-            # T [V | K], What S
-            fl = th * (2 * 64 * 256 + 2 * 2 * 128 * 128 + 2 * 64 * 128 + 2 * 64 * 256 + 2 * 128 * 128)
+            # chunk-dense flops per token-head: scores, A U, Q S, state update (as the diagonal kinds) + K K^T, K S, T R
+            fl = th * (2 * 64 * 256 + 2 * 2 * 128 * 128 + 2 * 64 * 128 + 2 * 128 * 128 + 2 * 64 * 128)
             e = {"B": B, "H": H, "T": T, "ms_per_step": sec * 1e3, "tokens_per_s": B * T / sec, "steps": steps,
                  "kernel_ms": {n_: float(np.mean(v_)) for n_, v_ in per.items()},
                  "ms_per_step_fwd_bwd": sec_fb * 1e3, "tokens_per_s_fwd_bwd": B * T / sec_fb,
